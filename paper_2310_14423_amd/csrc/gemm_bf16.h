@@ -7,18 +7,17 @@
 // (checked on the hardware): lane l holds A[row l%32][k (l/32)*8 .. +7], B[k (l/32)*8 .. +7]
 // [col l%32], and accumulator element i is D[(i/4)*8 + (l/32)*4 + i%4][l%32].
 //
-// Tiling: a workgroup of WM x WN wavefronts computes a BM x BN tile; K is walked in slabs of
-// BK = 64 (or 32) staged through two LDS buffers.  The slabs are copied global -> LDS directly
-// (global_load_lds_dwordx4: no register staging, no LDS store instructions), slab j+1 in
-// flight while slab j is multiplied.  That instruction writes 64 lanes x 16 B to 1 KiB of
-// consecutive LDS, so rows are stored unpadded (8 pieces of 16 B) and bank conflicts are
-// avoided by an XOR swizzle instead: slot s of row r holds piece s ^ ((r >> 1) & 7) (BK = 32:
-// s ^ ((r >> 2) & 3)), which spreads the 128-bit fragment reads of 16 consecutive rows over all
-// 64 banks (measured: no conflicts).  Timed on MI355X at 12608 x 768 x 3072, batch 8: register-staged copy 0.58 ms,
-// direct copy 0.49 ms, plus the XCD-aware tile order 0.47 ms (1.01 PFLOP/s).
+// Tiling: a workgroup of WM x WN wavefronts computes a BM x BN tile; K is walked in stages of
+// 32 through a ring of NS LDS buffers.  The stages are copied global -> LDS directly
+// (global_load_lds_dwordx4: no register staging, no LDS store instructions), NS - 1 of them ahead;
+// a wavefront waits for its share of the next stage only (a counted vmcnt, not 0).  That
+// instruction writes 64 lanes x 16 B to 1 KiB of consecutive LDS, so rows are stored unpadded
+// (4 pieces of 16 B) and bank conflicts are avoided by an XOR swizzle instead: slot s of row r
+// holds piece s ^ ((r >> 2) & 3), which spreads the 128-bit fragment reads of 16 consecutive rows
+// over all 64 banks (measured: no conflicts).
 // M and N may be ragged: out-of-range rows are clamped to the last valid row on load (they
 // only feed accumulator rows that are never stored) and the epilogue is bounds-checked.
-// K must be a multiple of BK and lda/ldb multiples of 8 elements (16-byte rows).
+// K must be a multiple of 32, N of 64, and lda a multiple of 8 elements (16-byte rows).
 //
 // The two operands are handed to the instruction in swapped roles (the B rows as its "A", the A
 // rows as its "B"), so that it produces the transposed tile: lane l then owns, for token row
@@ -28,8 +27,8 @@
 // Operand layout.  Besides plain row-major, a bf16 matrix [R][C] (C a multiple of 32) can be stored
 // in blocks of 32 rows x 32 columns, each block 2 KiB contiguous, blocks ordered [row block]
 // [column block] (blk_off below).  Both kinds of GEMM then copy consecutive memory: a 256-row x
-// 64-deep slab of this kernel's operands is 8 pieces of 4 KiB (two neighbouring blocks) instead of
-// 256 pieces of 128 B a whole row (1.5 - 6 KiB) apart, and a 32-token x 192- or 384-feature slab of
+// 32-deep stage of this kernel's operands is 8 pieces of 2 KiB (one block each) instead of
+// 256 pieces of 64 B a whole row (1.5 - 6 KiB) apart, and a 32-token x 192- or 384-feature slab of
 // the weight-gradient kernel (gemm_pp.h), which walks the same arrays along their rows, is 12 or
 // 24 KiB in one piece instead of 32 pieces; every global -> LDS copy instruction moves 1 KiB of
 // consecutive memory.  (Blocks of 256 rows x 32 columns, 32 KiB per slab here, were timed first:
@@ -39,6 +38,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace qsr {
 
@@ -71,42 +71,74 @@ struct GemmNT {
 
 // Epilogue.  The MFMA leaves lane l with 4 consecutive columns of row l%32, i.e. one store
 // instruction would touch 32 different rows.  Each wavefront therefore passes its tile, 32 rows
-// at a time, through a private LDS area (the slab buffers are free by then) and re-reads it
-// so that 16 consecutive lanes hold one row's consecutive columns: whole 128- or 256-byte row
-// segments per global instruction (N must be a multiple of 4).  Rows are padded by 16 B:
-// conflict-free both ways.  The functor has two parts, so that what it reads from global memory
-// can be requested one 32-row block ahead of its use:
-//     Aux  epi.pre(z, m, n)            -- loads for C[z][m][n..n+3] (may be empty; also called
-//                                         with coordinates clamped into the matrix, N >= 4)
-//     void epi(z, m, n, v[4], aux)     -- consumes the accumulators and stores
+// at a time, through a private LDS area (the ring is free by then) and re-reads it so that
+// consecutive lanes hold one row's consecutive columns: whole 128- or 256-byte row segments per
+// global instruction.  Rows are padded by 16 B: conflict-free both ways.  A lane takes VEC = 8
+// consecutive columns where the outputs are bf16 (16-byte accesses) and 4 where they are fp32.
+//
+// Addresses: an element of a lane is a wavefront-uniform base (worker, tile, row within the tile:
+// scalar registers) plus a 32-bit lane offset that is the same for all rows of the tile, so a row
+// costs no vector instruction.  (Written with 64-bit element offsets per access, the address
+// arithmetic was 8 vector slots per element of the GELU epilogue's 32.)
+// The functor provides
+//     VEC, Aux
+//     Lane lane(z, row, col, r, c)   -- r, c: the lane's row and column relative to the uniform
+//                                       (row, col); called once
+//     Aux  pre(Lane, dr)             -- loads for the lane's columns, dr rows further down (may be empty);
+//                                       requested one 32-row block ahead of their use
+//     void operator()(Lane, dr, v[VEC], aux)
+// with dr a compile-time constant after unrolling; EpiPtr below does the offsets.
 struct NoAux {};
+
+// One array as the epilogue sees it: uniform base and lane offset.  T elements, row-major with row
+// stride ld, or in 32 x 32 blocks (ld the number of columns).  dr, the rows further down, must not
+// carry the lane's row over the edge of a 32-row block except in whole blocks: row (uniform) is a
+// multiple of 32 and r + dr % 32 < 32 holds for every access.
+template <class T, bool BLK>
+struct EpiPtr {
+    T *base; unsigned off; long long ld;
+    __device__ __forceinline__ EpiPtr(T *p, long long ld_, int row, int col, int r, int c) : ld(ld_)
+    {
+        if (BLK) {
+            base = p + ((long long)(row >> 5) * (ld >> 5) + (col >> 5)) * 1024;
+            off = (unsigned)((c >> 5) * 1024 + r * 32 + (c & 31));
+        } else {
+            base = p + (long long)row * ld + col;
+            off = (unsigned)(r * (int)ld + c);
+        }
+    }
+    __device__ __forceinline__ T *at(int dr) const
+    {
+        return base + (BLK ? (long long)(dr >> 5) * (ld >> 5) * 1024 + (dr & 31) * 32 : (long long)dr * ld) + off;
+    }
+};
 
 template <int TM, int TN, class Epi>
 __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *stage, int lane,
                                                  int row0, int col0, int M, int N, int z, const Epi &epi)
 {
     constexpr int W = TN * 32, LD = W + 4;             // floats per staged row
-    constexpr int LPR = W / 4;                         // lanes per row on the way out
+    constexpr int VEC = Epi::VEC;
+    constexpr int LPR = W / VEC;                       // lanes per row on the way out
     constexpr int RPI = 64 / LPR;                      // rows per read instruction
-    constexpr int ITERS = 32 / RPI;
+    constexpr int ITERS = (32 + RPI - 1) / RPI;
     static_assert(32 % RPI == 0, "rows per instruction must divide the block");
-    const bool active = lane / LPR < RPI;              // TN = 3: 24 lanes per row, the last 16 lanes idle
-    const int c = (lane % LPR) * 4, col = col0 + c;
-    // What the functor reads from global memory is requested one block ahead, before the stores of
-    // the block in between: vector memory operations complete in order, so a wait for loads issued
-    // after a block's stores would also wait for those stores.  Unconditional, with coordinates
-    // clamped into the matrix: no branch, so the loads of a block are issued together.
+    const bool active = 64 % LPR == 0 || lane < RPI * LPR;   // TN = 3: some of the last lanes are idle
+    const int r0 = active ? lane / LPR : 0, c = (lane % LPR) * VEC;
+    const auto lp = epi.lane(z, row0, col0, r0, c);
     typename Epi::Aux aux[2][ITERS];
-    auto request = [&](int i, int buf) {
+    auto block = [&](auto full_c, int i) {
+        constexpr bool FULL = decltype(full_c)::value;
+        auto request = [&](int ib, int buf) {
 #pragma unroll
-        for (int it = 0; it < ITERS; ++it) {
-            const int row = row0 + i * 32 + min(it * RPI + lane / LPR, 31);
-            aux[buf][it] = epi.pre(z, min(row, M - 1), min(col, N - 4));
-        }
-    };
-    request(0, 0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
+            for (int it = 0; it < ITERS; ++it)
+                if (active && (FULL || (row0 + ib * 32 + it * RPI + r0 < M && col0 + c < N)))
+                    aux[buf][it] = epi.pre(lp, ib * 32 + it * RPI);
+        };
+        // What the functor reads from global memory is requested one block ahead, before the stores of
+        // the block in between: vector memory operations complete in order, so a wait for loads issued
+        // after a block's stores would also wait for those stores.
+        if (i == 0) request(0, 0);
         if (i + 1 < TM) request(i + 1, (i + 1) & 1);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
@@ -116,48 +148,56 @@ __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *s
                     make_float4(acc[i][j][eg * 4 + 0], acc[i][j][eg * 4 + 1], acc[i][j][eg * 4 + 2],
                                 acc[i][j][eg * 4 + 3]);
         __builtin_amdgcn_wave_barrier();               // LDS executes a wavefront's accesses in order
+        float4 t[ITERS][VEC / 4];                      // all reads of a block go out before the first use
 #pragma unroll
-        for (int it = 0; it < ITERS; ++it) {
-            const int r = min(it * RPI + lane / LPR, 31);
-            const float4 t = *(const float4 *)(stage + r * LD + c);
-            const int row = row0 + i * 32 + r;
-            if (active && row < M && col < N) {
-                const float v[4] = {t.x, t.y, t.z, t.w};
-                epi(z, row, col, v, aux[i & 1][it]);
+        for (int it = 0; it < ITERS; ++it)
+#pragma unroll
+            for (int u = 0; u < VEC / 4; ++u) t[it][u] = *(const float4 *)(stage + (it * RPI + r0) * LD + c + u * 4);
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it)
+            if (active && (FULL || (row0 + i * 32 + it * RPI + r0 < M && col0 + c < N))) {
+                float v[VEC];
+#pragma unroll
+                for (int u = 0; u < VEC / 4; ++u) {
+                    v[u * 4] = t[it][u].x; v[u * 4 + 1] = t[it][u].y; v[u * 4 + 2] = t[it][u].z; v[u * 4 + 3] = t[it][u].w;
+                }
+                epi(lp, i * 32 + it * RPI, v, aux[i & 1][it]);
             }
-        }
         __builtin_amdgcn_wave_barrier();
+    };
+    // a tile inside the matrix takes no test per row
+    if (row0 + TM * 32 <= M && col0 + W <= N) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) block(std::true_type{}, i);
+    } else {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) block(std::false_type{}, i);
     }
 }
 
-// BLKA: A is stored in 32 x 32 blocks (see above); B always is.  In LDS a slab of a blocked operand
-// is [2 column blocks][rows][32 k], rows of 64 B, slot s of row r holding piece s ^ ((r >> 2) & 3);
-// a row-major A slab is [rows][64 k] with slot = piece ^ ((r >> 1) & 7).
-template <int BM, int BN, int BK, int WM, int WN, bool BLKA, class Epi>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_nt_bf16_kernel(GemmNT p, Epi epi, int batch)
+// BLKA: A is stored in 32 x 32 blocks (see above); B always is.  In LDS a stage is [BM rows][32 k] of
+// A, then [BN rows][32 k] of B, rows of 64 B, slot s of row r holding piece s ^ ((r >> 2) & 3).
+// WPS: wavefronts per SIMD the registers are budgeted for.
+template <int BM, int BN, int WM, int WN, int WPS, int NS, bool BLKA, class Epi>
+__global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT p, Epi epi, int batch)
 {
-    static_assert(BK == 64, "a slab is two 32-column blocks, or rows of 8 pieces of 16 B");
-    static_assert(BM == 256 && BN == 256, "tiles are one row block of the blocked layout");
-    constexpr int PPR = BK / 8;             // 16-byte pieces per row (row-major slab)
-    constexpr int RPC = 64 / PPR;           // rows per 1 KiB chunk (row-major slab)
-    constexpr int SWZ = 1;                  // row-major slab: slot = piece ^ ((row >> SWZ) & (PPR - 1))
-    constexpr int NW = WM * WN;
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    constexpr int A_CHUNKS = BM / RPC, B_CHUNKS = BN / RPC;   // 1 KiB chunks per slab
-    constexpr int A_PER_WAVE = A_CHUNKS / NW, B_PER_WAVE = B_CHUNKS / NW;
-    static_assert(A_CHUNKS % NW == 0 && B_CHUNKS % NW == 0, "chunks / waves");
-    constexpr int STAGE_ELEMS = (BM + BN) * BK;
-
+    constexpr int BK = 32, NW = WM * WN;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NF = TM + TN, MM = TM * TN;
+    constexpr int CA = BM / 16, CB = BN / 16;           // 1 KiB chunks (16 rows x 64 B) per stage
+    constexpr int CPW = (CA + CB) / NW;                 // ... and wavefront
+    static_assert((CA + CB) % NW == 0 && BM % 32 == 0 && BN % 32 == 0, "chunks / waves");
+    constexpr int STAGE = (BM + BN) * BK;
     extern __shared__ __attribute__((aligned(1024))) unsigned char gemm_smem[];
     bf16_t *smem = (bf16_t *)gemm_smem;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WN, wn = wave % WN;
     // Workgroups go to the 8 XCDs round-robin by linear id (the grid's x extent is a multiple of
     // 8).  Tile order: batch entry (worker), then panels of 4 N-tiles, then M-tile, then N-tile
     // inside the panel; each XCD takes a contiguous eighth of that order.  One XCD's L2 then sees
     // one worker's B operand (for 8 workers), and the tiles that run together share their A rows
     // and B rows: 30-45 % fewer bytes fetched into L2 than with the batch as a grid dimension.
+    // (Panels of 2, 3, 6 or 12 tiles: the same to 3 %, the narrow ones slower at N = 768.)
     const int nx = (p.N + BN - 1) / BN, ny = (p.M + BM - 1) / BM;
     int tile = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     if (tile >= batch * nx * ny) return;
@@ -172,45 +212,33 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_nt_bf16_kernel(GemmNT p, Ep
     const bf16_t *A = p.A + (long long)z * p.sA;
     const bf16_t *B = p.B + (long long)z * p.sB;
 
-    // Per-lane global source of each 1 KiB chunk this wave copies.  Row-major operand: chunk c is 8
-    // rows x 128 B, LDS slot (row, s) holds the global piece s ^ ((row >> 1) & 7) of that row.
-    // Blocked operand: chunk c is 16 rows x 64 B, half of a 32 x 32 block (c / 16 the column block of
-    // the slab, c % 16 the run of rows), consecutive in memory up to the permutation of the four
-    // 16-byte pieces inside each row: slot s of row r holds piece s ^ ((r >> 2) & 3).  Rows beyond the
-    // matrix inside the last 256-row panel are allocated (their values only reach accumulator rows
-    // never stored).
-    const bf16_t *srcA[A_PER_WAVE], *srcB[B_PER_WAVE];
-    const int blk_lane = (lane >> 2) * 32 + (((lane & 3) ^ ((lane >> 4) & 3)) * 8);   // inside a blocked chunk
-    constexpr long long A_SLAB = BLKA ? 2 * 1024 : BK, B_SLAB = 2 * 1024;              // elements per slab step
+    // Per-lane global source of each 1 KiB chunk this wave copies: chunk c is 16 rows, LDS slot
+    // (row, s) holds the global piece s ^ ((row >> 2) & 3) of that row.  Blocked operand: half of a
+    // 32 x 32 block, consecutive in memory up to that permutation; rows beyond the matrix inside the
+    // last 256-row panel are allocated (their values only reach accumulator rows never stored), and
+    // every tile shape divides 256.  Row-major A: 16 pieces of 64 B, rows clamped.
+    const bf16_t *src[CPW];
+    const int piece = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;
+    const int blk_lane = (lane >> 2) * 32 + piece;
 #pragma unroll
-    for (int i = 0; i < A_PER_WAVE; ++i) {
-        const int c = wave * A_PER_WAVE + i;
-        if (BLKA) {
-            srcA[i] = A + ((long long)(by * 8 + ((c & 15) >> 1)) * (p.K >> 5) + (c >> 4)) * 1024 + (c & 1) * 512 + blk_lane;
+    for (int i = 0; i < CPW; ++i) {
+        const int c = wave * CPW + i;
+        if (c < CA) {
+            if (BLKA) src[i] = A + ((long long)((m0 >> 5) + (c >> 1)) * (p.K >> 5)) * 1024 + (c & 1) * 512 + blk_lane;
+            else src[i] = A + (long long)min(m0 + c * 16 + (lane >> 2), p.M - 1) * p.lda + piece;
         } else {
-            const int row = c * RPC + lane / PPR;
-            const int piece = (lane % PPR) ^ ((row >> SWZ) & (PPR - 1));
-            srcA[i] = A + (long long)min(m0 + row, p.M - 1) * p.lda + piece * 8;
+            src[i] = B + ((long long)((n0 >> 5) + ((c - CA) >> 1)) * (p.K >> 5)) * 1024 + (c & 1) * 512 + blk_lane;
         }
-    }
-#pragma unroll
-    for (int i = 0; i < B_PER_WAVE; ++i) {
-        const int c = wave * B_PER_WAVE + i;
-        srcB[i] = B + ((long long)(bx * 8 + ((c & 15) >> 1)) * (p.K >> 5) + (c >> 4)) * 1024 + (c & 1) * 512 + blk_lane;
     }
     typedef __attribute__((address_space(3))) void lds_void;
     typedef __attribute__((address_space(1))) const void glb_void;
-    auto issue = [&](int stage, int k0) {
-        bf16_t *sa = smem + stage * STAGE_ELEMS, *sb = sa + BM * BK;
-#pragma unroll
-        for (int i = 0; i < A_PER_WAVE; ++i)
-            __builtin_amdgcn_global_load_lds((glb_void *)(srcA[i] + (long long)(k0 / BK) * A_SLAB),
-                                             (lds_void *)(sa + (wave * A_PER_WAVE + i) * 512), 16, 0, 0);
-#pragma unroll
-        for (int i = 0; i < B_PER_WAVE; ++i)
-            __builtin_amdgcn_global_load_lds((glb_void *)(srcB[i] + (long long)(k0 / BK) * B_SLAB),
-                                             (lds_void *)(sb + (wave * B_PER_WAVE + i) * 512), 16, 0, 0);
+    int d_stage = 0;                                    // stage the next copy goes to
+    auto issue = [&](int i) {
+        const int c = wave * CPW + i;
+        __builtin_amdgcn_global_load_lds((glb_void *)src[i], (lds_void *)(smem + d_stage * STAGE + c * 512), 16, 0, 0);
+        src[i] += BLKA || c >= CA ? 1024 : BK;
     };
+    auto issued = [&]() { d_stage = d_stage + 1 == NS ? 0 : d_stage + 1; };
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -220,83 +248,122 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_nt_bf16_kernel(GemmNT p, Ep
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    // Main loop, software-pipelined over the 16-wide k-steps of a slab: the fragments of step
-    // ks+1 are read from LDS while the MFMAs of step ks issue, and the last step of a slab is
-    // held in registers across the barrier, so that its MFMAs cover the burst of first fragment
-    // reads of the next slab that all wavefronts start at once after the barrier (worth 10 % at
-    // K = 3072 over stopping with empty MFMA queues at every barrier).  The compiler waits for ALL
-    // outstanding LDS reads in two of the four steps of a slab (lgkmcnt(0) right after the next
-    // step's six reads went out); with the reads written as asm and waited for by hand (at most
-    // six outstanding) every step's reads fly behind the previous step's multiplications, and the
-    // kernels take the same time to 2 %: the SIMD's other wavefront already filled those gaps.
-    const int nk = p.K / BK;
-    constexpr int KS = BK / 16;
-    static_assert(KS % 2 == 0, "fragment double buffer parity");
     bf16x8 fa[2][TM], fb[2][TN];
-    auto load_frags = [&](int stage, int ks, int fbuf) {
-        const bf16_t *sa = smem + stage * STAGE_ELEMS, *sb = sa + BM * BK;
-        const int piece = ks * 2 + (lane >> 5);               // of the 8 pieces of a 64-deep row
-        // blocked slab: column block piece / 4, rows of four pieces
-        const int blk_base = (piece >> 2) * (256 * 32), bp = piece & 3;
+    int offA[2], offB[2];                               // the lane's place in a stage, per 16-wide k-step
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int row = wm * TM * 32 + i * 32 + (lane & 31);
-            if (BLKA) fa[fbuf][i] = *(const bf16x8 *)(sa + blk_base + row * 32 + ((bp ^ ((row >> 2) & 3)) * 8));
-            else fa[fbuf][i] = *(const bf16x8 *)(sa + row * BK + ((piece ^ ((row >> SWZ) & (PPR - 1))) * 8));
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int row = wn * TN * 32 + j * 32 + (lane & 31);
-            fb[fbuf][j] = *(const bf16x8 *)(sb + blk_base + row * 32 + ((bp ^ ((row >> 2) & 3)) * 8));
-        }
-    };
-    auto mfmas = [&](int fbuf) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[fbuf][j], fa[fbuf][i], acc[i][j], 0, 0, 0);
-    };
-    issue(0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0): this wavefront's part of slab 0 landed
-    __syncthreads();
-    if (nk > 1) issue(1, BK);
-    load_frags(0, 0, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-#pragma unroll
-        for (int ks = 0; ks < KS - 1; ++ks) {
-            load_frags(cur, ks + 1, (ks + 1) & 1);
-            mfmas(ks & 1);
-        }
-        if (kt + 1 < nk) {
-            // vmcnt(0): my part of slab kt+1 landed; lgkmcnt(0): my reads of slab kt are done
-            __builtin_amdgcn_s_waitcnt(0x0070);
-            __syncthreads();                           // slab kt+1 complete, slab kt's buffer free
-            if (kt + 2 < nk) issue(cur, (kt + 2) * BK);
-            load_frags(cur ^ 1, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);         // keep the pending MFMAs behind those reads
-        }
-        mfmas((KS - 1) & 1);
+    for (int ks = 0; ks < 2; ++ks) {
+        const int pc = ks * 2 + (lane >> 5), r = lane & 31, sw = (pc ^ ((r >> 2) & 3)) * 8;
+        offA[ks] = (wm * TM * 32 + r) * 32 + sw;
+        offB[ks] = BM * BK + (wn * TN * 32 + r) * 32 + sw;
     }
+    // fragment q of a k-step, in the order the multiplications need them: b0, a0, the other b, the other a
+    auto read = [&](int stage, int ks, int q) {
+        const bf16_t *s = smem + stage * STAGE;
+        if (q == 0) fb[ks][0] = *(const bf16x8 *)(s + offB[ks]);
+        else if (q == 1) fa[ks][0] = *(const bf16x8 *)(s + offA[ks]);
+        else if (q <= TN) fb[ks][q - 1] = *(const bf16x8 *)(s + offB[ks] + (q - 1) * 1024);
+        else fa[ks][q - TN] = *(const bf16x8 *)(s + offA[ks] + (q - TN) * 1024);
+    };
+    auto multiply = [&](int ks, int m) {                // serpentine: neighbours share an operand
+        const int i = m / TN, j = (i & 1) ? TN - 1 - m % TN : m % TN;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    };
+    // a barrier that no memory access is moved across
+    auto barrier = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // vmcnt(left), lgkmcnt(0)
+    auto wait = [&](auto left) {
+        constexpr int n = decltype(left)::value;
+        __builtin_amdgcn_s_waitcnt(0x0070 | (n & 15) | ((n >> 4) << 14));
+    };
 
-    __syncthreads();                                   // every wavefront is done with the slabs
+    // Main loop.  A stage is two k-steps.  While step 0's MFMAs issue, the fragments of step 1 are
+    // read; then comes the barrier (everyone's copies of the next stage have landed, everyone is
+    // through reading this one); while step 1's MFMAs issue, the fragments of the next stage's step
+    // 0 are read and the stage NS further on is requested into the buffer just freed.  The order is
+    // pinned instruction by instruction (sched_barrier after every MFMA): one LDS read or one copy
+    // between two MFMAs.  Left to the compiler, a k-step's six reads go out in one burst in front
+    // of its eight MFMAs and both wavefronts of a SIMD do so together.  Timed on MI355X at
+    // 12608 x 768 x 3072, batch 8, same box: bf16 output 465 -> 393 us (K = 3072), main loop alone
+    // 430 -> 371 us = 1.28 PFLOP/s; the loop without its copies runs at 1.5-1.6 PFLOP/s, and bare
+    // MFMAs on random operands at 1.84 (2.28 on zeros: the clock drops with the power they draw).
+    // Neither 3, 4 or 5 stages nor raised wave priority around the MFMAs make a difference; four
+    // wavefronts of 128 x 128 (a third fewer LDS reads) ran the same loop in 361-393 us on the same
+    // boxes, and lost it again in the epilogues, where one wavefront per SIMD has nothing to hide
+    // its waits behind (751 against 631 us with the GELU epilogue).
+    const int nk = p.K / BK;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (s < nk) {
+#pragma unroll
+            for (int i = 0; i < CPW; ++i) issue(i);
+            issued();
+        }
+    if (nk >= NS) wait(std::integral_constant<int, CPW * (NS - 1)>{});
+    else wait(std::integral_constant<int, 0>{});
+    barrier();
+    int cur = 0;
+#pragma unroll
+    for (int q = 0; q < NF; ++q) read(0, 0, q);
+    auto stage = [&](auto last_c, auto issue_c, auto left) {
+        constexpr bool LAST = decltype(last_c)::value, ISSUE = decltype(issue_c)::value;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MM; ++m) {
+            multiply(0, m);
+#pragma unroll
+            for (int q = 0; q < NF; ++q)
+                if ((NF <= MM ? q : q * MM / NF) == m) read(cur, 1, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!LAST) {
+            wait(left);
+            barrier();
+            cur = cur + 1 == NS ? 0 : cur + 1;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int m = 0; m < MM; ++m) {
+            multiply(1, m);
+#pragma unroll
+            for (int q = 0; q < NF; ++q)
+                if (!LAST && (NF <= MM ? q : q * MM / NF) == m) read(cur, 0, q);
+#pragma unroll
+            for (int i = 0; i < CPW; ++i)
+                if (!LAST && ISSUE && (CPW <= MM ? MM - CPW + i : i * MM / CPW) == m) issue(i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!LAST && ISSUE) issued();
+    };
+    // copies outstanding at a stage's wait: stages kt + 2 .. kt + NS - 1 while that many exist
+    int kt = 0;
+    for (; kt + NS < nk; ++kt) stage(std::false_type{}, std::true_type{}, std::integral_constant<int, CPW * (NS - 2)>{});
+    if (kt + NS == nk && kt + 1 < nk) { stage(std::false_type{}, std::false_type{}, std::integral_constant<int, CPW * (NS - 2)>{}); ++kt; }
+    for (; kt + 1 < nk; ++kt) stage(std::false_type{}, std::false_type{}, std::integral_constant<int, 0>{});
+    stage(std::true_type{}, std::false_type{}, std::integral_constant<int, 0>{});
+
+    __syncthreads();                                   // every wavefront is done with the ring
     epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane,
                              m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, z, epi);
 }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));   // operand of the LDS transpose read
 
-template <int BM, int BN, int BK, int WM, int WN, bool BLKA, class Epi>
+template <int BM, int BN, int WM, int WN, int WPS, int NS, bool BLKA, class Epi>
 inline hipError_t launch_gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
-    if (p.K % BK != 0 || p.K < BK) return hipErrorInvalidValue;
+    static_assert(256 % BM == 0 && 256 % BN == 0, "blocked operands are allocated in panels of 256 rows");
+    if (p.K % 32 != 0 || p.K < 32 || p.N % 64 != 0) return hipErrorInvalidValue;
     const unsigned tiles = (unsigned)((p.N + BN - 1) / BN) * (unsigned)((p.M + BM - 1) / BM) * (unsigned)batch;
     dim3 grid((tiles + 7) / 8 * 8, 1, 1);
-    constexpr size_t smem = 2 * (size_t)(BM + BN) * BK * sizeof(bf16_t);
+    constexpr size_t ring = (size_t)NS * (BM + BN) * 32 * sizeof(bf16_t);
+    constexpr size_t staging = (size_t)WM * WN * 32 * (BN / WN + 4) * sizeof(float);
+    constexpr size_t smem = ring > staging ? ring : staging;
     static_assert(smem <= 160 * 1024, "tile does not fit the 160 KB LDS");
-    static_assert((size_t)WM * WN * 32 * (BN / WN + 4) * sizeof(float) <= smem, "epilogue staging does not fit the slab buffers");
-    auto kern = gemm_nt_bf16_kernel<BM, BN, BK, WM, WN, BLKA, Epi>;
+    auto kern = gemm_nt_bf16_kernel<BM, BN, WM, WN, WPS, NS, BLKA, Epi>;
     static bool lds_limit_raised = false;     // per instantiation; contexts are not thread-safe
     if (smem > 64 * 1024 && !lds_limit_raised) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);

@@ -468,41 +468,71 @@ __device__ __forceinline__ void gelu_parts(float h, float &cdf, float &pdf)
     pdf = 0.3989422804014327f * ex;
 }
 
-__device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d)
+// (All outputs of the GEMMs are stored non-temporally: written back through L2 they evicted the operands the
+// other tiles share, 493 against 445 us for a bf16 output of 12608 x 3072 per worker, K = 768.)
+__device__ __forceinline__ bf16x8 pack8(const float (&v)[8])
 {
-    bf16x4 r = {(bf16_t)a, (bf16_t)b, (bf16_t)c, (bf16_t)d};
+    bf16x8 r;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = (bf16_t)v[i];
     return r;
 }
 
 struct EpiScaleF32 {             // C = scale * acc
     float *C; long long ldc, sC; float scale;
+    static constexpr int VEC = 4;
     typedef NoAux Aux;
-    __device__ Aux pre(int, int, int) const { return Aux{}; }
-    __device__ void operator()(int z, int m, int n, const float (&v)[4], const Aux &) const
+    typedef EpiPtr<float, false> Lane;
+    __device__ Lane lane(int z, int row, int col, int r, int c) const { return Lane(C + (long long)z * sC, ldc, row, col, r, c); }
+    __device__ Aux pre(const Lane &, int) const { return Aux{}; }
+    __device__ void operator()(const Lane &l, int dr, const float (&v)[4], const Aux &) const
     {
-        st_nt4((float4 *)(C + (long long)z * sC + (long long)m * ldc + n),
-               make_float4(v[0] * scale, v[1] * scale, v[2] * scale, v[3] * scale));
+        st_nt4((float4 *)l.at(dr), make_float4(v[0] * scale, v[1] * scale, v[2] * scale, v[3] * scale));
     }
 };
 template <bool BLK>
 struct EpiBf16 {                 // C = bf16(acc), row-major or blocked
     bf16_t *C; long long ldc, sC;
+    static constexpr int VEC = 8;
     typedef NoAux Aux;
-    __device__ Aux pre(int, int, int) const { return Aux{}; }
-    __device__ void operator()(int z, int m, int n, const float (&v)[4], const Aux &) const
+    typedef EpiPtr<bf16_t, BLK> Lane;
+    __device__ Lane lane(int z, int row, int col, int r, int c) const { return Lane(C + (long long)z * sC, ldc, row, col, r, c); }
+    __device__ Aux pre(const Lane &, int) const { return Aux{}; }
+    __device__ void operator()(const Lane &l, int dr, const float (&v)[8], const Aux &) const
     {
-        const long long o = BLK ? blk_off(m, n, ldc) : (long long)m * ldc + n;
-        *(bf16x4 *)(C + (long long)z * sC + o) = pack4(v[0], v[1], v[2], v[3]);
+        __builtin_nontemporal_store(pack8(v), (bf16x8 *)l.at(dr));
+    }
+};
+// the lane's VEC bias values, the same for all its rows
+template <int VEC>
+struct EpiBias {
+    float b[VEC];
+    __device__ EpiBias(const float *p)
+    {
+#pragma unroll
+        for (int u = 0; u < VEC; u += 4) {
+            const float4 t = *(const float4 *)(p + u);
+            b[u] = t.x; b[u + 1] = t.y; b[u + 2] = t.z; b[u + 3] = t.w;
+        }
     }
 };
 struct EpiBiasBf16 {             // C = bf16(acc + bias)
-    const float *bias; long long sBias; bf16_t *C; long long ldc, sC;
+    const float *bias; long long sBias; bf16_t *C; long long ldc, sC; int N;
+    static constexpr int VEC = 8;
     typedef NoAux Aux;
-    __device__ Aux pre(int, int, int) const { return Aux{}; }
-    __device__ void operator()(int z, int m, int n, const float (&v)[4], const Aux &) const
+    struct Lane { EpiPtr<bf16_t, false> o; EpiBias<8> b; };
+    __device__ Lane lane(int z, int row, int col, int r, int c) const
     {
-        const float4 b = *(const float4 *)(bias + (long long)z * sBias + n);
-        *(bf16x4 *)(C + (long long)z * sC + (long long)m * ldc + n) = pack4(v[0] + b.x, v[1] + b.y, v[2] + b.z, v[3] + b.w);
+        return Lane{EpiPtr<bf16_t, false>(C + (long long)z * sC, ldc, row, col, r, c),
+                    EpiBias<8>(bias + (long long)z * sBias + min(col + c, N - 8))};
+    }
+    __device__ Aux pre(const Lane &, int) const { return Aux{}; }
+    __device__ void operator()(const Lane &l, int dr, const float (&v)[8], const Aux &) const
+    {
+        float r[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] = v[i] + l.b.b[i];
+        __builtin_nontemporal_store(pack8(r), (bf16x8 *)l.o.at(dr));
     }
 };
 struct EpiBiasGelu {             // h = acc + b1; H = bf16(gelu'(h)); A = bf16(gelu(h)), both blocked
@@ -510,82 +540,97 @@ struct EpiBiasGelu {             // h = acc + b1; H = bf16(gelu'(h)); A = bf16(g
     // hand here: storing the derivative instead of h costs two instructions per element now and
     // saves the whole GELU evaluation in the data-gradient epilogue.
     const float *bias; long long sBias; bf16_t *H; long long sH; bf16_t *A; long long sA; long long ld;
+    static constexpr int VEC = 8;
     typedef NoAux Aux;
-    __device__ Aux pre(int, int, int) const { return Aux{}; }
-    __device__ void operator()(int z, int m, int n, const float (&v)[4], const Aux &) const
+    struct Lane { EpiPtr<bf16_t, true> h, a; EpiBias<8> b; };
+    __device__ Lane lane(int z, int row, int col, int r, int c) const
     {
-        const float4 b = *(const float4 *)(bias + (long long)z * sBias + n);
-        const float h[4] = {v[0] + b.x, v[1] + b.y, v[2] + b.z, v[3] + b.w};
-        float a[4], dg[4];
+        return Lane{EpiPtr<bf16_t, true>(H + (long long)z * sH, ld, row, col, r, c),
+                    EpiPtr<bf16_t, true>(A + (long long)z * sA, ld, row, col, r, c),
+                    EpiBias<8>(bias + (long long)z * sBias + min(col + c, (int)ld - 8))};
+    }
+    __device__ Aux pre(const Lane &, int) const { return Aux{}; }
+    __device__ void operator()(const Lane &l, int dr, const float (&v)[8], const Aux &) const
+    {
+        float a[8], dg[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 8; ++i) {
+            const float h = v[i] + l.b.b[i];
             float c, pdf;
-            gelu_parts(h[i], c, pdf);
-            a[i] = h[i] * c;
-            dg[i] = fmaf(h[i], pdf, c);
+            gelu_parts(h, c, pdf);
+            a[i] = h * c;
+            dg[i] = fmaf(h, pdf, c);
         }
-        const long long o = blk_off(m, n, ld);
-        __builtin_nontemporal_store(pack4(dg[0], dg[1], dg[2], dg[3]), (bf16x4 *)(H + (long long)z * sH + o));
-        __builtin_nontemporal_store(pack4(a[0], a[1], a[2], a[3]), (bf16x4 *)(A + (long long)z * sA + o));
+        __builtin_nontemporal_store(pack8(dg), (bf16x8 *)l.h.at(dr));
+        __builtin_nontemporal_store(pack8(a), (bf16x8 *)l.a.at(dr));
     }
 };
 struct EpiBiasResidual {         // x_out = x_in + acc + b2
     const float *bias; long long sBias; const float *Xin; float *Xout; long long sX; long long ld;
+    static constexpr int VEC = 4;
     typedef float4 Aux;
-    __device__ Aux pre(int z, int m, int n) const
+    struct Lane { EpiPtr<const float, false> x; EpiPtr<float, false> o; EpiBias<4> b; };
+    __device__ Lane lane(int z, int row, int col, int r, int c) const
     {
-        return *(const float4 *)(Xin + (long long)z * sX + (long long)m * ld + n);
+        return Lane{EpiPtr<const float, false>(Xin + (long long)z * sX, ld, row, col, r, c),
+                    EpiPtr<float, false>(Xout + (long long)z * sX, ld, row, col, r, c),
+                    EpiBias<4>(bias + (long long)z * sBias + min(col + c, (int)ld - 4))};
     }
-    __device__ void operator()(int z, int m, int n, const float (&v)[4], const Aux &x) const
+    __device__ Aux pre(const Lane &l, int dr) const { return ld_nt4((const float4 *)l.x.at(dr)); }
+    __device__ void operator()(const Lane &l, int dr, const float (&v)[4], const Aux &x) const
     {
-        const long long o = (long long)z * sX + (long long)m * ld + n;
-        const float4 b = *(const float4 *)(bias + (long long)z * sBias + n);
-        st_nt4((float4 *)(Xout + o), make_float4(x.x + v[0] + b.x, x.y + v[1] + b.y, x.z + v[2] + b.z, x.w + v[3] + b.w));
+        st_nt4((float4 *)l.o.at(dr), make_float4(x.x + v[0] + l.b.b[0], x.y + v[1] + l.b.b[1], x.z + v[2] + l.b.b[2], x.w + v[3] + l.b.b[3]));
     }
 };
 struct EpiGeluBwd {              // dh = acc * gelu'(h), H holding gelu'(h) from the forward pass; both blocked
     const bf16_t *H; long long sH; bf16_t *DH; long long sDH; long long ld;
-    typedef bf16x4 Aux;
-    __device__ Aux pre(int z, int m, int n) const
+    static constexpr int VEC = 8;
+    typedef bf16x8 Aux;
+    struct Lane { EpiPtr<const bf16_t, true> h; EpiPtr<bf16_t, true> o; };
+    __device__ Lane lane(int z, int row, int col, int r, int c) const
     {
-        return *(const bf16x4 *)(H + (long long)z * sH + blk_off(m, n, ld));
+        return Lane{EpiPtr<const bf16_t, true>(H + (long long)z * sH, ld, row, col, r, c),
+                    EpiPtr<bf16_t, true>(DH + (long long)z * sDH, ld, row, col, r, c)};
     }
-    __device__ void operator()(int z, int m, int n, const float (&v)[4], const Aux &hb) const
+    __device__ Aux pre(const Lane &l, int dr) const { return __builtin_nontemporal_load((const bf16x8 *)l.h.at(dr)); }
+    __device__ void operator()(const Lane &l, int dr, const float (&v)[8], const Aux &hb) const
     {
-        float r[4];
+        float r[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = v[i] * (float)hb[i];
-        __builtin_nontemporal_store(pack4(r[0], r[1], r[2], r[3]), (bf16x4 *)(DH + (long long)z * sDH + blk_off(m, n, ld)));
+        for (int i = 0; i < 8; ++i) r[i] = v[i] * (float)hb[i];
+        __builtin_nontemporal_store(pack8(r), (bf16x8 *)l.o.at(dr));
     }
 };
 
-// Tile shapes (BM, BN, BK, wavefronts in M, wavefronts in N), from timing the GEMM shapes of the
-// benchmark size (tokens x width x hidden = 12608 x 768 x 3072, batch 8) on MI355X:
-// 256x256x64 tiles with 8 wavefronts are fastest where the token axis is M (fwd, dgrad: 4800 or
-// 1200 workgroups), also for the two GEMMs with the heavy GELU epilogues (128x256x32 tiles, two
-// workgroups per CU so that one's epilogue could overlap the other's main loop, timed the same to
-// 4 % slower: they fetch 1.5 times the bytes from L2, which is what bounds the main loop).
-// The same tile on 4 wavefronts of 128x128 (2, 2: a third fewer LDS fragment reads per
-// instruction, the 256 accumulator registers in the AGPRs, one wavefront per SIMD) compiles
-// without spills and is 8 - 17 % slower (500 against 461 us, 872 against 744 with the GELU
-// epilogue): with one wavefront per SIMD nothing covers its own waits.
-// The weight gradients (768 x 3072 outputs per worker, reduction over the tokens) go to the
-// persistent two-group kernel of gemm_pp.h, whose 192x384 tiles make exactly 256 workgroups for 8
-// workers.
-#define QSR_GEMM_BIG 256, 256, 64, 2, 4
-
-// NT: the plain tiled kernel.  The persistent form (one workgroup per CU, a ring of four 32-deep
-// stages copied as one stream across tile boundaries, two wavefront groups a phase apart), on the
-// blocked operands and in place in the iteration: 441 against 461 us for the plain K = 3072 GEMM,
-// but 855 against 744 and 813 against 635 us for the two K = 768 GEMMs with epilogue traffic (a
-// workgroup that goes on to its next tile must first see its epilogue's stores complete, where a
-// fresh workgroup starts at once, and its two groups take their epilogues one after the other).  TN: the persistent two-group kernel where the problem allows it.
-// BLKA: the activation operand is blocked (the weights always are)
+// Tile shape of an NT GEMM (BM, BN, wavefronts in M, in N, per SIMD, stages) by the number of tiles and the
+// length of the contraction, from timing every GEMM of the model with every shape on MI355X (us; batch x tokens x
+// width x hidden, the two numbers a GELU forward GEMM with N = hidden and a bf16-output one with N = width):
+//                              256x256, 1 WG/CU   128x256, 2 WG/CU   128x128, 3 WG/CU   64x64, 4 WG/CU
+//   8 x 12608 x 768 x 3072        577 / 404          561 / 424           629 / 526            -
+//   2 x 12608 x 768 x 3072        155 / 134          140 / 115           154 / 111         210 / 176
+//   8 x 12608 x 384 x 1536        213 / 163          200 / 159           201 / 142         262 / 238
+//   8 x 1576 x 768 x 3072          92 / 68            87 / 73             83 / 65          106 / 90
+//   8 x 1040 x 192 x 768         18.3 / 19.1        12.9 / 12.1         11.9 / 8.7        12.6 / 8.0
+//   2 x 400 x 768 x 3072         25.5 / 54.0        16.7 / 30.7         11.6 / 23.9       12.1 / 17.1
+//   2 x 1040 x 192 x 768         16.9 / 18.6        11.6 / 11.4          8.0 / 8.0         5.9 / 5.9
+// Two workgroups per compute unit overlap one's epilogue with the other's main loop, which pays at K = 768, where
+// the epilogue is half the time (426 against 439 us for a plain bf16 output of N = 3072); at K = 3072 the larger
+// tile's smaller copy volume wins once there are enough tiles for several rounds of the chip.  The smaller tiles
+// are for problems that would leave compute units without work: below two rounds of 128 x 256 (or where it would
+// pad N by a fifth or more) 128 x 128, and below 160 of those 64 x 64.
+// BLKA: the activation operand is blocked (the weights always are).
 template <bool BLKA, class Epi>
 static hipError_t gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
-    return launch_gemm_nt<QSR_GEMM_BIG, BLKA>(p, epi, batch, s);
+    auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * batch; };
+    const bool wide = 5LL * ((p.N + 255) / 256) * 256 < 6LL * p.N;
+    if (wide && p.K >= 1024 && tiles(256, 256) >= 1024) return launch_gemm_nt<256, 256, 2, 4, 2, 4, BLKA>(p, epi, batch, s);
+    if (wide && tiles(128, 256) >= 1024) return launch_gemm_nt<128, 256, 1, 4, 2, 3, BLKA>(p, epi, batch, s);
+    if (tiles(128, 128) >= 160) return launch_gemm_nt<128, 128, 2, 2, 3, 3, BLKA>(p, epi, batch, s);
+    return launch_gemm_nt<64, 64, 2, 2, 4, 4, BLKA>(p, epi, batch, s);
 }
+// TN: the persistent two-group kernel of gemm_pp.h, whose 192x384 tiles make exactly 256 workgroups for 8
+// workers of the benchmark size.
 template <bool BLKA, bool BLKB, class Epi>
 static hipError_t gemm_tn(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
@@ -753,7 +798,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
             TRY(ln_fwd(sub, oga));
             {
                 GemmNT p{w.U + (long long)sub * MdB, w.WqTb + l * wWqT, M, 3 * d, d, d, d, w.sU, w.sWq};
-                EpiBiasBf16 epi{theta + obq, P, QKVl, 3LL * d, w.sQKV};
+                EpiBiasBf16 epi{theta + obq, P, QKVl, 3LL * d, w.sQKV, 3 * d};
                 TRY(gemm_nt<true>(p, epi, K, s));
             }
             att.QKV = QKVl; att.O = Ol; att.LSE = w.LSE + (long long)l * heads * M;
