@@ -4,9 +4,9 @@
 // the gradient buffer, the factor min(1, c / (||g_k||_2 + 1e-6)); the update kernels multiply
 // the gradient by it as they read it, so clipping costs one more read of the gradients (4 B per
 // replica-parameter) and no write.
-// The sum of squares is deterministic: every lane adds its elements in index order with an
+// The sum of squares is deterministic: every lane adds its elements in a fixed order with an
 // error-free transformation of each addition, a workgroup combines its lanes in a fixed tree in
-// double precision, and one workgroup per row adds the partial sums in index order.
+// double precision, and one workgroup per row adds the partial sums in a fixed order.
 #include <mutex>
 
 #include "opt_elem.h"
@@ -16,28 +16,47 @@ namespace qsr {
 
 constexpr int CLIP_THREADS = 256;
 
-// partial[k * nb + b] = sum of squares of the b-th chunk of row k
+// partial[k * nb + b] = sum of squares of the b-th chunk of row k.  HBM- or cache-bound (4 B per element):
+// 128-bit loads from the first 16-byte boundary on whatever the row's alignment, four in flight per lane with a
+// sum of their own each (one load per trip ran 8 x 3000001 in 27.6 us, every load waiting for the one before).
 __global__ __launch_bounds__(CLIP_THREADS) void sqnorm_partial_kernel(
     const float *__restrict__ g, long long P, long long chunk, double *__restrict__ partial)
 {
     __shared__ double red[CLIP_THREADS];
+    constexpr int U = 4;
     const int k = blockIdx.y, b = blockIdx.x, nb = gridDim.x;
     const float *row = g + (long long)k * P;
     const long long i0 = (long long)b * chunk, i1 = min(P, i0 + chunk);
-    float s = 0.f, c = 0.f;
-    if ((((uintptr_t)(row + i0)) & 15) == 0) {
-        const long long n4 = (i1 - i0) / 4;
-        const float4 *r4 = (const float4 *)(row + i0);
-        for (long long i = threadIdx.x; i < n4; i += CLIP_THREADS) {
-            const float4 v = ld_nt4(r4 + i);
-            add_comp(s, c, v.x * v.x); add_comp(s, c, v.y * v.y);
-            add_comp(s, c, v.z * v.z); add_comp(s, c, v.w * v.w);
+    float s[U] = {0.f, 0.f, 0.f, 0.f}, c[U] = {0.f, 0.f, 0.f, 0.f};
+    if (i0 < i1) {
+        const long long head = min(i1 - i0, (long long)((16 - ((uintptr_t)(row + i0) & 15)) & 15) / 4);
+        const long long v0 = i0 + head, n4 = (i1 - v0) / 4;
+        const float4 *r4 = (const float4 *)(row + v0);
+        long long i = threadIdx.x;
+        for (; i + (U - 1) * CLIP_THREADS < n4; i += U * CLIP_THREADS) {
+            float4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = ld_nt4(r4 + i + u * CLIP_THREADS);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                add_comp(s[u], c[u], v[u].x * v[u].x); add_comp(s[u], c[u], v[u].y * v[u].y);
+                add_comp(s[u], c[u], v[u].z * v[u].z); add_comp(s[u], c[u], v[u].w * v[u].w);
+            }
         }
-        for (long long i = i0 + n4 * 4 + threadIdx.x; i < i1; i += CLIP_THREADS) add_comp(s, c, row[i] * row[i]);
-    } else {
-        for (long long i = i0 + threadIdx.x; i < i1; i += CLIP_THREADS) add_comp(s, c, row[i] * row[i]);
+        for (; i < n4; i += CLIP_THREADS) {
+            const float4 v = ld_nt4(r4 + i);
+            add_comp(s[0], c[0], v.x * v.x); add_comp(s[0], c[0], v.y * v.y);
+            add_comp(s[0], c[0], v.z * v.z); add_comp(s[0], c[0], v.w * v.w);
+        }
+        // at most three elements in front of the first boundary and three behind the last
+        if ((long long)threadIdx.x < head) add_comp(s[1], c[1], row[i0 + threadIdx.x] * row[i0 + threadIdx.x]);
+        const long long t = v0 + n4 * 4 + threadIdx.x;
+        if (t < i1) add_comp(s[2], c[2], row[t] * row[t]);
     }
-    red[threadIdx.x] = (double)s + (double)c;
+    double acc = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc += (double)s[u] + (double)c[u];
+    red[threadIdx.x] = acc;
     __syncthreads();
     for (int w = CLIP_THREADS / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
@@ -46,15 +65,25 @@ __global__ __launch_bounds__(CLIP_THREADS) void sqnorm_partial_kernel(
     if (threadIdx.x == 0) partial[(long long)k * nb + b] = red[0];
 }
 
-// coef[k] = min(1, max_norm / (sqrt(sum_b partial[k][b]) + 1e-6)); norm[k] = that square root
-__global__ void clip_coef_kernel(const double *__restrict__ partial, int nb, float max_norm,
-                                 float *__restrict__ coef, float *__restrict__ norm)
+// coef[k] = min(1, max_norm / (sqrt(sum_b partial[k][b]) + 1e-6)); norm[k] = that square root.  One workgroup per
+// row (nb <= 1024: at most four partial sums per lane, then a fixed tree; one lane adding them all took 12-15 us);
+// same_rows: row 0's sum serves all rows.
+__global__ __launch_bounds__(CLIP_THREADS) void clip_coef_kernel(const double *__restrict__ partial, int nb, float max_norm,
+                                                                 int same_rows, float *__restrict__ coef, float *__restrict__ norm)
 {
-    if (threadIdx.x != 0) return;
+    __shared__ double red[CLIP_THREADS];
     const int k = blockIdx.x;
-    double ss = 0.0;
-    for (int b = 0; b < nb; ++b) ss += partial[(long long)k * nb + b];
-    const double nrm = sqrt(ss);
+    const double *p = partial + (same_rows ? 0 : (long long)k * nb);
+    double acc = 0.0;
+    for (int b = threadIdx.x; b < nb; b += CLIP_THREADS) acc += p[b];
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int w = CLIP_THREADS / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x != 0) return;
+    const double nrm = sqrt(red[0]);
     const double cf = (double)max_norm / (nrm + 1e-6);
     coef[k] = cf < 1.0 ? (float)cf : 1.0f;
     norm[k] = (float)nrm;
@@ -69,15 +98,15 @@ int clip_blocks_per_row(long long P)
 }
 
 hipError_t launch_clip_coef(const float *g, int K, long long P, float max_norm, double *partial, float *coef,
-                            float *norm, hipStream_t s)
+                            float *norm, hipStream_t s, bool same_rows)
 {
     const int nb = clip_blocks_per_row(P);
     long long chunk = (P + nb - 1) / nb;
     chunk = (chunk + 3) / 4 * 4;                    // chunk starts stay 16-byte aligned where the row is
-    sqnorm_partial_kernel<<<dim3((unsigned)nb, (unsigned)K), CLIP_THREADS, 0, s>>>(g, P, chunk, partial);
+    sqnorm_partial_kernel<<<dim3((unsigned)nb, same_rows ? 1u : (unsigned)K), CLIP_THREADS, 0, s>>>(g, P, chunk, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    clip_coef_kernel<<<K, 64, 0, s>>>(partial, nb, max_norm, coef, norm);
+    clip_coef_kernel<<<K, CLIP_THREADS, 0, s>>>(partial, nb, max_norm, same_rows ? 1 : 0, coef, norm);
     return hipGetLastError();
 }
 

@@ -24,11 +24,12 @@ __global__ __launch_bounds__(64) void fill_normal_kernel(float *__restrict__ out
         long long p = q * 4;
         if (vec) {
             st_nt4((float4 *)(row + p), z);
+        } else if (p + 3 < n) {                  // rows that start off the 16-byte grid: still one store per group
+            st4u(row + p, z);
         } else {
             row[p] = z.x;
             if (p + 1 < n) row[p + 1] = z.y;
             if (p + 2 < n) row[p + 2] = z.z;
-            if (p + 3 < n) row[p + 3] = z.w;
         }
     }
 }

@@ -444,7 +444,7 @@ extern "C" int qsr_init(const qsr_config *cfg, float *params, float *grads, floa
     // copy of the scheduler state that alternates from iteration to iteration): the update kernel takes
     // the scheduler's step on the iterations that end no round, and no scheduler kernel is launched there.
     c->cur = 0; c->ticked = false;
-    c->fold_tick = c->graph_iters == 0 && !cfg->parallel && (cfg->clip_norm <= 0.0 || (cfg->P & 3) == 0);
+    c->fold_tick = c->graph_iters == 0 && (!cfg->parallel || (cfg->P & 3) == 0);
     c->dims = make_dims(cfg);
     rc = init_impl(c, theta0);
     c->cfg.milestones = nullptr;
@@ -536,13 +536,15 @@ extern "C" int qsr_local_step(qsr_ctx *c)
     const bool all = c->capturing;
     const bool sync_now = mirror_sync_now(c);
     const bool fused = cfg.fuse_sync != 0;
-    DevState *st_next = (c->fold_tick && !all && !sync_now) ? c->d_state + (c->cur ^ 1) : nullptr;
+    // With Parallel OPT every step ends a round and nothing averages parameters behind the update.
+    const bool shared_g = cfg.parallel != 0 && (cfg.P & 3) == 0;
+    DevState *st_next = (c->fold_tick && !all && (!sync_now || shared_g)) ? c->d_state + (c->cur ^ 1) : nullptr;
     if (!fused || all || !sync_now) {                   // OPT for all K workers at once
         Bracket br(c, 1);
         if (br.rc != QSR_OK) return br.rc;
         if (cfg.clip_norm > 0.0)                        // App. C: per-worker factors min(1, c / (||g_k|| + 1e-6))
             HIP_TRY(launch_clip_coef(c->grads, cfg.K, cfg.P, (float)cfg.clip_norm, c->d_clip_part,
-                                     c->d_clip_coef, c->d_clip_coef + cfg.K, c->stream));
+                                     c->d_clip_coef, c->d_clip_coef + cfg.K, c->stream, cfg.parallel != 0));
         if (cfg.fuse_gradient && cfg.opt == QSR_OPT_SGDM)   // Eq. (1) and OPT in one pass (noise model)
             HIP_TRY(launch_update_sgdm_noise(c->params, c->grads, c->state0, cfg.K, cfg.P, st_cur(c), c->d_scal,
                                              (float)cfg.momentum, (float)cfg.weight_decay, (float)cfg.grad_sigma,
@@ -555,11 +557,11 @@ extern "C" int qsr_local_step(qsr_ctx *c)
         else if (cfg.opt == QSR_OPT_SGDM)
             HIP_TRY(launch_update_sgdm(c->params, c->grads, c->state0, cfg.K, cfg.P, st_cur(c), c->d_scal,
                                        (float)cfg.momentum, (float)cfg.weight_decay, fused, c->d_clip_coef,
-                                       c->stream, st_next, &c->sp));
+                                       shared_g, c->stream, st_next, &c->sp));
         else
             HIP_TRY(launch_update_adamw(c->params, c->grads, c->state0, c->state1, cfg.K, cfg.P, st_cur(c),
                                         c->d_scal, (float)(1.0 - cfg.beta1), (float)(1.0 - cfg.beta2),
-                                        (float)cfg.eps, fused, c->d_clip_coef, c->stream, st_next, &c->sp));
+                                        (float)cfg.eps, fused, c->d_clip_coef, shared_g, c->stream, st_next, &c->sp));
         int rc = br.close(c->t_host);
         if (rc != QSR_OK) return rc;
         if (st_next) { c->cur ^= 1; c->ticked = true; }    // the advanced state is in the other copy now
@@ -689,6 +691,9 @@ static int fetch_state(qsr_ctx *c)
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (c->h_state->mismatch) return QSR_EMIRROR;
     if (c->need_sync_call && !c->ticked) { c->h_state->t += 1; c->h_state->h += 1; }
+    // Parallel OPT (H = 1 always): the folded step has closed the round already, which the protocol
+    // counts at qsr_maybe_sync
+    if (c->ticked && c->cfg.parallel) { c->h_state->s -= 1; c->h_state->h = 1; c->h_state->H = 1; }
     return QSR_OK;
 }
 

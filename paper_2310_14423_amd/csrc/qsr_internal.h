@@ -50,6 +50,40 @@ __device__ __forceinline__ void st_nt4(float4 *p, float4 v)
     __builtin_nontemporal_store(w, (vf4 *)p);
 }
 
+// Four consecutive floats at any 4-byte address: rows whose length is not a multiple of 4 start
+// anywhere, and the hardware takes 128-bit global accesses at 4-byte alignment.  Cached, not
+// streaming: a wavefront's run of 1 KiB starts and ends inside a 128-byte line, whose other part its
+// neighbour writes, and L2 has to hold the line until both have.
+typedef float vf4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 ld4u(const float *p)
+{
+    vf4u v = *(const vf4u *)p;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st4u(float *p, float4 v)
+{
+    vf4u w = {v.x, v.y, v.z, v.w};
+    *(vf4u *)p = w;
+}
+// Column group c of a row of P floats: P4 = P / 4 whole groups of four, then rem = P % 4 left over.
+// rem == 0: every row is 16-byte aligned (the buffers are).
+__device__ __forceinline__ float4 ld_group(const float *row, long long c, long long P4, int rem)
+{
+    const float *p = row + c * 4;
+    if (rem == 0) return ld_nt4((const float4 *)p);
+    if (c < P4) return ld4u(p);
+    return make_float4(p[0], rem > 1 ? p[1] : 0.f, rem > 2 ? p[2] : 0.f, 0.f);
+}
+__device__ __forceinline__ void st_group(float *row, long long c, long long P4, int rem, float4 v)
+{
+    float *p = row + c * 4;
+    if (rem == 0) { st_nt4((float4 *)p, v); return; }
+    if (c < P4) { st4u(p, v); return; }
+    p[0] = v.x;
+    if (rem > 1) p[1] = v.y;
+    if (rem > 2) p[2] = v.z;
+}
+
 // streams of the counter-based generator (second counter word)
 enum : uint32_t { STREAM_GRAD = 0, STREAM_X = 1, STREAM_NOISE = 2, STREAM_LABEL = 3 };
 
@@ -67,16 +101,17 @@ hipError_t launch_sched_advance(DevState *st, SchedParams sp, int expect_sync, h
 
 // fused_sync: leave the step that completes a round to launch_update_*_sync.
 // row_coef: K clipping factors the gradient rows are multiplied by as they are read, or nullptr.
-// st_next != nullptr (with sp; not for clipped rows whose length is not a multiple of 4): the kernel also
-// takes the scheduler's end-of-iteration step, on an iteration that does not end a round: the advanced
-// state goes to *st_next, a second copy that no kernel of this iteration reads.
+// shared_g: the K gradient rows are known to be equal (Parallel OPT), and every iteration ends a round.
+// st_next != nullptr (with sp): the kernel also takes the scheduler's end-of-iteration step, on an iteration
+// that does not end a round (or with shared_g): the advanced state goes to *st_next, a second copy that
+// no kernel of this iteration reads.
 hipError_t launch_update_sgdm(float *theta, float *g, float *buf, int K, long long P,
                               const DevState *st, const StepScalars *sc, float mu, float lambda,
-                              bool fused_sync, const float *row_coef, hipStream_t s,
+                              bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s,
                               DevState *st_next = nullptr, const SchedParams *sp = nullptr);
 hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K, long long P,
                                const DevState *st, const StepScalars *sc, float c1, float c2,
-                               float eps, bool fused_sync, const float *row_coef, hipStream_t s,
+                               float eps, bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s,
                                DevState *st_next = nullptr, const SchedParams *sp = nullptr);
 // the same updates with the optimizer-only workloads' gradient g = sigma * N(0,1) drawn inside the
 // kernel (and written to g if store_g); P must be a multiple of 4
@@ -97,10 +132,11 @@ hipError_t launch_update_adamw_sync(float *theta, const float *g, float *m, floa
                                     float eps, const float *row_coef, hipStream_t s);
 
 // gradient clipping: coef[k] = min(1, max_norm / (||g_k|| + 1e-6)), norm[k] = ||g_k||;
-// partial: K * clip_blocks_per_row(P) doubles of scratch
+// partial: K * clip_blocks_per_row(P) doubles of scratch.  same_rows: the rows are known to be equal, only the
+// first is read.
 int clip_blocks_per_row(long long P);
 hipError_t launch_clip_coef(const float *g, int K, long long P, float max_norm, double *partial, float *coef,
-                            float *norm, hipStream_t s);
+                            float *norm, hipStream_t s, bool same_rows = false);
 // device address, on the current device, of the partial-sum array inside the library's image
 // (qsr_clip_factors_static); looked up at the first call on a device.  Returns a QSR_* code.
 int clip_static_setup(double **out);

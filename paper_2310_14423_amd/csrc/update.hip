@@ -22,8 +22,13 @@ __device__ __forceinline__ void stg_nt(float4 *p, float4 v) { st_nt4(p, v); }
 
 // `fused_sync`: the context folds the averaging into the last local step of a round (see the
 // *_sync kernels below), so the plain update leaves that step alone.
-// CLIP: the launch has one grid row per worker (blockIdx.y), n4 and n are one worker's row, and
-// the gradient is multiplied by that worker's clipping factor as it is read.
+// CLIP: the gradient is multiplied by its worker's clipping factor as it is read.  The buffers stay one
+// vector of K*P elements, 16-byte aligned whatever P is; a workgroup's run of 512 elements holds at
+// most one row boundary (P >= 512), found once per trip.  (With one grid row per worker, rows of
+// odd length had to go one element at a time: 85 us for 8 x 3000001 SGD, 20 B per element.)
+// SHARED (Parallel OPT): all workers' gradients are the same row, so only row 0 is read: one grid row per worker,
+// n4 and n one worker's row; the row stays in the caches while the workers go over it (343 us for 28 B per element
+// at 16 x 4000004 AdamW before).
 // NOISE (optimizer-only workloads): the gradient is not read but drawn here, g = sigma * N(0,1)
 // from the same Philox counters and with the same arithmetic as fill_normal_kernel.  The separate
 // fill is bound by its arithmetic (about 220 vector instructions per four normals), this kernel by
@@ -41,28 +46,63 @@ struct NoiseDraw { float sigma; uint64_t seed; int store; };
 // to the other copy, which the next iteration's kernels are handed.  No kernel of this iteration
 // reads that one, so no ordering between workgroups is needed, and the one-thread scheduler launch
 // (4 us of dispatch latency, 3 % of a perceptron iteration) goes away.
-__device__ __forceinline__ void tick_into(const DevState *st, DevState *st_next, const SchedParams &sp)
+// (With Parallel OPT every iteration is a round and no averaging kernel reads the state behind the update: there
+// the step that is folded in logs the round as well; sync: what the host's mirror expects.)
+__device__ __forceinline__ void tick_into(const DevState *st, DevState *st_next, const SchedParams &sp, int sync)
 {
     DevState nx = *st;
-    sched_advance(&nx, sp, 0);
+    sched_advance(&nx, sp, sync);
     *st_next = nx;
 }
 
-template <bool CLIP, bool NOISE>
+// Worker of an element of the flat K*P vector.
+struct RowAt { long long k, bound; float c0, c1; };   // row of a run's first element, where it ends, its factor and the next row's
+struct RowMap {
+    long long P; int K; double invP;
+    __device__ __forceinline__ long long row(long long e) const
+    {
+        long long k = (long long)((double)e * invP);
+        if (k * P > e) --k;                              // the product is off by an ulp at most
+        if ((k + 1) * P <= e) ++k;
+        return k;
+    }
+    __device__ __forceinline__ RowAt at(long long e, const float *coef) const
+    {
+        RowAt r;
+        r.k = row(e);
+        r.bound = (r.k + 1) * P;
+        r.c0 = coef[min(r.k, (long long)K - 1)];
+        r.c1 = coef[min(r.k + 1, (long long)K - 1)];
+        return r;
+    }
+};
+__device__ __forceinline__ void scale_by_row(float4 &b, long long e, const RowAt &ra, const RowMap &rm,
+                                             const float *__restrict__ coef)
+{
+    if (rm.P >= UPD_THREADS * UPD_UNROLL * 4) {          // at most one boundary in the run
+        b.x *= e < ra.bound ? ra.c0 : ra.c1;     b.y *= e + 1 < ra.bound ? ra.c0 : ra.c1;
+        b.z *= e + 2 < ra.bound ? ra.c0 : ra.c1; b.w *= e + 3 < ra.bound ? ra.c0 : ra.c1;
+    } else {
+        b.x *= coef[rm.row(e)];     b.y *= coef[rm.row(e + 1)];
+        b.z *= coef[rm.row(e + 2)]; b.w *= coef[rm.row(e + 3)];
+    }
+}
+
+template <bool CLIP, bool NOISE, bool SHARED>
 __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
     float4 *__restrict__ theta, float4 *__restrict__ g, float4 *__restrict__ m,
     float4 *__restrict__ v, long long n4, long long n, const DevState *__restrict__ st,
     const StepScalars *__restrict__ sc, float c1, float c2, float eps, int fused_sync,
-    const float *__restrict__ row_coef, NoiseDraw nd, DevState *__restrict__ st_next, SchedParams sp)
+    const float *__restrict__ row_coef, RowMap rm, NoiseDraw nd, DevState *__restrict__ st_next, SchedParams sp)
 {
-    if (st_next != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tick_into(st, st_next, sp);
+    if (st_next != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tick_into(st, st_next, sp, SHARED ? 1 : 0);
     if (fused_sync && st->h + 1 == st->H) return;
-    float gs = 1.0f;
-    if (CLIP || NOISE) {
+    if (NOISE || SHARED) {
         const long long off = (long long)blockIdx.y * n4;      // rows are 16-byte aligned here
-        theta += off; g += off; m += off; v += off;
-        if (CLIP) gs = row_coef[blockIdx.y];
+        theta += off; m += off; v += off;
+        if (!SHARED) g += off;
     }
+    const float gs = SHARED && row_coef != nullptr ? row_coef[0] : 1.0f;
     const long long t = st->t;
     const StepScalars s = sc[t];
     const long long stride = (long long)gridDim.x * UPD_THREADS * UPD_UNROLL;
@@ -74,9 +114,17 @@ __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
             long long i = base + (long long)u * UPD_THREADS;
             if (i < n4) {
                 a[u] = ldg_nt(theta + i); c[u] = ldg_nt(m + i); d[u] = ldg_nt(v + i);
-                if (!NOISE) b[u] = ldg_nt(g + i);
+                if (!NOISE) b[u] = SHARED ? g[i] : ldg_nt(g + i);
             }
-            if (CLIP) { b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
+            if (SHARED) { b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
+        }
+        if (CLIP) {
+            const RowAt ra = rm.at((base - threadIdx.x) * 4, row_coef);
+#pragma unroll
+            for (int u = 0; u < UPD_UNROLL; ++u) {
+                const long long i = base + (long long)u * UPD_THREADS;
+                if (i < n4) scale_by_row(b[u], i * 4, ra, rm, row_coef);
+            }
         }
         if (NOISE) {
 #pragma unroll
@@ -108,31 +156,32 @@ __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
         }
     }
     // ragged tail (n not a multiple of 4): at most 3 elements, done by the first threads
-    if (!CLIP && !NOISE && blockIdx.x == 0 && threadIdx.x < (int)(n - n4 * 4)) {
+    if (!NOISE && !SHARED && blockIdx.x == 0 && threadIdx.x < (int)(n - n4 * 4)) {
         long long i = n4 * 4 + threadIdx.x;
         float *th = (float *)theta, *mm = (float *)m, *vv = (float *)v;
-        const float *gg = (const float *)g;
+        float gi = ((const float *)g)[i];
+        if (CLIP) gi *= row_coef[rm.row(i)];
         float a = th[i], c = mm[i], d = vv[i];
-        adamw_elem(a, gg[i], c, d, s.x, s.y, s.z, c1, c2, eps);
+        adamw_elem(a, gi, c, d, s.x, s.y, s.z, c1, c2, eps);
         th[i] = a; mm[i] = c; vv[i] = d;
     }
 }
 
-template <bool CLIP, bool NOISE>
+template <bool CLIP, bool NOISE, bool SHARED>
 __global__ __launch_bounds__(UPD_THREADS) void update_sgdm_kernel(
     float4 *__restrict__ theta, float4 *__restrict__ g, float4 *__restrict__ buf,
     long long n4, long long n, const DevState *__restrict__ st,
     const StepScalars *__restrict__ sc, float mu, float lambda, int fused_sync,
-    const float *__restrict__ row_coef, NoiseDraw nd, DevState *__restrict__ st_next, SchedParams sp)
+    const float *__restrict__ row_coef, RowMap rm, NoiseDraw nd, DevState *__restrict__ st_next, SchedParams sp)
 {
-    if (st_next != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tick_into(st, st_next, sp);
+    if (st_next != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tick_into(st, st_next, sp, SHARED ? 1 : 0);
     if (fused_sync && st->h + 1 == st->H) return;
-    float gs = 1.0f;
-    if (CLIP || NOISE) {
+    if (NOISE || SHARED) {
         const long long off = (long long)blockIdx.y * n4;
-        theta += off; g += off; buf += off;
-        if (CLIP) gs = row_coef[blockIdx.y];
+        theta += off; buf += off;
+        if (!SHARED) g += off;
     }
+    const float gs = SHARED && row_coef != nullptr ? row_coef[0] : 1.0f;
     const long long t = st->t;
     const float eta = sc[t].x;
     const long long stride = (long long)gridDim.x * UPD_THREADS * UPD_UNROLL;
@@ -144,9 +193,17 @@ __global__ __launch_bounds__(UPD_THREADS) void update_sgdm_kernel(
             long long i = base + (long long)u * UPD_THREADS;
             if (i < n4) {
                 a[u] = ldg_nt(theta + i); c[u] = ldg_nt(buf + i);
-                if (!NOISE) b[u] = ldg_nt(g + i);
+                if (!NOISE) b[u] = SHARED ? g[i] : ldg_nt(g + i);
             }
-            if (CLIP) { b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
+            if (SHARED) { b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
+        }
+        if (CLIP) {
+            const RowAt ra = rm.at((base - threadIdx.x) * 4, row_coef);
+#pragma unroll
+            for (int u = 0; u < UPD_UNROLL; ++u) {
+                const long long i = base + (long long)u * UPD_THREADS;
+                if (i < n4) scale_by_row(b[u], i * 4, ra, rm, row_coef);
+            }
         }
         if (NOISE) {
 #pragma unroll
@@ -177,12 +234,13 @@ __global__ __launch_bounds__(UPD_THREADS) void update_sgdm_kernel(
             }
         }
     }
-    if (!CLIP && !NOISE && blockIdx.x == 0 && threadIdx.x < (int)(n - n4 * 4)) {
+    if (!NOISE && !SHARED && blockIdx.x == 0 && threadIdx.x < (int)(n - n4 * 4)) {
         long long i = n4 * 4 + threadIdx.x;
         float *th = (float *)theta, *bb = (float *)buf;
-        const float *gg = (const float *)g;
+        float gi = ((const float *)g)[i];
+        if (CLIP) gi *= row_coef[rm.row(i)];
         float a = th[i], c = bb[i];
-        sgdm_elem(a, gg[i], c, eta, mu, lambda);
+        sgdm_elem(a, gi, c, eta, mu, lambda);
         th[i] = a; bb[i] = c;
     }
 }
@@ -215,86 +273,6 @@ constexpr int SYNC_ROWS = 4;
 constexpr int SYNC_THREADS = 256;
 
 __global__ __launch_bounds__(SYNC_THREADS) void update_adamw_sync_kernel(
-    float4 *__restrict__ theta, const float4 *__restrict__ g, float4 *__restrict__ m,
-    float4 *__restrict__ v, int K, long long P4, const DevState *__restrict__ st,
-    const StepScalars *__restrict__ sc, float c1, float c2, float eps, const float *__restrict__ row_coef)
-{
-    if (st->h + 1 != st->H) return;
-    const StepScalars s = sc[st->t];
-    const float fK = (float)K;
-    const long long stride = (long long)gridDim.x * SYNC_THREADS;
-    for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < P4; i += stride) {
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), cmp = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int k0 = 0; k0 < K; k0 += SYNC_ROWS) {
-            float4 a[SYNC_ROWS], b[SYNC_ROWS], c[SYNC_ROWS], d[SYNC_ROWS];
-#pragma unroll
-            for (int u = 0; u < SYNC_ROWS; ++u)
-                if (k0 + u < K) {
-                    const long long o = (long long)(k0 + u) * P4 + i;
-                    a[u] = ldg_nt(theta + o); b[u] = ldg_nt(g + o); c[u] = ldg_nt(m + o); d[u] = ldg_nt(v + o);
-                    if (row_coef != nullptr) { const float gs = row_coef[k0 + u]; b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
-                }
-#pragma unroll
-            for (int u = 0; u < SYNC_ROWS; ++u)
-                if (k0 + u < K) {
-                    const long long o = (long long)(k0 + u) * P4 + i;
-                    adamw_elem(a[u].x, b[u].x, c[u].x, d[u].x, s.x, s.y, s.z, c1, c2, eps);
-                    adamw_elem(a[u].y, b[u].y, c[u].y, d[u].y, s.x, s.y, s.z, c1, c2, eps);
-                    adamw_elem(a[u].z, b[u].z, c[u].z, d[u].z, s.x, s.y, s.z, c1, c2, eps);
-                    adamw_elem(a[u].w, b[u].w, c[u].w, d[u].w, s.x, s.y, s.z, c1, c2, eps);
-                    stg_nt(m + o, c[u]); stg_nt(v + o, d[u]);
-                    add_comp(acc.x, cmp.x, a[u].x); add_comp(acc.y, cmp.y, a[u].y);
-                    add_comp(acc.z, cmp.z, a[u].z); add_comp(acc.w, cmp.w, a[u].w);
-                }
-        }
-        const float4 mean = make_float4((acc.x + cmp.x) / fK, (acc.y + cmp.y) / fK,
-                                        (acc.z + cmp.z) / fK, (acc.w + cmp.w) / fK);
-        for (int k = 0; k < K; ++k) stg_nt(theta + (long long)k * P4 + i, mean);
-    }
-}
-
-__global__ __launch_bounds__(SYNC_THREADS) void update_sgdm_sync_kernel(
-    float4 *__restrict__ theta, const float4 *__restrict__ g, float4 *__restrict__ buf, int K,
-    long long P4, const DevState *__restrict__ st, const StepScalars *__restrict__ sc, float mu,
-    float lambda, const float *__restrict__ row_coef)
-{
-    if (st->h + 1 != st->H) return;
-    const float eta = sc[st->t].x;
-    const float fK = (float)K;
-    const long long stride = (long long)gridDim.x * SYNC_THREADS;
-    for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < P4; i += stride) {
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), cmp = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int k0 = 0; k0 < K; k0 += SYNC_ROWS) {
-            float4 a[SYNC_ROWS], b[SYNC_ROWS], c[SYNC_ROWS];
-#pragma unroll
-            for (int u = 0; u < SYNC_ROWS; ++u)
-                if (k0 + u < K) {
-                    const long long o = (long long)(k0 + u) * P4 + i;
-                    a[u] = ldg_nt(theta + o); b[u] = ldg_nt(g + o); c[u] = ldg_nt(buf + o);
-                    if (row_coef != nullptr) { const float gs = row_coef[k0 + u]; b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
-                }
-#pragma unroll
-            for (int u = 0; u < SYNC_ROWS; ++u)
-                if (k0 + u < K) {
-                    const long long o = (long long)(k0 + u) * P4 + i;
-                    sgdm_elem(a[u].x, b[u].x, c[u].x, eta, mu, lambda);
-                    sgdm_elem(a[u].y, b[u].y, c[u].y, eta, mu, lambda);
-                    sgdm_elem(a[u].z, b[u].z, c[u].z, eta, mu, lambda);
-                    sgdm_elem(a[u].w, b[u].w, c[u].w, eta, mu, lambda);
-                    stg_nt(buf + o, c[u]);
-                    add_comp(acc.x, cmp.x, a[u].x); add_comp(acc.y, cmp.y, a[u].y);
-                    add_comp(acc.z, cmp.z, a[u].z); add_comp(acc.w, cmp.w, a[u].w);
-                }
-        }
-        const float4 mean = make_float4((acc.x + cmp.x) / fK, (acc.y + cmp.y) / fK,
-                                        (acc.z + cmp.z) / fK, (acc.w + cmp.w) / fK);
-        for (int k = 0; k < K; ++k) stg_nt(theta + (long long)k * P4 + i, mean);
-    }
-}
-
-// rows whose length is not a multiple of 4 are not 16-byte aligned: one element per lane
-// (v == nullptr: SGD with momentum, m is its buffer, c1 = mu, c2 = lambda)
-__global__ __launch_bounds__(SYNC_THREADS) void update_sync_scalar_kernel(
     float *__restrict__ theta, const float *__restrict__ g, float *__restrict__ m,
     float *__restrict__ v, int K, long long P, const DevState *__restrict__ st,
     const StepScalars *__restrict__ sc, float c1, float c2, float eps, const float *__restrict__ row_coef)
@@ -302,51 +280,77 @@ __global__ __launch_bounds__(SYNC_THREADS) void update_sync_scalar_kernel(
     if (st->h + 1 != st->H) return;
     const StepScalars s = sc[st->t];
     const float fK = (float)K;
+    const long long P4 = P >> 2, C4 = (P + 3) >> 2;
+    const int rem = (int)(P & 3);
     const long long stride = (long long)gridDim.x * SYNC_THREADS;
-    for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < P; i += stride) {
-        float acc = 0.f, cmp = 0.f;
-        for (int k = 0; k < K; ++k) {
-            const long long o = (long long)k * P + i;
-            float a = theta[o], c = m[o];
-            const float gk = row_coef != nullptr ? g[o] * row_coef[k] : g[o];
-            if (v != nullptr) {
-                float d = v[o];
-                adamw_elem(a, gk, c, d, s.x, s.y, s.z, c1, c2, eps);
-                v[o] = d;
-            } else {
-                sgdm_elem(a, gk, c, s.x, c1, c2);
-            }
-            m[o] = c;
-            add_comp(acc, cmp, a);
+    for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < C4; i += stride) {
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), cmp = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int k0 = 0; k0 < K; k0 += SYNC_ROWS) {
+            float4 a[SYNC_ROWS], b[SYNC_ROWS], c[SYNC_ROWS], d[SYNC_ROWS];
+#pragma unroll
+            for (int u = 0; u < SYNC_ROWS; ++u)
+                if (k0 + u < K) {
+                    const long long o = (long long)(k0 + u) * P;
+                    a[u] = ld_group(theta + o, i, P4, rem); b[u] = ld_group(g + o, i, P4, rem); c[u] = ld_group(m + o, i, P4, rem); d[u] = ld_group(v + o, i, P4, rem);
+                    if (row_coef != nullptr) { const float gs = row_coef[k0 + u]; b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
+                }
+#pragma unroll
+            for (int u = 0; u < SYNC_ROWS; ++u)
+                if (k0 + u < K) {
+                    const long long o = (long long)(k0 + u) * P;
+                    adamw_elem(a[u].x, b[u].x, c[u].x, d[u].x, s.x, s.y, s.z, c1, c2, eps);
+                    adamw_elem(a[u].y, b[u].y, c[u].y, d[u].y, s.x, s.y, s.z, c1, c2, eps);
+                    adamw_elem(a[u].z, b[u].z, c[u].z, d[u].z, s.x, s.y, s.z, c1, c2, eps);
+                    adamw_elem(a[u].w, b[u].w, c[u].w, d[u].w, s.x, s.y, s.z, c1, c2, eps);
+                    st_group(m + o, i, P4, rem, c[u]); st_group(v + o, i, P4, rem, d[u]);
+                    add_comp(acc.x, cmp.x, a[u].x); add_comp(acc.y, cmp.y, a[u].y);
+                    add_comp(acc.z, cmp.z, a[u].z); add_comp(acc.w, cmp.w, a[u].w);
+                }
         }
-        const float mean = (acc + cmp) / fK;
-        for (int k = 0; k < K; ++k) theta[(long long)k * P + i] = mean;
+        const float4 mean = make_float4((acc.x + cmp.x) / fK, (acc.y + cmp.y) / fK,
+                                        (acc.z + cmp.z) / fK, (acc.w + cmp.w) / fK);
+        for (int k = 0; k < K; ++k) st_group(theta + (long long)k * P, i, P4, rem, mean);
     }
 }
 
-// clipped update of rows that are not 16-byte aligned (P not a multiple of 4): one element per
-// lane, one grid row per worker (v == nullptr: SGD with momentum, c1 = mu, c2 = lambda)
-__global__ __launch_bounds__(SYNC_THREADS) void update_clip_scalar_kernel(
-    float *__restrict__ theta, const float *__restrict__ g, float *__restrict__ m,
-    float *__restrict__ v, long long P, const DevState *__restrict__ st,
-    const StepScalars *__restrict__ sc, float c1, float c2, float eps, int fused_sync,
-    const float *__restrict__ row_coef)
+__global__ __launch_bounds__(SYNC_THREADS) void update_sgdm_sync_kernel(
+    float *__restrict__ theta, const float *__restrict__ g, float *__restrict__ buf, int K,
+    long long P, const DevState *__restrict__ st, const StepScalars *__restrict__ sc, float mu,
+    float lambda, const float *__restrict__ row_coef)
 {
-    if (fused_sync && st->h + 1 == st->H) return;
-    const StepScalars s = sc[st->t];
-    const float gs = row_coef[blockIdx.y];
+    if (st->h + 1 != st->H) return;
+    const float eta = sc[st->t].x;
+    const float fK = (float)K;
+    const long long P4 = P >> 2, C4 = (P + 3) >> 2;
+    const int rem = (int)(P & 3);
     const long long stride = (long long)gridDim.x * SYNC_THREADS;
-    for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < P; i += stride) {
-        const long long o = (long long)blockIdx.y * P + i;
-        float a = theta[o], c = m[o];
-        if (v != nullptr) {
-            float d = v[o];
-            adamw_elem(a, g[o] * gs, c, d, s.x, s.y, s.z, c1, c2, eps);
-            v[o] = d;
-        } else {
-            sgdm_elem(a, g[o] * gs, c, s.x, c1, c2);
+    for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < C4; i += stride) {
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), cmp = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int k0 = 0; k0 < K; k0 += SYNC_ROWS) {
+            float4 a[SYNC_ROWS], b[SYNC_ROWS], c[SYNC_ROWS];
+#pragma unroll
+            for (int u = 0; u < SYNC_ROWS; ++u)
+                if (k0 + u < K) {
+                    const long long o = (long long)(k0 + u) * P;
+                    a[u] = ld_group(theta + o, i, P4, rem); b[u] = ld_group(g + o, i, P4, rem); c[u] = ld_group(buf + o, i, P4, rem);
+                    if (row_coef != nullptr) { const float gs = row_coef[k0 + u]; b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
+                }
+#pragma unroll
+            for (int u = 0; u < SYNC_ROWS; ++u)
+                if (k0 + u < K) {
+                    const long long o = (long long)(k0 + u) * P;
+                    sgdm_elem(a[u].x, b[u].x, c[u].x, eta, mu, lambda);
+                    sgdm_elem(a[u].y, b[u].y, c[u].y, eta, mu, lambda);
+                    sgdm_elem(a[u].z, b[u].z, c[u].z, eta, mu, lambda);
+                    sgdm_elem(a[u].w, b[u].w, c[u].w, eta, mu, lambda);
+                    st_group(buf + o, i, P4, rem, c[u]);
+                    add_comp(acc.x, cmp.x, a[u].x); add_comp(acc.y, cmp.y, a[u].y);
+                    add_comp(acc.z, cmp.z, a[u].z); add_comp(acc.w, cmp.w, a[u].w);
+                }
         }
-        theta[o] = a; m[o] = c;
+        const float4 mean = make_float4((acc.x + cmp.x) / fK, (acc.y + cmp.y) / fK,
+                                        (acc.z + cmp.z) / fK, (acc.w + cmp.w) / fK);
+        for (int k = 0; k < K; ++k) st_group(theta + (long long)k * P, i, P4, rem, mean);
     }
 }
 
@@ -363,12 +367,7 @@ hipError_t launch_update_adamw_sync(float *theta, const float *g, float *m, floa
                                     const DevState *st, const StepScalars *sc, float c1, float c2,
                                     float eps, const float *row_coef, hipStream_t s)
 {
-    if ((P & 3) == 0)
-        update_adamw_sync_kernel<<<sync_grid(P / 4), SYNC_THREADS, 0, s>>>(
-            (float4 *)theta, (const float4 *)g, (float4 *)m, (float4 *)v, K, P / 4, st, sc, c1, c2, eps, row_coef);
-    else
-        update_sync_scalar_kernel<<<sync_grid(P), SYNC_THREADS, 0, s>>>(theta, g, m, v, K, P, st, sc, c1, c2, eps,
-                                                                        row_coef);
+    update_adamw_sync_kernel<<<sync_grid((P + 3) / 4), SYNC_THREADS, 0, s>>>(theta, g, m, v, K, P, st, sc, c1, c2, eps, row_coef);
     return hipGetLastError();
 }
 
@@ -376,57 +375,55 @@ hipError_t launch_update_sgdm_sync(float *theta, const float *g, float *buf, int
                                    const DevState *st, const StepScalars *sc, float mu, float lambda,
                                    const float *row_coef, hipStream_t s)
 {
-    if ((P & 3) == 0)
-        update_sgdm_sync_kernel<<<sync_grid(P / 4), SYNC_THREADS, 0, s>>>(
-            (float4 *)theta, (const float4 *)g, (float4 *)buf, K, P / 4, st, sc, mu, lambda, row_coef);
-    else
-        update_sync_scalar_kernel<<<sync_grid(P), SYNC_THREADS, 0, s>>>(theta, g, buf, nullptr, K, P, st, sc, mu,
-                                                                        lambda, 0.f, row_coef);
+    update_sgdm_sync_kernel<<<sync_grid((P + 3) / 4), SYNC_THREADS, 0, s>>>(theta, g, buf, K, P, st, sc, mu, lambda, row_coef);
     return hipGetLastError();
 }
 
-// row_coef != nullptr: clipped update, one grid row per worker
+// row_coef != nullptr: clipped update.  shared_g: all rows of g are the same (rows of whole float4 only:
+// anything else reads its own row, with the same result).
 hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K, long long P,
                                const DevState *st, const StepScalars *sc, float c1, float c2,
-                               float eps, bool fused_sync, const float *row_coef, hipStream_t s, DevState *st_next,
-                               const SchedParams *sp)
+                               float eps, bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s,
+                               DevState *st_next, const SchedParams *sp)
 {
     const SchedParams spv = sp ? *sp : SchedParams{};
     const int fs = fused_sync ? 1 : 0;
     const NoiseDraw none{0.f, 0, 0};
-    if (row_coef == nullptr) {
-        const long long n = (long long)K * P, n4 = n / 4;
-        update_adamw_kernel<false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
-            (float4 *)theta, (float4 *)g, (float4 *)m, (float4 *)v, n4, n, st, sc, c1, c2, eps, fs, nullptr, none, st_next, spv);
-    } else if ((P & 3) == 0) {
-        update_adamw_kernel<true, false><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
-            (float4 *)theta, (float4 *)g, (float4 *)m, (float4 *)v, P / 4, P, st, sc, c1, c2, eps, fs, row_coef, none, st_next, spv);
-    } else {
-        update_clip_scalar_kernel<<<dim3((unsigned)sync_grid(P), (unsigned)K), SYNC_THREADS, 0, s>>>(
-            theta, g, m, v, P, st, sc, c1, c2, eps, fs, row_coef);
-    }
+    const RowMap rm{P, K, 1.0 / (double)P};
+    const long long n = (long long)K * P, n4 = n / 4;
+    float4 *th4 = (float4 *)theta, *g4 = (float4 *)g, *m4 = (float4 *)m, *v4 = (float4 *)v;
+    if (shared_g && (P & 3) == 0)
+        update_adamw_kernel<false, false, true><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
+            th4, g4, m4, v4, P / 4, P, st, sc, c1, c2, eps, fs, row_coef, rm, none, st_next, spv);
+    else if (row_coef != nullptr)
+        update_adamw_kernel<true, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
+            th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, row_coef, rm, none, st_next, spv);
+    else
+        update_adamw_kernel<false, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
+            th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, nullptr, rm, none, st_next, spv);
     return hipGetLastError();
 }
 
 hipError_t launch_update_sgdm(float *theta, float *g, float *buf, int K, long long P,
                               const DevState *st, const StepScalars *sc, float mu, float lambda,
-                              bool fused_sync, const float *row_coef, hipStream_t s, DevState *st_next,
+                              bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s, DevState *st_next,
                               const SchedParams *sp)
 {
     const SchedParams spv = sp ? *sp : SchedParams{};
     const int fs = fused_sync ? 1 : 0;
     const NoiseDraw none{0.f, 0, 0};
-    if (row_coef == nullptr) {
-        const long long n = (long long)K * P, n4 = n / 4;
-        update_sgdm_kernel<false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
-            (float4 *)theta, (float4 *)g, (float4 *)buf, n4, n, st, sc, mu, lambda, fs, nullptr, none, st_next, spv);
-    } else if ((P & 3) == 0) {
-        update_sgdm_kernel<true, false><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
-            (float4 *)theta, (float4 *)g, (float4 *)buf, P / 4, P, st, sc, mu, lambda, fs, row_coef, none, st_next, spv);
-    } else {
-        update_clip_scalar_kernel<<<dim3((unsigned)sync_grid(P), (unsigned)K), SYNC_THREADS, 0, s>>>(
-            theta, g, buf, nullptr, P, st, sc, mu, lambda, 0.f, fs, row_coef);
-    }
+    const RowMap rm{P, K, 1.0 / (double)P};
+    const long long n = (long long)K * P, n4 = n / 4;
+    float4 *th4 = (float4 *)theta, *g4 = (float4 *)g, *b4 = (float4 *)buf;
+    if (shared_g && (P & 3) == 0)
+        update_sgdm_kernel<false, false, true><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
+            th4, g4, b4, P / 4, P, st, sc, mu, lambda, fs, row_coef, rm, none, st_next, spv);
+    else if (row_coef != nullptr)
+        update_sgdm_kernel<true, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
+            th4, g4, b4, n4, n, st, sc, mu, lambda, fs, row_coef, rm, none, st_next, spv);
+    else
+        update_sgdm_kernel<false, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
+            th4, g4, b4, n4, n, st, sc, mu, lambda, fs, nullptr, rm, none, st_next, spv);
     return hipGetLastError();
 }
 
@@ -438,8 +435,8 @@ hipError_t launch_update_adamw_noise(float *theta, float *g, float *m, float *v,
 {
     if ((P & 3) != 0) return hipErrorInvalidValue;
     const SchedParams spv = sp ? *sp : SchedParams{};
-    update_adamw_kernel<false, true><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
-        (float4 *)theta, (float4 *)g, (float4 *)m, (float4 *)v, P / 4, P, st, sc, c1, c2, eps, 0, nullptr,
+    update_adamw_kernel<false, true, false><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
+        (float4 *)theta, (float4 *)g, (float4 *)m, (float4 *)v, P / 4, P, st, sc, c1, c2, eps, 0, nullptr, RowMap{P, K, 0.0},
         NoiseDraw{sigma, seed, store_g ? 1 : 0}, st_next, spv);
     return hipGetLastError();
 }
@@ -450,8 +447,8 @@ hipError_t launch_update_sgdm_noise(float *theta, float *g, float *buf, int K, l
 {
     if ((P & 3) != 0) return hipErrorInvalidValue;
     const SchedParams spv = sp ? *sp : SchedParams{};
-    update_sgdm_kernel<false, true><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
-        (float4 *)theta, (float4 *)g, (float4 *)buf, P / 4, P, st, sc, mu, lambda, 0, nullptr,
+    update_sgdm_kernel<false, true, false><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
+        (float4 *)theta, (float4 *)g, (float4 *)buf, P / 4, P, st, sc, mu, lambda, 0, nullptr, RowMap{P, K, 0.0},
         NoiseDraw{sigma, seed, store_g ? 1 : 0}, st_next, spv);
     return hipGetLastError();
 }

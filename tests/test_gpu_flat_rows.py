@@ -1,0 +1,60 @@
+"""GPU: rows of any length and alignment through the kernels that treat the [K][P] buffers as one vector or in
+groups of four columns (averaging, clipped and fused updates, gradient fill), against the oracle; Parallel OPT's
+update of a shared gradient row."""
+import numpy as np
+import pytest
+
+import workloads
+from test_gpu_parity import test_average_rows as average_rows_case
+from test_gpu_parity import test_gradient_clipping as clipping_case
+from util import assert_mirror_matches_device, assert_params_close, gpu_ctx, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+
+# one, two and three columns beyond the last group of four; each tile's largest K and the first beyond it
+@pytest.mark.parametrize("K,P", [(16, 257), (17, 258), (32, 1027), (33, 259), (64, 1030), (65, 515), (3, 2), (64, 4096)])
+def test_averaging_of_unaligned_rows(K, P):
+    average_rows_case(K, P)
+
+
+# rows shorter than, as long as and longer than the 512 elements a workgroup takes at a time
+@pytest.mark.parametrize("opt", ["adamw", "sgdm"])
+@pytest.mark.parametrize("K,P,extra", [(7, 3, {}), (6, 130, {}), (3, 511, {}), (5, 513, {}), (4, 1026, dict(fuse_sync=True)),
+                                       (5, 1001, dict(parallel=True, H_base=1, power=0, alpha=0.0)),
+                                       (3, 400003, {}), (3, 400002, dict(parallel=True, H_base=1, power=0, alpha=0.0)),
+                                       (3, 400004, dict(parallel=True, H_base=1, power=0, alpha=0.0))])
+def test_clipped_updates_of_any_row_length(opt, K, P, extra):
+    clipping_case(opt, K, P, extra)
+
+
+@pytest.mark.parametrize("P", [20001, 20002, 20003])
+def test_gradient_fill_of_unaligned_rows(P):
+    """The separately filled gradient of rows that start off the 16-byte grid equals the aligned rows' draw."""
+    w = workloads.get("flat60m", K=3, P=P, T=8)
+    ctx = gpu_ctx(w)
+    ref = gpu_ctx(dict(w, P=20004))
+    ctx.local_step(); ref.local_step()
+    assert np.array_equal(ctx.grads.cpu().numpy(), ref.grads.cpu().numpy()[:, :P])
+    ctx.close(); ref.close()
+
+
+@pytest.mark.parametrize("P", [1 << 18, (1 << 18) + 2, 4096])
+def test_parallel_opt_state_between_the_calls(P):
+    """Whether or not the update has closed the round already, the step counts after qsr_local_step and the round
+    closes in qsr_maybe_sync; results and log follow the oracle."""
+    w = workloads.get("flat60m", K=4, P=P, T=12, H_base=1, alpha=0.0, power=0, parallel=True, opt="sgdm", mu=0.9, eta_max=0.1)
+    ctx, orc = gpu_ctx(w), oracle_run(w)
+    for t in range(1, 12):
+        ctx.local_step()
+        assert ctx.get_state() == (t, t - 1, 1, 1)
+        assert len(ctx.read_sync_log()[0]) == t - 1
+        ctx.maybe_sync()
+        assert ctx.get_state() == (t, t, 0, 1)
+    ctx.step()
+    assert ctx.get_state() == (12, 12, 0, 0)
+    orc.step(12)
+    assert_params_close(ctx.params.cpu().numpy(), orc.theta, what="parallel")
+    assert list(ctx.read_sync_log()[0]) == list(orc.sync_log)
+    assert_mirror_matches_device(ctx)
+    ctx.close()
