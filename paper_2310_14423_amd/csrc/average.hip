@@ -27,7 +27,6 @@
 // returns that row when K is a power of two.
 #include "opt_elem.h"
 #include "qsr_internal.h"
-#include "sched_dev.h"
 
 namespace qsr {
 
@@ -93,28 +92,12 @@ __device__ __forceinline__ void average_tile_body(float *__restrict__ buf, int K
     }
 }
 
-// ADVANCE: the launch also closes the iteration.  Every workgroup reads the scheduler state when it
-// starts and takes a ticket when it is done; the one that draws the last ticket knows that all
-// others have read the state, and advances it.
-template <int KMAX, int W, int RUN, bool ADVANCE>
-__global__ __launch_bounds__(64 * W) void average_rows_tile_kernel(
-    float *__restrict__ buf, int K, long long P, const DevState *st, DevState *st_adv, SchedParams sp)
+template <int KMAX, int W, int RUN>
+__global__ __launch_bounds__(64 * W) void average_rows_tile_kernel(float *__restrict__ buf, int K, long long P,
+                                                                   const DevState *__restrict__ st)
 {
     extern __shared__ float4 avg_tile[];            // [K][RUN * 64]
-    const bool act = st == nullptr || st->h + 1 == st->H;   // the step that completes a round
-    if (ADVANCE) {
-        if (act) average_tile_body<KMAX, W, RUN>(buf, K, P, avg_tile);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            __threadfence();
-            if (atomicAdd(&st_adv->ticket, 1u) == gridDim.x - 1) {
-                st_adv->ticket = 0;
-                sched_advance(st_adv, sp, -1);
-            }
-        }
-        return;
-    }
-    if (!act) return;
+    if (st != nullptr && st->h + 1 != st->H) return;        // not the step that completes a round
     average_tile_body<KMAX, W, RUN>(buf, K, P, avg_tile);
 }
 
@@ -157,46 +140,32 @@ static int avg_grid(long long items, int threads)
     return (int)blocks;
 }
 
-template <int KMAX, int W, int RUN, bool ADVANCE>
-static hipError_t launch_tile(float *buf, int K, long long P, const DevState *st, DevState *st_adv, SchedParams sp,
-                              hipStream_t s)
+template <int KMAX, int W, int RUN>
+static hipError_t launch_tile(float *buf, int K, long long P, const DevState *st, hipStream_t s)
 {
     const size_t lds = (size_t)K * RUN * 64 * sizeof(float4);
     static bool raised = false;                       // above the default only for more than 48 rows of 1 KiB
     if (lds > 48 * 1024 && !raised) {
-        hipError_t e = hipFuncSetAttribute((const void *)average_rows_tile_kernel<KMAX, W, RUN, ADVANCE>,
+        hipError_t e = hipFuncSetAttribute((const void *)average_rows_tile_kernel<KMAX, W, RUN>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, KMAX * RUN * 64 * (int)sizeof(float4));
         if (e != hipSuccess) return e;
         raised = true;
     }
-    average_rows_tile_kernel<KMAX, W, RUN, ADVANCE><<<avg_grid((P + 3) / 4, RUN * 64), 64 * W, lds, s>>>(buf, K, P, st, st_adv, sp);
+    average_rows_tile_kernel<KMAX, W, RUN><<<avg_grid((P + 3) / 4, RUN * 64), 64 * W, lds, s>>>(buf, K, P, st);
     return hipGetLastError();
 }
 
-// st != nullptr: the launch acts only on the step that completes a round (h + 1 == H in the device's
-// scheduler state, read before the scheduler advances)
+// st != nullptr: the launch acts only on the step that completes a round (h + 1 == H in the copy of the scheduler
+// state that the iteration's kernels read)
 hipError_t launch_average_rows(float *buf, int K, long long P, const DevState *st, hipStream_t s)
 {
     const long long C4 = (P + 3) / 4;
     if (C4 > 0x7FFFFFFFll * 64) return hipErrorInvalidValue;
-    if (K <= 16) return launch_tile<16, 2, 1, false>(buf, K, P, st, nullptr, SchedParams{}, s);
-    if (K <= 32) return launch_tile<32, 2, 2, false>(buf, K, P, st, nullptr, SchedParams{}, s);
-    if (K <= 64) return launch_tile<64, 8, 1, false>(buf, K, P, st, nullptr, SchedParams{}, s);
+    if (K <= 16) return launch_tile<16, 2, 1>(buf, K, P, st, s);
+    if (K <= 32) return launch_tile<32, 2, 2>(buf, K, P, st, s);
+    if (K <= 64) return launch_tile<64, 8, 1>(buf, K, P, st, s);
     average_rows_vec4_kernel<<<avg_grid(C4, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
     return hipGetLastError();
-}
-
-// few workgroups (a ticket each), rows that the tile kernel takes
-bool average_can_advance(int K, long long P)
-{
-    return K <= 32 && (P + 3) / 4 <= 64 * 64;
-}
-
-hipError_t launch_average_rows_advance(float *buf, int K, long long P, DevState *st, SchedParams sp, hipStream_t s)
-{
-    if (!average_can_advance(K, P)) return hipErrorInvalidValue;
-    if (K <= 16) return launch_tile<16, 2, 1, true>(buf, K, P, st, st, sp, s);
-    return launch_tile<32, 2, 2, true>(buf, K, P, st, st, sp, s);
 }
 
 // Alg. 2's initialisation theta_k <- theta_bar^(0): copy src [P] into each of the K rows

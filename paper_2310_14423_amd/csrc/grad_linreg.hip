@@ -1,14 +1,21 @@
 // grad_linreg.hip -- local gradient (Eq. (1) of arXiv 2310.14423) of the linear least-squares
 // workload for all K workers: loss_k = 1/(2B) sum_i (x_i.w_k - y_i)^2 with fresh Gaussian
 // inputs x_i and targets y_i = x_i.w* + sigma*noise per (worker, iteration).
-//   1. X[k] <- N(0,1)                              (Philox, stream X: drawn by the kernel of step 2
-//      itself when rows are whole groups of four draws, else by the bulk fill kernel)
+//   1. X[k] <- N(0,1)                              (Philox, stream X, drawn by the kernel of step 2)
 //   2. r[k][i] = x_i.(w_k - w*) - sigma*eps_i      (one block per sample; the two inner
 //      products are taken as one, which avoids cancellation when w_k is close to w*)
 //   3. g[k][j] = (1/B) sum_i r[k][i] X[k][i][j];  loss[k] = 1/(2B) sum_i r^2
-// The problem is tiny (K*B*d = 131072 inputs at the benchmark size): latency-bound, kept simple.
+// The problem is tiny (K*B*d = 131072 inputs at the benchmark size): what counts is the number of
+// launches in the dependent chain (2 to 4 us each) and of memory latencies inside them.  Every
+// inner product needs all of w_k and every gradient entry all residuals, so two kernels per iteration
+// are the least without a barrier across the grid; step 3's kernel therefore also takes the OPT update
+// of its columns, which it holds for all workers, and in a recorded iteration the averaging and
+// the scheduler's step.  256 iterations of 4 x 1024 features x 32 samples: 2879 us with four
+// kernels per iteration (residuals, gradient, update, averaging).
+#include "opt_elem.h"
 #include "philox.h"
 #include "qsr_internal.h"
+#include "sched_dev.h"
 
 namespace qsr {
 
@@ -24,39 +31,133 @@ __device__ __forceinline__ float block_sum_256(float v, float *red)
     return s;
 }
 
-// DRAW: the sample's inputs are drawn here (d a multiple of 4: the row is d/4 whole groups of the
-// generator, the same counters and arithmetic as the fill kernel) and written to X for step 3.
-template <bool DRAW>
-__global__ __launch_bounds__(256) void linreg_residual_kernel(
+// One workgroup per sample.  Wavefronts 0-3 draw the sample's inputs (whole groups of the generator,
+// the same counters as a bulk fill of the flat [B][d] array: where d is not a multiple of 4 a row
+// starts or ends inside a group, which the neighbouring row's workgroup draws too), store them for
+// step 3 and take the inner product; wavefront 4 draws the observation noise meanwhile.
+__global__ __launch_bounds__(320) void linreg_residual_kernel(
     float *__restrict__ X, const float *__restrict__ theta, const float *__restrict__ wstar,
     float *__restrict__ r, long long B, long long d, float sigma, uint64_t seed,
     const DevState *__restrict__ st)
 {
-    __shared__ float red[4];
-    const int k = blockIdx.y;
+    __shared__ float red[5];
+    const int k = blockIdx.y, tid = threadIdx.x, wave = tid >> 6;
     const long long i = blockIdx.x;
-    float *x = X + ((long long)k * B + i) * d;
-    const float *w = theta + (long long)k * d;
+    const uint32_t t = (uint32_t)st->t;
     float acc = 0.f;
-    if (DRAW) {
-        const uint32_t t = (uint32_t)st->t;
-        const long long q0 = i * (d >> 2);                       // first group of this row
-        for (long long q = threadIdx.x; q < (d >> 2); q += 256) {
-            const float4 z = normal4(seed, STREAM_X, (uint32_t)k, t, (uint32_t)(q0 + q));
-            const long long j = q * 4;
-            *(float4 *)(x + j) = z;
-            const float4 wv = *(const float4 *)(w + j), ws = *(const float4 *)(wstar + j);
-            acc = fmaf(z.x, wv.x - ws.x, acc); acc = fmaf(z.y, wv.y - ws.y, acc);
-            acc = fmaf(z.z, wv.z - ws.z, acc); acc = fmaf(z.w, wv.w - ws.w, acc);
+    if (wave < 4) {
+        float *x = X + ((long long)k * B + i) * d;
+        const float *w = theta + (long long)k * d;
+        if ((d & 3) == 0) {
+            for (long long q = tid; q < (d >> 2); q += 256) {
+                const float4 wv = *(const float4 *)(w + q * 4), ws = *(const float4 *)(wstar + q * 4);
+                const float4 z = normal4(seed, STREAM_X, (uint32_t)k, t, (uint32_t)(i * (d >> 2) + q));
+                *(float4 *)(x + q * 4) = z;
+                acc = fmaf(z.x, wv.x - ws.x, acc); acc = fmaf(z.y, wv.y - ws.y, acc);
+                acc = fmaf(z.z, wv.z - ws.z, acc); acc = fmaf(z.w, wv.w - ws.w, acc);
+            }
+        } else {
+            const long long f0 = i * d, q0 = f0 >> 2, nq = ((f0 + d + 3) >> 2) - q0;
+            for (long long q = tid; q < nq; q += 256) {
+                const long long j0 = (q0 + q) * 4 - f0;          // column of the group's first element
+                float dw[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const long long j = j0 + e;
+                    dw[e] = j >= 0 && j < d ? w[j] - wstar[j] : 0.f;
+                }
+                const float4 z4 = normal4(seed, STREAM_X, (uint32_t)k, t, (uint32_t)(q0 + q));
+                const float z[4] = {z4.x, z4.y, z4.z, z4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const long long j = j0 + e;
+                    if (j >= 0 && j < d) { x[j] = z[e]; acc = fmaf(z[e], dw[e], acc); }
+                }
+            }
         }
-    } else {
-        for (long long j = threadIdx.x; j < d; j += 256) acc = fmaf(x[j], w[j] - wstar[j], acc);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+        if ((tid & 63) == 0) red[wave] = acc;
+    } else if (tid == 256) {
+        const float4 z = normal4(seed, STREAM_NOISE, (uint32_t)k, t, (uint32_t)(i >> 2));
+        red[4] = (i & 3) == 0 ? z.x : (i & 3) == 1 ? z.y : (i & 3) == 2 ? z.z : z.w;
     }
-    float dot = block_sum_256(acc, red);
-    if (threadIdx.x == 0) {
-        float4 z = normal4(seed, STREAM_NOISE, (uint32_t)k, (uint32_t)st->t, (uint32_t)(i >> 2));
-        float e = (i & 3) == 0 ? z.x : (i & 3) == 1 ? z.y : (i & 3) == 2 ? z.z : z.w;
-        r[(long long)k * B + i] = dot - sigma * e;
+    __syncthreads();
+    if (tid == 0) r[(long long)k * B + i] = (red[0] + red[1] + red[2] + red[3]) - sigma * red[4];
+}
+
+// Step 3 with the OPT update, one workgroup per 64 columns of all K workers: K * S wavefronts, each on a
+// worker's columns and every S-th run of samples (S = 16 / K: all loads of the benchmark size's 32
+// samples are in flight at once); the S partial sums are added in order through LDS by the worker's first
+// wavefront, which updates its columns.  average: the launch also averages, if the device's scheduler
+// says that a round ends, with the averaging kernel's arithmetic.  st_next as in the update kernels.
+struct LinregStep {
+    float *theta, *g, *s0, *s1;          // s1: AdamW
+    const StepScalars *sc;
+    float c1, c2, eps;                   // SGD: c1 = mu, c2 = lambda
+};
+template <bool ADAMW>
+__global__ __launch_bounds__(1024) void linreg_grad_update_kernel(
+    const float *__restrict__ X, const float *__restrict__ r, LinregStep p, float *__restrict__ loss, int K, int S,
+    long long B, long long d, const DevState *__restrict__ st, DevState *__restrict__ st_next, int average, SchedParams sp)
+{
+    __shared__ float part[16][64];
+    __shared__ float upd[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = wave / S, s = wave - k * S;
+    const long long j = (long long)blockIdx.x * 64 + lane;
+    const bool in = j < d;
+    // the last thread of the last workgroup, which has no column of its own where the others are busiest
+    if (st_next != nullptr && blockIdx.x == gridDim.x - 1 && threadIdx.x == blockDim.x - 1) tick_into(st, st_next, sp);
+    const bool sync = average != 0 && st->h + 1 == st->H;
+    const StepScalars sc = p.sc[st->t];
+    const long long o = (long long)k * d + j;
+    float th = 0.f, m = 0.f, v = 0.f;
+    if (s == 0 && in) {
+        th = p.theta[o]; m = p.s0[o];
+        if (ADAMW) v = p.s1[o];
+    }
+    const float *Xk = X + (long long)k * B * d + j;
+    const float *rk = r + (long long)k * B;
+    float acc = 0.f;
+    if (in) {
+        const long long per = (B + S - 1) / S, i0 = s * per, i1 = min(B, i0 + per);
+        for (long long i = i0; i < i1; i += 8) {         // a short last run is filled up with weight 0
+            float xv[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) xv[u] = Xk[min(i + u, i1 - 1) * d];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc = fmaf(i + u < i1 ? rk[i + u] : 0.f, xv[u], acc);
+        }
+    }
+    part[wave][lane] = acc;
+    if (blockIdx.x == 0 && s == 0) {
+        float a = 0.f;
+        for (long long i = lane; i < B; i += 64) a = fmaf(rk[i], rk[i], a);
+#pragma unroll
+        for (int q = 32; q > 0; q >>= 1) a += __shfl_down(a, q, 64);
+        if (lane == 0) loss[k] = 0.5f * a / (float)B;
+    }
+    __syncthreads();
+    if (s == 0) {
+        float gj = part[wave][lane];
+        for (int q = 1; q < S; ++q) gj += part[wave + q][lane];
+        gj *= 1.0f / (float)B;
+        if (ADAMW) adamw_elem(th, gj, m, v, sc.x, sc.y, sc.z, p.c1, p.c2, p.eps);
+        else sgdm_elem(th, gj, m, sc.x, p.c1, p.c2);
+        upd[k][lane] = th;
+        if (in) {
+            p.g[o] = gj; p.s0[o] = m;
+            if (ADAMW) p.s1[o] = v;
+            if (!sync) p.theta[o] = th;
+        }
+    }
+    if (!sync) return;                                   // the same for the whole launch
+    __syncthreads();
+    if (s == 0 && in) {
+        float a = 0.f, c = 0.f;
+        for (int q = 0; q < K; ++q) add_comp(a, c, upd[q][lane]);
+        p.theta[o] = (a + c) / (float)K;
     }
 }
 
@@ -100,26 +201,52 @@ size_t linreg_workspace_bytes(const ModelDims &d)
     return ((x + 255) & ~(size_t)255) + ((r + 255) & ~(size_t)255);
 }
 
+static float *linreg_r(const ModelDims &d, void *ws)
+{
+    size_t xb = ((size_t)d.K * d.B * d.d_in * sizeof(float) + 255) & ~(size_t)255;
+    return (float *)((char *)ws + xb);
+}
+
+static hipError_t launch_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
+                                  const DevState *st, hipStream_t s)
+{
+    linreg_residual_kernel<<<dim3((unsigned)d.B, (unsigned)d.K), 320, 0, s>>>(
+        (float *)ws, theta, wstar, linreg_r(d, ws), d.B, d.d_in, d.data_sigma, d.seed, st);
+    return hipGetLastError();
+}
+
 hipError_t launch_linreg_grad(const ModelDims &d, const float *theta, float *g, const float *wstar,
                               void *ws, float *loss, const DevState *st, hipStream_t s)
 {
-    float *X = (float *)ws;
-    size_t xb = ((size_t)d.K * d.B * d.d_in * sizeof(float) + 255) & ~(size_t)255;
-    float *r = (float *)((char *)ws + xb);
-    hipError_t e;
-    if ((d.d_in & 3) == 0) {
-        linreg_residual_kernel<true><<<dim3((unsigned)d.B, (unsigned)d.K), 256, 0, s>>>(
-            X, theta, wstar, r, d.B, d.d_in, d.data_sigma, d.seed, st);
-    } else {
-        e = launch_fill_normal(X, d.B * d.d_in, d.K, d.B * d.d_in, 1.0f, STREAM_X, d.seed, st, s);
-        if (e != hipSuccess) return e;
-        linreg_residual_kernel<false><<<dim3((unsigned)d.B, (unsigned)d.K), 256, 0, s>>>(
-            X, theta, wstar, r, d.B, d.d_in, d.data_sigma, d.seed, st);
-    }
-    e = hipGetLastError();
+    hipError_t e = launch_residual(d, theta, wstar, ws, st, s);
     if (e != hipSuccess) return e;
     linreg_grad_kernel<<<dim3((unsigned)((d.d_in + 255) / 256), (unsigned)d.K), 256, 0, s>>>(
-        X, r, g, loss, d.B, d.d_in);
+        (const float *)ws, linreg_r(d, ws), g, loss, d.B, d.d_in);
+    return hipGetLastError();
+}
+
+bool linreg_can_fuse(const ModelDims &d) { return d.K <= 16; }   // a wavefront per worker in a workgroup
+
+hipError_t launch_linreg_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
+                                  const DevState *st, hipStream_t s)
+{
+    return launch_residual(d, theta, wstar, ws, st, s);
+}
+
+hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g, float *s0, float *s1, void *ws,
+                                     float *loss, const StepScalars *sc, float c1, float c2, float eps,
+                                     const DevState *st, DevState *st_next, bool average, const SchedParams &sp,
+                                     hipStream_t s)
+{
+    if (!linreg_can_fuse(d)) return hipErrorInvalidValue;
+    const int S = 16 / d.K;
+    const LinregStep p{theta, g, s0, s1, sc, c1, c2, eps};
+    const dim3 grid((unsigned)((d.d_in + 63) / 64));
+    const int threads = d.K * S * 64;
+    if (s1) linreg_grad_update_kernel<true><<<grid, threads, 0, s>>>((const float *)ws, linreg_r(d, ws), p, loss, d.K, S,
+                                                                     d.B, d.d_in, st, st_next, average ? 1 : 0, sp);
+    else linreg_grad_update_kernel<false><<<grid, threads, 0, s>>>((const float *)ws, linreg_r(d, ws), p, loss, d.K, S,
+                                                                   d.B, d.d_in, st, st_next, average ? 1 : 0, sp);
     return hipGetLastError();
 }
 

@@ -39,10 +39,11 @@ struct qsr_ctx {
     void *workspace;
     size_t workspace_bytes;
     // library-owned device memory
-    DevState *d_state;       // two copies; `cur` is the one this iteration's kernels read (see fold_tick)
+    DevState *d_state;       // two copies; `cur` is the one the next kernels read (see ticked)
     int cur;
-    bool fold_tick;          // the update kernel takes the scheduler's step on iterations that end no round
-    bool ticked;             // ... and has done so for the local step whose qsr_maybe_sync is pending
+    bool ticked;             // the update kernel has advanced the scheduler (into the copy that is current now) for
+                             // the local step whose qsr_maybe_sync is pending
+    bool fuse_linreg;        // least squares: the gradient kernel takes the update of its columns too
     double *d_eta;
     StepScalars *d_scal;
     long long *d_log_t, *d_log_H;
@@ -71,6 +72,7 @@ struct qsr_ctx {
     // replay: the launches of graph_iters iterations, captured once (qsr_run)
     hipGraphExec_t graph_exec;
     int graph_iters;
+    int graph_cur;           // the copy of the scheduler state the recorded launches begin and end on
 };
 
 static inline DevState *st_cur(qsr_ctx *c) { return c->d_state + c->cur; }
@@ -440,12 +442,13 @@ extern "C" int qsr_init(const qsr_config *cfg, float *params, float *grads, floa
     // launched only where the mirror says a round ends, while a graph has to hold a launch in every
     // iteration for the device to skip (7 us per iteration for the perceptron's 814 090 parameters).
     c->graph_iters = (cfg->model == QSR_MODEL_RESMLP || (long long)cfg->K * cfg->P >= (1ll << 20)) ? 0 : 8;
-    // Contexts whose iterations are never replayed from a graph (a recorded launch could not be handed the
-    // copy of the scheduler state that alternates from iteration to iteration): the update kernel takes
-    // the scheduler's step on the iterations that end no round, and no scheduler kernel is launched there.
-    c->cur = 0; c->ticked = false;
-    c->fold_tick = c->graph_iters == 0 && (!cfg->parallel || (cfg->P & 3) == 0);
+    // The update kernel takes the scheduler's step into the other copy of the state, so that an iteration needs no
+    // scheduler kernel.  Recorded iterations alternate between the copies too: a graph holds an even number
+    // of them and is replayed from the copy it was recorded on.
+    c->cur = 0; c->ticked = false; c->graph_cur = 0;
     c->dims = make_dims(cfg);
+    c->fuse_linreg = cfg->model == QSR_MODEL_LINREG && linreg_can_fuse(c->dims) && !cfg->parallel && !cfg->fuse_sync &&
+                     !cfg->average_state && cfg->clip_norm <= 0.0;
     rc = init_impl(c, theta0);
     c->cfg.milestones = nullptr;
     c->cfg.eta_table = nullptr;
@@ -508,8 +511,11 @@ extern "C" int qsr_local_step(qsr_ctx *c)
                                       st_cur(c), c->stream));
             break;
         case QSR_MODEL_LINREG:
-            HIP_TRY(launch_linreg_grad(c->dims, c->params, c->grads, c->model_const, c->workspace,
-                                       c->d_loss, st_cur(c), c->stream));
+            if (c->fuse_linreg)
+                HIP_TRY(launch_linreg_residual(c->dims, c->params, c->model_const, c->workspace, st_cur(c), c->stream));
+            else
+                HIP_TRY(launch_linreg_grad(c->dims, c->params, c->grads, c->model_const, c->workspace,
+                                           c->d_loss, st_cur(c), c->stream));
             break;
         case QSR_MODEL_MLP2:
             HIP_TRY(launch_mlp2_grad(c->dims, c->params, c->grads, c->model_const, c->workspace,
@@ -536,35 +542,44 @@ extern "C" int qsr_local_step(qsr_ctx *c)
     const bool all = c->capturing;
     const bool sync_now = mirror_sync_now(c);
     const bool fused = cfg.fuse_sync != 0;
-    // With Parallel OPT every step ends a round and nothing averages parameters behind the update.
-    const bool shared_g = cfg.parallel != 0 && (cfg.P & 3) == 0;
-    DevState *st_next = (c->fold_tick && !all && (!sync_now || shared_g)) ? c->d_state + (c->cur ^ 1) : nullptr;
+    const bool shared_g = cfg.parallel != 0;            // all rows of the gradient are the mean now
+    const DevState *st = st_cur(c);                     // what every kernel of this iteration reads
+    SchedParams sp = c->sp;
+    sp.expect_sync = all ? -1 : (sync_now ? 1 : 0);
     if (!fused || all || !sync_now) {                   // OPT for all K workers at once
         Bracket br(c, 1);
         if (br.rc != QSR_OK) return br.rc;
+        DevState *st_next = c->d_state + (c->cur ^ 1);
         if (cfg.clip_norm > 0.0)                        // App. C: per-worker factors min(1, c / (||g_k|| + 1e-6))
             HIP_TRY(launch_clip_coef(c->grads, cfg.K, cfg.P, (float)cfg.clip_norm, c->d_clip_part,
                                      c->d_clip_coef, c->d_clip_coef + cfg.K, c->stream, cfg.parallel != 0));
-        if (cfg.fuse_gradient && cfg.opt == QSR_OPT_SGDM)   // Eq. (1) and OPT in one pass (noise model)
-            HIP_TRY(launch_update_sgdm_noise(c->params, c->grads, c->state0, cfg.K, cfg.P, st_cur(c), c->d_scal,
+        if (c->fuse_linreg) {                           // the rest of the gradient, and OPT, in one pass
+            const bool sgd = cfg.opt == QSR_OPT_SGDM;
+            HIP_TRY(launch_linreg_grad_update(c->dims, c->params, c->grads, c->state0, sgd ? nullptr : c->state1,
+                                              c->workspace, c->d_loss, c->d_scal,
+                                              (float)(sgd ? cfg.momentum : 1.0 - cfg.beta1),
+                                              (float)(sgd ? cfg.weight_decay : 1.0 - cfg.beta2), (float)cfg.eps,
+                                              st, st_next, all, sp, c->stream));
+        } else if (cfg.fuse_gradient && cfg.opt == QSR_OPT_SGDM)   // Eq. (1) and OPT in one pass (noise model)
+            HIP_TRY(launch_update_sgdm_noise(c->params, c->grads, c->state0, cfg.K, cfg.P, st, c->d_scal,
                                              (float)cfg.momentum, (float)cfg.weight_decay, (float)cfg.grad_sigma,
-                                             cfg.seed, cfg.fuse_gradient == 1, c->stream, st_next, &c->sp));
+                                             cfg.seed, cfg.fuse_gradient == 1, c->stream, st_next, &sp));
         else if (cfg.fuse_gradient)
-            HIP_TRY(launch_update_adamw_noise(c->params, c->grads, c->state0, c->state1, cfg.K, cfg.P, st_cur(c),
+            HIP_TRY(launch_update_adamw_noise(c->params, c->grads, c->state0, c->state1, cfg.K, cfg.P, st,
                                               c->d_scal, (float)(1.0 - cfg.beta1), (float)(1.0 - cfg.beta2),
                                               (float)cfg.eps, (float)cfg.grad_sigma, cfg.seed, cfg.fuse_gradient == 1,
-                                              c->stream, st_next, &c->sp));
+                                              c->stream, st_next, &sp));
         else if (cfg.opt == QSR_OPT_SGDM)
-            HIP_TRY(launch_update_sgdm(c->params, c->grads, c->state0, cfg.K, cfg.P, st_cur(c), c->d_scal,
+            HIP_TRY(launch_update_sgdm(c->params, c->grads, c->state0, cfg.K, cfg.P, st, c->d_scal,
                                        (float)cfg.momentum, (float)cfg.weight_decay, fused, c->d_clip_coef,
-                                       shared_g, c->stream, st_next, &c->sp));
+                                       shared_g, c->stream, st_next, &sp));
         else
-            HIP_TRY(launch_update_adamw(c->params, c->grads, c->state0, c->state1, cfg.K, cfg.P, st_cur(c),
+            HIP_TRY(launch_update_adamw(c->params, c->grads, c->state0, c->state1, cfg.K, cfg.P, st,
                                         c->d_scal, (float)(1.0 - cfg.beta1), (float)(1.0 - cfg.beta2),
-                                        (float)cfg.eps, fused, c->d_clip_coef, shared_g, c->stream, st_next, &c->sp));
+                                        (float)cfg.eps, fused, c->d_clip_coef, shared_g, c->stream, st_next, &sp));
         int rc = br.close(c->t_host);
         if (rc != QSR_OK) return rc;
-        if (st_next) { c->cur ^= 1; c->ticked = true; }    // the advanced state is in the other copy now
+        c->cur ^= 1; c->ticked = true;                  // the advanced state is in the other copy now
     }
     if (fused && (all || sync_now)) {                   // the round's last step: OPT and All-Reduce in one pass
         Bracket br(c, 2);                               // timed like an averaging launch
@@ -573,10 +588,10 @@ extern "C" int qsr_local_step(qsr_ctx *c)
             HIP_TRY(launch_clip_coef(c->grads, cfg.K, cfg.P, (float)cfg.clip_norm, c->d_clip_part,
                                      c->d_clip_coef, c->d_clip_coef + cfg.K, c->stream));
         if (cfg.opt == QSR_OPT_SGDM)
-            HIP_TRY(launch_update_sgdm_sync(c->params, c->grads, c->state0, cfg.K, cfg.P, st_cur(c), c->d_scal,
+            HIP_TRY(launch_update_sgdm_sync(c->params, c->grads, c->state0, cfg.K, cfg.P, st, c->d_scal,
                                             (float)cfg.momentum, (float)cfg.weight_decay, c->d_clip_coef, c->stream));
         else
-            HIP_TRY(launch_update_adamw_sync(c->params, c->grads, c->state0, c->state1, cfg.K, cfg.P, st_cur(c),
+            HIP_TRY(launch_update_adamw_sync(c->params, c->grads, c->state0, c->state1, cfg.K, cfg.P, st,
                                              c->d_scal, (float)(1.0 - cfg.beta1), (float)(1.0 - cfg.beta2),
                                              (float)cfg.eps, c->d_clip_coef, c->stream));
         int rc = br.close(c->t_host + 1);
@@ -591,36 +606,29 @@ extern "C" int qsr_maybe_sync(qsr_ctx *c)
 {
     if (!c) return QSR_EINVAL;
     if (!c->need_sync_call) return QSR_ESTATE;
-    if (c->ticked) {                     // no round ends here and the update kernel has advanced the scheduler
-        mirror_advance(c);
-        c->ticked = false;
-        c->need_sync_call = false;
-        return QSR_OK;
-    }
     const bool all = c->capturing;
     const bool sync_now = mirror_sync_now(c);
-    // Replayed iterations of small problems: the averaging launch, which a graph holds in every
-    // iteration, also closes the iteration (one launch less where a launch is a third of the work)
-    if (all && !c->cfg.parallel && !c->cfg.fuse_sync && !c->cfg.average_state && average_can_advance(c->cfg.K, c->cfg.P)) {
-        HIP_TRY(launch_average_rows_advance(c->params, c->cfg.K, c->cfg.P, st_cur(c), c->sp, c->stream));
-        mirror_advance(c);
-        c->need_sync_call = false;
-        return QSR_OK;
-    }
-    // Parallel OPT keeps the workers identical, the fused form has averaged in qsr_local_step already
-    if (!c->cfg.parallel && !c->cfg.fuse_sync && (all || sync_now)) {
+    // the copy of the scheduler state this iteration's kernels read
+    DevState *st = c->d_state + (c->ticked ? c->cur ^ 1 : c->cur);
+    // Parallel OPT keeps the workers identical, the fused forms have averaged in qsr_local_step already
+    if (!c->cfg.parallel && !c->cfg.fuse_sync && (c->fuse_linreg ? !all && sync_now : all || sync_now)) {
         Bracket br(c, 2);
         if (br.rc != QSR_OK) return br.rc;
-        HIP_TRY(launch_average_rows(c->params, c->cfg.K, c->cfg.P, st_cur(c), c->stream));
+        HIP_TRY(launch_average_rows(c->params, c->cfg.K, c->cfg.P, st, c->stream));
         int rc = br.close(c->t_host);
         if (rc != QSR_OK) return rc;
-        if (c->cfg.average_state) {          // same device-side decision, taken before the scheduler advances
-            HIP_TRY(launch_average_rows(c->state0, c->cfg.K, c->cfg.P, st_cur(c), c->stream));
-            if (c->state1) HIP_TRY(launch_average_rows(c->state1, c->cfg.K, c->cfg.P, st_cur(c), c->stream));
+        if (c->cfg.average_state) {          // same device-side decision
+            HIP_TRY(launch_average_rows(c->state0, c->cfg.K, c->cfg.P, st, c->stream));
+            if (c->state1) HIP_TRY(launch_average_rows(c->state1, c->cfg.K, c->cfg.P, st, c->stream));
         }
     }
-    HIP_TRY(launch_sched_advance(st_cur(c), c->sp, all ? -1 : (sync_now ? 1 : 0), c->stream));
+    if (!c->ticked) {                        // the fused update-and-average launch has no scheduler step of its own
+        SchedParams sp = c->sp;
+        sp.expect_sync = sync_now ? 1 : 0;
+        HIP_TRY(launch_sched_advance(st, sp, c->stream));
+    }
     mirror_advance(c);
+    c->ticked = false;
     c->need_sync_call = false;
     return QSR_OK;
 }
@@ -659,18 +667,25 @@ extern "C" int qsr_run(qsr_ctx *c, int64_t n)
             return run_one_by_one(c, n);
         }
         c->capturing = true;
+        c->graph_cur = c->cur;
         rc = run_one_by_one(c, per);
         c->capturing = false;
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(c->stream, &g);
         c->t_host = t_keep;
         c->need_sync_call = false;
+        c->ticked = false;
+        c->cur = c->graph_cur;
         c->m_t = m_keep[0]; c->m_s = m_keep[1]; c->m_h = m_keep[2]; c->m_H = m_keep[3];
         c->m_log_t.resize(log_keep); c->m_log_H.resize(log_keep);
         if (rc == QSR_OK && e == hipSuccess) e = hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0);
         if (g) (void)hipGraphDestroy(g);
         if (rc != QSR_OK) return rc;
         if (e != hipSuccess) { c->graph_exec = nullptr; g_last_hip = (int)e; return QSR_EHIP; }
+    }
+    if (n >= per && c->cur != c->graph_cur) {
+        HIP_TRY(launch_sched_copy(c->d_state + c->graph_cur, st_cur(c), c->stream));
+        c->cur = c->graph_cur;
     }
     while (n >= per) {
         HIP_TRY(hipGraphLaunch(c->graph_exec, c->stream));
@@ -681,19 +696,16 @@ extern "C" int qsr_run(qsr_ctx *c, int64_t n)
     return run_one_by_one(c, n);
 }
 
-// Device scheduler state to the host.  Between qsr_local_step and its qsr_maybe_sync the device has
-// not advanced its counters yet where the advance is the last launch of an iteration: the step just
-// enqueued is added here, so that callers see t and h count it, as the protocol says.  (Where the
-// update kernel has taken the step itself, the counters already include it.)
+// Device scheduler state to the host.  Between qsr_local_step and its qsr_maybe_sync callers see t and h count
+// the step just enqueued and the round still open, as the protocol says: that is the copy the step's kernels
+// read plus one, whether or not the update kernel has advanced the other copy already.
 static int fetch_state(qsr_ctx *c)
 {
-    HIP_TRY(hipMemcpyAsync(c->h_state, st_cur(c), sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
+    const DevState *st = c->d_state + (c->ticked ? c->cur ^ 1 : c->cur);
+    HIP_TRY(hipMemcpyAsync(c->h_state, st, sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (c->h_state->mismatch) return QSR_EMIRROR;
-    if (c->need_sync_call && !c->ticked) { c->h_state->t += 1; c->h_state->h += 1; }
-    // Parallel OPT (H = 1 always): the folded step has closed the round already, which the protocol
-    // counts at qsr_maybe_sync
-    if (c->ticked && c->cfg.parallel) { c->h_state->s -= 1; c->h_state->h = 1; c->h_state->H = 1; }
+    if (c->need_sync_call) { c->h_state->t += 1; c->h_state->h += 1; }
     return QSR_OK;
 }
 

@@ -15,7 +15,6 @@ struct DevState {
     long long h;        // local steps done in the current round
     long long H;        // synchronization period of the current round (0 once t == T)
     int mismatch;       // set (and kept) when the host's mirror of the schedule expected another decision
-    unsigned ticket;    // workgroups of an averaging launch that have finished (that launch then closes the iteration)
 };
 
 // Per-iteration scalars of the OPT update, prepared on the host in double precision and
@@ -35,6 +34,8 @@ struct SchedParams {
     const double *eta;      // [T] device
     long long *log_t;       // [T] device: iteration count at each averaging
     long long *log_H;       // [T] device: period of each finished round
+    int expect_sync;        // per launch: what the host's mirror of the schedule expects of this iteration (1: it ends
+                            // a round), compared with the device's own decision; -1 = no check (recorded launches)
 };
 
 // 128-bit streaming (non-temporal) global accesses: data touched once per kernel
@@ -94,17 +95,18 @@ void set_last_hip_error(int code);
 hipError_t launch_sched_init(DevState *st, SchedParams sp, hipStream_t s);
 hipError_t launch_sched_set(DevState *st, SchedParams sp, long long t, long long s_, long long h, long long H,
                             hipStream_t s);
-// end of an iteration: t += 1, h += 1 and, if that was the round's H-th step, the round is logged and
-// the next one opened.  expect_sync: what the host's mirror of the schedule decided (1 / 0), checked
-// against the device's own decision, or -1 for no check (launches replayed from a graph).
-hipError_t launch_sched_advance(DevState *st, SchedParams sp, int expect_sync, hipStream_t s);
+// *dst <- *src (the two copies of the scheduler state)
+hipError_t launch_sched_copy(DevState *dst, const DevState *src, hipStream_t s);
+// end of an iteration (where no update kernel has taken the step): t += 1, h += 1 and, if that was the round's
+// H-th step, the round is logged and the next one opened
+hipError_t launch_sched_advance(DevState *st, SchedParams sp, hipStream_t s);
 
 // fused_sync: leave the step that completes a round to launch_update_*_sync.
 // row_coef: K clipping factors the gradient rows are multiplied by as they are read, or nullptr.
-// shared_g: the K gradient rows are known to be equal (Parallel OPT), and every iteration ends a round.
-// st_next != nullptr (with sp): the kernel also takes the scheduler's end-of-iteration step, on an iteration
-// that does not end a round (or with shared_g): the advanced state goes to *st_next, a second copy that
-// no kernel of this iteration reads.
+// shared_g: the K gradient rows are known to be equal (Parallel OPT).
+// st_next != nullptr (with sp): the kernel also takes the scheduler's end-of-iteration step: the advanced
+// state goes to *st_next, a second copy that no kernel of this iteration reads (an averaging kernel behind
+// it decides on the copy the iteration began with).
 hipError_t launch_update_sgdm(float *theta, float *g, float *buf, int K, long long P,
                               const DevState *st, const StepScalars *sc, float mu, float lambda,
                               bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s,
@@ -144,12 +146,6 @@ int clip_static_setup(double **out);
 // mean over the K rows of buf [K][P], written to all rows; with st != nullptr the launch acts only
 // if the iteration in progress completes its round (st->h + 1 == st->H, read before the advance)
 hipError_t launch_average_rows(float *buf, int K, long long P, const DevState *st, hipStream_t s);
-// The same launch also closing the iteration: the workgroup that finishes last advances the scheduler
-// (sched_advance, no mirror check), which saves the one-thread launch behind it where an iteration
-// is a handful of microsecond kernels.  Only for launches of few workgroups: average_can_advance.
-bool average_can_advance(int K, long long P);
-hipError_t launch_average_rows_advance(float *buf, int K, long long P, DevState *st, SchedParams sp, hipStream_t s);
-
 hipError_t launch_broadcast_rows(float *dst, const float *src, int K, long long P, hipStream_t s);
 hipError_t launch_fill_zero(float *dst, long long n, hipStream_t s);
 
@@ -172,6 +168,17 @@ struct ModelDims {
 size_t linreg_workspace_bytes(const ModelDims &d);
 hipError_t launch_linreg_grad(const ModelDims &d, const float *theta, float *g, const float *wstar,
                               void *ws, float *loss, const DevState *st, hipStream_t s);
+
+// The same gradient in two launches of which the second also takes the OPT update (s1 != nullptr: AdamW with
+// c1 = 1 - beta1, c2 = 1 - beta2; else SGD with c1 = mu, c2 = lambda), the scheduler's step (st_next as above)
+// and, with average, the round's averaging where the device's scheduler says so.
+bool linreg_can_fuse(const ModelDims &d);
+hipError_t launch_linreg_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
+                                  const DevState *st, hipStream_t s);
+hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g, float *s0, float *s1, void *ws,
+                                     float *loss, const StepScalars *sc, float c1, float c2, float eps,
+                                     const DevState *st, DevState *st_next, bool average, const SchedParams &sp,
+                                     hipStream_t s);
 
 size_t mlp2_workspace_bytes(const ModelDims &d);
 hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, const float *means,

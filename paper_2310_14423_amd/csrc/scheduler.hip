@@ -12,7 +12,7 @@ __global__ void sched_init_kernel(DevState *st, SchedParams sp)
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     st->t = 0; st->s = 0; st->h = 0;
     st->H = get_H(sp, 0);
-    st->mismatch = 0; st->ticket = 0;
+    st->mismatch = 0;
 }
 
 // resume: install a saved (t, s, h, H); log entries of earlier rounds are cleared
@@ -22,16 +22,26 @@ __global__ void sched_set_kernel(DevState *st, SchedParams sp, long long t, long
     for (long long i = threadIdx.x; i < s; i += blockDim.x) { sp.log_t[i] = 0; sp.log_H[i] = 0; }
     if (threadIdx.x != 0) return;
     st->t = t; st->s = s; st->h = h; st->H = H;
-    st->mismatch = 0; st->ticket = 0;
+    st->mismatch = 0;
 }
 
 // the last launch of an iteration when no other kernel closes it
-__global__ void sched_advance_kernel(DevState *st, SchedParams sp, int expect_sync)
+__global__ void sched_advance_kernel(DevState *st, SchedParams sp)
 {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    sched_advance(st, sp, expect_sync);
+    sched_advance(st, sp);
 }
 
+__global__ void sched_copy_kernel(DevState *dst, const DevState *src)
+{
+    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *src;
+}
+
+hipError_t launch_sched_copy(DevState *dst, const DevState *src, hipStream_t s)
+{
+    sched_copy_kernel<<<1, 64, 0, s>>>(dst, src);
+    return hipGetLastError();
+}
 hipError_t launch_sched_init(DevState *st, SchedParams sp, hipStream_t s)
 {
     sched_init_kernel<<<1, 64, 0, s>>>(st, sp);
@@ -43,9 +53,9 @@ hipError_t launch_sched_set(DevState *st, SchedParams sp, long long t, long long
     sched_set_kernel<<<1, 256, 0, s>>>(st, sp, t, s_, h, H);
     return hipGetLastError();
 }
-hipError_t launch_sched_advance(DevState *st, SchedParams sp, int expect_sync, hipStream_t s)
+hipError_t launch_sched_advance(DevState *st, SchedParams sp, hipStream_t s)
 {
-    sched_advance_kernel<<<1, 64, 0, s>>>(st, sp, expect_sync);
+    sched_advance_kernel<<<1, 64, 0, s>>>(st, sp);
     return hipGetLastError();
 }
 

@@ -40,21 +40,6 @@ __device__ __forceinline__ void stg_nt(float4 *p, float4 v) { st_nt4(p, v); }
 // the kernel moves 12 B read + 12 B written = 24 B per element.
 struct NoiseDraw { float sigma; uint64_t seed; int store; };
 
-// The scheduler's end-of-iteration step taken by the update kernel itself, on an iteration that
-// does not end a round (the host's mirror says so; a disagreement is latched as a mismatch): the
-// state is read from the copy every kernel of this iteration reads and the advanced state written
-// to the other copy, which the next iteration's kernels are handed.  No kernel of this iteration
-// reads that one, so no ordering between workgroups is needed, and the one-thread scheduler launch
-// (4 us of dispatch latency, 3 % of a perceptron iteration) goes away.
-// (With Parallel OPT every iteration is a round and no averaging kernel reads the state behind the update: there
-// the step that is folded in logs the round as well; sync: what the host's mirror expects.)
-__device__ __forceinline__ void tick_into(const DevState *st, DevState *st_next, const SchedParams &sp, int sync)
-{
-    DevState nx = *st;
-    sched_advance(&nx, sp, sync);
-    *st_next = nx;
-}
-
 // Worker of an element of the flat K*P vector.
 struct RowAt { long long k, bound; float c0, c1; };   // row of a run's first element, where it ends, its factor and the next row's
 struct RowMap {
@@ -95,7 +80,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
     const StepScalars *__restrict__ sc, float c1, float c2, float eps, int fused_sync,
     const float *__restrict__ row_coef, RowMap rm, NoiseDraw nd, DevState *__restrict__ st_next, SchedParams sp)
 {
-    if (st_next != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tick_into(st, st_next, sp, SHARED ? 1 : 0);
+    if (st_next != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tick_into(st, st_next, sp);
     if (fused_sync && st->h + 1 == st->H) return;
     if (NOISE || SHARED) {
         const long long off = (long long)blockIdx.y * n4;      // rows are 16-byte aligned here
@@ -174,7 +159,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_sgdm_kernel(
     const StepScalars *__restrict__ sc, float mu, float lambda, int fused_sync,
     const float *__restrict__ row_coef, RowMap rm, NoiseDraw nd, DevState *__restrict__ st_next, SchedParams sp)
 {
-    if (st_next != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tick_into(st, st_next, sp, SHARED ? 1 : 0);
+    if (st_next != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tick_into(st, st_next, sp);
     if (fused_sync && st->h + 1 == st->H) return;
     if (NOISE || SHARED) {
         const long long off = (long long)blockIdx.y * n4;

@@ -1,0 +1,43 @@
+"""GPU: the least-squares iteration in two kernels (up to 16 workers; three beyond) at the sizes where it can go
+wrong: feature counts that are no multiple of 4 or 64, few and many samples per wavefront, the largest number of
+workers of a workgroup; one by one and replayed, against each other bit for bit and against the oracle."""
+import numpy as np
+import pytest
+
+import workloads
+from util import assert_mirror_matches_device, assert_params_close, gpu_ctx, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K,d,B,opt", [(3, 1003, 17, "sgdm"), (16, 131, 76, "sgdm"), (17, 66, 9, "sgdm"), (1, 5, 1, "sgdm"),
+                                       (5, 65, 33, "adamw"), (9, 1024, 8, "adamw"), (4, 64, 128, "sgdm"), (2, 3, 5, "adamw")])
+def test_least_squares_shapes(K, d, B, opt):
+    import torch
+    kw = dict(mu=0.9, lam=1e-4) if opt == "sgdm" else dict(beta1=0.9, beta2=0.99, eps=1e-3, lam=0.01)
+    w = workloads.get("lsq", K=K, d_in=d, B_loc=B, T=40, opt=opt, eta_max=0.1 / (1 + d / B), alpha=0.2 / (1 + d / B), **kw)
+    orc = oracle_run(w)
+    orc.step(40)
+    ctx = gpu_ctx(w)
+    ctx.step(40)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        rep = gpu_ctx(w)
+        rep.run(40)
+        rep.stream.synchronize()
+    for a, b in ((ctx.params, rep.params), (ctx.grads, rep.grads), (ctx.state0, rep.state0)):
+        assert torch.equal(a, b)
+    assert np.array_equal(ctx.read_loss(), rep.read_loss())
+    p = ctx.params.cpu().numpy()
+    assert list(ctx.read_sync_log()[0]) == list(orc.sync_log) and all(np.array_equal(p[k], p[0]) for k in range(K))
+    assert_mirror_matches_device(rep)
+    assert_params_close(p, orc.theta, what="params")
+    ctx.close(); rep.close()
+    # one gradient and loss by themselves
+    ctx = gpu_ctx(w)
+    ctx.local_step()
+    g, loss = ctx.grads.cpu().numpy(), ctx.read_loss()
+    for k in range(K):
+        want, wl = orc.grad(k, 0, np.zeros(d))
+        assert_params_close(g[k], want, what="grad k=%d" % k)
+        assert loss[k] == pytest.approx(wl, rel=1e-5)
+    ctx.close()
