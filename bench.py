@@ -262,7 +262,7 @@ def run_workload(name, steps, warmup, kernel_timing=True, fuse_gradient=True, pl
             flops += w["n_blocks"] * K * w["B_loc"] * (3 * 2.0 * 4 * w["d_in"] ** 2 + 6 * 2.0 * w["seq_len"] * w["d_in"])
         g_ms = ms[0] / cnt[0]
         ach = flops / (g_ms * 1e-3) / 1e12
-        roofline = {"kernel": "gradient stage: gemm_nt_bf16_kernel / gemm_pp_tn_kernel%s + helpers" % (" / attn_*_kernel" if w.get("n_heads", 0) else ""),
+        roofline = {"kernel": "gradient stage: gemm_nt_bf16_kernel / gemm_tn_kernel%s + helpers" % (" / attn_*_kernel" if w.get("n_heads", 0) else ""),
                     "bound": "mfma", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": ach / MFMA_BF16_PEAK_TFLOPS, "traffic": None, "avg_ms": g_ms,
                     "median_ms": median[0], "min_ms": best[0],

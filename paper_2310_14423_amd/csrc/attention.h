@@ -1,7 +1,7 @@
 // attention.h -- the core of multi-head self-attention, o = softmax(q k^T / sqrt(dk)) v within each
 // sequence, forward and backward, on the gfx950 bf16 matrix cores (the attention half of the ViT-B
 // encoder block that Sec. 4 / App. C.2 of arXiv 2310.14423 trains: heads of width 64, sequences of
-// 196-197 tokens).  The projections around it are ordinary GEMMs (gemm_bf16.h, gemm_pp.h).
+// 196-197 tokens).  The projections around it are ordinary GEMMs (gemm_bf16.h, gemm_tn.h).
 //
 // One workgroup per (sequence, head, worker); sequences are short, so a whole head's K and V (or
 // Q and dO) tiles sit in LDS, as they are in memory ([token][feature]), and each wavefront owns one

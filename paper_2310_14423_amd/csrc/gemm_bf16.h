@@ -29,7 +29,7 @@
 // [column block] (blk_off below).  Both kinds of GEMM then copy consecutive memory: a 256-row x
 // 32-deep stage of this kernel's operands is 8 pieces of 2 KiB (one block each) instead of
 // 256 pieces of 64 B a whole row (1.5 - 6 KiB) apart, and a 32-token x 192- or 384-feature slab of
-// the weight-gradient kernel (gemm_pp.h), which walks the same arrays along their rows, is 12 or
+// the weight-gradient kernel (gemm_tn.h), which walks the same arrays along their rows, is 12 or
 // 24 KiB in one piece instead of 32 pieces; every global -> LDS copy instruction moves 1 KiB of
 // consecutive memory.  (Blocks of 256 rows x 32 columns, 32 KiB per slab here, were timed first:
 // this kernel gained 3-4 %, the weight-gradient kernel, whose slab was then 2 KiB pieces exactly
@@ -61,7 +61,7 @@ struct GemmNT {
     int M, N, K;
     long long lda, ldb;
     long long sA, sB;      // per-batch strides (elements)
-    // TN form (gemm_pp.h) only:
+    // TN form (gemm_tn.h) only:
     float *colsum_B;       // optional: colsum_B[z*s_colsum + n] = sum_k B[z][k][n]
     long long s_colsum;
     const bf16_t *zeros;   // 64 bytes of zeros, read in place of k-rows beyond K (needed if K % 32 != 0)

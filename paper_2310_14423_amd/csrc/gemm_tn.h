@@ -1,0 +1,313 @@
+// gemm_tn.h -- batched bf16 "TN" GEMM for gfx950: the weight gradients of the residual-MLP workload,
+//
+//     C[z][m][n] = sum_k A[z][k][m] * B[z][k][n]      (both operands stored [k][feature], k = token)
+//
+// so the 8 consecutive k a lane of the MFMA needs lie in 8 different rows.  The stages are kept in
+// LDS as they are in memory (tokens x features) and the fragments are fetched with the gfx950 LDS
+// transpose read (ds_read_b64_tr_b16): within each group of 16 lanes, lane j receives element
+// j%4 of the 64-bit words addressed by lanes j/4, j/4+4, j/4+8, j/4+12 of the group (checked on
+// the hardware).  Pointing lane r = q + 4e of a group at token e, features 4q..4q+3 of a
+// 4-token x 16-feature block therefore hands lane j feature j and the 4 tokens in order; two
+// such reads give the 8 k values of an MFMA operand, and the four groups of a wavefront cover
+// 32 features x 16 tokens in exactly the instruction's operand layout.
+//
+//  * Stages of 32 tokens are copied global -> LDS directly (global_load_lds_dwordx4) into a ring of NS
+//    buffers, NS - 1 ahead, LDS keeping [32-feature column block][32 tokens][32 features], the form
+//    the transpose reads take without bank conflicts.  Token rows beyond K are read from a block of
+//    zeros.
+//  * The order of the main loop is pinned as in gemm_bf16.h: LDS reads and copies go out one or two at
+//    a time between MFMAs, one barrier per stage.  (Two wavefront groups a phase apart, one
+//    multiplying while the other fetches, with two barriers per stage: 468 us against 407 us at 8 x 12608
+//    tokens x 768 x 3072, same box.)
+//  * Large problems: tiles of 192 x 384 (wavefront 96 x 96).  768 x 3072 outputs per worker are 32
+//    such tiles, so 8 workers fill the 256 compute units exactly once.  The reduction of
+//    problems with fewer tiles can be cut into ranges (GemmNT::split): each (tile, range) is a
+//    workgroup of its own, handed to the epilogue as a batch entry of its own; the caller adds the
+//    partial results up in a fixed order.
+//  * Small problems: tiles of 64 x 64 whose reduction is shared by KG = 4 groups of four wavefronts in one
+//    workgroup, each with its own ring on a quarter of the tokens; the groups' results are added in
+//    order through LDS, with no second launch.
+//  * Tile order: worker, panels of 4 N-tiles, M-tile, N-tile inside the panel; each XCD (workgroup id
+//    mod 8) takes a contiguous eighth of that order: one XCD's L2 sees one worker's activations.
+//  * Bias gradients (column sums of B over the tokens) come from the B fragments the wavefronts of the
+//    first tile row already hold for their MFMAs: one bf16 dot product with ones per register pair.
+//
+// lda/ldb must be multiples of 8 elements, M and N multiples of 64 (ragged against the tile: operand
+// columns are clamped on load, the epilogue is bounds-checked); K may be ragged if GemmNT::zeros
+// is given.
+#pragma once
+#include <type_traits>
+
+#include "gemm_bf16.h"
+
+namespace qsr {
+
+// BLKA / BLKB: the operand is stored in 32-token x 32-feature blocks (gemm_bf16.h); lda / ldb then
+// hold its feature count.  A 1 KiB chunk of a stage (16 tokens x 32 features of one column block) is
+// then 1 KiB of consecutive memory; row-major it is 16 pieces of 64 B a whole row apart.  Either way a
+// stage lies 32 * ld elements behind the one before.
+template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, bool BLKB, class Epi>
+__global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT p, Epi epi, int Z)
+{
+    constexpr int BK = 32, NW = WM * WN;                          // wavefronts of a group
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32, MM = TM * TN, NF = TM + TN;
+    constexpr int PANEL = 4;                                      // N-tiles per panel of the tile order
+    constexpr int STAGE = (BM + BN) * BK;                         // elements
+    constexpr int CA = BM / 16, CHUNKS = (BM + BN) / 16;          // 1 KiB chunks per stage
+    constexpr int CPW = (CHUNKS + NW - 1) / NW;                   // ... and wavefront (the last ones may have one less)
+    extern __shared__ __attribute__((aligned(1024))) unsigned char gemm_smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = wave_wg / NW, wave = wave_wg % NW;
+    const int wm = wave / WN, wn = wave % WN;
+    const int nx = (p.N + BN - 1) / BN, ny = (p.M + BM - 1) / BM;
+    const int split = p.split > 1 ? p.split : 1;                  // ranges of the reduction, each a work item
+    const int per_z = nx * ny;
+    int f = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (f >= Z * split * per_z) return;
+    const int zz = f / per_z;                                     // batch * split + range
+    f -= zz * per_z;
+    const int pn = f / (ny * PANEL);
+    f -= pn * ny * PANEL;
+    const int bw = min(PANEL, nx - pn * PANEL);
+    const int my = f / bw;
+    const int m0 = my * BM, n0 = (pn * PANEL + f - my * bw) * BN;
+
+    // this group's tokens [k_begin, k_end), and the stages every group walks (a group that runs out
+    // multiplies zeros)
+    const int z = zz / split, r0 = (zz - z * split) * (split > 1 ? p.k_chunk : 0);
+    const int r1 = split > 1 ? min(p.K, r0 + p.k_chunk) : p.K;
+    const int nk = ((r1 - r0 + BK - 1) / BK + KG - 1) / KG;
+    const int k_begin = r0 + grp * nk * BK, k_end = min(r1, k_begin + nk * BK);
+
+    // ---- copies: chunk c of a stage is 1 KiB of LDS (16 tokens x 32 features of one column block)
+    bf16_t *ring = (bf16_t *)gemm_smem + grp * NS * STAGE;
+    const bf16_t *src[CPW];
+    const bf16_t *A = p.A + (long long)z * p.sA + (long long)k_begin * p.lda;    // k_begin is a multiple of 32:
+    const bf16_t *B = p.B + (long long)z * p.sB + (long long)k_begin * p.ldb;    // the first block row of the range
+    const int tok = lane >> 2;
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        const int c = i * NW + wave;
+        const bool isA = c < CA;
+        const int cc = isA ? c : c - CA, t = (cc & 1) * 16 + tok;                // token inside the stage
+        const int fc = min((isA ? m0 : n0) + (cc >> 1) * 32, (isA ? p.M : p.N) - 32) + (lane & 3) * 8;
+        if (isA) src[i] = BLKA ? A + (long long)(fc >> 5) * 1024 + t * 32 + (fc & 31) : A + (long long)t * p.lda + fc;
+        else src[i] = BLKB ? B + (long long)(fc >> 5) * 1024 + t * 32 + (fc & 31) : B + (long long)t * p.ldb + fc;
+    }
+    const long long stepA = (long long)BK * p.lda, stepB = (long long)BK * p.ldb;   // elements per stage
+    const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)ring;
+    int d_stage = 0, d_row = k_begin;                 // buffer and first token of the next stage to copy
+    auto issue = [&](int i) {
+        const int c = i * NW + wave;
+        if (CHUNKS % NW == 0 || c < CHUNKS) {
+            const bf16_t *g = src[i];
+            if (d_row + BK > k_end) {                 // the range's last stage, or one beyond it
+                const int cc = c < CA ? c : c - CA;
+                if (d_row + (cc & 1) * 16 + tok >= k_end) g = p.zeros + (lane & 3) * 8;
+            }
+            // as asm: behind the builtin, the compiler takes every transpose read for a possible reader of the copies
+            // in flight and waits for all of them first
+            const unsigned dst = __builtin_amdgcn_readfirstlane(lds_ring + d_stage * (STAGE * 2) + c * 1024);
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(g) : "memory");
+            src[i] += c < CA ? stepA : stepB;
+        }
+    };
+    auto issued = [&]() { d_stage = d_stage + 1 == NS ? 0 : d_stage + 1; d_row += BK; };
+    const bool short_wave = CHUNKS % NW != 0 && (CPW - 1) * NW + wave >= CHUNKS;
+
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    float csum[TN];                                   // column sums of B: lane l has 8 tokens of column l % 32 per fragment
+#pragma unroll
+    for (int j = 0; j < TN; ++j) csum[j] = 0.f;
+    const bool colsum_wg = p.colsum_B != nullptr && m0 == 0;
+    const bool do_colsum = colsum_wg && wm == 0;
+
+    bf16x8 fa[2][TM], fb[2][TN];
+    // lane's place in the transpose reads inside a 16-token x 32-feature operand block
+    const int g16 = lane >> 4, r16 = lane & 15;
+    const int lane_off = ((g16 >> 1) * 8 + (r16 >> 2)) * 32 + (g16 & 1) * 16 + (r16 & 3) * 4;
+    auto frag = [&](const bf16_t *blk, int ks) {      // blk: [32 tokens][32 features] of one column block
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        const bf16_t *q0 = blk + ks * 512 + lane_off;
+        union { struct { s16x4 a, b; } s; bf16x8 v; } u;
+        u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)q0);
+        u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(q0 + 4 * 32));
+        return u.v;
+    };
+    auto read = [&](int stage, int ks, int q) {       // in the order the multiplications need them
+        const bf16_t *sa = ring + stage * STAGE + wm * TM * 1024, *sb = ring + stage * STAGE + BM * BK + wn * TN * 1024;
+        if (q == 0) fb[ks][0] = frag(sb, ks);
+        else if (q == 1) fa[ks][0] = frag(sa, ks);
+        else if (q <= TN) fb[ks][q - 1] = frag(sb + (q - 1) * 1024, ks);
+        else fa[ks][q - TN] = frag(sa + (q - TN) * 1024, ks);
+    };
+    auto multiply = [&](int ks, int m) {              // serpentine: neighbours share an operand
+        const int i = m / TN, j = (i & 1) ? TN - 1 - m % TN : m % TN;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    };
+    auto add_columns = [&](int ks) {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bf16x2 two = {fb[ks][j][2 * e], fb[ks][j][2 * e + 1]};
+                csum[j] = __builtin_amdgcn_fdot2_f32_bf16(two, ones, csum[j], false);
+            }
+    };
+    auto barrier = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // waits until at most `stages` of this wavefront's stage copies are outstanding, and for its LDS reads
+    auto wait = [&](auto stages) {
+        constexpr int FULL = CPW * decltype(stages)::value, SHORT = (CPW - 1) * decltype(stages)::value;
+        if (short_wave) __builtin_amdgcn_s_waitcnt(0x0070 | (SHORT & 15) | ((SHORT >> 4) << 14));
+        else __builtin_amdgcn_s_waitcnt(0x0070 | (FULL & 15) | ((FULL >> 4) << 14));
+    };
+
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (s < nk) {
+#pragma unroll
+            for (int i = 0; i < CPW; ++i) issue(i);
+            issued();
+        }
+    if (nk >= NS) wait(std::integral_constant<int, NS - 1>{});
+    else wait(std::integral_constant<int, 0>{});
+    barrier();
+    int cur = 0;
+#pragma unroll
+    for (int q = 0; q < NF; ++q) read(0, 0, q);
+    auto stage = [&](auto last_c, auto issue_c, auto left) {
+        constexpr bool LAST = decltype(last_c)::value, ISSUE = decltype(issue_c)::value;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MM; ++m) {
+            multiply(0, m);
+#pragma unroll
+            for (int q = 0; q < NF; ++q)
+                if ((NF <= MM ? q : q * MM / NF) == m) read(cur, 1, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (do_colsum) add_columns(0);
+        if (!LAST) {
+            wait(left);
+            barrier();
+            cur = cur + 1 == NS ? 0 : cur + 1;
+        }
+        if (do_colsum) add_columns(1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MM; ++m) {
+            multiply(1, m);
+#pragma unroll
+            for (int q = 0; q < NF; ++q)
+                if (!LAST && (NF <= MM ? q : q * MM / NF) == m) read(cur, 0, q);
+#pragma unroll
+            for (int i = 0; i < CPW; ++i)
+                if (!LAST && ISSUE && (CPW <= MM ? MM - CPW + i : i * MM / CPW) == m) issue(i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!LAST && ISSUE) issued();
+    };
+    // stages outstanding at a wait: kt + 2 .. kt + NS - 1 while that many exist
+    int kt = 0;
+    for (; kt + NS < nk; ++kt) stage(std::false_type{}, std::true_type{}, std::integral_constant<int, NS - 2>{});
+    if (kt + NS == nk && kt + 1 < nk) { stage(std::false_type{}, std::false_type{}, std::integral_constant<int, NS - 2>{}); ++kt; }
+    for (; kt + 1 < nk; ++kt) stage(std::false_type{}, std::false_type{}, std::integral_constant<int, 0>{});
+    stage(std::true_type{}, std::false_type{}, std::integral_constant<int, 0>{});
+    __syncthreads();                                  // everyone is through with the rings
+
+    // The ring's memory from here on: epilogue staging, column sums [group][token half][column], the other groups'
+    // accumulators
+    constexpr int STAGING = NW * 32 * (TN * 32 + 4);  // floats
+    constexpr int COLS = KG * 2 * BN, ACCS = (KG - 1) * NW * MM * 16 * 64;
+    static_assert((STAGING + COLS + ACCS) * 4 <= KG * NS * STAGE * 2, "epilogue inside the rings");
+    float *cols = (float *)gemm_smem + STAGING, *accs = cols + COLS;
+    if (do_colsum) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) cols[(grp * 2 + (lane >> 5)) * BN + wn * (BN / WN) + j * 32 + (lane & 31)] = csum[j];
+    }
+    if (KG > 1 && grp > 0) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    accs[((((grp - 1) * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane] = acc[i][j][e];
+    }
+    __syncthreads();
+    if (colsum_wg && tid < BN && n0 + tid < p.N) {
+        float s = 0.f;
+#pragma unroll
+        for (int q = 0; q < KG * 2; ++q) s += cols[q * BN + tid];
+        p.colsum_B[(long long)zz * p.s_colsum + n0 + tid] = s;
+    }
+    if (KG > 1) {
+        if (grp > 0) return;
+#pragma unroll
+        for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] += accs[(((g * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane];
+    }
+    epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane,
+                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, zz, epi);
+}
+
+// Whether launch_gemm_tn can take the problem.
+inline bool gemm_tn_supports(const GemmNT &p)
+{
+    if (p.K < 1 || p.lda % 8 != 0 || p.ldb % 8 != 0) return false;
+    if (p.M % 64 != 0 || p.N % 64 != 0 || p.M < 64 || p.N < 64) return false;
+    if (p.split > 1 && (p.k_chunk < 32 || p.k_chunk % 32 != 0 || (long long)(p.split - 1) * p.k_chunk >= p.K)) return false;
+    return p.zeros != nullptr;
+}
+
+// compute units of the current device
+inline int gemm_cu_count()
+{
+    static int n_cu = 0;                      // contexts are not thread-safe; one GPU per process
+    if (n_cu == 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 8)
+            n_cu = 256;
+    }
+    return n_cu;
+}
+
+template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, bool BLKB, class Epi>
+inline hipError_t launch_gemm_tn(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
+{
+    // blocked operands: 32-column blocks (the ranges of a split reduction start at multiples of 32 tokens)
+    if (!gemm_tn_supports(p) || (BLKA && p.lda % 32 != 0) || (BLKB && p.ldb % 32 != 0)) return hipErrorInvalidValue;
+    constexpr size_t smem = (size_t)KG * NS * (BM + BN) * 32 * 2;
+    static_assert(smem <= 160 * 1024, "rings do not fit the 160 KB LDS");
+    auto kern = gemm_tn_kernel<BM, BN, WM, WN, KG, WPS, NS, BLKA, BLKB, Epi>;
+    static bool lds_limit_raised = false;     // per instantiation; contexts are not thread-safe
+    if (smem > 64 * 1024 && !lds_limit_raised) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        lds_limit_raised = true;
+    }
+    const unsigned items = (unsigned)((p.M + BM - 1) / BM) * (unsigned)((p.N + BN - 1) / BN) * (unsigned)batch *
+                           (unsigned)(p.split > 1 ? p.split : 1);
+    kern<<<(items + 7) / 8 * 8, WM * WN * KG * 64, smem, s>>>(p, epi, batch);
+    return hipGetLastError();
+}
+
+}  // namespace qsr

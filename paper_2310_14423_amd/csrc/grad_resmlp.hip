@@ -28,7 +28,7 @@
 // GEMMs of the same kinds, and the attention core of attention.h.
 #include "attention.h"
 #include "gemm_bf16.h"
-#include "gemm_pp.h"
+#include "gemm_tn.h"
 #include "qsr_internal.h"
 
 namespace qsr {
@@ -629,17 +629,6 @@ static hipError_t gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_
     if (tiles(128, 128) >= 160) return launch_gemm_nt<128, 128, 2, 2, 3, 3, BLKA>(p, epi, batch, s);
     return launch_gemm_nt<64, 64, 2, 2, 4, 4, BLKA>(p, epi, batch, s);
 }
-// TN: the persistent two-group kernel of gemm_pp.h, whose 192x384 tiles make exactly 256 workgroups for 8
-// workers of the benchmark size.
-template <bool BLKA, bool BLKB, class Epi>
-static hipError_t gemm_tn(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
-{
-    // widths are multiples of 64 and a block of zeros stands in for ragged token counts, so every
-    // weight gradient of this model qualifies
-    if (!gemm_pp_tn_supports(p)) return hipErrorInvalidValue;
-    return launch_gemm_pp_tn<BLKA, BLKB>(p, epi, batch, s);
-}
-
 #define TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
 
 // out[z][i] = part[z][0][i] + part[z][1][i] + ... (ascending: a fixed order), i < n, n a multiple of 4
@@ -659,34 +648,53 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float *__restrict
 }
 
 // Weight gradient dW[z] = A[z]^T B[z] (p.M x p.N, rows contiguous, per-worker stride sOut) with the
-// bias gradient (column sums of B) as a by-product.  A gradient with few tiles for the chip's
-// persistent workgroups has its token reduction cut into up to WGRAD_SPLIT ranges, whose partial
-// results are added up afterwards (the 768 x 768 output projection of 8 workers is 64 tiles of
-// 192 x 384 for 256 compute units: 0.37 ms as one range each, as long as a gradient four times
-// its size).
+// bias gradient (column sums of B) as a by-product.  Widths are multiples of 64 and a block of zeros stands in
+// for ragged token counts, so every weight gradient of this model qualifies.
+// Tile shape by the number of tiles and the length of the reduction, from timing on MI355X (us; batch x tokens x
+// width x hidden: gradient of the second weight / of a width x width projection; s4: cut into four ranges, without
+// the 6-16 us that adding them up takes):
+//                              192x384          128x128, 3 WG/CU    128x128, 2 groups    64x64, 4 groups   before
+//   8 x 12608 x 768 x 3072   407 / 297, s4 117   589 / 193           616 / 217              - / -          468 / 372 (s4 128)
+//   2 x 12608 x 768 x 3072   271 / 269, s4 113   177 / 115, s4 51    192 / 97             236 / 99         375 / 357
+//   1 x 12608 x 768 x 3072   291 / 275, s4 84    121 / 116, s4 35    101 / 97             131 / 47         374 / 360
+//   8 x 1576 x 768 x 3072     61 / 43             68 / 28             84 / 32             148 / 42          68 / 53
+//   4 x 2000 x 512 x 2048     53 / 50             26 / 22             25 / 20              43 / 11          67 / 65
+//   2 x 400 x 768 x 3072      18 / 16             11 / 7.6            15 / 8.0             25 / 10.5        21 / 20
+//   2 x 1040 x 192 x 768      32 / 30             13 / 13             12 / 12             8.0 / 7.7         39 / 38
+// Hence: the large tile from 160 of them on; a long reduction (4096 tokens) with fewer is cut into up to WGRAD_SPLIT
+// ranges, on the large tile while that makes about 200 workgroups, else on the small one; a short one goes to
+// 128 x 128 (two groups per workgroup below 200 of them) and from 110 of those down to 64 x 64 with four groups.
 template <bool BLKA, bool BLKB>
 static hipError_t wgrad(GemmNT p, float *dW, float *db, long long sOut, const ResWs &w, int batch, hipStream_t s)
 {
     p.zeros = w.ZERO;
-    const int tiles = ((p.M + 191) / 192) * ((p.N + 383) / 384) * batch;
-    const int cus = gemm_pp_cu_count();
-    int split = tiles * 2 <= cus ? (cus / tiles < WGRAD_SPLIT ? cus / tiles : WGRAD_SPLIT) : 1;
-    const int k_chunk = ((p.K + split - 1) / split + 31) / 32 * 32;
-    split = (p.K + k_chunk - 1) / k_chunk;
-    if (split <= 1) {
-        p.colsum_B = db; p.s_colsum = sOut;
-        EpiScaleF32 epi{dW, p.N, sOut, 1.0f};
-        return gemm_tn<BLKA, BLKB>(p, epi, batch, s);
-    }
+    auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * batch; };
+    const long long big = tiles(192, 384), mid = tiles(128, 128);
     const long long MN = (long long)p.M * p.N;
-    p.split = split; p.k_chunk = k_chunk;
-    p.colsum_B = w.SPLITKB; p.s_colsum = p.N;
-    EpiScaleF32 epi{w.SPLITK, p.N, MN, 1.0f};
-    TRY((gemm_tn<BLKA, BLKB>(p, epi, batch, s)));
-    splitk_sum_kernel<<<dim3((unsigned)((MN / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITK, MN, split, dW, sOut);
-    TRY(hipGetLastError());
-    splitk_sum_kernel<<<dim3((unsigned)((p.N / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITKB, p.N, split, db, sOut);
-    return hipGetLastError();
+    if (big < 160 && p.K >= 4096) {
+        const bool large = big >= 48;
+        const long long want = large ? gemm_cu_count() / big : 3LL * gemm_cu_count() / mid;
+        int split = (int)(want < 1 ? 1 : want > WGRAD_SPLIT ? WGRAD_SPLIT : want);
+        const int k_chunk = ((p.K + split - 1) / split + 31) / 32 * 32;
+        split = (p.K + k_chunk - 1) / k_chunk;
+        if (split > 1) {
+            p.split = split; p.k_chunk = k_chunk;
+            p.colsum_B = w.SPLITKB; p.s_colsum = p.N;
+            EpiScaleF32 epi{w.SPLITK, p.N, MN, 1.0f};
+            if (large) TRY((launch_gemm_tn<192, 384, 2, 4, 1, 2, 4, BLKA, BLKB>(p, epi, batch, s)));
+            else TRY((launch_gemm_tn<128, 128, 2, 2, 1, 3, 3, BLKA, BLKB>(p, epi, batch, s)));
+            splitk_sum_kernel<<<dim3((unsigned)((MN / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITK, MN, split, dW, sOut);
+            TRY(hipGetLastError());
+            splitk_sum_kernel<<<dim3((unsigned)((p.N / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITKB, p.N, split, db, sOut);
+            return hipGetLastError();
+        }
+    }
+    p.colsum_B = db; p.s_colsum = sOut;
+    EpiScaleF32 epi{dW, p.N, sOut, 1.0f};
+    if (big >= 160) return launch_gemm_tn<192, 384, 2, 4, 1, 2, 4, BLKA, BLKB>(p, epi, batch, s);
+    if (mid >= 200) return launch_gemm_tn<128, 128, 2, 2, 1, 3, 3, BLKA, BLKB>(p, epi, batch, s);
+    if (mid >= 110) return launch_gemm_tn<128, 128, 2, 2, 2, 2, 4, BLKA, BLKB>(p, epi, batch, s);
+    return launch_gemm_tn<64, 64, 2, 2, 4, 4, 3, BLKA, BLKB>(p, epi, batch, s);
 }
 
 hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g, const float *teacher,
@@ -707,7 +715,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     // are resident at once (a launch of 1.5 times the chip's wavefront slots runs as one full wave of
     // workgroups and a half-empty one).  Resident wavefronts per CU follow from the kernel's registers.
     const int vpl_ln = (d + 255) / 256;
-    const int ln_slots = gemm_pp_cu_count() * (vpl_ln <= 1 ? 28 : vpl_ln == 2 ? 20 : vpl_ln == 3 ? 16 : 12);
+    const int ln_slots = gemm_cu_count() * (vpl_ln <= 1 ? 28 : vpl_ln == 2 ? 20 : vpl_ln == 3 ? 16 : 12);
     int rows_per_wave = (int)(((long long)K * M + ln_slots - 1) / ln_slots);
     if (rows_per_wave < LN_ROWS_PER_WAVE) rows_per_wave = LN_ROWS_PER_WAVE;
     const int wave_rows = (M + rows_per_wave - 1) / rows_per_wave;

@@ -17,6 +17,14 @@ pytestmark = pytest.mark.gpu
     dict(d_in=64, d_hidden=4096, n_blocks=1, B_loc=1021, K=8),
     # N = 192: one and a half 128 x 128 tiles wide
     dict(d_in=192, d_hidden=64, n_blocks=1, B_loc=4000, K=8),
+    # weight gradients on 128 x 128 tiles with two groups (128 of them), a short token count for both groups
+    dict(d_in=64, d_hidden=2048, n_blocks=1, B_loc=300, K=8),
+    # reductions long enough to be cut into ranges: on 128 x 128 tiles, the last range ragged
+    dict(d_in=64, d_hidden=128, n_blocks=1, B_loc=4129, K=2),
+    # on 192 x 384 tiles (48 of them, rows and columns beyond the matrix)
+    dict(d_in=64, d_hidden=4608, n_blocks=1, B_loc=4100, K=4),
+    # fewer tokens than a stage
+    dict(d_in=64, d_hidden=64, n_blocks=1, B_loc=7, K=1),
 ])
 def test_gradient_where_the_tile_shape_changes(dims):
     w = workloads.get("resmlp", T=4, T_warm=1, **dims)
