@@ -29,6 +29,7 @@
 #include "attention.h"
 #include "gemm_bf16.h"
 #include "gemm_tn.h"
+#include "philox.h"
 #include "qsr_internal.h"
 
 namespace qsr {
@@ -37,7 +38,19 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr float LN_EPS = 1e-5f;
 constexpr int WGRAD_SPLIT = 4;          // most ranges a weight gradient's token reduction is cut into
-constexpr int LN_ROWS_PER_WAVE = 16;     // least token rows per wavefront of the LayerNorm backward pass
+
+// Token rows per wavefront of the LayerNorm backward pass: enough that all wavefronts of the launch are resident at
+// once (a launch of 1.5 times the chip's wavefront slots runs as one full wave of workgroups and a half-empty one:
+// 283 against 234 us at 8 x 12608 rows of 768), resident wavefronts per compute unit following from the kernel's
+// registers; and not fewer than 4, since each wavefront leaves a row of partial sums for the parameter
+// gradients.  (With at least 16, few tokens left most of the chip idle: 27 us at 2 x 1040 rows of 192.)
+static int ln_rows_per_wave(long long K, long long M, long long d)
+{
+    const int vpl = (int)((d + 255) / 256);
+    const long long slots = 256LL * (vpl <= 1 ? 28 : vpl == 2 ? 20 : vpl == 3 ? 16 : 12);
+    const long long rows = (K * M + slots - 1) / slots;
+    return (int)(rows < 4 ? 4 : rows);
+}
 
 struct ResWs {
     // per-replica strides are the element counts of one replica's array
@@ -106,7 +119,7 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.W1b = (bf16_t *)take(w.sW, 2, K);  w.W1Tb = (bf16_t *)take(w.sW, 2, K);
     w.W2b = (bf16_t *)take(w.sW, 2, K);  w.W2Tb = (bf16_t *)take(w.sW, 2, K);
     w.WTt = (bf16_t *)take(blk_elems(d, d), 2, 1);
-    const long long wave_rows = (M + LN_ROWS_PER_WAVE - 1) / LN_ROWS_PER_WAVE;
+    const long long rows_per_wave = ln_rows_per_wave(K, M, d), wave_rows = (M + rows_per_wave - 1) / rows_per_wave;
     w.sPART = padded(2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
     w.sLPART = padded((M * d + 1023) / 1024, 4); w.LPART = (float *)take(w.sLPART, 4, K);
     w.ZERO = (bf16_t *)take(128, 2, 1);
@@ -144,66 +157,77 @@ size_t resmlp_workspace_bytes(const ModelDims &d)
 // layout / conversion kernels
 // ---------------------------------------------------------------------------------------------
 
-// in [R][C] (row stride ld_in) -> out [R][C] bf16 (optional) and outT [C][R] bf16, both in the
-// blocked layout of gemm_bf16.h (R and C multiples of 32), 64x64 tiles through LDS.  Batch index
-// blockIdx.z = z * n_inner + l: z with the element strides s_in, s_out, s_t (workers), l with the
-// strides l_in (input) and l_out, l_t (the blocks of the model), so that one launch converts a weight
-// of all blocks.
-template <class TIn>
-__global__ __launch_bounds__(256) void cvt_transpose_kernel(const TIn *__restrict__ in, long long ld_in,
-                                                            long long s_in, long long l_in, bf16_t *__restrict__ out,
-                                                            long long s_out, long long l_out, bf16_t *__restrict__ outT,
-                                                            long long s_t, long long l_t, int R, int C, int n_inner)
+// bf16 copies of fp32 matrices [R][C] (R and C multiples of 64, rows contiguous) in the blocked layout of
+// gemm_bf16.h, as they are (optional) and transposed: all weights of all blocks and workers, and the
+// teacher map, in one launch.  HBM-bound (4 B read, 4 written per weight): a workgroup takes a 64 x 64 tile, 128-bit
+// loads all in flight at once, 128-bit stores both ways, the transposed ones through LDS.  Timed on MI355X:
+// 12 blocks 768/3072 with attention x 8 workers 1047 us (5.2 TB/s), 2 x 192/768 with attention x 2 workers 5.3 us (one launch
+// per kind of matrix, one element per lane: 1430 and 58 us).
+struct CvtMat {
+    const float *in; long long s_in, l_in;           // worker and block strides
+    bf16_t *out, *outT; long long s_out;             // worker stride of both; the blocks' copies are R*C padded apart
+    int R, C, n_l, n_z;                              // blocks and workers
+    int first;                                       // first workgroup
+};
+struct CvtList { CvtMat m[5]; int n; };
+
+__global__ __launch_bounds__(256) void cvt_transpose_kernel(CvtList list)
 {
     __shared__ bf16_t tile[64][66];
-    const int z = blockIdx.z / n_inner, l = blockIdx.z - z * n_inner;
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    in += (long long)z * s_in + (long long)l * l_in;
-    for (int r = ty; r < 64; r += 4) {
-        bf16_t v = (bf16_t)0.0f;
-        if (r0 + r < R && c0 + tx < C) {
-            v = (bf16_t)in[(long long)(r0 + r) * ld_in + c0 + tx];
-            if (out) out[(long long)z * s_out + (long long)l * l_out + blk_off(r0 + r, c0 + tx, C)] = v;
-        }
-        tile[r][tx] = v;
+    int e = 0;
+    while (e + 1 < list.n && (int)blockIdx.x >= list.m[e + 1].first) ++e;
+    const CvtMat &q = list.m[e];
+    const int R = q.R, C = q.C, tx = C >> 6, per = tx * (R >> 6);
+    int b = blockIdx.x - q.first;
+    const int zl = b / per;
+    b -= zl * per;
+    const int z = zl / q.n_l, l = zl - z * q.n_l;
+    const int r0 = (b / tx) * 64, c0 = (b % tx) * 64;
+    const int t = threadIdx.x, row = t >> 3, c = (t & 7) * 8;
+    const float *src = q.in + (long long)z * q.s_in + (long long)l * q.l_in + (long long)(r0 + row) * C + c0 + c;
+    float4 v[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) v[i][u] = *(const float4 *)(src + (long long)i * 32 * C + u * 4);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const bf16x8 w = {(bf16_t)v[i][0].x, (bf16_t)v[i][0].y, (bf16_t)v[i][0].z, (bf16_t)v[i][0].w,
+                          (bf16_t)v[i][1].x, (bf16_t)v[i][1].y, (bf16_t)v[i][1].z, (bf16_t)v[i][1].w};
+        if (q.out)
+            *(bf16x8 *)(q.out + (long long)z * q.s_out + l * blk_elems(R, C) + blk_off(r0 + row + i * 32, c0 + c, C)) = w;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) tile[row + i * 32][c + k] = w[k];
     }
     __syncthreads();
-    if (outT) {
-        for (int c = ty; c < 64; c += 4)
-            if (c0 + c < C && r0 + tx < R)
-                outT[(long long)z * s_t + (long long)l * l_t + blk_off(c0 + c, r0 + tx, R)] = tile[tx][c];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        bf16x8 w;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k] = tile[c + k][row + i * 32];
+        *(bf16x8 *)(q.outT + (long long)z * q.s_out + l * blk_elems(C, R) + blk_off(c0 + row + i * 32, r0 + c, R)) = w;
     }
 }
 
-template <class TIn>
-static hipError_t launch_cvt_transpose(const TIn *in, long long ld_in, long long s_in, long long l_in, bf16_t *out,
-                                       long long s_out, bf16_t *outT, long long s_t,
-                                       int R, int C, int batch, int n_inner, hipStream_t s)
+// Sample(): tokens x_0 ~ N(0,1), [M][d] per worker, in fp32 and in bf16 (blocked), four per lane (d a multiple of
+// 64), the draws of a bulk fill of the flat array; blockIdx.y = worker.  The first workgroup also clears the 256
+// bytes that stand in for missing rows in the weight-gradient GEMMs.
+__global__ __launch_bounds__(256) void sample_tokens_kernel(float *__restrict__ X, long long sX, bf16_t *__restrict__ U,
+                                                            long long sU, long long n4, int d, uint64_t seed,
+                                                            const DevState *__restrict__ st, bf16_t *__restrict__ zero)
 {
-    if ((long long)batch * n_inner > 65535 || R % 32 != 0 || C % 32 != 0) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((C + 63) / 64), (unsigned)((R + 63) / 64), (unsigned)(batch * n_inner));
-    cvt_transpose_kernel<TIn><<<grid, 256, 0, s>>>(in, ld_in, s_in, l_in, out, s_out, blk_elems(R, C), outT, s_t,
-                                                   blk_elems(C, R), R, C, n_inner);
-    return hipGetLastError();
-}
-
-// out[z] = bf16(in[z]) for a row-major [rows][d] fp32 array, written in the blocked layout; four
-// elements per lane and trip (d a multiple of 4); blockIdx.y = worker
-__global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float *__restrict__ in, long long s_in,
-                                                          bf16_t *__restrict__ out, long long s_out,
-                                                          long long n4, int d)
-{
-    const float4 *src = (const float4 *)(in + (long long)blockIdx.y * s_in);
-    bf16_t *dst = out + (long long)blockIdx.y * s_out;
-    const long long stride = (long long)gridDim.x * 256;
+    const uint32_t t = (uint32_t)st->t;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 128) zero[threadIdx.x] = (bf16_t)0.0f;
+    float4 *x = (float4 *)(X + (long long)blockIdx.y * sX);
+    bf16_t *u = U + (long long)blockIdx.y * sU;
     const int d4 = d >> 2;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
-        const float4 v = src[i];
-        const bf16x4 b = {(bf16_t)v.x, (bf16_t)v.y, (bf16_t)v.z, (bf16_t)v.w};
-        const long long row = i / d4;
-        *(bf16x4 *)(dst + blk_off(row, (i - row * d4) * 4, d)) = b;
-    }
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n4) return;
+    const float4 z = normal4(seed, STREAM_X, blockIdx.y, t, (uint32_t)i);
+    st_nt4(x + i, z);
+    const long long row = i / d4;
+    const bf16x4 b = {(bf16_t)z.x, (bf16_t)z.y, (bf16_t)z.z, (bf16_t)z.w};
+    *(bf16x4 *)(u + blk_off(row, (i - row * d4) * 4, d)) = b;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -358,41 +382,41 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU,
 // ---------------------------------------------------------------------------------------------
 // column sums: final stage of the LayerNorm parameter gradients
 // ---------------------------------------------------------------------------------------------
-// out[z][j] = sum_c PART[z][c][j].  A workgroup owns 64 columns; its 4 wavefronts each sum a
-// contiguous quarter of the chunks in ascending order and the four partial sums are added in
-// wavefront order (fixed order: deterministic).
-__global__ __launch_bounds__(256) void colsum_final_kernel(const float *__restrict__ PART, long long sPART,
+// out[z][j] = sum_c PART[z][c][j].  A workgroup owns 64 columns; its 16 wavefronts each sum a
+// contiguous run of the chunks in ascending order, eight loads in flight, and the partial sums are added in
+// wavefront order (fixed order: deterministic).  (Four wavefronts: 11.8 us for 505 chunks, a chain of loads.)
+constexpr int COLSUM_WAVES = 16;
+__global__ __launch_bounds__(64 * COLSUM_WAVES) void colsum_final_kernel(const float *__restrict__ PART, long long sPART,
                                                            float *__restrict__ out, long long sOut,
                                                            int chunks, int cols)
 {
     // blockIdx.z selects the partial array (0: dgamma, 1: dbeta); the results are adjacent
-    __shared__ float red[4][64];
+    __shared__ float red[COLSUM_WAVES][64];
     const int z = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = blockIdx.x * 64 + lane;
     const float *p = PART + (long long)z * sPART + (long long)blockIdx.z * chunks * cols;
     out += (long long)blockIdx.z * cols;
-    const int per = (chunks + 3) / 4;
+    const int per = (chunks + COLSUM_WAVES - 1) / COLSUM_WAVES;
     const int c0 = wave * per, c1 = min(chunks, c0 + per);
-    // 8 independent partial sums per lane (rows c0+u, c0+u+8, ...), so that 8 loads are in flight;
-    // combined in a fixed order
     float a8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (j < cols) {
-        int c = c0;
-        for (; c + 8 <= c1; c += 8) {
+        for (int c = c0; c < c1; c += 8) {               // a short last run is filled up with zeros
             float r[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) r[u] = p[(long long)(c + u) * cols + j];
+            for (int u = 0; u < 8; ++u) r[u] = p[(long long)min(c + u, c1 - 1) * cols + j];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a8[u] += r[u];
+            for (int u = 0; u < 8; ++u) a8[u] += c + u < c1 ? r[u] : 0.f;
         }
-        for (int u = 0; c < c1; ++c, ++u) a8[u] += p[(long long)c * cols + j];
     }
-    const float acc = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
-    red[wave][lane] = acc;
+    red[wave][lane] = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
     __syncthreads();
-    if (wave == 0 && j < cols)
-        out[(long long)z * sOut + j] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+    if (wave == 0 && j < cols) {
+        float s = red[0][lane];
+#pragma unroll
+        for (int q = 1; q < COLSUM_WAVES; ++q) s += red[q][lane];
+        out[(long long)z * sOut + j] = s;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -427,17 +451,29 @@ __global__ __launch_bounds__(256) void loss_kernel(const float *__restrict__ XL,
     if (threadIdx.x == 0) LPART[(long long)z * sLPART + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-__global__ __launch_bounds__(256) void loss_final_kernel(const float *__restrict__ LPART, long long sLPART,
-                                                         int nparts, float scale, float *__restrict__ loss)
+// (256 lanes took 17 us for 9456 parts, one load after the other)
+__global__ __launch_bounds__(1024) void loss_final_kernel(const float *__restrict__ LPART, long long sLPART,
+                                                          int nparts, float scale, float *__restrict__ loss)
 {
-    __shared__ float red[4];
+    __shared__ float red[16];
     const int z = blockIdx.x;
+    const float *p = LPART + (long long)z * sLPART;
     float acc = 0.f;
-    for (int i = threadIdx.x; i < nparts; i += 256) acc += LPART[(long long)z * sLPART + i];
+    for (int i = threadIdx.x; i < nparts; i += 4096) {
+        float r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = i + u * 1024 < nparts ? p[i + u * 1024] : 0.f;
+        acc += (r[0] + r[1]) + (r[2] + r[3]);
+    }
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) loss[z] = (red[0] + red[1] + red[2] + red[3]) * scale;
+    if (threadIdx.x == 0) {
+        float s = 0.f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s += red[q];
+        loss[z] = s * scale;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -711,14 +747,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     ResWs w = carve(dm, ws, nullptr);
     const long long Md = (long long)M * d;            // a row-major [M][d] array (fp32 state and its relatives)
     const long long MdB = w.mdB, MdhB = w.mdhB;       // a blocked [M][d] / [M][dh] bf16 array
-    // Rows per wavefront of the LayerNorm backward pass: enough that all wavefronts of the launch
-    // are resident at once (a launch of 1.5 times the chip's wavefront slots runs as one full wave of
-    // workgroups and a half-empty one).  Resident wavefronts per CU follow from the kernel's registers.
-    const int vpl_ln = (d + 255) / 256;
-    const int ln_slots = gemm_cu_count() * (vpl_ln <= 1 ? 28 : vpl_ln == 2 ? 20 : vpl_ln == 3 ? 16 : 12);
-    int rows_per_wave = (int)(((long long)K * M + ln_slots - 1) / ln_slots);
-    if (rows_per_wave < LN_ROWS_PER_WAVE) rows_per_wave = LN_ROWS_PER_WAVE;
-    const int wave_rows = (M + rows_per_wave - 1) / rows_per_wave;
+    const int rows_per_wave = ln_rows_per_wave(K, M, d), wave_rows = (M + rows_per_wave - 1) / rows_per_wave;
 
     AttnArgs att{};
     if (heads > 0) {
@@ -761,36 +790,40 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
 #undef LN_BWD
 #undef LN_BWD_ARGS
         TRY(hipGetLastError());
-        colsum_final_kernel<<<dim3((unsigned)((d + 63) / 64), (unsigned)K, 2), 256, 0, s>>>(
+        colsum_final_kernel<<<dim3((unsigned)((d + 63) / 64), (unsigned)K, 2), 64 * COLSUM_WAVES, 0, s>>>(
             w.PART, w.sPART, g + off_gamma, P, wave_rows, d);
         return hipGetLastError();
     };
 
-    TRY(launch_fill_zero((float *)w.ZERO, 64, s));
-    // bf16 copies of the weights in both orientations (the master weights changed last step): one
-    // launch per kind of weight, over all blocks and workers
+    // bf16 copies of the weights in both orientations (the master weights changed last step), and the teacher map
     {
         const long long oW1 = per_attn + 2LL * d, oW2 = oW1 + (long long)d * dh + dh;
-        TRY(launch_cvt_transpose<float>(theta + oW1, dh, P, per_block, w.W1b, w.sW, w.W1Tb, w.sW, d, dh, K, L, s));
-        TRY(launch_cvt_transpose<float>(theta + oW2, d, P, per_block, w.W2b, w.sW, w.W2Tb, w.sW, dh, d, K, L, s));
+        CvtList list{};
+        long long first = 0;
+        auto add = [&](const float *in, long long s_in, bf16_t *out, bf16_t *outT, long long s_out, int R, int C, int n_l, int n_z) {
+            list.m[list.n++] = CvtMat{in, s_in, per_block, out, outT, s_out, R, C, n_l, n_z, (int)first};
+            first += (long long)(R / 64) * (C / 64) * n_l * n_z;
+        };
+        add(theta + oW1, P, w.W1b, w.W1Tb, w.sW, d, dh, L, K);
+        add(theta + oW2, P, w.W2b, w.W2Tb, w.sW, dh, d, L, K);
         if (heads > 0) {
             const long long oWq = 2LL * d, oWo = oWq + 3 * dd + 3LL * d;
-            TRY(launch_cvt_transpose<float>(theta + oWq, 3LL * d, P, per_block, w.Wqb, w.sWq, w.WqTb, w.sWq, d, 3 * d, K, L, s));
-            TRY(launch_cvt_transpose<float>(theta + oWo, d, P, per_block, w.Wob, w.sWo, w.WoTb, w.sWo, d, d, K, L, s));
+            add(theta + oWq, P, w.Wqb, w.WqTb, w.sWq, d, 3 * d, L, K);
+            add(theta + oWo, P, w.Wob, w.WoTb, w.sWo, d, d, L, K);
         }
+        add(teacher, 0, nullptr, w.WTt, 0, d, d, 1, 1);
+        if (first > 0x7FFFFFFFll) return hipErrorInvalidValue;
+        cvt_transpose_kernel<<<(unsigned)first, 256, 0, s>>>(list);
+        TRY(hipGetLastError());
     }
-    TRY(launch_cvt_transpose<float>(teacher, d, 0, 0, nullptr, 0, w.WTt, 0, d, d, 1, 1, s));
     // elements of one block's blocked weight copies: as stored ([rows][cols]) and transposed
     const long long wW1 = w.wB[0], wW1T = w.wB[1], wW2 = w.wB[1], wW2T = w.wB[0];
     const long long wWq = blk_elems(d, 3 * d), wWqT = blk_elems(3 * d, d), wWo = blk_elems(d, d);
 
     // Sample(): tokens x_0 (fp32 in X[0], bf16 in U), teacher targets y = x_0 W_T / sqrt(d)
-    TRY(launch_fill_normal(w.X, w.sX, K, Md, 1.0f, STREAM_X, dm.seed, st, s));
-    {
-        long long blocks = (Md / 4 + 255) / 256; if (blocks > 65535) blocks = 65535;   // d is a multiple of 64
-        f32_to_bf16_kernel<<<dim3((unsigned)blocks, (unsigned)K), 256, 0, s>>>(w.X, w.sX, w.U, w.sU, Md / 4, d);
-        TRY(hipGetLastError());
-    }
+    sample_tokens_kernel<<<dim3((unsigned)((Md / 4 + 255) / 256), (unsigned)K), 256, 0, s>>>(
+        w.X, w.sX, w.U, w.sU, Md / 4, d, dm.seed, st, w.ZERO);
+    TRY(hipGetLastError());
     {
         GemmNT p{w.U, w.WTt, M, d, d, d, d, w.sU, 0};
         EpiScaleF32 epi{w.Y, d, w.sY, 1.0f / sqrtf((float)d)};
@@ -843,7 +876,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         loss_kernel<<<dim3((unsigned)nparts, (unsigned)K), 256, 0, s>>>(
             w.X + (long long)(nsub * L) * Md, w.sX, w.Y, w.sY, w.DX, w.sDX, w.DXb, w.sDXb, w.LPART, w.sLPART, Md, inv);
         TRY(hipGetLastError());
-        loss_final_kernel<<<K, 256, 0, s>>>(w.LPART, w.sLPART, nparts, 0.5f * inv, loss);
+        loss_final_kernel<<<K, 1024, 0, s>>>(w.LPART, w.sLPART, nparts, 0.5f * inv, loss);
         TRY(hipGetLastError());
     }
 
