@@ -13,6 +13,7 @@ namespace qsr {
 struct Mlp2Ws {
     float *X, *hid, *dhid, *logit;
     float *part;           // [K][tiles of 16 rows][17]: column sums of dlogit and the summed loss of a tile
+                           // (more than 16 classes: [K][B], the samples' losses)
     int *label;
 };
 
@@ -90,56 +91,44 @@ __global__ __launch_bounds__(64) void mlp2_sample_kernel(float *__restrict__ X, 
     }
 }
 
-// More than 16 classes: per sample, logits -> (softmax - onehot)/B in place; per worker, the mean
-// cross-entropy.  One block per worker, samples strided over its threads.
+// More than 16 classes: logits -> (softmax - onehot)/B in place, and the sample's cross-entropy.  One wavefront per
+// sample, the classes across its lanes (as one lane per sample and one workgroup per worker it took 43 us for
+// 5 x 50 samples of 100 classes).
 __global__ __launch_bounds__(256) void mlp2_softmax_ce_kernel(float *__restrict__ z_dz,
                                                               const int *__restrict__ label,
-                                                              float *__restrict__ loss, long long B, int C)
+                                                              float *__restrict__ sample_loss, long long B, int C)
 {
-    __shared__ float red[4];
-    const int k = blockIdx.x;
+    const int k = blockIdx.y, lane = threadIdx.x & 63;
+    const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= B) return;
     const float invB = 1.0f / (float)B;
-    float lsum = 0.f;
-    for (long long i = threadIdx.x; i < B; i += 256) {
-        float *z = z_dz + ((long long)k * B + i) * C;
-        const int y = label[(long long)k * B + i];
-        float mx = z[0];
-        for (int o = 1; o < C; ++o) mx = fmaxf(mx, z[o]);
-        float se = 0.f;
-        for (int o = 0; o < C; ++o) se += expf(z[o] - mx);
-        lsum += logf(se) - (z[y] - mx);
-        const float inv = 1.0f / se;
-        for (int o = 0; o < C; ++o) z[o] = (expf(z[o] - mx) * inv - (o == y ? 1.f : 0.f)) * invB;
-    }
+    float *z = z_dz + ((long long)k * B + i) * C;
+    const int y = label[(long long)k * B + i];
+    float v[16];                                         // C <= 1024
+    float mx = -INFINITY;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_down(lsum, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = lsum;
-    __syncthreads();
-    if (threadIdx.x == 0) loss[k] = (red[0] + red[1] + red[2] + red[3]) * invB;
-}
-
-// out[k][j] = sum_i A[k][i][j]   (bias gradients).  One thread per column, rows added in ascending
-// order; eight loads are in flight at a time, since the launch has too few wavefronts to hide the
-// latency of one load per addition.
-__global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ A,
-                                                     float *__restrict__ out, long long rows,
-                                                     long long cols, long long sA, long long sOut)
-{
-    const int k = blockIdx.y;
-    const long long j = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (j >= cols) return;
-    const float *a = A + (long long)k * sA + j;
-    float acc = 0.f;
-    long long i = 0;
-    for (; i + 8 <= rows; i += 8) {
-        float v[8];
+    for (int u = 0; u < 16; ++u)
+        if (u * 64 < C) {
+            v[u] = u * 64 + lane < C ? z[u * 64 + lane] : -INFINITY;
+            mx = fmaxf(mx, v[u]);
+        }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = a[(i + u) * cols];
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    float se = 0.f, zy = 0.f;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u];
-    }
-    for (; i < rows; ++i) acc += a[i * cols];
-    out[(long long)k * sOut + j] = acc;
+    for (int u = 0; u < 16; ++u)
+        if (u * 64 < C) {
+            if (u * 64 + lane == y) zy = v[u] - mx;
+            v[u] = u * 64 + lane < C ? expf(v[u] - mx) : 0.f;
+            se += v[u];
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { se += __shfl_xor(se, o, 64); zy += __shfl_xor(zy, o, 64); }
+    const float inv = 1.0f / se;
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+        if (u * 64 + lane < C) z[u * 64 + lane] = (v[u] * inv - (u * 64 + lane == y ? 1.f : 0.f)) * invB;
+    if (lane == 0) sample_loss[(long long)k * B + i] = logf(se) - zy;
 }
 
 // Output layer forward and loss for at most 16 classes, one workgroup per 16 samples of a worker:
@@ -381,7 +370,7 @@ hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, co
         a.C = w.logit; a.ldc = dz; a.sC = B * dz;
         a.M = (int)B; a.N = (int)dz; a.Kd = (int)dh; a.bias = theta + ob2; a.sBias = P;
         if ((e = launch_dgemm_nn<EPI_BIAS>(a, K, s)) != hipSuccess) return e;
-        mlp2_softmax_ce_kernel<<<K, 256, 0, s>>>(w.logit, w.label, loss, B, (int)dz);
+        mlp2_softmax_ce_kernel<<<dim3((unsigned)((B + 3) / 4), (unsigned)K), 256, 0, s>>>(w.logit, w.label, w.part, B, (int)dz);
         if ((e = hipGetLastError()) != hipSuccess) return e;
 
         // backward; w.logit now holds d loss / d logits
@@ -390,10 +379,9 @@ hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, co
         a.B = w.logit; a.ldb = dz; a.sB = B * dz;
         a.C = g + oW2; a.ldc = dz; a.sC = P;
         a.M = (int)dh; a.N = (int)dz; a.Kd = (int)B;
+        a.colsum = g + ob2; a.sCol = P;                        // gb2, and the mean cross-entropy
+        a.part = w.part; a.n_part = (int)B; a.part_out = loss; a.part_scale = 1.0f / (float)B;
         if ((e = launch_sgemm<true, false, EPI_NONE>(a, K, s)) != hipSuccess) return e;
-        colsum_kernel<<<dim3((unsigned)((dz + 255) / 256), (unsigned)K), 256, 0, s>>>(
-            w.logit, g + ob2, B, dz, B * dz, P);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
 
         a = GemmArgs{};                                        // dhid = (dlogits W2^T) * [hid > 0]
         a.A = w.logit; a.lda = dz; a.sA = B * dz;
@@ -401,9 +389,6 @@ hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, co
         a.C = w.dhid; a.ldc = dh; a.sC = B * dh;
         a.M = (int)B; a.N = (int)dh; a.Kd = (int)dz; a.aux = w.hid;
         if ((e = launch_sgemm<false, true, EPI_MASK_POS>(a, K, s)) != hipSuccess) return e;
-        colsum_kernel<<<dim3((unsigned)((dh + 255) / 256), (unsigned)K), 256, 0, s>>>(
-            w.dhid, g + ob1, B, dh, B * dh, P);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
 
     a = GemmArgs{};                                        // gW1 = X^T dhid
@@ -411,6 +396,7 @@ hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, co
     a.B = w.dhid; a.ldb = dh; a.sB = B * dh;
     a.C = g + oW1; a.ldc = dh; a.sC = P;
     a.M = (int)di; a.N = (int)dh; a.Kd = (int)B;
+    if (dz > 16) { a.colsum = g + ob1; a.sCol = P; }       // gb1 (else the output layer's backward kernel has done it)
     return launch_sgemm<true, false, EPI_NONE>(a, K, s);
 }
 

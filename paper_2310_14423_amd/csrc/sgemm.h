@@ -27,6 +27,11 @@ struct GemmArgs {
     const float *bias;         // [N], per-batch stride sBias
     long long sBias;
     const float *aux;          // EPI_MASK_POS: same layout as C; C = aux > 0 ? acc : 0
+    // weight gradients (A transposed, B as it is): column sums of B as a by-product, the bias gradient
+    float *colsum;             // [N], per-batch stride sCol, or nullptr
+    long long sCol;
+    const float *part;         // with colsum, or nullptr: out[b] = scale * sum of part[b*n_part ..], fixed order
+    int n_part; float *part_out; float part_scale;
 };
 
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
@@ -35,8 +40,8 @@ template <bool TA, bool TB, int EPI, int KSPLIT>
 __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
 {
     constexpr int TM = 64, TN = 64, TK = 16, PAD = 32;   // rows k and k+1 of a slab 32 banks apart
-    __shared__ float As_all[KSPLIT][TK][TM + PAD];
-    __shared__ float Bs_all[KSPLIT][TK][TN + PAD];
+    __shared__ __attribute__((aligned(16))) float As_all[KSPLIT][TK][TM + PAD];
+    __shared__ __attribute__((aligned(16))) float Bs_all[KSPLIT][TK][TN + PAD];
     // The workgroup is KSPLIT groups of 256 threads; group grp contracts over its own run of
     // slabs with its own LDS slabs.  With one workgroup of four wavefronts per compute unit (the
     // batch is 128 rows) every slab's load -> LDS -> barrier -> MFMA chain ran unhidden; a second
@@ -65,7 +70,21 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
     constexpr int PF = 3;
     constexpr int R = TK / 4;                       // elements of each operand per thread and slab
     float ra[PF][R], rb[PF][R];
+    // A transposed, B as it is: both run along their rows, one 128-bit load of each per thread and slab where
+    // rows and bases are 16-byte aligned
+    const bool vec = TA && !TB && ((a.lda | a.ldb | a.M | a.N) & 3) == 0 &&
+                     ((((unsigned long long)A) | ((unsigned long long)B)) & 15) == 0;
+    const int vk = tid >> 4, vc = (tid & 15) * 4;
     auto gload = [&](int k0, float (&xa)[R], float (&xb)[R]) {
+        if (vec) {
+            float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
+            const int gk = k0 + vk;
+            if (gk < a.Kd && m0 + vc < a.M) va = *(const float4 *)(A + (long long)gk * a.lda + m0 + vc);
+            if (gk < a.Kd && n0 + vc < a.N) vb = *(const float4 *)(B + (long long)gk * a.ldb + n0 + vc);
+            xa[0] = va.x; xa[1] = va.y; xa[2] = va.z; xa[3] = va.w;
+            xb[0] = vb.x; xb[1] = vb.y; xb[2] = vb.z; xb[3] = vb.w;
+            return;
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             int kk, m;
@@ -88,6 +107,11 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
         }
     };
     auto sstore = [&](const float (&xa)[R], const float (&xb)[R]) {
+        if (vec) {
+            *(float4 *)&As[vk][vc] = make_float4(xa[0], xa[1], xa[2], xa[3]);
+            *(float4 *)&Bs[vk][vc] = make_float4(xb[0], xb[1], xb[2], xb[3]);
+            return;
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (TA) As[(tid >> 6) + 4 * r][tid & 63] = xa[r];
@@ -100,6 +124,8 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
     // Kd load zeros
     const int nslab = ((a.Kd + TK - 1) / TK + KSPLIT - 1) / KSPLIT;
     const int kbase = grp * nslab * TK;
+    const bool col_wg = TA && !TB && a.colsum != nullptr && blockIdx.y == 0;   // the workgroups of the first rows
+    float cs = 0.f;
 #pragma unroll
     for (int u = 0; u < PF; ++u)
         if (u < nslab) gload(kbase + u * TK, ra[u], rb[u]);
@@ -111,6 +137,10 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
                 sstore(ra[u], rb[u]);
                 if (sl + PF < nslab) gload(kbase + (sl + PF) * TK, ra[u], rb[u]);
                 __syncthreads();
+                if (TA && !TB && col_wg && tid < 64) {
+#pragma unroll
+                    for (int kk = 0; kk < TK; ++kk) cs += Bs[kk][tid];
+                }
                     // lane l supplies A[row l%32][k l/32] and B[k l/32][column l%32] of the instruction
 #pragma unroll
                 for (int kk = 0; kk < TK; kk += 2) {
@@ -123,6 +153,23 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
         }
     }
 
+    if (TA && !TB && col_wg) {
+        if (tid < 64) As[0][tid] = cs;                // the slabs are done with
+        __syncthreads();
+        if (grp == 0 && tid < 64 && n0 + tid < a.N) {
+            float v = As_all[0][0][tid];
+#pragma unroll
+            for (int g = 1; g < KSPLIT; ++g) v += As_all[g][0][tid];
+            a.colsum[bz * a.sCol + n0 + tid] = v;
+        }
+        if (a.part != nullptr && blockIdx.x == 0 && threadIdx.x < 64) {
+            float v = 0.f;
+            for (int i = lane; i < a.n_part; i += 64) v += a.part[bz * a.n_part + i];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+            if (lane == 0) a.part_out[bz] = v * a.part_scale;
+        }
+    }
     float *C = a.C + bz * a.sC;
     if constexpr (KSPLIT > 1) {       // the other groups' partial sums, added in group order
         __shared__ float part[KSPLIT - 1][4][16][64];
@@ -156,7 +203,9 @@ template <bool TA, bool TB, int EPI>
 inline hipError_t launch_sgemm(const GemmArgs &a, int batch, hipStream_t s)
 {
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 63) / 64), (unsigned)batch);
-    if (a.Kd >= 256) sgemm_kernel<TA, TB, EPI, 2><<<grid, 512, 0, s>>>(a);
+    // two groups per workgroup for a long contraction, and for a shorter one that would leave compute units idle
+    const long long wgs = (long long)grid.x * grid.y * grid.z;
+    if (a.Kd >= 256 || (a.Kd >= 64 && wgs < 256)) sgemm_kernel<TA, TB, EPI, 2><<<grid, 512, 0, s>>>(a);
     else sgemm_kernel<TA, TB, EPI, 1><<<grid, 256, 0, s>>>(a);
     return hipGetLastError();
 }
@@ -170,14 +219,17 @@ inline hipError_t launch_sgemm(const GemmArgs &a, int batch, hipStream_t s)
 // order of k inside a group of 16 is a permutation, the same for both operands).  The LDS-tiled
 // form above ran 8 x 128 x 784 x 1024 in 50.5 us with two groups; this one 52.2 us with two and
 // 46.7 us with four (35 TFLOP/s; the instruction's measured issue rate is 47).
-template <int EPI, int KSPLIT>
-__global__ __launch_bounds__(256 * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
+// WT = 1: 32x32 output tile, a group is one wavefront: for problems of few tiles, where more workgroups and shorter
+// shares of the contraction count (5 x 50 x 333 x 500 and 5 x 50 x 500 x 100: 28-32 us with 64x64 tiles and two
+// groups, 13.7 us with 32x32 and sixteen).
+template <int EPI, int KSPLIT, int WT>
+__global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
 {
-    constexpr int PF = 3;
-    const int grp = threadIdx.x >> 8, tid = threadIdx.x & 255;
+    constexpr int PF = 3, TILE = WT == 4 ? 64 : 32;
+    const int grp = threadIdx.x / (64 * WT), tid = threadIdx.x % (64 * WT);
     const int lane = tid & 63, wm = tid >> 7, wn = (tid >> 6) & 1;
     const int r = lane & 15, q = lane >> 4;
-    const int m0 = blockIdx.y * 64 + wm * 32, n0 = blockIdx.x * 64 + wn * 32;
+    const int m0 = blockIdx.y * TILE + wm * 32, n0 = blockIdx.x * TILE + wn * 32;
     const long long bz = blockIdx.z;
     const float *A = a.A + bz * a.sA;
     const float *B = a.B + bz * a.sB;
@@ -246,7 +298,7 @@ __global__ __launch_bounds__(256 * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
 
     float *C = a.C + bz * a.sC;
     if constexpr (KSPLIT > 1) {       // the groups' partial sums, added pairwise in a fixed order
-        __shared__ double dpart[KSPLIT / 2][4][16][64];
+        __shared__ double dpart[KSPLIT / 2][WT][16][64];
 #pragma unroll
         for (int stride = KSPLIT / 2; stride >= 1; stride >>= 1) {
             if (grp >= stride && grp < 2 * stride) {
@@ -283,11 +335,18 @@ template <int EPI>
 inline hipError_t launch_dgemm_nn(const GemmArgs &a, int batch, hipStream_t s)
 {
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 63) / 64), (unsigned)batch);
+    if ((long long)grid.x * grid.y * grid.z < 200) {      // below that even 64x64 tiles with four groups leave the chip idle
+        dim3 small((unsigned)((a.N + 31) / 32), (unsigned)((a.M + 31) / 32), (unsigned)batch);
+        if (a.Kd >= 256) dgemm_nn_kernel<EPI, 16, 1><<<small, 1024, 0, s>>>(a);
+        else if (a.Kd >= 64) dgemm_nn_kernel<EPI, 4, 1><<<small, 256, 0, s>>>(a);
+        else dgemm_nn_kernel<EPI, 1, 1><<<small, 64, 0, s>>>(a);
+        return hipGetLastError();
+    }
     // measured issue rate of the fp64 matrix instruction on MI355X: 33 TFLOP/s with one wavefront per
     // SIMD, 44 with two, 47 with four (registers only, four independent accumulators each)
-    if (a.Kd >= 512) dgemm_nn_kernel<EPI, 4><<<grid, 1024, 0, s>>>(a);
-    else if (a.Kd >= 128) dgemm_nn_kernel<EPI, 2><<<grid, 512, 0, s>>>(a);
-    else dgemm_nn_kernel<EPI, 1><<<grid, 256, 0, s>>>(a);
+    if (a.Kd >= 512) dgemm_nn_kernel<EPI, 4, 4><<<grid, 1024, 0, s>>>(a);
+    else if (a.Kd >= 128) dgemm_nn_kernel<EPI, 2, 4><<<grid, 512, 0, s>>>(a);
+    else dgemm_nn_kernel<EPI, 1, 4><<<grid, 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
