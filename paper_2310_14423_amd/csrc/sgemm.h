@@ -218,7 +218,7 @@ inline hipError_t launch_sgemm(const GemmArgs &a, int batch, hipStream_t s)
 // along k feeds four instructions in a row, the matching four rows of B one element each; the
 // order of k inside a group of 16 is a permutation, the same for both operands).  The LDS-tiled
 // form above ran 8 x 128 x 784 x 1024 in 50.5 us with two groups; this one 52.2 us with two and
-// 46.7 us with four (35 TFLOP/s; the instruction's measured issue rate is 47).
+// 46.7 us with four (35 TFLOP/s).  Kept for rows that 128-bit copies cannot take (dgemm_nn_lds_kernel below).
 // WT = 1: 32x32 output tile, a group is one wavefront: for problems of few tiles, where more workgroups and shorter
 // shares of the contraction count (5 x 50 x 333 x 500 and 5 x 50 x 500 x 100: 28-32 us with 64x64 tiles and two
 // groups, 13.7 us with 32x32 and sixteen).
@@ -331,19 +331,220 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
             }
 }
 
+// The same product where rows and bases allow 128-bit copies of A (and 32- or 128-bit copies of B, BX4): every
+// wavefront keeps a ring of NS stages of 16 k (32 rows of A, 32 columns of B, 4 KiB) in LDS of its own, copied
+// there directly (global_load_lds), so there is no barrier in the main loop and no load whose arrival stalls the
+// wavefront: a stage's fragments are read while the stage before is multiplied.  In LDS the 16-byte pieces of
+// an A row (64 B) are permuted by (row / 4) % 4 and the 64-byte groups of two B rows by (k / 4) % 4, which makes the
+// 128-bit reads of A and the 32-bit reads of B free of bank conflicts.  k beyond Kd is cleared in the
+// registers, rows and columns beyond the matrix are clamped and not stored.
+// The fp64 matrix instruction issues at 75-78 TFLOP/s from one wavefront per SIMD on (70-72 with the conversions);
+// 8 x 128 x 784 x 1024: 46.3 us with guarded loads straight to registers, 35.9 us this way (four groups, two stages;
+// two groups and four stages 37.2, one group 47.6).
+template <int EPI, int KSPLIT, int WT, int NS, bool BX4>
+__global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_lds_kernel(GemmArgs a)
+{
+    constexpr int TILE = WT == 4 ? 64 : 32, STAGE = 1024;    // floats per stage: 512 of A, 512 of B
+    constexpr int CP = 2 + (BX4 ? 2 : 8);                    // copies per stage
+    extern __shared__ __attribute__((aligned(1024))) float dg_ring[];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = wv / WT, w4 = wv % WT, wm = WT == 4 ? w4 >> 1 : 0, wn = WT == 4 ? w4 & 1 : 0;
+    const int r = lane & 15, q = lane >> 4;
+    const int m0 = blockIdx.y * TILE + wm * 32, n0 = blockIdx.x * TILE + wn * 32;
+    const long long bz = blockIdx.z;
+    const float *A = a.A + bz * a.sA;
+    const float *B = a.B + bz * a.sB;
+    float *ring = dg_ring + wv * NS * STAGE;
+    const int ng = (a.Kd + 15) / 16, per = (ng + KSPLIT - 1) / KSPLIT;
+    const int g0 = grp * per, nk = max(0, min(ng, g0 + per) - g0);
+
+    // the lane's place in each 1 KiB (256 B) copy: row of A and its piece, k and column of B
+    const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)ring;
+    constexpr int CB = BX4 ? 2 : 8;
+    const float *srcA[2], *srcB[CB];
+    int kA[2], kB[CB];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int row = c * 16 + (lane >> 2);
+        kA[c] = ((lane & 3) ^ ((row >> 2) & 3)) * 4;
+        srcA[c] = A + (long long)min(m0 + row, a.M - 1) * a.lda + g0 * 16 + kA[c];
+    }
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        // pair of rows pp, 64-byte group gl (in memory order: column half + 2 * row parity), column inside it
+        const int pp = BX4 ? c * 4 + (lane >> 4) : c;
+        const int gl = (BX4 ? (lane >> 2) & 3 : lane >> 4) ^ ((pp >> 1) & 3);
+        const int col = (gl & 1) * 16 + (BX4 ? (lane & 3) * 4 : lane & 15);
+        kB[c] = pp * 2 + (gl >> 1);
+        srcB[c] = B + min(n0 + col, BX4 ? a.N - 4 : a.N - 1) + (long long)(g0 * 16 + kB[c]) * a.ldb;
+    }
+    const long long stepB = 16 * a.ldb;
+    int d_slot = 0, d_k = g0 * 16;                           // slot and first k of the next stage to copy
+    auto issue = [&]() {
+        const unsigned dst = __builtin_amdgcn_readfirstlane(lds_ring + d_slot * (STAGE * 4));
+        if (d_k + 16 > a.Kd) {                               // k is clamped, and cleared once it is in registers
+#pragma unroll
+            for (int c = 0; c < 2; ++c) srcA[c] -= max(d_k + kA[c] - (a.Kd - 4), 0);
+#pragma unroll
+            for (int c = 0; c < CB; ++c) srcB[c] -= (long long)max(d_k + kB[c] - (a.Kd - 1), 0) * a.ldb;
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            // as asm: behind the builtin, the compiler takes every LDS read for a possible reader of the copies in flight
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst + c * 1024), "v"(srcA[c]) : "memory");
+            srcA[c] += 16;
+        }
+#pragma unroll
+        for (int c = 0; c < CB; ++c) {
+            if (BX4) asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst + 2048 + c * 1024), "v"(srcB[c]) : "memory");
+            else asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" :: "s"(dst + 2048 + c * 256), "v"(srcB[c]) : "memory");
+            srcB[c] += stepB;
+        }
+        d_slot = d_slot + 1 == NS ? 0 : d_slot + 1;
+        d_k += 16;
+    };
+    struct Frag { float4 a[2]; float b[2][4]; } fr[2];
+    auto read = [&](int slot, Frag &f) {
+        const float *sa = ring + slot * STAGE, *sb = sa + 512;
+#pragma unroll
+        for (int bi = 0; bi < 2; ++bi) {
+            const int row = bi * 16 + r;
+            f.a[bi] = *(const float4 *)(sa + row * 16 + ((q ^ ((row >> 2) & 3)) * 4));
+        }
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {                    // k = 4 q + j of the stage
+                const int k = 4 * q + j;
+                f.b[bj][j] = sb[(k >> 1) * 64 + (((bj + 2 * (k & 1)) ^ q) * 16) + r];
+            }
+    };
+    f64x4_t dacc[2][2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { dacc[0][0][e] = 0.0; dacc[0][1][e] = 0.0; dacc[1][0][e] = 0.0; dacc[1][1][e] = 0.0; }
+    auto multiply = [&](const Frag &f) {
+        const float av[2][4] = {{f.a[0].x, f.a[0].y, f.a[0].z, f.a[0].w}, {f.a[1].x, f.a[1].y, f.a[1].z, f.a[1].w}};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                for (int bj = 0; bj < 2; ++bj)
+                    dacc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[bi][j], (double)f.b[bj][j], dacc[bi][bj], 0, 0, 0);
+    };
+    auto clear_tail = [&](Frag &f, int k0) {                 // k >= Kd
+        float *x[2] = {&f.a[0].x, &f.a[1].x};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (k0 + 4 * q + j >= a.Kd) { x[0][j] = 0.f; x[1][j] = 0.f; f.b[0][j] = 0.f; f.b[1][j] = 0.f; }
+    };
+    // vmcnt(n): at most n of this wavefront's copies outstanding
+#define DG_WAIT_VM(n) do { asm volatile("" ::: "memory"); __builtin_amdgcn_s_waitcnt(0x0f70 | ((n) & 15) | (((n) >> 4) << 14)); asm volatile("" ::: "memory"); } while (0)
+#define DG_WAIT_LDS() do { asm volatile("" ::: "memory"); __builtin_amdgcn_s_waitcnt(0xc07f); asm volatile("" ::: "memory"); } while (0)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (s < nk) issue();
+    if (nk > 0) {
+        if (nk >= NS) DG_WAIT_VM(CP * (NS - 1)); else DG_WAIT_VM(0);
+        read(0, fr[0]);
+        if (nk == 1) clear_tail(fr[0], g0 * 16);
+        int slot = 0;
+        for (int kt = 0; kt < nk; kt += 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int k = kt + u;
+                if (k >= nk) break;
+                DG_WAIT_LDS();                               // the fragments of stage k are in: its slot is free
+                if (k + NS < nk) issue();
+                slot = slot + 1 == NS ? 0 : slot + 1;
+                if (k + 1 < nk) {
+                    if (k + NS < nk) DG_WAIT_VM(CP * (NS - 1));      // stage k + 1 has landed
+                    else DG_WAIT_VM(0);
+                    read(slot, fr[u ^ 1]);
+                    if (k + 2 == nk) clear_tail(fr[u ^ 1], (g0 + k + 1) * 16);
+                }
+                multiply(fr[u]);
+            }
+        }
+    }
+    float *C = a.C + bz * a.sC;
+    if constexpr (KSPLIT > 1) {       // the groups' partial sums, added pairwise in a fixed order
+        __syncthreads();              // the rings are done with
+        double *dpart = (double *)dg_ring;
+#pragma unroll
+        for (int stride = KSPLIT / 2; stride >= 1; stride >>= 1) {
+            if (grp >= stride && grp < 2 * stride) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) dpart[(((grp - stride) * WT + w4) * 16 + i) * 64 + lane] = dacc[i >> 3][(i >> 2) & 1][i & 3];
+            }
+            __syncthreads();
+            if (grp < stride) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) dacc[i >> 3][(i >> 2) & 1][i & 3] += dpart[((grp * WT + w4) * 16 + i) * 64 + lane];
+            }
+            __syncthreads();
+        }
+        if (grp > 0) return;
+    }
+    // accumulator element e of lane l is C[4*e + l/16][l%16] of its 16x16 block
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int gm = m0 + bi * 16 + 4 * e + q;
+                const int gn = n0 + bj * 16 + r;
+                if (gm >= a.M || gn >= a.N) continue;
+                double v = dacc[bi][bj][e];
+                if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS) v += (double)a.bias[bz * a.sBias + gn];
+                if (EPI == EPI_BIAS_RELU) v = v > 0.0 ? v : 0.0;
+                C[(long long)gm * a.ldc + gn] = (float)v;
+            }
+#undef DG_WAIT_VM
+#undef DG_WAIT_LDS
+}
+
+template <int EPI, int KSPLIT, int WT, int NS>
+inline hipError_t launch_dgemm_lds(const GemmArgs &a, int batch, bool bx4, hipStream_t s)
+{
+    constexpr int TILE = WT == 4 ? 64 : 32;
+    constexpr size_t ring = (size_t)WT * KSPLIT * NS * 4096, parts = (size_t)(KSPLIT / 2) * WT * 16 * 64 * 8;
+    constexpr size_t smem = ring > parts ? ring : parts;
+    static_assert(smem <= 160 * 1024, "rings");
+    static bool raised = false;               // per instantiation; contexts are not thread-safe
+    if (smem > 64 * 1024 && !raised) {
+        hipError_t e = hipFuncSetAttribute((const void *)dgemm_nn_lds_kernel<EPI, KSPLIT, WT, NS, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)dgemm_nn_lds_kernel<EPI, KSPLIT, WT, NS, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    dim3 grid((unsigned)((a.N + TILE - 1) / TILE), (unsigned)((a.M + TILE - 1) / TILE), (unsigned)batch);
+    if (bx4) dgemm_nn_lds_kernel<EPI, KSPLIT, WT, NS, true><<<grid, 64 * WT * KSPLIT, smem, s>>>(a);
+    else dgemm_nn_lds_kernel<EPI, KSPLIT, WT, NS, false><<<grid, 64 * WT * KSPLIT, smem, s>>>(a);
+    return hipGetLastError();
+}
+
 template <int EPI>
 inline hipError_t launch_dgemm_nn(const GemmArgs &a, int batch, hipStream_t s)
 {
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 63) / 64), (unsigned)batch);
-    if ((long long)grid.x * grid.y * grid.z < 200) {      // below that even 64x64 tiles with four groups leave the chip idle
+    const bool few = (long long)grid.x * grid.y * grid.z < 200;
+    // 128-bit copies of A: 16-byte rows in every batch entry; of B as well, or 32-bit ones
+    const bool ax4 = ((a.lda | a.sA | a.Kd) & 3) == 0 && (((unsigned long long)a.A) & 15) == 0;
+    const bool bx4 = ((a.ldb | a.sB | a.N) & 3) == 0 && (((unsigned long long)a.B) & 15) == 0;
+    if (ax4 && a.Kd >= 64) {
+        if (!few) return launch_dgemm_lds<EPI, 4, 4, 2>(a, batch, bx4, s);
+        if (a.Kd >= 256) return launch_dgemm_lds<EPI, 16, 1, 2>(a, batch, bx4, s);
+        return launch_dgemm_lds<EPI, 4, 1, 4>(a, batch, bx4, s);
+    }
+    if (few) {      // below that even 64x64 tiles with four groups leave the chip idle
         dim3 small((unsigned)((a.N + 31) / 32), (unsigned)((a.M + 31) / 32), (unsigned)batch);
         if (a.Kd >= 256) dgemm_nn_kernel<EPI, 16, 1><<<small, 1024, 0, s>>>(a);
         else if (a.Kd >= 64) dgemm_nn_kernel<EPI, 4, 1><<<small, 256, 0, s>>>(a);
         else dgemm_nn_kernel<EPI, 1, 1><<<small, 64, 0, s>>>(a);
         return hipGetLastError();
     }
-    // measured issue rate of the fp64 matrix instruction on MI355X: 33 TFLOP/s with one wavefront per
-    // SIMD, 44 with two, 47 with four (registers only, four independent accumulators each)
     if (a.Kd >= 512) dgemm_nn_kernel<EPI, 4, 4><<<grid, 1024, 0, s>>>(a);
     else if (a.Kd >= 128) dgemm_nn_kernel<EPI, 2, 4><<<grid, 512, 0, s>>>(a);
     else dgemm_nn_kernel<EPI, 1, 4><<<grid, 256, 0, s>>>(a);

@@ -1,0 +1,21 @@
+"""GPU: the perceptron's gradient at the sizes where its kernels change form: fp64 products through LDS rings or
+straight from memory, 128- or 32-bit copies, contractions that are no multiple of a stage or shorter than the
+wavefronts' shares, few and many tiles, many classes (column sums and loss inside the GEMMs)."""
+import pytest
+
+from test_gpu_parity import test_mlp2_gradient_single_step as gradient_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dims", [
+    dict(d_in=260, d_hidden=72, d_out=20, B_loc=21, K=3),       # 32 x 32 tiles; shares without a stage; rows 16-byte aligned
+    dict(d_in=64, d_hidden=1000, d_out=4, B_loc=70, K=8),       # 64 x 64 tiles, 128-bit copies of the weights, four stages
+    dict(d_in=68, d_hidden=1000, d_out=5, B_loc=70, K=8),       # 32-bit copies, a last stage of four
+    dict(d_in=67, d_hidden=1000, d_out=5, B_loc=70, K=8),       # straight from memory, many tiles
+    dict(d_in=333, d_hidden=50, d_out=100, B_loc=5, K=2),       # straight from memory, few tiles
+    dict(d_in=32, d_hidden=64, d_out=1024, B_loc=9, K=1),       # the most classes
+    dict(d_in=48, d_hidden=17, d_out=65, B_loc=130, K=2),       # one class beyond a wavefront's lanes
+])
+def test_gradient_where_the_kernels_change(dims):
+    gradient_case(dims)
