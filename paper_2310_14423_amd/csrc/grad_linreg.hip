@@ -225,7 +225,16 @@ hipError_t launch_linreg_grad(const ModelDims &d, const float *theta, float *g, 
     return hipGetLastError();
 }
 
-bool linreg_can_fuse(const ModelDims &d) { return d.K <= 16; }   // a wavefront per worker in a workgroup
+// A wavefront per worker in a workgroup, and no share of samples so long that its chain of loads outlasts the wider
+// gradient kernel and a separate update.  One iteration, fused against separate (us; as it was):
+//   16 x 1024 features x 64 samples 16.4 / 13.3 (15.3), x 128 27.0 / 19.3 (20.7);  9 x 1024 x 32 9.8 / 9.8 (12.0),
+//   x 64 13.4 / 11.9 (13.9);  8 x 1024 x 128 16.3 / 16.0 (17.7);  5 x 1024 x 128 13.0 / 14.8 (16.7)
+bool linreg_can_fuse(const ModelDims &d)
+{
+    if (d.K > 16) return false;
+    const long long S = 16 / d.K, per = (d.B + S - 1) / S;
+    return per <= (S > 1 ? 64 : 32);
+}
 
 hipError_t launch_linreg_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
                                   const DevState *st, hipStream_t s)

@@ -1,4 +1,4 @@
-"""GPU: the least-squares iteration in two kernels (up to 16 workers; three beyond) at the sizes where it can go
+"""GPU: the least-squares iteration in two kernels (up to 16 workers and 32 or 64 samples per wavefront; more beyond) at the sizes where it can go
 wrong: feature counts that are no multiple of 4 or 64, few and many samples per wavefront, the largest number of
 workers of a workgroup; one by one and replayed, against each other bit for bit and against the oracle."""
 import numpy as np
@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("K,d,B,opt", [(3, 1003, 17, "sgdm"), (16, 131, 76, "sgdm"), (17, 66, 9, "sgdm"), (1, 5, 1, "sgdm"),
-                                       (5, 65, 33, "adamw"), (9, 1024, 8, "adamw"), (4, 64, 128, "sgdm"), (2, 3, 5, "adamw")])
+                                       (5, 65, 33, "adamw"), (9, 1024, 8, "adamw"), (4, 64, 128, "sgdm"), (2, 3, 5, "adamw"),
+                                       (9, 66, 32, "sgdm"), (9, 66, 33, "adamw"), (8, 70, 128, "sgdm"), (8, 70, 129, "sgdm")])
 def test_least_squares_shapes(K, d, B, opt):
     import torch
     kw = dict(mu=0.9, lam=1e-4) if opt == "sgdm" else dict(beta1=0.9, beta2=0.99, eps=1e-3, lam=0.01)
