@@ -15,8 +15,7 @@
  * points live in device memory; the two calls above only enqueue kernels on the caller's
  * stream and never synchronise.  The host keeps a mirror of the four integers, advanced with the
  * same arithmetic from the same table, which only decides which kernels are enqueued for an
- * iteration (an averaging kernel where a round ends; where none ends, the update kernel may carry the
- * scheduler's counting step instead of a launch of its own); the device takes every decision again,
+ * iteration (an averaging kernel where a round ends); the device takes every decision again,
  * logs the rounds, and any disagreement
  * between the two is reported as QSR_EMIRROR by the calls that read the state.  All `float*` / `void*` buffer arguments are DEVICE
  * pointers unless marked (host); they stay owned by the caller, who must keep them alive
@@ -225,7 +224,8 @@ int qsr_restart(qsr_ctx *ctx);
  * averaged, 3 = averaging launches that the device-side decision skipped (none when the
  * iterations are enqueued one by one: an averaging kernel is then launched only where a round
  * ends).  With fuse_sync, 2 holds the fused update-and-average launches and 1 the plain updates
- * of the other steps.  Read before qsr_restart: the split of 2 and 3 uses the log of the
+ * of the other steps.  Where the least-squares update runs in the gradient's second kernel (few
+ * samples for each wavefront), that kernel counts under 1.  Read before qsr_restart: the split of 2 and 3 uses the log of the
  * current run. */
 int qsr_timing(qsr_ctx *ctx, int enable);
 int qsr_read_timing(qsr_ctx *ctx, double ms[4], int64_t count[4]);
