@@ -2,7 +2,8 @@
 // All-Reduce line of Alg. 2, arXiv 2310.14423), as a reduction over the K axis of the [K][P]
 // buffer on one GPU.  HBM-bound: 4 B read + 4 B written per replica-parameter.
 //
-// K <= 64: a workgroup owns a tile of columns and stages it in LDS as [K][columns]: its wavefronts
+// Buffers that the caches hold: one or two columns per lane (avg_narrow_most).  Larger ones with K <= 64: a
+// workgroup owns a tile of columns and stages it in LDS as [K][columns]: its wavefronts
 // split the K rows between them (wavefront w copies rows w, w + W, ... with 128-bit loads, 1 or
 // 2 KiB contiguous from each), and after a barrier every lane adds up its columns from LDS and
 // the wavefront writes the mean back to the rows it loaded.  Any K: each lane owns four
@@ -131,6 +132,35 @@ __global__ __launch_bounds__(AVG_THREADS) void average_rows_vec4_kernel(
     }
 }
 
+// any K, buffers that the caches hold: a lane owns one column (V = 2: two, rows then being 8-byte aligned), so that
+// short rows still fill the chip and no lane has a serial chain of 4 * K additions; plain loads and stores
+template <int V>
+__global__ __launch_bounds__(AVG_THREADS) void average_rows_kernel(float *__restrict__ buf, int K, long long P,
+                                                                   const DevState *__restrict__ st)
+{
+    typedef float vec __attribute__((ext_vector_type(V)));
+    if (st != nullptr && st->h + 1 != st->H) return;
+    const long long i = ((long long)blockIdx.x * AVG_THREADS + threadIdx.x) * V;
+    if (i >= P) return;
+    float acc[V] = {}, cmp[V] = {};
+    for (int k0 = 0; k0 < K; k0 += AVG_KU) {
+        vec r[AVG_KU];
+#pragma unroll
+        for (int u = 0; u < AVG_KU; ++u)
+            if (k0 + u < K) r[u] = *(const vec *)(buf + (long long)(k0 + u) * P + i);
+#pragma unroll
+        for (int u = 0; u < AVG_KU; ++u)
+            if (k0 + u < K) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) add_comp(acc[e], cmp[e], r[u][e]);
+            }
+    }
+    vec mean;
+#pragma unroll
+    for (int e = 0; e < V; ++e) mean[e] = (acc[e] + cmp[e]) / (float)K;
+    for (int k = 0; k < K; ++k) *(vec *)(buf + (long long)k * P + i) = mean;
+}
+
 static int avg_grid(long long items, int threads)
 {
     long long blocks = (items + threads - 1) / threads;
@@ -155,15 +185,44 @@ static hipError_t launch_tile(float *buf, int K, long long P, const DevState *st
     return hipGetLastError();
 }
 
+// Largest K * P that takes one or two columns per lane.  Launches in a row on one buffer, narrow against tiles (us):
+//   P % 4 == 0   32 x 131072   7.0 / 12.0   24 x 1e6     29 / 40    32 x 1.5e6     57 / 86    100 x 1e6    166 / 151
+//     the same on buffers taken in turn, more than the caches hold: 24 x 1e6 40 / 44, 24 x 2e6 79 / 77,
+//     32 x 1.5e6 80 / 87, 8 x 3e6 39 / 36, 16 x 3e6 77 / 72, 40 x 600000 45 / 45
+//   P odd        25 x 5173      6.5 / 10.0  16 x 500001 15.1 / 10.9 32 x 1500001  80 / 90     24 x 3000001 126 / 112
+//                64 x 300001   32.4 / 35.3  64 x 600003  64 / 66    40 x 1500001  98 / 85
+//   P % 4 == 2   25 x 3000002  112 / 118    29 x 2000002 82 / 109   64 x 1000002  91 / 100
+// With fewer than 8 rows a lane has too few loads in flight, and where the launch is part of every iteration and
+// mostly returns at once (in_step) many small workgroups cost more than they save: short rows only.
+static long long avg_narrow_most(int K, long long P, bool in_step)
+{
+    if (P <= 131072) return 24000000;
+    if (in_step || K < 8) return 0;
+    switch (P & 3) {
+    case 0: return K <= 16 || K > 32 ? 0 : K <= 24 ? 24000000 : 50000000;
+    case 2: return K <= 16 ? 6000000 : K <= 24 ? 48000000 : K <= 32 ? 100000000 : K <= 64 ? 66000000 : 32000000;
+    default: return K <= 16 ? 0 : K <= 32 ? 50000000 : K <= 64 ? 40000000 : 20000000;
+    }
+}
+
 // st != nullptr: the launch acts only on the step that completes a round (h + 1 == H in the copy of the scheduler
 // state that the iteration's kernels read)
 hipError_t launch_average_rows(float *buf, int K, long long P, const DevState *st, hipStream_t s)
 {
     const long long C4 = (P + 3) / 4;
     if (C4 > 0x7FFFFFFFll * 64) return hipErrorInvalidValue;
+    if ((long long)K * P <= avg_narrow_most(K, P, st != nullptr)) {
+        if ((P & 3) == 2)                            // rows are 8-byte aligned: two columns at a time
+            average_rows_kernel<2><<<avg_grid(P / 2, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
+        else
+            average_rows_kernel<1><<<avg_grid(P, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
+        return hipGetLastError();
+    }
     if (K <= 16) return launch_tile<16, 2, 1>(buf, K, P, st, s);
     if (K <= 32) return launch_tile<32, 2, 2>(buf, K, P, st, s);
-    if (K <= 64) return launch_tile<64, 8, 1>(buf, K, P, st, s);
+    // rows in registers against tiles, buffers in turn (us): 40 x 600000 38 / 45, 64 x 750000 76 / 82, 40 x 1.8e6 112 / 111
+    const bool small = (P & 3) == 0 && (long long)K * P <= 66000000;
+    if (K <= 64 && !small) return launch_tile<64, 8, 1>(buf, K, P, st, s);
     average_rows_vec4_kernel<<<avg_grid(C4, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
     return hipGetLastError();
 }

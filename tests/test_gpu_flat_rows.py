@@ -12,8 +12,11 @@ from util import assert_mirror_matches_device, assert_params_close, gpu_ctx, ora
 pytestmark = pytest.mark.gpu
 
 
-# one, two and three columns beyond the last group of four; each tile's largest K and the first beyond it
-@pytest.mark.parametrize("K,P", [(16, 257), (17, 258), (32, 1027), (33, 259), (64, 1030), (65, 515), (3, 2), (64, 4096)])
+# one, two and three columns beyond the last group of four; each kernel's largest K and the first beyond it, on either
+# side of the sizes that take one or two columns per lane
+@pytest.mark.parametrize("K,P", [(16, 257), (17, 258), (32, 1027), (33, 259), (64, 1030), (65, 515), (3, 2), (64, 4096),
+                                 (7, 131073), (8, 131076), (17, 131076), (33, 131076), (16, 200001), (16, 375002), (17, 131074), (20, 2400003),
+                                 (32, 1600001), (33, 1250003), (65, 330005)])
 def test_averaging_of_unaligned_rows(K, P):
     average_rows_case(K, P)
 
