@@ -369,7 +369,6 @@ static int init_impl(qsr_ctx *c, const float *theta0)
     }
 
     HIP_TRY(hipMalloc((void **)&c->d_state, 2 * sizeof(DevState)));
-    HIP_TRY(hipMemset(c->d_state, 0, 2 * sizeof(DevState)));
     HIP_TRY(hipMalloc((void **)&c->d_eta, T * sizeof(double)));
     HIP_TRY(hipMalloc((void **)&c->d_scal, T * sizeof(StepScalars)));
     HIP_TRY(hipMalloc((void **)&c->d_log_t, T * sizeof(long long)));
@@ -397,7 +396,9 @@ static int init_impl(qsr_ctx *c, const float *theta0)
     HIP_TRY(launch_fill_zero(c->state0, n, c->stream));
     if (c->state1) HIP_TRY(launch_fill_zero(c->state1, n, c->stream));
     HIP_TRY(launch_fill_zero(c->d_loss, cfg.K, c->stream));
-    HIP_TRY(launch_sched_init(st_cur(c), c->sp, c->stream));
+    // everything the context's kernels read is written on c->stream: a stream that does not wait for the null stream would
+    // overtake work put there
+    HIP_TRY(launch_sched_init(c->d_state, c->sp, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     mirror_reset(c, 0, 0, 0, host_get_H(c->sp, c->eta.data(), 0));
     return QSR_OK;
@@ -786,7 +787,7 @@ extern "C" int qsr_set_state(qsr_ctx *c, const int64_t state[4])
 extern "C" int qsr_restart(qsr_ctx *c)
 {
     if (!c) return QSR_EINVAL;
-    HIP_TRY(launch_sched_init(st_cur(c), c->sp, c->stream));
+    HIP_TRY(launch_sched_init(c->d_state, c->sp, c->stream));
     c->t_host = 0;
     c->need_sync_call = false;
     c->ticked = false;

@@ -92,6 +92,7 @@ enum : uint32_t { STREAM_GRAD = 0, STREAM_X = 1, STREAM_NOISE = 2, STREAM_LABEL 
 void set_last_hip_error(int code);
 
 // ---- launchers (each returns the hipError_t of its launch) --------------------------------
+// st[0] and st[1] <- the state at t = 0 (both copies)
 hipError_t launch_sched_init(DevState *st, SchedParams sp, hipStream_t s);
 hipError_t launch_sched_set(DevState *st, SchedParams sp, long long t, long long s_, long long h, long long H,
                             hipStream_t s);

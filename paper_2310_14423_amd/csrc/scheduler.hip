@@ -7,12 +7,13 @@
 
 namespace qsr {
 
+// st: both copies of the state, which start equal
 __global__ void sched_init_kernel(DevState *st, SchedParams sp)
 {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    st->t = 0; st->s = 0; st->h = 0;
-    st->H = get_H(sp, 0);
-    st->mismatch = 0;
+    const DevState first{0, 0, 0, get_H(sp, 0), 0};
+    st[0] = first;
+    st[1] = first;
 }
 
 // resume: install a saved (t, s, h, H); log entries of earlier rounds are cleared
