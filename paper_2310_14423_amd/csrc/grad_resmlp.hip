@@ -31,13 +31,13 @@
 #include "gemm_tn.h"
 #include "philox.h"
 #include "qsr_internal.h"
+#include "wgrad_plan.h"
 
 namespace qsr {
 
 static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr float LN_EPS = 1e-5f;
-constexpr int WGRAD_SPLIT = 4;          // most ranges a weight gradient's token reduction is cut into
 
 // Token rows per wavefront of the LayerNorm backward pass: enough that all wavefronts of the launch are resident at
 // once (a launch of 1.5 times the chip's wavefront slots runs as one full wave of workgroups and a half-empty one:
@@ -73,6 +73,7 @@ struct ResWs {
     float *LPART;  long long sLPART;   // loss partials
     bf16_t *ZERO;                      // 256 bytes of zeros (stand-in rows of ragged GEMM slabs)
     float *SPLITK, *SPLITKB;           // [K][WGRAD_SPLIT][largest weight matrix], [K][WGRAD_SPLIT][widest bias]
+    WgradSpace split_space;            // their sizes
     // attention sub-blocks only
     bf16_t *QKV;   long long sQKV;     // [L][M][3d]
     bf16_t *O;     long long sO;       // [L][M][d]   attention output before the projection
@@ -123,11 +124,9 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.sPART = padded(2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
     w.sLPART = padded((M * d + 1023) / 1024, 4); w.LPART = (float *)take(w.sLPART, 4, K);
     w.ZERO = (bf16_t *)take(128, 2, 1);
-    {
-        const long long widest = heads > 0 && 3 * d > dh ? 3 * d : dh;
-        w.SPLITK = (float *)take(K * WGRAD_SPLIT * d * widest, 4, 1);
-        w.SPLITKB = (float *)take(K * WGRAD_SPLIT * widest, 4, 1);
-    }
+    w.split_space = wgrad_space(K, d, dh, heads > 0);
+    w.SPLITK = (float *)take(w.split_space.products, 4, 1);
+    w.SPLITKB = (float *)take(w.split_space.biases, 4, 1);
     w.QKV = w.O = w.DO = w.DQKV = w.Wqb = w.WqTb = w.Wob = w.WoTb = nullptr; w.LSE = nullptr;
     w.sQKV = w.sO = w.sLSE = w.sDO = w.sDQKV = w.sWq = w.sWo = 0;
     if (heads > 0) {
@@ -686,51 +685,34 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float *__restrict
 // Weight gradient dW[z] = A[z]^T B[z] (p.M x p.N, rows contiguous, per-worker stride sOut) with the
 // bias gradient (column sums of B) as a by-product.  Widths are multiples of 64 and a block of zeros stands in
 // for ragged token counts, so every weight gradient of this model qualifies.
-// Tile shape by the number of tiles and the length of the reduction, from timing on MI355X (us; batch x tokens x
-// width x hidden: gradient of the second weight / of a width x width projection; s4: cut into four ranges, without
-// the 6-16 us that adding them up takes):
-//                              192x384          128x128, 3 WG/CU    128x128, 2 groups    64x64, 4 groups   before
-//   8 x 12608 x 768 x 3072   407 / 297, s4 117   589 / 193           616 / 217              - / -          468 / 372 (s4 128)
-//   2 x 12608 x 768 x 3072   271 / 269, s4 113   177 / 115, s4 51    192 / 97             236 / 99         375 / 357
-//   1 x 12608 x 768 x 3072   291 / 275, s4 84    121 / 116, s4 35    101 / 97             131 / 47         374 / 360
-//   8 x 1576 x 768 x 3072     61 / 43             68 / 28             84 / 32             148 / 42          68 / 53
-//   4 x 2000 x 512 x 2048     53 / 50             26 / 22             25 / 20              43 / 11          67 / 65
-//   2 x 400 x 768 x 3072      18 / 16             11 / 7.6            15 / 8.0             25 / 10.5        21 / 20
-//   2 x 1040 x 192 x 768      32 / 30             13 / 13             12 / 12             8.0 / 7.7         39 / 38
-// Hence: the large tile from 160 of them on; a long reduction (4096 tokens) with fewer is cut into up to WGRAD_SPLIT
-// ranges, on the large tile while that makes about 200 workgroups, else on the small one; a short one goes to
-// 128 x 128 (two groups per workgroup below 200 of them) and from 110 of those down to 64 x 64 with four groups.
+// Tile shape and token ranges: wgrad_plan.h.
 template <bool BLKA, bool BLKB>
 static hipError_t wgrad(GemmNT p, float *dW, float *db, long long sOut, const ResWs &w, int batch, hipStream_t s)
 {
     p.zeros = w.ZERO;
-    auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * batch; };
-    const long long big = tiles(192, 384), mid = tiles(128, 128);
+    const WgradPlan plan = wgrad_plan(p.M, p.N, p.K, batch, gemm_cu_count());
     const long long MN = (long long)p.M * p.N;
-    if (big < 160 && p.K >= 4096) {
-        const bool large = big >= 48;
-        const long long want = large ? gemm_cu_count() / big : 3LL * gemm_cu_count() / mid;
-        int split = (int)(want < 1 ? 1 : want > WGRAD_SPLIT ? WGRAD_SPLIT : want);
-        const int k_chunk = ((p.K + split - 1) / split + 31) / 32 * 32;
-        split = (p.K + k_chunk - 1) / k_chunk;
-        if (split > 1) {
-            p.split = split; p.k_chunk = k_chunk;
-            p.colsum_B = w.SPLITKB; p.s_colsum = p.N;
-            EpiScaleF32 epi{w.SPLITK, p.N, MN, 1.0f};
-            if (large) TRY((launch_gemm_tn<192, 384, 2, 4, 1, 2, 4, BLKA, BLKB>(p, epi, batch, s)));
-            else TRY((launch_gemm_tn<128, 128, 2, 2, 1, 3, 3, BLKA, BLKB>(p, epi, batch, s)));
-            splitk_sum_kernel<<<dim3((unsigned)((MN / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITK, MN, split, dW, sOut);
-            TRY(hipGetLastError());
-            splitk_sum_kernel<<<dim3((unsigned)((p.N / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITKB, p.N, split, db, sOut);
-            return hipGetLastError();
-        }
+    if (plan.split > 1) {
+        const long long parts = (long long)batch * plan.split;
+        if (parts * MN > w.split_space.products || parts * p.N > w.split_space.biases) return hipErrorInvalidValue;
+        p.split = plan.split; p.k_chunk = plan.k_chunk;
+        p.colsum_B = w.SPLITKB; p.s_colsum = p.N;
+        EpiScaleF32 epi{w.SPLITK, p.N, MN, 1.0f};
+        if (plan.tile == WGRAD_192x384) TRY((launch_gemm_tn<192, 384, 2, 4, 1, 2, 4, BLKA, BLKB>(p, epi, batch, s)));
+        else TRY((launch_gemm_tn<128, 128, 2, 2, 1, 3, 3, BLKA, BLKB>(p, epi, batch, s)));
+        splitk_sum_kernel<<<dim3((unsigned)((MN / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITK, MN, plan.split, dW, sOut);
+        TRY(hipGetLastError());
+        splitk_sum_kernel<<<dim3((unsigned)((p.N / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITKB, p.N, plan.split, db, sOut);
+        return hipGetLastError();
     }
     p.colsum_B = db; p.s_colsum = sOut;
     EpiScaleF32 epi{dW, p.N, sOut, 1.0f};
-    if (big >= 160) return launch_gemm_tn<192, 384, 2, 4, 1, 2, 4, BLKA, BLKB>(p, epi, batch, s);
-    if (mid >= 200) return launch_gemm_tn<128, 128, 2, 2, 1, 3, 3, BLKA, BLKB>(p, epi, batch, s);
-    if (mid >= 110) return launch_gemm_tn<128, 128, 2, 2, 2, 2, 4, BLKA, BLKB>(p, epi, batch, s);
-    return launch_gemm_tn<64, 64, 2, 2, 4, 4, 3, BLKA, BLKB>(p, epi, batch, s);
+    switch (plan.tile) {
+    case WGRAD_192x384: return launch_gemm_tn<192, 384, 2, 4, 1, 2, 4, BLKA, BLKB>(p, epi, batch, s);
+    case WGRAD_128x128: return launch_gemm_tn<128, 128, 2, 2, 1, 3, 3, BLKA, BLKB>(p, epi, batch, s);
+    case WGRAD_128x128_2GROUPS: return launch_gemm_tn<128, 128, 2, 2, 2, 2, 4, BLKA, BLKB>(p, epi, batch, s);
+    default: return launch_gemm_tn<64, 64, 2, 2, 4, 4, 3, BLKA, BLKB>(p, epi, batch, s);
+    }
 }
 
 hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g, const float *teacher,

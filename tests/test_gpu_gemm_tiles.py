@@ -23,6 +23,8 @@ pytestmark = pytest.mark.gpu
     dict(d_in=64, d_hidden=128, n_blocks=1, B_loc=4129, K=2),
     # on 192 x 384 tiles (48 of them, rows and columns beyond the matrix)
     dict(d_in=64, d_hidden=4608, n_blocks=1, B_loc=4100, K=4),
+    # a hidden layer narrower than the model: the second weight's gradient has more columns than any other's, cut into ranges
+    dict(d_in=192, d_hidden=64, n_blocks=1, B_loc=4129, K=2),
     # fewer tokens than a stage
     dict(d_in=64, d_hidden=64, n_blocks=1, B_loc=7, K=1),
 ])
