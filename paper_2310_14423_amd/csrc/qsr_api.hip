@@ -497,6 +497,15 @@ struct Bracket {
 // ------------------------------------------------------------------------------------------
 // the iteration
 // ------------------------------------------------------------------------------------------
+// whether launches on the stream are being recorded (the null stream cannot be)
+static bool caller_records(hipStream_t s)
+{
+    if (s == nullptr) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return status == hipStreamCaptureStatusActive;
+}
+
 extern "C" int qsr_local_step(qsr_ctx *c)
 {
     if (!c) return QSR_EINVAL;
@@ -545,12 +554,15 @@ extern "C" int qsr_local_step(qsr_ctx *c)
     const bool fused = cfg.fuse_sync != 0;
     const bool shared_g = cfg.parallel != 0;            // all rows of the gradient are the mean now
     const DevState *st = st_cur(c);                     // what every kernel of this iteration reads
+    // A caller who records iterations into a graph of their own may replay any number of them: those advance the
+    // scheduler in place (qsr_maybe_sync), since a replay always starts from the same copy.
+    const bool in_place = !all && caller_records(c->stream);
     SchedParams sp = c->sp;
     sp.expect_sync = all ? -1 : (sync_now ? 1 : 0);
     if (!fused || all || !sync_now) {                   // OPT for all K workers at once
         Bracket br(c, 1);
         if (br.rc != QSR_OK) return br.rc;
-        DevState *st_next = c->d_state + (c->cur ^ 1);
+        DevState *st_next = in_place ? nullptr : c->d_state + (c->cur ^ 1);
         if (cfg.clip_norm > 0.0)                        // App. C: per-worker factors min(1, c / (||g_k|| + 1e-6))
             HIP_TRY(launch_clip_coef(c->grads, cfg.K, cfg.P, (float)cfg.clip_norm, c->d_clip_part,
                                      c->d_clip_coef, c->d_clip_coef + cfg.K, c->stream, cfg.parallel != 0));
@@ -580,7 +592,7 @@ extern "C" int qsr_local_step(qsr_ctx *c)
                                         (float)cfg.eps, fused, c->d_clip_coef, shared_g, c->stream, st_next, &sp));
         int rc = br.close(c->t_host);
         if (rc != QSR_OK) return rc;
-        c->cur ^= 1; c->ticked = true;                  // the advanced state is in the other copy now
+        if (st_next) { c->cur ^= 1; c->ticked = true; } // the advanced state is in the other copy now
     }
     if (fused && (all || sync_now)) {                   // the round's last step: OPT and All-Reduce in one pass
         Bracket br(c, 2);                               // timed like an averaging launch
@@ -623,7 +635,8 @@ extern "C" int qsr_maybe_sync(qsr_ctx *c)
             if (c->state1) HIP_TRY(launch_average_rows(c->state1, c->cfg.K, c->cfg.P, st, c->stream));
         }
     }
-    if (!c->ticked) {                        // the fused update-and-average launch has no scheduler step of its own
+    if (!c->ticked) {                        // the fused update-and-average launch has no scheduler step of its own, and
+                                             // iterations that the caller records take theirs here
         SchedParams sp = c->sp;
         sp.expect_sync = sync_now ? 1 : 0;
         HIP_TRY(launch_sched_advance(st, sp, c->stream));

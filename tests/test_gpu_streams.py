@@ -1,4 +1,5 @@
-"""GPU: contexts on a stream other than the null stream, whose kernels do not wait for the null stream."""
+"""GPU: contexts on a stream other than the null stream, whose kernels do not wait for the null stream and whose
+iterations a caller may record into a graph of their own."""
 import pytest
 
 import workloads
@@ -39,3 +40,36 @@ def test_context_made_while_the_null_stream_is_busy(name, kw):
         assert_mirror_matches_device(ctx)
         assert_params_close(ctx.params.cpu().numpy(), orc.theta, what=name)
         ctx.close()
+
+
+@pytest.mark.parametrize("name,kw", [
+    ("lsq", dict(K=3, d_in=66, B_loc=9, eta_max=0.02, alpha=0.0)),
+    ("lsq", dict(K=17, d_in=66, B_loc=9, eta_max=0.02, alpha=0.0)),
+    ("mlp", dict(d_in=72, d_hidden=96, d_out=10, B_loc=48, K=3, milestones=(60, 100), eta_max=0.02, alpha=0.0)),
+    ("flat60m", dict(K=3, P=9001, alpha=0.0, clip_norm=0.05)),
+    ("flat60m", dict(K=3, P=9001, alpha=0.0, fuse_sync=True)),
+    ("flat60m", dict(K=4, P=1 << 18, alpha=0.0, parallel=True)),
+])
+def test_iteration_recorded_by_the_caller(name, kw):
+    """One iteration (every one ends a round) in the caller's graph: each replay counts and continues."""
+    import torch
+    w = workloads.get(name, T=150, H_base=1, power=0, **kw)
+    ref = gpu_ctx(w)
+    ref.step(13)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ctx = gpu_ctx(w)
+        ctx.step(3)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            ctx.step(1)
+        for done, replays in ((5, 2), (8, 3), (13, 5)):
+            for _ in range(replays):
+                graph.replay()
+            assert ctx.get_state() == (done, done, 0, 1)
+        assert list(ctx.read_sync_log()[0]) == list(range(1, 14))
+        side.synchronize()
+    for a, b in ((ctx.params, ref.params), (ctx.state0, ref.state0), (ctx.grads, ref.grads)):
+        assert torch.equal(a, b)
+    ctx.close(); ref.close()
