@@ -109,7 +109,7 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT 
             // as asm: behind the builtin, the compiler takes every transpose read for a possible reader of the copies
             // in flight and waits for all of them first
             const unsigned dst = __builtin_amdgcn_readfirstlane(lds_ring + d_stage * (STAGE * 2) + c * 1024);
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(g) : "memory");
+            asm volatile("global_load_lds_dwordx4 %1, off" :: "{m0}"(dst), "v"(g) : "memory");
             src[i] += c < CA ? stepA : stepB;
         }
     };
