@@ -107,9 +107,10 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT 
                 if (d_row + (cc & 1) * 16 + tok >= k_end) g = p.zeros + (lane & 3) * 8;
             }
             // as asm: behind the builtin, the compiler takes every transpose read for a possible reader of the copies
-            // in flight and waits for all of them first
+            // in flight and waits for all of them first.  The s_nop is the wait state that such a copy needs behind a
+            // write of m0 (the compiler sets m0 right before the statement, and counts wait states for its own copies only).
             const unsigned dst = __builtin_amdgcn_readfirstlane(lds_ring + d_stage * (STAGE * 2) + c * 1024);
-            asm volatile("global_load_lds_dwordx4 %1, off" :: "{m0}"(dst), "v"(g) : "memory");
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(dst), "v"(g) : "memory");
             src[i] += c < CA ? stepA : stepB;
         }
     };

@@ -390,14 +390,15 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_lds_kernel(GemmArgs
         }
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            // as asm: behind the builtin, the compiler takes every LDS read for a possible reader of the copies in flight
-            asm volatile("global_load_lds_dwordx4 %1, off" :: "{m0}"(dst + c * 1024), "v"(srcA[c]) : "memory");
+            // as asm: behind the builtin, the compiler takes every LDS read for a possible reader of the copies in flight;
+            // the s_nop is the wait state that a copy needs behind the compiler's write of m0
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(dst + c * 1024), "v"(srcA[c]) : "memory");
             srcA[c] += 16;
         }
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
-            if (BX4) asm volatile("global_load_lds_dwordx4 %1, off" :: "{m0}"(dst + 2048 + c * 1024), "v"(srcB[c]) : "memory");
-            else asm volatile("global_load_lds_dword %1, off" :: "{m0}"(dst + 2048 + c * 256), "v"(srcB[c]) : "memory");
+            if (BX4) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(dst + 2048 + c * 1024), "v"(srcB[c]) : "memory");
+            else asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, off" :: "{m0}"(dst + 2048 + c * 256), "v"(srcB[c]) : "memory");
             srcB[c] += stepB;
         }
         d_slot = d_slot + 1 == NS ? 0 : d_slot + 1;

@@ -19,3 +19,10 @@ def test_m0_is_an_operand():
     assert len(copies) >= 4
     for name, stmt in copies:
         assert '"{m0}"' in stmt and not re.search(r"\bm0\s*,", stmt), (name, stmt)
+
+
+def test_wait_state_behind_the_write_of_m0():
+    """One wait state between a scalar write of m0 and a copy that uses it: the compiler inserts it for its own
+    instructions, not for one inside a statement."""
+    for name, stmt in _copies():
+        assert re.match(r'"s_nop 0\\n\\tglobal_load_lds_dword', stmt.strip()), (name, stmt)
