@@ -37,12 +37,12 @@ __device__ __forceinline__ float block_sum_256(float v, float *red)
 // step 3 and take the inner product; wavefront 4 draws the observation noise meanwhile.
 __global__ __launch_bounds__(320) void linreg_residual_kernel(
     float *__restrict__ X, const float *__restrict__ theta, const float *__restrict__ wstar,
-    float *__restrict__ r, long long B, long long d, float sigma, uint64_t seed,
+    float *__restrict__ r, long long i0, long long B, long long d, float sigma, uint64_t seed,
     const DevState *__restrict__ st)
 {
     __shared__ float red[5];
     const int k = blockIdx.y, tid = threadIdx.x, wave = tid >> 6;
-    const long long i = blockIdx.x;
+    const long long i = i0 + blockIdx.x;
     const uint32_t t = (uint32_t)st->t;
     float acc = 0.f;
     if (wave < 4) {
@@ -210,9 +210,15 @@ static float *linreg_r(const ModelDims &d, void *ws)
 static hipError_t launch_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
                                   const DevState *st, hipStream_t s)
 {
-    linreg_residual_kernel<<<dim3((unsigned)d.B, (unsigned)d.K), 320, 0, s>>>(
-        (float *)ws, theta, wstar, linreg_r(d, ws), d.B, d.d_in, d.data_sigma, d.seed, st);
-    return hipGetLastError();
+    // a launch takes fewer than 2^32 threads in a grid dimension: runs of 2^23 samples
+    for (long long i0 = 0; i0 < d.B; i0 += 1ll << 23) {
+        const long long n = d.B - i0 < (1ll << 23) ? d.B - i0 : 1ll << 23;
+        linreg_residual_kernel<<<dim3((unsigned)n, (unsigned)d.K), 320, 0, s>>>(
+            (float *)ws, theta, wstar, linreg_r(d, ws), i0, d.B, d.d_in, d.data_sigma, d.seed, st);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_linreg_grad(const ModelDims &d, const float *theta, float *g, const float *wstar,

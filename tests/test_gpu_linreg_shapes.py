@@ -42,3 +42,24 @@ def test_least_squares_shapes(K, d, B, opt):
         assert_params_close(g[k], want, what="grad k=%d" % k)
         assert loss[k] == pytest.approx(wl, rel=1e-5)
     ctx.close()
+
+
+def test_more_samples_than_one_launch_takes():
+    """One workgroup of 320 threads per sample, and at most 2^32 - 1 threads in a grid dimension: 13.4 M samples."""
+    B = (1 << 32) // 320 + 2
+    w = workloads.get("lsq", K=1, d_in=1, B_loc=B, T=2, eta_max=0.01, alpha=0.0)
+    wstar = workloads.model_const(w).astype(np.float32)         # theta = w*: residuals of the noise alone, a sum that stays small
+    X, y = oracle_run(w, theta0=wstar).linreg_batch(0, 0)
+    ctx = gpu_ctx(w, theta0=wstar)
+    ctx.local_step()
+    ws = ctx.workspace.cpu().numpy().view(np.float32)
+    x, r = ws[:B], ws[(B + 63) // 64 * 64:][:B]                # the two arrays of the workspace, 256-byte aligned
+    want = X[:, 0] * wstar.astype(np.float64)[0] - y
+    assert np.max(np.abs(x - X[:, 0])) < 2e-6                   # 5.4 at most, four ulps
+    assert np.max(np.abs(r - want)) < 2e-6
+    # an fp32 sum of B terms, one after the other: a random walk of B roundings of up to half an ulp of the partial sum
+    terms = want * X[:, 0]
+    walk = 2.0 ** -24 * np.max(np.abs(np.cumsum(terms))) * np.sqrt(B / 3)
+    assert abs(ctx.grads.item() - np.mean(terms)) < 4 * walk / B
+    assert ctx.read_loss()[0] == pytest.approx(0.5 * np.mean(want * want), rel=1e-4)
+    ctx.close()
