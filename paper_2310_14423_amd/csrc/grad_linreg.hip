@@ -239,6 +239,8 @@ bool linreg_can_fuse(const ModelDims &d)
 {
     if (d.K > 16) return false;
     const long long S = 16 / d.K, per = (d.B + S - 1) / S;
+    // 2^28 features and more: the launch would pass the limit of 2^32 threads in a grid dimension
+    if ((d.d_in + 63) / 64 * (d.K * S * 64) >= 1ll << 32) return false;
     return per <= (S > 1 ? 64 : 32);
 }
 

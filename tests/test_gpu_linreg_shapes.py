@@ -63,3 +63,21 @@ def test_more_samples_than_one_launch_takes():
     assert abs(ctx.grads.item() - np.mean(terms)) < 4 * walk / B
     assert ctx.read_loss()[0] == pytest.approx(0.5 * np.mean(want * want), rel=1e-4)
     ctx.close()
+
+
+def test_more_features_than_one_fused_launch_takes():
+    """2^28 features: 64 to a workgroup of 1024 threads would be 2^32 threads."""
+    import torch
+    import paper_2310_14423_amd as qsr
+    d = (1 << 28) + 4
+    w = workloads.get("lsq", K=1, d_in=d, B_loc=1, T=3, H_base=2, mu=0.9, lam=0.0, eta_max=0.25, alpha=0.0, data_sigma=0.0)
+    ctx = qsr.Context(w, model_const=np.full(d, 2.0 ** -14, dtype=np.float32))      # theta = 0
+    ctx.step(1)
+    ws = ctx.workspace.view(torch.float32)
+    x, r = ws[:d], ws[(d + 63) // 64 * 64]
+    # a quarter of a thousand threads add up 2^20 products each, one after the other: 2^-24 sqrt(2^20 / 3) of the sum, times four
+    assert float(r) == pytest.approx(-float(x.sum(dtype=torch.float64)) * 2.0 ** -14, rel=2e-4, abs=2e-4)
+    assert torch.equal(ctx.grads[0], r * x) and torch.equal(ctx.state0, ctx.grads) and torch.equal(ctx.params, -0.25 * ctx.grads)
+    assert ctx.read_loss()[0] == pytest.approx(0.5 * float(r) ** 2, rel=1e-6)
+    assert ctx.get_state() == (1, 0, 1, 2)
+    ctx.close()
