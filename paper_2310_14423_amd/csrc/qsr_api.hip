@@ -73,6 +73,7 @@ struct qsr_ctx {
     hipGraphExec_t graph_exec;
     int graph_iters;
     int graph_cur;           // the copy of the scheduler state the recorded launches begin and end on
+    bool replayed;           // since the state was last installed; recorded launches do not compare themselves with the mirror
 };
 
 static inline DevState *st_cur(qsr_ctx *c) { return c->d_state + c->cur; }
@@ -285,6 +286,7 @@ static long long host_get_H(const SchedParams &sp, const double *eta, long long 
 static void mirror_reset(qsr_ctx *c, long long t, long long s, long long h, long long H)
 {
     c->m_t = t; c->m_s = s; c->m_h = h; c->m_H = H;
+    c->replayed = false;
     c->m_log_t.assign((size_t)s, 0);
     c->m_log_H.assign((size_t)s, 0);
 }
@@ -446,7 +448,7 @@ extern "C" int qsr_init(const qsr_config *cfg, float *params, float *grads, floa
     // The update kernel takes the scheduler's step into the other copy of the state, so that an iteration needs no
     // scheduler kernel.  Recorded iterations alternate between the copies too: a graph holds an even number
     // of them and is replayed from the copy it was recorded on.
-    c->cur = 0; c->ticked = false; c->graph_cur = 0;
+    c->cur = 0; c->ticked = false; c->graph_cur = 0; c->replayed = false;
     c->dims = make_dims(cfg);
     c->fuse_linreg = cfg->model == QSR_MODEL_LINREG && linreg_can_fuse(c->dims) && !cfg->parallel && !cfg->fuse_sync &&
                      !cfg->average_state && cfg->clip_norm <= 0.0;
@@ -703,6 +705,7 @@ extern "C" int qsr_run(qsr_ctx *c, int64_t n)
     }
     while (n >= per) {
         HIP_TRY(hipGraphLaunch(c->graph_exec, c->stream));
+        c->replayed = true;
         c->t_host += per;
         for (long long i = 0; i < per; ++i) mirror_advance(c);
         n -= per;
@@ -718,7 +721,9 @@ static int fetch_state(qsr_ctx *c)
     const DevState *st = c->d_state + (c->ticked ? c->cur ^ 1 : c->cur);
     HIP_TRY(hipMemcpyAsync(c->h_state, st, sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    if (c->h_state->mismatch) return QSR_EMIRROR;
+    const DevState &d = *c->h_state;
+    if (d.mismatch) return QSR_EMIRROR;
+    if (c->replayed && (d.t != c->m_t || d.s != c->m_s || d.h != c->m_h || d.H != c->m_H)) return QSR_EMIRROR;
     if (c->need_sync_call) { c->h_state->t += 1; c->h_state->h += 1; }
     return QSR_OK;
 }

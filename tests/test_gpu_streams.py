@@ -73,3 +73,29 @@ def test_iteration_recorded_by_the_caller(name, kw):
     for a, b in ((ctx.params, ref.params), (ctx.state0, ref.state0), (ctx.grads, ref.grads)):
         assert torch.equal(a, b)
     ctx.close(); ref.close()
+
+
+def test_replays_are_held_against_the_mirror():
+    """Recorded launches make no check of their own: a device that has gone another way than the host's mirror (here
+    one step ahead, by a graph of the caller's) is reported by the next call that reads the state."""
+    import torch
+    import paper_2310_14423_amd as qsr
+    w = workloads.get("flat60m", K=2, P=1024, T=150, H_base=3, power=0, alpha=0.0)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ctx = gpu_ctx(w)
+        ctx.run(39)
+        assert ctx.get_state() == (39, 13, 0, 3)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            ctx.step(1)
+        graph.replay()
+        assert ctx.get_state() == (40, 13, 1, 3)        # recorded once, run once
+        graph.replay()                                  # ends no round either, as recorded
+        with pytest.raises(qsr.QSRError) as e:
+            ctx.get_state()
+        assert e.value.code == -6
+        ctx.restart()
+        ctx.run(40)
+        assert ctx.get_state() == (40, 13, 1, 3)
+        ctx.close()
