@@ -2,24 +2,14 @@
 // All-Reduce line of Alg. 2, arXiv 2310.14423), as a reduction over the K axis of the [K][P]
 // buffer on one GPU.  HBM-bound: 4 B read + 4 B written per replica-parameter.
 //
-// Buffers that the caches hold: one or two columns per lane (avg_narrow_most).  Larger ones with K <= 64: a
-// workgroup owns a tile of columns and stages it in LDS as [K][columns]: its wavefronts
-// split the K rows between them (wavefront w copies rows w, w + W, ... with 128-bit loads, 1 or
-// 2 KiB contiguous from each), and after a barrier every lane adds up its columns from LDS and
-// the wavefront writes the mean back to the rows it loaded.  Any K: each lane owns four
-// consecutive parameters and walks the K rows in registers, 16 in flight at a time.  Rows whose
-// length is not a multiple of 4 take the same kernels with unaligned 128-bit accesses
-// (ld_group / st_group); one or two elements per lane, as they were read before, ran 3.4-4.4 TB/s.
-// What decides is the number of loads a lane has in flight: 8 wavefronts for up to 16 rows left one
-// load per lane at K = 8.  Timed on MI355X, launches in a row on one buffer (us):
-//                        8 x 3000001  8 x 814090  16 x 60e6  24 x 6000002  32 x 20e6  32 x 20000003  64 x 6e6
-//   2 wavefronts x 1 KiB     33.9        9.1        1343          -           -           -           914 (4 x)
-//   8 wavefronts x 1 KiB     41.6       14.7        1545         300 (4 x)   959        1158          586
-//   2 wavefronts x 2 KiB      -           -          -           247         894        1077           -
-//   rows in registers        33.1        9.7        1382         255         990        1240          578
-//   as it was                41.2       10.8        1539         263         890        1262          592
-// Chosen: 2 x 1 KiB up to K = 16, 2 x 2 KiB up to K = 32, 8 x 1 KiB up to K = 64 (a plain copy kernel
-// reaches 5.8 TB/s on this chip; 16 x 60e6 in 1343 us is 5.7).
+// Three kernels, chosen by size and alignment (launch_average_rows, where the timings stand):
+//  - a tile of columns staged in LDS as [K][columns], K <= 64: the workgroup's wavefronts split the K rows between
+//    them (wavefront w copies rows w, w + W, ... with 128-bit loads, 1 or 2 KiB contiguous from each), and after a
+//    barrier every lane adds up its columns from LDS and the wavefront writes the mean back to the rows it loaded;
+//  - rows in registers, any K: each lane owns four consecutive parameters and walks the K rows, 16 in flight;
+//  - one or two columns per lane, any K.
+// Rows whose length is not a multiple of 4 take the first two with unaligned 128-bit accesses (ld_group / st_group).
+// A plain copy kernel reaches 5.8 TB/s on this chip; 16 x 60e6 in 1325 us is 5.8.
 //
 // In every variant the sum runs over k in ascending order in fp32 with an error-free
 // transformation of every addition (the rounding error of each partial sum is carried in a
@@ -34,12 +24,14 @@ namespace qsr {
 constexpr int AVG_THREADS = 64;
 constexpr int AVG_KU = 16;
 
-// LDS-staged tile: W wavefronts, RUN x 64 float4 columns (RUN KiB contiguous per row and wavefront)
-template <int KMAX, int W, int RUN>
+// LDS-staged tile: W wavefronts, RUN x 64 float4 columns (RUN KiB contiguous per row and wavefront).
+// ALIGNED (here and below): P is known to be a multiple of 4.  With the test of P's remainder around every access
+// 32 x 2250000 took 127 us for 120, 32 x 3125000 176 for 169.
+template <int KMAX, int W, int RUN, bool ALIGNED>
 __device__ __forceinline__ void average_tile_body(float *__restrict__ buf, int K, long long P, float4 *avg_tile)
 {
     const long long P4 = P >> 2;
-    const int rem = (int)(P & 3);
+    const int rem = ALIGNED ? 0 : (int)(P & 3);
     const long long C4 = P4 + (rem != 0);            // column groups, the last one possibly partial
     constexpr int TC = RUN * 64;
     constexpr int RPW = (KMAX + W - 1) / W;          // rows per wavefront
@@ -93,23 +85,24 @@ __device__ __forceinline__ void average_tile_body(float *__restrict__ buf, int K
     }
 }
 
-template <int KMAX, int W, int RUN>
+template <int KMAX, int W, int RUN, bool ALIGNED>
 __global__ __launch_bounds__(64 * W) void average_rows_tile_kernel(float *__restrict__ buf, int K, long long P,
                                                                    const DevState *__restrict__ st)
 {
     extern __shared__ float4 avg_tile[];            // [K][RUN * 64]
     if (st != nullptr && st->h + 1 != st->H) return;        // not the step that completes a round
-    average_tile_body<KMAX, W, RUN>(buf, K, P, avg_tile);
+    average_tile_body<KMAX, W, RUN, ALIGNED>(buf, K, P, avg_tile);
 }
 
 // any K: a lane owns four consecutive columns, AVG_KU rows in flight at a time
+template <bool ALIGNED>
 __global__ __launch_bounds__(AVG_THREADS) void average_rows_vec4_kernel(
     float *__restrict__ buf, int K, long long P, const DevState *__restrict__ st)
 {
     if (st != nullptr && st->h + 1 != st->H) return;
     const float fK = (float)K;
     const long long P4 = P >> 2, C4 = (P + 3) >> 2;
-    const int rem = (int)(P & 3);
+    const int rem = ALIGNED ? 0 : (int)(P & 3);
     const long long stride = (long long)gridDim.x * AVG_THREADS;
     for (long long i = (long long)blockIdx.x * AVG_THREADS + threadIdx.x; i < C4; i += stride) {
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -132,8 +125,9 @@ __global__ __launch_bounds__(AVG_THREADS) void average_rows_vec4_kernel(
     }
 }
 
-// any K, buffers that the caches hold: a lane owns one column (V = 2: two, rows then being 8-byte aligned), so that
-// short rows still fill the chip and no lane has a serial chain of 4 * K additions; plain loads and stores
+// any K: a lane owns one column (V = 2: two, rows then being 8-byte aligned), so that short rows still fill the chip
+// and no lane has a serial chain of 4 * K additions; plain loads and stores, which find what the caches hold and leave
+// the result there for the update behind
 template <int V>
 __global__ __launch_bounds__(AVG_THREADS) void average_rows_kernel(float *__restrict__ buf, int K, long long P,
                                                                    const DevState *__restrict__ st)
@@ -170,61 +164,91 @@ static int avg_grid(long long items, int threads)
     return (int)blocks;
 }
 
-template <int KMAX, int W, int RUN>
+template <int KMAX, int W, int RUN, bool ALIGNED>
 static hipError_t launch_tile(float *buf, int K, long long P, const DevState *st, hipStream_t s)
 {
     const size_t lds = (size_t)K * RUN * 64 * sizeof(float4);
     static bool raised = false;                       // above the default only for more than 48 rows of 1 KiB
     if (lds > 48 * 1024 && !raised) {
-        hipError_t e = hipFuncSetAttribute((const void *)average_rows_tile_kernel<KMAX, W, RUN>,
+        hipError_t e = hipFuncSetAttribute((const void *)average_rows_tile_kernel<KMAX, W, RUN, ALIGNED>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, KMAX * RUN * 64 * (int)sizeof(float4));
         if (e != hipSuccess) return e;
         raised = true;
     }
-    average_rows_tile_kernel<KMAX, W, RUN><<<avg_grid((P + 3) / 4, RUN * 64), 64 * W, lds, s>>>(buf, K, P, st);
+    average_rows_tile_kernel<KMAX, W, RUN, ALIGNED><<<avg_grid((P + 3) / 4, RUN * 64), 64 * W, lds, s>>>(buf, K, P, st);
     return hipGetLastError();
 }
 
-// Largest K * P that takes one or two columns per lane.  Launches in a row on one buffer, narrow against tiles (us):
-//   P % 4 == 0   32 x 131072   7.0 / 12.0   24 x 1e6     29 / 40    32 x 1.5e6     57 / 86    100 x 1e6    166 / 151
-//     the same on buffers taken in turn, more than the caches hold: 24 x 1e6 40 / 44, 24 x 2e6 79 / 77,
-//     32 x 1.5e6 80 / 87, 8 x 3e6 39 / 36, 16 x 3e6 77 / 72, 40 x 600000 45 / 45
-//   P odd        25 x 5173      6.5 / 10.0  16 x 500001 15.1 / 10.9 32 x 1500001  80 / 90     24 x 3000001 126 / 112
-//                64 x 300001   32.4 / 35.3  64 x 600003  64 / 66    40 x 1500001  98 / 85
-//   P % 4 == 2   25 x 3000002  112 / 118    29 x 2000002 82 / 109   64 x 1000002  91 / 100
-// With fewer than 8 rows a lane has too few loads in flight, and where the launch is part of every iteration and
-// mostly returns at once (in_step) many small workgroups cost more than they save: short rows only.
-static long long avg_narrow_most(int K, long long P, bool in_step)
+// V columns per lane
+template <int V>
+static hipError_t launch_narrow(float *buf, int K, long long P, const DevState *st, hipStream_t s)
 {
-    if (P <= 131072) return 24000000;
-    if (in_step || K < 8) return 0;
-    switch (P & 3) {
-    case 0: return K <= 16 || K > 32 ? 0 : K <= 24 ? 24000000 : 50000000;
-    case 2: return K <= 16 ? 6000000 : K <= 24 ? 48000000 : K <= 32 ? 100000000 : K <= 64 ? 66000000 : 32000000;
-    default: return K <= 16 ? 0 : K <= 32 ? 50000000 : K <= 64 ? 40000000 : 20000000;
-    }
+    average_rows_kernel<V><<<avg_grid(P / V, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
+    return hipGetLastError();
+}
+template <bool ALIGNED>
+static hipError_t launch_vec4(float *buf, int K, long long P, const DevState *st, hipStream_t s)
+{
+    average_rows_vec4_kernel<ALIGNED><<<avg_grid((P + 3) / 4, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
+    return hipGetLastError();
 }
 
+// Which kernel, by alignment, K and K * P, from 4000 timed sizes (K to 120, K * P from 1e5 to 6e8, every P mod 4) on one
+// buffer again and again ("hot") and on buffers in turn that together exceed the caches ("cold"), and from whole
+// iterations.  One size on either side of each line, hot / cold in us; two, one: columns per lane; tile: wavefronts x KiB.
+//   short rows: one column keeps the chip busy          32 x 131072   one 6.5 / 9.4    four in registers 7.3 / 8.9    tile 12 / 11
+//   P a multiple of 4, the buffer in the caches (K * P <= 56e6): two columns
+//                                                        24 x 1e6     two 29.5 / 42     tile 2 x 2 40 / 43
+//                                                        16 x 3e6     two 56 / 77       tile 2 x 1 73 / 72
+//                                                        24 x 2e6     two 56 / 79       tile 2 x 2 74 / 76
+//                             beyond                     24 x 3e6     two 88 / 116      tile 2 x 2 109 / 109
+//                             K <= 16, below 24e6        12 x 1e6     two 15.6 / 21.4   tile 2 x 1 17.2 / 19.6
+//                             K <= 8                      8 x 3e6     two 29 / 38       tile 2 x 1 34 / 35
+//     K * P > 56e6, K of 9 to 32                         12 x 16666668 tile 2 x 2 344 / 335  tile 2 x 1 377 / 373  tile 8 x 1 349 / 346
+//     K of 9 to 16 beyond 5e8                            16 x 60e6    alone: tile 2 x 1 1325 / 1343, 2 x 2 1349 / 1365;
+//                                                                     a whole AdamW iteration: 5990 with 2 x 2, 5880 with 8 x 1
+//     K > 32                                             64 x 750000  in registers 74 / 76  tile 8 x 1 80 / 82   two 61 / 92
+//                                                        48 x 4166664 in registers 377 / 382  tile 8 x 1 408 / 402
+//   other P, K <= 16                                     16 x 1500001 tile 2 x 1 34 / 44   one 42 / 48;  beyond 6e6 also where P is even
+//                                                        12 x 250002  two 5.7 / 7.7        tile 2 x 1 6.2 / 8.4 (fewer than 8 rows: too few
+//                                                                     loads in flight a lane, 10 % behind in hot buffers)
+//     K > 16, few columns                                24 x 200002  two 7.9 / 10.9       in registers 9.2 / 12.1
+//                                                        40 x 250002  two 15.2 / 20.8      in registers 17.2 / 20.4
+//     K > 16                                             24 x 500001  in registers 17 / 23  one 22 / 26  tile 2 x 2 31 / 27
+//     K of 17 to 32 beyond 100e6                         24 x 6000002 tile 2 x 2 241 / 245  in registers 253 / 252
+//                                   below                24 x 3500002 tile 2 x 2 130 / 145  in registers 122 / 144
+//     K of 33 to 64 beyond 72e6                          64 x 2000001 tile 8 x 1 220 / 229  in registers 238 / 245
+//                                   below                48 x 1200001 tile 8 x 1 86 / 106   in registers 74 / 105
+//     K > 64                                             100 x 2000002 in registers 393 / 395  two 427 / 428
+//                                   odd beyond 150e6     70 - 120 workers, mean of 45 sizes: one column 3 % ahead
 // st != nullptr: the launch acts only on the step that completes a round (h + 1 == H in the copy of the scheduler
 // state that the iteration's kernels read)
 hipError_t launch_average_rows(float *buf, int K, long long P, const DevState *st, hipStream_t s)
 {
-    const long long C4 = (P + 3) / 4;
-    if (C4 > 0x7FFFFFFFll * 64) return hipErrorInvalidValue;
-    if ((long long)K * P <= avg_narrow_most(K, P, st != nullptr)) {
-        if ((P & 3) == 2)                            // rows are 8-byte aligned: two columns at a time
-            average_rows_kernel<2><<<avg_grid(P / 2, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
-        else
-            average_rows_kernel<1><<<avg_grid(P, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
-        return hipGetLastError();
+    if ((P + 3) / 4 > 0x7FFFFFFFll * 64) return hipErrorInvalidValue;
+    const long long n = (long long)K * P;
+    const bool even = (P & 3) == 2;                  // rows are 8-byte aligned: two columns at a time
+    if (P <= 131072 && n <= 24000000)
+        return even ? launch_narrow<2>(buf, K, P, st, s) : launch_narrow<1>(buf, K, P, st, s);
+    if ((P & 3) == 0) {
+        if (K > 32) return n <= 24000000 ? launch_vec4<true>(buf, K, P, st, s) : launch_vec4<false>(buf, K, P, st, s);
+        if (K > 8 && (K > 16 || n >= 24000000)) {
+            if (n <= 56000000) return launch_narrow<2>(buf, K, P, st, s);
+            if (K > 16 || n <= 500000000) return launch_tile<32, 2, 2, true>(buf, K, P, st, s);
+            if (st != nullptr) return launch_tile<16, 8, 1, true>(buf, K, P, st, s);
+        }
+        return launch_tile<16, 2, 1, false>(buf, K, P, st, s);   // (the test of the remainder costs nothing here: 1331 / 1366)
     }
-    if (K <= 16) return launch_tile<16, 2, 1>(buf, K, P, st, s);
-    if (K <= 32) return launch_tile<32, 2, 2>(buf, K, P, st, s);
-    // rows in registers against tiles, buffers in turn (us): 40 x 600000 38 / 45, 64 x 750000 76 / 82, 40 x 1.8e6 112 / 111
-    const bool small = (P & 3) == 0 && (long long)K * P <= 66000000;
-    if (K <= 64 && !small) return launch_tile<64, 8, 1>(buf, K, P, st, s);
-    average_rows_vec4_kernel<<<avg_grid(C4, AVG_THREADS), AVG_THREADS, 0, s>>>(buf, K, P, st);
-    return hipGetLastError();
+    if (K <= 16) {
+        if (even && K >= 8 && n <= 6000000) return launch_narrow<2>(buf, K, P, st, s);
+        return launch_tile<16, 2, 1, false>(buf, K, P, st, s);
+    }
+    if (n <= 6000000 || (n <= 24000000 && (P <= 200000 || (even && K > 32))))
+        return even ? launch_narrow<2>(buf, K, P, st, s) : launch_narrow<1>(buf, K, P, st, s);
+    if (K <= 32 && n > 100000000) return launch_tile<32, 2, 2, false>(buf, K, P, st, s);
+    if (K > 32 && K <= 64 && n > 72000000) return launch_tile<64, 8, 1, false>(buf, K, P, st, s);
+    if (K > 64 && !even && n > 150000000) return launch_narrow<1>(buf, K, P, st, s);
+    return launch_vec4<false>(buf, K, P, st, s);
 }
 
 // Alg. 2's initialisation theta_k <- theta_bar^(0): copy src [P] into each of the K rows

@@ -16,7 +16,12 @@ pytestmark = pytest.mark.gpu
 # side of the sizes that take one or two columns per lane
 @pytest.mark.parametrize("K,P", [(16, 257), (17, 258), (32, 1027), (33, 259), (64, 1030), (65, 515), (3, 2), (64, 4096),
                                  (7, 131073), (8, 131076), (17, 131076), (33, 131076), (16, 200001), (16, 375002), (17, 131074), (20, 2400003),
-                                 (32, 1600001), (33, 1250003), (65, 330005)])
+                                 (32, 1600001), (33, 1250003), (65, 330005),
+                                 # aligned: 24e6 and 56e6 elements
+                                 (12, 1999996), (12, 2000000), (20, 2800000), (20, 2800004), (33, 727272), (33, 727276),
+                                 # not aligned: 6e6 and 24e6 elements, 200000 columns, 72e6, 100e6 and 150e6 elements
+                                 (17, 352941), (31, 199997), (31, 200005), (33, 200005), (33, 200006), (65, 369231),
+                                 (64, 1125001), (64, 1124997), (17, 5882355), (100, 1500001)])
 def test_averaging_of_unaligned_rows(K, P):
     average_rows_case(K, P)
 
@@ -60,4 +65,26 @@ def test_parallel_opt_state_between_the_calls(P):
     assert_params_close(ctx.params.cpu().numpy(), orc.theta, what="parallel")
     assert list(ctx.read_sync_log()[0]) == list(orc.sync_log)
     assert_mirror_matches_device(ctx)
+    ctx.close()
+
+
+def test_averaging_of_very_large_buffers_in_a_run():
+    """More than 5e8 elements of 9 to 16 workers, where the averaging of a run takes a kernel of its own: zero gradients
+    and no decay leave the parameters to the averaging alone."""
+    import torch
+    K, P = 9, 55555560
+    w = workloads.get("flat60m", K=K, P=P, T=4, opt="sgdm", mu=0.0, lam=0.0, eta_max=0.1, H_base=2, power=0, alpha=0.0, model="external")
+    ctx = gpu_ctx(w)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    start = torch.randn(K, P, device="cuda", generator=gen)
+    ctx.params.copy_(start)
+    ctx.step(1)
+    assert torch.equal(ctx.params, start)
+    ctx.step(1)
+    for c in range(0, P, 1 << 23):
+        want = start[:, c:c + (1 << 23)].double().mean(0)
+        got = ctx.params[:, c:c + (1 << 23)]
+        assert bool((got == got[:1]).all())
+        # the sum carries its rounding errors along: one rounding of it and one of the division
+        assert bool(((got[0].double() - want).abs() <= 2.0 ** -23 * want.abs() + 1e-12).all())
     ctx.close()
