@@ -257,6 +257,7 @@ constexpr int SYNC_ROWS = 4;
 // skipped launch then has four times fewer workgroups to retire than with one-wavefront blocks
 constexpr int SYNC_THREADS = 256;
 
+template <bool ALIGNED>
 __global__ __launch_bounds__(SYNC_THREADS) void update_adamw_sync_kernel(
     float *__restrict__ theta, const float *__restrict__ g, float *__restrict__ m,
     float *__restrict__ v, int K, long long P, const DevState *__restrict__ st,
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(SYNC_THREADS) void update_adamw_sync_kernel(
     const StepScalars s = sc[st->t];
     const float fK = (float)K;
     const long long P4 = P >> 2, C4 = (P + 3) >> 2;
-    const int rem = (int)(P & 3);
+    const int rem = ALIGNED ? 0 : (int)(P & 3);
     const long long stride = (long long)gridDim.x * SYNC_THREADS;
     for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < C4; i += stride) {
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), cmp = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -298,6 +299,7 @@ __global__ __launch_bounds__(SYNC_THREADS) void update_adamw_sync_kernel(
     }
 }
 
+template <bool ALIGNED>
 __global__ __launch_bounds__(SYNC_THREADS) void update_sgdm_sync_kernel(
     float *__restrict__ theta, const float *__restrict__ g, float *__restrict__ buf, int K,
     long long P, const DevState *__restrict__ st, const StepScalars *__restrict__ sc, float mu,
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(SYNC_THREADS) void update_sgdm_sync_kernel(
     const float eta = sc[st->t].x;
     const float fK = (float)K;
     const long long P4 = P >> 2, C4 = (P + 3) >> 2;
-    const int rem = (int)(P & 3);
+    const int rem = ALIGNED ? 0 : (int)(P & 3);
     const long long stride = (long long)gridDim.x * SYNC_THREADS;
     for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < C4; i += stride) {
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), cmp = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -339,6 +341,37 @@ __global__ __launch_bounds__(SYNC_THREADS) void update_sgdm_sync_kernel(
     }
 }
 
+// Short rows that are no multiple of 4: one element per lane (v == nullptr: SGD with momentum, m is its buffer, c1 = mu, c2 = lambda)
+__global__ __launch_bounds__(SYNC_THREADS) void update_sync_scalar_kernel(
+    float *__restrict__ theta, const float *__restrict__ g, float *__restrict__ m,
+    float *__restrict__ v, int K, long long P, const DevState *__restrict__ st,
+    const StepScalars *__restrict__ sc, float c1, float c2, float eps, const float *__restrict__ row_coef)
+{
+    if (st->h + 1 != st->H) return;
+    const StepScalars s = sc[st->t];
+    const float fK = (float)K;
+    const long long stride = (long long)gridDim.x * SYNC_THREADS;
+    for (long long i = (long long)blockIdx.x * SYNC_THREADS + threadIdx.x; i < P; i += stride) {
+        float acc = 0.f, cmp = 0.f;
+        for (int k = 0; k < K; ++k) {
+            const long long o = (long long)k * P + i;
+            float a = theta[o], c = m[o];
+            const float gk = row_coef != nullptr ? g[o] * row_coef[k] : g[o];
+            if (v != nullptr) {
+                float d = v[o];
+                adamw_elem(a, gk, c, d, s.x, s.y, s.z, c1, c2, eps);
+                v[o] = d;
+            } else {
+                sgdm_elem(a, gk, c, s.x, c1, c2);
+            }
+            m[o] = c;
+            add_comp(acc, cmp, a);
+        }
+        const float mean = (acc + cmp) / fK;
+        for (int k = 0; k < K; ++k) theta[(long long)k * P + i] = mean;
+    }
+}
+
 static int sync_grid(long long items)
 {
     long long blocks = (items + SYNC_THREADS - 1) / SYNC_THREADS;
@@ -348,11 +381,21 @@ static int sync_grid(long long items)
     return (int)blocks;
 }
 
+// Rows that are no multiple of 4: one element per lane while the columns are too few to fill the chip otherwise
+// (a lane's walk over the K rows is then the time, and four elements with the tests of the row's end make it longer).
+// One iteration that ends a round, one element / four, us: SGD 16 x 20001 9.9 / 12.1, 64 x 100003 32 / 39, 16 x 300001
+// 18.3 / 18.2, 16 x 500001 26.8 / 24.7, 32 x 700002 90 / 77; AdamW 16 x 100003 13.7 / 19.3, 32 x 300001 41 / 46,
+// 64 x 500001 205 / 194, 32 x 700002 128 / 116.
+static bool sync_one_per_lane(long long P) { return P <= 400000; }
+
 hipError_t launch_update_adamw_sync(float *theta, const float *g, float *m, float *v, int K, long long P,
                                     const DevState *st, const StepScalars *sc, float c1, float c2,
                                     float eps, const float *row_coef, hipStream_t s)
 {
-    update_adamw_sync_kernel<<<sync_grid((P + 3) / 4), SYNC_THREADS, 0, s>>>(theta, g, m, v, K, P, st, sc, c1, c2, eps, row_coef);
+    const int blocks = sync_grid((P + 3) / 4);
+    if ((P & 3) == 0) update_adamw_sync_kernel<true><<<blocks, SYNC_THREADS, 0, s>>>(theta, g, m, v, K, P, st, sc, c1, c2, eps, row_coef);
+    else if (sync_one_per_lane(P)) update_sync_scalar_kernel<<<sync_grid(P), SYNC_THREADS, 0, s>>>(theta, g, m, v, K, P, st, sc, c1, c2, eps, row_coef);
+    else update_adamw_sync_kernel<false><<<blocks, SYNC_THREADS, 0, s>>>(theta, g, m, v, K, P, st, sc, c1, c2, eps, row_coef);
     return hipGetLastError();
 }
 
@@ -360,7 +403,10 @@ hipError_t launch_update_sgdm_sync(float *theta, const float *g, float *buf, int
                                    const DevState *st, const StepScalars *sc, float mu, float lambda,
                                    const float *row_coef, hipStream_t s)
 {
-    update_sgdm_sync_kernel<<<sync_grid((P + 3) / 4), SYNC_THREADS, 0, s>>>(theta, g, buf, K, P, st, sc, mu, lambda, row_coef);
+    const int blocks = sync_grid((P + 3) / 4);
+    if ((P & 3) == 0) update_sgdm_sync_kernel<true><<<blocks, SYNC_THREADS, 0, s>>>(theta, g, buf, K, P, st, sc, mu, lambda, row_coef);
+    else if (sync_one_per_lane(P)) update_sync_scalar_kernel<<<sync_grid(P), SYNC_THREADS, 0, s>>>(theta, g, buf, nullptr, K, P, st, sc, mu, lambda, 0.f, row_coef);
+    else update_sgdm_sync_kernel<false><<<blocks, SYNC_THREADS, 0, s>>>(theta, g, buf, K, P, st, sc, mu, lambda, row_coef);
     return hipGetLastError();
 }
 

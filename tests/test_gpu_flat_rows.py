@@ -28,7 +28,9 @@ def test_averaging_of_unaligned_rows(K, P):
 
 # rows shorter than, as long as and longer than the 512 elements a workgroup takes at a time
 @pytest.mark.parametrize("opt", ["adamw", "sgdm"])
-@pytest.mark.parametrize("K,P,extra", [(7, 3, {}), (6, 130, {}), (3, 511, {}), (5, 513, {}), (4, 1026, dict(fuse_sync=True)),
+@pytest.mark.parametrize("K,P,extra", [(7, 3, {}), (6, 130, {}), (3, 511, {}), (5, 513, {}), (4, 1026, dict(fuse_sync=True)), (4, 1028, dict(fuse_sync=True)),
+                                       # the fused synchronization's longest rows of one element per lane, and the first of four
+                                       (3, 399999, dict(fuse_sync=True)), (3, 400001, dict(fuse_sync=True)),
                                        (5, 1001, dict(parallel=True, H_base=1, power=0, alpha=0.0)),
                                        (3, 400003, {}), (3, 400002, dict(parallel=True, H_base=1, power=0, alpha=0.0)),
                                        (3, 400004, dict(parallel=True, H_base=1, power=0, alpha=0.0))])
