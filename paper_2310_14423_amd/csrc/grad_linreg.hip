@@ -35,6 +35,9 @@ __device__ __forceinline__ float block_sum_256(float v, float *red)
 // the same counters as a bulk fill of the flat [B][d] array: where d is not a multiple of 4 a row
 // starts or ends inside a group, which the neighbouring row's workgroup draws too), store them for
 // step 3 and take the inner product; wavefront 4 draws the observation noise meanwhile.
+// WIDE (d no multiple of 4): 128-bit accesses for the groups inside the row, whose two ends take a path of their own after
+// them: see launch_residual.
+template <bool WIDE>
 __global__ __launch_bounds__(320) void linreg_residual_kernel(
     float *__restrict__ X, const float *__restrict__ theta, const float *__restrict__ wstar,
     float *__restrict__ r, long long i0, long long B, long long d, float sigma, uint64_t seed,
@@ -60,6 +63,21 @@ __global__ __launch_bounds__(320) void linreg_residual_kernel(
             const long long f0 = i * d, q0 = f0 >> 2, nq = ((f0 + d + 3) >> 2) - q0;
             for (long long q = tid; q < nq; q += 256) {
                 const long long j0 = (q0 + q) * 4 - f0;          // column of the group's first element
+                if (WIDE) {
+                    const float4 z = normal4(seed, STREAM_X, (uint32_t)k, t, (uint32_t)(q0 + q));
+                    if (j0 >= 0 && j0 + 3 < d) {                 // all groups but the row's first and last
+                        const float4 wv = ld4u(w + j0), ws = ld4u(wstar + j0);
+                        st4u(x + j0, z);
+                        acc = fmaf(z.x, wv.x - ws.x, acc); acc = fmaf(z.y, wv.y - ws.y, acc);
+                        acc = fmaf(z.z, wv.z - ws.z, acc); acc = fmaf(z.w, wv.w - ws.w, acc);
+                    } else {
+                        const float zz[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (j0 + e >= 0 && j0 + e < d) { x[j0 + e] = zz[e]; acc = fmaf(zz[e], w[j0 + e] - wstar[j0 + e], acc); }
+                    }
+                    continue;
+                }
                 float dw[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -210,10 +228,15 @@ static float *linreg_r(const ModelDims &d, void *ws)
 static hipError_t launch_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
                                   const DevState *st, hipStream_t s)
 {
+    // Rows that are no multiple of 4 long: 128-bit accesses where there is enough work to be bound by them, 32-bit ones
+    // where latency is all (an iteration, us, 128 / 32 bits: 8 x 184 x 2706723 10755 / 16600, 16 x 348 x 45554 601 / 874,
+    // 24 x 341 x 270 42 / 45, 3 x 17 x 1003 8.25 / 8.14, 2 x 54 x 211 7.98 / 7.70).
+    const bool wide = d.d_in >= 4096 || d.K * d.B >= 1024;
+    auto kern = wide ? linreg_residual_kernel<true> : linreg_residual_kernel<false>;
     // a launch takes fewer than 2^32 threads in a grid dimension: runs of 2^23 samples
     for (long long i0 = 0; i0 < d.B; i0 += 1ll << 23) {
         const long long n = d.B - i0 < (1ll << 23) ? d.B - i0 : 1ll << 23;
-        linreg_residual_kernel<<<dim3((unsigned)n, (unsigned)d.K), 320, 0, s>>>(
+        kern<<<dim3((unsigned)n, (unsigned)d.K), 320, 0, s>>>(
             (float *)ws, theta, wstar, linreg_r(d, ws), i0, d.B, d.d_in, d.data_sigma, d.seed, st);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -12,7 +12,11 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("K,d,B,opt", [(3, 1003, 17, "sgdm"), (16, 131, 76, "sgdm"), (17, 66, 9, "sgdm"), (1, 5, 1, "sgdm"),
                                        (5, 65, 33, "adamw"), (9, 1024, 8, "adamw"), (4, 64, 128, "sgdm"), (2, 3, 5, "adamw"),
-                                       (9, 66, 32, "sgdm"), (9, 66, 33, "adamw"), (8, 70, 128, "sgdm"), (8, 70, 129, "sgdm")])
+                                       (9, 66, 32, "sgdm"), (9, 66, 33, "adamw"), (8, 70, 128, "sgdm"), (8, 70, 129, "sgdm"),
+                                       # rows of 4 to 7 columns: both ends of a row in one or two groups
+                                       (2, 4, 5, "sgdm"), (2, 6, 7, "sgdm"), (3, 7, 70, "sgdm"), (2, 1, 6, "sgdm"), (2, 2, 7, "sgdm"),
+                                       # 1024 workgroups: 128-bit accesses inside such rows
+                                       (8, 6, 128, "sgdm"), (8, 67, 128, "sgdm"), (8, 3, 128, "sgdm"), (3, 4098, 5, "sgdm"), (3, 4097, 5, "sgdm")])
 def test_least_squares_shapes(K, d, B, opt):
     import torch
     kw = dict(mu=0.9, lam=1e-4) if opt == "sgdm" else dict(beta1=0.9, beta2=0.99, eps=1e-3, lam=0.01)
