@@ -346,8 +346,7 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
 // 128-bit reads of A and the 32-bit reads of B free of bank conflicts.  k beyond Kd is cleared in the
 // registers, rows and columns beyond the matrix are clamped and not stored.
 // The fp64 matrix instruction issues at 75-78 TFLOP/s from one wavefront per SIMD on (70-72 with the conversions);
-// 8 x 128 x 784 x 1024: 46.3 us with guarded loads straight to registers, 35.9 us this way (four groups, two stages;
-// two groups and four stages 37.2, one group 47.6).
+// 8 x 128 x 784 x 1024: 46.3 us with guarded loads straight to registers, 35.9 us this way (four groups, two stages).
 template <int EPI, int KSPLIT, int WT, int NS, bool BX4>
 __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_lds_kernel(GemmArgs a)
 {
@@ -542,6 +541,11 @@ inline hipError_t launch_dgemm_nn(const GemmArgs &a, int batch, hipStream_t s)
     const bool ax4 = ((a.lda | a.sA | a.Kd) & 3) == 0 && (((unsigned long long)a.A) & 15) == 0;
     const bool bx4 = ((a.ldb | a.sB | a.N) & 3) == 0 && (((unsigned long long)a.B) & 15) == 0;
     if (ax4 && a.Kd >= 64) {
+        // Groups per workgroup: several only where the tiles leave compute units idle (us, one / two / four groups):
+        // 256 tiles, contraction 784 38 / 34.6 / 33.8, 256 15.9 / 15.3 / 15.7;  752 tiles 784 89 / 88 / 98, 128 21 / 23 / 30;
+        // 5292 tiles 784 559 / 569 / 666, 112 95 / 114 / 181 (guarded loads 125)
+        if (!few && (long long)grid.x * grid.y * grid.z >= 512) return launch_dgemm_lds<EPI, 1, 4, 2>(a, batch, bx4, s);
+        if (!few && a.Kd < 512) return launch_dgemm_lds<EPI, 2, 4, 2>(a, batch, bx4, s);
         if (!few) return launch_dgemm_lds<EPI, 4, 4, 2>(a, batch, bx4, s);
         if (a.Kd >= 256) return launch_dgemm_lds<EPI, 16, 1, 2>(a, batch, bx4, s);
         return launch_dgemm_lds<EPI, 4, 1, 4>(a, batch, bx4, s);
