@@ -45,7 +45,7 @@ __global__ __launch_bounds__(320) void linreg_residual_kernel(
 {
     __shared__ float red[5];
     const int k = blockIdx.y, tid = threadIdx.x, wave = tid >> 6;
-    const long long i = i0 + blockIdx.x;
+    const long long i = (WIDE ? i0 : 0) + blockIdx.x;    // batches of more than one launch are WIDE
     const uint32_t t = (uint32_t)st->t;
     float acc = 0.f;
     if (wave < 4) {
