@@ -9,8 +9,9 @@
 //
 // Tiling: a workgroup of WM x WN wavefronts computes a BM x BN tile; K is walked in stages of
 // 32 through a ring of NS LDS buffers.  The stages are copied global -> LDS directly
-// (global_load_lds_dwordx4: no register staging, no LDS store instructions), NS - 1 of them ahead;
-// a wavefront waits for its share of the next stage only (a counted vmcnt, not 0).  That
+// (global_load_lds_dwordx4: no register staging, no LDS store instructions), NS of them ahead (a buffer is
+// requested again as soon as its stage has been read); a wavefront waits for its share of the next stage only (a
+// counted vmcnt, not 0).  That
 // instruction writes 64 lanes x 16 B to 1 KiB of consecutive LDS, so rows are stored unpadded
 // (4 pieces of 16 B) and bank conflicts are avoided by an XOR swizzle instead: slot s of row r
 // holds piece s ^ ((r >> 2) & 3), which spreads the 128-bit fragment reads of 16 consecutive rows

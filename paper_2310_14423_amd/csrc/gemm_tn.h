@@ -12,7 +12,7 @@
 // 32 features x 16 tokens in exactly the instruction's operand layout.
 //
 //  * Stages of 32 tokens are copied global -> LDS directly (global_load_lds_dwordx4) into a ring of NS
-//    buffers, NS - 1 ahead, LDS keeping [32-feature column block][32 tokens][32 features], the form
+//    buffers, NS ahead, LDS keeping [32-feature column block][32 tokens][32 features], the form
 //    the transpose reads take without bank conflicts.  Token rows beyond K are read from a block of
 //    zeros.
 //  * The order of the main loop is pinned as in gemm_bf16.h: LDS reads and copies go out one or two at

@@ -34,7 +34,7 @@ __device__ __forceinline__ void stg_nt(float4 *p, float4 v) { st_nt4(p, v); }
 // fill is bound by its arithmetic (about 220 vector instructions per four normals), this kernel by
 // HBM, and the draw hides completely behind the loads of theta, m and v (timed on MI355X at
 // 16 x 60e6: 4.02 ms against 4.63 ms for the update that reads g plus 1.01 ms for the fill).
-// One grid row per worker, like CLIP.  With `store` the draw is also written to the gradient
+// One grid row per worker: the draw's counters are a worker's own.  With `store` the draw is also written to the gradient
 // buffer (4 B written in place of the 4 B read: 28 B per element as before, but the write-heavier
 // mix runs at 5.5 TB/s instead of 5.8: 4.91 ms); without, the gradient never exists in HBM and
 // the kernel moves 12 B read + 12 B written = 24 B per element.
