@@ -17,8 +17,15 @@ namespace qsr {
 constexpr int UPD_THREADS = 64;
 constexpr int UPD_UNROLL = 2;      // float4 per array per thread per trip
 
-__device__ __forceinline__ float4 ldg_nt(const float4 *p) { return ld_nt4(p); }
-__device__ __forceinline__ void stg_nt(float4 *p, float4 v) { st_nt4(p, v); }
+// KEEP: plain accesses, for buffers that the caches hold from one launch to the next
+template <bool KEEP>
+__device__ __forceinline__ float4 ldg(const float4 *p) { return KEEP ? *p : ld_nt4(p); }
+template <bool KEEP>
+__device__ __forceinline__ void stg(float4 *p, float4 v)
+{
+    if (KEEP) *p = v;
+    else st_nt4(p, v);
+}
 
 // `fused_sync`: the context folds the averaging into the last local step of a round (see the
 // *_sync kernels below), so the plain update leaves that step alone.
@@ -73,7 +80,7 @@ __device__ __forceinline__ void scale_by_row(float4 &b, long long e, const RowAt
     }
 }
 
-template <bool CLIP, bool NOISE, bool SHARED>
+template <bool CLIP, bool NOISE, bool SHARED, bool KEEP = false>
 __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
     float4 *__restrict__ theta, float4 *__restrict__ g, float4 *__restrict__ m,
     float4 *__restrict__ v, long long n4, long long n, const DevState *__restrict__ st,
@@ -98,8 +105,8 @@ __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
         for (int u = 0; u < UPD_UNROLL; ++u) {
             long long i = base + (long long)u * UPD_THREADS;
             if (i < n4) {
-                a[u] = ldg_nt(theta + i); c[u] = ldg_nt(m + i); d[u] = ldg_nt(v + i);
-                if (!NOISE) b[u] = SHARED ? g[i] : ldg_nt(g + i);
+                a[u] = ldg<KEEP>(theta + i); c[u] = ldg<KEEP>(m + i); d[u] = ldg<KEEP>(v + i);
+                if (!NOISE) b[u] = SHARED ? g[i] : ldg<KEEP>(g + i);
             }
             if (SHARED) { b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
         }
@@ -124,7 +131,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
 #pragma unroll
                 for (int u = 0; u < UPD_UNROLL; ++u) {
                     long long i = base + (long long)u * UPD_THREADS;
-                    if (i < n4) stg_nt(g + i, b[u]);
+                    if (i < n4) stg<KEEP>(g + i, b[u]);
                 }
             }
         }
@@ -136,7 +143,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
                 adamw_elem(a[u].y, b[u].y, c[u].y, d[u].y, s.x, s.y, s.z, c1, c2, eps);
                 adamw_elem(a[u].z, b[u].z, c[u].z, d[u].z, s.x, s.y, s.z, c1, c2, eps);
                 adamw_elem(a[u].w, b[u].w, c[u].w, d[u].w, s.x, s.y, s.z, c1, c2, eps);
-                stg_nt(theta + i, a[u]); stg_nt(m + i, c[u]); stg_nt(v + i, d[u]);
+                stg<KEEP>(theta + i, a[u]); stg<KEEP>(m + i, c[u]); stg<KEEP>(v + i, d[u]);
             }
         }
     }
@@ -152,7 +159,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_adamw_kernel(
     }
 }
 
-template <bool CLIP, bool NOISE, bool SHARED>
+template <bool CLIP, bool NOISE, bool SHARED, bool KEEP = false>
 __global__ __launch_bounds__(UPD_THREADS) void update_sgdm_kernel(
     float4 *__restrict__ theta, float4 *__restrict__ g, float4 *__restrict__ buf,
     long long n4, long long n, const DevState *__restrict__ st,
@@ -177,8 +184,8 @@ __global__ __launch_bounds__(UPD_THREADS) void update_sgdm_kernel(
         for (int u = 0; u < UPD_UNROLL; ++u) {
             long long i = base + (long long)u * UPD_THREADS;
             if (i < n4) {
-                a[u] = ldg_nt(theta + i); c[u] = ldg_nt(buf + i);
-                if (!NOISE) b[u] = SHARED ? g[i] : ldg_nt(g + i);
+                a[u] = ldg<KEEP>(theta + i); c[u] = ldg<KEEP>(buf + i);
+                if (!NOISE) b[u] = SHARED ? g[i] : ldg<KEEP>(g + i);
             }
             if (SHARED) { b[u].x *= gs; b[u].y *= gs; b[u].z *= gs; b[u].w *= gs; }
         }
@@ -203,7 +210,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_sgdm_kernel(
 #pragma unroll
                 for (int u = 0; u < UPD_UNROLL; ++u) {
                     long long i = base + (long long)u * UPD_THREADS;
-                    if (i < n4) stg_nt(g + i, b[u]);
+                    if (i < n4) stg<KEEP>(g + i, b[u]);
                 }
             }
         }
@@ -215,7 +222,7 @@ __global__ __launch_bounds__(UPD_THREADS) void update_sgdm_kernel(
                 sgdm_elem(a[u].y, b[u].y, c[u].y, eta, mu, lambda);
                 sgdm_elem(a[u].z, b[u].z, c[u].z, eta, mu, lambda);
                 sgdm_elem(a[u].w, b[u].w, c[u].w, eta, mu, lambda);
-                stg_nt(theta + i, a[u]); stg_nt(buf + i, c[u]);
+                stg<KEEP>(theta + i, a[u]); stg<KEEP>(buf + i, c[u]);
             }
         }
     }
@@ -410,6 +417,12 @@ hipError_t launch_update_sgdm_sync(float *theta, const float *g, float *buf, int
     return hipGetLastError();
 }
 
+// The clipped update of buffers that the caches hold: its norm pass and the averaging or fused synchronization behind it
+// read what it read and wrote.  One iteration with rounds of four, plain / streaming accesses, us: SGD fused
+// 200 x 3457 30.4 / 37.3, 64 x 20001 19.7 / 21.7, 16 x 1000000 60 / 67; AdamW fused 64 x 4311 21 / 25; separate
+// 16 x 1000000 80 / 93, 8 x 300000 22.3 / 21.6.
+static bool clip_keeps(int K, long long P) { return (long long)K * P <= 16000000; }
+
 // row_coef != nullptr: clipped update.  shared_g: all rows of g are the same (rows of whole float4 only:
 // anything else reads its own row, with the same result).
 hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K, long long P,
@@ -426,6 +439,9 @@ hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K
     if (shared_g && (P & 3) == 0)
         update_adamw_kernel<false, false, true><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
             th4, g4, m4, v4, P / 4, P, st, sc, c1, c2, eps, fs, row_coef, rm, none, st_next, spv);
+    else if (row_coef != nullptr && clip_keeps(K, P))
+        update_adamw_kernel<true, false, false, true><<<update_grid(n4), UPD_THREADS, 0, s>>>(
+            th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, row_coef, rm, none, st_next, spv);
     else if (row_coef != nullptr)
         update_adamw_kernel<true, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, row_coef, rm, none, st_next, spv);
@@ -449,6 +465,9 @@ hipError_t launch_update_sgdm(float *theta, float *g, float *buf, int K, long lo
     if (shared_g && (P & 3) == 0)
         update_sgdm_kernel<false, false, true><<<dim3((unsigned)update_grid(P / 4), (unsigned)K), UPD_THREADS, 0, s>>>(
             th4, g4, b4, P / 4, P, st, sc, mu, lambda, fs, row_coef, rm, none, st_next, spv);
+    else if (row_coef != nullptr && clip_keeps(K, P))
+        update_sgdm_kernel<true, false, false, true><<<update_grid(n4), UPD_THREADS, 0, s>>>(
+            th4, g4, b4, n4, n, st, sc, mu, lambda, fs, row_coef, rm, none, st_next, spv);
     else if (row_coef != nullptr)
         update_sgdm_kernel<true, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, b4, n4, n, st, sc, mu, lambda, fs, row_coef, rm, none, st_next, spv);

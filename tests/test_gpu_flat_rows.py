@@ -90,3 +90,29 @@ def test_averaging_of_very_large_buffers_in_a_run():
         # the sum carries its rounding errors along: one rounding of it and one of the division
         assert bool(((got[0].double() - want).abs() <= 2.0 ** -23 * want.abs() + 1e-12).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("opt", ["adamw", "sgdm"])
+@pytest.mark.parametrize("P", [3200001, 3200004])
+def test_clipped_update_beyond_what_the_caches_hold(opt, P):
+    """More than 16e6 elements take streaming accesses, fewer plain ones: the rows four workers have in common with five
+    come out with the same bits."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    scale = torch.tensor([0.02, 1.9, 2.1, 60.0, 5.0], device="cuda")[:, None] / P ** 0.5
+    start = torch.randn(5, P, device="cuda", generator=gen)
+    grads = [torch.randn(5, P, device="cuda", generator=gen) * scale for _ in range(3)]
+    ctxs = []
+    for K in (4, 5):
+        w = workloads.get("flat60m", K=K, P=P, T=50, opt=opt, mu=0.9, model="external", clip_norm=2.0, H_base=40, power=0, alpha=0.0)
+        ctx = gpu_ctx(w)
+        ctx.params.copy_(start[:K])
+        for g in grads:
+            ctx.grads.copy_(g[:K])
+            ctx.step(1)
+        ctxs.append(ctx)
+    few, many = ctxs
+    assert torch.equal(few.params, many.params[:4]) and torch.equal(few.state0, many.state0[:4])
+    assert opt == "sgdm" or torch.equal(few.state1, many.state1[:4])
+    assert not torch.equal(few.params, start[:4])
+    few.close(); many.close()
