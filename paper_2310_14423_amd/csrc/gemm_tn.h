@@ -21,33 +21,66 @@
 //    tokens x 768 x 3072, same box.)
 //  * Large problems: tiles of 192 x 384 (wavefront 96 x 96).  768 x 3072 outputs per worker are 32
 //    such tiles, so 8 workers fill the 256 compute units exactly once.  The reduction of
-//    problems with fewer tiles can be cut into ranges (GemmNT::split): each (tile, range) is a
-//    workgroup of its own, handed to the epilogue as a batch entry of its own; the caller adds the
-//    partial results up in a fixed order.
+//    problems with fewer tiles can be cut into ranges (TnGroup::split): each (tile, range) is a
+//    workgroup of its own; the caller adds the partial results up in a fixed order.
 //  * Small problems: tiles of 64 x 64 whose reduction is shared by KG = 4 groups of four wavefronts in one
 //    workgroup, each with its own ring on a quarter of the tokens; the groups' results are added in
 //    order through LDS, with no second launch.
-//  * Tile order: worker, panels of 4 N-tiles, M-tile, N-tile inside the panel; each XCD (workgroup id
+//  * Tile order: worker, block of the model, problem, panels of 4 N-tiles, M-tile, N-tile inside the panel; each XCD (workgroup id
 //    mod 8) takes a contiguous eighth of that order: one XCD's L2 sees one worker's activations.
 //  * Bias gradients (column sums of B over the tokens) come from the B fragments the wavefronts of the
 //    first tile row already hold for their MFMAs: one bf16 dot product with ones per register pair.
 //
 // lda/ldb must be multiples of 8 elements, M and N multiples of 64 (ragged against the tile: operand
-// columns are clamped on load, the epilogue is bounds-checked); K may be ragged if GemmNT::zeros
-// is given.
+// columns are clamped on load, the epilogue is bounds-checked); K may be ragged.
 #pragma once
 #include <type_traits>
 
 #include "gemm_bf16.h"
+#include "qsr_internal.h"
 
 namespace qsr {
 
-// BLKA / BLKB: the operand is stored in 32-token x 32-feature blocks (gemm_bf16.h); lda / ldb then
-// hold its feature count.  A 1 KiB chunk of a stage (16 tokens x 32 features of one column block) is
-// then 1 KiB of consecutive memory; row-major it is 16 pieces of 64 B a whole row apart.  Either way a
-// stage lies 32 * ld elements behind the one before.
-template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, bool BLKB, class Epi>
-__global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT p, Epi epi, int Z)
+struct EpiF32 {                  // C = acc, rows of ldc
+    float *C; long long ldc;
+    static constexpr int VEC = 4;
+    typedef NoAux Aux;
+    typedef EpiPtr<float, false> Lane;
+    __device__ Lane lane(int, int row, int col, int r, int c) const { return Lane(C, ldc, row, col, r, c); }
+    __device__ Aux pre(const Lane &, int) const { return Aux{}; }
+    __device__ void operator()(const Lane &l, int dr, const float (&v)[4], const Aux &) const
+    {
+        st_nt4((float4 *)l.at(dr), make_float4(v[0], v[1], v[2], v[3]));
+    }
+};
+
+// One weight gradient of a launch, of every block (l) and worker: A and B as above, block and worker strides in
+// elements, blkA / blkB: the operand is stored in 32-token x 32-feature blocks (gemm_bf16.h); lda / ldb then hold
+// its feature count.  A 1 KiB chunk of a stage (16 tokens x 32 features of one column block) is then 1 KiB of
+// consecutive memory; row-major it is 16 pieces of 64 B a whole row apart.  Either way a stage lies 32 * ld elements
+// behind the one before.
+struct TnProblem {
+    const bf16_t *A, *B;
+    long long lda, ldb, sA, sB, lA, lB;
+    long long off, off_colsum;             // of the product (rows of N) and of B's column sums in a worker's output
+    int M, N, blkA, blkB;
+    int first;                             // first tile among a block's
+};
+// A launch: out[worker * s_out + l * l_out + off + m * N + n].  split > 1: the reduction is cut into `split` ranges of
+// k_chunk tokens (a multiple of 32), and range s of worker z takes the place of worker z * split + s.
+// Several weight gradients share a launch because most leave a last round of the chip half empty by themselves:
+// 8 x 12608 tokens, q|k|v projection (192 tiles of 192 x 384 for 256 compute units) and output projection (64).
+constexpr int TN_PROBLEMS = 4;
+struct TnGroup {
+    TnProblem p[TN_PROBLEMS];
+    int n, n_l, per_l;                     // problems, blocks, tiles of a block
+    int K, split, k_chunk;                 // tokens and their ranges
+    const bf16_t *zeros;                   // 64 bytes of zeros, read in place of token rows beyond a range
+    float *out; long long s_out, l_out;
+};
+
+template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS>
+__global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup g, int Z)
 {
     constexpr int BK = 32, NW = WM * WN;                          // wavefronts of a group
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32, MM = TM * TN, NF = TM + TN;
@@ -60,31 +93,39 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT 
     const int tid = threadIdx.x, lane = tid & 63, wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave_wg / NW, wave = wave_wg % NW;
     const int wm = wave / WN, wn = wave % WN;
-    const int nx = (p.N + BN - 1) / BN, ny = (p.M + BM - 1) / BM;
-    const int split = p.split > 1 ? p.split : 1;                  // ranges of the reduction, each a work item
-    const int per_z = nx * ny;
+    const int split = g.split > 1 ? g.split : 1;                  // ranges of the reduction, each a work item
+    const int per_z = g.per_l * g.n_l;
     int f = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     if (f >= Z * split * per_z) return;
-    const int zz = f / per_z;                                     // batch * split + range
+    const int zz = f / per_z;                                     // worker * split + range
     f -= zz * per_z;
+    const int l = f / g.per_l;
+    f -= l * g.per_l;
+    int e = 0;
+    while (e + 1 < g.n && f >= g.p[e + 1].first) ++e;
+    const TnProblem &p = g.p[e];
+    f -= p.first;
+    const int nx = (p.N + BN - 1) / BN, ny = (p.M + BM - 1) / BM;
     const int pn = f / (ny * PANEL);
     f -= pn * ny * PANEL;
     const int bw = min(PANEL, nx - pn * PANEL);
     const int my = f / bw;
     const int m0 = my * BM, n0 = (pn * PANEL + f - my * bw) * BN;
+    float *out = g.out + (long long)zz * g.s_out + l * g.l_out;
 
     // this group's tokens [k_begin, k_end), and the stages every group walks (a group that runs out
     // multiplies zeros)
-    const int z = zz / split, r0 = (zz - z * split) * (split > 1 ? p.k_chunk : 0);
-    const int r1 = split > 1 ? min(p.K, r0 + p.k_chunk) : p.K;
+    const int z = zz / split, r0 = (zz - z * split) * (split > 1 ? g.k_chunk : 0);
+    const int r1 = split > 1 ? min(g.K, r0 + g.k_chunk) : g.K;
     const int nk = ((r1 - r0 + BK - 1) / BK + KG - 1) / KG;
     const int k_begin = r0 + grp * nk * BK, k_end = min(r1, k_begin + nk * BK);
 
     // ---- copies: chunk c of a stage is 1 KiB of LDS (16 tokens x 32 features of one column block)
     bf16_t *ring = (bf16_t *)gemm_smem + grp * NS * STAGE;
     const bf16_t *src[CPW];
-    const bf16_t *A = p.A + (long long)z * p.sA + (long long)k_begin * p.lda;    // k_begin is a multiple of 32:
-    const bf16_t *B = p.B + (long long)z * p.sB + (long long)k_begin * p.ldb;    // the first block row of the range
+    const bf16_t *A = p.A + (long long)z * p.sA + l * p.lA + (long long)k_begin * p.lda;    // k_begin is a multiple of 32:
+    const bf16_t *B = p.B + (long long)z * p.sB + l * p.lB + (long long)k_begin * p.ldb;    // the first block row of the range
+    const bool blkA = p.blkA != 0, blkB = p.blkB != 0;
     const int tok = lane >> 2;
 #pragma unroll
     for (int i = 0; i < CPW; ++i) {
@@ -92,8 +133,8 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT 
         const bool isA = c < CA;
         const int cc = isA ? c : c - CA, t = (cc & 1) * 16 + tok;                // token inside the stage
         const int fc = min((isA ? m0 : n0) + (cc >> 1) * 32, (isA ? p.M : p.N) - 32) + (lane & 3) * 8;
-        if (isA) src[i] = BLKA ? A + (long long)(fc >> 5) * 1024 + t * 32 + (fc & 31) : A + (long long)t * p.lda + fc;
-        else src[i] = BLKB ? B + (long long)(fc >> 5) * 1024 + t * 32 + (fc & 31) : B + (long long)t * p.ldb + fc;
+        if (isA) src[i] = blkA ? A + (long long)(fc >> 5) * 1024 + t * 32 + (fc & 31) : A + (long long)t * p.lda + fc;
+        else src[i] = blkB ? B + (long long)(fc >> 5) * 1024 + t * 32 + (fc & 31) : B + (long long)t * p.ldb + fc;
     }
     const long long stepA = (long long)BK * p.lda, stepB = (long long)BK * p.ldb;   // elements per stage
     const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)ring;
@@ -101,16 +142,16 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT 
     auto issue = [&](int i) {
         const int c = i * NW + wave;
         if (CHUNKS % NW == 0 || c < CHUNKS) {
-            const bf16_t *g = src[i];
+            const bf16_t *q = src[i];
             if (d_row + BK > k_end) {                 // the range's last stage, or one beyond it
                 const int cc = c < CA ? c : c - CA;
-                if (d_row + (cc & 1) * 16 + tok >= k_end) g = p.zeros + (lane & 3) * 8;
+                if (d_row + (cc & 1) * 16 + tok >= k_end) q = g.zeros + (lane & 3) * 8;
             }
             // as asm: behind the builtin, the compiler takes every transpose read for a possible reader of the copies
             // in flight and waits for all of them first.  The s_nop is the wait state that such a copy needs behind a
             // write of m0 (the compiler sets m0 right before the statement, and counts wait states for its own copies only).
             const unsigned dst = __builtin_amdgcn_readfirstlane(lds_ring + d_stage * (STAGE * 2) + c * 1024);
-            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(dst), "v"(g) : "memory");
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(dst), "v"(q) : "memory");
             src[i] += c < CA ? stepA : stepB;
         }
     };
@@ -127,7 +168,7 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT 
     float csum[TN];                                   // column sums of B: lane l has 8 tokens of column l % 32 per fragment
 #pragma unroll
     for (int j = 0; j < TN; ++j) csum[j] = 0.f;
-    const bool colsum_wg = p.colsum_B != nullptr && m0 == 0;
+    const bool colsum_wg = m0 == 0;
     const bool do_colsum = colsum_wg && wm == 0;
 
     bf16x8 fa[2][TM], fb[2][TN];
@@ -253,30 +294,36 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(GemmNT 
         float s = 0.f;
 #pragma unroll
         for (int q = 0; q < KG * 2; ++q) s += cols[q * BN + tid];
-        p.colsum_B[(long long)zz * p.s_colsum + n0 + tid] = s;
+        out[p.off_colsum + n0 + tid] = s;
     }
     if (KG > 1) {
         if (grp > 0) return;
 #pragma unroll
-        for (int g = 0; g < KG - 1; ++g)
+        for (int gg = 0; gg < KG - 1; ++gg)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] += accs[(((g * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane];
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] += accs[(((gg * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane];
     }
+    const EpiF32 epi{out + p.off, p.N};
     epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane,
-                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, zz, epi);
+                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, 0, epi);
 }
 
-// Whether launch_gemm_tn can take the problem.
-inline bool gemm_tn_supports(const GemmNT &p)
+// Whether launch_gemm_tn can take the group (blocked operands: 32-column blocks; the ranges of a split reduction
+// start at multiples of 32 tokens).
+inline bool gemm_tn_supports(const TnGroup &g)
 {
-    if (p.K < 1 || p.lda % 8 != 0 || p.ldb % 8 != 0) return false;
-    if (p.M % 64 != 0 || p.N % 64 != 0 || p.M < 64 || p.N < 64) return false;
-    if (p.split > 1 && (p.k_chunk < 32 || p.k_chunk % 32 != 0 || (long long)(p.split - 1) * p.k_chunk >= p.K)) return false;
-    return p.zeros != nullptr;
+    if (g.n < 1 || g.n > TN_PROBLEMS || g.n_l < 1 || g.K < 1 || g.zeros == nullptr) return false;
+    if (g.split > 1 && (g.k_chunk < 32 || g.k_chunk % 32 != 0 || (long long)(g.split - 1) * g.k_chunk >= g.K)) return false;
+    for (int e = 0; e < g.n; ++e) {
+        const TnProblem &p = g.p[e];
+        if (p.lda % (p.blkA ? 32 : 8) != 0 || p.ldb % (p.blkB ? 32 : 8) != 0) return false;
+        if (p.M % 64 != 0 || p.N % 64 != 0 || p.M < 64 || p.N < 64) return false;
+    }
+    return true;
 }
 
 // compute units of the current device
@@ -291,23 +338,28 @@ inline int gemm_cu_count()
     return n_cu;
 }
 
-template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, bool BLKB, class Epi>
-inline hipError_t launch_gemm_tn(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
+template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS>
+inline hipError_t launch_gemm_tn(TnGroup g, int batch, hipStream_t s)
 {
-    // blocked operands: 32-column blocks (the ranges of a split reduction start at multiples of 32 tokens)
-    if (!gemm_tn_supports(p) || (BLKA && p.lda % 32 != 0) || (BLKB && p.ldb % 32 != 0)) return hipErrorInvalidValue;
+    if (!gemm_tn_supports(g)) return hipErrorInvalidValue;
     constexpr size_t smem = (size_t)KG * NS * (BM + BN) * 32 * 2;
     static_assert(smem <= 160 * 1024, "rings do not fit the 160 KB LDS");
-    auto kern = gemm_tn_kernel<BM, BN, WM, WN, KG, WPS, NS, BLKA, BLKB, Epi>;
+    auto kern = gemm_tn_kernel<BM, BN, WM, WN, KG, WPS, NS>;
     static bool lds_limit_raised = false;     // per instantiation; contexts are not thread-safe
     if (smem > 64 * 1024 && !lds_limit_raised) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         lds_limit_raised = true;
     }
-    const unsigned items = (unsigned)((p.M + BM - 1) / BM) * (unsigned)((p.N + BN - 1) / BN) * (unsigned)batch *
-                           (unsigned)(p.split > 1 ? p.split : 1);
-    kern<<<(items + 7) / 8 * 8, WM * WN * KG * 64, smem, s>>>(p, epi, batch);
+    long long per_l = 0;
+    for (int e = 0; e < g.n; ++e) {
+        g.p[e].first = (int)per_l;
+        per_l += (long long)((g.p[e].M + BM - 1) / BM) * ((g.p[e].N + BN - 1) / BN);
+    }
+    g.per_l = (int)per_l;
+    const long long items = per_l * g.n_l * batch * (g.split > 1 ? g.split : 1);
+    if ((items + 7) / 8 * 8 * (WM * WN * KG * 64) >= 1ll << 32) return hipErrorInvalidValue;   // threads of a launch
+    kern<<<(unsigned)((items + 7) / 8 * 8), WM * WN * KG * 64, smem, s>>>(g, batch);
     return hipGetLastError();
 }
 

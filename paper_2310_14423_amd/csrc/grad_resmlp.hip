@@ -72,8 +72,9 @@ struct ResWs {
     float *PART;   long long sPART;    // [2][wave_rows][d] partial dgamma, dbeta
     float *LPART;  long long sLPART;   // loss partials
     bf16_t *ZERO;                      // 256 bytes of zeros (stand-in rows of ragged GEMM slabs)
-    float *SPLITK, *SPLITKB;           // [K][WGRAD_SPLIT][largest weight matrix], [K][WGRAD_SPLIT][widest bias]
-    WgradSpace split_space;            // their sizes
+    float *SPLITK; long long split_floats;   // partial weight gradients of a launch, [K][ranges][its part of a worker's gradient]
+    // All weight gradients in one launch: a copy of DXb for each sub-block (sDXb covers them), of DH and of DQKV for each block
+    bool defer;
     // attention sub-blocks only
     bf16_t *QKV;   long long sQKV;     // [L][M][3d]
     bf16_t *O;     long long sO;       // [L][M][d]   attention output before the projection
@@ -113,8 +114,9 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.sA = padded(L * w.mdhB, 2);        w.A = (bf16_t *)take(w.sA, 2, K);
     w.sY = padded(M * d, 4);             w.Y = (float *)take(w.sY, 4, K);
     w.sDX = padded(M * d, 4);            w.DX = (float *)take(w.sDX, 4, K);
-    w.sDXb = padded(M * d, 2);           w.DXb = (bf16_t *)take(w.sDXb, 2, K);
-    w.sDH = padded(w.mdhB, 2);           w.DH = (bf16_t *)take(w.sDH, 2, K);
+    w.defer = wgrad_defer(K, M, d, dh, heads > 0, L);
+    w.sDXb = padded((w.defer ? sub : 1) * M * d, 2); w.DXb = (bf16_t *)take(w.sDXb, 2, K);
+    w.sDH = padded((w.defer ? L : 1) * w.mdhB, 2); w.DH = (bf16_t *)take(w.sDH, 2, K);
     w.sDU = padded(w.mdB > M * d ? w.mdB : M * d, 4); w.DU = (float *)take(w.sDU, 4, K);
     w.sW = padded(L * wmax, 2);
     w.W1b = (bf16_t *)take(w.sW, 2, K);  w.W1Tb = (bf16_t *)take(w.sW, 2, K);
@@ -124,9 +126,14 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.sPART = padded(2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
     w.sLPART = padded((M * d + 1023) / 1024, 4); w.LPART = (float *)take(w.sLPART, 4, K);
     w.ZERO = (bf16_t *)take(128, 2, 1);
-    w.split_space = wgrad_space(K, d, dh, heads > 0);
-    w.SPLITK = (float *)take(w.split_space.products, 4, 1);
-    w.SPLITKB = (float *)take(w.split_space.biases, 4, 1);
+    // (the span of a launch of all blocks holds the LayerNorm parameters as well)
+    const long long big_mlp = K * (wgrad_tiles(192, 384, (int)d, (int)dh) + wgrad_tiles(192, 384, (int)dh, (int)d));
+    const long long big_attn = heads > 0 ? K * (wgrad_tiles(192, 384, (int)d, (int)(3 * d)) + wgrad_tiles(192, 384, (int)d, (int)d)) : 0;
+    const bool may_split = w.defer ? wgrad_may_split(L * (big_mlp + big_attn), M)
+                                   : wgrad_may_split(big_mlp, M) || (heads > 0 && wgrad_may_split(big_attn, M));
+    const WgradSpace parts = wgrad_space(K, d, dh, heads > 0, w.defer ? L : 1);
+    w.split_floats = may_split ? parts.products + parts.biases + (w.defer ? K * WGRAD_SPLIT * 2 * sub * d : 0) : 0;
+    w.SPLITK = (float *)take(w.split_floats, 4, 1);
     w.QKV = w.O = w.DO = w.DQKV = w.Wqb = w.WqTb = w.Wob = w.WoTb = nullptr; w.LSE = nullptr;
     w.sQKV = w.sO = w.sLSE = w.sDO = w.sDQKV = w.sWq = w.sWo = 0;
     if (heads > 0) {
@@ -134,7 +141,7 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
         w.sO = padded(L * M * d, 2);         w.O = (bf16_t *)take(w.sO, 2, K);
         w.sLSE = padded(L * heads * M, 4);   w.LSE = (float *)take(w.sLSE, 4, K);
         w.sDO = padded(M * d, 2);            w.DO = (bf16_t *)take(w.sDO, 2, K);
-        w.sDQKV = padded(M * 3 * d, 2);      w.DQKV = (bf16_t *)take(w.sDQKV, 2, K);
+        w.sDQKV = padded((w.defer ? L : 1) * M * 3 * d, 2); w.DQKV = (bf16_t *)take(w.sDQKV, 2, K);
         const long long wq = blk_elems(3 * d, d) > blk_elems(d, 3 * d) ? blk_elems(3 * d, d) : blk_elems(d, 3 * d);
         w.sWq = padded(L * wq, 2);                           // blocked [d][3d] and [3d][d]
         w.Wqb = (bf16_t *)take(w.sWq, 2, K); w.WqTb = (bf16_t *)take(w.sWq, 2, K);
@@ -300,8 +307,8 @@ __device__ __forceinline__ float4 load4f(const bf16_t *p)
 // dx_out may be dx_in (each element is read and then written by the same lane): the launcher does
 // that, so the update of dx is one stream of addresses instead of two.
 // and per-wavefront partial sums of dgamma = sum_m du*xhat, dbeta = sum_m du (reduced by
-// colsum_final_kernel).
-template <int VPL, typename TDU>
+// colsum_final_kernel).  TODX: the first sub-block's input is data, whose gradient nobody reads: only the sums then.
+template <int VPL, typename TDU, bool TODX>
 __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU, long long sDU,
                                                      const float *__restrict__ X, long long sX,
                                                      const float *__restrict__ MU,
@@ -349,6 +356,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU,
                 dg[c][e] = fmaf(du[e], xh[c][e], dg[c][e]); db[c][e] += du[e];
             }
         }
+        if (!TODX) continue;
         const float m1 = wave_sum(s1) / (float)d, m2 = wave_sum(s2) / (float)d;
 #pragma unroll
         for (int c = 0; c < VPL; ++c) {
@@ -666,53 +674,75 @@ static hipError_t gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_
 }
 #define TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
 
-// out[z][i] = part[z][0][i] + part[z][1][i] + ... (ascending: a fixed order), i < n, n a multiple of 4
-__global__ __launch_bounds__(256) void splitk_sum_kernel(const float *__restrict__ part, long long n, int split,
-                                                         float *__restrict__ out, long long sOut)
+// out[z][i] = part[z][0][i] + part[z][1][i] + ... (ascending: a fixed order) for the n elements from `first` on of each
+// block (blockIdx.z, l_out apart), n a multiple of 4
+__global__ __launch_bounds__(256) void splitk_sum_kernel(const float *__restrict__ part, long long span, int split,
+                                                         float *__restrict__ out, long long sOut, long long l_out,
+                                                         long long first, long long n)
 {
-    const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= n) return;
+    const long long j = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (j >= n) return;
     const int z = blockIdx.y;
-    const float *p = part + (long long)z * split * n + i;
+    const long long i = blockIdx.z * l_out + first + j;
+    const float *p = part + (long long)z * split * span + i;
     float4 a = *(const float4 *)p;
     for (int s = 1; s < split; ++s) {
-        const float4 b = *(const float4 *)(p + (long long)s * n);
+        const float4 b = *(const float4 *)(p + (long long)s * span);
         a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
     }
     *(float4 *)(out + (long long)z * sOut + i) = a;
 }
 
-// Weight gradient dW[z] = A[z]^T B[z] (p.M x p.N, rows contiguous, per-worker stride sOut) with the
-// bias gradient (column sums of B) as a by-product.  Widths are multiples of 64 and a block of zeros stands in
-// for ragged token counts, so every weight gradient of this model qualifies.
+// Weight gradients dW = A^T B with the bias gradients (column sums of B) as by-products, collected into one launch: of
+// n_l blocks whose gradients lie l_out apart, at `base` of a worker's gradient.  Widths are multiples of 64 and a block of
+// zeros stands in for ragged token counts, so every weight gradient of this model qualifies.
 // Tile shape and token ranges: wgrad_plan.h.
-template <bool BLKA, bool BLKB>
-static hipError_t wgrad(GemmNT p, float *dW, float *db, long long sOut, const ResWs &w, int batch, hipStream_t s)
+struct WgradLaunch {
+    TnGroup t{};
+    long long lo = 0, hi = 0;                            // what a block's part of the launch covers of its gradient
+    long long lo2 = 0, hi2 = 0;                          // a second range, where all sub-blocks share the launch
+    void add(const bf16_t *A, bool blkA, long long lda, long long sA, long long lA, const bf16_t *B, bool blkB, long long ldb,
+             long long sB, long long lB, int M, int N, long long off, long long off_b)
+    {
+        TnProblem &p = t.p[t.n++];
+        p.A = A; p.B = B; p.lda = lda; p.ldb = ldb; p.sA = sA; p.sB = sB; p.lA = lA; p.lB = lB;
+        p.off = off; p.off_colsum = off_b; p.M = M; p.N = N; p.blkA = blkA; p.blkB = blkB;
+    }
+};
+static hipError_t launch_wgrad(WgradLaunch q, float *g, long long P, int tokens, const ResWs &w, int batch, hipStream_t s)
 {
-    p.zeros = w.ZERO;
-    const WgradPlan plan = wgrad_plan(p.M, p.N, p.K, batch, gemm_cu_count());
-    const long long MN = (long long)p.M * p.N;
+    TnGroup &t = q.t;
+    t.zeros = w.ZERO; t.K = tokens;
+    long long big = 0, mid = 0;
+    for (int e = 0; e < t.n; ++e) {
+        big += wgrad_tiles(192, 384, t.p[e].M, t.p[e].N);
+        mid += wgrad_tiles(128, 128, t.p[e].M, t.p[e].N);
+    }
+    const WgradPlan plan = wgrad_plan_tiles(big * t.n_l * batch, mid * t.n_l * batch, tokens, gemm_cu_count());
+    t.split = plan.split; t.k_chunk = plan.k_chunk;
+    const long long span = (t.n_l - 1) * t.l_out + (q.hi2 > q.hi ? q.hi2 : q.hi) - q.lo;
+    t.out = g + q.lo; t.s_out = P;
     if (plan.split > 1) {
-        const long long parts = (long long)batch * plan.split;
-        if (parts * MN > w.split_space.products || parts * p.N > w.split_space.biases) return hipErrorInvalidValue;
-        p.split = plan.split; p.k_chunk = plan.k_chunk;
-        p.colsum_B = w.SPLITKB; p.s_colsum = p.N;
-        EpiScaleF32 epi{w.SPLITK, p.N, MN, 1.0f};
-        if (plan.tile == WGRAD_192x384) TRY((launch_gemm_tn<192, 384, 2, 4, 1, 2, 4, BLKA, BLKB>(p, epi, batch, s)));
-        else TRY((launch_gemm_tn<128, 128, 2, 2, 1, 3, 3, BLKA, BLKB>(p, epi, batch, s)));
-        splitk_sum_kernel<<<dim3((unsigned)((MN / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITK, MN, plan.split, dW, sOut);
-        TRY(hipGetLastError());
-        splitk_sum_kernel<<<dim3((unsigned)((p.N / 4 + 255) / 256), (unsigned)batch), 256, 0, s>>>(w.SPLITKB, p.N, plan.split, db, sOut);
-        return hipGetLastError();
+        if (batch * plan.split * span > w.split_floats) return hipErrorInvalidValue;
+        t.out = w.SPLITK; t.s_out = span;
     }
-    p.colsum_B = db; p.s_colsum = sOut;
-    EpiScaleF32 epi{dW, p.N, sOut, 1.0f};
+    for (int e = 0; e < t.n; ++e) { t.p[e].off -= q.lo; t.p[e].off_colsum -= q.lo; }
     switch (plan.tile) {
-    case WGRAD_192x384: return launch_gemm_tn<192, 384, 2, 4, 1, 2, 4, BLKA, BLKB>(p, epi, batch, s);
-    case WGRAD_128x128: return launch_gemm_tn<128, 128, 2, 2, 1, 3, 3, BLKA, BLKB>(p, epi, batch, s);
-    case WGRAD_128x128_2GROUPS: return launch_gemm_tn<128, 128, 2, 2, 2, 2, 4, BLKA, BLKB>(p, epi, batch, s);
-    default: return launch_gemm_tn<64, 64, 2, 2, 4, 4, 3, BLKA, BLKB>(p, epi, batch, s);
+    case WGRAD_192x384: TRY((launch_gemm_tn<192, 384, 2, 4, 1, 2, 4>(t, batch, s))); break;
+    case WGRAD_128x128: TRY((launch_gemm_tn<128, 128, 2, 2, 1, 3, 3>(t, batch, s))); break;
+    case WGRAD_128x128_2GROUPS: TRY((launch_gemm_tn<128, 128, 2, 2, 2, 2, 4>(t, batch, s))); break;
+    default: TRY((launch_gemm_tn<64, 64, 2, 2, 4, 4, 3>(t, batch, s))); break;
     }
+    if (plan.split > 1) {
+        const long long first[2] = {0, q.lo2 - q.lo}, n[2] = {q.hi - q.lo, q.hi2 - q.lo2};
+        for (int r = 0; r < 2; ++r)
+            if (n[r] > 0) {
+                splitk_sum_kernel<<<dim3((unsigned)((n[r] / 4 + 255) / 256), (unsigned)batch, (unsigned)t.n_l), 256, 0, s>>>(
+                    w.SPLITK, span, plan.split, g + q.lo, P, t.l_out, first[r], n[r]);
+                TRY(hipGetLastError());
+            }
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g, const float *teacher,
@@ -726,6 +756,8 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     const long long per_attn = heads > 0 ? 2LL * d + 3 * dd + 3LL * d + dd + d : 0;
     const long long per_block = per_attn + 2LL * d + (long long)d * dh + dh + (long long)dh * d + d;
     if (heads > 0 && !attn_supports(d, heads, S, M)) return hipErrorInvalidValue;
+    const long long oWq = 2LL * d, obq = oWq + 3 * dd, oWo = obq + 3LL * d, obo = oWo + dd;      // inside a block
+    const long long oW1 = per_attn + 2LL * d, ob1 = oW1 + (long long)d * dh, oW2 = ob1 + dh, ob2 = oW2 + (long long)dh * d;
     ResWs w = carve(dm, ws, nullptr);
     const long long Md = (long long)M * d;            // a row-major [M][d] array (fp32 state and its relatives)
     const long long MdB = w.mdB, MdhB = w.mdhB;       // a blocked [M][d] / [M][dh] bf16 array
@@ -763,10 +795,13 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     // (d loss / d state sub, also in bf16), and the LayerNorm parameter gradients
     auto ln_bwd = [&](int sub, long long off_gamma) -> hipError_t {
         dim3 grid((unsigned)((wave_rows + 3) / 4), (unsigned)K);
+        bf16_t *const dxb_to = w.DXb + (long long)(w.defer && sub > 0 ? sub - 1 : 0) * Md;   // of the sub-block before, if there is one
 #define LN_BWD_ARGS w.X + (long long)sub * Md, w.sX, w.MU + (long long)sub * M, w.RSTD + (long long)sub * M, w.sStat, theta, P, off_gamma, \
-                    w.DX, w.DX, w.sDX, w.DXb, w.sDXb, w.PART, w.sPART, wave_rows, rows_per_wave, M, d
-#define LN_BWD(VPL) do { if (du16) ln_bwd_kernel<VPL, bf16_t><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
-                         else ln_bwd_kernel<VPL, float><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); } while (0)
+                    w.DX, w.DX, w.sDX, dxb_to, w.sDXb, w.PART, w.sPART, wave_rows, rows_per_wave, M, d
+#define LN_BWD(VPL) do { if (du16 && sub > 0) ln_bwd_kernel<VPL, bf16_t, true><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
+                         else if (du16) ln_bwd_kernel<VPL, bf16_t, false><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
+                         else if (sub > 0) ln_bwd_kernel<VPL, float, true><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); \
+                         else ln_bwd_kernel<VPL, float, false><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); } while (0)
         const int vpl = (d + 255) / 256;
         if (vpl <= 1) LN_BWD(1); else if (vpl <= 2) LN_BWD(2); else if (vpl <= 3) LN_BWD(3); else LN_BWD(4);
 #undef LN_BWD
@@ -779,7 +814,6 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
 
     // bf16 copies of the weights in both orientations (the master weights changed last step), and the teacher map
     {
-        const long long oW1 = per_attn + 2LL * d, oW2 = oW1 + (long long)d * dh + dh;
         CvtList list{};
         long long first = 0;
         auto add = [&](const float *in, long long s_in, bf16_t *out, bf16_t *outT, long long s_out, int R, int C, int n_l, int n_z) {
@@ -789,7 +823,6 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         add(theta + oW1, P, w.W1b, w.W1Tb, w.sW, d, dh, L, K);
         add(theta + oW2, P, w.W2b, w.W2Tb, w.sW, dh, d, L, K);
         if (heads > 0) {
-            const long long oWq = 2LL * d, oWo = oWq + 3 * dd + 3LL * d;
             add(theta + oWq, P, w.Wqb, w.WqTb, w.sWq, d, 3 * d, L, K);
             add(theta + oWo, P, w.Wob, w.WoTb, w.sWo, d, d, L, K);
         }
@@ -856,36 +889,56 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         const int nparts = (int)((Md + 1023) / 1024);
         const float inv = 1.0f / ((float)M * (float)d);
         loss_kernel<<<dim3((unsigned)nparts, (unsigned)K), 256, 0, s>>>(
-            w.X + (long long)(nsub * L) * Md, w.sX, w.Y, w.sY, w.DX, w.sDX, w.DXb, w.sDXb, w.LPART, w.sLPART, Md, inv);
+            w.X + (long long)(nsub * L) * Md, w.sX, w.Y, w.sY, w.DX, w.sDX, w.DXb + (long long)(w.defer ? nsub * L - 1 : 0) * Md, w.sDXb, w.LPART, w.sLPART, Md, inv);
         TRY(hipGetLastError());
         loss_final_kernel<<<K, 1024, 0, s>>>(w.LPART, w.sLPART, nparts, 0.5f * inv, loss);
         TRY(hipGetLastError());
     }
 
+    // The weight gradients of one block's MLP half and of its attention half (w.defer: as the first of all blocks')
+    const int kept = w.defer ? 1 : 0;                    // copies of the gradients w.r.t. activations: one, or one for each block
+    auto wgrad_mlp = [&](WgradLaunch &q, int l) {
+        const long long sub = (long long)nsub * l + nsub - 1, lo = l * per_block;
+        // W1 and b1:  dW1 = u^T dh, db1 = column sums of dh
+        q.add(w.U + sub * MdB, true, d, w.sU, nsub * MdB, w.DH + kept * l * MdhB, true, dh, w.sDH, kept * MdhB, d, dh, lo + oW1, lo + ob1);
+        // W2 and b2:  dW2 = a^T dx, db2 = column sums of dx
+        q.add(w.A + l * MdhB, true, dh, w.sA, MdhB, w.DXb + kept * sub * Md, false, d, w.sDXb, kept * nsub * Md, dh, d, lo + oW2, lo + ob2);
+        q.lo = lo + oW1; q.hi = lo + ob2 + d;
+    };
+    auto wgrad_attn = [&](WgradLaunch &q, int l) {
+        const long long sub = (long long)nsub * l, lo = l * per_block;
+        // Wqkv and bqkv:  dWqkv = u^T dqkv, dbqkv = column sums of dqkv
+        q.add(w.U + sub * MdB, true, d, w.sU, nsub * MdB, w.DQKV + (long long)kept * l * M * 3 * d, false, 3LL * d, w.sDQKV,
+              (long long)kept * M * 3 * d, d, 3 * d, lo + oWq, lo + obq);
+        // Wo and bo:  dWo = o^T dx, dbo = column sums of dx
+        q.add(w.O + l * Md, false, d, w.sO, Md, w.DXb + kept * sub * Md, false, d, w.sDXb, kept * nsub * Md, d, d, lo + oWo, lo + obo);
+        q.lo = lo + oWq; q.hi = lo + obo + d;
+    };
+    auto one_block = [&](WgradLaunch &q) -> hipError_t {
+        q.t.n_l = 1; q.t.l_out = per_block;
+        return launch_wgrad(q, g, P, M, w, K, s);
+    };
+
     // backward; DX (and its bf16 copy DXb) holds d loss / d (output of the sub-block at hand)
     for (int l = L - 1; l >= 0; --l) {
         int sub = nsub * l + nsub - 1;
-        const long long og = l * per_block + per_attn, oW1 = og + 2LL * d, ob1 = oW1 + (long long)d * dh,
-                        oW2 = ob1 + dh, ob2 = oW2 + (long long)dh * d;
-        // W2 and b2:  dW2 = a^T dx, db2 = column sums of dx (by-product of the same GEMM)
-        {
-            GemmNT p{w.A + (long long)l * MdhB, w.DXb, dh, d, M, dh, d, w.sA, w.sDXb};
-            TRY((wgrad<true, false>(p, g + oW2, g + ob2, P, w, K, s)));
-        }
+        const long long og = l * per_block + per_attn;
+        bf16_t *DHl = w.DH + kept * l * MdhB;
+        const bf16_t *dxb = w.DXb + (long long)kept * sub * Md;
         // dh = (dx W2^T) * gelu'(h)
         {
-            GemmNT p{w.DXb, w.W2b + l * wW2, M, dh, d, d, d, w.sDXb, w.sW};
-            EpiGeluBwd epi{w.H + (long long)l * MdhB, w.sH, w.DH, w.sDH, dh};
+            GemmNT p{dxb, w.W2b + l * wW2, M, dh, d, d, d, w.sDXb, w.sW};
+            EpiGeluBwd epi{w.H + (long long)l * MdhB, w.sH, DHl, w.sDH, dh};
             TRY(gemm_nt<false>(p, epi, K, s));
         }
-        // W1 and b1:  dW1 = u^T dh, db1 = column sums of dh
-        {
-            GemmNT p{w.U + (long long)sub * MdB, w.DH, d, dh, M, d, dh, w.sU, w.sDH};
-            TRY((wgrad<true, true>(p, g + oW1, g + ob1, P, w, K, s)));
+        if (!w.defer) {
+            WgradLaunch q;
+            wgrad_mlp(q, l);
+            TRY(one_block(q));
         }
         // du = dh W1^T, then LayerNorm backward + residual
         {
-            GemmNT p{w.DH, w.W1b + l * wW1, M, d, dh, dh, dh, w.sDH, w.sW};
+            GemmNT p{DHl, w.W1b + l * wW1, M, d, dh, dh, dh, w.sDH, w.sW};
             if (du16) {
                 EpiBf16<false> epi{DU16, d, sDU16};
                 TRY(gemm_nt<true>(p, epi, K, s));
@@ -897,35 +950,42 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         TRY(ln_bwd(sub, og));
         if (heads > 0) {
             --sub;
-            const long long oga = l * per_block, oWq = oga + 2LL * d, obq = oWq + 3 * dd, oWo = obq + 3LL * d,
-                            obo = oWo + dd;
+            const long long oga = l * per_block;
             bf16_t *QKVl = w.QKV + (long long)l * M * 3 * d, *Ol = w.O + (long long)l * Md;
-            // Wo and bo:  dWo = o^T dx, dbo = column sums of dx
-            {
-                GemmNT p{Ol, w.DXb, d, d, M, d, d, w.sO, w.sDXb};
-                TRY((wgrad<false, false>(p, g + oWo, g + obo, P, w, K, s)));
-            }
+            bf16_t *DQKVl = w.DQKV + (long long)kept * l * M * 3 * d;
+            const bf16_t *dxa = w.DXb + (long long)kept * sub * Md;
             // do = dx Wo^T
             {
-                GemmNT p{w.DXb, w.Wob + l * wWo, M, d, d, d, d, w.sDXb, w.sWo};
+                GemmNT p{dxa, w.Wob + l * wWo, M, d, d, d, d, w.sDXb, w.sWo};
                 EpiBf16<false> epi{w.DO, d, w.sDO};
                 TRY(gemm_nt<false>(p, epi, K, s));
             }
-            att.QKV = QKVl; att.O = Ol; att.LSE = w.LSE + (long long)l * heads * M;
+            att.QKV = QKVl; att.O = Ol; att.LSE = w.LSE + (long long)l * heads * M; att.DQKV = DQKVl;
             TRY(launch_attn_bwd(att, heads, K, s));
-            // Wqkv and bqkv:  dWqkv = u^T dqkv, dbqkv = column sums of dqkv
-            {
-                GemmNT p{w.U + (long long)sub * MdB, w.DQKV, d, 3 * d, M, d, 3LL * d, w.sU, w.sDQKV};
-                TRY((wgrad<true, false>(p, g + oWq, g + obq, P, w, K, s)));
+            if (!w.defer) {
+                WgradLaunch q;
+                wgrad_attn(q, l);
+                TRY(one_block(q));
             }
             // du = dqkv Wqkv^T, then LayerNorm backward + residual
             {
-                GemmNT p{w.DQKV, w.Wqb + l * wWq, M, d, 3 * d, 3LL * d, 3LL * d, w.sDQKV, w.sWq};
+                GemmNT p{DQKVl, w.Wqb + l * wWq, M, d, 3 * d, 3LL * d, 3LL * d, w.sDQKV, w.sWq};
                 EpiScaleF32 epi{w.DU, d, w.sDU, 1.0f};
                 TRY(gemm_nt<false>(p, epi, K, s));
             }
             TRY(ln_bwd(sub, oga));
         }
+    }
+    if (w.defer) {                                       // all weight gradients of all blocks
+        WgradLaunch q;
+        wgrad_mlp(q, 0);
+        if (heads > 0) {
+            const long long lo = q.lo, hi = q.hi;
+            wgrad_attn(q, 0);
+            q.lo2 = lo; q.hi2 = hi;
+        }
+        q.t.n_l = L; q.t.l_out = per_block;
+        TRY(launch_wgrad(q, g, P, M, w, K, s));
     }
     return hipSuccess;
 }

@@ -7,16 +7,15 @@ namespace qsr {
 
 constexpr int WGRAD_SPLIT = 4;          // most ranges a weight gradient's token reduction is cut into
 
-// Floats of the partial products and of the partial bias gradients for K workers of a model of width d, hidden
-// width dh: the weights are d x dh, dh x d and, with attention, d x 3d and d x d; a bias is as long as its weight's
-// second dimension.
+// Floats of the partial products and of the partial bias gradients of one launch for K workers of a model of width d,
+// hidden width dh: a launch holds the weights d x dh and dh x d or, with attention, d x 3d and d x d, of one block, or of
+// all n_blocks; a bias is as long as its weight's second dimension.
 struct WgradSpace { long long products, biases; };
-inline WgradSpace wgrad_space(long long K, long long d, long long dh, bool attention)
+inline WgradSpace wgrad_space(long long K, long long d, long long dh, bool attention, long long n_blocks = 1)
 {
-    const long long weight = d * (attention && 3 * d > dh ? 3 * d : dh);
-    long long bias = d > dh ? d : dh;
-    if (attention && 3 * d > bias) bias = 3 * d;
-    return {K * WGRAD_SPLIT * weight, K * WGRAD_SPLIT * bias};
+    const long long mlp = 2 * d * dh, attn = attention ? 4 * d * d : 0, mlp_b = d + dh, attn_b = attention ? 4 * d : 0;
+    if (n_blocks > 1) return {K * WGRAD_SPLIT * n_blocks * (mlp + attn), K * WGRAD_SPLIT * n_blocks * (mlp_b + attn_b)};
+    return {K * WGRAD_SPLIT * (mlp > attn ? mlp : attn), K * WGRAD_SPLIT * (mlp_b > attn_b ? mlp_b : attn_b)};
 }
 
 // Tile shape by the number of tiles and the length of the reduction, from timing on MI355X (us; batch x tokens x
@@ -35,11 +34,12 @@ inline WgradSpace wgrad_space(long long K, long long d, long long dh, bool atten
 // 128 x 128 (two groups per workgroup below 200 of them) and from 110 of those down to 64 x 64 with four groups.
 enum WgradTile { WGRAD_192x384, WGRAD_128x128, WGRAD_128x128_2GROUPS, WGRAD_64x64_4GROUPS };
 struct WgradPlan { WgradTile tile; int split, k_chunk; };    // split > 1: ranges of k_chunk tokens (a multiple of 32)
-inline WgradPlan wgrad_plan(int M, int N, int tokens, int batch, int n_cu)
+// whether a launch may be cut into token ranges; big: its tiles of 192 x 384
+inline bool wgrad_may_split(long long big, long long tokens) { return big < 160 && tokens >= 4096; }
+// big, mid: the launch's tiles of 192 x 384 and of 128 x 128
+inline WgradPlan wgrad_plan_tiles(long long big, long long mid, int tokens, int n_cu)
 {
-    auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch; };
-    const long long big = tiles(192, 384), mid = tiles(128, 128);
-    if (big < 160 && tokens >= 4096) {
+    if (wgrad_may_split(big, tokens)) {
         const bool large = big >= 48;
         const long long want = large ? n_cu / big : 3LL * n_cu / mid;
         int split = (int)(want < 1 ? 1 : want > WGRAD_SPLIT ? WGRAD_SPLIT : want);
@@ -48,6 +48,26 @@ inline WgradPlan wgrad_plan(int M, int N, int tokens, int batch, int n_cu)
         if (split > 1) return {large ? WGRAD_192x384 : WGRAD_128x128, split, k_chunk};
     }
     return {big >= 160 ? WGRAD_192x384 : mid >= 200 ? WGRAD_128x128 : mid >= 110 ? WGRAD_128x128_2GROUPS : WGRAD_64x64_4GROUPS, 1, 0};
+}
+inline long long wgrad_tiles(int bm, int bn, int M, int N) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
+// one weight gradient alone
+inline WgradPlan wgrad_plan(int M, int N, int tokens, int batch, int n_cu)
+{
+    return wgrad_plan_tiles(wgrad_tiles(192, 384, M, N) * batch, wgrad_tiles(128, 128, M, N) * batch, tokens, n_cu);
+}
+
+#ifndef WGRAD_DEFER_TILES
+#define WGRAD_DEFER_TILES 1024
+#endif
+// Whether the weight gradients of all blocks wait for one launch behind the backward pass (each block then keeps its
+// operands) instead of two launches per block.
+inline bool wgrad_defer(long long K, long long tokens, long long d, long long dh, bool attention, long long n_blocks)
+{
+    if (n_blocks < 2) return false;
+    const long long tiles = K * (wgrad_tiles(128, 128, (int)d, (int)dh) + wgrad_tiles(128, 128, (int)dh, (int)d) +
+                                 (attention ? wgrad_tiles(128, 128, (int)d, (int)(3 * d)) + wgrad_tiles(128, 128, (int)d, (int)d) : 0));
+    const long long bytes = K * tokens * n_blocks * (d + dh + (attention ? 4 * d : 0)) * 2;
+    return tiles < WGRAD_DEFER_TILES && bytes <= (1ll << 31);
 }
 
 }  // namespace qsr
