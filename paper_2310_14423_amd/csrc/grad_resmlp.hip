@@ -126,13 +126,8 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.sPART = padded(2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
     w.sLPART = padded((M * d + 1023) / 1024, 4); w.LPART = (float *)take(w.sLPART, 4, K);
     w.ZERO = (bf16_t *)take(128, 2, 1);
-    // (the span of a launch of all blocks holds the LayerNorm parameters as well)
-    const long long big_mlp = K * (wgrad_tiles(192, 384, (int)d, (int)dh) + wgrad_tiles(192, 384, (int)dh, (int)d));
-    const long long big_attn = heads > 0 ? K * (wgrad_tiles(192, 384, (int)d, (int)(3 * d)) + wgrad_tiles(192, 384, (int)d, (int)d)) : 0;
-    const bool may_split = w.defer ? wgrad_may_split(L * (big_mlp + big_attn), M)
-                                   : wgrad_may_split(big_mlp, M) || (heads > 0 && wgrad_may_split(big_attn, M));
-    const WgradSpace parts = wgrad_space(K, d, dh, heads > 0, w.defer ? L : 1);
-    w.split_floats = may_split ? parts.products + parts.biases + (w.defer ? K * WGRAD_SPLIT * 2 * sub * d : 0) : 0;
+    const WgradSpace parts = wgrad_space(K, d, dh, heads > 0, w.defer ? L : 1);   // (all blocks: the LayerNorm parameters as well)
+    w.split_floats = M < WGRAD_SPLIT_TOKENS ? 0 : wgrad_part_floats((parts.products + parts.biases) / WGRAD_SPLIT + (w.defer ? K * 2 * sub * d : 0));
     w.SPLITK = (float *)take(w.split_floats, 4, 1);
     w.QKV = w.O = w.DO = w.DQKV = w.Wqb = w.WqTb = w.Wob = w.WoTb = nullptr; w.LSE = nullptr;
     w.sQKV = w.sO = w.sLSE = w.sDO = w.sDQKV = w.sWq = w.sWo = 0;
@@ -713,14 +708,12 @@ static hipError_t launch_wgrad(WgradLaunch q, float *g, long long P, int tokens,
 {
     TnGroup &t = q.t;
     t.zeros = w.ZERO; t.K = tokens;
-    long long big = 0, mid = 0;
-    for (int e = 0; e < t.n; ++e) {
-        big += wgrad_tiles(192, 384, t.p[e].M, t.p[e].N);
-        mid += wgrad_tiles(128, 128, t.p[e].M, t.p[e].N);
-    }
-    const WgradPlan plan = wgrad_plan_tiles(big * t.n_l * batch, mid * t.n_l * batch, tokens, gemm_cu_count());
-    t.split = plan.split; t.k_chunk = plan.k_chunk;
+    WgradLoad load;
+    for (int e = 0; e < t.n; ++e) load.add(t.p[e].M, t.p[e].N, (long long)t.n_l * batch);
+    load.stretches = q.hi2 > q.lo2 ? 2 : 1;
     const long long span = (t.n_l - 1) * t.l_out + (q.hi2 > q.hi ? q.hi2 : q.hi) - q.lo;
+    const WgradPlan plan = wgrad_plan_load(load, tokens, gemm_cu_count(), w.split_floats, batch * span);
+    t.split = plan.split; t.k_chunk = plan.k_chunk;
     t.out = g + q.lo; t.s_out = P;
     if (plan.split > 1) {
         if (batch * plan.split * span > w.split_floats) return hipErrorInvalidValue;
