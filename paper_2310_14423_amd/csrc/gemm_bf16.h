@@ -83,7 +83,11 @@ struct GemmNT {
 //                                       requested one 32-row block ahead of their use
 //     void operator()(Lane, dr, v[VEC], aux)
 // with dr a compile-time constant after unrolling; EpiPtr below does the offsets.
+// and, if it has such a member,
+//     void finish(Lane, z, unit)     -- at the end; unit: the wavefront's number among the tiles of batch entry z
 struct NoAux {};
+template <class Epi, class = void> struct EpiHasFinish : std::false_type {};
+template <class Epi> struct EpiHasFinish<Epi, std::void_t<decltype(&Epi::finish)>> : std::true_type {};
 
 // One array as the epilogue sees it: uniform base and lane offset.  T elements, row-major with row
 // stride ld, or in 32 x 32 blocks (ld the number of columns).  dr, the rows further down, must not
@@ -110,7 +114,7 @@ struct EpiPtr {
 
 template <int TM, int TN, class Epi>
 __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *stage, int lane,
-                                                 int row0, int col0, int M, int N, int z, const Epi &epi)
+                                                 int row0, int col0, int M, int N, int z, int unit, const Epi &epi)
 {
     constexpr int W = TN * 32, LD = W + 4;             // floats per staged row
     constexpr int VEC = Epi::VEC;
@@ -168,6 +172,7 @@ __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *s
 #pragma unroll
         for (int i = 0; i < TM; ++i) block(std::false_type{}, i);
     }
+    if constexpr (EpiHasFinish<Epi>::value) epi.finish(lp, z, unit);
 }
 
 // BLKA: A is stored in 32 x 32 blocks (see above); B always is.  In LDS a stage is [BM rows][32 k] of
@@ -342,7 +347,7 @@ __global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT 
 
     __syncthreads();                                   // every wavefront is done with the ring
     epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane,
-                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, z, epi);
+                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, z, (by * nx + bx) * NW + wave, epi);
 }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));   // operand of the LDS transpose read

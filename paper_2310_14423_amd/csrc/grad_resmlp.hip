@@ -60,11 +60,10 @@ struct ResWs {
     bf16_t *H;     long long sH;       // [L][M][dh]  gelu'(pre-activation)
     bf16_t *U;     long long sU;       // [sub][M][d] LayerNorm output
     bf16_t *A;     long long sA;       // [L][M][dh]  GELU output
-    float *Y;      long long sY;       // [M][d]
     float *DX;     long long sDX;      // [M][d]
     bf16_t *DXb;   long long sDXb;     // [M][d]
     bf16_t *DH;    long long sDH;      // [M][dh]
-    float *DU;     long long sDU;      // [M][d]
+    float *DU;     long long sDU;      // [M][d]; holds the tokens in bf16 (blocked) until the loss is known
     bf16_t *W1b, *W1Tb, *W2b, *W2Tb; long long sW; // [L][blocked d x dh or dh x d] each
     long long mdB, mdhB;               // elements of one blocked [M][d] / [M][dh] activation
     long long wB[2];                   // elements of one blocked [d][dh] / [dh][d] weight
@@ -112,7 +111,6 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.sH = padded(L * w.mdhB, 2);        w.H = (bf16_t *)take(w.sH, 2, K);
     w.sU = padded(sub * w.mdB, 2);       w.U = (bf16_t *)take(w.sU, 2, K);
     w.sA = padded(L * w.mdhB, 2);        w.A = (bf16_t *)take(w.sA, 2, K);
-    w.sY = padded(M * d, 4);             w.Y = (float *)take(w.sY, 4, K);
     w.sDX = padded(M * d, 4);            w.DX = (float *)take(w.sDX, 4, K);
     w.defer = wgrad_defer(K, M, d, dh, heads > 0, L);
     w.sDXb = padded((w.defer ? sub : 1) * M * d, 2); w.DXb = (bf16_t *)take(w.sDXb, 2, K);
@@ -124,7 +122,8 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.WTt = (bf16_t *)take(blk_elems(d, d), 2, 1);
     const long long rows_per_wave = ln_rows_per_wave(K, M, d), wave_rows = (M + rows_per_wave - 1) / rows_per_wave;
     w.sPART = padded(2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
-    w.sLPART = padded((M * d + 1023) / 1024, 4); w.LPART = (float *)take(w.sLPART, 4, K);
+    w.sLPART = padded(4 * ((M + 63) / 64) * (d / 64) + 8, 4);   // a wavefront of a tile each: most for 64 x 64
+     w.LPART = (float *)take(w.sLPART, 4, K);
     w.ZERO = (bf16_t *)take(128, 2, 1);
     const WgradSpace parts = wgrad_space(K, d, dh, heads > 0, w.defer ? L : 1);   // (all blocks: the LayerNorm parameters as well)
     w.split_floats = M < WGRAD_SPLIT_TOKENS ? 0 : wgrad_part_floats((parts.products + parts.biases) / WGRAD_SPLIT + (w.defer ? K * 2 * sub * d : 0));
@@ -210,27 +209,6 @@ __global__ __launch_bounds__(256) void cvt_transpose_kernel(CvtList list)
     }
 }
 
-// Sample(): tokens x_0 ~ N(0,1), [M][d] per worker, in fp32 and in bf16 (blocked), four per lane (d a multiple of
-// 64), the draws of a bulk fill of the flat array; blockIdx.y = worker.  The first workgroup also clears the 256
-// bytes that stand in for missing rows in the weight-gradient GEMMs.
-__global__ __launch_bounds__(256) void sample_tokens_kernel(float *__restrict__ X, long long sX, bf16_t *__restrict__ U,
-                                                            long long sU, long long n4, int d, uint64_t seed,
-                                                            const DevState *__restrict__ st, bf16_t *__restrict__ zero)
-{
-    const uint32_t t = (uint32_t)st->t;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 128) zero[threadIdx.x] = (bf16_t)0.0f;
-    float4 *x = (float4 *)(X + (long long)blockIdx.y * sX);
-    bf16_t *u = U + (long long)blockIdx.y * sU;
-    const int d4 = d >> 2;
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n4) return;
-    const float4 z = normal4(seed, STREAM_X, blockIdx.y, t, (uint32_t)i);
-    st_nt4(x + i, z);
-    const long long row = i / d4;
-    const bf16x4 b = {(bf16_t)z.x, (bf16_t)z.y, (bf16_t)z.z, (bf16_t)z.w};
-    *(bf16x4 *)(u + blk_off(row, (i - row * d4) * 4, d)) = b;
-}
-
 // ---------------------------------------------------------------------------------------------
 // LayerNorm
 // ---------------------------------------------------------------------------------------------
@@ -241,44 +219,39 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// One wavefront per token row, the row held in registers as VPL float4 per lane (d <= 256 VPL,
-// d a multiple of 32): statistics in fp32, output u = gamma*xhat + beta in bf16 (64-bit stores) in
-// the blocked layout.
-template <int VPL>
-__global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ X, long long sX,
-                                                     const float *__restrict__ theta, long long sTh,
-                                                     long long off_gamma, bf16_t *__restrict__ U,
-                                                     long long sU, float *__restrict__ MU,
-                                                     float *__restrict__ RSTD, long long sStat, int M, int d)
+template <int LPR>
+__device__ __forceinline__ float row_sum(float v)      // over the LPR lanes of a row
 {
-    const int z = blockIdx.y;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= M) return;
-    const float *x = X + (long long)z * sX + (long long)row * d;
-    const float *gam = theta + (long long)z * sTh + off_gamma, *bet = gam + d;
-    float4 xv[VPL];
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// A token row lies in the registers of LPR lanes as VPL float4 each (d <= 4 LPR VPL, d a multiple of 64): narrow rows share a
+// wavefront.  Statistics in fp32, output u = gamma*xhat + beta in bf16 (64-bit stores) in the blocked layout.
+template <int VPL, int LPR>
+__device__ __forceinline__ void ln_row(const float4 (&xv)[VPL], const float *gam, bf16_t *u, float *mu_out, float *rstd_out,
+                                       int row, int d)
+{
+    const int lane = threadIdx.x & (LPR - 1);
+    const float *bet = gam + d;
     float s = 0.f;
 #pragma unroll
-    for (int c = 0; c < VPL; ++c) {
-        const int j = (lane + c * 64) * 4;
-        xv[c] = j < d ? *(const float4 *)(x + j) : make_float4(0.f, 0.f, 0.f, 0.f);
-        s += (xv[c].x + xv[c].y) + (xv[c].z + xv[c].w);
-    }
-    const float mean = wave_sum(s) / (float)d;
+    for (int c = 0; c < VPL; ++c) s += (xv[c].x + xv[c].y) + (xv[c].z + xv[c].w);
+    const float mean = row_sum<LPR>(s) / (float)d;
     float q = 0.f;
 #pragma unroll
     for (int c = 0; c < VPL; ++c) {
-        const int j = (lane + c * 64) * 4;
+        const int j = (lane + c * LPR) * 4;
         if (j < d) {
             float a = xv[c].x - mean, b = xv[c].y - mean, e = xv[c].z - mean, f = xv[c].w - mean;
             q = fmaf(a, a, q); q = fmaf(b, b, q); q = fmaf(e, e, q); q = fmaf(f, f, q);
         }
     }
-    const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + LN_EPS);
-    bf16_t *u = U + (long long)z * sU;                  // blocked [M][d]
+    const float rstd = 1.0f / sqrtf(row_sum<LPR>(q) / (float)d + LN_EPS);
 #pragma unroll
     for (int c = 0; c < VPL; ++c) {
-        const int j = (lane + c * 64) * 4;
+        const int j = (lane + c * LPR) * 4;
         if (j < d) {
             const float4 gv = *(const float4 *)(gam + j), bv = *(const float4 *)(bet + j);
             bf16x4 o = {(bf16_t)fmaf(gv.x, (xv[c].x - mean) * rstd, bv.x), (bf16_t)fmaf(gv.y, (xv[c].y - mean) * rstd, bv.y),
@@ -286,8 +259,68 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ X
             *(bf16x4 *)(u + blk_off(row, j, d)) = o;
         }
     }
-    if (lane == 0) { MU[(long long)z * sStat + row] = mean; RSTD[(long long)z * sStat + row] = rstd; }
+    if (lane == 0) { *mu_out = mean; *rstd_out = rstd; }
 }
+
+template <int VPL, int LPR>
+__global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ X, long long sX,
+                                                     const float *__restrict__ theta, long long sTh,
+                                                     long long off_gamma, bf16_t *__restrict__ U,
+                                                     long long sU, float *__restrict__ MU,
+                                                     float *__restrict__ RSTD, long long sStat, int M, int d)
+{
+    const int z = blockIdx.y;
+    const int row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR, lane = threadIdx.x & (LPR - 1);
+    if (row >= M) return;
+    const float *x = X + (long long)z * sX + (long long)row * d;
+    float4 xv[VPL];
+#pragma unroll
+    for (int c = 0; c < VPL; ++c) {
+        const int j = (lane + c * LPR) * 4;
+        xv[c] = j < d ? *(const float4 *)(x + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    ln_row<VPL, LPR>(xv, theta + (long long)z * sTh + off_gamma, U + (long long)z * sU, MU + (long long)z * sStat + row,
+                     RSTD + (long long)z * sStat + row, row, d);
+}
+
+// Sample() and the first LayerNorm: tokens x_0 ~ N(0,1), [M][d] per worker, the draws of a bulk fill of the flat array,
+// stored in fp32 and in bf16 (blocked; the teacher map's operand), and normalized while the row is at hand.  Bound by the
+// draws' arithmetic.  The first workgroup also clears the 256 bytes that stand in for missing rows in the weight-gradient
+// GEMMs.
+template <int VPL, int LPR>
+__global__ __launch_bounds__(256) void sample_ln_kernel(float *__restrict__ X, long long sX, bf16_t *__restrict__ X0,
+                                                        long long sX0, const float *__restrict__ theta, long long sTh,
+                                                        long long off_gamma, bf16_t *__restrict__ U, long long sU,
+                                                        float *__restrict__ MU, float *__restrict__ RSTD, long long sStat,
+                                                        int M, int d, uint64_t seed, const DevState *__restrict__ st,
+                                                        bf16_t *__restrict__ zero)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 128) zero[threadIdx.x] = (bf16_t)0.0f;
+    const int z = blockIdx.y;
+    const int row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR, lane = threadIdx.x & (LPR - 1);
+    if (row >= M) return;
+    const uint32_t t = (uint32_t)st->t;
+    const long long i0 = (long long)row * (d >> 2);
+    float4 *x = (float4 *)(X + (long long)z * sX) + i0;
+    bf16_t *x0 = X0 + (long long)z * sX0;
+    float4 xv[VPL];
+#pragma unroll
+    for (int c = 0; c < VPL; ++c) {
+        const int q = lane + c * LPR;
+        xv[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (q * 4 < d) {
+            xv[c] = normal4(seed, STREAM_X, (uint32_t)z, t, (uint32_t)(i0 + q));
+            st_nt4(x + q, xv[c]);
+            const bf16x4 b = {(bf16_t)xv[c].x, (bf16_t)xv[c].y, (bf16_t)xv[c].z, (bf16_t)xv[c].w};
+            *(bf16x4 *)(x0 + blk_off(row, q * 4, d)) = b;
+        }
+    }
+    ln_row<VPL, LPR>(xv, theta + (long long)z * sTh + off_gamma, U + (long long)z * sU, MU + (long long)z * sStat + row,
+                     RSTD + (long long)z * sStat + row, row, d);
+}
+// registers and lanes of a row of d
+#define LN_BY_WIDTH(d, F) do { if ((d) <= 64) F(1, 16); else if ((d) <= 128) F(1, 32); else if ((d) <= 256) F(1, 64); \
+                               else if ((d) <= 512) F(2, 64); else if ((d) <= 768) F(3, 64); else F(4, 64); } while (0)
 
 __device__ __forceinline__ float4 load4f(const float *p) { return *(const float4 *)p; }
 __device__ __forceinline__ float4 load4f(const bf16_t *p)
@@ -424,35 +457,6 @@ __global__ __launch_bounds__(64 * COLSUM_WAVES) void colsum_final_kernel(const f
 // ---------------------------------------------------------------------------------------------
 // loss
 // ---------------------------------------------------------------------------------------------
-// r = x_L - y; dx = r/(M d) (fp32 and bf16); per-block partial sums of r^2
-__global__ __launch_bounds__(256) void loss_kernel(const float *__restrict__ XL, long long sX,
-                                                   const float *__restrict__ Y, long long sY,
-                                                   float *__restrict__ DX, long long sDX,
-                                                   bf16_t *__restrict__ DXb, long long sDXb,
-                                                   float *__restrict__ LPART, long long sLPART,
-                                                   long long n, float inv)
-{
-    __shared__ float red[4];
-    const int z = blockIdx.y;
-    float acc = 0.f;
-    const long long base = (long long)blockIdx.x * 1024;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        long long i = base + u * 256 + threadIdx.x;
-        if (i < n) {
-            float r = XL[(long long)z * sX + i] - Y[(long long)z * sY + i];
-            acc = fmaf(r, r, acc);
-            float g = r * inv;
-            DX[(long long)z * sDX + i] = g;
-            DXb[(long long)z * sDXb + i] = (bf16_t)g;
-        }
-    }
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) LPART[(long long)z * sLPART + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-}
-
 // (256 lanes took 17 us for 9456 parts, one load after the other)
 __global__ __launch_bounds__(1024) void loss_final_kernel(const float *__restrict__ LPART, long long sLPART,
                                                           int nparts, float scale, float *__restrict__ loss)
@@ -516,6 +520,37 @@ __device__ __forceinline__ bf16x8 pack8(const float (&v)[8])
     return r;
 }
 
+struct EpiLoss {                 // y = scale * acc; r = x_L - y; dx = inv * r in fp32 and bf16; sums of r^2
+    // The targets never exist in memory (written and read again by a kernel of its own: 155 + 178 us at 8 x 12608 x 768).
+    const float *X; long long sX; float *DX; long long sDX; bf16_t *DXb; long long sDXb; float *LPART; long long sLPART;
+    long long ld; float scale, inv;
+    static constexpr int VEC = 4;
+    typedef float4 Aux;
+    struct Lane { EpiPtr<const float, false> x; EpiPtr<float, false> o; EpiPtr<bf16_t, false> b; mutable double sum; };
+    __device__ Lane lane(int z, int row, int col, int r, int c) const
+    {
+        return Lane{EpiPtr<const float, false>(X + (long long)z * sX, ld, row, col, r, c),
+                    EpiPtr<float, false>(DX + (long long)z * sDX, ld, row, col, r, c),
+                    EpiPtr<bf16_t, false>(DXb + (long long)z * sDXb, ld, row, col, r, c), 0.0};
+    }
+    __device__ Aux pre(const Lane &l, int dr) const { return ld_nt4((const float4 *)l.x.at(dr)); }
+    __device__ void operator()(const Lane &l, int dr, const float (&v)[4], const Aux &x) const
+    {
+        const float r[4] = {x.x - v[0] * scale, x.y - v[1] * scale, x.z - v[2] * scale, x.w - v[3] * scale};
+        l.sum += (double)fmaf(r[0], r[0], r[1] * r[1]) + (double)fmaf(r[2], r[2], r[3] * r[3]);
+        const float g[4] = {r[0] * inv, r[1] * inv, r[2] * inv, r[3] * inv};
+        st_nt4((float4 *)l.o.at(dr), make_float4(g[0], g[1], g[2], g[3]));
+        const bf16x4 b = {(bf16_t)g[0], (bf16_t)g[1], (bf16_t)g[2], (bf16_t)g[3]};
+        __builtin_nontemporal_store(b, (bf16x4 *)l.b.at(dr));
+    }
+    __device__ void finish(const Lane &l, int z, int unit) const
+    {
+        double s = l.sum;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if ((threadIdx.x & 63) == 0) LPART[(long long)z * sLPART + unit] = (float)s;
+    }
+};
 struct EpiScaleF32 {             // C = scale * acc
     float *C; long long ldc, sC; float scale;
     static constexpr int VEC = 4;
@@ -656,16 +691,36 @@ struct EpiGeluBwd {              // dh = acc * gelu'(h), H holding gelu'(h) from
 // tile's smaller copy volume wins once there are enough tiles for several rounds of the chip.  The smaller tiles
 // are for problems that would leave compute units without work: below two rounds of 128 x 256 (or where it would
 // pad N by a fifth or more) 128 x 128, and below 160 of those 64 x 64.
+enum NtShape { NT_256x256, NT_128x256, NT_128x128, NT_64x64 };
+static NtShape nt_shape(const GemmNT &p, int batch)
+{
+    auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * batch; };
+    const bool wide = 5LL * ((p.N + 255) / 256) * 256 < 6LL * p.N;
+    if (wide && p.K >= 1024 && tiles(256, 256) >= 1024) return NT_256x256;
+    if (wide && tiles(128, 256) >= 1024) return NT_128x256;
+    return tiles(128, 128) >= 160 ? NT_128x128 : NT_64x64;
+}
+// wavefronts of all tiles of a batch entry
+static int nt_units(const GemmNT &p, int batch)
+{
+    auto tiles = [&](int bm, int bn) { return ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
+    switch (nt_shape(p, batch)) {
+    case NT_256x256: return 8 * tiles(256, 256);
+    case NT_128x256: return 4 * tiles(128, 256);
+    case NT_128x128: return 4 * tiles(128, 128);
+    default: return 4 * tiles(64, 64);
+    }
+}
 // BLKA: the activation operand is blocked (the weights always are).
 template <bool BLKA, class Epi>
 static hipError_t gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
-    auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * batch; };
-    const bool wide = 5LL * ((p.N + 255) / 256) * 256 < 6LL * p.N;
-    if (wide && p.K >= 1024 && tiles(256, 256) >= 1024) return launch_gemm_nt<256, 256, 2, 4, 2, 4, BLKA>(p, epi, batch, s);
-    if (wide && tiles(128, 256) >= 1024) return launch_gemm_nt<128, 256, 1, 4, 2, 3, BLKA>(p, epi, batch, s);
-    if (tiles(128, 128) >= 160) return launch_gemm_nt<128, 128, 2, 2, 3, 3, BLKA>(p, epi, batch, s);
-    return launch_gemm_nt<64, 64, 2, 2, 4, 4, BLKA>(p, epi, batch, s);
+    switch (nt_shape(p, batch)) {
+    case NT_256x256: return launch_gemm_nt<256, 256, 2, 4, 2, 4, BLKA>(p, epi, batch, s);
+    case NT_128x256: return launch_gemm_nt<128, 256, 1, 4, 2, 3, BLKA>(p, epi, batch, s);
+    case NT_128x128: return launch_gemm_nt<128, 128, 2, 2, 3, 3, BLKA>(p, epi, batch, s);
+    default: return launch_gemm_nt<64, 64, 2, 2, 4, 4, BLKA>(p, epi, batch, s);
+    }
 }
 #define TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
 
@@ -767,11 +822,10 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
 
     // LayerNorm of residual state number `sub` with the parameters at off_gamma
     auto ln_fwd = [&](int sub, long long off_gamma) -> hipError_t {
-        dim3 grid((unsigned)((M + 3) / 4), (unsigned)K);
-#define LN_FWD(VPL) ln_fwd_kernel<VPL><<<grid, 256, 0, s>>>(w.X + (long long)sub * Md, w.sX, theta, P, off_gamma, \
+#define LN_FWD(VPL, LPR) ln_fwd_kernel<VPL, LPR><<<dim3((unsigned)((M + 256 / LPR - 1) / (256 / LPR)), (unsigned)K), 256, 0, s>>>( \
+                        w.X + (long long)sub * Md, w.sX, theta, P, off_gamma, \
                         w.U + (long long)sub * MdB, w.sU, w.MU + (long long)sub * M, w.RSTD + (long long)sub * M, w.sStat, M, d)
-        const int vpl = (d + 255) / 256;
-        if (vpl <= 1) LN_FWD(1); else if (vpl <= 2) LN_FWD(2); else if (vpl <= 3) LN_FWD(3); else LN_FWD(4);
+        LN_BY_WIDTH(d, LN_FWD);
 #undef LN_FWD
         return hipGetLastError();
     };
@@ -828,15 +882,14 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     const long long wW1 = w.wB[0], wW1T = w.wB[1], wW2 = w.wB[1], wW2T = w.wB[0];
     const long long wWq = blk_elems(d, 3 * d), wWqT = blk_elems(3 * d, d), wWo = blk_elems(d, d);
 
-    // Sample(): tokens x_0 (fp32 in X[0], bf16 in U), teacher targets y = x_0 W_T / sqrt(d)
-    sample_tokens_kernel<<<dim3((unsigned)((Md / 4 + 255) / 256), (unsigned)K), 256, 0, s>>>(
-        w.X, w.sX, w.U, w.sU, Md / 4, d, dm.seed, st, w.ZERO);
+    // Sample(): tokens x_0 (fp32 in X[0], bf16 in DU), and the first sub-block's LayerNorm
+    bf16_t *const X0 = (bf16_t *)w.DU;
+    const long long sX0 = 2 * w.sDU;
+#define SAMPLE_LN(VPL, LPR) sample_ln_kernel<VPL, LPR><<<dim3((unsigned)((M + 256 / LPR - 1) / (256 / LPR)), (unsigned)K), 256, 0, s>>>( \
+                        w.X, w.sX, X0, sX0, theta, P, heads > 0 ? 0 : per_attn, w.U, w.sU, w.MU, w.RSTD, w.sStat, M, d, dm.seed, st, w.ZERO)
+    LN_BY_WIDTH(d, SAMPLE_LN);
+#undef SAMPLE_LN
     TRY(hipGetLastError());
-    {
-        GemmNT p{w.U, w.WTt, M, d, d, d, d, w.sU, 0};
-        EpiScaleF32 epi{w.Y, d, w.sY, 1.0f / sqrtf((float)d)};
-        TRY(gemm_nt<true>(p, epi, K, s));
-    }
 
     // forward
     for (int l = 0; l < L; ++l) {
@@ -844,7 +897,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         if (heads > 0) {
             const long long oga = l * per_block, obq = oga + 2LL * d + 3 * dd, obo = obq + 3LL * d + dd;
             bf16_t *QKVl = w.QKV + (long long)l * M * 3 * d, *Ol = w.O + (long long)l * Md;
-            TRY(ln_fwd(sub, oga));
+            if (sub > 0) TRY(ln_fwd(sub, oga));
             {
                 GemmNT p{w.U + (long long)sub * MdB, w.WqTb + l * wWqT, M, 3 * d, d, d, d, w.sU, w.sWq};
                 EpiBiasBf16 epi{theta + obq, P, QKVl, 3LL * d, w.sQKV, 3 * d};
@@ -864,7 +917,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         const float *Xl = w.X + (long long)sub * Md;
         float *Xn = w.X + (long long)(sub + 1) * Md;
         bf16_t *Ul = w.U + (long long)sub * MdB, *Al = w.A + (long long)l * MdhB;
-        TRY(ln_fwd(sub, og));
+        if (sub > 0) TRY(ln_fwd(sub, og));
         {
             GemmNT p{Ul, w.W1Tb + l * wW1T, M, dh, d, d, d, w.sU, w.sW};
             EpiBiasGelu epi{theta + ob1, P, w.H + (long long)l * MdhB, w.sH, Al, w.sA, dh};
@@ -877,14 +930,14 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         }
     }
 
-    // loss and d loss / d x_L
+    // targets y = x_0 W_T / sqrt(d), loss and d loss / d x_L
     {
-        const int nparts = (int)((Md + 1023) / 1024);
         const float inv = 1.0f / ((float)M * (float)d);
-        loss_kernel<<<dim3((unsigned)nparts, (unsigned)K), 256, 0, s>>>(
-            w.X + (long long)(nsub * L) * Md, w.sX, w.Y, w.sY, w.DX, w.sDX, w.DXb + (long long)(w.defer ? nsub * L - 1 : 0) * Md, w.sDXb, w.LPART, w.sLPART, Md, inv);
-        TRY(hipGetLastError());
-        loss_final_kernel<<<K, 1024, 0, s>>>(w.LPART, w.sLPART, nparts, 0.5f * inv, loss);
+        GemmNT p{X0, w.WTt, M, d, d, d, d, sX0, 0};
+        EpiLoss epi{w.X + (long long)(nsub * L) * Md, w.sX, w.DX, w.sDX, w.DXb + (long long)(w.defer ? nsub * L - 1 : 0) * Md, w.sDXb,
+                    w.LPART, w.sLPART, d, 1.0f / sqrtf((float)d), inv};
+        TRY(gemm_nt<true>(p, epi, K, s));
+        loss_final_kernel<<<K, 1024, 0, s>>>(w.LPART, w.sLPART, nt_units(p, K), 0.5f * inv, loss);
         TRY(hipGetLastError());
     }
 
