@@ -39,18 +39,23 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr float LN_EPS = 1e-5f;
 
-// Token rows per wavefront of the LayerNorm backward pass: enough that all wavefronts of the launch are resident at
-// once (a launch of 1.5 times the chip's wavefront slots runs as one full wave of workgroups and a half-empty one:
-// 283 against 234 us at 8 x 12608 rows of 768), resident wavefronts per compute unit following from the kernel's
-// registers; and not fewer than 4, since each wavefront leaves a row of partial sums for the parameter
-// gradients.  (With at least 16, few tokens left most of the chip idle: 27 us at 2 x 1040 rows of 192.)
+// The LayerNorm backward pass: LPR lanes hold a token row of d, 64 / LPR rows lie side by side in a wavefront and R of those
+// are in flight at once.  Rows of a wavefront: enough that all wavefronts of the launch are resident at once (a
+// launch of 1.5 times the chip's wavefront slots runs as one full wave of workgroups and a half-empty one: 283 against 234 us
+// at 8 x 12608 rows of 768), resident wavefronts per compute unit following from the kernel's registers; and not
+// fewer than 4, since each wavefront leaves a row of partial sums for the parameter gradients (with at least 16, few
+// tokens left most of the chip idle: 27 us at 2 x 1040 rows of 192).
+constexpr int LN_ROWS_MIN = 4;
 static int ln_rows_per_wave(long long K, long long M, long long d)
 {
     const int vpl = (int)((d + 255) / 256);
-    const long long slots = 256LL * (vpl <= 1 ? 28 : vpl == 2 ? 20 : vpl == 3 ? 16 : 12);
+    const long long slots = 256LL * (vpl <= 2 ? 20 : vpl == 3 ? 16 : 12);
     const long long rows = (K * M + slots - 1) / slots;
-    return (int)(rows < 4 ? 4 : rows);
+    return (int)(rows < LN_ROWS_MIN ? LN_ROWS_MIN : rows);
 }
+// Rows in flight: what the registers hold where latency is all (the least rows per wavefront), one or two where the
+// wavefronts beside it hide it.
+template <int VPL> constexpr int ln_bwd_rows(bool few) { return few ? (VPL <= 2 ? 4 : 2) : (VPL == 1 ? 2 : 1); }
 
 struct ResWs {
     // per-replica strides are the element counts of one replica's array
@@ -121,7 +126,7 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.W2b = (bf16_t *)take(w.sW, 2, K);  w.W2Tb = (bf16_t *)take(w.sW, 2, K);
     w.WTt = (bf16_t *)take(blk_elems(d, d), 2, 1);
     const long long rows_per_wave = ln_rows_per_wave(K, M, d), wave_rows = (M + rows_per_wave - 1) / rows_per_wave;
-    w.sPART = padded(2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
+    w.sPART = padded((w.defer ? sub : 1) * 2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
     w.sLPART = padded(4 * ((M + 63) / 64) * (d / 64) + 8, 4);   // a wavefront of a tile each: most for 64 x 64
      w.LPART = (float *)take(w.sLPART, 4, K);
     w.ZERO = (bf16_t *)take(128, 2, 1);
@@ -212,13 +217,6 @@ __global__ __launch_bounds__(256) void cvt_transpose_kernel(CvtList list)
 // ---------------------------------------------------------------------------------------------
 // LayerNorm
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 template <int LPR>
 __device__ __forceinline__ float row_sum(float v)      // over the LPR lanes of a row
 {
@@ -336,7 +334,7 @@ __device__ __forceinline__ float4 load4f(const bf16_t *p)
 // that, so the update of dx is one stream of addresses instead of two.
 // and per-wavefront partial sums of dgamma = sum_m du*xhat, dbeta = sum_m du (reduced by
 // colsum_final_kernel).  TODX: the first sub-block's input is data, whose gradient nobody reads: only the sums then.
-template <int VPL, typename TDU, bool TODX>
+template <int VPL, int LPR, int R, typename TDU, bool TODX>
 __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU, long long sDU,
                                                      const float *__restrict__ X, long long sX,
                                                      const float *__restrict__ MU,
@@ -348,65 +346,104 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU,
                                                      float *__restrict__ PART, long long sPART,
                                                      int wave_rows, int rows_per_wave, int M, int d)
 {
+    constexpr int G = 64 / LPR;                          // rows side by side
     const int z = blockIdx.y;
-    const int wr = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wr = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & (LPR - 1), grp = (threadIdx.x & 63) / LPR;
     if (wr >= wave_rows) return;
     const float *gam = theta + (long long)z * sTh + off_gamma;
+    const TDU *du_z = DU + (long long)z * sDU;
+    const float *x_z = X + (long long)z * sX, *di_z = DXin + (long long)z * sDX;
+    const float *mu_z = MU + (long long)z * sStat, *rs_z = RSTD + (long long)z * sStat;
     float g[VPL][4], dg[VPL][4], db[VPL][4];
 #pragma unroll
     for (int c = 0; c < VPL; ++c) {
-        const int j = (lane + c * 64) * 4;
+        const int j = (lane + c * LPR) * 4;
         const float4 gv = j < d ? *(const float4 *)(gam + j) : make_float4(0.f, 0.f, 0.f, 0.f);
         g[c][0] = gv.x; g[c][1] = gv.y; g[c][2] = gv.z; g[c][3] = gv.w;
 #pragma unroll
         for (int e = 0; e < 4; ++e) { dg[c][e] = 0.f; db[c][e] = 0.f; }
     }
     const int r_end = min(M, (wr + 1) * rows_per_wave);
-    for (int row = wr * rows_per_wave; row < r_end; ++row) {
-        const long long o = (long long)row * d;
-        const float mean = MU[(long long)z * sStat + row], rstd = RSTD[(long long)z * sStat + row];
-        float xh[VPL][4], dn[VPL][4];
-        float s1 = 0.f, s2 = 0.f;
+    for (int row0 = wr * rows_per_wave + grp; row0 < r_end; row0 += R * G) {
+        float4 duv[R][VPL], xv[R][VPL], di[R][VPL];
+        float mean[R], rstd[R];
+        // all loads of R rows first; a row beyond the run is read again as the first one and counts for nothing
 #pragma unroll
-        for (int c = 0; c < VPL; ++c) {
-            const int j = (lane + c * 64) * 4;
-            float4 duv = make_float4(0.f, 0.f, 0.f, 0.f), xv = make_float4(mean, mean, mean, mean);
-            if (j < d) {
-                duv = load4f(DU + (long long)z * sDU + o + j);     // row-major in either type: no GEMM reads it
-                xv = *(const float4 *)(X + (long long)z * sX + o + j);
+        for (int u = 0; u < R; ++u) {
+            const int row = u == 0 || row0 + u * G < r_end ? row0 + u * G : row0;
+            const long long o = (long long)row * d;
+            mean[u] = mu_z[row]; rstd[u] = rs_z[row];
+#pragma unroll
+            for (int c = 0; c < VPL; ++c) {
+                const int j = (lane + c * LPR) * 4;
+                if (j < d) {
+                    duv[u][c] = load4f(du_z + o + j);    // row-major in either type: no GEMM reads it
+                    xv[u][c] = *(const float4 *)(x_z + o + j);
+                    if (TODX) di[u][c] = *(const float4 *)(di_z + o + j);
+                }
             }
-            const float du[4] = {duv.x, duv.y, duv.z, duv.w}, xx[4] = {xv.x, xv.y, xv.z, xv.w};
+        }
+        float s1[R], s2[R];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                xh[c][e] = (xx[e] - mean) * rstd;
-                dn[c][e] = du[e] * g[c][e];
-                s1 += dn[c][e]; s2 = fmaf(dn[c][e], xh[c][e], s2);
-                dg[c][e] = fmaf(du[e], xh[c][e], dg[c][e]); db[c][e] += du[e];
+        for (int u = 0; u < R; ++u) {
+            const bool in = u == 0 || row0 + u * G < r_end;
+            s1[u] = 0.f; s2[u] = 0.f;
+#pragma unroll
+            for (int c = 0; c < VPL; ++c) {
+                const int j = (lane + c * LPR) * 4;
+                if (j >= d || !in) { duv[u][c] = make_float4(0.f, 0.f, 0.f, 0.f); xv[u][c] = make_float4(mean[u], mean[u], mean[u], mean[u]); }
+                const float du[4] = {duv[u][c].x, duv[u][c].y, duv[u][c].z, duv[u][c].w};
+                const float xx[4] = {xv[u][c].x, xv[u][c].y, xv[u][c].z, xv[u][c].w};
+                float xh[4], dn[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    xh[e] = (xx[e] - mean[u]) * rstd[u];
+                    dn[e] = du[e] * g[c][e];
+                    s1[u] += dn[e]; s2[u] = fmaf(dn[e], xh[e], s2[u]);
+                    dg[c][e] = fmaf(du[e], xh[e], dg[c][e]); db[c][e] += du[e];
+                }
+                xv[u][c] = make_float4(xh[0], xh[1], xh[2], xh[3]);
+                duv[u][c] = make_float4(dn[0], dn[1], dn[2], dn[3]);
             }
         }
         if (!TODX) continue;
-        const float m1 = wave_sum(s1) / (float)d, m2 = wave_sum(s2) / (float)d;
 #pragma unroll
-        for (int c = 0; c < VPL; ++c) {
-            const int j = (lane + c * 64) * 4;
-            if (j < d) {
-                const float4 di = *(const float4 *)(DXin + (long long)z * sDX + o + j);
-                float4 v;
-                v.x = di.x + rstd * (dn[c][0] - m1 - xh[c][0] * m2);
-                v.y = di.y + rstd * (dn[c][1] - m1 - xh[c][1] * m2);
-                v.z = di.z + rstd * (dn[c][2] - m1 - xh[c][2] * m2);
-                v.w = di.w + rstd * (dn[c][3] - m1 - xh[c][3] * m2);
-                *(float4 *)(DXout + (long long)z * sDX + o + j) = v;
-                bf16x4 b = {(bf16_t)v.x, (bf16_t)v.y, (bf16_t)v.z, (bf16_t)v.w};
-                *(bf16x4 *)(DXb + (long long)z * sDXb + o + j) = b;
+        for (int u = 0; u < R; ++u) {
+            const float m1 = row_sum<LPR>(s1[u]) / (float)d, m2 = row_sum<LPR>(s2[u]) / (float)d;
+            const int row = row0 + u * G;
+            if (u > 0 && row >= r_end) continue;
+            const long long o = (long long)row * d;
+#pragma unroll
+            for (int c = 0; c < VPL; ++c) {
+                const int j = (lane + c * LPR) * 4;
+                if (j < d) {
+                    float4 v;
+                    v.x = di[u][c].x + rstd[u] * (duv[u][c].x - m1 - xv[u][c].x * m2);
+                    v.y = di[u][c].y + rstd[u] * (duv[u][c].y - m1 - xv[u][c].y * m2);
+                    v.z = di[u][c].z + rstd[u] * (duv[u][c].z - m1 - xv[u][c].z * m2);
+                    v.w = di[u][c].w + rstd[u] * (duv[u][c].w - m1 - xv[u][c].w * m2);
+                    *(float4 *)(DXout + (long long)z * sDX + o + j) = v;
+                    bf16x4 b = {(bf16_t)v.x, (bf16_t)v.y, (bf16_t)v.z, (bf16_t)v.w};
+                    *(bf16x4 *)(DXb + (long long)z * sDXb + o + j) = b;
+                }
             }
         }
+    }
+    // rows side by side are added up across the wavefront
+    if (G > 1) {
+#pragma unroll
+        for (int c = 0; c < VPL; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int o = LPR; o < 64; o <<= 1) { dg[c][e] += __shfl_xor(dg[c][e], o, 64); db[c][e] += __shfl_xor(db[c][e], o, 64); }
+        if (grp > 0) return;
     }
     float *pg = PART + (long long)z * sPART + (long long)wr * d;
     float *pb = PART + (long long)z * sPART + ((long long)wave_rows + wr) * d;
 #pragma unroll
     for (int c = 0; c < VPL; ++c) {
-        const int j = (lane + c * 64) * 4;
+        const int j = (lane + c * LPR) * 4;
         if (j < d) {
             *(float4 *)(pg + j) = make_float4(dg[c][0], dg[c][1], dg[c][2], dg[c][3]);
             *(float4 *)(pb + j) = make_float4(db[c][0], db[c][1], db[c][2], db[c][3]);
@@ -417,68 +454,64 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU,
 // ---------------------------------------------------------------------------------------------
 // column sums: final stage of the LayerNorm parameter gradients
 // ---------------------------------------------------------------------------------------------
-// out[z][j] = sum_c PART[z][c][j].  A workgroup owns 64 columns; its 16 wavefronts each sum a
-// contiguous run of the chunks in ascending order, eight loads in flight, and the partial sums are added in
-// wavefront order (fixed order: deterministic).  (Four wavefronts: 11.8 us for 505 chunks, a chain of loads.)
+// Column sums of the partial rows that the wavefronts of a LayerNorm backward pass leave, and (last entry of blockIdx.z) the
+// loss from its partial sums.  A workgroup owns 64 columns of dgamma or dbeta of one worker and LayerNorm; its 16
+// wavefronts each sum a contiguous run of the chunks in ascending order, eight loads in flight, and the partial sums are
+// added in wavefront order (fixed order: deterministic).  (Four wavefronts: 11.8 us for 505 chunks, a chain of loads.)
+struct ColsumArgs {
+    const float *part; long long s_part; int chunks, cols;      // [worker][LayerNorm][dgamma, dbeta][chunks][cols]
+    float *out; long long s_out;                                // a worker's gradient
+    long long off[2], l_out; int nsub;                          // LayerNorm i: at off[i % nsub] + i / nsub * l_out
+    int sums;                                                   // LayerNorms times two
+    const float *lpart; long long s_lpart; int n_lpart; float scale; float *loss;
+};
 constexpr int COLSUM_WAVES = 16;
-__global__ __launch_bounds__(64 * COLSUM_WAVES) void colsum_final_kernel(const float *__restrict__ PART, long long sPART,
-                                                           float *__restrict__ out, long long sOut,
-                                                           int chunks, int cols)
+__global__ __launch_bounds__(64 * COLSUM_WAVES) void colsum_final_kernel(ColsumArgs q)
 {
-    // blockIdx.z selects the partial array (0: dgamma, 1: dbeta); the results are adjacent
     __shared__ float red[COLSUM_WAVES][64];
-    const int z = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + lane;
-    const float *p = PART + (long long)z * sPART + (long long)blockIdx.z * chunks * cols;
-    out += (long long)blockIdx.z * cols;
-    const int per = (chunks + COLSUM_WAVES - 1) / COLSUM_WAVES;
-    const int c0 = wave * per, c1 = min(chunks, c0 + per);
+    const int z = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if ((int)blockIdx.z == q.sums) {                     // the loss (256 lanes took 17 us for 9456 parts, one load after the other)
+        if (blockIdx.x > 0) return;
+        const float *p = q.lpart + (long long)z * q.s_lpart;
+        float acc = 0.f;
+        for (int i = threadIdx.x; i < q.n_lpart; i += 4096) {
+            float r[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) r[u] = i + u * 1024 < q.n_lpart ? p[i + u * 1024] : 0.f;
+            acc += (r[0] + r[1]) + (r[2] + r[3]);
+        }
+        acc = row_sum<64>(acc);
+        if (lane == 0) red[wave][0] = acc;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < COLSUM_WAVES; ++w) s += red[w][0];
+            q.loss[z] = s * q.scale;
+        }
+        return;
+    }
+    const int j = blockIdx.x * 64 + lane, ln = blockIdx.z >> 1, beta = blockIdx.z & 1;
+    const float *p = q.part + (long long)z * q.s_part + (long long)blockIdx.z * q.chunks * q.cols;
+    const int per = (q.chunks + COLSUM_WAVES - 1) / COLSUM_WAVES;
+    const int c0 = wave * per, c1 = min(q.chunks, c0 + per);
     float a8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (j < cols) {
+    if (j < q.cols) {
         for (int c = c0; c < c1; c += 8) {               // a short last run is filled up with zeros
             float r[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) r[u] = p[(long long)min(c + u, c1 - 1) * cols + j];
+            for (int u = 0; u < 8; ++u) r[u] = p[(long long)min(c + u, c1 - 1) * q.cols + j];
 #pragma unroll
             for (int u = 0; u < 8; ++u) a8[u] += c + u < c1 ? r[u] : 0.f;
         }
     }
     red[wave][lane] = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
     __syncthreads();
-    if (wave == 0 && j < cols) {
+    if (wave == 0 && j < q.cols) {
         float s = red[0][lane];
 #pragma unroll
-        for (int q = 1; q < COLSUM_WAVES; ++q) s += red[q][lane];
-        out[(long long)z * sOut + j] = s;
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// loss
-// ---------------------------------------------------------------------------------------------
-// (256 lanes took 17 us for 9456 parts, one load after the other)
-__global__ __launch_bounds__(1024) void loss_final_kernel(const float *__restrict__ LPART, long long sLPART,
-                                                          int nparts, float scale, float *__restrict__ loss)
-{
-    __shared__ float red[16];
-    const int z = blockIdx.x;
-    const float *p = LPART + (long long)z * sLPART;
-    float acc = 0.f;
-    for (int i = threadIdx.x; i < nparts; i += 4096) {
-        float r[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) r[u] = i + u * 1024 < nparts ? p[i + u * 1024] : 0.f;
-        acc += (r[0] + r[1]) + (r[2] + r[3]);
-    }
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float s = 0.f;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) s += red[q];
-        loss[z] = s * scale;
+        for (int w = 1; w < COLSUM_WAVES; ++w) s += red[w][lane];
+        q.out[(long long)z * q.s_out + (q.nsub > 1 && (ln & 1) ? q.off[1] : q.off[0]) + (q.nsub > 1 ? ln >> 1 : ln) * q.l_out + beta * q.cols + j] = s;
     }
 }
 
@@ -840,22 +873,30 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     const long long sDU16 = 2 * w.sDU;
     // its backward pass plus the residual path: DX (d loss / d state sub+1) and DU -> DX in place
     // (d loss / d state sub, also in bf16), and the LayerNorm parameter gradients
+    int loss_parts = 0;
     auto ln_bwd = [&](int sub, long long off_gamma) -> hipError_t {
         dim3 grid((unsigned)((wave_rows + 3) / 4), (unsigned)K);
         bf16_t *const dxb_to = w.DXb + (long long)(w.defer && sub > 0 ? sub - 1 : 0) * Md;   // of the sub-block before, if there is one
 #define LN_BWD_ARGS w.X + (long long)sub * Md, w.sX, w.MU + (long long)sub * M, w.RSTD + (long long)sub * M, w.sStat, theta, P, off_gamma, \
-                    w.DX, w.DX, w.sDX, dxb_to, w.sDXb, w.PART, w.sPART, wave_rows, rows_per_wave, M, d
-#define LN_BWD(VPL) do { if (du16 && sub > 0) ln_bwd_kernel<VPL, bf16_t, true><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
-                         else if (du16) ln_bwd_kernel<VPL, bf16_t, false><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
-                         else if (sub > 0) ln_bwd_kernel<VPL, float, true><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); \
-                         else ln_bwd_kernel<VPL, float, false><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); } while (0)
-        const int vpl = (d + 255) / 256;
-        if (vpl <= 1) LN_BWD(1); else if (vpl <= 2) LN_BWD(2); else if (vpl <= 3) LN_BWD(3); else LN_BWD(4);
+                    w.DX, w.DX, w.sDX, dxb_to, w.sDXb, w.PART + (w.defer ? 2LL * sub * wave_rows * d : 0), w.sPART, wave_rows, rows_per_wave, M, d
+#define LN_BWD_R(VPL, LPR, R) do { \
+            if (du16 && sub > 0) ln_bwd_kernel<VPL, LPR, R, bf16_t, true><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
+            else if (du16) ln_bwd_kernel<VPL, LPR, R, bf16_t, false><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
+            else if (sub > 0) ln_bwd_kernel<VPL, LPR, R, float, true><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); \
+            else ln_bwd_kernel<VPL, LPR, R, float, false><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); } while (0)
+#define LN_BWD(VPL, LPR) do { if (rows_per_wave == LN_ROWS_MIN) LN_BWD_R(VPL, LPR, ln_bwd_rows<VPL>(true)); \
+                              else LN_BWD_R(VPL, LPR, ln_bwd_rows<VPL>(false)); } while (0)
+        LN_BY_WIDTH(d, LN_BWD);
 #undef LN_BWD
+#undef LN_BWD_R
 #undef LN_BWD_ARGS
         TRY(hipGetLastError());
-        colsum_final_kernel<<<dim3((unsigned)((d + 63) / 64), (unsigned)K, 2), 64 * COLSUM_WAVES, 0, s>>>(
-            w.PART, w.sPART, g + off_gamma, P, wave_rows, d);
+        // the sums over wavefronts: after each pass, or after the last one for all where the partial rows are kept
+        if (w.defer && sub > 0) return hipSuccess;
+        ColsumArgs q{w.PART, w.sPART, wave_rows, d, g, P, {0, per_attn}, per_block, nsub, w.defer ? 2 * nsub * L : 2,
+                     w.LPART, w.sLPART, loss_parts, 0.5f / ((float)M * (float)d), loss};
+        if (!w.defer || nsub == 1) { q.off[0] = off_gamma; q.nsub = 1; }
+        colsum_final_kernel<<<dim3((unsigned)((d + 63) / 64), (unsigned)K, (unsigned)(q.sums + (sub == 0 ? 1 : 0))), 64 * COLSUM_WAVES, 0, s>>>(q);
         return hipGetLastError();
     };
 
@@ -937,8 +978,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         EpiLoss epi{w.X + (long long)(nsub * L) * Md, w.sX, w.DX, w.sDX, w.DXb + (long long)(w.defer ? nsub * L - 1 : 0) * Md, w.sDXb,
                     w.LPART, w.sLPART, d, 1.0f / sqrtf((float)d), inv};
         TRY(gemm_nt<true>(p, epi, K, s));
-        loss_final_kernel<<<K, 1024, 0, s>>>(w.LPART, w.sLPART, nt_units(p, K), 0.5f * inv, loss);
-        TRY(hipGetLastError());
+        loss_parts = nt_units(p, K);                     // summed up with the last LayerNorm gradients
     }
 
     // The weight gradients of one block's MLP half and of its attention half (w.defer: as the first of all blocks')
