@@ -112,10 +112,14 @@ struct EpiPtr {
     }
 };
 
-template <int TM, int TN, class Epi>
+// `compute` leaves the tile in acc and says whether this wavefront stores it.  A wavefront with one block of 32 x 32 asks for
+// what its epilogue reads ahead of that: with few tiles in flight nothing else hides the latency.
+template <int TM, int TN, class Epi, class Compute>
 __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *stage, int lane,
-                                                 int row0, int col0, int M, int N, int z, int unit, const Epi &epi)
+                                                 int row0, int col0, int M, int N, int z, int unit, const Epi &epi, Compute compute)
 {
+    constexpr bool EARLY = TM * TN == 1;
+    if constexpr (!EARLY) if (!compute()) return;
     constexpr int W = TN * 32, LD = W + 4;             // floats per staged row
     constexpr int VEC = Epi::VEC;
     constexpr int LPR = W / VEC;                       // lanes per row on the way out
@@ -126,6 +130,12 @@ __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *s
     const int r0 = active ? lane / LPR : 0, c = (lane % LPR) * VEC;
     const auto lp = epi.lane(z, row0, col0, r0, c);
     typename Epi::Aux aux[2][ITERS];
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it)
+            if (active && row0 + it * RPI + r0 < M && col0 + c < N) aux[0][it] = epi.pre(lp, it * RPI);
+        if (!compute()) return;
+    }
     auto block = [&](auto full_c, int i) {
         constexpr bool FULL = decltype(full_c)::value;
         auto request = [&](int ib, int buf) {
@@ -137,7 +147,7 @@ __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *s
         // What the functor reads from global memory is requested one block ahead, before the stores of
         // the block in between: vector memory operations complete in order, so a wait for loads issued
         // after a block's stores would also wait for those stores.
-        if (i == 0) request(0, 0);
+        if (i == 0 && !EARLY) request(0, 0);
         if (i + 1 < TM) request(i + 1, (i + 1) & 1);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
@@ -177,9 +187,10 @@ __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *s
 
 // BLKA: A is stored in 32 x 32 blocks (see above); B always is.  In LDS a stage is [BM rows][32 k] of
 // A, then [BN rows][32 k] of B, rows of 64 B, slot s of row r holding piece s ^ ((r >> 2) & 3).
-// WPS: wavefronts per SIMD the registers are budgeted for.
-template <int BM, int BN, int WM, int WN, int WPS, int NS, bool BLKA, class Epi>
-__global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT p, Epi epi, int batch)
+// WPS: wavefronts per SIMD the registers are budgeted for.  KG: groups of wavefronts that share a tile's contraction, each
+// with a ring of its own on a KG-th of it (K a multiple of 32 KG); the results are added in order through LDS.
+template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, class Epi>
+__global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(GemmNT p, Epi epi, int batch)
 {
     constexpr int BK = 32, NW = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NF = TM + TN, MM = TM * TN;
@@ -188,9 +199,10 @@ __global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT 
     static_assert((CA + CB) % NW == 0 && BM % 32 == 0 && BN % 32 == 0, "chunks / waves");
     constexpr int STAGE = (BM + BN) * BK;
     extern __shared__ __attribute__((aligned(1024))) unsigned char gemm_smem[];
-    bf16_t *smem = (bf16_t *)gemm_smem;
 
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = wave_wg / NW, wave = wave_wg % NW;
+    bf16_t *smem = (bf16_t *)gemm_smem + grp * NS * STAGE;
     const int wm = wave / WN, wn = wave % WN;
     // Workgroups go to the 8 XCDs round-robin by linear id (the grid's x extent is a multiple of
     // 8).  Tile order: batch entry (worker), then panels of 4 N-tiles, then M-tile, then N-tile
@@ -209,8 +221,9 @@ __global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT 
     const int bw = min(PANEL, nx - pn * PANEL);
     const int by = tile / bw, bx = pn * PANEL + tile - by * bw;
     const int m0 = by * BM, n0 = bx * BN;
-    const bf16_t *A = p.A + (long long)z * p.sA;
-    const bf16_t *B = p.B + (long long)z * p.sB;
+    const int nk = p.K / (BK * KG);                    // stages of a group
+    const bf16_t *A = p.A + (long long)z * p.sA + (long long)grp * nk * (BLKA ? 1024 : BK);
+    const bf16_t *B = p.B + (long long)z * p.sB + (long long)grp * nk * 1024;
 
     // Per-lane global source of each 1 KiB chunk this wave copies: chunk c is 16 rows, LDS slot
     // (row, s) holds the global piece s ^ ((row >> 2) & 3) of that row.  Blocked operand: half of a
@@ -294,7 +307,7 @@ __global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT 
     // wavefronts of 128 x 128 (a third fewer LDS reads) ran the same loop in 361-393 us on the same
     // boxes, and lost it again in the epilogues, where one wavefront per SIMD has nothing to hide
     // its waits behind (751 against 631 us with the GELU epilogue).
-    const int nk = p.K / BK;
+    auto compute = [&]() -> bool {
 #pragma unroll
     for (int s = 0; s < NS; ++s)
         if (s < nk) {
@@ -345,32 +358,57 @@ __global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT 
     for (; kt + 1 < nk; ++kt) stage(std::false_type{}, std::false_type{}, std::integral_constant<int, 0>{});
     stage(std::true_type{}, std::false_type{}, std::integral_constant<int, 0>{});
 
-    __syncthreads();                                   // every wavefront is done with the ring
-    epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane,
-                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, z, (by * nx + bx) * NW + wave, epi);
+        __syncthreads();                               // every wavefront is done with the rings
+        if constexpr (KG > 1) {
+            constexpr int STAGING = NW * 32 * (TN * 32 + 4);   // floats
+            float *accs = (float *)gemm_smem + STAGING;
+            if (grp > 0) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e)
+                            accs[((((grp - 1) * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane] = acc[i][j][e];
+            }
+            __syncthreads();
+            if (grp > 0) return false;
+#pragma unroll
+            for (int gg = 0; gg < KG - 1; ++gg)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) acc[i][j][e] += accs[(((gg * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane];
+        }
+        return true;
+    };
+    epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane, m0 + wm * TM * 32,
+                             n0 + wn * TN * 32, p.M, p.N, z, (by * nx + bx) * NW + wave, epi, compute);
 }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));   // operand of the LDS transpose read
 
-template <int BM, int BN, int WM, int WN, int WPS, int NS, bool BLKA, class Epi>
+template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, class Epi>
 inline hipError_t launch_gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
     static_assert(256 % BM == 0 && 256 % BN == 0, "blocked operands are allocated in panels of 256 rows");
-    if (p.K % 32 != 0 || p.K < 32 || p.N % 64 != 0) return hipErrorInvalidValue;
+    if (p.K % (32 * KG) != 0 || p.K < 32 || p.N % 64 != 0) return hipErrorInvalidValue;
     const unsigned tiles = (unsigned)((p.N + BN - 1) / BN) * (unsigned)((p.M + BM - 1) / BM) * (unsigned)batch;
     dim3 grid((tiles + 7) / 8 * 8, 1, 1);
-    constexpr size_t ring = (size_t)NS * (BM + BN) * 32 * sizeof(bf16_t);
-    constexpr size_t staging = (size_t)WM * WN * 32 * (BN / WN + 4) * sizeof(float);
+    constexpr size_t ring = (size_t)KG * NS * (BM + BN) * 32 * sizeof(bf16_t);
+    constexpr size_t staging = ((size_t)WM * WN * 32 * (BN / WN + 4) + (size_t)(KG - 1) * BM * BN) * sizeof(float);
     constexpr size_t smem = ring > staging ? ring : staging;
     static_assert(smem <= 160 * 1024, "tile does not fit the 160 KB LDS");
-    auto kern = gemm_nt_bf16_kernel<BM, BN, WM, WN, WPS, NS, BLKA, Epi>;
+    auto kern = gemm_nt_bf16_kernel<BM, BN, WM, WN, KG, WPS, NS, BLKA, Epi>;
     static bool lds_limit_raised = false;     // per instantiation; contexts are not thread-safe
     if (smem > 64 * 1024 && !lds_limit_raised) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         lds_limit_raised = true;
     }
-    kern<<<grid, WM * WN * 64, smem, s>>>(p, epi, batch);
+    kern<<<grid, WM * WN * KG * 64, smem, s>>>(p, epi, batch);
     return hipGetLastError();
 }
 

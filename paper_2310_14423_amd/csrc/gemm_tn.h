@@ -309,7 +309,7 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup
     }
     const EpiF32 epi{out + p.off, p.N};
     epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane,
-                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, 0, 0, epi);
+                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, 0, 0, epi, []() { return true; });
 }
 
 // Whether launch_gemm_tn can take the group (blocked operands: 32-column blocks; the ranges of a split reduction

@@ -708,7 +708,7 @@ struct EpiGeluBwd {              // dh = acc * gelu'(h), H holding gelu'(h) from
     }
 };
 
-// Tile shape of an NT GEMM (BM, BN, wavefronts in M, in N, per SIMD, stages) by the number of tiles and the
+// Tile shape of an NT GEMM (BM, BN, wavefronts in M, in N, groups, per SIMD, stages) by the number of tiles and the
 // length of the contraction, from timing every GEMM of the model with every shape on MI355X (us; batch x tokens x
 // width x hidden, the two numbers a GELU forward GEMM with N = hidden and a bf16-output one with N = width):
 //                              256x256, 1 WG/CU   128x256, 2 WG/CU   128x128, 3 WG/CU   64x64, 4 WG/CU
@@ -723,15 +723,19 @@ struct EpiGeluBwd {              // dh = acc * gelu'(h), H holding gelu'(h) from
 // the epilogue is half the time (426 against 439 us for a plain bf16 output of N = 3072); at K = 3072 the larger
 // tile's smaller copy volume wins once there are enough tiles for several rounds of the chip.  The smaller tiles
 // are for problems that would leave compute units without work: below two rounds of 128 x 256 (or where it would
-// pad N by a fifth or more) 128 x 128, and below 160 of those 64 x 64.
-enum NtShape { NT_256x256, NT_128x256, NT_128x128, NT_64x64 };
+// pad N by a fifth or more) 128 x 128, and below 160 of those (768 where they would pad N by a third or more: 2 x 2228 x 192 x
+// 192 6.5 us, 64 x 64 5.3) 64 x 64.  A contraction of 1024 and more with at most a tile of those per compute unit is shared by
+// two groups of wavefronts: 0.84 of the time (18 problems, 0.76 to 0.89); at 512 to 1023 0.93, not worth another order of
+// summation, below that and with more tiles the same or slower; four groups 0.87 to 1.3.
+enum NtShape { NT_256x256, NT_128x256, NT_128x128, NT_64x64, NT_64x64_2GROUPS };
 static NtShape nt_shape(const GemmNT &p, int batch)
 {
     auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * batch; };
     const bool wide = 5LL * ((p.N + 255) / 256) * 256 < 6LL * p.N;
     if (wide && p.K >= 1024 && tiles(256, 256) >= 1024) return NT_256x256;
     if (wide && tiles(128, 256) >= 1024) return NT_128x256;
-    return tiles(128, 128) >= 160 ? NT_128x128 : NT_64x64;
+    if (tiles(128, 128) >= (p.N <= 192 && p.N % 128 != 0 ? 768 : 160)) return NT_128x128;
+    return p.K >= 1024 && p.K % 64 == 0 && tiles(64, 64) <= 256 ? NT_64x64_2GROUPS : NT_64x64;
 }
 // wavefronts of all tiles of a batch entry
 static int nt_units(const GemmNT &p, int batch)
@@ -749,10 +753,11 @@ template <bool BLKA, class Epi>
 static hipError_t gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
     switch (nt_shape(p, batch)) {
-    case NT_256x256: return launch_gemm_nt<256, 256, 2, 4, 2, 4, BLKA>(p, epi, batch, s);
-    case NT_128x256: return launch_gemm_nt<128, 256, 1, 4, 2, 3, BLKA>(p, epi, batch, s);
-    case NT_128x128: return launch_gemm_nt<128, 128, 2, 2, 3, 3, BLKA>(p, epi, batch, s);
-    default: return launch_gemm_nt<64, 64, 2, 2, 4, 4, BLKA>(p, epi, batch, s);
+    case NT_256x256: return launch_gemm_nt<256, 256, 2, 4, 1, 2, 4, BLKA>(p, epi, batch, s);
+    case NT_128x256: return launch_gemm_nt<128, 256, 1, 4, 1, 2, 3, BLKA>(p, epi, batch, s);
+    case NT_128x128: return launch_gemm_nt<128, 128, 2, 2, 1, 3, 3, BLKA>(p, epi, batch, s);
+    case NT_64x64_2GROUPS: return launch_gemm_nt<64, 64, 2, 2, 2, 4, 4, BLKA>(p, epi, batch, s);
+    default: return launch_gemm_nt<64, 64, 2, 2, 1, 4, 4, BLKA>(p, epi, batch, s);
     }
 }
 #define TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
