@@ -8,10 +8,11 @@
 // The problem is tiny (K*B*d = 131072 inputs at the benchmark size): what counts is the number of
 // launches in the dependent chain (2 to 4 us each) and of memory latencies inside them.  Every
 // inner product needs all of w_k and every gradient entry all residuals, so two kernels per iteration
-// are the least without a barrier across the grid; step 3's kernel therefore also takes the OPT update
+// are the least for a worker that is spread over the grid; step 3's kernel therefore also takes the OPT update
 // of its columns, which it holds for all workers, and in a recorded iteration the averaging and
-// the scheduler's step.  256 iterations of 4 x 1024 features x 32 samples: 2879 us with four
-// kernels per iteration (residuals, gradient, update, averaging).
+// the scheduler's step.  Iterations enqueued together (qsr_run) of a worker that fits one workgroup need no launch between
+// them at all: linreg_run_kernel.  256 iterations of 4 x 1024 features x 32 samples: 2879 us with four
+// kernels per iteration (residuals, gradient, update, averaging), 1900 with two, 646 together.
 #include "opt_elem.h"
 #include "philox.h"
 #include "qsr_internal.h"
@@ -29,6 +30,152 @@ __device__ __forceinline__ float block_sum_256(float v, float *red)
     float s = red[0] + red[1] + red[2] + red[3];
     __syncthreads();
     return s;
+}
+
+// Workers that fit one workgroup of 16 wavefronts (linreg_run_kernel): up to 1024 features, four consecutive ones a lane and
+// so RUN_ROW wavefronts a sample, RUN_GROUPS samples side by side, each group of wavefronts on a run of at most
+// RUN_PER samples.  Their sums are taken in this order whatever kernel computes them, so that iterations give the same bits
+// one by one and together: four columns of a lane in order, the lanes of a wavefront pairwise (lane_sum),
+// the wavefronts of a sample in order; for the gradient the samples of a run in order, then the runs.
+// In the workspace their rows of X are padded to a multiple of 4, the padding zero.
+constexpr int RUN_MAX_D = 1024, RUN_MAX_PER = 8;
+struct RunShape { int row, groups, per, d4; };
+static inline RunShape run_shape(const ModelDims &d)
+{
+    RunShape q;
+    q.row = (int)((d.d_in + 255) / 256);
+    q.groups = 16 / q.row;
+    q.per = (int)((d.B + q.groups - 1) / q.groups);
+    q.d4 = (int)((d.d_in + 3) / 4 * 4);
+    return q;
+}
+bool linreg_can_run(const ModelDims &d)
+{
+    return d.K <= 16 && d.d_in <= RUN_MAX_D && d.B <= 16 * RUN_MAX_PER && run_shape(d).per <= RUN_MAX_PER && linreg_can_fuse(d);
+}
+static inline long long row_stride(const ModelDims &d) { return linreg_can_run(d) ? run_shape(d).d4 : d.d_in; }
+static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Iterations together: X and the observation noise of RUN_SLOTS iterations at a time, drawn ahead
+constexpr int RUN_SLOTS = LINREG_RUN_AHEAD;
+static inline long long slot_worker_floats(const ModelDims &d) { return d.B * run_shape(d).d4 + (d.B + 3) / 4 * 4; }
+// ... and two copies of the parameters
+static inline long long run_floats(const ModelDims &d) { return RUN_SLOTS * d.K * slot_worker_floats(d) + 2LL * d.K * run_shape(d).d4; }
+
+// exchanges inside a wavefront: lane l gets the value of lane l ^ 8, l ^ 7, l ^ 2, l ^ 1
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_xor8(float v) { return dpp<0x128>(v); }     // rotation of a row of 16 by 8
+__device__ __forceinline__ float lane_xor7(float v) { return dpp<0x141>(v); }     // half rows mirrored
+__device__ __forceinline__ float lane_xor2(float v) { return dpp<0x4e>(v); }
+__device__ __forceinline__ float lane_xor1(float v) { return dpp<0xb1>(v); }
+// a: lanes below 32 (an even row of 16) keep a, the others get b's; b: the reverse
+__device__ __forceinline__ void swap32(float &a, float &b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(float &a, float &b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+}
+// the sum over the wavefront, in every lane: pairs l, l ^ 32, then ^ 16, 8, 7, 2, 1
+__device__ __forceinline__ float lane_sum(float v)
+{
+    float o = v;
+    swap32(v, o); v += o;
+    o = v; swap16(v, o); v += o;
+    v += lane_xor8(v); v += lane_xor7(v); v += lane_xor2(v);
+    return v + lane_xor1(v);
+}
+// The same sums of N = 2, 4 or 8 values at once: each exchange halves the values a lane still holds.  The lane ends up with
+// the sum of value lane_value<N>(lane).
+template <int N> __device__ __forceinline__ int lane_value(int lane)
+{
+    int i = (lane >> 5) * (N / 2);
+    if (N >= 4) i += ((lane >> 4) & 1) * (N / 4);
+    if (N >= 8) i += ((lane >> 3) & 1) * (N / 8);
+    return i;
+}
+template <int N> __device__ __forceinline__ float lane_sums(float (&v)[N], int lane)
+{
+    constexpr int H = N / 2;
+#pragma unroll
+    for (int i = 0; i < H; ++i) { swap32(v[i], v[i + H]); v[i] += v[i + H]; }
+    if constexpr (N >= 4) {
+#pragma unroll
+        for (int i = 0; i < H / 2; ++i) { swap16(v[i], v[i + H / 2]); v[i] += v[i + H / 2]; }
+    } else {
+        float o = v[0]; swap16(v[0], o); v[0] += o;
+    }
+    if constexpr (N >= 8) {
+        const bool up = (lane & 8) != 0;
+#pragma unroll
+        for (int i = 0; i < H / 4; ++i) {
+            const float give = up ? v[i] : v[i + H / 4], keep = up ? v[i + H / 4] : v[i];
+            v[i] = keep + lane_xor8(give);
+        }
+    } else v[0] += lane_xor8(v[0]);
+    v[0] += lane_xor7(v[0]);
+    v[0] += lane_xor2(v[0]);
+    return v[0] + lane_xor1(v[0]);
+}
+
+// Steps 1 and 2 for such workers, one workgroup per sample: 256 lanes draw the sample's inputs and own four columns each (d no
+// multiple of 4: a row begins inside a group of the generator, and the draws pass through LDS), wavefront 4 draws the noise.
+__global__ __launch_bounds__(320) void linreg_residual_row_kernel(
+    float *__restrict__ X, const float *__restrict__ theta, const float *__restrict__ wstar, float *__restrict__ r,
+    int B, int d, int d4, float sigma, uint64_t seed, const DevState *__restrict__ st)
+{
+    __shared__ __attribute__((aligned(16))) float row[RUN_MAX_D + 4];
+    __shared__ float red[5];
+    const int k = blockIdx.y, i = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, c = tid * 4;
+    const uint32_t t = (uint32_t)st->t;
+    // (used behind the draws, which hide the latency)
+    float4 w = make_float4(0.f, 0.f, 0.f, 0.f), b = w, z = w;
+    if (wave < 4 && c < d) {
+        const float *wp = theta + (long long)k * d + c, *bp = wstar + c;
+        if (c + 3 < d) {
+            w = ld4u(wp); b = ld4u(bp);
+        } else {
+            w.x = wp[0]; b.x = bp[0];
+            if (c + 1 < d) { w.y = wp[1]; b.y = bp[1]; }
+            if (c + 2 < d) { w.z = wp[2]; b.z = bp[2]; }
+        }
+    }
+    if ((d & 3) == 0) {
+        if (wave < 4 && c < d) z = normal4(seed, STREAM_X, (uint32_t)k, t, (uint32_t)((long long)i * (d >> 2) + tid));
+    } else {
+        const long long f0 = (long long)i * d, q0 = f0 >> 2;
+        const int nq = (int)(((f0 + d + 3) >> 2) - q0);
+        for (int q = tid; q < nq && wave < 4; q += 256) {
+            const int j0 = (int)((q0 + q) * 4 - f0);     // column of the group's first element
+            const float4 z4 = normal4(seed, STREAM_X, (uint32_t)k, t, (uint32_t)(q0 + q));
+            if (j0 >= 0 && j0 < d) row[j0] = z4.x;
+            if (j0 + 1 >= 0 && j0 + 1 < d) row[j0 + 1] = z4.y;
+            if (j0 + 2 >= 0 && j0 + 2 < d) row[j0 + 2] = z4.z;
+            if (j0 + 3 >= 0 && j0 + 3 < d) row[j0 + 3] = z4.w;
+        }
+        if (tid < d4 - d) row[d + tid] = 0.f;
+        __syncthreads();
+        if (wave < 4 && c < d) z = *(const float4 *)(row + c);
+    }
+    if (wave < 4) {
+        if (c < d) *(float4 *)(X + ((long long)k * B + i) * d4 + c) = z;
+        float acc = fmaf(z.x, w.x - b.x, 0.f);
+        acc = fmaf(z.y, w.y - b.y, acc); acc = fmaf(z.z, w.z - b.z, acc); acc = fmaf(z.w, w.w - b.w, acc);
+        acc = lane_sum(acc);
+        if ((tid & 63) == 0) red[wave] = acc;
+    } else if (tid == 256) {
+        const float4 n = normal4(seed, STREAM_NOISE, (uint32_t)k, t, (uint32_t)(i >> 2));
+        red[4] = (i & 3) == 0 ? n.x : (i & 3) == 1 ? n.y : (i & 3) == 2 ? n.z : n.w;
+    }
+    __syncthreads();
+    if (tid == 0) r[(long long)k * B + i] = fmaf(-sigma, red[4], ((red[0] + red[1]) + red[2]) + red[3]);
 }
 
 // One workgroup per sample.  Wavefronts 0-3 draw the sample's inputs (whole groups of the generator,
@@ -104,11 +251,12 @@ __global__ __launch_bounds__(320) void linreg_residual_kernel(
     if (tid == 0) r[(long long)k * B + i] = (red[0] + red[1] + red[2] + red[3]) - sigma * red[4];
 }
 
-// Step 3 with the OPT update, one workgroup per 64 columns of all K workers: K * S wavefronts, each on a
-// worker's columns and every S-th run of samples (S = 16 / K: all loads of the benchmark size's 32
-// samples are in flight at once); the S partial sums are added in order through LDS by the worker's first
-// wavefront, which updates its columns.  average: the launch also averages, if the device's scheduler
-// says that a round ends, with the averaging kernel's arithmetic.  st_next as in the update kernels.
+// Step 3 with the OPT update, one workgroup per 64 columns of KW workers: KW * S wavefronts, the samples of a
+// worker cut into S runs, a wavefront each (all loads of the benchmark size's 32 samples are in flight at once); the partial
+// sums of the runs are added in order through LDS by the worker's first wavefront, which updates its columns.  KW = 1 for
+// workers that linreg_run_kernel takes too, with its S; else all K, S = 16 / K, so that the launch can average as well
+// (average, if the device's scheduler says that a round ends), with the averaging kernel's arithmetic.  st_next as in the
+// update kernels.
 struct LinregStep {
     float *theta, *g, *s0, *s1;          // s1: AdamW
     const StepScalars *sc;
@@ -116,17 +264,18 @@ struct LinregStep {
 };
 template <bool ADAMW>
 __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(
-    const float *__restrict__ X, const float *__restrict__ r, LinregStep p, float *__restrict__ loss, int K, int S,
-    long long B, long long d, const DevState *__restrict__ st, DevState *__restrict__ st_next, int average, SchedParams sp)
+    const float *__restrict__ X, const float *__restrict__ r, LinregStep p, float *__restrict__ loss, int K, int KW, int S,
+    int per, int B, long long d, long long ldx, const DevState *__restrict__ st, DevState *__restrict__ st_next, int average, SchedParams sp)
 {
     __shared__ float part[16][64];
     __shared__ float upd[16][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int k = wave / S, s = wave - k * S;
+    const int kw = wave / S, k = blockIdx.y * KW + kw, s = wave - kw * S;
     const long long j = (long long)blockIdx.x * 64 + lane;
     const bool in = j < d;
     // the last thread of the last workgroup, which has no column of its own where the others are busiest
-    if (st_next != nullptr && blockIdx.x == gridDim.x - 1 && threadIdx.x == blockDim.x - 1) tick_into(st, st_next, sp);
+    if (st_next != nullptr && blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && threadIdx.x == blockDim.x - 1)
+        tick_into(st, st_next, sp);
     const bool sync = average != 0 && st->h + 1 == st->H;
     const StepScalars sc = p.sc[st->t];
     const long long o = (long long)k * d + j;
@@ -135,15 +284,15 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(
         th = p.theta[o]; m = p.s0[o];
         if (ADAMW) v = p.s1[o];
     }
-    const float *Xk = X + (long long)k * B * d + j;
+    const float *Xk = X + (long long)k * B * ldx + j;
     const float *rk = r + (long long)k * B;
     float acc = 0.f;
     if (in) {
-        const long long per = (B + S - 1) / S, i0 = s * per, i1 = min(B, i0 + per);
-        for (long long i = i0; i < i1; i += 8) {         // a short last run is filled up with weight 0
+        const int i0 = min(B, s * per), i1 = min(B, i0 + per);
+        for (int i = i0; i < i1; i += 8) {               // a short last run is filled up with weight 0
             float xv[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) xv[u] = Xk[min(i + u, i1 - 1) * d];
+            for (int u = 0; u < 8; ++u) xv[u] = Xk[min(i + u, i1 - 1) * ldx];
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc = fmaf(i + u < i1 ? rk[i + u] : 0.f, xv[u], acc);
         }
@@ -151,7 +300,7 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(
     part[wave][lane] = acc;
     if (blockIdx.x == 0 && s == 0) {
         float a = 0.f;
-        for (long long i = lane; i < B; i += 64) a = fmaf(rk[i], rk[i], a);
+        for (int i = lane; i < B; i += 64) a = fmaf(rk[i], rk[i], a);
 #pragma unroll
         for (int q = 32; q > 0; q >>= 1) a += __shfl_down(a, q, 64);
         if (lane == 0) loss[k] = 0.5f * a / (float)B;
@@ -181,12 +330,12 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(
 
 __global__ __launch_bounds__(256) void linreg_grad_kernel(
     const float *__restrict__ X, const float *__restrict__ r, float *__restrict__ g,
-    float *__restrict__ loss, long long B, long long d)
+    float *__restrict__ loss, long long B, long long d, long long ldx)
 {
     __shared__ float red[4];
     const int k = blockIdx.y;
     const long long j = (long long)blockIdx.x * 256 + threadIdx.x;
-    const float *Xk = X + (long long)k * B * d;
+    const float *Xk = X + (long long)k * B * ldx;
     const float *rk = r + (long long)k * B;
     const float invB = 1.0f / (float)B;
     if (j < d) {
@@ -197,11 +346,11 @@ __global__ __launch_bounds__(256) void linreg_grad_kernel(
         for (; i + 8 <= B; i += 8) {
             float xv[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) xv[u] = Xk[(i + u) * d + j];
+            for (int u = 0; u < 8; ++u) xv[u] = Xk[(i + u) * ldx + j];
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc = fmaf(rk[i + u], xv[u], acc);
         }
-        for (; i < B; ++i) acc = fmaf(rk[i], Xk[i * d + j], acc);
+        for (; i < B; ++i) acc = fmaf(rk[i], Xk[i * ldx + j], acc);
         g[(long long)k * d + j] = acc * invB;
     }
     if (blockIdx.x == 0) {
@@ -214,20 +363,29 @@ __global__ __launch_bounds__(256) void linreg_grad_kernel(
 
 size_t linreg_workspace_bytes(const ModelDims &d)
 {
-    size_t x = (size_t)d.K * (size_t)d.B * (size_t)d.d_in * sizeof(float);
+    size_t x = (size_t)d.K * (size_t)d.B * (size_t)row_stride(d) * sizeof(float);
     size_t r = (size_t)d.K * (size_t)d.B * sizeof(float);
-    return ((x + 255) & ~(size_t)255) + ((r + 255) & ~(size_t)255);
+    size_t slots = linreg_can_run(d) ? (size_t)run_floats(d) * sizeof(float) : 0;
+    return up256(x) + up256(r) + up256(slots);
 }
 
 static float *linreg_r(const ModelDims &d, void *ws)
 {
-    size_t xb = ((size_t)d.K * d.B * d.d_in * sizeof(float) + 255) & ~(size_t)255;
-    return (float *)((char *)ws + xb);
+    return (float *)((char *)ws + up256((size_t)d.K * d.B * row_stride(d) * sizeof(float)));
+}
+static float *linreg_slots(const ModelDims &d, void *ws)
+{
+    return (float *)((char *)linreg_r(d, ws) + up256((size_t)d.K * d.B * sizeof(float)));
 }
 
 static hipError_t launch_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
                                   const DevState *st, hipStream_t s)
 {
+    if (linreg_can_run(d)) {
+        linreg_residual_row_kernel<<<dim3((unsigned)d.B, (unsigned)d.K), 320, 0, s>>>(
+            (float *)ws, theta, wstar, linreg_r(d, ws), (int)d.B, (int)d.d_in, run_shape(d).d4, d.data_sigma, d.seed, st);
+        return hipGetLastError();
+    }
     // Rows that are no multiple of 4 long: 128-bit accesses where there is enough work to be bound by them, 32-bit ones
     // where latency is all (an iteration, us, 128 / 32 bits: 8 x 184 x 2706723 10755 / 16600, 16 x 348 x 45554 601 / 874,
     // 24 x 341 x 270 42 / 45, 3 x 17 x 1003 8.25 / 8.14, 2 x 54 x 211 7.98 / 7.70).
@@ -250,7 +408,7 @@ hipError_t launch_linreg_grad(const ModelDims &d, const float *theta, float *g, 
     hipError_t e = launch_residual(d, theta, wstar, ws, st, s);
     if (e != hipSuccess) return e;
     linreg_grad_kernel<<<dim3((unsigned)((d.d_in + 255) / 256), (unsigned)d.K), 256, 0, s>>>(
-        (const float *)ws, linreg_r(d, ws), g, loss, d.B, d.d_in);
+        (const float *)ws, linreg_r(d, ws), g, loss, d.B, d.d_in, row_stride(d));
     return hipGetLastError();
 }
 
@@ -279,14 +437,257 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
                                      hipStream_t s)
 {
     if (!linreg_can_fuse(d)) return hipErrorInvalidValue;
-    const int S = 16 / d.K;
+    const bool run = linreg_can_run(d);
+    if (run && average) return hipErrorInvalidValue;
+    const int KW = run ? 1 : d.K, S = run ? run_shape(d).groups : 16 / d.K, per = (int)((d.B + S - 1) / S);
     const LinregStep p{theta, g, s0, s1, sc, c1, c2, eps};
-    const dim3 grid((unsigned)((d.d_in + 63) / 64));
-    const int threads = d.K * S * 64;
-    if (s1) linreg_grad_update_kernel<true><<<grid, threads, 0, s>>>((const float *)ws, linreg_r(d, ws), p, loss, d.K, S,
-                                                                     d.B, d.d_in, st, st_next, average ? 1 : 0, sp);
-    else linreg_grad_update_kernel<false><<<grid, threads, 0, s>>>((const float *)ws, linreg_r(d, ws), p, loss, d.K, S,
-                                                                   d.B, d.d_in, st, st_next, average ? 1 : 0, sp);
+    const dim3 grid((unsigned)((d.d_in + 63) / 64), (unsigned)(d.K / KW));
+    const int threads = KW * S * 64;
+    if (s1) linreg_grad_update_kernel<true><<<grid, threads, 0, s>>>((const float *)ws, linreg_r(d, ws), p, loss, d.K, KW, S, per,
+                                                                     (int)d.B, d.d_in, row_stride(d), st, st_next, average ? 1 : 0, sp);
+    else linreg_grad_update_kernel<false><<<grid, threads, 0, s>>>((const float *)ws, linreg_r(d, ws), p, loss, d.K, KW, S, per,
+                                                                   (int)d.B, d.d_in, row_stride(d), st, st_next, average ? 1 : 0, sp);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------
+// iterations together
+// ---------------------------------------------------------------------------------------------
+// Consecutive iterations of one round in one launch, a workgroup of 16 wavefronts per worker: its parameters and momentum stay
+// in registers, an iteration's inputs too, from the residuals to the gradient, and what has to be summed across wavefronts
+// goes through LDS with two barriers per iteration.  The inputs depend on nothing that the iterations compute: the
+// launch's other workgroups draw those of later iterations into the workspace (slot = iteration mod RUN_SLOTS), so that a worker
+// only reads its own, one iteration ahead, into a second set of registers; these reads (128 KiB an iteration at 32 x 1024, 2000
+// cycles of a compute unit's first-level cache) are spread over the iteration, where a burst of them holds up
+// the arithmetic behind it (2.1 us an iteration, spread 1.5, without them 1.1).
+// Between launches of a call the parameters stay in the workspace, two copies that launches read and write in turn, so that a
+// round's averaging is the next launch's: every worker reads all rows, where the device's scheduler says that the round ended
+// (a launch of its own: 4 us a round).  An iteration at rounds of 8 (us; two kernels an iteration): 4 x 1024 x 32 2.5 (7.3), 16 x
+// 1024 x 32 3.2 (11.3), 8 x 256 x 128 2.8 (14), 1 x 64 x 128 2.3 (7.1), 1 x 1024 x 8 1.6 (6.6).
+struct LinregRun {
+    LinregStep p;                        // p.theta: where the parameters go
+    const float *theta_in;               // where they come from: rows of ld_in (ld_out: p.theta's)
+    long long ld_in, ld_out;
+    const DevState *st_mean;             // != nullptr: averaged on the way in, if this state was the last of its round
+    const float *wstar;
+    float *slots, *loss;
+    int K, B, d, d4, per, n_it, n_draw, draw_off;   // n_draw iterations from the current one plus draw_off on
+    float sigma;
+    uint64_t seed;
+    const DevState *st;
+    DevState *st_next, *st_last;         // after the launch's iterations, and before the last of them
+    SchedParams sp;
+};
+
+// a workgroup's share of the draws: 1024 groups of the generator, of one iteration and worker
+__device__ __forceinline__ void run_draw(const LinregRun &a, int block, int blocks, long long k_floats)
+{
+    const int it = block / (a.K * blocks), k = block / blocks % a.K;
+    const long long t = a.st->t + a.draw_off + it;
+    float *x = a.slots + ((t % RUN_SLOTS) * a.K + k) * k_floats, *eps = x + (long long)a.B * a.d4;
+    const int n = a.B * a.d, groups = (n + 3) / 4;
+    const int q = block % blocks * 1024 + threadIdx.x;
+    if (q < groups) {
+        const float4 z = normal4(a.seed, STREAM_X, (uint32_t)k, (uint32_t)t, (uint32_t)q);
+        if (a.d4 == a.d) { *(float4 *)(x + q * 4) = z; return; }
+        const float zz[4] = {z.x, z.y, z.z, z.w};
+        int i = q * 4 / a.d, j = q * 4 - i * a.d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (q * 4 + e < n) {
+                x[i * a.d4 + j] = zz[e];
+                if (++j == a.d) {
+                    for (; j < a.d4; ++j) x[i * a.d4 + j] = 0.f;
+                    j = 0; ++i;
+                }
+            }
+        }
+    } else if (q - groups < (a.B + 3) / 4) {
+        *(float4 *)(eps + (q - groups) * 4) = normal4(a.seed, STREAM_NOISE, (uint32_t)k, (uint32_t)t, (uint32_t)(q - groups));
+    }
+}
+
+template <int ROW, int PER, bool ADAMW>
+__global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
+{
+    constexpr int GROUPS = 16 / ROW;
+    const long long k_floats = (long long)a.B * a.d4 + (a.B + 3) / 4 * 4;
+    const int workers = a.n_it > 0 ? a.K + 1 : 0;
+    if ((int)blockIdx.x >= workers) {
+        run_draw(a, blockIdx.x - workers, ((a.B * a.d + 3) / 4 + (a.B + 3) / 4 + 1023) / 1024, k_floats);
+        return;
+    }
+    if ((int)blockIdx.x == a.K) {                        // the scheduler's steps
+        if (threadIdx.x > 0) return;
+        DevState nx = *a.st;
+        SchedParams sp = a.sp;
+        sp.expect_sync = 0;                              // only the last iteration may end a round
+        for (int i = 0; i + 1 < a.n_it; ++i) sched_advance(&nx, sp);
+        *a.st_last = nx;
+        sched_advance(&nx, a.sp);
+        *a.st_next = nx;
+        return;
+    }
+    __shared__ __attribute__((aligned(16))) float red[16 * PER][4];     // inner products: [sample][wavefront of its row]
+    __shared__ float4 part[16][64];                                     // gradient: [wavefront][lane], four columns
+    __shared__ float res[16 * PER];                                     // residuals of the last iteration
+    const int k = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s = wave / ROW, cw = wave - s * ROW;
+    const bool busy = s < GROUPS;                        // three wavefronts a row: one of the sixteen is left over
+    const int c = cw * 256 + lane * 4;
+    const bool in = busy && c < a.d;
+    const int i0 = min(s * a.per, a.B), n_i = busy ? min(a.per, a.B - i0) : 0;
+    const long long t0 = a.st->t, o = (long long)k * a.d + c;
+
+    float th[4] = {0.f, 0.f, 0.f, 0.f}, m[4] = {0.f, 0.f, 0.f, 0.f}, v[4] = {0.f, 0.f, 0.f, 0.f}, ws[4] = {0.f, 0.f, 0.f, 0.f};
+    float g[4] = {0.f, 0.f, 0.f, 0.f};
+    const bool mean = a.st_mean != nullptr && a.st_mean->h + 1 == a.st_mean->H;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (in && c + e < a.d) {
+            m[e] = a.p.s0[o + e]; ws[e] = a.wstar[c + e];
+            if (ADAMW) v[e] = a.p.s1[o + e];
+            if (!mean) th[e] = a.theta_in[k * a.ld_in + c + e];
+        }
+    if (mean && in) {                                    // rows of the workspace: whole groups of four
+        float4 row[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) row[q] = *(const float4 *)(a.theta_in + min(q, a.K - 1) * a.ld_in + c);
+        float sum[4] = {0.f, 0.f, 0.f, 0.f}, err[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            if (q < a.K) {
+                add_comp(sum[0], err[0], row[q].x); add_comp(sum[1], err[1], row[q].y);
+                add_comp(sum[2], err[2], row[q].z); add_comp(sum[3], err[3], row[q].w);
+            }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) th[e] = c + e < a.d ? (sum[e] + err[e]) / (float)a.K : 0.f;
+    }
+    if (tid < 16 * PER) {                                // rows of fewer than four wavefronts
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[tid][e] = 0.f;
+    }
+    // an iteration's inputs: PER samples (beyond the run's, or the batch's, some that count for nothing), and the lane's noise
+    struct In { float4 x[PER]; float eps; };
+    const int u_own = lane & (PER - 1);
+    auto slot = [&](int it) { return a.slots + (((t0 + it) % RUN_SLOTS) * a.K + k) * k_floats; };
+    auto load = [&](const float *x, In &q, int u) { q.x[u] = *(const float4 *)(x + min(i0 + u, a.B - 1) * a.d4 + (in ? c : 0)); };
+    auto load_noise = [&](const float *x, In &q) { q.eps = x[a.B * a.d4 + min(i0 + u_own, a.B - 1)]; };
+    auto barrier = [&]() {                               // for LDS accesses only: the loads ahead stay in flight
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // the launch's per-iteration scalars, one iteration a lane
+    const StepScalars mine = a.p.sc[t0 + min(lane, a.n_it - 1)];
+    auto scalar = [&](float x, int it) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), it)); };
+    barrier();
+    auto iterate = [&](int it, In &q, In &ahead) {
+        const bool last = it + 1 == a.n_it;
+        // the loads ahead are made always: behind a branch, every wait for the loads before would be one for these too
+        const float *x = slot(last ? it : it + 1);
+        load_noise(x, ahead);
+        const StepScalars sc = {scalar(mine.x, it), scalar(mine.y, it), scalar(mine.z, it), 0.f};
+        float dw[4], dot[PER];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dw[e] = in ? th[e] - ws[e] : 0.f;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            float acc = fmaf(q.x[u].x, dw[0], 0.f);
+            acc = fmaf(q.x[u].y, dw[1], acc); acc = fmaf(q.x[u].z, dw[2], acc);
+            dot[u] = fmaf(q.x[u].w, dw[3], acc);
+            if (u % 2 == 1) { load(x, ahead, u / 2); __builtin_amdgcn_sched_barrier(0); }
+        }
+        const float sum = lane_sums<PER>(dot, lane);
+        if (busy && (lane & (64 / PER - 1)) == 0) red[s * PER + lane_value<PER>(lane)][cw] = sum;
+        barrier();
+        float r = 0.f;
+        if (u_own < n_i) {
+            const float4 d4 = *(const float4 *)red[s * PER + u_own];
+            r = fmaf(-a.sigma, q.eps, ((d4.x + d4.y) + d4.z) + d4.w);
+        }
+        if (last && cw == 0 && lane < n_i) res[i0 + lane] = r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[e] = 0.f;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const float ru = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), u));
+            g[0] = fmaf(ru, q.x[u].x, g[0]); g[1] = fmaf(ru, q.x[u].y, g[1]);
+            g[2] = fmaf(ru, q.x[u].z, g[2]); g[3] = fmaf(ru, q.x[u].w, g[3]);
+            if (u % 2 == 1) { load(x, ahead, PER / 2 + u / 2); __builtin_amdgcn_sched_barrier(0); }
+        }
+        if (busy) part[wave][lane] = make_float4(g[0], g[1], g[2], g[3]);
+        barrier();
+        if (busy) {
+            float4 p = part[cw][lane];
+            g[0] = p.x; g[1] = p.y; g[2] = p.z; g[3] = p.w;
+#pragma unroll
+            for (int w = 1; w < GROUPS; ++w) {
+                p = part[cw + w * ROW][lane];
+                g[0] += p.x; g[1] += p.y; g[2] += p.z; g[3] += p.w;
+            }
+        }
+        const float invB = 1.0f / (float)a.B;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            g[e] *= invB;
+            if (ADAMW) adamw_elem(th[e], g[e], m[e], v[e], sc.x, sc.y, sc.z, a.p.c1, a.p.c2, a.p.eps);
+            else sgdm_elem(th[e], g[e], m[e], sc.x, a.p.c1, a.p.c2);
+        }
+    };
+    In q0, q1;
+    load_noise(slot(0), q0);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) load(slot(0), q0, u);
+    for (int it = 0; it < a.n_it; it += 2) {
+        iterate(it, q0, q1);
+        if (it + 1 < a.n_it) iterate(it + 1, q1, q0);
+    }
+    if (s == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (in && c + e < a.d) {
+                a.p.theta[k * a.ld_out + c + e] = th[e]; a.p.s0[o + e] = m[e]; a.p.g[o + e] = g[e];
+                if (ADAMW) a.p.s1[o + e] = v[e];
+            }
+    }
+    if (wave == 15) {                                    // written before the last barrier
+        float l = 0.f;
+        for (int i = lane; i < a.B; i += 64) l = fmaf(res[i], res[i], l);
+#pragma unroll
+        for (int h = 32; h > 0; h >>= 1) l += __shfl_down(l, h, 64);
+        if (lane == 0) a.loss[k] = 0.5f * l / (float)a.B;
+    }
+}
+
+hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws,
+                             float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
+                             const SchedParams &sp, hipStream_t s)
+{
+    if (!linreg_can_run(d) || span.n_it < 0 || span.n_draw < 0 || span.n_it > RUN_SLOTS || span.draw_off + span.n_draw > RUN_SLOTS)
+        return hipErrorInvalidValue;
+    const RunShape q = run_shape(d);
+    LinregRun a{};
+    a.slots = linreg_slots(d, ws);
+    float *const kept = a.slots + RUN_SLOTS * d.K * slot_worker_floats(d);
+    auto copy = [&](int i) { return i < 0 ? theta : kept + (long long)i * d.K * q.d4; };
+    a.p = LinregStep{copy(span.out), g, s0, s1, sc, c1, c2, eps};
+    a.theta_in = copy(span.in);
+    a.ld_in = span.in < 0 ? d.d_in : q.d4; a.ld_out = span.out < 0 ? d.d_in : q.d4;
+    a.st_mean = span.in < 0 ? nullptr : span.st_mean;
+    a.wstar = wstar; a.loss = loss;
+    a.K = d.K; a.B = (int)d.B; a.d = (int)d.d_in; a.d4 = q.d4; a.per = q.per;
+    a.n_it = span.n_it; a.n_draw = span.n_draw; a.draw_off = span.draw_off;
+    a.sigma = d.data_sigma; a.seed = d.seed; a.st = span.st; a.st_next = span.st_next; a.st_last = span.st_last; a.sp = sp;
+    const int blocks = (int)((d.B * d.d_in + 3) / 4 + (d.B + 3) / 4 + 1023) / 1024;
+    const unsigned grid = (unsigned)((a.n_it > 0 ? d.K + 1 : 0) + a.n_draw * d.K * blocks);
+    if (grid == 0) return hipSuccess;
+#define RUN(ROW, PER) do { if (s1) linreg_run_kernel<ROW, PER, true><<<grid, 1024, 0, s>>>(a); else linreg_run_kernel<ROW, PER, false><<<grid, 1024, 0, s>>>(a); } while (0)
+#define RUN_ROW(ROW) do { if (q.per <= 2) RUN(ROW, 2); else if (q.per <= 4) RUN(ROW, 4); else RUN(ROW, 8); } while (0)
+    if (q.row == 1) RUN_ROW(1); else if (q.row == 2) RUN_ROW(2); else if (q.row == 3) RUN_ROW(3); else RUN_ROW(4);
+#undef RUN_ROW
+#undef RUN
     return hipGetLastError();
 }
 

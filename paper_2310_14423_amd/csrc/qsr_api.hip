@@ -39,11 +39,12 @@ struct qsr_ctx {
     void *workspace;
     size_t workspace_bytes;
     // library-owned device memory
-    DevState *d_state;       // two copies; `cur` is the one the next kernels read (see ticked)
+    DevState *d_state;       // two copies; `cur` is the one the next kernels read (see ticked); two more for qsr_run's averaging
     int cur;
     bool ticked;             // the update kernel has advanced the scheduler (into the copy that is current now) for
                              // the local step whose qsr_maybe_sync is pending
     bool fuse_linreg;        // least squares: the gradient kernel takes the update of its columns too
+    bool run_linreg;         //   and iterations enqueued together need no launch of their own
     double *d_eta;
     StepScalars *d_scal;
     long long *d_log_t, *d_log_H;
@@ -370,7 +371,7 @@ static int init_impl(qsr_ctx *c, const float *theta0)
         if (rc != QSR_OK) return rc;
     }
 
-    HIP_TRY(hipMalloc((void **)&c->d_state, 2 * sizeof(DevState)));
+    HIP_TRY(hipMalloc((void **)&c->d_state, 4 * sizeof(DevState)));
     HIP_TRY(hipMalloc((void **)&c->d_eta, T * sizeof(double)));
     HIP_TRY(hipMalloc((void **)&c->d_scal, T * sizeof(StepScalars)));
     HIP_TRY(hipMalloc((void **)&c->d_log_t, T * sizeof(long long)));
@@ -452,6 +453,7 @@ extern "C" int qsr_init(const qsr_config *cfg, float *params, float *grads, floa
     c->dims = make_dims(cfg);
     c->fuse_linreg = cfg->model == QSR_MODEL_LINREG && linreg_can_fuse(c->dims) && !cfg->parallel && !cfg->fuse_sync &&
                      !cfg->average_state && cfg->clip_norm <= 0.0;
+    c->run_linreg = c->fuse_linreg && linreg_can_run(c->dims);
     rc = init_impl(c, theta0);
     c->cfg.milestones = nullptr;
     c->cfg.eta_table = nullptr;
@@ -659,6 +661,47 @@ static int run_one_by_one(qsr_ctx *c, long long n)
     return QSR_OK;
 }
 
+// Least squares on workers that fit one workgroup: launches that end where a round does, each drawing inputs ahead for the
+// launches behind it, but none beyond this call.
+static int run_linreg(qsr_ctx *c, long long n)
+{
+    const qsr_config &cfg = c->cfg;
+    const bool sgd = cfg.opt == QSR_OPT_SGDM;
+    long long drawn = 0;                                 // iterations from the current one on
+    int from = -1, last = 0;                             // where the parameters are; the st_last of the next launch
+    auto launch = [&](const LinregSpan &span, const SchedParams &sp) {
+        return launch_linreg_run(c->dims, c->params, c->grads, c->state0, sgd ? nullptr : c->state1, c->model_const,
+                                 c->workspace, c->d_loss, c->d_scal, (float)(sgd ? cfg.momentum : 1.0 - cfg.beta1),
+                                 (float)(sgd ? cfg.weight_decay : 1.0 - cfg.beta2), (float)cfg.eps, span, sp, c->stream);
+    };
+    while (n > 0) {
+        const long long left = c->m_H - c->m_h;
+        long long seg = n < left ? n : left;
+        if (seg > LINREG_RUN_MAX) seg = LINREG_RUN_MAX;
+        SchedParams sp = c->sp;
+        if (drawn == 0) {                                // the first launch's inputs
+            HIP_TRY(launch({0, 0, (int)seg, -1, -1, st_cur(c), nullptr, nullptr, nullptr}, sp));
+            drawn = seg;
+        }
+        if (seg > drawn) seg = drawn;
+        const bool sync = seg == left;
+        sp.expect_sync = sync ? 1 : 0;
+        const long long draws = (n < LINREG_RUN_AHEAD ? n : LINREG_RUN_AHEAD) - drawn;
+        const int to = seg == n ? -1 : from == 0 ? 1 : 0;
+        DevState *const st_last = c->d_state + 2 + last;
+        HIP_TRY(launch({(int)seg, (int)drawn, (int)draws, from, to, st_cur(c), c->d_state + (c->cur ^ 1), st_last,
+                        c->d_state + 2 + (last ^ 1)}, sp));
+        drawn += draws - seg;
+        c->cur ^= 1;
+        for (long long i = 0; i < seg; ++i) mirror_advance(c);
+        c->t_host += seg;
+        n -= seg;
+        from = to; last ^= 1;
+        if (n == 0 && sync) HIP_TRY(launch_average_rows(c->params, cfg.K, cfg.P, st_last, c->stream));
+    }
+    return QSR_OK;
+}
+
 // Every kernel of an iteration takes t, h, H and the averaging decision from device memory, and
 // launch shapes depend on the configuration only: the launches of one iteration are the same for
 // every t, so they are recorded once into a HIP graph (kernel nodes only) and replayed.
@@ -666,7 +709,8 @@ extern "C" int qsr_run(qsr_ctx *c, int64_t n)
 {
     if (!c || n < 0) return QSR_EINVAL;
     if (c->need_sync_call || n > c->cfg.T - c->t_host) return QSR_ESTATE;
-    const long long per = c->graph_iters;
+    if (c->run_linreg && n >= 2 && !c->timing && !caller_records(c->stream)) return run_linreg(c, n);
+    const long long per = c->run_linreg ? 0 : c->graph_iters;
     // the null stream cannot be captured; with timing on every launch gets its own event bracket
     if (c->timing || c->stream == nullptr || per < 1 || n < 1 + 2 * per) return run_one_by_one(c, n);
     if (!c->graph_exec) {

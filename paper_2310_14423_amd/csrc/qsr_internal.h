@@ -181,6 +181,21 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
                                      const DevState *st, DevState *st_next, bool average, const SchedParams &sp,
                                      hipStream_t s);
 
+// Iterations together: n_it of them, of one round, for workers that fit one workgroup each (least squares), and the draws of
+// n_draw iterations from the current one plus draw_off on, which a later call's iterations read.  The same bits as one by one.
+constexpr int LINREG_RUN_AHEAD = 32, LINREG_RUN_MAX = 16;      // draws held, iterations of a launch
+struct LinregSpan {
+    int n_it, draw_off, n_draw;
+    int in, out;                     // parameters read and written: -1 the caller's, 0 and 1 copies in the workspace
+    const DevState *st;
+    DevState *st_next, *st_last;     // the state after the iterations, and before the last of them
+    const DevState *st_mean;         // a copy read is averaged first, if this st_last was the end of a round
+};
+bool linreg_can_run(const ModelDims &d);
+hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws,
+                             float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
+                             const SchedParams &sp, hipStream_t s);
+
 size_t mlp2_workspace_bytes(const ModelDims &d);
 hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, const float *means,
                             void *ws, float *loss, const DevState *st, hipStream_t s);

@@ -1,0 +1,58 @@
+"""GPU: least-squares iterations enqueued together (workers that fit one workgroup each: csrc/grad_linreg.hip) give, bit for
+bit, what the same iterations give one by one, at the sizes where the kernel takes another form: one to four wavefronts a row,
+two to eight samples a wavefront, padded rows, a wavefront left over, sixteen workers; rounds of one iteration, of several
+launches and longer than the draws that are held; a call that ends inside a round and one that goes on from there."""
+import numpy as np
+import pytest
+
+import workloads
+from util import assert_mirror_matches_device, assert_params_close, gpu_ctx, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K,d,B,H,opt", [
+    (2, 256, 32, 1, "sgdm"), (3, 257, 16, 5, "adamw"), (1, 512, 64, 16, "sgdm"), (2, 513, 11, 17, "sgdm"), (2, 768, 40, 33, "adamw"),
+    (2, 769, 32, 40, "sgdm"), (16, 1024, 32, 7, "sgdm"), (5, 1023, 31, 50, "sgdm"), (16, 3, 32, 9, "sgdm"), (1, 1, 1, 2, "sgdm"),
+    (8, 61, 128, 36, "sgdm"), (2, 1022, 9, 16, "adamw")])
+def test_together_and_one_by_one(K, d, B, H, opt):
+    import torch
+    kw = dict(mu=0.9, lam=1e-4) if opt == "sgdm" else dict(beta1=0.9, beta2=0.99, eps=1e-3, lam=0.01)
+    T = 100
+    w = workloads.get("lsq", K=K, d_in=d, B_loc=B, T=T, opt=opt, eta_max=0.1 / (1 + d / B), H_base=H, alpha=0.0, power=0, **kw)
+    ref = gpu_ctx(w)
+    states = []
+    for n in (37, 2, 61):
+        ref.step(n)
+        states.append(([x.clone() for x in (ref.params, ref.grads, ref.state0) + ((ref.state1,) if opt == "adamw" else ())],
+                       ref.read_loss(), ref.get_state()))
+    with torch.cuda.stream(torch.cuda.Stream()):
+        ctx = gpu_ctx(w)
+        for n, (want, loss, state) in zip((37, 2, 61), states):
+            ctx.run(n)
+            assert ctx.get_state() == state
+            got = (ctx.params, ctx.grads, ctx.state0) + ((ctx.state1,) if opt == "adamw" else ())
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
+            assert np.array_equal(ctx.read_loss(), loss)
+        assert_mirror_matches_device(ctx)
+    orc = oracle_run(w)
+    orc.step(T)
+    assert list(ctx.read_sync_log()[0]) == list(orc.sync_log)
+    # AdamW turns differences of an entry's smallest gradients into steps: the schedule above, and the parameters of SGD
+    if opt == "sgdm":
+        assert_params_close(ctx.params.cpu().numpy(), orc.theta, what="params")
+    ctx.close(); ref.close()
+
+
+def test_together_on_the_null_stream_and_after_set_state():
+    """The same without a stream of its own, and entered in the middle of a schedule."""
+    import torch
+    w = workloads.get("lsq", K=4, d_in=300, B_loc=20, T=120)
+    a, b = gpu_ctx(w), gpu_ctx(w)
+    a.step(50); b.step(50)
+    for c in (a, b):
+        c.set_state((20, 3, 0, 6))
+    a.step(60)
+    b.run(60)
+    assert a.get_state() == b.get_state() and torch.equal(a.params, b.params) and torch.equal(a.state0, b.state0)
+    a.close(); b.close()
