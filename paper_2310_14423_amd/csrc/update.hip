@@ -423,6 +423,12 @@ hipError_t launch_update_sgdm_sync(float *theta, const float *g, float *buf, int
 // 16 x 1000000 80 / 93, 8 x 300000 22.3 / 21.6.
 static bool clip_keeps(int K, long long P) { return (long long)K * P <= 16000000; }
 
+// The plain update of buffers that the caches hold together with what produces its gradient and reads its parameters: one
+// iteration with a gradient written before each (us, plain / streaming; three problems in turn): AdamW 8 x 814090 37.5 / 40.4
+// (41.3 / 42.4), 4 x 2000000 44.8 / 47.2 (51.5 / 50.0), 8 x 2000000 85 / 95 (98 / 94), 4 x 8000001 204 / 179; SGD 8 x 814090
+// 29.2 / 29.2 (30.9 / 32.9), 4 x 2000000 36.5 / 35.9 (38.9 / 38.3); four perceptron iterations of 8 x 814090 427 / 437.
+static bool update_keeps(int K, long long P) { return (long long)K * P <= 7000000; }
+
 // row_coef != nullptr: clipped update.  shared_g: all rows of g are the same (rows of whole float4 only:
 // anything else reads its own row, with the same result).
 hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K, long long P,
@@ -445,6 +451,9 @@ hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K
     else if (row_coef != nullptr)
         update_adamw_kernel<true, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, row_coef, rm, none, st_next, spv);
+    else if (update_keeps(K, P))
+        update_adamw_kernel<false, false, false, true><<<update_grid(n4), UPD_THREADS, 0, s>>>(
+            th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, nullptr, rm, none, st_next, spv);
     else
         update_adamw_kernel<false, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, nullptr, rm, none, st_next, spv);
@@ -471,6 +480,9 @@ hipError_t launch_update_sgdm(float *theta, float *g, float *buf, int K, long lo
     else if (row_coef != nullptr)
         update_sgdm_kernel<true, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, b4, n4, n, st, sc, mu, lambda, fs, row_coef, rm, none, st_next, spv);
+    else if (update_keeps(K, P))
+        update_sgdm_kernel<false, false, false, true><<<update_grid(n4), UPD_THREADS, 0, s>>>(
+            th4, g4, b4, n4, n, st, sc, mu, lambda, fs, nullptr, rm, none, st_next, spv);
     else
         update_sgdm_kernel<false, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, b4, n4, n, st, sc, mu, lambda, fs, nullptr, rm, none, st_next, spv);
