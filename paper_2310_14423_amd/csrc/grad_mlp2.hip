@@ -10,8 +10,11 @@
 
 namespace qsr {
 
+// Rows of X, hid, dhid and, with more than 16 classes, logit are padded to a multiple of 4 floats, so that every product reads
+// them with 128-bit accesses whatever the widths (the padding is read and never counts).
 struct Mlp2Ws {
     float *X, *hid, *dhid, *logit;
+    long long ldx, ldh, ldz;
     float *part;           // [K][tiles of 16 rows][17]: column sums of dlogit and the summed loss of a tile
                            // (more than 16 classes: [K][B], the samples' losses)
     int *label;
@@ -25,10 +28,11 @@ static Mlp2Ws carve(const ModelDims &d, void *ws, size_t *total)
     size_t off = 0;
     Mlp2Ws w;
     size_t K = (size_t)d.K, B = (size_t)d.B;
-    w.X = (float *)(p + off);     off += up256(K * B * d.d_in * sizeof(float));
-    w.hid = (float *)(p + off);   off += up256(K * B * d.d_hidden * sizeof(float));
-    w.dhid = (float *)(p + off);  off += up256(K * B * d.d_hidden * sizeof(float));
-    w.logit = (float *)(p + off); off += up256(K * B * d.d_out * sizeof(float));
+    w.ldx = (d.d_in + 3) / 4 * 4; w.ldh = (d.d_hidden + 3) / 4 * 4; w.ldz = d.d_out > 16 ? (d.d_out + 3) / 4 * 4 : d.d_out;
+    w.X = (float *)(p + off);     off += up256(K * B * w.ldx * sizeof(float));
+    w.hid = (float *)(p + off);   off += up256(K * B * w.ldh * sizeof(float));
+    w.dhid = (float *)(p + off);  off += up256(K * B * w.ldh * sizeof(float));
+    w.logit = (float *)(p + off); off += up256(K * B * w.ldz * sizeof(float));
     w.part = (float *)(p + off);  off += up256(K * ((B + 15) / 16) * 17 * sizeof(float));
     w.label = (int *)(p + off);   off += up256(K * B * sizeof(int));
     if (total) *total = off;
@@ -49,13 +53,13 @@ size_t mlp2_workspace_bytes(const ModelDims &d)
 // its own; the thread that holds a row's first element also stores the label for the loss.
 __global__ __launch_bounds__(64) void mlp2_sample_kernel(float *__restrict__ X, int *__restrict__ label,
                                                          const float *__restrict__ means, long long B,
-                                                         long long d_in, uint32_t classes, float sigma,
+                                                         long long d_in, long long ldx, uint32_t classes, float sigma,
                                                          uint64_t seed, const DevState *__restrict__ st)
 {
     const uint32_t t = (uint32_t)st->t;
     const uint32_t k = blockIdx.y;
     const long long n = B * d_in, groups = (n + 3) / 4;
-    float *x = X + (long long)k * n;
+    float *x = X + (long long)k * B * ldx;
     int *lab = label + (long long)k * B;
     auto label_of = [&](long long i) {
         const U4 r = draw4(seed, STREAM_LABEL, k, t, (uint32_t)(i >> 2));
@@ -69,24 +73,23 @@ __global__ __launch_bounds__(64) void mlp2_sample_kernel(float *__restrict__ X, 
         const long long p = q * 4;
         long long i = p / d_in, j = p - i * d_in;
         int c = label_of(i);
-        float v[4];
+        if (ldx == d_in) {                               // four columns of one row
+            const float *mu = means + (long long)c * d_in + j;
+            if (j == 0) lab[i] = c;
+            const float4 o = make_float4(z[0] * sigma + mu[0], z[1] * sigma + mu[1], z[2] * sigma + mu[2], z[3] * sigma + mu[3]);
+            *(float4 *)(x + p) = o;
+            continue;
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if (p + e < n) {
                 if (j == 0) lab[i] = c;
-                v[e] = z[e] * sigma + means[(long long)c * d_in + j];
+                x[i * ldx + j] = z[e] * sigma + means[(long long)c * d_in + j];
                 if (++j == d_in) {
                     j = 0; ++i;
                     if (e < 3 && p + e + 1 < n) c = label_of(i);
                 }
             }
-        }
-        if ((n & 3) == 0) {
-            *(float4 *)(x + p) = make_float4(v[0], v[1], v[2], v[3]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (p + e < n) x[p + e] = v[e];
         }
     }
 }
@@ -96,13 +99,13 @@ __global__ __launch_bounds__(64) void mlp2_sample_kernel(float *__restrict__ X, 
 // 5 x 50 samples of 100 classes).
 __global__ __launch_bounds__(256) void mlp2_softmax_ce_kernel(float *__restrict__ z_dz,
                                                               const int *__restrict__ label,
-                                                              float *__restrict__ sample_loss, long long B, int C)
+                                                              float *__restrict__ sample_loss, long long B, int C, long long ldz)
 {
     const int k = blockIdx.y, lane = threadIdx.x & 63;
     const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= B) return;
     const float invB = 1.0f / (float)B;
-    float *z = z_dz + ((long long)k * B + i) * C;
+    float *z = z_dz + ((long long)k * B + i) * ldz;
     const int y = label[(long long)k * B + i];
     float v[16];                                         // C <= 1024
     float mx = -INFINITY;
@@ -147,15 +150,14 @@ __global__ __launch_bounds__(512) void mlp2_logits_ce_kernel(const float *__rest
                                                              const int *__restrict__ label,
                                                              float *__restrict__ dlogit,
                                                              float *__restrict__ part,
-                                                             int B, int dh, int C)
+                                                             int B, int dh, int ldh, int C)
 {
     __shared__ double dpart[7][4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int r = lane & 15, q = lane >> 4;
     const int k = blockIdx.y, row0 = blockIdx.x * 16;
-    const float *A = hid + (long long)k * B * dh;
+    const float *A = hid + (long long)k * B * ldh;
     const float *W = theta + (long long)k * P + oW2;
-    const bool vec = (dh & 3) == 0 && (((unsigned long long)A) & 15) == 0;
     const int ng = (dh + 15) / 16, ngw = (ng + 7) / 8;
     const int g0 = w * ngw, g1 = min(ng, g0 + ngw);
     const int arow = row0 + r;
@@ -165,8 +167,8 @@ __global__ __launch_bounds__(512) void mlp2_logits_ce_kernel(const float *__rest
     struct Frag { float a[4], b[4]; };
     auto gload = [&](int g, Frag &f) {
         const int kk = g * 16 + 4 * q;
-        const float *ar = A + (long long)arow * dh + kk;
-        if (arow < B && vec && kk + 3 < dh) {
+        const float *ar = A + (long long)arow * ldh + kk;
+        if (arow < B && kk + 3 < dh) {
             const float4 v = *(const float4 *)ar;
             f.a[0] = v.x; f.a[1] = v.y; f.a[2] = v.z; f.a[3] = v.w;
         } else {
@@ -257,7 +259,7 @@ __global__ __launch_bounds__(512) void mlp2_out_bwd_kernel(const float *__restri
                                                            float *__restrict__ dhid, float *__restrict__ g,
                                                            long long P, long long oW2, long long ob1, long long ob2,
                                                            const float *__restrict__ part, int tiles,
-                                                           float *__restrict__ loss, int B, int dh, int C)
+                                                           float *__restrict__ loss, int B, int dh, int ldh, int C)
 {
     __shared__ __attribute__((aligned(16))) float dl_s[128][16];
     __shared__ float red[8][64][17];
@@ -270,8 +272,8 @@ __global__ __launch_bounds__(512) void mlp2_out_bwd_kernel(const float *__restri
         w2[c] = (jin && c < C) ? theta[(long long)k * P + oW2 + (long long)j * C + c] : 0.f;
         gw[c] = 0.f;
     }
-    const float *hk = hid + (long long)k * B * dh;
-    float *dk = dhid + (long long)k * B * dh;
+    const float *hk = hid + (long long)k * B * ldh;
+    float *dk = dhid + (long long)k * B * ldh;
     for (int i0 = 0; i0 < B; i0 += 128) {
         __syncthreads();
         for (int idx = tid; idx < 128 * 16; idx += 512) {
@@ -285,7 +287,7 @@ __global__ __launch_bounds__(512) void mlp2_out_bwd_kernel(const float *__restri
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int i = i0 + ti + 8 * (half * 8 + u);
-                hv[u] = (jin && i < B) ? hk[(long long)i * dh + j] : 0.f;
+                hv[u] = (jin && i < B) ? hk[(long long)i * ldh + j] : 0.f;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(512) void mlp2_out_bwd_kernel(const float *__restri
 #pragma unroll
                 for (int c = 0; c < 16; ++c) d = fmaf(dl[c], w2[c], d);
                 d = hv[u] > 0.f ? d : 0.f;
-                if (jin && i < B) dk[(long long)i * dh + j] = d;
+                if (jin && i < B) dk[(long long)i * ldh + j] = d;
                 cs += d;
 #pragma unroll
                 for (int c = 0; c < 16; ++c) gw[c] = fmaf(hv[u], dl[c], gw[c]);
@@ -341,15 +343,15 @@ hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, co
     {
         long long bx = ((B * di + 3) / 4 + 63) / 64;
         if (bx > 0x7FFFFFFFll) bx = 0x7FFFFFFFll;
-        mlp2_sample_kernel<<<dim3((unsigned)bx, (unsigned)K), 64, 0, s>>>(w.X, w.label, means, B, di, (uint32_t)dz,
+        mlp2_sample_kernel<<<dim3((unsigned)bx, (unsigned)K), 64, 0, s>>>(w.X, w.label, means, B, di, w.ldx, (uint32_t)dz,
                                                                         (float)d.data_sigma, d.seed, st);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // forward
     GemmArgs a{};
-    a.A = w.X; a.lda = di; a.sA = B * di;
+    a.A = w.X; a.lda = w.ldx; a.sA = B * w.ldx;
     a.B = theta + oW1; a.ldb = dh; a.sB = P;
-    a.C = w.hid; a.ldc = dh; a.sC = B * dh;
+    a.C = w.hid; a.ldc = w.ldh; a.sC = B * w.ldh;
     a.M = (int)B; a.N = (int)dh; a.Kd = (int)di; a.bias = theta + ob1; a.sBias = P;
     if ((e = launch_dgemm_nn<EPI_BIAS_RELU>(a, K, s)) != hipSuccess) return e;   // double accumulation
 
@@ -358,46 +360,44 @@ hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, co
         // the loss) in a second
         const int tiles = (int)((B + 15) / 16);
         mlp2_logits_ce_kernel<<<dim3((unsigned)tiles, (unsigned)K), 512, 0, s>>>(
-            w.hid, theta, P, oW2, ob2, w.label, w.logit, w.part, (int)B, (int)dh, (int)dz);
+            w.hid, theta, P, oW2, ob2, w.label, w.logit, w.part, (int)B, (int)dh, (int)w.ldh, (int)dz);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         mlp2_out_bwd_kernel<<<dim3((unsigned)((dh + 63) / 64), (unsigned)K), 512, 0, s>>>(
-            w.hid, w.logit, theta, w.dhid, g, P, oW2, ob1, ob2, w.part, tiles, loss, (int)B, (int)dh, (int)dz);
+            w.hid, w.logit, theta, w.dhid, g, P, oW2, ob1, ob2, w.part, tiles, loss, (int)B, (int)dh, (int)w.ldh, (int)dz);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         a = GemmArgs{};
-        a.A = w.hid; a.lda = dh; a.sA = B * dh;
+        a.A = w.hid; a.lda = w.ldh; a.sA = B * w.ldh;
         a.B = theta + oW2; a.ldb = dz; a.sB = P;
-        a.C = w.logit; a.ldc = dz; a.sC = B * dz;
+        a.C = w.logit; a.ldc = w.ldz; a.sC = B * w.ldz;
         a.M = (int)B; a.N = (int)dz; a.Kd = (int)dh; a.bias = theta + ob2; a.sBias = P;
         if ((e = launch_dgemm_nn<EPI_BIAS>(a, K, s)) != hipSuccess) return e;
-        mlp2_softmax_ce_kernel<<<dim3((unsigned)((B + 3) / 4), (unsigned)K), 256, 0, s>>>(w.logit, w.label, w.part, B, (int)dz);
+        mlp2_softmax_ce_kernel<<<dim3((unsigned)((B + 3) / 4), (unsigned)K), 256, 0, s>>>(w.logit, w.label, w.part, B, (int)dz, w.ldz);
         if ((e = hipGetLastError()) != hipSuccess) return e;
 
         // backward; w.logit now holds d loss / d logits
         a = GemmArgs{};                                        // gW2 = hid^T dlogits
-        a.A = w.hid; a.lda = dh; a.sA = B * dh;
-        a.B = w.logit; a.ldb = dz; a.sB = B * dz;
+        a.A = w.hid; a.lda = w.ldh; a.sA = B * w.ldh;
+        a.B = w.logit; a.ldb = w.ldz; a.sB = B * w.ldz;
         a.C = g + oW2; a.ldc = dz; a.sC = P;
         a.M = (int)dh; a.N = (int)dz; a.Kd = (int)B;
         a.colsum = g + ob2; a.sCol = P;                        // gb2, and the mean cross-entropy
         a.part = w.part; a.n_part = (int)B; a.part_out = loss; a.part_scale = 1.0f / (float)B;
-        if ((e = launch_sgemm<true, false, EPI_NONE>(a, K, s)) != hipSuccess) return e;
-
-        a = GemmArgs{};                                        // dhid = (dlogits W2^T) * [hid > 0]
-        a.A = w.logit; a.lda = dz; a.sA = B * dz;
-        a.B = theta + oW2; a.ldb = dz; a.sB = P;
-        a.C = w.dhid; a.ldc = dh; a.sC = B * dh;
-        a.M = (int)B; a.N = (int)dh; a.Kd = (int)dz; a.aux = w.hid;
-        if ((e = launch_sgemm<false, true, EPI_MASK_POS>(a, K, s)) != hipSuccess) return e;
+        GemmArgs h{};                                          // dhid = (dlogits W2^T) * [hid > 0]
+        h.A = w.logit; h.lda = w.ldz; h.sA = B * w.ldz;
+        h.B = theta + oW2; h.ldb = dz; h.sB = P;               // (b2 lies behind W2's last row)
+        h.C = w.dhid; h.ldc = w.ldh; h.sC = B * w.ldh;
+        h.M = (int)B; h.N = (int)dh; h.Kd = (int)dz; h.aux = w.hid;
+        if ((e = launch_sgemm_pair<EPI_MASK_POS>(a, h, K, s)) != hipSuccess) return e;
     }
 
     a = GemmArgs{};                                        // gW1 = X^T dhid
-    a.A = w.X; a.lda = di; a.sA = B * di;
-    a.B = w.dhid; a.ldb = dh; a.sB = B * dh;
+    a.A = w.X; a.lda = w.ldx; a.sA = B * w.ldx;
+    a.B = w.dhid; a.ldb = w.ldh; a.sB = B * w.ldh;
     a.C = g + oW1; a.ldc = dh; a.sC = P;
     a.M = (int)di; a.N = (int)dh; a.Kd = (int)B;
     if (dz > 16) { a.colsum = g + ob1; a.sCol = P; }       // gb1 (else the output layer's backward kernel has done it)
-    return launch_sgemm<true, false, EPI_NONE>(a, K, s);
+    return launch_sgemm_tn(a, K, s);
 }
 
 }  // namespace qsr

@@ -4,8 +4,7 @@
 // block on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation, two
 // k per instruction), global loads three slabs ahead in registers.  A long contraction is cut in
 // two halves that two such groups of four wavefronts in one workgroup run side by side (KSPLIT =
-// 2; the halves are added through LDS at the end).  Every global access is bounds-checked, so
-// any M, N, Kd is accepted.  Fixed order: deterministic.
+// 2; the halves are added through LDS at the end).  Any M, N, Kd is accepted.  Fixed order: deterministic.
 // dgemm_nn_kernel: fp32 operands (row-major, not transposed) multiplied and accumulated in double
 // precision on the fp64 matrix cores (v_mfma_f64_16x16x4_f64): products of fp32 values are exact in
 // double, so the result is the exact sum rounded once.  Used for the hidden layer's
@@ -13,6 +12,8 @@
 // orders of magnitude once the logits have grown into the hundreds.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include "qsr_internal.h"
 
 namespace qsr {
 
@@ -36,22 +37,28 @@ struct GemmArgs {
 
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
-template <bool TA, bool TB, int EPI, int KSPLIT, bool VEC>
-__global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
+// Every row of an operand that is read along its rows (A transposed, B as it is) starts at 16 bytes and may be read to the next
+// multiple of 4 elements: one 128-bit load of each per thread and slab.  The other form (A as it is, B transposed: both read
+// along k, four elements a thread) takes B's rows at any address, and reads up to three elements beyond their end.  No
+// load is behind a test of its own (rows beyond the matrix are read as the last one, k beyond Kd cleared in registers): as a
+// branch around each load and a wait behind it, 5 x 50 x 500 x 100 took 14.4 us.
+// Workgroup (bx, by, bz) of 256 KSPLIT threads.
+struct SgemmLds { float A[16][96], B[16][96]; };
+template <bool TA, bool TB, int EPI, int KSPLIT>
+__device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, int bz_, SgemmLds *lds)
 {
-    constexpr int TM = 64, TN = 64, TK = 16, PAD = 32;   // rows k and k+1 of a slab 32 banks apart
-    __shared__ __attribute__((aligned(16))) float As_all[KSPLIT][TK][TM + PAD];
-    __shared__ __attribute__((aligned(16))) float Bs_all[KSPLIT][TK][TN + PAD];
+    static_assert(TA != TB, "weight gradients (A transposed) and data gradients (B transposed)");
+    constexpr int TM = 64, TN = 64, TK = 16;             // LDS rows of 96: rows k and k+1 of a slab 32 banks apart
     // The workgroup is KSPLIT groups of 256 threads; group grp contracts over its own run of
     // slabs with its own LDS slabs.  With one workgroup of four wavefronts per compute unit (the
     // batch is 128 rows) every slab's load -> LDS -> barrier -> MFMA chain ran unhidden; a second
     // group per SIMD fills part of those gaps (hidden layer forward, 8 x 128 x 784 x 1024: 46 -> 37 us).
     const int grp = threadIdx.x >> 8, tid = threadIdx.x & 255;
-    float (*As)[TM + PAD] = As_all[grp];
-    float (*Bs)[TN + PAD] = Bs_all[grp];
+    float (*As)[96] = lds[grp].A;
+    float (*Bs)[96] = lds[grp].B;
     const int lane = tid & 63, wm = tid >> 7, wn = (tid >> 6) & 1;   // wavefront (wm, wn) owns a 32x32 block
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-    const long long bz = blockIdx.z;
+    const int m0 = by * TM, n0 = bx * TN;
+    const long long bz = bz_;
     const float *A = a.A + bz * a.sA;
     const float *B = a.B + bz * a.sB;
     typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -70,58 +77,44 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
     constexpr int PF = 3;
     constexpr int R = TK / 4;                       // elements of each operand per thread and slab
     float ra[PF][R], rb[PF][R];
-    // VEC (A transposed, B as it is): both run along their rows, one 128-bit load of each per thread and slab
-    const int vk = tid >> 4, vc = (tid & 15) * 4;
+    // A transposed, B as it is: row k of a slab and four columns.  Else: row of the tile and four k.
+    const int vk = TA ? tid >> 4 : (tid & 3) * 4, vc = TA ? (tid & 15) * 4 : tid >> 2;
+    const float *pa = TA ? A + min(m0 + vc, (a.M - 1) / 4 * 4) : A + (long long)min(m0 + vc, a.M - 1) * a.lda;
+    const float *pb = TA ? B + min(n0 + vc, (a.N - 1) / 4 * 4) : B + (long long)min(n0 + vc, a.N - 1) * a.ldb;
     auto gload = [&](int k0, float (&xa)[R], float (&xb)[R]) {
-        if (VEC) {
-            float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
-            const int gk = k0 + vk;
-            if (gk < a.Kd && m0 + vc < a.M) va = *(const float4 *)(A + (long long)gk * a.lda + m0 + vc);
-            if (gk < a.Kd && n0 + vc < a.N) vb = *(const float4 *)(B + (long long)gk * a.ldb + n0 + vc);
-            xa[0] = va.x; xa[1] = va.y; xa[2] = va.z; xa[3] = va.w;
-            xb[0] = vb.x; xb[1] = vb.y; xb[2] = vb.z; xb[3] = vb.w;
-            return;
+        const int gk = k0 + vk;
+        float4 va, vb;
+        if (TA) {
+            const int k = min(gk, a.Kd - 1);
+            va = *(const float4 *)(pa + (long long)k * a.lda);
+            vb = *(const float4 *)(pb + (long long)k * a.ldb);
+            if (gk >= a.Kd) va = vb = make_float4(0.f, 0.f, 0.f, 0.f);
+        } else {
+            const int k = min(gk, (a.Kd - 1) / 4 * 4);
+            va = *(const float4 *)(pa + k);
+            vb = ld4u(pb + k);
+            if (gk >= a.Kd) { va.x = 0.f; vb.x = 0.f; }
+            if (gk + 1 >= a.Kd) { va.y = 0.f; vb.y = 0.f; }
+            if (gk + 2 >= a.Kd) { va.z = 0.f; vb.z = 0.f; }
+            if (gk + 3 >= a.Kd) { va.w = 0.f; vb.w = 0.f; }
         }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            int kk, m;
-            if (TA) { m = tid & 63; kk = (tid >> 6) + 4 * r; }
-            else    { kk = tid % TK; m = tid / TK + (256 / TK) * r; }
-            int gm = m0 + m, gk = k0 + kk;
-            float v = 0.f;
-            if (gm < a.M && gk < a.Kd) v = TA ? A[(long long)gk * a.lda + gm] : A[(long long)gm * a.lda + gk];
-            xa[r] = v;
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            int kk, n;
-            if (TB) { kk = tid % TK; n = tid / TK + (256 / TK) * r; }
-            else    { n = tid & 63; kk = (tid >> 6) + 4 * r; }
-            int gn = n0 + n, gk = k0 + kk;
-            float v = 0.f;
-            if (gn < a.N && gk < a.Kd) v = TB ? B[(long long)gn * a.ldb + gk] : B[(long long)gk * a.ldb + gn];
-            xb[r] = v;
-        }
+        xa[0] = va.x; xa[1] = va.y; xa[2] = va.z; xa[3] = va.w;
+        xb[0] = vb.x; xb[1] = vb.y; xb[2] = vb.z; xb[3] = vb.w;
     };
     auto sstore = [&](const float (&xa)[R], const float (&xb)[R]) {
-        if (VEC) {
+        if (TA) {
             *(float4 *)&As[vk][vc] = make_float4(xa[0], xa[1], xa[2], xa[3]);
             *(float4 *)&Bs[vk][vc] = make_float4(xb[0], xb[1], xb[2], xb[3]);
-            return;
-        }
+        } else {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (TA) As[(tid >> 6) + 4 * r][tid & 63] = xa[r];
-            else    As[tid % TK][tid / TK + (256 / TK) * r] = xa[r];
-            if (TB) Bs[tid % TK][tid / TK + (256 / TK) * r] = xb[r];
-            else    Bs[(tid >> 6) + 4 * r][tid & 63] = xb[r];
+            for (int r = 0; r < R; ++r) { As[vk + r][vc] = xa[r]; Bs[vk + r][vc] = xb[r]; }
         }
     };
     // every group runs the same number of slabs (the barriers are the workgroup's); slabs past
     // Kd load zeros
     const int nslab = ((a.Kd + TK - 1) / TK + KSPLIT - 1) / KSPLIT;
     const int kbase = grp * nslab * TK;
-    const bool col_wg = TA && !TB && a.colsum != nullptr && blockIdx.y == 0;   // the workgroups of the first rows
+    const bool col_wg = TA && !TB && a.colsum != nullptr && by == 0;   // the workgroups of the first rows
     float cs = 0.f;
 #pragma unroll
     for (int u = 0; u < PF; ++u)
@@ -154,12 +147,12 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
         if (tid < 64) As[0][tid] = cs;                // the slabs are done with
         __syncthreads();
         if (grp == 0 && tid < 64 && n0 + tid < a.N) {
-            float v = As_all[0][0][tid];
+            float v = lds[0].A[0][tid];
 #pragma unroll
-            for (int g = 1; g < KSPLIT; ++g) v += As_all[g][0][tid];
+            for (int g = 1; g < KSPLIT; ++g) v += lds[g].A[0][tid];
             a.colsum[bz * a.sCol + n0 + tid] = v;
         }
-        if (a.part != nullptr && blockIdx.x == 0 && threadIdx.x < 64) {
+        if (a.part != nullptr && bx == 0 && threadIdx.x < 64) {
             float v = 0.f;
             for (int i = lane; i < a.n_part; i += 64) v += a.part[bz * a.n_part + i];
 #pragma unroll
@@ -196,24 +189,53 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
     }
 }
 
-template <bool TA, bool TB, int EPI>
-inline hipError_t launch_sgemm(const GemmArgs &a, int batch, hipStream_t s)
+template <bool TA, bool TB, int EPI, int KSPLIT>
+__global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
 {
+    __shared__ __attribute__((aligned(16))) SgemmLds lds[KSPLIT];
+    sgemm_tile<TA, TB, EPI, KSPLIT>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
+}
+// A weight gradient and a data gradient that do not depend on each other, in one launch: workgroups below `first` of
+// the grid's x extent take the weight gradient's tiles, the others the data gradient's.
+template <int EPI, int KSPLIT>
+__global__ __launch_bounds__(256 * KSPLIT) void sgemm_pair_kernel(GemmArgs w, GemmArgs d, int first, int nxw, int nxd)
+{
+    __shared__ __attribute__((aligned(16))) SgemmLds lds[KSPLIT];
+    int b = blockIdx.x;
+    if (b < first) { sgemm_tile<true, false, EPI_NONE, KSPLIT>(w, b % nxw, b / nxw, blockIdx.z, lds); return; }
+    b -= first;
+    sgemm_tile<false, true, EPI, KSPLIT>(d, b % nxd, b / nxd, blockIdx.z, lds);
+}
+
+// two groups per workgroup for a long contraction, and for a shorter one that would leave compute units idle
+static inline bool sgemm_two(int Kd, long long workgroups) { return Kd >= 256 || (Kd >= 64 && workgroups < 256); }
+static inline bool sgemm_rows_ok(const float *p, long long ld, long long s, int cols)
+{
+    return ((ld | s) & 3) == 0 && ld >= (cols + 3) / 4 * 4 && ((unsigned long long)p & 15) == 0;
+}
+
+// C = A^T B
+inline hipError_t launch_sgemm_tn(const GemmArgs &a, int batch, hipStream_t s)
+{
+    if (!sgemm_rows_ok(a.A, a.lda, a.sA, a.M) || !sgemm_rows_ok(a.B, a.ldb, a.sB, a.N)) return hipErrorInvalidValue;
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 63) / 64), (unsigned)batch);
-    // two groups per workgroup for a long contraction, and for a shorter one that would leave compute units idle
-    const long long wgs = (long long)grid.x * grid.y * grid.z;
-    const bool two = a.Kd >= 256 || (a.Kd >= 64 && wgs < 256);
-    // 128-bit loads where rows and bases are 16-byte aligned in every batch entry.  Kernels of their own: with the choice
-    // inside, the 32-bit loads of 6 x 681 x 862 x 424 took 76 us for 56
-    if constexpr (TA && !TB) {
-        if (((a.lda | a.ldb | a.M | a.N | a.sA | a.sB) & 3) == 0 && ((((unsigned long long)a.A) | ((unsigned long long)a.B)) & 15) == 0) {
-            if (two) sgemm_kernel<TA, TB, EPI, 2, true><<<grid, 512, 0, s>>>(a);
-            else sgemm_kernel<TA, TB, EPI, 1, true><<<grid, 256, 0, s>>>(a);
-            return hipGetLastError();
-        }
-    }
-    if (two) sgemm_kernel<TA, TB, EPI, 2, false><<<grid, 512, 0, s>>>(a);
-    else sgemm_kernel<TA, TB, EPI, 1, false><<<grid, 256, 0, s>>>(a);
+    if (sgemm_two(a.Kd, (long long)grid.x * grid.y * grid.z)) sgemm_kernel<true, false, EPI_NONE, 2><<<grid, 512, 0, s>>>(a);
+    else sgemm_kernel<true, false, EPI_NONE, 1><<<grid, 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+// w: C = A^T B; d: C = epilogue(A B^T), the rows of its B followed by at least three more floats
+template <int EPI>
+inline hipError_t launch_sgemm_pair(const GemmArgs &w, const GemmArgs &d, int batch, hipStream_t s)
+{
+    if (!sgemm_rows_ok(w.A, w.lda, w.sA, w.M) || !sgemm_rows_ok(w.B, w.ldb, w.sB, w.N) || !sgemm_rows_ok(d.A, d.lda, d.sA, d.Kd))
+        return hipErrorInvalidValue;
+    const int nxw = (w.N + 63) / 64, nxd = (d.N + 63) / 64;
+    const long long first = (long long)nxw * ((w.M + 63) / 64), all = first + (long long)nxd * ((d.M + 63) / 64);
+    if (all > 0x7FFFFFll) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)all, 1, (unsigned)batch);
+    if (sgemm_two(w.Kd > d.Kd ? w.Kd : d.Kd, all * batch)) sgemm_pair_kernel<EPI, 2><<<grid, 512, 0, s>>>(w, d, (int)first, nxw, nxd);
+    else sgemm_pair_kernel<EPI, 1><<<grid, 256, 0, s>>>(w, d, (int)first, nxw, nxd);
     return hipGetLastError();
 }
 
@@ -390,7 +412,7 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_lds_kernel(GemmArgs
         const unsigned dst = __builtin_amdgcn_readfirstlane(lds_ring + d_slot * (STAGE * 4));
         if (d_k + 16 > a.Kd) {                               // k is clamped, and cleared once it is in registers
 #pragma unroll
-            for (int c = 0; c < 2; ++c) srcA[c] -= max(d_k + kA[c] - (a.Kd - 4), 0);
+            for (int c = 0; c < 2; ++c) srcA[c] -= max(d_k + kA[c] - (a.Kd - 1) / 4 * 4, 0);
 #pragma unroll
             for (int c = 0; c < CB; ++c) srcB[c] -= (long long)max(d_k + kB[c] - (a.Kd - 1), 0) * a.ldb;
         }
@@ -537,8 +559,8 @@ inline hipError_t launch_dgemm_nn(const GemmArgs &a, int batch, hipStream_t s)
 {
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 63) / 64), (unsigned)batch);
     const bool few = (long long)grid.x * grid.y * grid.z < 200;
-    // 128-bit copies of A: 16-byte rows in every batch entry; of B as well, or 32-bit ones
-    const bool ax4 = ((a.lda | a.sA | a.Kd) & 3) == 0 && (((unsigned long long)a.A) & 15) == 0;
+    // 128-bit copies of A: 16-byte rows in every batch entry, readable to a multiple of 4; of B as well, or 32-bit ones
+    const bool ax4 = sgemm_rows_ok(a.A, a.lda, a.sA, a.Kd);
     const bool bx4 = ((a.ldb | a.sB | a.N) & 3) == 0 && (((unsigned long long)a.B) & 15) == 0;
     if (ax4 && a.Kd >= 64) {
         // Groups per workgroup: several only where the tiles leave compute units idle (us, one / two / four groups):
