@@ -260,7 +260,18 @@ __device__ __forceinline__ void ln_row(const float4 (&xv)[VPL], const float *gam
     if (lane == 0) { *mu_out = mean; *rstd_out = rstd; }
 }
 
-template <int VPL, int LPR>
+// The residual stream and its gradient are streamed where they are beyond the caches, so that these keep the bf16 arrays that the
+// products read: 8 x 12608 rows of 768 with attention, backward pass 253 -> 233 us (6.0 TB/s), 12 blocks 74.2 -> 72.5 ms of
+// kernels (72.9 without the forward pass's loads).
+static bool ln_stream(long long K, long long M, long long d) { return K * M * d >= 16000000; }
+template <bool NT> __device__ __forceinline__ float4 load4f(const float *p) { return NT ? ld_nt4((const float4 *)p) : *(const float4 *)p; }
+template <bool NT> __device__ __forceinline__ float4 load4f(const bf16_t *p)
+{
+    const bf16x4 v = NT ? __builtin_nontemporal_load((const bf16x4 *)p) : *(const bf16x4 *)p;
+    return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+}
+
+template <int VPL, int LPR, bool NT>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ X, long long sX,
                                                      const float *__restrict__ theta, long long sTh,
                                                      long long off_gamma, bf16_t *__restrict__ U,
@@ -275,7 +286,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ X
 #pragma unroll
     for (int c = 0; c < VPL; ++c) {
         const int j = (lane + c * LPR) * 4;
-        xv[c] = j < d ? *(const float4 *)(x + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+        xv[c] = j < d ? load4f<NT>(x + j) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     ln_row<VPL, LPR>(xv, theta + (long long)z * sTh + off_gamma, U + (long long)z * sU, MU + (long long)z * sStat + row,
                      RSTD + (long long)z * sStat + row, row, d);
@@ -320,13 +331,6 @@ __global__ __launch_bounds__(256) void sample_ln_kernel(float *__restrict__ X, l
 #define LN_BY_WIDTH(d, F) do { if ((d) <= 64) F(1, 16); else if ((d) <= 128) F(1, 32); else if ((d) <= 256) F(1, 64); \
                                else if ((d) <= 512) F(2, 64); else if ((d) <= 768) F(3, 64); else F(4, 64); } while (0)
 
-template <bool NT> __device__ __forceinline__ float4 load4f(const float *p) { return NT ? ld_nt4((const float4 *)p) : *(const float4 *)p; }
-template <bool NT> __device__ __forceinline__ float4 load4f(const bf16_t *p)
-{
-    const bf16x4 v = NT ? __builtin_nontemporal_load((const bf16x4 *)p) : *(const bf16x4 *)p;
-    return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
-}
-
 // Backward of LayerNorm plus the residual path, one wavefront per rows_per_wave token rows,
 // VPL float4 per lane:
 //   dn = du*gamma; dx_out = dx_in + rstd*(dn - mean(dn) - xhat*mean(dn*xhat))
@@ -334,8 +338,7 @@ template <bool NT> __device__ __forceinline__ float4 load4f(const bf16_t *p)
 // that, so the update of dx is one stream of addresses instead of two.
 // and per-wavefront partial sums of dgamma = sum_m du*xhat, dbeta = sum_m du (reduced by
 // colsum_final_kernel).  TODX: the first sub-block's input is data, whose gradient nobody reads: only the sums then.
-// NT: DU and X, read here for the last time, with streaming loads (8 x 12608 rows of 768: 253 us without, 229 = 6.1 TB/s with
-// them, 233 with all fp32 arrays streamed); not where everything fits the caches.
+// NT: all but the bf16 gradient, which the next products read, with streaming accesses (ln_stream).
 template <int VPL, int LPR, int R, bool NT, typename TDU, bool TODX>
 __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU, long long sDU,
                                                      const float *__restrict__ X, long long sX,
@@ -383,7 +386,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU,
                 if (j < d) {
                     duv[u][c] = load4f<NT>(du_z + o + j);    // row-major in either type: no GEMM reads it
                     xv[u][c] = load4f<NT>(x_z + o + j);
-                    if (TODX) di[u][c] = *(const float4 *)(di_z + o + j);
+                    if (TODX) di[u][c] = load4f<NT>(di_z + o + j);
                 }
             }
         }
@@ -426,7 +429,8 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU,
                     v.y = di[u][c].y + rstd[u] * (duv[u][c].y - m1 - xv[u][c].y * m2);
                     v.z = di[u][c].z + rstd[u] * (duv[u][c].z - m1 - xv[u][c].z * m2);
                     v.w = di[u][c].w + rstd[u] * (duv[u][c].w - m1 - xv[u][c].w * m2);
-                    *(float4 *)(DXout + (long long)z * sDX + o + j) = v;
+                    if (NT) st_nt4((float4 *)(DXout + (long long)z * sDX + o + j), v);
+                    else *(float4 *)(DXout + (long long)z * sDX + o + j) = v;
                     bf16x4 b = {(bf16_t)v.x, (bf16_t)v.y, (bf16_t)v.z, (bf16_t)v.w};
                     *(bf16x4 *)(DXb + (long long)z * sDXb + o + j) = b;
                 }
@@ -862,12 +866,15 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         att.c2 = 1.4426950408889634f * att.scale;
     }
 
+    const bool stream = ln_stream(K, M, d);
     // LayerNorm of residual state number `sub` with the parameters at off_gamma
     auto ln_fwd = [&](int sub, long long off_gamma) -> hipError_t {
-#define LN_FWD(VPL, LPR) ln_fwd_kernel<VPL, LPR><<<dim3((unsigned)((M + 256 / LPR - 1) / (256 / LPR)), (unsigned)K), 256, 0, s>>>( \
+#define LN_FWD_NT(VPL, LPR, NT) ln_fwd_kernel<VPL, LPR, NT><<<dim3((unsigned)((M + 256 / LPR - 1) / (256 / LPR)), (unsigned)K), 256, 0, s>>>( \
                         w.X + (long long)sub * Md, w.sX, theta, P, off_gamma, \
                         w.U + (long long)sub * MdB, w.sU, w.MU + (long long)sub * M, w.RSTD + (long long)sub * M, w.sStat, M, d)
+#define LN_FWD(VPL, LPR) do { if (stream) LN_FWD_NT(VPL, LPR, true); else LN_FWD_NT(VPL, LPR, false); } while (0)
         LN_BY_WIDTH(d, LN_FWD);
+#undef LN_FWD_NT
 #undef LN_FWD
         return hipGetLastError();
     };
@@ -894,6 +901,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
             else if (sub > 0) ln_bwd_kernel<VPL, LPR, R, NT, float, true><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); \
             else ln_bwd_kernel<VPL, LPR, R, NT, float, false><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); } while (0)
 #define LN_BWD(VPL, LPR) do { if (rows_per_wave == LN_ROWS_MIN) LN_BWD_R(VPL, LPR, ln_bwd_rows<VPL>(true), false); \
+                              else if (!stream) LN_BWD_R(VPL, LPR, ln_bwd_rows<VPL>(false), false); \
                               else LN_BWD_R(VPL, LPR, ln_bwd_rows<VPL>(false), true); } while (0)
         LN_BY_WIDTH(d, LN_BWD);
 #undef LN_BWD
