@@ -27,6 +27,21 @@ constexpr int AVG_KU = 16;
 // LDS-staged tile: W wavefronts, RUN x 64 float4 columns (RUN KiB contiguous per row and wavefront).
 // ALIGNED (here and below): P is known to be a multiple of 4.  With the test of P's remainder around every access
 // 32 x 2250000 took 127 us for 120, 32 x 3125000 176 for 169.
+// Which part of the columns a workgroup takes.  Rows of other lengths than multiples of 4 start anywhere in a 128-byte line, so
+// that neighbouring parts share a line of every row; workgroups go to the 8 XCDs round-robin by their id, and in order each of
+// those lines would be written half by one XCD's L2 and half by another's.  Where rows are not aligned each XCD takes 64
+// parts in a row instead (the rest of the grid goes in order).  us, in order / 16 / 64 / 256 parts: 8 x 3000001 33.3 / 30.4 / 31.0 /
+// 30.5 (buffers in turn 36.1 / 32.4 / 32.4 / 32.7), 8 x 814090 10.8 / 9.9 / 9.6 / 10.5, 17 x 20000001 583 / 532 / 530 / 530,
+// 12 x 16666665 327 / 310 / 307 / 309, 24 x 6000002 240.6 / 235.0 / 235.6 / 237, 48 x 4166663 370 / 347 / 344 / 338, 64 x 2000001 228 /
+// 217 / 213 / 219, 100 x 2000002 395 / 380 / 375 / 378.  Aligned rows share nothing and stay in order: 16 x 60000000 1352 / 1462 /
+// 1422 / 1459, 32 x 9000004 469 / 482 / 490 / 495.
+__device__ __forceinline__ long long column_part(long long P)
+{
+    constexpr unsigned EACH = 64, TURN = 8 * EACH;
+    const unsigned b = blockIdx.x, r = b % TURN, first = b - r;
+    return (P & 3) != 0 && first + TURN <= gridDim.x ? first + r % 8 * EACH + r / 8 : b;
+}
+
 template <int KMAX, int W, int RUN, bool ALIGNED>
 __device__ __forceinline__ void average_tile_body(float *__restrict__ buf, int K, long long P, float4 *avg_tile)
 {
@@ -36,7 +51,7 @@ __device__ __forceinline__ void average_tile_body(float *__restrict__ buf, int K
     constexpr int TC = RUN * 64;
     constexpr int RPW = (KMAX + W - 1) / W;          // rows per wavefront
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const long long c0 = (long long)blockIdx.x * TC;
+    const long long c0 = (ALIGNED ? (long long)blockIdx.x : column_part(P)) * TC;
     float4 r[RPW][RUN];
 #pragma unroll
     for (int j = 0; j < RPW; ++j) {
@@ -104,7 +119,7 @@ __global__ __launch_bounds__(AVG_THREADS) void average_rows_vec4_kernel(
     const long long P4 = P >> 2, C4 = (P + 3) >> 2;
     const int rem = ALIGNED ? 0 : (int)(P & 3);
     const long long stride = (long long)gridDim.x * AVG_THREADS;
-    for (long long i = (long long)blockIdx.x * AVG_THREADS + threadIdx.x; i < C4; i += stride) {
+    for (long long i = (ALIGNED ? (long long)blockIdx.x : column_part(P)) * AVG_THREADS + threadIdx.x; i < C4; i += stride) {
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
         float4 cmp = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int k0 = 0; k0 < K; k0 += AVG_KU) {
@@ -134,7 +149,7 @@ __global__ __launch_bounds__(AVG_THREADS) void average_rows_kernel(float *__rest
 {
     typedef float vec __attribute__((ext_vector_type(V)));
     if (st != nullptr && st->h + 1 != st->H) return;
-    const long long i = ((long long)blockIdx.x * AVG_THREADS + threadIdx.x) * V;
+    const long long i = (column_part(P) * AVG_THREADS + threadIdx.x) * V;
     if (i >= P) return;
     float acc[V] = {}, cmp[V] = {};
     for (int k0 = 0; k0 < K; k0 += AVG_KU) {
