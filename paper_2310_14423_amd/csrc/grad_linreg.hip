@@ -125,57 +125,77 @@ template <int N> __device__ __forceinline__ float lane_sums(float (&v)[N], int l
     return v[0] + lane_xor1(v[0]);
 }
 
-// Steps 1 and 2 for such workers, one workgroup per sample: 256 lanes draw the sample's inputs and own four columns each (d no
-// multiple of 4: a row begins inside a group of the generator, and the draws pass through LDS), wavefront 4 draws the noise.
-__global__ __launch_bounds__(320) void linreg_residual_row_kernel(
-    float *__restrict__ X, const float *__restrict__ theta, const float *__restrict__ wstar, float *__restrict__ r,
-    int B, int d, int d4, float sigma, uint64_t seed, const DevState *__restrict__ st)
+// Steps 1 and 2 for such workers, one workgroup per sample: 256 lanes draw the sample's inputs and own four columns each, a lane
+// of wavefront 4 draws the noise.  Rows that are no multiple of 4 long begin inside a group of the generator: there the
+// draws pass through LDS, whole groups at a time (what lies beyond the row's ends is masked where it is read), and the 257th
+// group that such a row can touch is drawn by wavefront 4 too.  The parameters are loaded without a branch: behind one, each
+// load was waited for before the draws.  Bound by latency; 3 x 1003 features x 17 samples 3.4 us, 4 x 1024 x 32 3.1 us
+// (behind branches 3.4; four guarded stores a group 4.0 at 3 x 1003 x 17).  One structure as the argument: enqueueing an
+// iteration's two kernels, 7.8 us with ten and fifteen arguments, takes 7.1, and single iterations of 3 x 1003 x 17 wait for the host.
+struct LinregRows {
+    float *X;
+    const float *theta, *wstar;
+    float *r;
+    int B, d, d4;
+    float sigma;
+    uint64_t seed;
+    const DevState *st;
+};
+template <bool ALIGNED>
+__global__ __launch_bounds__(320) void linreg_residual_row_kernel(LinregRows a)
 {
-    __shared__ __attribute__((aligned(16))) float row[RUN_MAX_D + 4];
+    const int B = a.B, d = a.d;
+    __shared__ __attribute__((aligned(16))) float row[ALIGNED ? 4 : 4 + RUN_MAX_D + 4];   // column j at 4 + j, j from -3 on
     __shared__ float red[5];
     const int k = blockIdx.y, i = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, c = tid * 4;
-    const uint32_t t = (uint32_t)st->t;
-    // (used behind the draws, which hide the latency)
-    float4 w = make_float4(0.f, 0.f, 0.f, 0.f), b = w, z = w;
-    if (wave < 4 && c < d) {
-        const float *wp = theta + (long long)k * d + c, *bp = wstar + c;
-        if (c + 3 < d) {
-            w = ld4u(wp); b = ld4u(bp);
-        } else {
-            w.x = wp[0]; b.x = bp[0];
-            if (c + 1 < d) { w.y = wp[1]; b.y = bp[1]; }
-            if (c + 2 < d) { w.z = wp[2]; b.z = bp[2]; }
-        }
-    }
-    if ((d & 3) == 0) {
-        if (wave < 4 && c < d) z = normal4(seed, STREAM_X, (uint32_t)k, t, (uint32_t)((long long)i * (d >> 2) + tid));
+    uint32_t t = (uint32_t)a.st->t;
+    const float *wp = a.theta + (long long)k * d;
+    float4 w, b;                                         // used behind the draws, which hide the latency
+    if (ALIGNED) {
+        const int j = min(c, d - 4);
+        w = ld4u(wp + j); b = ld4u(a.wstar + j);
     } else {
-        const long long f0 = (long long)i * d, q0 = f0 >> 2;
-        const int nq = (int)(((f0 + d + 3) >> 2) - q0);
-        for (int q = tid; q < nq && wave < 4; q += 256) {
-            const int j0 = (int)((q0 + q) * 4 - f0);     // column of the group's first element
-            const float4 z4 = normal4(seed, STREAM_X, (uint32_t)k, t, (uint32_t)(q0 + q));
-            if (j0 >= 0 && j0 < d) row[j0] = z4.x;
-            if (j0 + 1 >= 0 && j0 + 1 < d) row[j0 + 1] = z4.y;
-            if (j0 + 2 >= 0 && j0 + 2 < d) row[j0 + 2] = z4.z;
-            if (j0 + 3 >= 0 && j0 + 3 < d) row[j0 + 3] = z4.w;
+        const int j[4] = {min(c, d - 1), min(c + 1, d - 1), min(c + 2, d - 1), min(c + 3, d - 1)};
+        w = make_float4(wp[j[0]], wp[j[1]], wp[j[2]], wp[j[3]]);
+        b = make_float4(a.wstar[j[0]], a.wstar[j[1]], a.wstar[j[2]], a.wstar[j[3]]);
+    }
+    asm volatile("" : "+s"(t));                          // requested first of all, not where the draws begin
+    const long long f0 = (long long)i * d, q0 = f0 >> 2;
+    const int nq = (int)(((f0 + d + 3) >> 2) - q0), q = min(tid, 256);
+    const bool noise = tid == 256;
+    float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (noise || (tid < 258 && q < nq))
+        z = normal4(a.seed, noise ? STREAM_NOISE : STREAM_X, (uint32_t)k, t, noise ? (uint32_t)(i >> 2) : (uint32_t)(q0 + q));
+    if (noise) red[4] = (i & 3) == 0 ? z.x : (i & 3) == 1 ? z.y : (i & 3) == 2 ? z.z : z.w;
+    if (!ALIGNED) {
+        if (!noise && tid < 258 && q < nq) {
+            float *to = row + 4 + (int)((q0 + q) * 4 - f0);
+            to[0] = z.x; to[1] = z.y; to[2] = z.z; to[3] = z.w;
         }
-        if (tid < d4 - d) row[d + tid] = 0.f;
         __syncthreads();
-        if (wave < 4 && c < d) z = *(const float4 *)(row + c);
+        if (wave < 4 && c < d) {
+            z = *(const float4 *)(row + 4 + c);
+            if (c + 1 >= d) z.y = 0.f;
+            if (c + 2 >= d) z.z = 0.f;
+            if (c + 3 >= d) z.w = 0.f;
+        }
     }
     if (wave < 4) {
-        if (c < d) *(float4 *)(X + ((long long)k * B + i) * d4 + c) = z;
-        float acc = fmaf(z.x, w.x - b.x, 0.f);
-        acc = fmaf(z.y, w.y - b.y, acc); acc = fmaf(z.z, w.z - b.z, acc); acc = fmaf(z.w, w.w - b.w, acc);
+        float acc = 0.f;
+        if (c < d) {
+            *(float4 *)(a.X + ((long long)k * B + i) * a.d4 + c) = z;
+            float dw[4] = {w.x - b.x, w.y - b.y, w.z - b.z, w.w - b.w};
+#pragma unroll
+            for (int e = 1; e < 4; ++e)
+                if (!ALIGNED && c + e >= d) dw[e] = 0.f;
+            acc = fmaf(z.x, dw[0], 0.f);
+            acc = fmaf(z.y, dw[1], acc); acc = fmaf(z.z, dw[2], acc); acc = fmaf(z.w, dw[3], acc);
+        }
         acc = lane_sum(acc);
         if ((tid & 63) == 0) red[wave] = acc;
-    } else if (tid == 256) {
-        const float4 n = normal4(seed, STREAM_NOISE, (uint32_t)k, t, (uint32_t)(i >> 2));
-        red[4] = (i & 3) == 0 ? n.x : (i & 3) == 1 ? n.y : (i & 3) == 2 ? n.z : n.w;
     }
     __syncthreads();
-    if (tid == 0) r[(long long)k * B + i] = fmaf(-sigma, red[4], ((red[0] + red[1]) + red[2]) + red[3]);
+    if (tid == 0) a.r[(long long)k * B + i] = fmaf(-a.sigma, red[4], ((red[0] + red[1]) + red[2]) + red[3]);
 }
 
 // One workgroup per sample.  Wavefronts 0-3 draw the sample's inputs (whole groups of the generator,
@@ -382,8 +402,9 @@ static hipError_t launch_residual(const ModelDims &d, const float *theta, const 
                                   const DevState *st, hipStream_t s)
 {
     if (linreg_can_run(d)) {
-        linreg_residual_row_kernel<<<dim3((unsigned)d.B, (unsigned)d.K), 320, 0, s>>>(
-            (float *)ws, theta, wstar, linreg_r(d, ws), (int)d.B, (int)d.d_in, run_shape(d).d4, d.data_sigma, d.seed, st);
+        auto row = d.d_in % 4 == 0 ? linreg_residual_row_kernel<true> : linreg_residual_row_kernel<false>;
+        row<<<dim3((unsigned)d.B, (unsigned)d.K), 320, 0, s>>>(
+            LinregRows{(float *)ws, theta, wstar, linreg_r(d, ws), (int)d.B, (int)d.d_in, run_shape(d).d4, d.data_sigma, d.seed, st});
         return hipGetLastError();
     }
     // Rows that are no multiple of 4 long: 128-bit accesses where there is enough work to be bound by them, 32-bit ones
