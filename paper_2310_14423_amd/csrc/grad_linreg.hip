@@ -271,32 +271,47 @@ __global__ __launch_bounds__(320) void linreg_residual_kernel(
     if (tid == 0) r[(long long)k * B + i] = (red[0] + red[1] + red[2] + red[3]) - sigma * red[4];
 }
 
-// Step 3 with the OPT update, one workgroup per 64 columns of KW workers: KW * S wavefronts, the samples of a
-// worker cut into S runs, a wavefront each (all loads of the benchmark size's 32 samples are in flight at once); the partial
-// sums of the runs are added in order through LDS by the worker's first wavefront, which updates its columns.  KW = 1 for
-// workers that linreg_run_kernel takes too, with its S; else all K, S = 16 / K, so that the launch can average as well
-// (average, if the device's scheduler says that a round ends), with the averaging kernel's arithmetic.  st_next as in the
-// update kernels.
+// Step 3 with the OPT update, one workgroup per 64 columns of KW workers.  The samples of a worker are cut into `runs` runs of
+// `per`, whose sums are added in order; each of its S wavefronts (threadIdx.y) takes `each` consecutive ones, eight samples'
+// loads in flight, and leaves their sums in LDS, and the first one adds them up and updates the columns.  All K workers
+// (KW = K, S = 16 / K): the launch can average as well (average, if the device's scheduler says that a round ends),
+// with the averaging kernel's arithmetic.  KW = 1, a wavefront per run: iterations one by one of workers that
+// linreg_run_kernel takes too, in its runs either way.  st_next as in the update kernels.  Bound by latency, of the
+// instructions too (each launch fetches them anew: 16 samples unrolled, or the next eight requested ahead in code of their
+// own, 0.5 to 1 us slower).  4 x 1024 x 32, KW = 1: 3.4 us (4.2 with KW = K).
 struct LinregStep {
     float *theta, *g, *s0, *s1;          // s1: AdamW
     const StepScalars *sc;
     float c1, c2, eps;                   // SGD: c1 = mu, c2 = lambda
 };
+struct LinregGradStep {
+    const float *X, *r;
+    LinregStep p;
+    float *loss;
+    int K, runs, each, per, B, average;
+    long long d, ldx;
+    const DevState *st;
+    DevState *st_next;
+    SchedParams sp;
+};
 template <bool ADAMW>
-__global__ __launch_bounds__(1024) void linreg_grad_update_kernel(
-    const float *__restrict__ X, const float *__restrict__ r, LinregStep p, float *__restrict__ loss, int K, int KW, int S,
-    int per, int B, long long d, long long ldx, const DevState *__restrict__ st, DevState *__restrict__ st_next, int average, SchedParams sp)
+__global__ __launch_bounds__(1024) void linreg_grad_update_kernel(LinregGradStep a)
 {
-    __shared__ float part[16][64];
-    __shared__ float upd[16][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int kw = wave / S, k = blockIdx.y * KW + kw, s = wave - kw * S;
+    const LinregStep &p = a.p;
+    const DevState *const st = a.st;
+    const int runs = a.runs, each = a.each, per = a.per, B = a.B;
+    const long long d = a.d, ldx = a.ldx;
+    extern __shared__ float step_part[];                 // [KW][runs][64]
+    float (*part)[64] = (float (*)[64])step_part;
+    const int lane = threadIdx.x, s = __builtin_amdgcn_readfirstlane(threadIdx.y), kw = __builtin_amdgcn_readfirstlane(threadIdx.z);
+    const int k = blockIdx.y * blockDim.z + kw;
     const long long j = (long long)blockIdx.x * 64 + lane;
     const bool in = j < d;
     // the last thread of the last workgroup, which has no column of its own where the others are busiest
-    if (st_next != nullptr && blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && threadIdx.x == blockDim.x - 1)
-        tick_into(st, st_next, sp);
-    const bool sync = average != 0 && st->h + 1 == st->H;
+    if (a.st_next != nullptr && blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && lane == 63 && s == (int)blockDim.y - 1 &&
+        kw == (int)blockDim.z - 1)
+        tick_into(st, a.st_next, a.sp);
+    const bool sync = a.average != 0 && st->h + 1 == st->H;
     const StepScalars sc = p.sc[st->t];
     const long long o = (long long)k * d + j;
     float th = 0.f, m = 0.f, v = 0.f;
@@ -304,35 +319,44 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(
         th = p.theta[o]; m = p.s0[o];
         if (ADAMW) v = p.s1[o];
     }
-    const float *Xk = X + (long long)k * B * ldx + j;
-    const float *rk = r + (long long)k * B;
+    const int run0 = min(runs, s * each), run1 = min(runs, run0 + each);
+    const int i0 = min(B, run0 * per), i1 = min(B, run1 * per);
+    const float *rk = a.r + (long long)k * B;
+    const float rv = i0 + lane < i1 ? rk[i0 + lane] : 0.f;      // the wavefront's residuals, one a lane
+    const float *row = a.X + ((long long)k * B + i0) * ldx;
+    const unsigned col = (unsigned)min(j, d - 1);
+    float (*to)[64] = part + kw * runs + run0;           // of the run at hand, which ends behind sample `end`
+    int end = i0 + per;
     float acc = 0.f;
-    if (in) {
-        const int i0 = min(B, s * per), i1 = min(B, i0 + per);
-        for (int i = i0; i < i1; i += 8) {               // a short last run is filled up with weight 0
-            float xv[8];
+    for (int i = i0; i < i1; i += 8) {                   // a short last group is filled up with weight 0
+        float xv[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) xv[u] = Xk[min(i + u, i1 - 1) * ldx];
+        for (int u = 0; u < 8; ++u) {
+            xv[u] = row[col];
+            row += i + u + 1 < i1 ? ldx : 0;
+        }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc = fmaf(i + u < i1 ? rk[i + u] : 0.f, xv[u], acc);
+        for (int u = 0; u < 8; ++u) {
+            acc = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(rv), i - i0 + u)), xv[u], acc);
+            if (i + u + 1 == end && end < i1) { (*to++)[lane] = acc; acc = 0.f; end += per; }
         }
     }
-    part[wave][lane] = acc;
+    if (i0 < i1) (*to)[lane] = acc;
     if (blockIdx.x == 0 && s == 0) {
-        float a = 0.f;
-        for (int i = lane; i < B; i += 64) a = fmaf(rk[i], rk[i], a);
+        float l = 0.f;
+        for (int i = lane; i < B; i += 64) l = fmaf(rk[i], rk[i], l);
 #pragma unroll
-        for (int q = 32; q > 0; q >>= 1) a += __shfl_down(a, q, 64);
-        if (lane == 0) loss[k] = 0.5f * a / (float)B;
+        for (int q = 32; q > 0; q >>= 1) l += __shfl_down(l, q, 64);
+        if (lane == 0) a.loss[k] = 0.5f * l / (float)B;
     }
     __syncthreads();
     if (s == 0) {
-        float gj = part[wave][lane];
-        for (int q = 1; q < S; ++q) gj += part[wave + q][lane];
+        float gj = part[kw * runs][lane];
+        for (int q = 1; q < runs; ++q) gj += part[kw * runs + q][lane];
         gj *= 1.0f / (float)B;
         if (ADAMW) adamw_elem(th, gj, m, v, sc.x, sc.y, sc.z, p.c1, p.c2, p.eps);
         else sgdm_elem(th, gj, m, sc.x, p.c1, p.c2);
-        upd[k][lane] = th;
+        part[kw * runs][lane] = th;                      // for the average
         if (in) {
             p.g[o] = gj; p.s0[o] = m;
             if (ADAMW) p.s1[o] = v;
@@ -342,9 +366,9 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(
     if (!sync) return;                                   // the same for the whole launch
     __syncthreads();
     if (s == 0 && in) {
-        float a = 0.f, c = 0.f;
-        for (int q = 0; q < K; ++q) add_comp(a, c, upd[q][lane]);
-        p.theta[o] = (a + c) / (float)K;
+        float sum = 0.f, err = 0.f;
+        for (int q = 0; q < a.K; ++q) add_comp(sum, err, part[q * runs][lane]);
+        p.theta[o] = (sum + err) / (float)a.K;
     }
 }
 
@@ -446,6 +470,34 @@ bool linreg_can_fuse(const ModelDims &d)
     return per <= (S > 1 ? 64 : 32);
 }
 
+// How linreg_grad_update_kernel shares the samples out
+struct StepShape { int KW, S, runs, each, per; };
+static StepShape step_shape(const ModelDims &d, bool average)
+{
+    const bool run = linreg_can_run(d), alone = run && !average;
+    StepShape q;
+    q.KW = alone ? 1 : d.K;
+    q.S = alone ? run_shape(d).groups : 16 / d.K;
+    q.per = run ? run_shape(d).per : (int)((d.B + q.S - 1) / q.S);
+    q.runs = (int)((d.B + q.per - 1) / q.per);           // none of them empty
+    q.each = (q.runs + q.S - 1) / q.S;
+    return q;
+}
+
+// A round of one iteration in two kernels takes longer with the samples of a wavefront, as linreg_run_kernel with the samples
+// and columns of a workgroup.  us a round, two kernels / linreg_run_kernel (two replayed kernels with samples cut into 16 / K runs):
+//   1 x 117 x 38 6.9 / 7.2 (7.6)    4 x 1024 x 32 7.6 / 9.6 (7.6)   16 x 1024 x 8 8.3 / 9.2 (8.0)    3 x 512 x 64 7.9 / 9.4 (8.1)
+//   8 x 256 x 128 16.4 / 10.1 (14.5)   7 x 64 x 128 15.9 / 8.5 (13.8)   16 x 1024 x 32 12.3 / 11.1 (11.7)   6 x 668 x 28 9.0 / 9.4 (8.2)
+// Over 245 random sizes the choice is within 0.5 % of the better one on average (10.5 % at most), and 9 % faster than the
+// replayed kernels; slower than those where five runs go to four to six workers' wavefronts unevenly: 4 x 668 x 25 8.5 (7.6).
+bool linreg_single_rounds(const ModelDims &d)
+{
+    if (!linreg_can_run(d)) return false;
+    const StepShape q = step_shape(d, true);
+    const int samples = q.each * q.per;
+    return samples <= 8 || (samples <= 16 && (q.per > 4 || d.d_in > 768)) || (samples <= 24 && q.per > 4 && d.d_in > 768);
+}
+
 hipError_t launch_linreg_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
                                   const DevState *st, hipStream_t s)
 {
@@ -458,16 +510,13 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
                                      hipStream_t s)
 {
     if (!linreg_can_fuse(d)) return hipErrorInvalidValue;
-    const bool run = linreg_can_run(d);
-    if (run && average) return hipErrorInvalidValue;
-    const int KW = run ? 1 : d.K, S = run ? run_shape(d).groups : 16 / d.K, per = (int)((d.B + S - 1) / S);
-    const LinregStep p{theta, g, s0, s1, sc, c1, c2, eps};
-    const dim3 grid((unsigned)((d.d_in + 63) / 64), (unsigned)(d.K / KW));
-    const int threads = KW * S * 64;
-    if (s1) linreg_grad_update_kernel<true><<<grid, threads, 0, s>>>((const float *)ws, linreg_r(d, ws), p, loss, d.K, KW, S, per,
-                                                                     (int)d.B, d.d_in, row_stride(d), st, st_next, average ? 1 : 0, sp);
-    else linreg_grad_update_kernel<false><<<grid, threads, 0, s>>>((const float *)ws, linreg_r(d, ws), p, loss, d.K, KW, S, per,
-                                                                   (int)d.B, d.d_in, row_stride(d), st, st_next, average ? 1 : 0, sp);
+    const StepShape q = step_shape(d, average);
+    if (q.each * q.per > 64) return hipErrorInvalidValue;        // a wavefront's residuals lie one a lane
+    const LinregGradStep a{(const float *)ws, linreg_r(d, ws), LinregStep{theta, g, s0, s1, sc, c1, c2, eps}, loss, d.K, q.runs, q.each,
+                           q.per, (int)d.B, average ? 1 : 0, d.d_in, row_stride(d), st, st_next, sp};
+    const dim3 grid((unsigned)((d.d_in + 63) / 64), (unsigned)(d.K / q.KW)), block(64, (unsigned)q.S, (unsigned)q.KW);
+    auto kern = s1 ? linreg_grad_update_kernel<true> : linreg_grad_update_kernel<false>;
+    kern<<<grid, block, (size_t)q.KW * q.runs * 64 * sizeof(float), s>>>(a);
     return hipGetLastError();
 }
 

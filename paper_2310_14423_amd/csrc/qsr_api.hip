@@ -662,23 +662,45 @@ static int run_one_by_one(qsr_ctx *c, long long n)
 }
 
 // Least squares on workers that fit one workgroup: launches that end where a round does, each drawing inputs ahead for the
-// launches behind it, but none beyond this call.
+// launches behind it, but none beyond this call.  Rounds of one iteration take two kernels instead, the second of which
+// averages, where that is faster (linreg_single_rounds); from launches behind one another they do so from SINGLE_ROUNDS
+// such rounds in a row on, since the parameters then go through the caller's array and a launch of the averaging.
+constexpr int SINGLE_ROUNDS = 4;
 static int run_linreg(qsr_ctx *c, long long n)
 {
     const qsr_config &cfg = c->cfg;
     const bool sgd = cfg.opt == QSR_OPT_SGDM;
+    const float c1 = (float)(sgd ? cfg.momentum : 1.0 - cfg.beta1), c2 = (float)(sgd ? cfg.weight_decay : 1.0 - cfg.beta2);
+    float *const state1 = sgd ? nullptr : c->state1;
     long long drawn = 0;                                 // iterations from the current one on
     int from = -1, last = 0;                             // where the parameters are; the st_last of the next launch
     auto launch = [&](const LinregSpan &span, const SchedParams &sp) {
-        return launch_linreg_run(c->dims, c->params, c->grads, c->state0, sgd ? nullptr : c->state1, c->model_const,
-                                 c->workspace, c->d_loss, c->d_scal, (float)(sgd ? cfg.momentum : 1.0 - cfg.beta1),
-                                 (float)(sgd ? cfg.weight_decay : 1.0 - cfg.beta2), (float)cfg.eps, span, sp, c->stream);
+        return launch_linreg_run(c->dims, c->params, c->grads, c->state0, state1, c->model_const, c->workspace, c->d_loss,
+                                 c->d_scal, c1, c2, (float)cfg.eps, span, sp, c->stream);
+    };
+    // whether the rounds from iteration t on, the first of H iterations, are `rounds` of one iteration each
+    auto singles = [&](long long t, long long H, int rounds) {
+        if (!linreg_single_rounds(c->dims)) return false;
+        for (; rounds > 0 && H == 1; --rounds, ++t) H = host_get_H(c->sp, c->eta.data(), t + 1);
+        return rounds == 0;
     };
     while (n > 0) {
         const long long left = c->m_H - c->m_h;
+        SchedParams sp = c->sp;
+        if (from < 0 && c->m_h == 0 && singles(c->m_t, c->m_H, 1)) {
+            sp.expect_sync = 1;
+            HIP_TRY(launch_linreg_residual(c->dims, c->params, c->model_const, c->workspace, st_cur(c), c->stream));
+            HIP_TRY(launch_linreg_grad_update(c->dims, c->params, c->grads, c->state0, state1, c->workspace, c->d_loss, c->d_scal,
+                                              c1, c2, (float)cfg.eps, st_cur(c), c->d_state + (c->cur ^ 1), true, sp, c->stream));
+            c->cur ^= 1;
+            mirror_advance(c);
+            c->t_host += 1;
+            n -= 1;
+            drawn = 0;
+            continue;
+        }
         long long seg = n < left ? n : left;
         if (seg > LINREG_RUN_MAX) seg = LINREG_RUN_MAX;
-        SchedParams sp = c->sp;
         if (drawn == 0) {                                // the first launch's inputs
             HIP_TRY(launch({0, 0, (int)seg, -1, -1, st_cur(c), nullptr, nullptr, nullptr}, sp));
             drawn = seg;
@@ -687,7 +709,9 @@ static int run_linreg(qsr_ctx *c, long long n)
         const bool sync = seg == left;
         sp.expect_sync = sync ? 1 : 0;
         const long long draws = (n < LINREG_RUN_AHEAD ? n : LINREG_RUN_AHEAD) - drawn;
-        const int to = seg == n ? -1 : from == 0 ? 1 : 0;
+        const bool leave = seg == n || (sync && n - seg >= SINGLE_ROUNDS &&
+                                        singles(c->m_t + seg, host_get_H(c->sp, c->eta.data(), c->m_t + seg), SINGLE_ROUNDS));
+        const int to = leave ? -1 : from == 0 ? 1 : 0;
         DevState *const st_last = c->d_state + 2 + last;
         HIP_TRY(launch({(int)seg, (int)drawn, (int)draws, from, to, st_cur(c), c->d_state + (c->cur ^ 1), st_last,
                         c->d_state + 2 + (last ^ 1)}, sp));
@@ -697,7 +721,7 @@ static int run_linreg(qsr_ctx *c, long long n)
         c->t_host += seg;
         n -= seg;
         from = to; last ^= 1;
-        if (n == 0 && sync) HIP_TRY(launch_average_rows(c->params, cfg.K, cfg.P, st_last, c->stream));
+        if (leave && sync) HIP_TRY(launch_average_rows(c->params, cfg.K, cfg.P, st_last, c->stream));
     }
     return QSR_OK;
 }

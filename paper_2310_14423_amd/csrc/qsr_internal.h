@@ -192,6 +192,8 @@ struct LinregSpan {
     const DevState *st_mean;         // a copy read is averaged first, if this st_last was the end of a round
 };
 bool linreg_can_run(const ModelDims &d);
+// whether rounds of one iteration are faster in two kernels that average than as such a launch each
+bool linreg_single_rounds(const ModelDims &d);
 hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws,
                              float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
                              const SchedParams &sp, hipStream_t s);

@@ -55,3 +55,32 @@ def test_together_after_set_state():
     b.run(60)
     assert a.get_state() == b.get_state() and torch.equal(a.params, b.params) and torch.equal(a.state0, b.state0)
     a.close(); b.close()
+
+
+@pytest.mark.parametrize("K,d,B,opt", [
+    # rounds of one iteration in two kernels, samples shared out in the runs of the other kernel: one, two and five wavefronts a
+    # worker, several runs a wavefront, a run cut short, workers without a second wavefront
+    (4, 668, 25, "sgdm"), (16, 257, 8, "adamw"), (3, 1003, 17, "sgdm"), (2, 256, 32, "sgdm"), (1, 5, 3, "sgdm"), (11, 916, 17, "sgdm"),
+    (6, 300, 16, "adamw"), (16, 1024, 32, "sgdm"), (8, 61, 128, "sgdm")])
+def test_rounds_of_one_iteration(K, d, B, opt):
+    """Long rounds, nineteen of one iteration, long ones, two of one iteration (fewer than are worth another way through the
+    kernels), one to the end; entered and left at different places by the calls."""
+    import torch
+    kw = dict(mu=0.9, lam=1e-4) if opt == "sgdm" else dict(beta1=0.9, beta2=0.99, eps=1e-3, lam=0.01)
+    T, eta = 100, 0.02 / (1 + d / B)
+    w = workloads.get("lsq", K=K, d_in=d, B_loc=B, T=T, opt=opt, eta_max=7 * eta, H_base=1, alpha=7.5 * eta, power=1, **kw)
+    table = np.full(T, eta)                                      # H = 7, but H = 1 where the rate is seven times as high
+    table[21:40] = table[61:63] = 7 * eta
+    for calls in ((100,), (23, 5, 33, 39), (2, 58, 40)):
+        ref, ctx = gpu_ctx(w, eta_table=table), gpu_ctx(w, eta_table=table)
+        for n in calls:
+            ref.step(n)
+            ctx.run(n)
+            assert ctx.get_state() == ref.get_state()
+            for a, b in zip((ctx.params, ctx.grads, ctx.state0, ctx.state1), (ref.params, ref.grads, ref.state0, ref.state1)):
+                assert a is b is None or torch.equal(a, b)
+            assert np.array_equal(ctx.read_loss(), ref.read_loss())
+        H = list(ctx.read_sync_log()[1])
+        assert H[:3] == [7] * 3 and H[3:22] == [1] * 19 and H[22:25] == [7] * 3 and H[25:27] == [1] * 2 and sum(H) == T
+        assert_mirror_matches_device(ctx)
+        ctx.close(); ref.close()
