@@ -100,12 +100,13 @@ inline WgradPlan wgrad_plan(int M, int N, int tokens, int batch, int n_cu)
 
 // Whether the weight gradients of all blocks wait for one launch behind the backward pass (each block then keeps its
 // operands, at most 2 GiB) instead of two launches per block: where the estimates say that it is faster.  Decided for the
-// whole chip's 256 compute units, since it decides the workspace's layout.  2 x 1040 tokens x 192 x 768, two blocks with
+// whole chip's 256 compute units, since it decides the workspace's layout.  The sums behind it take two workgroups along the
+// grid's z extent for each LayerNorm and one more, of at most 65536.  2 x 1040 tokens x 192 x 768, two blocks with
 // attention: 67 us of weight gradients in 8 launches, 13 in one.
 inline bool wgrad_defer(long long K, long long tokens, long long d, long long dh, bool attention, long long n_blocks)
 {
     const long long bytes = K * tokens * n_blocks * (d + dh + (attention ? 4 * d : 0)) * 2;
-    if (n_blocks < 2 || bytes > (1ll << 31)) return false;
+    if (n_blocks < 2 || bytes > (1ll << 31) || (attention ? 4 : 2) * n_blocks + 1 > 65536) return false;
     WgradLoad mlp, attn, all;
     for (WgradLoad *q : {&mlp, &all}) {
         const long long copies = q == &all ? K * n_blocks : K;

@@ -44,13 +44,42 @@ int main()
 """
 
 
-@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
-def test_partial_results_fit_their_workspace(tmp_path):
+MANY_BLOCKS = r"""
+#include <cstdio>
+#include "wgrad_plan.h"
+using namespace qsr;
+int main()
+{
+    for (int attention = 0; attention < 2; ++attention)
+        for (long long n : {2ll, 1000ll, 16383ll, 16384ll, 32767ll, 32768ll, 40000ll})
+            printf("%d %lld %d\n", attention, n, (int)wgrad_defer(1, 64, 64, 64, attention, n));
+    return 0;
+}
+"""
+
+
+def _run(tmp_path, code):
     src, exe = tmp_path / "driver.cpp", tmp_path / "driver"
-    src.write_text(DRIVER)
+    src.write_text(code)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(ROOT, "paper_2310_14423_amd", "csrc"),
                     str(src), "-o", str(exe)], check=True, timeout=120)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stdout
+    return out
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_no_launch_of_all_blocks_beyond_the_grid(tmp_path):
+    """The launches behind a shared weight-gradient launch have an entry along the grid's z extent (at most 65536) for every
+    LayerNorm parameter of every block."""
+    rows = [tuple(map(int, l.split())) for l in _run(tmp_path, MANY_BLOCKS).stdout.splitlines()]
+    for attention, n_blocks, deferred in rows:
+        assert not deferred or 2 * n_blocks * (1 + attention) + 1 <= 65536
+    assert {n for _, n, deferred in rows if deferred} >= {2, 1000, 16383, 32767}      # as far as the grid goes
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_partial_results_fit_their_workspace(tmp_path):
+    out = _run(tmp_path, DRIVER)
     cut, wide = map(int, out.stdout.split())
     assert cut > 1000 and wide > 100          # the cut ones, and those of a model that is wider than its hidden layer
