@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include "qsr_internal.h"
+#include "tile_grid.h"
 
 namespace qsr {
 
@@ -195,13 +196,14 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
     __shared__ __attribute__((aligned(16))) SgemmLds lds[KSPLIT];
     sgemm_tile<TA, TB, EPI, KSPLIT>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
 }
-// A weight gradient and a data gradient that do not depend on each other, in one launch: workgroups below `first` of
-// the grid's x extent take the weight gradient's tiles, the others the data gradient's.
+// A weight gradient and a data gradient that do not depend on each other, in one launch: workgroups below `first` of `all`
+// take the weight gradient's tiles, the others the data gradient's.
 template <int EPI, int KSPLIT>
-__global__ __launch_bounds__(256 * KSPLIT) void sgemm_pair_kernel(GemmArgs w, GemmArgs d, int first, int nxw, int nxd)
+__global__ __launch_bounds__(256 * KSPLIT) void sgemm_pair_kernel(GemmArgs w, GemmArgs d, unsigned first, unsigned all, unsigned nxw, unsigned nxd)
 {
     __shared__ __attribute__((aligned(16))) SgemmLds lds[KSPLIT];
-    int b = blockIdx.x;
+    unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
+    if (b >= all) return;
     if (b < first) { sgemm_tile<true, false, EPI_NONE, KSPLIT>(w, b % nxw, b / nxw, blockIdx.z, lds); return; }
     b -= first;
     sgemm_tile<false, true, EPI, KSPLIT>(d, b % nxd, b / nxd, blockIdx.z, lds);
@@ -230,12 +232,13 @@ inline hipError_t launch_sgemm_pair(const GemmArgs &w, const GemmArgs &d, int ba
 {
     if (!sgemm_rows_ok(w.A, w.lda, w.sA, w.M) || !sgemm_rows_ok(w.B, w.ldb, w.sB, w.N) || !sgemm_rows_ok(d.A, d.lda, d.sA, d.Kd))
         return hipErrorInvalidValue;
-    const int nxw = (w.N + 63) / 64, nxd = (d.N + 63) / 64;
-    const long long first = (long long)nxw * ((w.M + 63) / 64), all = first + (long long)nxd * ((d.M + 63) / 64);
-    if (all > 0x7FFFFFll) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)all, 1, (unsigned)batch);
-    if (sgemm_two(w.Kd > d.Kd ? w.Kd : d.Kd, all * batch)) sgemm_pair_kernel<EPI, 2><<<grid, 512, 0, s>>>(w, d, (int)first, nxw, nxd);
-    else sgemm_pair_kernel<EPI, 1><<<grid, 256, 0, s>>>(w, d, (int)first, nxw, nxd);
+    const long long nxw = (w.N + 63) / 64, nxd = (d.N + 63) / 64, first = nxw * ((w.M + 63) / 64), all = first + nxd * ((d.M + 63) / 64);
+    const bool two = sgemm_two(w.Kd > d.Kd ? w.Kd : d.Kd, all * batch);
+    const TileGrid t = tile_grid(all, two ? 512 : 256);
+    if (t.x == 0 || all > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    const dim3 grid(t.x, t.y, (unsigned)batch);
+    if (two) sgemm_pair_kernel<EPI, 2><<<grid, 512, 0, s>>>(w, d, (unsigned)first, (unsigned)all, (unsigned)nxw, (unsigned)nxd);
+    else sgemm_pair_kernel<EPI, 1><<<grid, 256, 0, s>>>(w, d, (unsigned)first, (unsigned)all, (unsigned)nxw, (unsigned)nxd);
     return hipGetLastError();
 }
 
