@@ -43,10 +43,18 @@ typedef double f64x4_t __attribute__((ext_vector_type(4)));
 // along k, four elements a thread) takes B's rows at any address, and reads up to three elements beyond their end.  No
 // load is behind a test of its own (rows beyond the matrix are read as the last one, k beyond Kd cleared in registers): as a
 // branch around each load and a wait behind it, 5 x 50 x 500 x 100 took 14.4 us.
-// Workgroup (bx, by, bz) of 256 KSPLIT threads.
-struct SgemmLds { float A[16][96], B[16][96]; };
+// Workgroup (bx, by, bz) of 256 KSPLIT threads.  The LDS is the kernel's, one for whichever tiles it has, and the other
+// groups' partial sums come after the slabs: a workgroup of two groups holds 24 KiB, and six would fit the 160 KiB of a
+// compute unit (with a static array for the sums in each kind of tile it was 56, and two did).
+struct SgemmSlabs { float A[16][96], B[16][96]; };
+template <int KSPLIT> union SgemmLds {
+    SgemmSlabs slab[KSPLIT];
+    float part[KSPLIT - 1][4][16][64];
+};
+template <> union SgemmLds<1> { SgemmSlabs slab[1]; };
+static_assert(sizeof(SgemmLds<2>) == 24 * 1024, "partial sums inside the slabs");
 template <bool TA, bool TB, int EPI, int KSPLIT>
-__device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, int bz_, SgemmLds *lds)
+__device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, int bz_, SgemmLds<KSPLIT> &lds)
 {
     static_assert(TA != TB, "weight gradients (A transposed) and data gradients (B transposed)");
     constexpr int TM = 64, TN = 64, TK = 16;             // LDS rows of 96: rows k and k+1 of a slab 32 banks apart
@@ -55,8 +63,8 @@ __device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, in
     // batch is 128 rows) every slab's load -> LDS -> barrier -> MFMA chain ran unhidden; a second
     // group per SIMD fills part of those gaps (hidden layer forward, 8 x 128 x 784 x 1024: 46 -> 37 us).
     const int grp = threadIdx.x >> 8, tid = threadIdx.x & 255;
-    float (*As)[96] = lds[grp].A;
-    float (*Bs)[96] = lds[grp].B;
+    float (*As)[96] = lds.slab[grp].A;
+    float (*Bs)[96] = lds.slab[grp].B;
     const int lane = tid & 63, wm = tid >> 7, wn = (tid >> 6) & 1;   // wavefront (wm, wn) owns a 32x32 block
     const int m0 = by * TM, n0 = bx * TN;
     const long long bz = bz_;
@@ -148,9 +156,9 @@ __device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, in
         if (tid < 64) As[0][tid] = cs;                // the slabs are done with
         __syncthreads();
         if (grp == 0 && tid < 64 && n0 + tid < a.N) {
-            float v = lds[0].A[0][tid];
+            float v = lds.slab[0].A[0][tid];
 #pragma unroll
-            for (int g = 1; g < KSPLIT; ++g) v += lds[g].A[0][tid];
+            for (int g = 1; g < KSPLIT; ++g) v += lds.slab[g].A[0][tid];
             a.colsum[bz * a.sCol + n0 + tid] = v;
         }
         if (a.part != nullptr && bx == 0 && threadIdx.x < 64) {
@@ -163,17 +171,17 @@ __device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, in
     }
     float *C = a.C + bz * a.sC;
     if constexpr (KSPLIT > 1) {       // the other groups' partial sums, added in group order
-        __shared__ float part[KSPLIT - 1][4][16][64];
+        if (TA && !TB && col_wg) __syncthreads();     // the column sums are read
         if (grp > 0) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) part[grp - 1][tid >> 6][i][lane] = acc[i];
+            for (int i = 0; i < 16; ++i) lds.part[grp - 1][tid >> 6][i][lane] = acc[i];
         }
         __syncthreads();
         if (grp > 0) return;
 #pragma unroll
         for (int g = 0; g < KSPLIT - 1; ++g)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] += part[g][tid >> 6][i][lane];
+            for (int i = 0; i < 16; ++i) acc[i] += lds.part[g][tid >> 6][i][lane];
     }
 
     // accumulator element i of lane l is C[(i/4)*8 + (l/32)*4 + i%4][l%32] of the wavefront's block
@@ -193,7 +201,7 @@ __device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, in
 template <bool TA, bool TB, int EPI, int KSPLIT>
 __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
 {
-    __shared__ __attribute__((aligned(16))) SgemmLds lds[KSPLIT];
+    __shared__ __attribute__((aligned(16))) SgemmLds<KSPLIT> lds;
     sgemm_tile<TA, TB, EPI, KSPLIT>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
 }
 // A weight gradient and a data gradient that do not depend on each other, in one launch: workgroups below `first` of `all`
@@ -201,7 +209,7 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
 template <int EPI, int KSPLIT>
 __global__ __launch_bounds__(256 * KSPLIT) void sgemm_pair_kernel(GemmArgs w, GemmArgs d, unsigned first, unsigned all, unsigned nxw, unsigned nxd)
 {
-    __shared__ __attribute__((aligned(16))) SgemmLds lds[KSPLIT];
+    __shared__ __attribute__((aligned(16))) SgemmLds<KSPLIT> lds;
     unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
     if (b >= all) return;
     if (b < first) { sgemm_tile<true, false, EPI_NONE, KSPLIT>(w, b % nxw, b / nxw, blockIdx.z, lds); return; }
