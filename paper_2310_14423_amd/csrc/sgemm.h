@@ -207,10 +207,11 @@ __global__ __launch_bounds__(256 * KSPLIT) void sgemm_kernel(GemmArgs a)
 // A weight gradient and a data gradient that do not depend on each other, in one launch: workgroups below `first` of `all`
 // take the weight gradient's tiles, the others the data gradient's.
 template <int EPI, int KSPLIT>
-__global__ __launch_bounds__(256 * KSPLIT) void sgemm_pair_kernel(GemmArgs w, GemmArgs d, unsigned first, unsigned all, unsigned nxw, unsigned nxd)
+__global__ __launch_bounds__(256 * KSPLIT) void sgemm_pair_kernel(GemmArgs w, GemmArgs d, unsigned first, unsigned all, unsigned row,
+                                                                  unsigned nxw, unsigned nxd)
 {
     __shared__ __attribute__((aligned(16))) SgemmLds<KSPLIT> lds;
-    unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
+    unsigned b = blockIdx.y * row + blockIdx.x;        // row: the grid's x extent
     if (b >= all) return;
     if (b < first) { sgemm_tile<true, false, EPI_NONE, KSPLIT>(w, b % nxw, b / nxw, blockIdx.z, lds); return; }
     b -= first;
@@ -245,44 +246,35 @@ inline hipError_t launch_sgemm_pair(const GemmArgs &w, const GemmArgs &d, int ba
     const TileGrid t = tile_grid(all, two ? 512 : 256);
     if (t.x == 0 || all > 0x7FFFFFFFll) return hipErrorInvalidValue;
     const dim3 grid(t.x, t.y, (unsigned)batch);
-    if (two) sgemm_pair_kernel<EPI, 2><<<grid, 512, 0, s>>>(w, d, (unsigned)first, (unsigned)all, (unsigned)nxw, (unsigned)nxd);
-    else sgemm_pair_kernel<EPI, 1><<<grid, 256, 0, s>>>(w, d, (unsigned)first, (unsigned)all, (unsigned)nxw, (unsigned)nxd);
+    if (two) sgemm_pair_kernel<EPI, 2><<<grid, 512, 0, s>>>(w, d, (unsigned)first, (unsigned)all, t.x, (unsigned)nxw, (unsigned)nxd);
+    else sgemm_pair_kernel<EPI, 1><<<grid, 256, 0, s>>>(w, d, (unsigned)first, (unsigned)all, t.x, (unsigned)nxw, (unsigned)nxd);
     return hipGetLastError();
 }
 
-// C = epilogue(A B) in double precision, A [M][Kd] and B [Kd][N] fp32 and row-major, C fp32.
-// 64x64 output tile per workgroup, four wavefronts of a 32x32 block each (2 x 2 instructions of
-// 16x16x4), KSPLIT such groups side by side on their shares of the contraction, added through LDS at
-// the end.  No LDS in the main loop and no barrier: a lane's share of an instruction's operands,
-// A[row l%16][k l/16] and B[k l/16][column l%16], comes straight from global memory (a float4 of A
-// along k feeds four instructions in a row, the matching four rows of B one element each; the
-// order of k inside a group of 16 is a permutation, the same for both operands).  The LDS-tiled
-// form above ran 8 x 128 x 784 x 1024 in 50.5 us with two groups; this one 52.2 us with two and
-// 46.7 us with four (35 TFLOP/s).  Kept for rows that 128-bit copies cannot take (dgemm_nn_lds_kernel below).
-// WT = 1: 32x32 output tile, a group is one wavefront: for problems of few tiles, where more workgroups and shorter
-// shares of the contraction count (5 x 50 x 333 x 500 and 5 x 50 x 500 x 100: 28-32 us with 64x64 tiles and two
-// groups, 13.7 us with 32x32 and sixteen).
-template <int EPI, int KSPLIT, int WT>
-__global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
+// C = epilogue(A B) in double precision, A [M][Kd] and B [Kd][N] fp32 and row-major, C fp32, for contractions shorter than
+// 64 (dgemm_nn_lds_kernel below takes the others): at most four groups of 16, too few for its rings.  A wavefront has a
+// block of 32 x 32 (2 x 2 instructions of 16x16x4): WT = 4, a workgroup takes 64 x 64; WT = 1, 32 x 32, for problems of
+// few tiles.  No LDS and no barrier: a lane's share of an instruction's operands, A[row l%16][k l/16] and
+// B[k l/16][column l%16], comes straight from global memory (a float4 of A along k feeds four instructions in a
+// row, the matching four rows of B one element each; the order of k inside a group of 16 is a permutation, the same
+// for both operands).  Rows of A start at 16 bytes.
+template <int EPI, int WT>
+__global__ __launch_bounds__(64 * WT) void dgemm_nn_kernel(GemmArgs a)
 {
     constexpr int PF = 3, TILE = WT == 4 ? 64 : 32;
-    const int grp = threadIdx.x / (64 * WT), tid = threadIdx.x % (64 * WT);
-    const int lane = tid & 63, wm = tid >> 7, wn = (tid >> 6) & 1;
+    const int tid = threadIdx.x, lane = tid & 63, wm = tid >> 7, wn = (tid >> 6) & 1;
     const int r = lane & 15, q = lane >> 4;
     const int m0 = blockIdx.y * TILE + wm * 32, n0 = blockIdx.x * TILE + wn * 32;
     const long long bz = blockIdx.z;
     const float *A = a.A + bz * a.sA;
     const float *B = a.B + bz * a.sB;
-    const bool vecA = (a.lda & 3) == 0 && (((unsigned long long)A) & 15) == 0;
-    const int ng = (a.Kd + 15) / 16, ngg = (ng + KSPLIT - 1) / KSPLIT;
-    const int g0 = grp * ngg, g1 = min(ng, g0 + ngg);
+    const int ng = (a.Kd + 15) / 16;
 
     // Guarded loads: the compiler turns each into a short branch with a wait behind it, so the
-    // PF groups "ahead" are in fact waited for where they are loaded, and the wavefronts of the
-    // KSPLIT groups hide each other's latency.  Timed at 8 x 128 x 784 x 1024 (KSPLIT = 4): 46.7 us
-    // this way; 56.6 us with clamped addresses and selects, 73.3 us with unconditional clamped loads
-    // and the masks applied at the point of use (loads truly in flight three groups ahead; 62.0 us two
-    // groups ahead, without register spills).
+    // PF groups "ahead" are in fact waited for where they are loaded, and the wavefronts beside
+    // hide the latency.  Timed at 8 x 128 x 784 x 1024, four groups of wavefronts sharing the contraction:
+    // 46.7 us this way; 56.6 us with clamped addresses and selects, 73.3 us with unconditional clamped loads
+    // and the masks applied at the point of use (62.0 us two groups ahead, without register spills).
     struct Frag { float a[2][4]; float b[2][4]; };
     auto gload = [&](int g, Frag &f) {
         const int k = g * 16 + 4 * q;
@@ -290,7 +282,7 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
         for (int bi = 0; bi < 2; ++bi) {
             const int gm = m0 + bi * 16 + r;
             const float *ar = A + (long long)gm * a.lda + k;
-            if (gm < a.M && vecA && k + 3 < a.Kd) {
+            if (gm < a.M && k + 3 < a.Kd) {
                 const float4 v = *(const float4 *)ar;
                 f.a[bi][0] = v.x; f.a[bi][1] = v.y; f.a[bi][2] = v.z; f.a[bi][3] = v.w;
             } else {
@@ -323,37 +315,20 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
     Frag fr[PF];
 #pragma unroll
     for (int u = 0; u < PF; ++u)
-        if (g0 + u < g1) gload(g0 + u, fr[u]);
-    for (int gb = g0; gb < g1; gb += PF) {
+        if (u < ng) gload(u, fr[u]);
+    for (int gb = 0; gb < ng; gb += PF) {
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
             const int g = gb + u;                   // uniform over the wavefront
-            if (g < g1) {
+            if (g < ng) {
                 const Frag f = fr[u];
-                if (g + PF < g1) gload(g + PF, fr[u]);
+                if (g + PF < ng) gload(g + PF, fr[u]);
                 multiply(f);
             }
         }
     }
 
     float *C = a.C + bz * a.sC;
-    if constexpr (KSPLIT > 1) {       // the groups' partial sums, added pairwise in a fixed order
-        __shared__ double dpart[KSPLIT / 2][WT][16][64];
-#pragma unroll
-        for (int stride = KSPLIT / 2; stride >= 1; stride >>= 1) {
-            if (grp >= stride && grp < 2 * stride) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) dpart[grp - stride][tid >> 6][i][lane] = dacc[i >> 3][(i >> 2) & 1][i & 3];
-            }
-            __syncthreads();
-            if (grp < stride) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) dacc[i >> 3][(i >> 2) & 1][i & 3] += dpart[grp][tid >> 6][i][lane];
-            }
-            __syncthreads();
-        }
-        if (grp > 0) return;
-    }
     // accumulator element e of lane l is C[4*e + l/16][l%16] of its 16x16 block
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
@@ -371,7 +346,7 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
             }
 }
 
-// The same product where rows and bases allow 128-bit copies of A (and 32- or 128-bit copies of B, BX4): every
+// The same product for longer contractions, A in 128-bit copies, B in 32- or 128-bit ones (BX4): every
 // wavefront keeps a ring of NS stages of 16 k (32 rows of A, 32 columns of B, 4 KiB) in LDS of its own, copied
 // there directly (global_load_lds), so there is no barrier in the main loop and no load whose arrival stalls the
 // wavefront: a stage's fragments are read while the stage before is multiplied.  In LDS the 16-byte pieces of
@@ -379,7 +354,9 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_kernel(GemmArgs a)
 // 128-bit reads of A and the 32-bit reads of B free of bank conflicts.  k beyond Kd is cleared in the
 // registers, rows and columns beyond the matrix are clamped and not stored.
 // The fp64 matrix instruction issues at 75-78 TFLOP/s from one wavefront per SIMD on (70-72 with the conversions);
-// 8 x 128 x 784 x 1024: 46.3 us with guarded loads straight to registers, 35.9 us this way (four groups, two stages).
+// 8 x 128 x 784 x 1024: 46.3 us with guarded loads straight to registers, 35.9 us this way (four groups, two stages);
+// 5 x 50 x 333 x 500 and 5 x 50 x 500 x 100, few tiles: 28-32 us with 64x64 tiles and two groups from registers, 13.7 us with
+// 32x32 tiles and sixteen.
 template <int EPI, int KSPLIT, int WT, int NS, bool BX4>
 __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_lds_kernel(GemmArgs a)
 {
@@ -571,29 +548,20 @@ inline hipError_t launch_dgemm_nn(const GemmArgs &a, int batch, hipStream_t s)
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 63) / 64), (unsigned)batch);
     const bool few = (long long)grid.x * grid.y * grid.z < 200;
     // 128-bit copies of A: 16-byte rows in every batch entry, readable to a multiple of 4; of B as well, or 32-bit ones
-    const bool ax4 = sgemm_rows_ok(a.A, a.lda, a.sA, a.Kd);
+    if (!sgemm_rows_ok(a.A, a.lda, a.sA, a.Kd)) return hipErrorInvalidValue;
     const bool bx4 = ((a.ldb | a.sB | a.N) & 3) == 0 && (((unsigned long long)a.B) & 15) == 0;
-    if (ax4 && a.Kd >= 64) {
-        // Groups per workgroup: several only where the tiles leave compute units idle (us, one / two / four groups):
-        // 256 tiles, contraction 784 38 / 34.6 / 33.8, 256 15.9 / 15.3 / 15.7;  752 tiles 784 89 / 88 / 98, 128 21 / 23 / 30;
-        // 5292 tiles 784 559 / 569 / 666, 112 95 / 114 / 181 (guarded loads 125)
-        if (!few && (long long)grid.x * grid.y * grid.z >= 512) return launch_dgemm_lds<EPI, 1, 4, 2>(a, batch, bx4, s);
-        if (!few && a.Kd < 512) return launch_dgemm_lds<EPI, 2, 4, 2>(a, batch, bx4, s);
-        if (!few) return launch_dgemm_lds<EPI, 4, 4, 2>(a, batch, bx4, s);
-        if (a.Kd >= 256) return launch_dgemm_lds<EPI, 16, 1, 2>(a, batch, bx4, s);
-        return launch_dgemm_lds<EPI, 4, 1, 4>(a, batch, bx4, s);
-    }
-    if (few) {      // below that even 64x64 tiles with four groups leave the chip idle
-        dim3 small((unsigned)((a.N + 31) / 32), (unsigned)((a.M + 31) / 32), (unsigned)batch);
-        if (a.Kd >= 256) dgemm_nn_kernel<EPI, 16, 1><<<small, 1024, 0, s>>>(a);
-        else if (a.Kd >= 64) dgemm_nn_kernel<EPI, 4, 1><<<small, 256, 0, s>>>(a);
-        else dgemm_nn_kernel<EPI, 1, 1><<<small, 64, 0, s>>>(a);
+    if (a.Kd < 64) {
+        const dim3 small((unsigned)((a.N + 31) / 32), (unsigned)((a.M + 31) / 32), (unsigned)batch);
+        if (few) dgemm_nn_kernel<EPI, 1><<<small, 64, 0, s>>>(a);       // 64x64 tiles would leave the chip idle
+        else dgemm_nn_kernel<EPI, 4><<<grid, 256, 0, s>>>(a);
         return hipGetLastError();
     }
-    if (a.Kd >= 512) dgemm_nn_kernel<EPI, 4, 4><<<grid, 1024, 0, s>>>(a);
-    else if (a.Kd >= 128) dgemm_nn_kernel<EPI, 2, 4><<<grid, 512, 0, s>>>(a);
-    else dgemm_nn_kernel<EPI, 1, 4><<<grid, 256, 0, s>>>(a);
-    return hipGetLastError();
+    // Groups per workgroup: several only where the tiles leave compute units idle (us, one / two / four groups):
+    // 256 tiles, contraction 784 38 / 34.6 / 33.8, 256 15.9 / 15.3 / 15.7;  752 tiles 784 89 / 88 / 98, 128 21 / 23 / 30;
+    // 5292 tiles 784 559 / 569 / 666, 112 95 / 114 / 181 (guarded loads 125)
+    if (few) return a.Kd >= 256 ? launch_dgemm_lds<EPI, 16, 1, 2>(a, batch, bx4, s) : launch_dgemm_lds<EPI, 4, 1, 4>(a, batch, bx4, s);
+    if ((long long)grid.x * grid.y * grid.z >= 512) return launch_dgemm_lds<EPI, 1, 4, 2>(a, batch, bx4, s);
+    return a.Kd < 512 ? launch_dgemm_lds<EPI, 2, 4, 2>(a, batch, bx4, s) : launch_dgemm_lds<EPI, 4, 4, 2>(a, batch, bx4, s);
 }
 
 }  // namespace qsr
