@@ -136,7 +136,11 @@ typedef struct {
 int qsr_validate(const qsr_config *cfg, const char **why);
 
 /* Bytes of device workspace qsr_init needs for this configuration (activations, batches,
- * bf16 weight copies).  0 for the EXTERNAL and NOISE models.  QSR_EINVAL on a bad config. */
+ * bf16 weight copies).  0 for the EXTERNAL and NOISE models.  QSR_EINVAL on a bad config.
+ * LINREG with at most 16 workers that fit a workgroup each (1024 features x 32 samples, 256 x 128), local updates,
+ * no clipping and no averaged state: the inputs of 33 iterations, for qsr_run (67 MB at 16 x 1024
+ * features x 32 samples), also where a caller only takes single steps.  RESMLP with several blocks of few
+ * tokens: the operands of all blocks' weight gradients, at most 2 GiB. */
 int qsr_workspace_bytes(const qsr_config *cfg, size_t *bytes);
 
 /* The whole schedule of a configuration, computed on the host alone (no GPU): Eq. (2) with the

@@ -33,8 +33,9 @@ __device__ __forceinline__ float block_sum_256(float v, float *red)
 }
 
 // Workers that fit one workgroup of 16 wavefronts (linreg_run_kernel): up to 1024 features, four consecutive ones a lane and
-// so RUN_ROW wavefronts a sample, RUN_GROUPS samples side by side, each group of wavefronts on a run of at most
-// RUN_PER samples.  Their sums are taken in this order whatever kernel computes them, so that iterations give the same bits
+// so RunShape::row wavefronts a sample, `groups` samples side by side, each group of wavefronts on a run of at most
+// `per` samples.  linreg_run_kernel and, where the update goes with the gradient, the kernels of single iterations
+// (linreg_residual_row_kernel, linreg_grad_update_kernel) take their sums in this order, so that iterations give the same bits
 // one by one and together: four columns of a lane in order, the lanes of a wavefront pairwise (lane_sum),
 // the wavefronts of a sample in order; for the gradient the samples of a run in order, then the runs.
 // In the workspace their rows of X are padded to a multiple of 4, the padding zero.
@@ -405,11 +406,11 @@ __global__ __launch_bounds__(256) void linreg_grad_kernel(
     }
 }
 
-size_t linreg_workspace_bytes(const ModelDims &d)
+size_t linreg_workspace_bytes(const ModelDims &d, bool together)
 {
     size_t x = (size_t)d.K * (size_t)d.B * (size_t)row_stride(d) * sizeof(float);
     size_t r = (size_t)d.K * (size_t)d.B * sizeof(float);
-    size_t slots = linreg_can_run(d) ? (size_t)run_floats(d) * sizeof(float) : 0;
+    size_t slots = together ? (size_t)run_floats(d) * sizeof(float) : 0;
     return up256(x) + up256(r) + up256(slots);
 }
 

@@ -193,6 +193,14 @@ static ModelDims make_dims(const qsr_config *c)
     return d;
 }
 
+// Least squares: whether the gradient kernel takes the update of its columns, and whether iterations enqueued together go
+// through launches of several.
+static bool fuses_linreg(const qsr_config *c, const ModelDims &d)
+{
+    return c->model == QSR_MODEL_LINREG && linreg_can_fuse(d) && !c->parallel && !c->fuse_sync && !c->average_state && c->clip_norm <= 0.0;
+}
+static bool runs_linreg(const qsr_config *c, const ModelDims &d) { return fuses_linreg(c, d) && linreg_can_run(d); }
+
 extern "C" int qsr_workspace_bytes(const qsr_config *cfg, size_t *bytes)
 {
     if (!bytes) return QSR_EINVAL;
@@ -201,7 +209,7 @@ extern "C" int qsr_workspace_bytes(const qsr_config *cfg, size_t *bytes)
     if (rc != QSR_OK) return rc;
     ModelDims d = make_dims(cfg);
     switch (cfg->model) {
-    case QSR_MODEL_LINREG: *bytes = linreg_workspace_bytes(d); break;
+    case QSR_MODEL_LINREG: *bytes = linreg_workspace_bytes(d, runs_linreg(cfg, d)); break;
     case QSR_MODEL_MLP2: *bytes = mlp2_workspace_bytes(d); break;
     case QSR_MODEL_RESMLP: *bytes = resmlp_workspace_bytes(d); break;
     default: break;
@@ -451,9 +459,8 @@ extern "C" int qsr_init(const qsr_config *cfg, float *params, float *grads, floa
     // of them and is replayed from the copy it was recorded on.
     c->cur = 0; c->ticked = false; c->graph_cur = 0; c->replayed = false;
     c->dims = make_dims(cfg);
-    c->fuse_linreg = cfg->model == QSR_MODEL_LINREG && linreg_can_fuse(c->dims) && !cfg->parallel && !cfg->fuse_sync &&
-                     !cfg->average_state && cfg->clip_norm <= 0.0;
-    c->run_linreg = c->fuse_linreg && linreg_can_run(c->dims);
+    c->fuse_linreg = fuses_linreg(cfg, c->dims);
+    c->run_linreg = runs_linreg(cfg, c->dims);
     rc = init_impl(c, theta0);
     c->cfg.milestones = nullptr;
     c->cfg.eta_table = nullptr;

@@ -166,7 +166,8 @@ struct ModelDims {
     uint64_t seed;
 };
 
-size_t linreg_workspace_bytes(const ModelDims &d);
+// together: launch_linreg_run will be used, which keeps the inputs of LINREG_RUN_AHEAD iterations
+size_t linreg_workspace_bytes(const ModelDims &d, bool together);
 hipError_t launch_linreg_grad(const ModelDims &d, const float *theta, float *g, const float *wstar,
                               void *ws, float *loss, const DevState *st, hipStream_t s);
 

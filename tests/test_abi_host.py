@@ -193,3 +193,14 @@ def test_clip_factors_argument_checks():
     assert call(p, 2, 8, 1.0, C.c_void_p(4097), 64, p, p) == -1      # misaligned workspace
     assert call(p, 2, 8, 1.0, p, 8, p, p) == -4                       # workspace too small
     assert call(p, 2, 8, 1.0, p, 64, None, p) == -1
+
+
+@pytest.mark.parametrize("K,d,B", [(16, 1024, 32), (3, 1003, 17), (1, 1, 1)])
+def test_least_squares_workspace_holds_iterations_ahead_only_where_they_are_run_together(K, d, B):
+    up = lambda x: (x + 255) // 256 * 256
+    one = up(K * B * ((d + 3) // 4 * 4) * 4) + up(K * B * 4)      # X, rows padded, and the residuals
+    size = lambda **kw: qsr.workspace_bytes(make_config(workloads.get("lsq", K=K, d_in=d, B_loc=B, **kw))[0])
+    ahead = 32 * (K * B * ((d + 3) // 4 * 4) + K * ((B + 3) // 4 * 4)) * 4
+    assert one + ahead <= size() <= one + ahead + 2 * K * (d + 3) * 4 + 256
+    for kw in (dict(clip_norm=1.0), dict(average_state=True), dict(fuse_sync=True), dict(parallel=True, H_base=1, power=0)):
+        assert size(**kw) == one, kw
