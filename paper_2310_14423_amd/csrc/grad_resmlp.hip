@@ -29,6 +29,7 @@
 #include "attention.h"
 #include "gemm_bf16.h"
 #include "gemm_tn.h"
+#include "ln_rows.h"
 #include "philox.h"
 #include "qsr_internal.h"
 #include "wgrad_plan.h"
@@ -38,24 +39,6 @@ namespace qsr {
 static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr float LN_EPS = 1e-5f;
-
-// The LayerNorm backward pass: LPR lanes hold a token row of d, 64 / LPR rows lie side by side in a wavefront and R of those
-// are in flight at once.  Rows of a wavefront: enough that all wavefronts of the launch are resident at once (a
-// launch of 1.5 times the chip's wavefront slots runs as one full wave of workgroups and a half-empty one: 283 against 234 us
-// at 8 x 12608 rows of 768), resident wavefronts per compute unit following from the kernel's registers; and not
-// fewer than 4, since each wavefront leaves a row of partial sums for the parameter gradients (with at least 16, few
-// tokens left most of the chip idle: 27 us at 2 x 1040 rows of 192).
-constexpr int LN_ROWS_MIN = 4;
-static int ln_rows_per_wave(long long K, long long M, long long d)
-{
-    const int vpl = (int)((d + 255) / 256);
-    const long long slots = 256LL * (vpl <= 2 ? 20 : vpl == 3 ? 16 : 12);
-    const long long rows = (K * M + slots - 1) / slots;
-    return (int)(rows < LN_ROWS_MIN ? LN_ROWS_MIN : rows);
-}
-// Rows in flight: what the registers hold where latency is all (the least rows per wavefront), one or two where the
-// wavefronts beside it hide it.
-template <int VPL> constexpr int ln_bwd_rows(bool few) { return few ? (VPL <= 2 ? 4 : 2) : (VPL == 1 ? 2 : 1); }
 
 struct ResWs {
     // per-replica strides are the element counts of one replica's array
@@ -125,7 +108,7 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.W1b = (bf16_t *)take(w.sW, 2, K);  w.W1Tb = (bf16_t *)take(w.sW, 2, K);
     w.W2b = (bf16_t *)take(w.sW, 2, K);  w.W2Tb = (bf16_t *)take(w.sW, 2, K);
     w.WTt = (bf16_t *)take(blk_elems(d, d), 2, 1);
-    const long long rows_per_wave = ln_rows_per_wave(K, M, d), wave_rows = (M + rows_per_wave - 1) / rows_per_wave;
+    const long long wave_rows = ln_bwd_plan(K, M, d).waves;
     w.sPART = padded((w.defer ? sub : 1) * 2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
     w.sLPART = padded(4 * ((M + 63) / 64) * (d / 64) + 8, 4);   // a wavefront of a tile each: most for 64 x 64
      w.LPART = (float *)take(w.sLPART, 4, K);
@@ -327,12 +310,8 @@ __global__ __launch_bounds__(256) void sample_ln_kernel(float *__restrict__ X, l
     ln_row<VPL, LPR>(xv, theta + (long long)z * sTh + off_gamma, U + (long long)z * sU, MU + (long long)z * sStat + row,
                      RSTD + (long long)z * sStat + row, row, d);
 }
-// registers and lanes of a row of d
-#define LN_BY_WIDTH(d, F) do { if ((d) <= 64) F(1, 16); else if ((d) <= 128) F(1, 32); else if ((d) <= 256) F(1, 64); \
-                               else if ((d) <= 512) F(2, 64); else if ((d) <= 768) F(3, 64); else F(4, 64); } while (0)
 
-// Backward of LayerNorm plus the residual path, one wavefront per rows_per_wave token rows,
-// VPL float4 per lane:
+// Backward of LayerNorm plus the residual path, rows shared out as in ln_rows.h, VPL float4 per lane:
 //   dn = du*gamma; dx_out = dx_in + rstd*(dn - mean(dn) - xhat*mean(dn*xhat))
 // dx_out may be dx_in (each element is read and then written by the same lane): the launcher does
 // that, so the update of dx is one stream of addresses instead of two.
@@ -855,7 +834,8 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     ResWs w = carve(dm, ws, nullptr);
     const long long Md = (long long)M * d;            // a row-major [M][d] array (fp32 state and its relatives)
     const long long MdB = w.mdB, MdhB = w.mdhB;       // a blocked [M][d] / [M][dh] bf16 array
-    const int rows_per_wave = ln_rows_per_wave(K, M, d), wave_rows = (M + rows_per_wave - 1) / rows_per_wave;
+    const LnBwdPlan ln_plan = ln_bwd_plan(K, M, d);
+    const int wave_rows = (int)ln_plan.waves;
 
     AttnArgs att{};
     if (heads > 0) {
@@ -900,9 +880,9 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
             else if (du16) ln_bwd_kernel<VPL, LPR, R, NT, bf16_t, false><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
             else if (sub > 0) ln_bwd_kernel<VPL, LPR, R, NT, float, true><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); \
             else ln_bwd_kernel<VPL, LPR, R, NT, float, false><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); } while (0)
-#define LN_BWD(VPL, LPR) do { if (rows_per_wave == LN_ROWS_MIN) LN_BWD_R(VPL, LPR, ln_bwd_rows<VPL>(true), false); \
-                              else if (!stream) LN_BWD_R(VPL, LPR, ln_bwd_rows<VPL>(false), false); \
-                              else LN_BWD_R(VPL, LPR, ln_bwd_rows<VPL>(false), true); } while (0)
+#define LN_BWD(VPL, LPR) do { if (ln_plan.few) LN_BWD_R(VPL, LPR, ln_bwd_rows(VPL, true), false); \
+                              else if (!stream) LN_BWD_R(VPL, LPR, ln_bwd_rows(VPL, false), false); \
+                              else LN_BWD_R(VPL, LPR, ln_bwd_rows(VPL, false), true); } while (0)
         LN_BY_WIDTH(d, LN_BWD);
 #undef LN_BWD
 #undef LN_BWD_R
