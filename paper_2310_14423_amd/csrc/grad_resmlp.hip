@@ -113,8 +113,7 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.sLPART = padded(4 * ((M + 63) / 64) * (d / 64) + 8, 4);   // a wavefront of a tile each: most for 64 x 64
      w.LPART = (float *)take(w.sLPART, 4, K);
     w.ZERO = (bf16_t *)take(128, 2, 1);
-    const WgradSpace parts = wgrad_space(K, d, dh, heads > 0, w.defer ? L : 1);   // (all blocks: the LayerNorm parameters as well)
-    w.split_floats = M < WGRAD_SPLIT_TOKENS ? 0 : wgrad_part_floats((parts.products + parts.biases) / WGRAD_SPLIT + (w.defer ? K * 2 * sub * d : 0));
+    w.split_floats = wgrad_split_floats(K, M, d, dh, heads > 0, L, w.defer);
     w.SPLITK = (float *)take(w.split_floats, 4, 1);
     w.QKV = w.O = w.DO = w.DQKV = w.Wqb = w.WqTb = w.Wob = w.WoTb = nullptr; w.LSE = nullptr;
     w.sQKV = w.sO = w.sLSE = w.sDO = w.sDQKV = w.sWq = w.sWo = 0;
@@ -769,7 +768,7 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float *__restrict
 }
 
 // Weight gradients dW = A^T B with the bias gradients (column sums of B) as by-products, collected into one launch: of
-// n_l blocks whose gradients lie l_out apart, at `base` of a worker's gradient.  Widths are multiples of 64 and a block of
+// n_l blocks whose gradients lie l_out apart in a worker's gradient, the first one's at [lo, hi) of it.  Widths are multiples of 64 and a block of
 // zeros stands in for ragged token counts, so every weight gradient of this model qualifies.
 // Tile shape and token ranges: wgrad_plan.h.
 struct WgradLaunch {
@@ -784,15 +783,13 @@ struct WgradLaunch {
         p.off = off; p.off_colsum = off_b; p.M = M; p.N = N; p.blkA = blkA; p.blkB = blkB;
     }
 };
-static hipError_t launch_wgrad(WgradLaunch q, float *g, long long P, int tokens, const ResWs &w, int batch, hipStream_t s)
+static hipError_t launch_wgrad(WgradLaunch q, const WgradCover &cover, float *g, long long P, int tokens, const ResWs &w, int batch, hipStream_t s)
 {
     TnGroup &t = q.t;
     t.zeros = w.ZERO; t.K = tokens;
-    WgradLoad load;
-    for (int e = 0; e < t.n; ++e) load.add(t.p[e].M, t.p[e].N, (long long)t.n_l * batch);
-    load.stretches = q.hi2 > q.lo2 ? 2 : 1;
     const long long span = (t.n_l - 1) * t.l_out + (q.hi2 > q.hi ? q.hi2 : q.hi) - q.lo;
-    const WgradPlan plan = wgrad_plan_load(load, tokens, gemm_cu_count(), w.split_floats, batch * span);
+    if (span != cover.floats) return hipErrorInvalidValue;
+    const WgradPlan plan = wgrad_plan_load(cover.load, tokens, gemm_cu_count(), w.split_floats, batch * span);
     t.split = plan.split; t.k_chunk = plan.k_chunk;
     t.out = g + q.lo; t.s_out = P;
     if (plan.split > 1) {
@@ -997,9 +994,9 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         q.add(w.O + l * Md, false, d, w.sO, Md, w.DXb + kept * sub * Md, false, d, w.sDXb, kept * nsub * Md, d, d, lo + oWo, lo + obo);
         q.lo = lo + oWq; q.hi = lo + obo + d;
     };
-    auto one_block = [&](WgradLaunch &q) -> hipError_t {
+    auto one_block = [&](WgradLaunch &q, bool mlp) -> hipError_t {
         q.t.n_l = 1; q.t.l_out = per_block;
-        return launch_wgrad(q, g, P, M, w, K, s);
+        return launch_wgrad(q, wgrad_cover(mlp, false, K, d, dh, heads > 0, L), g, P, M, w, K, s);
     };
 
     // backward; DX (and its bf16 copy DXb) holds d loss / d (output of the sub-block at hand)
@@ -1017,7 +1014,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         if (!w.defer) {
             WgradLaunch q;
             wgrad_mlp(q, l);
-            TRY(one_block(q));
+            TRY(one_block(q, true));
         }
         // du = dh W1^T, then LayerNorm backward + residual
         {
@@ -1048,7 +1045,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
             if (!w.defer) {
                 WgradLaunch q;
                 wgrad_attn(q, l);
-                TRY(one_block(q));
+                TRY(one_block(q, false));
             }
             // du = dqkv Wqkv^T, then LayerNorm backward + residual
             {
@@ -1068,7 +1065,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
             q.lo2 = lo; q.hi2 = hi;
         }
         q.t.n_l = L; q.t.l_out = per_block;
-        TRY(launch_wgrad(q, g, P, M, w, K, s));
+        TRY(launch_wgrad(q, wgrad_cover(true, true, K, d, dh, heads > 0, L), g, P, M, w, K, s));
     }
     return hipSuccess;
 }

@@ -89,15 +89,6 @@ inline WgradPlan wgrad_plan_load(const WgradLoad &q, int tokens, int n_cu, long 
     }
     return best;
 }
-// one weight gradient alone, of all workers
-inline WgradPlan wgrad_plan(int M, int N, int tokens, int batch, int n_cu)
-{
-    WgradLoad q;
-    q.add(M, N, batch);
-    const long long span = (long long)batch * ((long long)M * N + N);
-    return wgrad_plan_load(q, tokens, n_cu, wgrad_part_floats(span), span);
-}
-
 // Whether the weight gradients of all blocks wait for one launch behind the backward pass (each block then keeps its
 // operands, at most 2 GiB) instead of two launches per block: where the estimates say that it is faster.  Decided for the
 // whole chip's 256 compute units, since it decides the workspace's layout.  The sums behind it take two workgroups along the
@@ -123,6 +114,31 @@ inline bool wgrad_defer(long long K, long long tokens, long long d, long long dh
         return wgrad_plan_load(q, (int)tokens, 256, wgrad_part_floats(span), span).us;
     };
     return us(all) < (double)n_blocks * (us(mlp) + (attention ? us(attn) : 0.0));
+}
+
+
+// The launches of a model of n_blocks: the MLP halves (mlp) or the attention halves of one block or, with `all`, both of every
+// block.  What they cover of a worker's gradient, from the first weight to the last bias, and their load.
+struct WgradCover { long long floats; WgradLoad load; };
+inline WgradCover wgrad_cover(bool mlp, bool all, long long K, long long d, long long dh, bool attention, long long n_blocks)
+{
+    const long long w_mlp = 2 * d * dh + d + dh, w_attn = 4 * d * d + 4 * d;
+    const long long per_block = 2 * d + w_mlp + (attention ? 2 * d + w_attn : 0), copies = all ? K * n_blocks : K;
+    WgradCover q{mlp ? w_mlp : w_attn, {}};
+    if (all) q.floats = n_blocks * per_block - 2 * d;            // (the first LayerNorm's parameters lie in front)
+    if (mlp || all) { q.load.add(d, dh, copies); q.load.add(dh, d, copies); }
+    if (attention && (!mlp || all)) { q.load.add(d, 3 * d, copies); q.load.add(d, d, copies); }
+    q.load.stretches = all && attention ? 2 : 1;
+    return q;
+}
+
+// Floats of workspace for the partial results of any launch of the model (deferred: wgrad_defer)
+inline long long wgrad_split_floats(long long K, long long tokens, long long d, long long dh, bool attention, long long n_blocks, bool deferred)
+{
+    if (tokens < WGRAD_SPLIT_TOKENS) return 0;
+    const WgradSpace parts = wgrad_space(K, d, dh, attention, deferred ? n_blocks : 1);      // (all blocks: the LayerNorm parameters as well)
+    const long long norms = deferred ? K * 2 * (attention ? 2 : 1) * n_blocks * d : 0;
+    return wgrad_part_floats((parts.products + parts.biases) / WGRAD_SPLIT + norms);
 }
 
 }  // namespace qsr

@@ -3,25 +3,27 @@ oracle with the bf16 tolerances of test_gpu_parity.py (which also says where the
 import numpy as np
 import pytest
 
+import wgrad_host
 import workloads
-from test_gpu_parity import _assert_groups_close
+from test_gpu_parity import VIT_TAIL, _assert_groups_close
 from util import gpu_ctx, oracle_run
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dims", [
-    # NT GEMMs with N = d_hidden on 128 x 128 tiles (192 of them, ragged rows), N = d_in on 64 x 64, two stages
+    # NT GEMMs with N = d_hidden on 128 x 128 tiles (192 of them, ragged rows, two stages), N = d_in on 64 x 64 with two groups
     dict(d_in=64, d_hidden=1024, n_blocks=1, B_loc=700, K=4),
     # on 128 x 256 tiles (1024 of them: the first number that takes them), the last row tile ragged
     dict(d_in=64, d_hidden=4096, n_blocks=1, B_loc=1021, K=8),
-    # N = 192: one and a half 128 x 128 tiles wide
+    # N = 192, on 64 x 64 tiles, and one and a half 128 x 128 tiles wide (768 of them: the first number that takes them)
     dict(d_in=192, d_hidden=64, n_blocks=1, B_loc=4000, K=8),
+    dict(d_in=192, d_hidden=64, n_blocks=1, B_loc=6100, K=8),
     # weight gradients on 128 x 128 tiles with two groups (128 of them), a short token count for both groups
     dict(d_in=64, d_hidden=2048, n_blocks=1, B_loc=300, K=8),
-    # reductions long enough to be cut into ranges: on 128 x 128 tiles, the last range ragged
+    # weight gradients on 64 x 64 tiles with four groups, cut into four ranges, the last one ragged
     dict(d_in=64, d_hidden=128, n_blocks=1, B_loc=4129, K=2),
-    # on 192 x 384 tiles (48 of them, rows and columns beyond the matrix)
+    # the same tiles, in one range; a hidden layer 72 times as wide as the model
     dict(d_in=64, d_hidden=4608, n_blocks=1, B_loc=4100, K=4),
     # a hidden layer narrower than the model: the second weight's gradient has more columns than any other's, cut into ranges
     dict(d_in=192, d_hidden=64, n_blocks=1, B_loc=4129, K=2),
@@ -43,3 +45,43 @@ def test_gradient_where_the_tile_shape_changes(dims):
         assert loss[k] == pytest.approx(wl, rel=1e-2)
         _assert_groups_close(w, g[k], want, "tiles k=%d" % k)
     ctx.close()
+
+
+# Weight-gradient launches in every tile shape with ranges, of one block and of all blocks, and of each half of several blocks
+# one after the other: the model, then what the plan makes of it, which the test holds it to.
+PLANS = [
+    (dict(d_in=192, d_hidden=1088, n_blocks=1, B_loc=3000, K=8), [("mlp", "192x384", 3)]),
+    (dict(d_in=64, d_hidden=1088, n_blocks=1, B_loc=3000, K=8), [("mlp", "128x128", 3)]),
+    (dict(d_in=128, d_hidden=576, n_blocks=1, B_loc=1500, K=8), [("mlp", "128x128 two groups", 3)]),
+    (dict(d_in=64, d_hidden=64, n_blocks=2, B_loc=1040, K=1), [("all", "64x64 four groups", 3)]),
+    (dict(d_in=320, d_hidden=320, n_blocks=2, B_loc=2050, K=8), [("all", "192x384", 4)]),
+    (dict(d_in=64, n_heads=1, seq_len=41, d_hidden=64, n_blocks=2, B_loc=2050, K=1), [("all", "64x64 four groups", 4)]),
+    (dict(d_in=128, n_heads=2, seq_len=41, d_hidden=64, n_blocks=2, B_loc=2050, K=7), [("all", "128x128 two groups", 3)]),
+    (dict(d_in=192, n_heads=3, seq_len=50, d_hidden=192, n_blocks=2, B_loc=3000, K=6), [("all", "192x384", 4)]),
+    (dict(d_in=64, d_hidden=576, n_blocks=2, B_loc=130, K=40), [("mlp", "128x128", 1)]),
+    (dict(d_in=192, n_heads=3, seq_len=50, d_hidden=64, n_blocks=2, B_loc=5000, K=16),
+     [("mlp", "64x64 four groups", 2), ("attention", "128x128 two groups", 1)]),
+]
+
+
+@pytest.mark.parametrize("dims,want", PLANS)
+def test_gradient_by_weight_gradient_plan(dims, want):
+    """Groups of a hundred thousand entries: one in 100 000 of the MLP's may pass the bound, as in test_gpu_parity.py."""
+    heads = "n_heads" in dims
+    model = (dims["K"], dims["B_loc"], dims["d_in"], dims["d_hidden"], dims["n_blocks"], int(heads))
+    assert [p[1:4] for p in wgrad_host.plans([model])] == want
+    w = workloads.get("vit" if heads else "resmlp", T=4, T_warm=1, **dims)
+    th0 = workloads.theta0(w)
+    th0 = (th0 + 0.02 * np.random.default_rng(3).standard_normal(th0.size)).astype(np.float32)
+    ctx = gpu_ctx(w, theta0=th0)
+    orc = oracle_run(w, theta0=th0)
+    ctx.local_step()
+    g, loss = ctx.grads.cpu().numpy(), ctx.read_loss()
+    ctx.close()
+    for k in {0, dims["K"] - 1}:
+        want_g, wl = orc.grad(k, 0, th0.astype(np.float64))
+        assert loss[k] == pytest.approx(wl, rel=1e-2)
+        if heads:
+            _assert_groups_close(w, g[k], want_g, "plan k=%d" % k, tail=VIT_TAIL, weights_only_tail=True)
+        else:
+            _assert_groups_close(w, g[k], want_g, "plan k=%d" % k, tail=(1e-5, 1.5))

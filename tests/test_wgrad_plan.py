@@ -1,47 +1,15 @@
-"""The token ranges a weight gradient of the block models is cut into, against the workspace carved for their
+"""The token ranges a launch of weight gradients of the block models is cut into, against the workspace carved for their
 partial results (both host arithmetic, csrc/wgrad_plan.h): whatever the widths, one never exceeds the other."""
+import itertools
 import os
 import shutil
 import subprocess
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+import wgrad_host
 
-DRIVER = r"""
-#include <cstdio>
-#include <initializer_list>
-#include "wgrad_plan.h"
-using namespace qsr;
-int main()
-{
-    long long cut = 0, wide = 0;
-    const int tokens[] = {1, 31, 4095, 4096, 4129, 5000, 12608, 1 << 20};
-    for (int K : {1, 2, 3, 5, 8, 16, 64})
-        for (int d = 64; d <= 1024; d += 64)
-            for (int dh : {64, 128, 192, 256, 512, 768, 1024, 2048, 3072, 4608})
-                for (int attention = 0; attention < 2; ++attention) {
-                    const WgradSpace sp = wgrad_space(K, d, dh, attention);
-                    const int mn[4][2] = {{d, dh}, {dh, d}, {d, 3 * d}, {d, d}};
-                    for (int i = 0; i < (attention ? 4 : 2); ++i)
-                        for (int t : tokens) {
-                            const long long M = mn[i][0], N = mn[i][1];
-                            const WgradPlan p = wgrad_plan(M, N, t, K, 256);
-                            if (p.split <= 1) continue;
-                            ++cut;
-                            wide += dh < d && !attention;
-                            const bool ranges = p.split <= WGRAD_SPLIT && p.k_chunk % 32 == 0 &&
-                                                (long long)p.k_chunk * p.split >= t && (long long)p.k_chunk * (p.split - 1) < t;
-                            if (!ranges || K * p.split * M * N > sp.products || K * p.split * N > sp.biases) {
-                                printf("K=%d d=%d dh=%d attention=%d %lldx%lld tokens=%d split=%d\n", K, d, dh, attention, M, N, t, p.split);
-                                return 1;
-                            }
-                        }
-                }
-    printf("%lld %lld\n", cut, wide);
-    return 0;
-}
-"""
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 MANY_BLOCKS = r"""
@@ -79,7 +47,19 @@ def test_no_launch_of_all_blocks_beyond_the_grid(tmp_path):
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
-def test_partial_results_fit_their_workspace(tmp_path):
-    out = _run(tmp_path, DRIVER)
-    cut, wide = map(int, out.stdout.split())
-    assert cut > 1000 and wide > 100          # the cut ones, and those of a model that is wider than its hidden layer
+def test_partial_results_fit_their_workspace():
+    models = itertools.product((1, 2, 3, 5, 8, 16, 64), (1, 31, 1023, 1024, 1040, 4096, 4129, 12608, 1 << 20), range(64, 1025, 64),
+                               (64, 128, 192, 512, 1024, 3072, 4608), (1, 2, 5, 12), (0, 1))
+    cut, wide = {}, 0
+    for (K, M, d, dh, L, attention), what, tile, ranges, chunk, need, room in wgrad_host.plans(models):
+        # room for four ranges of this launch, of 256 MiB of them, or of none where the model's largest takes more than that in two
+        largest = max(2 * d * dh + d + dh, attention * (4 * d * d + 4 * d)) if what != "all" else need // ranges // K
+        assert room >= min(4 * (need // ranges), 1 << 26) or M < 1024 or 2 * K * (largest + 2 * d) > 1 << 26, (K, M, d, dh, L, attention, what)
+        if ranges <= 1:
+            continue
+        cut[what, tile] = cut.get((what, tile), 0) + 1
+        wide += dh < d and not attention
+        assert ranges <= 4 and chunk % 32 == 0 and chunk * (ranges - 1) < M <= chunk * ranges, (K, M, d, dh, L, attention, what)
+        assert need <= room, (K, M, d, dh, L, attention, what, tile, ranges, need, room)
+    # every launch in every tile shape with ranges, and those of a model that is wider than its hidden layer
+    assert len(cut) == 12 and min(cut.values()) >= 20 and wide > 100, (cut, wide)
