@@ -1,4 +1,4 @@
-"""qsr_run: iterations replayed from a captured HIP graph give, bit for bit, what the same
+"""qsr_run: iterations replayed from a captured HIP graph, or enqueued together, give, bit for bit, what the same
 iterations enqueued one by one give.  Each case replays the graph several times, with iterations
 enqueued one by one, synchronizing reads and a restart between the replays."""
 import numpy as np
@@ -10,7 +10,8 @@ from util import assert_mirror_matches_device, gpu_ctx
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    "lsq": dict(name="lsq"),
+    "lsq": dict(name="lsq"),                                # enqueued together, without a graph
+    "lsq, replayed": dict(name="lsq", d_in=1100, B_loc=24, K=5, eta_max=0.1 / (1 + 1100 / 24), alpha=0.2 / (1 + 1100 / 24)),
     "mlp": dict(name="mlp", d_in=72, d_hidden=96, d_out=10, B_loc=48, K=3, T=150, milestones=(60, 100),
                 eta_max=0.1, alpha=0.04),
     "adamw": dict(name="flat60m", K=4, P=20003, T=150, alpha=0.004),

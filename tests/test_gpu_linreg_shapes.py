@@ -1,6 +1,7 @@
 """GPU: the least-squares iteration in two kernels (up to 16 workers and 32 or 64 samples per wavefront; more beyond) at the sizes where it can go
 wrong: feature counts that are no multiple of 4 or 64, few and many samples per wavefront, the largest number of
-workers of a workgroup; one by one and replayed, against each other bit for bit and against the oracle."""
+workers of a workgroup, workers that fit a workgroup and ones that do not; one by one and in one call (enqueued together or
+replayed), against each other bit for bit and against the oracle."""
 import numpy as np
 import pytest
 
@@ -15,8 +16,13 @@ pytestmark = pytest.mark.gpu
                                        (9, 66, 32, "sgdm"), (9, 66, 33, "adamw"), (8, 70, 128, "sgdm"), (8, 70, 129, "sgdm"),
                                        # rows of 4 to 7 columns: both ends of a row in one or two groups
                                        (2, 4, 5, "sgdm"), (2, 6, 7, "sgdm"), (3, 7, 70, "sgdm"), (2, 1, 6, "sgdm"), (2, 2, 7, "sgdm"),
-                                       # 1024 workgroups: 128-bit accesses inside such rows
-                                       (8, 6, 128, "sgdm"), (8, 67, 128, "sgdm"), (8, 3, 128, "sgdm"), (3, 4098, 5, "sgdm"), (3, 4097, 5, "sgdm")])
+                                       # many samples of such rows
+                                       (8, 6, 128, "sgdm"), (8, 67, 128, "sgdm"), (8, 3, 128, "sgdm"), (3, 4098, 5, "sgdm"), (3, 4097, 5, "sgdm"),
+                                       # no workers of one workgroup, 1024 workgroups: 128-bit accesses inside short rows
+                                       (17, 3, 64, "sgdm"), (17, 6, 64, "sgdm"), (17, 7, 64, "sgdm"),
+                                       # ... and all workers in the gradient's workgroups: one wavefront each with 32 samples, three with
+                                       # 34 and a shorter last run, eight with 64
+                                       (16, 1100, 32, "sgdm"), (5, 1027, 100, "adamw"), (2, 1030, 500, "sgdm")])
 def test_least_squares_shapes(K, d, B, opt):
     import torch
     kw = dict(mu=0.9, lam=1e-4) if opt == "sgdm" else dict(beta1=0.9, beta2=0.99, eps=1e-3, lam=0.01)

@@ -8,8 +8,37 @@ from util import assert_mirror_matches_device, assert_params_close, gpu_ctx, ora
 pytestmark = pytest.mark.gpu
 
 
+def _stream_beside_null():
+    """A stream whose kernels run while the null stream is busy (there are only a few hardware queues, and a stream may share
+    the null stream's)."""
+    import time
+    import torch
+    x = torch.zeros(16, device="cuda")
+    a = torch.ones(8192, 8192, device="cuda")
+    torch.mm(a, a)
+    torch.cuda.synchronize()
+    for _ in range(30):                           # on the null stream, 0.2 s or so
+        torch.mm(a, a)
+    null = torch.cuda.Event()
+    null.record()
+    found = None
+    for _ in range(16):
+        s, done = torch.cuda.Stream(), torch.cuda.Event()
+        with torch.cuda.stream(s):
+            x.add_(1.0)
+            done.record()
+        time.sleep(0.003)
+        if done.query() and not null.query():
+            found = s
+            break
+    torch.cuda.synchronize()
+    assert found is not None
+    return found
+
+
 @pytest.mark.parametrize("name,kw", [
-    ("lsq", dict(K=8, d_in=70, B_loc=128, T=60, eta_max=0.06, alpha=0.12)),      # iterations replayed from a graph
+    ("lsq", dict(K=8, d_in=70, B_loc=128, T=60, eta_max=0.06, alpha=0.12)),      # iterations enqueued together
+    ("lsq", dict(K=5, d_in=1100, B_loc=24, T=60, eta_max=0.002, alpha=0.004)),   # iterations replayed from a graph
     ("flat60m", dict(K=4, P=1 << 18, T=60, eta_max=1e-3, alpha=0.004)),          # enqueued one by one
 ])
 def test_context_made_while_the_null_stream_is_busy(name, kw):
@@ -19,6 +48,7 @@ def test_context_made_while_the_null_stream_is_busy(name, kw):
     orc = oracle_run(w)
     orc.step(60)
     gpu_ctx(w).close()                            # library and allocator warm: making the next one is quick
+    side = _stream_beside_null()
     a = torch.ones(8192, 8192, device="cuda")
     b = torch.empty_like(a)
     torch.mm(a, a, out=b)
@@ -27,7 +57,7 @@ def test_context_made_while_the_null_stream_is_busy(name, kw):
         torch.mm(a, a, out=b)
     busy = torch.cuda.Event()
     busy.record()
-    with torch.cuda.stream(torch.cuda.Stream()):
+    with torch.cuda.stream(side):
         ctx = gpu_ctx(w)
         ctx.run(20)
         ctx.stream.synchronize()
