@@ -180,10 +180,15 @@ int qsr_maybe_sync(qsr_ctx *ctx);
 
 /* n global iterations of Alg. 2, each a qsr_local_step followed by its qsr_maybe_sync, with the
  * same results bit for bit.  Every kernel reads t, h, H and the averaging decision from device
- * memory, so the launches of an iteration do not depend on t: on a stream other than the null
- * stream, with qsr_timing off and n large enough to pay for it, they are recorded once into a
- * HIP graph (kernel nodes only) that is replayed, which removes most of the launch cost of the
- * short iterations of small models; otherwise the iterations are enqueued one by one.
+ * memory, so the launches of an iteration do not depend on t.
+ *  - LINREG whose workers fit a workgroup each (see qsr_workspace_bytes): the iterations of a round
+ *    go in launches of up to 16 each, the averaging into the next round's, on any stream; rounds of
+ *    one iteration in two kernels where that is faster.
+ *  - Other small models: on a stream other than the null stream, with n large enough to pay for it,
+ *    the launches of several iterations are recorded once into a HIP graph (kernel nodes only) that is
+ *    replayed, which removes most of the launch cost of short iterations.
+ *  - Otherwise, and with qsr_timing on or the caller recording the stream, the iterations are
+ *    enqueued one by one.
  * Asynchronous.  n >= 0; QSR_ESTATE if a qsr_maybe_sync is pending or fewer than n iterations
  * are left before T. */
 int qsr_run(qsr_ctx *ctx, int64_t n);

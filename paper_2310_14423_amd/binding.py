@@ -300,8 +300,9 @@ class Context:
             _check(L.qsr_maybe_sync(ctx), "qsr_maybe_sync")
 
     def run(self, n):
-        """n iterations in one call; replays a captured HIP graph when the context was made on a
-        stream other than the null stream (`with torch.cuda.stream(s): Context(...)`)."""
+        """n iterations in one call, the results those of step(n).  Least squares whose workers fit a workgroup each: several
+        iterations a launch.  Other small models: replays of a captured HIP graph when the context was made on a stream
+        other than the null stream (`with torch.cuda.stream(s): Context(...)`)."""
         _check(lib().qsr_run(self._ctx, C.c_int64(n)), "qsr_run")
 
     # ---- the rest of the ABI

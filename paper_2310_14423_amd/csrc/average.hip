@@ -24,9 +24,6 @@ namespace qsr {
 constexpr int AVG_THREADS = 64;
 constexpr int AVG_KU = 16;
 
-// LDS-staged tile: W wavefronts, RUN x 64 float4 columns (RUN KiB contiguous per row and wavefront).
-// ALIGNED (here and below): P is known to be a multiple of 4.  With the test of P's remainder around every access
-// 32 x 2250000 took 127 us for 120, 32 x 3125000 176 for 169.
 // Which part of the columns a workgroup takes.  Rows of other lengths than multiples of 4 start anywhere in a 128-byte line, so
 // that neighbouring parts share a line of every row; workgroups go to the 8 XCDs round-robin by their id, and in order each of
 // those lines would be written half by one XCD's L2 and half by another's.  Where rows are not aligned each XCD takes 64
@@ -42,6 +39,9 @@ __device__ __forceinline__ long long column_part(long long P)
     return (P & 3) != 0 && first + TURN <= gridDim.x ? first + r % 8 * EACH + r / 8 : b;
 }
 
+// LDS-staged tile: W wavefronts, RUN x 64 float4 columns (RUN KiB contiguous per row and wavefront).
+// ALIGNED (here and below): P is known to be a multiple of 4.  With the test of P's remainder around every access
+// 32 x 2250000 took 127 us for 120, 32 x 3125000 176 for 169.
 template <int KMAX, int W, int RUN, bool ALIGNED>
 __device__ __forceinline__ void average_tile_body(float *__restrict__ buf, int K, long long P, float4 *avg_tile)
 {
@@ -224,18 +224,21 @@ static hipError_t launch_vec4(float *buf, int K, long long P, const DevState *st
 //                                                                     a whole AdamW iteration: 5990 with 2 x 2, 5880 with 8 x 1
 //     K > 32                                             64 x 750000  in registers 74 / 76  tile 8 x 1 80 / 82   two 61 / 92
 //                                                        48 x 4166664 in registers 377 / 382  tile 8 x 1 408 / 402
-//   other P, K <= 16                                     16 x 1500001 tile 2 x 1 34 / 44   one 42 / 48;  beyond 6e6 also where P is even
-//                                                        12 x 250002  two 5.7 / 7.7        tile 2 x 1 6.2 / 8.4 (fewer than 8 rows: too few
+//   other P (in the order of column_part), K <= 16       16 x 1500001 tile 2 x 1 31 / 42   one 30 / 41   in registers 30 / 41;  16 x 6000002
+//                                                        tile 2 x 1 140 / 150  one 151 / 159  in registers 144 / 152
+//                                                        12 x 250002  two 6.6 / 7.7        tile 2 x 1 6.7 / 8.3 (fewer than 8 rows: too few
 //                                                                     loads in flight a lane, 10 % behind in hot buffers)
-//     K > 16, few columns                                24 x 200002  two 7.9 / 10.9       in registers 9.2 / 12.1
-//                                                        40 x 250002  two 15.2 / 20.8      in registers 17.2 / 20.4
-//     K > 16                                             24 x 500001  in registers 17 / 23  one 22 / 26  tile 2 x 2 31 / 27
-//     K of 17 to 32 beyond 100e6                         24 x 6000002 tile 2 x 2 241 / 245  in registers 253 / 252
-//                                   below                24 x 3500002 tile 2 x 2 130 / 145  in registers 122 / 144
-//     K of 33 to 64 beyond 72e6                          64 x 2000001 tile 8 x 1 220 / 229  in registers 238 / 245
-//                                   below                48 x 1200001 tile 8 x 1 86 / 106   in registers 74 / 105
-//     K > 64                                             100 x 2000002 in registers 393 / 395  two 427 / 428
-//                                   odd beyond 150e6     70 - 120 workers, mean of 45 sizes: one column 3 % ahead
+//     K > 16, few columns                                24 x 200002  two 7.5 / 10.2       in registers 9.2 / 12.2
+//                                                        40 x 250002  two 13.4 / 20.0      in registers 16.1 / 20.1
+//     K > 16                                             24 x 500001  in registers 15 / 22  one 16 / 23  tile 2 x 2 26 / 31
+//     K of 17 to 32 beyond 100e6                         24 x 6000002 tile 2 x 2 235 / 234  in registers 240 / 237  tile 8 x 1 229 / 228
+//                                   below                24 x 3500002 tile 2 x 2 129 / 142  in registers 116 / 138
+//     K of 33 to 64 beyond 72e6                          64 x 2000001 tile 8 x 1 214 / 215  in registers 237 / 242
+//                                   below                48 x 1200001 tile 8 x 1 82 / 106   in registers 68 / 103
+//     K > 64                                             100 x 2000002 in registers 379 / 381  two 402 / 405
+//                                   odd beyond 150e6     72 x 2100001 one 267 / 267  in registers 277 / 278
+// Of 27 unaligned sizes with every kernel the rule's is within 5 % of the fastest, but 28 x 4000002: tile 2 x 2 201 / 201, tile 8 x 1
+// 183 / 183, in registers 184 / 185.
 // st != nullptr: the launch acts only on the step that completes a round (h + 1 == H in the copy of the scheduler
 // state that the iteration's kernels read)
 hipError_t launch_average_rows(float *buf, int K, long long P, const DevState *st, hipStream_t s)
