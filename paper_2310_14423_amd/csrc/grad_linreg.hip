@@ -279,7 +279,8 @@ __global__ __launch_bounds__(320) void linreg_residual_kernel(
 // with the averaging kernel's arithmetic.  KW = 1, a wavefront per run: iterations one by one of workers that
 // linreg_run_kernel takes too, in its runs either way.  st_next as in the update kernels.  Bound by latency, of the
 // instructions too (each launch fetches them anew: 16 samples unrolled, or the next eight requested ahead in code of their
-// own, 0.5 to 1 us slower).  4 x 1024 x 32, KW = 1: 3.4 us (4.2 with KW = K).
+// own, 0.5 to 1 us slower), so that wavefronts of one run (SEVERAL false) have no ends of runs to look for: 16 x 1100 x 32 11.2 us an
+// iteration, 12.3 with them.  4 x 1024 x 32, KW = 1: 3.4 us (4.2 with KW = K).
 struct LinregStep {
     float *theta, *g, *s0, *s1;          // s1: AdamW
     const StepScalars *sc;
@@ -289,13 +290,13 @@ struct LinregGradStep {
     const float *X, *r;
     LinregStep p;
     float *loss;
-    int K, runs, each, per, B, average;
+    int K, runs, each, per, B, average, apart;   // apart: the scheduler's step has a workgroup of its own
     long long d, ldx;
     const DevState *st;
     DevState *st_next;
     SchedParams sp;
 };
-template <bool ADAMW>
+template <bool ADAMW, bool SEVERAL>
 __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(LinregGradStep a)
 {
     const LinregStep &p = a.p;
@@ -308,8 +309,12 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(LinregGradStep
     const int k = blockIdx.y * blockDim.z + kw;
     const long long j = (long long)blockIdx.x * 64 + lane;
     const bool in = j < d;
+    if ((long long)blockIdx.x * 64 >= d) {               // a workgroup behind the columns
+        if (blockIdx.y == 0 && lane == 0 && s == 0 && kw == 0) tick_into(st, a.st_next, a.sp);
+        return;
+    }
     // the last thread of the last workgroup, which has no column of its own where the others are busiest
-    if (a.st_next != nullptr && blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && lane == 63 && s == (int)blockDim.y - 1 &&
+    if (a.st_next != nullptr && !a.apart && blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && lane == 63 && s == (int)blockDim.y - 1 &&
         kw == (int)blockDim.z - 1)
         tick_into(st, a.st_next, a.sp);
     const bool sync = a.average != 0 && st->h + 1 == st->H;
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(LinregGradStep
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             acc = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(rv), i - i0 + u)), xv[u], acc);
-            if (i + u + 1 == end && end < i1) { (*to++)[lane] = acc; acc = 0.f; end += per; }
+            if (SEVERAL && i + u + 1 == end && end < i1) { (*to++)[lane] = acc; acc = 0.f; end += per; }
         }
     }
     if (i0 < i1) (*to)[lane] = acc;
@@ -487,9 +492,9 @@ static StepShape step_shape(const ModelDims &d, bool average)
 
 // A round of one iteration in two kernels takes longer with the samples of a wavefront, as linreg_run_kernel with the samples
 // and columns of a workgroup.  us a round, two kernels / linreg_run_kernel (two replayed kernels with samples cut into 16 / K runs):
-//   1 x 117 x 38 6.9 / 7.2 (7.6)    4 x 1024 x 32 7.6 / 9.6 (7.6)   16 x 1024 x 8 8.3 / 9.2 (8.0)    3 x 512 x 64 7.9 / 9.4 (8.1)
-//   8 x 256 x 128 16.4 / 10.1 (14.5)   7 x 64 x 128 15.9 / 8.5 (13.8)   16 x 1024 x 32 12.3 / 11.1 (11.7)   6 x 668 x 28 9.0 / 9.4 (8.2)
-// Over 245 random sizes the choice is within 0.5 % of the better one on average (10.5 % at most), and 9 % faster than the
+//   1 x 117 x 38 6.5 / 7.2 (7.6)    4 x 1024 x 32 7.1 / 9.7 (7.6)   16 x 1024 x 8 8.1 / 9.1 (7.9)    3 x 512 x 64 8.0 / 9.5 (8.2)
+//   8 x 256 x 128 16.1 / 10.2 (14.5)   7 x 64 x 128 15.3 / 8.5 (13.5)   16 x 1024 x 32 12.3 / 11.1 (11.7)   6 x 668 x 28 9.0 / 9.3 (8.1)
+// Over 245 random sizes the choice is within 0.6 % of the better one on average (12.5 % at most), and 9 % faster than the
 // replayed kernels; slower than those where five runs go to four to six workers' wavefronts unevenly: 4 x 668 x 25 8.5 (7.6).
 bool linreg_single_rounds(const ModelDims &d)
 {
@@ -513,10 +518,15 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
     if (!linreg_can_fuse(d)) return hipErrorInvalidValue;
     const StepShape q = step_shape(d, average);
     if (q.each * q.per > 64) return hipErrorInvalidValue;        // a wavefront's residuals lie one a lane
+    // The scheduler's step in a workgroup of its own: off the critical path, a workgroup more to start.  us an iteration at rounds
+    // of one, apart / in the last wavefront: 1 x 4096 x 128 8.7 / 9.1, 12 x 2048 x 10 8.0 / 8.3, 5 x 1027 x 100 12.7 / 12.6, 3 x 1003 x 17
+    // (single iterations) 7.2 / 6.9
+    const bool apart = st_next != nullptr && d.d_in > 1536;
     const LinregGradStep a{(const float *)ws, linreg_r(d, ws), LinregStep{theta, g, s0, s1, sc, c1, c2, eps}, loss, d.K, q.runs, q.each,
-                           q.per, (int)d.B, average ? 1 : 0, d.d_in, row_stride(d), st, st_next, sp};
-    const dim3 grid((unsigned)((d.d_in + 63) / 64), (unsigned)(d.K / q.KW)), block(64, (unsigned)q.S, (unsigned)q.KW);
-    auto kern = s1 ? linreg_grad_update_kernel<true> : linreg_grad_update_kernel<false>;
+                           q.per, (int)d.B, average ? 1 : 0, apart ? 1 : 0, d.d_in, row_stride(d), st, st_next, sp};
+    const dim3 grid((unsigned)((d.d_in + 63) / 64 + (apart ? 1 : 0)), (unsigned)(d.K / q.KW)), block(64, (unsigned)q.S, (unsigned)q.KW);
+    auto kern = q.each > 1 ? (s1 ? linreg_grad_update_kernel<true, true> : linreg_grad_update_kernel<false, true>)
+                           : (s1 ? linreg_grad_update_kernel<true, false> : linreg_grad_update_kernel<false, false>);
     kern<<<grid, block, (size_t)q.KW * q.runs * 64 * sizeof(float), s>>>(a);
     return hipGetLastError();
 }
