@@ -564,6 +564,7 @@ extern "C" int qsr_local_step(qsr_ctx *c)
     const bool sync_now = mirror_sync_now(c);
     const bool fused = cfg.fuse_sync != 0;
     const bool shared_g = cfg.parallel != 0;            // all rows of the gradient are the mean now
+    const bool own_g = cfg.model != QSR_MODEL_EXTERNAL;
     const DevState *st = st_cur(c);                     // what every kernel of this iteration reads
     // A caller who records iterations into a graph of their own may replay any number of them: those advance the
     // scheduler in place (qsr_maybe_sync), since a replay always starts from the same copy.
@@ -596,11 +597,11 @@ extern "C" int qsr_local_step(qsr_ctx *c)
         else if (cfg.opt == QSR_OPT_SGDM)
             HIP_TRY(launch_update_sgdm(c->params, c->grads, c->state0, cfg.K, cfg.P, st, c->d_scal,
                                        (float)cfg.momentum, (float)cfg.weight_decay, fused, c->d_clip_coef,
-                                       shared_g, c->stream, st_next, &sp));
+                                       shared_g, own_g, c->stream, st_next, &sp));
         else
             HIP_TRY(launch_update_adamw(c->params, c->grads, c->state0, c->state1, cfg.K, cfg.P, st,
                                         c->d_scal, (float)(1.0 - cfg.beta1), (float)(1.0 - cfg.beta2),
-                                        (float)cfg.eps, fused, c->d_clip_coef, shared_g, c->stream, st_next, &sp));
+                                        (float)cfg.eps, fused, c->d_clip_coef, shared_g, own_g, c->stream, st_next, &sp));
         int rc = br.close(c->t_host);
         if (rc != QSR_OK) return rc;
         if (st_next) { c->cur ^= 1; c->ticked = true; } // the advanced state is in the other copy now

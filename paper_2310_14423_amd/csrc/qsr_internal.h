@@ -105,16 +105,17 @@ hipError_t launch_sched_advance(DevState *st, SchedParams sp, hipStream_t s);
 // fused_sync: leave the step that completes a round to launch_update_*_sync.
 // row_coef: K clipping factors the gradient rows are multiplied by as they are read, or nullptr.
 // shared_g: the K gradient rows are known to be equal (Parallel OPT).
+// own_gradient: a kernel of this library has just written g (else a caller's backward pass).
 // st_next != nullptr (with sp): the kernel also takes the scheduler's end-of-iteration step: the advanced
 // state goes to *st_next, a second copy that no kernel of this iteration reads (an averaging kernel behind
 // it decides on the copy the iteration began with).
 hipError_t launch_update_sgdm(float *theta, float *g, float *buf, int K, long long P,
                               const DevState *st, const StepScalars *sc, float mu, float lambda,
-                              bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s,
+                              bool fused_sync, const float *row_coef, bool shared_g, bool own_gradient, hipStream_t s,
                               DevState *st_next = nullptr, const SchedParams *sp = nullptr);
 hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K, long long P,
                                const DevState *st, const StepScalars *sc, float c1, float c2,
-                               float eps, bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s,
+                               float eps, bool fused_sync, const float *row_coef, bool shared_g, bool own_gradient, hipStream_t s,
                                DevState *st_next = nullptr, const SchedParams *sp = nullptr);
 // the same updates with the optimizer-only workloads' gradient g = sigma * N(0,1) drawn inside the
 // kernel (and written to g if store_g); P must be a multiple of 4

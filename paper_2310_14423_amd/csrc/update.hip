@@ -423,17 +423,27 @@ hipError_t launch_update_sgdm_sync(float *theta, const float *g, float *buf, int
 // 16 x 1000000 80 / 93, 8 x 300000 22.3 / 21.6.
 static bool clip_keeps(int K, long long P) { return (long long)K * P <= 16000000; }
 
-// The plain update of buffers that the caches hold together with what produces its gradient and reads its parameters: one
-// iteration with a gradient written before each (us, plain / streaming; three problems in turn): AdamW 8 x 814090 37.5 / 40.4
-// (41.3 / 42.4), 4 x 2000000 44.8 / 47.2 (51.5 / 50.0), 8 x 2000000 85 / 95 (98 / 94), 4 x 8000001 204 / 179; SGD 8 x 814090
-// 29.2 / 29.2 (30.9 / 32.9), 4 x 2000000 36.5 / 35.9 (38.9 / 38.3); four perceptron iterations of 8 x 814090 427 / 437.
-static bool update_keeps(int K, long long P) { return (long long)K * P <= 7000000; }
+// The plain update of buffers that the caches hold together with what produces its gradient and reads its parameters.
+// Behind this library's own gradient kernels (own): up to 7e6 elements; over 140 random perceptrons an iteration takes 0.98 of the
+// time (0.95 to 1.00), over 33 block models 0.99.  Behind a caller's backward pass, of which nothing is known: arrays of 24 to
+// 96 MB, smaller than the last-level cache with some more and larger than half of what the second-level caches hold together;
+// below and above, plain accesses are up to 14 % slower as soon as several problems take turns.  us an iteration, plain /
+// streaming, a gradient written before each: one problem, three in turn:
+//   AdamW  1.0e6 elements 10.5 / 10.2   11.4 / 10.5        SGD  1.4e6  11.0 / 10.6   11.5 / 10.5
+//          1.6e6          12.4 / 12.9   14.4 / 15.1             2.1e6  13.2 / 12.9   14.2 / 14.7
+//          3.2e6          22.8 / 21.5   22.3 / 24.4             4.0e6  22.2 / 20.4   21.1 / 22.9
+//          5.0e6          31.1 / 32.3   30.8 / 34.3             6.0e6  29.3 / 29.1   28.9 / 32.0
+//          6.9e6          40.8 / 41.5   46.4 / 45.4 (four in turn 46.7 / 43.7)
+static bool update_keeps(long long n, int arrays, bool own)
+{
+    return n <= 7000000 && (own || (n * arrays * 4 >= 24000000 && n * arrays * 4 <= 96000000));
+}
 
 // row_coef != nullptr: clipped update.  shared_g: all rows of g are the same (rows of whole float4 only:
 // anything else reads its own row, with the same result).
 hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K, long long P,
                                const DevState *st, const StepScalars *sc, float c1, float c2,
-                               float eps, bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s,
+                               float eps, bool fused_sync, const float *row_coef, bool shared_g, bool own_gradient, hipStream_t s,
                                DevState *st_next, const SchedParams *sp)
 {
     const SchedParams spv = sp ? *sp : SchedParams{};
@@ -451,7 +461,7 @@ hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K
     else if (row_coef != nullptr)
         update_adamw_kernel<true, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, row_coef, rm, none, st_next, spv);
-    else if (update_keeps(K, P))
+    else if (update_keeps(n, 4, own_gradient))
         update_adamw_kernel<false, false, false, true><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, m4, v4, n4, n, st, sc, c1, c2, eps, fs, nullptr, rm, none, st_next, spv);
     else
@@ -462,8 +472,8 @@ hipError_t launch_update_adamw(float *theta, float *g, float *m, float *v, int K
 
 hipError_t launch_update_sgdm(float *theta, float *g, float *buf, int K, long long P,
                               const DevState *st, const StepScalars *sc, float mu, float lambda,
-                              bool fused_sync, const float *row_coef, bool shared_g, hipStream_t s, DevState *st_next,
-                              const SchedParams *sp)
+                              bool fused_sync, const float *row_coef, bool shared_g, bool own_gradient, hipStream_t s,
+                              DevState *st_next, const SchedParams *sp)
 {
     const SchedParams spv = sp ? *sp : SchedParams{};
     const int fs = fused_sync ? 1 : 0;
@@ -480,7 +490,7 @@ hipError_t launch_update_sgdm(float *theta, float *g, float *buf, int K, long lo
     else if (row_coef != nullptr)
         update_sgdm_kernel<true, false, false><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, b4, n4, n, st, sc, mu, lambda, fs, row_coef, rm, none, st_next, spv);
-    else if (update_keeps(K, P))
+    else if (update_keeps(n, 3, own_gradient))
         update_sgdm_kernel<false, false, false, true><<<update_grid(n4), UPD_THREADS, 0, s>>>(
             th4, g4, b4, n4, n, st, sc, mu, lambda, fs, nullptr, rm, none, st_next, spv);
     else

@@ -116,3 +116,28 @@ def test_clipped_update_beyond_what_the_caches_hold(opt, P):
     assert opt == "sgdm" or torch.equal(few.state1, many.state1[:4])
     assert not torch.equal(few.params, start[:4])
     few.close(); many.close()
+
+
+@pytest.mark.parametrize("opt,lo,hi", [("adamw", 1499999, 1500000), ("adamw", 6000000, 6000001), ("sgdm", 1999999, 2000001), ("sgdm", 6999999, 7000002)])
+def test_update_of_a_callers_gradient_where_its_accesses_change(opt, lo, hi):
+    """One row on either side of the sizes that the update streams past the caches: the same entries, the same bits, and all rows
+    of a longer buffer cut the same way."""
+    import torch
+    out = []
+    for K, P in ((1, lo), (1, hi), (3, (hi + 2) // 3)):
+        w = workloads.get("flat60m", K=K, P=P, T=40, opt=opt, model="external", mu=0.9, beta1=0.9, beta2=0.99, eps=1e-6, lam=0.01, H_base=9,
+                          alpha=0.0, power=0)
+        n = 3 * ((hi + 2) // 3)
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        theta, g = torch.randn(n, generator=gen, device="cuda"), torch.randn(3, n, generator=gen, device="cuda")
+        ctx = gpu_ctx(w, theta0=np.zeros(P, dtype=np.float32))
+        flat = lambda x: x.reshape(-1)
+        flat(ctx.params).copy_(theta[:K * P])
+        for i in range(3):
+            flat(ctx.grads).copy_(g[i][:K * P])
+            ctx.step(1)
+        out.append([flat(x).clone() for x in (ctx.params, ctx.state0) + ((ctx.state1,) if opt == "adamw" else ())])
+        ctx.close()
+    for other in out[1:]:
+        assert all(torch.equal(a[:lo], b[:lo]) for a, b in zip(out[0], other))
+    assert not torch.equal(out[0][0], theta[:lo])
