@@ -15,10 +15,11 @@ constexpr int ln_bwd_rows(int vpl, bool few) { return few ? (vpl <= 2 ? 4 : 2) :
 // The wavefronts of a worker take steps of `step` rows (64 / LPR side by side, ln_bwd_rows of each in flight) in turn.
 // Few enough of them that all wavefronts of the launch are resident at once (a launch of 1.5 times the chip's wavefront slots
 // runs as one full wave of workgroups and a half-empty one: 283 against 234 us at 8 x 12608 rows of 768), resident wavefronts
-// per compute unit following from the kernel's registers; and a whole step for each, since each leaves a row of partial
-// sums for the parameter gradients, a wavefront without rows one of zeros.  (At least four rows each whatever the step, three
-// of four wavefronts had none with rows of 64: 4 x 4000 tokens of 128, three blocks with attention, 404 against 395 us an
-// iteration.  At least 16, few tokens left most of the chip idle: 27 us a pass at 2 x 1040 rows of 192.)
+// per compute unit following from the kernel's registers; not fewer than four rows each, since each leaves a row of partial
+// sums for the parameter gradients (two each: 7 x 852 tokens of 704, three blocks with attention, 1374 against 1357 us an
+// iteration; at least 16, few tokens left most of the chip idle: 27 us a pass at 2 x 1040 rows of 192); and not fewer
+// than a step, since a wavefront without rows leaves a row of zeros (with rows of 64, three of four did; 4 x 4000
+// tokens of 128, three blocks with attention, 404 against 395 us).
 struct LnBwdPlan { bool few; int step; long long waves; };
 inline LnBwdPlan ln_bwd_plan(long long K, long long M, long long d)
 {
@@ -28,6 +29,7 @@ inline LnBwdPlan ln_bwd_plan(long long K, long long M, long long d)
     LnBwdPlan q;
     q.few = rows <= 4;
     q.step = side * ln_bwd_rows(vpl, q.few);
+    if (rows < 4) rows = 4;
     if (rows < q.step) rows = q.step;
     q.waves = (M + rows - 1) / rows;
     return q;

@@ -1,5 +1,5 @@
-"""The rows of the LayerNorm backward pass (csrc/ln_rows.h): every row belongs to a step, every wavefront has one, and the
-wavefronts of a launch stay within what the chip holds."""
+"""The rows of the LayerNorm backward pass (csrc/ln_rows.h): every row belongs to a step, every wavefront has one and four rows at
+least, and the wavefronts of a launch stay within what the chip holds."""
 import os
 import shutil
 import subprocess
@@ -35,6 +35,6 @@ def test_no_wavefront_without_rows(tmp_path):
     assert len(rows) == 4 * 9 * 16
     for K, M, d, step, waves in rows:
         steps = -(-M // step)
-        assert 1 <= waves <= steps, (K, M, d)
+        assert 1 <= waves <= steps and waves <= -(-M // 4), (K, M, d)
         assert K * waves <= K + 256 * 20, (K, M, d)
         assert step % (4 if d <= 64 else 2 if d <= 128 else 1) == 0
