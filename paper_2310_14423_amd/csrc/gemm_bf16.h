@@ -2,10 +2,13 @@
 //
 //     C[z][m][n] = sum_k A[z][m][k] * B[z][n][k]        (both operands K-contiguous)
 //
-// which is the operand order the MFMA instruction wants: v_mfma_f32_32x32x16_bf16 takes, per
+// which is the operand order the MFMA instruction wants: v_mfma_f32_16x16x32_bf16 takes, per
 // lane, 8 consecutive k of one row of A and 8 consecutive k of one column of B.  Lane layout
-// (checked on the hardware): lane l holds A[row l%32][k (l/32)*8 .. +7], B[k (l/32)*8 .. +7]
-// [col l%32], and accumulator element i is D[(i/4)*8 + (l/32)*4 + i%4][l%32].
+// (checked on the hardware): lane l holds A[row l%16][k (l/16)*8 .. +7], B[k (l/16)*8 .. +7]
+// [col l%16], and accumulator element i is D[(l/16)*4 + i][l%16].
+// The chip runs these products at its power limit, and this instruction takes less of it than
+// v_mfma_f32_32x32x16_bf16, which moves twice the accumulators through the registers for half the
+// operands: bare on random operands 2120 TFLOP/s against 1830 on MI355X (2440 and 2480 on zeros).
 //
 // Tiling: a workgroup of WM x WN wavefronts computes a BM x BN tile; K is walked in stages of
 // 32 through a ring of NS LDS buffers.  The stages are copied global -> LDS directly
@@ -13,16 +16,17 @@
 // requested again as soon as its stage has been read); a wavefront waits for its share of the next stage only (a
 // counted vmcnt, not 0).  That
 // instruction writes 64 lanes x 16 B to 1 KiB of consecutive LDS, so rows are stored unpadded
-// (4 pieces of 16 B) and bank conflicts are avoided by an XOR swizzle instead: slot s of row r
-// holds piece s ^ ((r >> 2) & 3), which spreads the 128-bit fragment reads of 16 consecutive rows
-// over all 64 banks (measured: no conflicts).
+// (4 pieces of 16 B) and bank conflicts are avoided by exchanging the halves of every second group of 8 rows: slot s of row r
+// holds piece s ^ ((r >> 3) & 1) * 2.  A 128-bit read takes the lanes of a half wavefront in two turns, 0-3, 12-15, 20-27 and
+// 4-11, 16-19, 28-31, and so covers all 64 banks in each (measured: no conflicts; with s ^ ((r >> 2) & 3), which suits
+// fragments of 32 rows x 16 k, every read conflicts).
 // M and N may be ragged: out-of-range rows are clamped to the last valid row on load (they
 // only feed accumulator rows that are never stored) and the epilogue is bounds-checked.
 // K must be a multiple of 32, N of 64, and lda a multiple of 8 elements (16-byte rows).
 //
 // The two operands are handed to the instruction in swapped roles (the B rows as its "A", the A
 // rows as its "B"), so that it produces the transposed tile: lane l then owns, for token row
-// m = l%32, four consecutive output columns n, which is what the epilogue's LDS staging writes
+// m = l%16, four consecutive output columns n, which is what the epilogue's LDS staging writes
 // with 128-bit stores (see epilogue_via_lds).
 //
 // Operand layout.  Besides plain row-major, a bf16 matrix [R][C] (C a multiple of 32) can be stored
@@ -55,6 +59,7 @@ __host__ __device__ __forceinline__ long long blk_elems(long long R, long long C
 typedef __bf16 bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 struct GemmNT {
@@ -64,12 +69,12 @@ struct GemmNT {
     long long sA, sB;      // per-batch strides (elements)
 };
 
-// Epilogue.  The MFMA leaves lane l with 4 consecutive columns of row l%32, i.e. one store
-// instruction would touch 32 different rows.  Each wavefront therefore passes its tile, 32 rows
+// Epilogue.  The MFMA leaves lane l with 4 consecutive columns of row l%16, i.e. one store
+// instruction would touch 16 different rows.  Each wavefront therefore passes its tile, 32 rows
 // at a time, through a private LDS area (the ring is free by then) and re-reads it so that
 // consecutive lanes hold one row's consecutive columns: whole 128- or 256-byte row segments per
-// global instruction.  Rows are padded by 16 B: conflict-free both ways.  A lane takes VEC = 8
-// consecutive columns where the outputs are bf16 (16-byte accesses) and 4 where they are fp32.
+// global instruction.  A lane takes VEC = 8 consecutive columns where the outputs are bf16 (16-byte accesses) and 4 where
+// they are fp32.  StagedTile says where a row's columns lie, so that there are no bank conflicts either way.
 //
 // Addresses: an element of a lane is a wavefront-uniform base (worker, tile, row within the tile:
 // scalar registers) plus a 32-bit lane offset that is the same for all rows of the tile, so a row
@@ -112,15 +117,32 @@ struct EpiPtr {
     }
 };
 
+// 32 rows of W floats in LDS.  The 16-byte units of rows of 32 or 64 are permuted by the row, which is conflict-free in the
+// turns that 128-bit accesses are made in (see the top; with rows padded by 16 bytes instead, a quarter of the LDS cycles of
+// the GELU kernel were conflicts); rows of other widths are padded.
+template <int W>
+struct StagedTile {
+    static constexpr bool PERMUTED = W == 32 || W == 64;
+    static constexpr int LD = PERMUTED ? W : W + 4, FLOATS = 32 * LD;
+    // of the unit of column c (a multiple of 4)
+    static __device__ __forceinline__ int at(int row, int c)
+    {
+        if (!PERMUTED) return row * LD + c;
+        return row * LD + ((c >> 2) ^ (W == 64 ? row & 15 : (row >> 1) & 7)) * 4;
+    }
+};
+
 // `compute` leaves the tile in acc and says whether this wavefront stores it.  A wavefront with one block of 32 x 32 asks for
 // what its epilogue reads ahead of that: with few tiles in flight nothing else hides the latency.
+// TM x TN blocks of 16 x 16.
 template <int TM, int TN, class Epi, class Compute>
-__device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *stage, int lane,
+__device__ __forceinline__ void epilogue_via_lds(f32x4 (&acc)[TM][TN], float *stage, int lane,
                                                  int row0, int col0, int M, int N, int z, int unit, const Epi &epi, Compute compute)
 {
-    constexpr bool EARLY = TM * TN == 1;
+    constexpr bool EARLY = TM * TN == 4;
     if constexpr (!EARLY) if (!compute()) return;
-    constexpr int W = TN * 32, LD = W + 4;             // floats per staged row
+    constexpr int W = TN * 16;                         // floats per staged row
+    typedef StagedTile<W> Staged;
     constexpr int VEC = Epi::VEC;
     constexpr int LPR = W / VEC;                       // lanes per row on the way out
     constexpr int RPI = 64 / LPR;                      // rows per read instruction
@@ -148,20 +170,18 @@ __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *s
         // the block in between: vector memory operations complete in order, so a wait for loads issued
         // after a block's stores would also wait for those stores.
         if (i == 0 && !EARLY) request(0, 0);
-        if (i + 1 < TM) request(i + 1, (i + 1) & 1);
+        if (i + 1 < TM / 2) request(i + 1, (i + 1) & 1);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int eg = 0; eg < 4; ++eg)
-                *(float4 *)(stage + (lane & 31) * LD + j * 32 + eg * 8 + (lane >> 5) * 4) =
-                    make_float4(acc[i][j][eg * 4 + 0], acc[i][j][eg * 4 + 1], acc[i][j][eg * 4 + 2],
-                                acc[i][j][eg * 4 + 3]);
+            for (int h = 0; h < 2; ++h)
+                *(f32x4 *)(stage + Staged::at(h * 16 + (lane & 15), j * 16 + (lane >> 4) * 4)) = acc[2 * i + h][j];
         __builtin_amdgcn_wave_barrier();               // LDS executes a wavefront's accesses in order
         float4 t[ITERS][VEC / 4];                      // all reads of a block go out before the first use
 #pragma unroll
         for (int it = 0; it < ITERS; ++it)
 #pragma unroll
-            for (int u = 0; u < VEC / 4; ++u) t[it][u] = *(const float4 *)(stage + (it * RPI + r0) * LD + c + u * 4);
+            for (int u = 0; u < VEC / 4; ++u) t[it][u] = *(const float4 *)(stage + Staged::at(it * RPI + r0, c + u * 4));
 #pragma unroll
         for (int it = 0; it < ITERS; ++it)
             if (active && (FULL || (row0 + i * 32 + it * RPI + r0 < M && col0 + c < N))) {
@@ -175,25 +195,35 @@ __device__ __forceinline__ void epilogue_via_lds(f32x16 (&acc)[TM][TN], float *s
         __builtin_amdgcn_wave_barrier();
     };
     // a tile inside the matrix takes no test per row
-    if (row0 + TM * 32 <= M && col0 + W <= N) {
+    if (row0 + TM * 16 <= M && col0 + W <= N) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) block(std::true_type{}, i);
+        for (int i = 0; i < TM / 2; ++i) block(std::true_type{}, i);
     } else {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) block(std::false_type{}, i);
+        for (int i = 0; i < TM / 2; ++i) block(std::false_type{}, i);
     }
     if constexpr (EpiHasFinish<Epi>::value) epi.finish(lp, z, unit);
 }
 
+// f(n - 1), ..., f(0), the numbers as types
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F f)
+{
+    if constexpr (N > 0) {
+        f(std::integral_constant<int, N - 1>{});
+        unrolled<N - 1>(f);
+    }
+}
+
 // BLKA: A is stored in 32 x 32 blocks (see above); B always is.  In LDS a stage is [BM rows][32 k] of
-// A, then [BN rows][32 k] of B, rows of 64 B, slot s of row r holding piece s ^ ((r >> 2) & 3).
+// A, then [BN rows][32 k] of B, rows of 64 B, slot s of row r holding piece s ^ ((r >> 3) & 1) * 2.
 // WPS: wavefronts per SIMD the registers are budgeted for.  KG: groups of wavefronts that share a tile's contraction, each
 // with a ring of its own on a KG-th of it (K a multiple of 32 KG); the results are added in order through LDS.
 template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, class Epi>
 __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(GemmNT p, Epi epi, int batch)
 {
     constexpr int BK = 32, NW = WM * WN;
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NF = TM + TN, MM = TM * TN;
+    constexpr int TM = BM / WM / 16, TN = BN / WN / 16, MM = TM * TN;
     constexpr int CA = BM / 16, CB = BN / 16;           // 1 KiB chunks (16 rows x 64 B) per stage
     constexpr int CPW = (CA + CB) / NW;                 // ... and wavefront
     static_assert((CA + CB) % NW == 0 && BM % 32 == 0 && BN % 32 == 0, "chunks / waves");
@@ -226,12 +256,12 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
     const bf16_t *B = p.B + (long long)z * p.sB + (long long)grp * nk * 1024;
 
     // Per-lane global source of each 1 KiB chunk this wave copies: chunk c is 16 rows, LDS slot
-    // (row, s) holds the global piece s ^ ((row >> 2) & 3) of that row.  Blocked operand: half of a
+    // (row, s) holds the global piece s ^ ((row >> 3) & 1) * 2 of that row.  Blocked operand: half of a
     // 32 x 32 block, consecutive in memory up to that permutation; rows beyond the matrix inside the
     // last 256-row panel are allocated (their values only reach accumulator rows never stored), and
     // every tile shape divides 256.  Row-major A: 16 pieces of 64 B, rows clamped.
     const bf16_t *src[CPW];
-    const int piece = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;
+    const int piece = ((lane & 3) ^ (lane >> 5) * 2) * 8;
     const int blk_lane = (lane >> 2) * 32 + piece;
 #pragma unroll
     for (int i = 0; i < CPW; ++i) {
@@ -243,43 +273,37 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
             src[i] = B + ((long long)((n0 >> 5) + ((c - CA) >> 1)) * (p.K >> 5)) * 1024 + (c & 1) * 512 + blk_lane;
         }
     }
-    typedef __attribute__((address_space(3))) void lds_void;
-    typedef __attribute__((address_space(1))) const void glb_void;
+    // The copies as asm: behind the builtin, the compiler waits for all LDS reads in flight at every use of one.  The s_nop is
+    // the wait state that such a copy needs behind a write of m0 (the compiler sets m0 right before the statement, and counts
+    // wait states for its own copies only).
+    const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
     int d_stage = 0;                                    // stage the next copy goes to
     auto issue = [&](int i) {
         const int c = wave * CPW + i;
-        __builtin_amdgcn_global_load_lds((glb_void *)src[i], (lds_void *)(smem + d_stage * STAGE + c * 512), 16, 0, 0);
+        const unsigned dst = __builtin_amdgcn_readfirstlane(lds_ring + d_stage * (STAGE * 2) + c * 1024);
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(dst), "v"(src[i]) : "memory");
         src[i] += BLKA || c >= CA ? 1024 : BK;
     };
     auto issued = [&]() { d_stage = d_stage + 1 == NS ? 0 : d_stage + 1; };
 
-    f32x16 acc[TM][TN];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    bf16x8 fa[2][TM], fb[2][TN];
-    int offA[2], offB[2];                               // the lane's place in a stage, per 16-wide k-step
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-        const int pc = ks * 2 + (lane >> 5), r = lane & 31, sw = (pc ^ ((r >> 2) & 3)) * 8;
-        offA[ks] = (wm * TM * 32 + r) * 32 + sw;
-        offB[ks] = BM * BK + (wn * TN * 32 + r) * 32 + sw;
-    }
-    // fragment q of a k-step, in the order the multiplications need them: b0, a0, the other b, the other a
-    auto read = [&](int stage, int ks, int q) {
-        const bf16_t *s = smem + stage * STAGE;
-        if (q == 0) fb[ks][0] = *(const bf16x8 *)(s + offB[ks]);
-        else if (q == 1) fa[ks][0] = *(const bf16x8 *)(s + offA[ks]);
-        else if (q <= TN) fb[ks][q - 1] = *(const bf16x8 *)(s + offB[ks] + (q - 1) * 1024);
-        else fa[ks][q - TN] = *(const bf16x8 *)(s + offA[ks] + (q - TN) * 1024);
-    };
-    auto multiply = [&](int ks, int m) {                // serpentine: neighbours share an operand
-        const int i = m / TN, j = (i & 1) ? TN - 1 - m % TN : m % TN;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    // A stage's fragments (16 rows x 32 k each) of A and B.  AHEAD, for small tiles: a second set holds the next stage's.
+    constexpr bool AHEAD = MM <= 4;
+    constexpr int SETS = AHEAD ? 2 : 1;
+    constexpr int HA = AHEAD ? TM : TM / 2, HB = TM - HA;    // rows of blocks multiplied before and behind a stage's barrier
+    bf16x8 fa[SETS][TM], fb[SETS][TN];
+    // the lane's place in a stage: row l%16 of a fragment, piece l/16
+    const int lane_off = (lane & 15) * 32 + (((lane >> 4) ^ ((lane >> 3) & 1) * 2) * 8);
+    const int offA = wm * TM * 512 + lane_off, offB = BM * BK + wn * TN * 512 + lane_off;
+    auto read_a = [&](int stage, int set, int i) { fa[set][i] = *(const bf16x8 *)(smem + stage * STAGE + offA + i * 512); };
+    auto read_b = [&](int stage, int set, int j) { fb[set][j] = *(const bf16x8 *)(smem + stage * STAGE + offB + j * 512); };
+    auto multiply = [&](int set, int i, int j) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
     };
     // a barrier that no memory access is moved across
     auto barrier = [&]() {
@@ -287,26 +311,27 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    // vmcnt(left), lgkmcnt(0)
-    auto wait = [&](auto left) {
-        constexpr int n = decltype(left)::value;
+    // until at most `stages` stages' copies are outstanding, and for all LDS reads
+    auto wait = [&](auto stages) {
+        constexpr int n = CPW * decltype(stages)::value;
+        static_assert(n < 64, "vmcnt has six bits");
         __builtin_amdgcn_s_waitcnt(0x0070 | (n & 15) | ((n >> 4) << 14));
     };
 
-    // Main loop.  A stage is two k-steps.  While step 0's MFMAs issue, the fragments of step 1 are
-    // read; then comes the barrier (everyone's copies of the next stage have landed, everyone is
-    // through reading this one); while step 1's MFMAs issue, the fragments of the next stage's step
-    // 0 are read and the stage NS further on is requested into the buffer just freed.  The order is
-    // pinned instruction by instruction (sched_barrier after every MFMA): one LDS read or one copy
-    // between two MFMAs.  Left to the compiler, a k-step's six reads go out in one burst in front
-    // of its eight MFMAs and both wavefronts of a SIMD do so together.  Timed on MI355X at
-    // 12608 x 768 x 3072, batch 8, same box: bf16 output 465 -> 393 us (K = 3072), main loop alone
-    // 430 -> 371 us = 1.28 PFLOP/s; the loop without its copies runs at 1.5-1.6 PFLOP/s, and bare
-    // MFMAs on random operands at 1.84 (2.28 on zeros: the clock drops with the power they draw).
-    // Neither 3, 4 or 5 stages nor raised wave priority around the MFMAs make a difference; four
-    // wavefronts of 128 x 128 (a third fewer LDS reads) ran the same loop in 361-393 us on the same
-    // boxes, and lost it again in the epilogues, where one wavefront per SIMD has nothing to hide
-    // its waits behind (751 against 631 us with the GELU epilogue).
+    // Main loop.  A stage's blocks are multiplied column by column of the wavefront's tile, the first half of its rows
+    // and then the second half, so that one set of fragments is enough: while the first half's MFMAs issue, the
+    // second half's A fragments are read (and the last column's B fragment, which the stage before needed to its end); then
+    // comes the barrier (everyone's copies of the next stage have landed, everyone is through reading this one); while the
+    // second half's MFMAs issue, the next stage's A fragments of the first half are read, each column's B fragment as soon as
+    // the column is through with the present one, and the stage NS further on is requested into the buffer just freed.
+    // Small tiles hold two sets: the barrier comes first, and the next stage is read while this one is multiplied.
+    // The order is pinned instruction by instruction (sched_barrier after every MFMA): one LDS read or one copy
+    // between two MFMAs.  Left to the compiler, the reads go out in one burst in front of the MFMAs and both wavefronts of a
+    // SIMD do so together.
+    // Timed on MI355X at 12608 x 768 x 3072, batch 8, bf16 output: 363 us = 1.31 PFLOP/s; with 32x32x16
+    // instructions, everything else alike, 407; with these and conflicts in the fragment reads 381.  Without its copies the
+    // same kernel takes 300 us, without its LDS reads 316, without its barriers 352 (at a lower clock: what they cost is power), the
+    // bare MFMAs 225.  Neither 3, 4 or 5 stages nor raised wave priority around the MFMAs make a difference.
     auto compute = [&]() -> bool {
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -315,52 +340,107 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
             for (int i = 0; i < CPW; ++i) issue(i);
             issued();
         }
-    if (nk >= NS) wait(std::integral_constant<int, CPW * (NS - 1)>{});
-    else wait(std::integral_constant<int, 0>{});
+    unrolled<NS>([&](auto left) { if ((nk < NS ? nk : NS) - 1 == decltype(left)::value) wait(left); });
     barrier();
     int cur = 0;
 #pragma unroll
-    for (int q = 0; q < NF; ++q) read(0, 0, q);
-    auto stage = [&](auto last_c, auto issue_c, auto left) {
+    for (int i = 0; i < HA; ++i) read_a(0, 0, i);
+#pragma unroll
+    for (int j = 0; j < TN - (AHEAD ? 0 : 1); ++j) read_b(0, 0, j);
+    if constexpr (AHEAD) {                             // sets alternate so that the last stage has set 0: the first, either
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[1][i] = fa[0][i];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[1][j] = fb[0][j];
+    }
+    // With scalar loads (the epilogue's arguments) in flight at its top, which complete in any order, the loop would wait for all
+    // LDS reads at its first MFMA.
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    auto next = [&]() { cur = cur + 1 == NS ? 0 : cur + 1; };
+    auto stage_ahead = [&](auto set_c, auto last_c, auto issue_c, auto left) {
+        constexpr int SET = decltype(set_c)::value;
         constexpr bool LAST = decltype(last_c)::value, ISSUE = decltype(issue_c)::value;
+        if (!LAST) {
+            wait(left);
+            barrier();
+            next();
+        }
         __builtin_amdgcn_sched_barrier(0);
+        if (!LAST) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) read_a(cur, SET ^ 1, i);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) read_b(cur, SET ^ 1, j);
+        }
 #pragma unroll
         for (int m = 0; m < MM; ++m) {
-            multiply(0, m);
+            multiply(SET, m % TM, m / TM);
 #pragma unroll
-            for (int q = 0; q < NF; ++q)
-                if ((NF <= MM ? q : q * MM / NF) == m) read(cur, 1, q);
+            for (int i = 0; i < CPW; ++i)
+                if (!LAST && ISSUE && (CPW <= MM ? i : i * MM / CPW) == m) issue(i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!LAST && ISSUE) issued();
+    };
+    auto stage_halves = [&](auto, auto last_c, auto issue_c, auto left) {
+        constexpr bool LAST = decltype(last_c)::value, ISSUE = decltype(issue_c)::value;
+        constexpr int MA = HA * TN, MB = HB * TN;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MA; ++m) {                  // serpentine: neighbours share an operand
+            const int j = m / HA, i = j & 1 ? HA - 1 - m % HA : m % HA;
+            multiply(0, i, j);
+            if (m == 0) read_b(cur, 0, TN - 1);
+            else if (m <= HB) read_a(cur, 0, HA + m - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (!LAST) {
             wait(left);
             barrier();
-            cur = cur + 1 == NS ? 0 : cur + 1;
+            next();
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int m = 0; m < MM; ++m) {
-            multiply(1, m);
+        for (int m = 0; m < MB; ++m) {
+            const int j = m / HB, i = HA + (j & 1 ? HB - 1 - m % HB : m % HB);
+            multiply(0, i, j);
+            if (!LAST) {
+                if (m < HA) read_a(cur, 0, m);
+                if (m % HB == HB - 1 && j < TN - 1) read_b(cur, 0, j);
+            }
 #pragma unroll
-            for (int q = 0; q < NF; ++q)
-                if (!LAST && (NF <= MM ? q : q * MM / NF) == m) read(cur, 0, q);
-#pragma unroll
-            for (int i = 0; i < CPW; ++i)
-                if (!LAST && ISSUE && (CPW <= MM ? MM - CPW + i : i * MM / CPW) == m) issue(i);
+            for (int c = 0; c < CPW; ++c)
+                if (!LAST && ISSUE && (CPW <= MB ? MB - CPW + c : c * MB / CPW) == m) issue(c);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (!LAST && ISSUE) issued();
     };
-    // copies outstanding at a stage's wait: stages kt + 2 .. kt + NS - 1 while that many exist
-    int kt = 0;
-    for (; kt + NS < nk; ++kt) stage(std::false_type{}, std::true_type{}, std::integral_constant<int, CPW * (NS - 2)>{});
-    if (kt + NS == nk && kt + 1 < nk) { stage(std::false_type{}, std::false_type{}, std::integral_constant<int, CPW * (NS - 2)>{}); ++kt; }
-    for (; kt + 1 < nk; ++kt) stage(std::false_type{}, std::false_type{}, std::integral_constant<int, 0>{});
-    stage(std::true_type{}, std::false_type{}, std::integral_constant<int, 0>{});
+    auto stage = [&](auto set_c, auto last_c, auto issue_c, auto left) {
+        if constexpr (AHEAD) stage_ahead(set_c, last_c, issue_c, left);
+        else stage_halves(set_c, last_c, issue_c, left);
+    };
+    // At a stage's wait the stages behind the next one are outstanding, NS - 2 of them while requests go on
+    constexpr std::integral_constant<int, NS - 2> full{};
+    constexpr std::integral_constant<int, 0> set0{};
+    constexpr std::integral_constant<int, SETS - 1> set1{};
+    static_assert(!AHEAD || NS % 2 == 0, "the stages behind the last request begin with set 1");
+    int todo = nk - NS;
+    if (AHEAD) {
+        if (todo > 0 && (todo & 1)) { stage(set0, std::false_type{}, std::true_type{}, full); --todo; }
+        for (; todo > 0; todo -= 2) { stage(set1, std::false_type{}, std::true_type{}, full); stage(set0, std::false_type{}, std::true_type{}, full); }
+    } else {
+        for (; todo > 0; --todo) stage(set0, std::false_type{}, std::true_type{}, full);
+    }
+    unrolled<NS - 1>([&](auto left) {                  // NS - 2, ..., 0 stages outstanding
+        constexpr int LEFT = decltype(left)::value;
+        if (nk >= LEFT + 2) stage(std::integral_constant<int, AHEAD ? (LEFT + 1) & 1 : 0>{}, std::false_type{}, std::false_type{}, left);
+    });
+    stage(set0, std::true_type{}, std::false_type{}, set0);
 
         __syncthreads();                               // every wavefront is done with the rings
         if constexpr (KG > 1) {
-            constexpr int STAGING = NW * 32 * (TN * 32 + 4);   // floats
+            constexpr int STAGING = NW * StagedTile<TN * 16>::FLOATS;
             float *accs = (float *)gemm_smem + STAGING;
             if (grp > 0) {
 #pragma unroll
@@ -368,8 +448,8 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
 #pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            accs[((((grp - 1) * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane] = acc[i][j][e];
+                        for (int e = 0; e < 4; ++e)
+                            accs[((((grp - 1) * NW + wave) * MM + i * TN + j) * 4 + e) * 64 + lane] = acc[i][j][e];
             }
             __syncthreads();
             if (grp > 0) return false;
@@ -380,12 +460,12 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
 #pragma unroll
-                        for (int e = 0; e < 16; ++e) acc[i][j][e] += accs[(((gg * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane];
+                        for (int e = 0; e < 4; ++e) acc[i][j][e] += accs[(((gg * NW + wave) * MM + i * TN + j) * 4 + e) * 64 + lane];
         }
         return true;
     };
-    epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane, m0 + wm * TM * 32,
-                             n0 + wn * TN * 32, p.M, p.N, z, (by * nx + bx) * NW + wave, epi, compute);
+    epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * StagedTile<TN * 16>::FLOATS, lane, m0 + wm * TM * 16,
+                             n0 + wn * TN * 16, p.M, p.N, z, (by * nx + bx) * NW + wave, epi, compute);
 }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));   // operand of the LDS transpose read
@@ -398,7 +478,7 @@ inline hipError_t launch_gemm_nt(const GemmNT &p, const Epi &epi, int batch, hip
     const unsigned tiles = (unsigned)((p.N + BN - 1) / BN) * (unsigned)((p.M + BM - 1) / BM) * (unsigned)batch;
     dim3 grid((tiles + 7) / 8 * 8, 1, 1);
     constexpr size_t ring = (size_t)KG * NS * (BM + BN) * 32 * sizeof(bf16_t);
-    constexpr size_t staging = ((size_t)WM * WN * 32 * (BN / WN + 4) + (size_t)(KG - 1) * BM * BN) * sizeof(float);
+    constexpr size_t staging = ((size_t)WM * WN * StagedTile<BN / WN>::FLOATS + (size_t)(KG - 1) * BM * BN) * sizeof(float);
     constexpr size_t smem = ring > staging ? ring : staging;
     static_assert(smem <= 160 * 1024, "tile does not fit the 160 KB LDS");
     auto kern = gemm_nt_bf16_kernel<BM, BN, WM, WN, KG, WPS, NS, BLKA, Epi>;

@@ -9,16 +9,16 @@
 // the hardware).  Pointing lane r = q + 4e of a group at token e, features 4q..4q+3 of a
 // 4-token x 16-feature block therefore hands lane j feature j and the 4 tokens in order; two
 // such reads give the 8 k values of an MFMA operand, and the four groups of a wavefront cover
-// 32 features x 16 tokens in exactly the instruction's operand layout.
+// 16 features x 32 tokens in exactly the operand layout of v_mfma_f32_16x16x32_bf16 (gemm_bf16.h).
 //
 //  * Stages of 32 tokens are copied global -> LDS directly (global_load_lds_dwordx4) into a ring of NS
-//    buffers, NS ahead, LDS keeping [32-feature column block][32 tokens][32 features], the form
-//    the transpose reads take without bank conflicts.  Token rows beyond K are read from a block of
-//    zeros.
+//    buffers, NS ahead, LDS keeping [32-feature column block][32 tokens][32 features], with the two halves of a token's
+//    64 bytes exchanged in every second group of 8 tokens: two groups of lanes read 8 tokens apart at the same time,
+//    which are a multiple of all banks apart.  Token rows beyond K are read from a block of zeros.
 //  * The order of the main loop is pinned as in gemm_bf16.h: LDS reads and copies go out one or two at
 //    a time between MFMAs, one barrier per stage.  (Two wavefront groups a phase apart, one
 //    multiplying while the other fetches, with two barriers per stage: 468 us against 407 us at 8 x 12608
-//    tokens x 768 x 3072, same box.)
+//    tokens x 768 x 3072, same box, both with 32x32x16 instructions; 386 with 16x16x32, which take less of the chip's power.)
 //  * Large problems: tiles of 192 x 384 (wavefront 96 x 96).  768 x 3072 outputs per worker are 32
 //    such tiles, so 8 workers fill the 256 compute units exactly once.  The reduction of
 //    problems with fewer tiles can be cut into ranges (TnGroup::split): each (tile, range) is a
@@ -83,7 +83,8 @@ template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS>
 __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup g, int Z)
 {
     constexpr int BK = 32, NW = WM * WN;                          // wavefronts of a group
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32, MM = TM * TN, NF = TM + TN;
+    constexpr int TM = BM / WM / 16, TN = BN / WN / 16, MM = TM * TN;
+    constexpr int HA = TM / 2, HB = TM - HA;                      // rows of the tile's blocks on either side of a stage's barrier
     constexpr int PANEL = 4;                                      // N-tiles per panel of the tile order
     constexpr int STAGE = (BM + BN) * BK;                         // elements
     constexpr int CA = BM / 16, CHUNKS = (BM + BN) / 16;          // 1 KiB chunks per stage
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup
         const int c = i * NW + wave;
         const bool isA = c < CA;
         const int cc = isA ? c : c - CA, t = (cc & 1) * 16 + tok;                // token inside the stage
-        const int fc = min((isA ? m0 : n0) + (cc >> 1) * 32, (isA ? p.M : p.N) - 32) + (lane & 3) * 8;
+        const int fc = min((isA ? m0 : n0) + (cc >> 1) * 32, (isA ? p.M : p.N) - 32) + ((lane & 3) ^ ((tok >> 3) << 1)) * 8;
         if (isA) src[i] = blkA ? A + (long long)(fc >> 5) * 1024 + t * 32 + (fc & 31) : A + (long long)t * p.lda + fc;
         else src[i] = blkB ? B + (long long)(fc >> 5) * 1024 + t * 32 + (fc & 31) : B + (long long)t * p.ldb + fc;
     }
@@ -158,50 +159,41 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup
     auto issued = [&]() { d_stage = d_stage + 1 == NS ? 0 : d_stage + 1; d_row += BK; };
     const bool short_wave = CHUNKS % NW != 0 && (CPW - 1) * NW + wave >= CHUNKS;
 
-    f32x16 acc[TM][TN];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    float csum[TN];                                   // column sums of B: lane l has 8 tokens of column l % 32 per fragment
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float csum[TN];                                   // column sums of B: lane l has 8 tokens of column l % 16 per fragment
 #pragma unroll
     for (int j = 0; j < TN; ++j) csum[j] = 0.f;
     const bool colsum_wg = m0 == 0;
     const bool do_colsum = colsum_wg && wm == 0;
 
-    bf16x8 fa[2][TM], fb[2][TN];
-    // lane's place in the transpose reads inside a 16-token x 32-feature operand block
+    bf16x8 fa[TM], fb[TN];                            // fragments of a stage: 16 features x 32 tokens
+    // lane's place in the transpose reads inside a 32-token x 32-feature block, for either half of the features
     const int g16 = lane >> 4, r16 = lane & 15;
-    const int lane_off = ((g16 >> 1) * 8 + (r16 >> 2)) * 32 + (g16 & 1) * 16 + (r16 & 3) * 4;
-    auto frag = [&](const bf16_t *blk, int ks) {      // blk: [32 tokens][32 features] of one column block
+    const int lane_tok = (g16 * 8 + (r16 >> 2)) * 32 + (r16 & 3) * 4;
+    const int lane_half[2] = {lane_tok + (g16 & 1) * 16, lane_tok + ((g16 & 1) ^ 1) * 16};
+    auto frag = [&](const bf16_t *side, int i) {      // side: a wavefront's column blocks of a stage, 32 features each
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-        const bf16_t *q0 = blk + ks * 512 + lane_off;
+        const bf16_t *q0 = side + (i >> 1) * 1024 + lane_half[i & 1];
         union { struct { s16x4 a, b; } s; bf16x8 v; } u;
         u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)q0);
         u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(q0 + 4 * 32));
         return u.v;
     };
-    auto read = [&](int stage, int ks, int q) {       // in the order the multiplications need them
-        const bf16_t *sa = ring + stage * STAGE + wm * TM * 1024, *sb = ring + stage * STAGE + BM * BK + wn * TN * 1024;
-        if (q == 0) fb[ks][0] = frag(sb, ks);
-        else if (q == 1) fa[ks][0] = frag(sa, ks);
-        else if (q <= TN) fb[ks][q - 1] = frag(sb + (q - 1) * 1024, ks);
-        else fa[ks][q - TN] = frag(sa + (q - TN) * 1024, ks);
-    };
-    auto multiply = [&](int ks, int m) {              // serpentine: neighbours share an operand
-        const int i = m / TN, j = (i & 1) ? TN - 1 - m % TN : m % TN;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
-    };
-    auto add_columns = [&](int ks) {
+    auto read_a = [&](int stage, int i) { fa[i] = frag(ring + stage * STAGE + wm * TM * 512, i); };
+    auto read_b = [&](int stage, int j) { fb[j] = frag(ring + stage * STAGE + BM * BK + wn * TN * 512, j); };
+    auto multiply = [&](int i, int j) { acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0); };
+    auto add_columns = [&]() {
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
         const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const bf16x2 two = {fb[ks][j][2 * e], fb[ks][j][2 * e + 1]};
+                const bf16x2 two = {fb[j][2 * e], fb[j][2 * e + 1]};
                 csum[j] = __builtin_amdgcn_fdot2_f32_bf16(two, ones, csum[j], false);
             }
     };
@@ -229,35 +221,43 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup
     barrier();
     int cur = 0;
 #pragma unroll
-    for (int q = 0; q < NF; ++q) read(0, 0, q);
-    auto stage = [&](auto last_c, auto issue_c, auto left) {
+    for (int i = 0; i < HA; ++i) read_a(0, i);
+#pragma unroll
+    for (int j = 0; j < TN - 1; ++j) read_b(0, j);
+    // With scalar loads (the epilogue's arguments) in flight at its top, which complete in any order, the loop would wait for all
+    // LDS reads at its first MFMA.
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    auto stage = [&](auto last_c, auto issue_c, auto left) {      // the order of gemm_bf16.h
         constexpr bool LAST = decltype(last_c)::value, ISSUE = decltype(issue_c)::value;
+        constexpr int MA = HA * TN, MB = HB * TN;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int m = 0; m < MM; ++m) {
-            multiply(0, m);
-#pragma unroll
-            for (int q = 0; q < NF; ++q)
-                if ((NF <= MM ? q : q * MM / NF) == m) read(cur, 1, q);
+        for (int m = 0; m < MA; ++m) {
+            const int j = m / HA, i = j & 1 ? HA - 1 - m % HA : m % HA;
+            multiply(i, j);
+            if (m == 0) read_b(cur, TN - 1);
+            else if (m <= HB) read_a(cur, HA + m - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (do_colsum) add_columns(0);
+        if (do_colsum) add_columns();
         if (!LAST) {
             wait(left);
             barrier();
             cur = cur + 1 == NS ? 0 : cur + 1;
         }
-        if (do_colsum) add_columns(1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int m = 0; m < MM; ++m) {
-            multiply(1, m);
+        for (int m = 0; m < MB; ++m) {
+            const int j = m / HB, i = HA + (j & 1 ? HB - 1 - m % HB : m % HB);
+            multiply(i, j);
+            if (!LAST) {
+                if (m < HA) read_a(cur, m);
+                if (m % HB == HB - 1 && j < TN - 1) read_b(cur, j);
+            }
 #pragma unroll
-            for (int q = 0; q < NF; ++q)
-                if (!LAST && (NF <= MM ? q : q * MM / NF) == m) read(cur, 0, q);
-#pragma unroll
-            for (int i = 0; i < CPW; ++i)
-                if (!LAST && ISSUE && (CPW <= MM ? MM - CPW + i : i * MM / CPW) == m) issue(i);
+            for (int c = 0; c < CPW; ++c)
+                if (!LAST && ISSUE && (CPW <= MB ? MB - CPW + c : c * MB / CPW) == m) issue(c);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (!LAST && ISSUE) issued();
@@ -270,15 +270,15 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup
     stage(std::true_type{}, std::false_type{}, std::integral_constant<int, 0>{});
     __syncthreads();                                  // everyone is through with the rings
 
-    // The ring's memory from here on: epilogue staging, column sums [group][token half][column], the other groups'
+    // The ring's memory from here on: epilogue staging, column sums [group][token quarter][column], the other groups'
     // accumulators
-    constexpr int STAGING = NW * 32 * (TN * 32 + 4);  // floats
-    constexpr int COLS = KG * 2 * BN, ACCS = (KG - 1) * NW * MM * 16 * 64;
+    constexpr int STAGING = NW * StagedTile<TN * 16>::FLOATS;
+    constexpr int COLS = KG * 4 * BN, ACCS = (KG - 1) * NW * MM * 4 * 64;
     static_assert((STAGING + COLS + ACCS) * 4 <= KG * NS * STAGE * 2, "epilogue inside the rings");
     float *cols = (float *)gemm_smem + STAGING, *accs = cols + COLS;
     if (do_colsum) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) cols[(grp * 2 + (lane >> 5)) * BN + wn * (BN / WN) + j * 32 + (lane & 31)] = csum[j];
+        for (int j = 0; j < TN; ++j) cols[(grp * 4 + (lane >> 4)) * BN + wn * (BN / WN) + j * 16 + (lane & 15)] = csum[j];
     }
     if (KG > 1 && grp > 0) {
 #pragma unroll
@@ -286,14 +286,14 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    accs[((((grp - 1) * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane] = acc[i][j][e];
+                for (int e = 0; e < 4; ++e)
+                    accs[((((grp - 1) * NW + wave) * MM + i * TN + j) * 4 + e) * 64 + lane] = acc[i][j][e];
     }
     __syncthreads();
     if (colsum_wg && tid < BN && n0 + tid < p.N) {
         float s = 0.f;
 #pragma unroll
-        for (int q = 0; q < KG * 2; ++q) s += cols[q * BN + tid];
+        for (int q = 0; q < KG * 4; ++q) s += cols[q * BN + tid];
         out[p.off_colsum + n0 + tid] = s;
     }
     if (KG > 1) {
@@ -305,11 +305,11 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] += accs[(((gg * NW + wave) * MM + i * TN + j) * 16 + e) * 64 + lane];
+                    for (int e = 0; e < 4; ++e) acc[i][j][e] += accs[(((gg * NW + wave) * MM + i * TN + j) * 4 + e) * 64 + lane];
     }
     const EpiF32 epi{out + p.off, p.N};
-    epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * (32 * (TN * 32 + 4)), lane,
-                             m0 + wm * TM * 32, n0 + wn * TN * 32, p.M, p.N, 0, 0, epi, []() { return true; });
+    epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * StagedTile<TN * 16>::FLOATS, lane,
+                             m0 + wm * TM * 16, n0 + wn * TN * 16, p.M, p.N, 0, 0, epi, []() { return true; });
 }
 
 // Whether launch_gemm_tn can take the group (blocked operands: 32-column blocks; the ranges of a split reduction
