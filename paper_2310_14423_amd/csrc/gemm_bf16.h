@@ -45,6 +45,8 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "nt_plan.h"
+
 namespace qsr {
 
 // element offset of (r, c) in the blocked layout of an [R][C] matrix; R is padded to 256 rows (the
@@ -132,7 +134,7 @@ struct StagedTile {
     }
 };
 
-// `compute` leaves the tile in acc and says whether this wavefront stores it.  A wavefront with one block of 32 x 32 asks for
+// `compute` leaves the tile in acc.  A wavefront with one block of 32 x 32 asks for
 // what its epilogue reads ahead of that: with few tiles in flight nothing else hides the latency.
 // TM x TN blocks of 16 x 16.
 template <int TM, int TN, class Epi, class Compute>
@@ -140,7 +142,7 @@ __device__ __forceinline__ void epilogue_via_lds(f32x4 (&acc)[TM][TN], float *st
                                                  int row0, int col0, int M, int N, int z, int unit, const Epi &epi, Compute compute)
 {
     constexpr bool EARLY = TM * TN == 4;
-    if constexpr (!EARLY) if (!compute()) return;
+    if constexpr (!EARLY) compute();
     constexpr int W = TN * 16;                         // floats per staged row
     typedef StagedTile<W> Staged;
     constexpr int VEC = Epi::VEC;
@@ -156,7 +158,7 @@ __device__ __forceinline__ void epilogue_via_lds(f32x4 (&acc)[TM][TN], float *st
 #pragma unroll
         for (int it = 0; it < ITERS; ++it)
             if (active && row0 + it * RPI + r0 < M && col0 + c < N) aux[0][it] = epi.pre(lp, it * RPI);
-        if (!compute()) return;
+        compute();
     }
     auto block = [&](auto full_c, int i) {
         constexpr bool FULL = decltype(full_c)::value;
@@ -205,6 +207,18 @@ __device__ __forceinline__ void epilogue_via_lds(f32x4 (&acc)[TM][TN], float *st
     if constexpr (EpiHasFinish<Epi>::value) epi.finish(lp, z, unit);
 }
 
+// The tiles of a launch: along N, along M, of a batch entry, all, an eighth of them (rounded up); reciprocals for quotient()
+struct NtGrid { int nx, ny, per_z, tiles, share; float inv_per_z, inv_panel; };
+// n / d for 0 <= n < 2^31, d >= 1, inv = 1.0f / d, in a handful of instructions: the estimate is off by n / d 2^-23 and less than
+// one more, which a step mends up to quotients of 2^22 (a launch's batch entries, a batch entry's panels)
+__device__ __forceinline__ int quotient(int n, int d, float inv)
+{
+    int q = __builtin_amdgcn_readfirstlane((int)((float)n * inv));
+    const int r = n - q * d;
+    q += r < 0 ? -1 : r >= d ? 1 : 0;
+    return q;
+}
+
 // f(n - 1), ..., f(0), the numbers as types
 template <int N, class F>
 __device__ __forceinline__ void unrolled(F f)
@@ -217,10 +231,9 @@ __device__ __forceinline__ void unrolled(F f)
 
 // BLKA: A is stored in 32 x 32 blocks (see above); B always is.  In LDS a stage is [BM rows][32 k] of
 // A, then [BN rows][32 k] of B, rows of 64 B, slot s of row r holding piece s ^ ((r >> 3) & 1) * 2.
-// WPS: wavefronts per SIMD the registers are budgeted for.  KG: groups of wavefronts that share a tile's contraction, each
-// with a ring of its own on a KG-th of it (K a multiple of 32 KG); the results are added in order through LDS.
-template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, class Epi>
-__global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(GemmNT p, Epi epi, int batch)
+// WPS: wavefronts per SIMD the registers are budgeted for.
+template <int BM, int BN, int WM, int WN, int WPS, int NS, bool BLKA, class Epi>
+__global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT p, Epi epi, NtGrid g)
 {
     constexpr int BK = 32, NW = WM * WN;
     constexpr int TM = BM / WM / 16, TN = BN / WN / 16, MM = TM * TN;
@@ -230,9 +243,8 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
     constexpr int STAGE = (BM + BN) * BK;
     extern __shared__ __attribute__((aligned(1024))) unsigned char gemm_smem[];
 
-    const int lane = threadIdx.x & 63, wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int grp = wave_wg / NW, wave = wave_wg % NW;
-    bf16_t *smem = (bf16_t *)gemm_smem + grp * NS * STAGE;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    bf16_t *smem = (bf16_t *)gemm_smem;
     const int wm = wave / WN, wn = wave % WN;
     // Workgroups go to the 8 XCDs round-robin by linear id (the grid's x extent is a multiple of
     // 8).  Tile order: batch entry (worker), then panels of 4 N-tiles, then M-tile, then N-tile
@@ -240,20 +252,21 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
     // one worker's B operand (for 8 workers), and the tiles that run together share their A rows
     // and B rows: 30-45 % fewer bytes fetched into L2 than with the batch as a grid dimension.
     // (Panels of 2, 3, 6 or 12 tiles: the same to 3 %, the narrow ones slower at N = 768.)
-    const int nx = (p.N + BN - 1) / BN, ny = (p.M + BM - 1) / BM;
-    int tile = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-    if (tile >= batch * nx * ny) return;
-    const int z = tile / (nx * ny);
-    tile -= z * nx * ny;
+    int tile = (blockIdx.x % 8) * g.share + blockIdx.x / 8;
+    if (tile >= g.tiles) return;
+    // all of a wavefront's requests depend on these: the arguments in one load, quotients by multiplication
+    const int z = quotient(tile, g.per_z, g.inv_per_z);
+    tile -= z * g.per_z;
     constexpr int PANEL = 4;
-    const int pn = tile / (ny * PANEL);
-    tile -= pn * ny * PANEL;
-    const int bw = min(PANEL, nx - pn * PANEL);
-    const int by = tile / bw, bx = pn * PANEL + tile - by * bw;
+    const int pn = quotient(tile, g.ny * PANEL, g.inv_panel);
+    tile -= pn * g.ny * PANEL;
+    const int bw = min(PANEL, g.nx - pn * PANEL);
+    const int by = bw == 4 ? tile >> 2 : bw == 2 ? tile >> 1 : bw == 1 ? tile : (int)(((unsigned long long)(unsigned)tile * 0xAAAAAAABull) >> 33);
+    const int bx = pn * PANEL + tile - by * bw;
     const int m0 = by * BM, n0 = bx * BN;
-    const int nk = p.K / (BK * KG);                    // stages of a group
-    const bf16_t *A = p.A + (long long)z * p.sA + (long long)grp * nk * (BLKA ? 1024 : BK);
-    const bf16_t *B = p.B + (long long)z * p.sB + (long long)grp * nk * 1024;
+    const int nk = p.K / BK;                           // stages
+    const bf16_t *A = p.A + (long long)z * p.sA;
+    const bf16_t *B = p.B + (long long)z * p.sB;
 
     // Per-lane global source of each 1 KiB chunk this wave copies: chunk c is 16 rows, LDS slot
     // (row, s) holds the global piece s ^ ((row >> 3) & 1) * 2 of that row.  Blocked operand: half of a
@@ -331,15 +344,20 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
     // Timed on MI355X at 12608 x 768 x 3072, batch 8, bf16 output: 363 us = 1.31 PFLOP/s; with 32x32x16
     // instructions, everything else alike, 407; with these and conflicts in the fragment reads 381.  Without its copies the
     // same kernel takes 300 us, without its LDS reads 316, without its barriers 352 (at a lower clock: what they cost is power), the
-    // bare MFMAs 225.  Neither 3, 4 or 5 stages nor raised wave priority around the MFMAs make a difference.
-    auto compute = [&]() -> bool {
+    // bare MFMAs 225.  With large tiles neither 3, 4 or 5 stages nor raised wave priority around the MFMAs make a difference.
+    auto compute = [&]() {
+    auto request = [&]() {
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-        if (s < nk) {
+        for (int i = 0; i < CPW; ++i) issue(i);
+        issued();
+    };
+    if constexpr (AHEAD) {                             // a loop: small problems wait for instructions as much as for data
+#pragma unroll 1
+        for (int s = 0; s < min(NS, nk); ++s) request();
+    } else {
 #pragma unroll
-            for (int i = 0; i < CPW; ++i) issue(i);
-            issued();
-        }
+        for (int s = 0; s < NS; ++s) if (s < nk) request();
+    }
     unrolled<NS>([&](auto left) { if ((nk < NS ? nk : NS) - 1 == decltype(left)::value) wait(left); });
     barrier();
     int cur = 0;
@@ -438,57 +456,38 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_nt_bf16_kernel(Ge
     });
     stage(set0, std::true_type{}, std::false_type{}, set0);
 
-        __syncthreads();                               // every wavefront is done with the rings
-        if constexpr (KG > 1) {
-            constexpr int STAGING = NW * StagedTile<TN * 16>::FLOATS;
-            float *accs = (float *)gemm_smem + STAGING;
-            if (grp > 0) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            accs[((((grp - 1) * NW + wave) * MM + i * TN + j) * 4 + e) * 64 + lane] = acc[i][j][e];
-            }
-            __syncthreads();
-            if (grp > 0) return false;
-#pragma unroll
-            for (int gg = 0; gg < KG - 1; ++gg)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[i][j][e] += accs[(((gg * NW + wave) * MM + i * TN + j) * 4 + e) * 64 + lane];
-        }
-        return true;
+        __syncthreads();                               // every wavefront is done with the ring
     };
     epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * StagedTile<TN * 16>::FLOATS, lane, m0 + wm * TM * 16,
-                             n0 + wn * TN * 16, p.M, p.N, z, (by * nx + bx) * NW + wave, epi, compute);
+                             n0 + wn * TN * 16, p.M, p.N, z, (by * g.nx + bx) * NW + wave, epi, compute);
 }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));   // operand of the LDS transpose read
 
-template <int BM, int BN, int WM, int WN, int KG, int WPS, int NS, bool BLKA, class Epi>
+template <NtShape SHAPE, int WM, int WN, int WPS, bool BLKA, class Epi>
 inline hipError_t launch_gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
+    constexpr int BM = NT_TILE[SHAPE].bm, BN = NT_TILE[SHAPE].bn, NS = NT_TILE[SHAPE].stages;
     static_assert(256 % BM == 0 && 256 % BN == 0, "blocked operands are allocated in panels of 256 rows");
-    if (p.K % (32 * KG) != 0 || p.K < 32 || p.N % 64 != 0) return hipErrorInvalidValue;
-    const unsigned tiles = (unsigned)((p.N + BN - 1) / BN) * (unsigned)((p.M + BM - 1) / BM) * (unsigned)batch;
-    dim3 grid((tiles + 7) / 8 * 8, 1, 1);
-    constexpr size_t ring = (size_t)KG * NS * (BM + BN) * 32 * sizeof(bf16_t);
-    constexpr size_t staging = ((size_t)WM * WN * StagedTile<BN / WN>::FLOATS + (size_t)(KG - 1) * BM * BN) * sizeof(float);
+    if (p.K % 32 != 0 || p.K < 32 || p.N % 64 != 0) return hipErrorInvalidValue;
+    const long long tiles = nt_tiles(SHAPE, p.M, p.N, batch);
+    if (tiles > (1 << 24)) return hipErrorInvalidValue;    // threads of a launch
+    dim3 grid((unsigned)(tiles + 7) / 8 * 8, 1, 1);
+    constexpr size_t ring = (size_t)NS * (BM + BN) * 32 * sizeof(bf16_t);
+    constexpr size_t staging = (size_t)WM * WN * StagedTile<BN / WN>::FLOATS * sizeof(float);
     constexpr size_t smem = ring > staging ? ring : staging;
     static_assert(smem <= 160 * 1024, "tile does not fit the 160 KB LDS");
-    auto kern = gemm_nt_bf16_kernel<BM, BN, WM, WN, KG, WPS, NS, BLKA, Epi>;
+    auto kern = gemm_nt_bf16_kernel<BM, BN, WM, WN, WPS, NS, BLKA, Epi>;
     static bool lds_limit_raised = false;     // per instantiation; contexts are not thread-safe
     if (smem > 64 * 1024 && !lds_limit_raised) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         lds_limit_raised = true;
     }
-    kern<<<grid, WM * WN * KG * 64, smem, s>>>(p, epi, batch);
+    NtGrid g;
+    g.nx = (p.N + BN - 1) / BN; g.ny = (p.M + BM - 1) / BM; g.per_z = g.nx * g.ny; g.tiles = (int)tiles; g.share = (int)(grid.x / 8);
+    g.inv_per_z = 1.0f / (float)g.per_z; g.inv_panel = 1.0f / (float)(4 * g.ny);
+    kern<<<grid, WM * WN * 64, smem, s>>>(p, epi, g);
     return hipGetLastError();
 }
 

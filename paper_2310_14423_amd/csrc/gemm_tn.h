@@ -309,7 +309,7 @@ __global__ __launch_bounds__(WM * WN * KG * 64, WPS) void gemm_tn_kernel(TnGroup
     }
     const EpiF32 epi{out + p.off, p.N};
     epilogue_via_lds<TM, TN>(acc, (float *)gemm_smem + wave * StagedTile<TN * 16>::FLOATS, lane,
-                             m0 + wm * TM * 16, n0 + wn * TN * 16, p.M, p.N, 0, 0, epi, []() { return true; });
+                             m0 + wm * TM * 16, n0 + wn * TN * 16, p.M, p.N, 0, 0, epi, []() {});
 }
 
 // Whether launch_gemm_tn can take the group (blocked operands: 32-column blocks; the ranges of a split reduction

@@ -544,6 +544,7 @@ struct EpiLoss {                 // y = scale * acc; r = x_L - y; dx = inv * r i
     const float *X; long long sX; float *DX; long long sDX; bf16_t *DXb; long long sDXb; float *LPART; long long sLPART;
     long long ld; float scale, inv;
     static constexpr int VEC = 4;
+    static constexpr NtOut OUT = NT_RESIDUAL;
     typedef float4 Aux;
     struct Lane { EpiPtr<const float, false> x; EpiPtr<float, false> o; EpiPtr<bf16_t, false> b; mutable double sum; };
     __device__ Lane lane(int z, int row, int col, int r, int c) const
@@ -573,6 +574,7 @@ struct EpiLoss {                 // y = scale * acc; r = x_L - y; dx = inv * r i
 struct EpiScaleF32 {             // C = scale * acc
     float *C; long long ldc, sC; float scale;
     static constexpr int VEC = 4;
+    static constexpr NtOut OUT = NT_F32;
     typedef NoAux Aux;
     typedef EpiPtr<float, false> Lane;
     __device__ Lane lane(int z, int row, int col, int r, int c) const { return Lane(C + (long long)z * sC, ldc, row, col, r, c); }
@@ -586,6 +588,7 @@ template <bool BLK>
 struct EpiBf16 {                 // C = bf16(acc), row-major or blocked
     bf16_t *C; long long ldc, sC;
     static constexpr int VEC = 8;
+    static constexpr NtOut OUT = NT_BF16;
     typedef NoAux Aux;
     typedef EpiPtr<bf16_t, BLK> Lane;
     __device__ Lane lane(int z, int row, int col, int r, int c) const { return Lane(C + (long long)z * sC, ldc, row, col, r, c); }
@@ -611,6 +614,7 @@ struct EpiBias {
 struct EpiBiasBf16 {             // C = bf16(acc + bias)
     const float *bias; long long sBias; bf16_t *C; long long ldc, sC; int N;
     static constexpr int VEC = 8;
+    static constexpr NtOut OUT = NT_BF16;
     typedef NoAux Aux;
     struct Lane { EpiPtr<bf16_t, false> o; EpiBias<8> b; };
     __device__ Lane lane(int z, int row, int col, int r, int c) const
@@ -633,6 +637,7 @@ struct EpiBiasGelu {             // h = acc + b1; H = bf16(gelu'(h)); A = bf16(g
     // saves the whole GELU evaluation in the data-gradient epilogue.
     const float *bias; long long sBias; bf16_t *H; long long sH; bf16_t *A; long long sA; long long ld;
     static constexpr int VEC = 8;
+    static constexpr NtOut OUT = NT_GELU;
     typedef NoAux Aux;
     struct Lane { EpiPtr<bf16_t, true> h, a; EpiBias<8> b; };
     __device__ Lane lane(int z, int row, int col, int r, int c) const
@@ -660,6 +665,7 @@ struct EpiBiasGelu {             // h = acc + b1; H = bf16(gelu'(h)); A = bf16(g
 struct EpiBiasResidual {         // x_out = x_in + acc + b2
     const float *bias; long long sBias; const float *Xin; float *Xout; long long sX; long long ld;
     static constexpr int VEC = 4;
+    static constexpr NtOut OUT = NT_RESIDUAL;
     typedef float4 Aux;
     struct Lane { EpiPtr<const float, false> x; EpiPtr<float, false> o; EpiBias<4> b; };
     __device__ Lane lane(int z, int row, int col, int r, int c) const
@@ -677,6 +683,7 @@ struct EpiBiasResidual {         // x_out = x_in + acc + b2
 struct EpiGeluBwd {              // dh = acc * gelu'(h), H holding gelu'(h) from the forward pass; both blocked
     const bf16_t *H; long long sH; bf16_t *DH; long long sDH; long long ld;
     static constexpr int VEC = 8;
+    static constexpr NtOut OUT = NT_FACTOR;
     typedef bf16x8 Aux;
     struct Lane { EpiPtr<const bf16_t, true> h; EpiPtr<bf16_t, true> o; };
     __device__ Lane lane(int z, int row, int col, int r, int c) const
@@ -694,57 +701,26 @@ struct EpiGeluBwd {              // dh = acc * gelu'(h), H holding gelu'(h) from
     }
 };
 
-// Tile shape of an NT GEMM (BM, BN, wavefronts in M, in N, groups, per SIMD, stages) by the number of tiles and the
-// length of the contraction, from timing every GEMM of the model with every shape on MI355X (us; batch x tokens x
-// width x hidden, the two numbers a GELU forward GEMM with N = hidden and a bf16-output one with N = width):
-//                              256x256, 1 WG/CU   128x256, 2 WG/CU   128x128, 3 WG/CU   64x64, 4 WG/CU
-//   8 x 12608 x 768 x 3072        577 / 404          561 / 424           629 / 526            -
-//   2 x 12608 x 768 x 3072        155 / 134          140 / 115           154 / 111         210 / 176
-//   8 x 12608 x 384 x 1536        213 / 163          200 / 159           201 / 142         262 / 238
-//   8 x 1576 x 768 x 3072          92 / 68            87 / 73             83 / 65          106 / 90
-//   8 x 1040 x 192 x 768         18.3 / 19.1        12.9 / 12.1         11.9 / 8.7        12.6 / 8.0
-//   2 x 400 x 768 x 3072         25.5 / 54.0        16.7 / 30.7         11.6 / 23.9       12.1 / 17.1
-//   2 x 1040 x 192 x 768         16.9 / 18.6        11.6 / 11.4          8.0 / 8.0         5.9 / 5.9
-// Two workgroups per compute unit overlap one's epilogue with the other's main loop, which pays at K = 768, where
-// the epilogue is half the time (426 against 439 us for a plain bf16 output of N = 3072); at K = 3072 the larger
-// tile's smaller copy volume wins once there are enough tiles for several rounds of the chip.  The smaller tiles
-// are for problems that would leave compute units without work: below two rounds of 128 x 256 (or where it would
-// pad N by a fifth or more) 128 x 128, and below 160 of those (768 where they would pad N by a third or more: 2 x 2228 x 192 x
-// 192 6.5 us, 64 x 64 5.3) 64 x 64.  A contraction of 1024 and more with at most a tile of those per compute unit is shared by
-// two groups of wavefronts: 0.84 of the time (18 problems, 0.76 to 0.89); at 512 to 1023 0.93, not worth another order of
-// summation, below that and with more tiles the same or slower; four groups 0.87 to 1.3.
-enum NtShape { NT_256x256, NT_128x256, NT_128x128, NT_64x64, NT_64x64_2GROUPS };
-static NtShape nt_shape(const GemmNT &p, int batch)
-{
-    auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * batch; };
-    const bool wide = 5LL * ((p.N + 255) / 256) * 256 < 6LL * p.N;
-    if (wide && p.K >= 1024 && tiles(256, 256) >= 1024) return NT_256x256;
-    if (wide && tiles(128, 256) >= 1024) return NT_128x256;
-    if (tiles(128, 128) >= (p.N <= 192 && p.N % 128 != 0 ? 768 : 160)) return NT_128x128;
-    return p.K >= 1024 && p.K % 64 == 0 && tiles(64, 64) <= 256 ? NT_64x64_2GROUPS : NT_64x64;
-}
-// wavefronts of all tiles of a batch entry
-static int nt_units(const GemmNT &p, int batch)
-{
-    auto tiles = [&](int bm, int bn) { return ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
-    switch (nt_shape(p, batch)) {
-    case NT_256x256: return 8 * tiles(256, 256);
-    case NT_128x256: return 4 * tiles(128, 256);
-    case NT_128x128: return 4 * tiles(128, 128);
-    default: return 4 * tiles(64, 64);
-    }
-}
+// The shapes of nt_plan.h with their wavefronts along M and N and the wavefronts per SIMD that the registers are budgeted for.
 // BLKA: the activation operand is blocked (the weights always are).
 template <bool BLKA, class Epi>
 static hipError_t gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
-    switch (nt_shape(p, batch)) {
-    case NT_256x256: return launch_gemm_nt<256, 256, 2, 4, 1, 2, 4, BLKA>(p, epi, batch, s);
-    case NT_128x256: return launch_gemm_nt<128, 256, 1, 4, 1, 2, 3, BLKA>(p, epi, batch, s);
-    case NT_128x128: return launch_gemm_nt<128, 128, 2, 2, 1, 3, 3, BLKA>(p, epi, batch, s);
-    case NT_64x64_2GROUPS: return launch_gemm_nt<64, 64, 2, 2, 2, 4, 4, BLKA>(p, epi, batch, s);
-    default: return launch_gemm_nt<64, 64, 2, 2, 1, 4, 4, BLKA>(p, epi, batch, s);
+    switch (nt_shape(Epi::OUT, p.M, p.N, p.K, batch, gemm_cu_count())) {
+    case NT_256x256: return launch_gemm_nt<NT_256x256, 2, 4, 2, BLKA>(p, epi, batch, s);
+    case NT_128x256: return launch_gemm_nt<NT_128x256, 1, 4, 2, BLKA>(p, epi, batch, s);
+    case NT_128x128_LONG: return launch_gemm_nt<NT_128x128_LONG, 2, 2, 2, BLKA>(p, epi, batch, s);
+    case NT_128x128: return launch_gemm_nt<NT_128x128, 2, 2, 3, BLKA>(p, epi, batch, s);
+    case NT_64x64_LONG: return launch_gemm_nt<NT_64x64_LONG, 2, 2, 2, BLKA>(p, epi, batch, s);
+    default: return launch_gemm_nt<NT_64x64, 2, 2, 4, BLKA>(p, epi, batch, s);
     }
+}
+// wavefronts of all tiles of a batch entry
+template <class Epi>
+static int nt_units(const GemmNT &p, int batch)
+{
+    const NtShape shape = nt_shape(Epi::OUT, p.M, p.N, p.K, batch, gemm_cu_count());
+    return (int)nt_tiles(shape, p.M, p.N, 1) * (shape == NT_256x256 ? 8 : 4);
 }
 #define TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
 
@@ -972,7 +948,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         EpiLoss epi{w.X + (long long)(nsub * L) * Md, w.sX, w.DX, w.sDX, w.DXb + (long long)(w.defer ? nsub * L - 1 : 0) * Md, w.sDXb,
                     w.LPART, w.sLPART, d, 1.0f / sqrtf((float)d), inv};
         TRY(gemm_nt<true>(p, epi, K, s));
-        loss_parts = nt_units(p, K);                     // summed up with the last LayerNorm gradients
+        loss_parts = nt_units<EpiLoss>(p, K);                     // summed up with the last LayerNorm gradients
     }
 
     // The weight gradients of one block's MLP half and of its attention half (w.defer: as the first of all blocks')

@@ -1,0 +1,39 @@
+"""The estimates behind the tile shapes (csrc/nt_plan.h): finite, growing with the work, the shape taken is the cheapest of those allowed,
+and the shapes at the sizes that the estimates were fitted to besides (CPU)."""
+import math
+import random
+import shutil
+
+import pytest
+
+import nt_host
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+def test_shapes_of_random_products():
+    rng = random.Random(5)
+    products = []
+    for _ in range(400):
+        M, N, K = int(math.exp(rng.uniform(0, math.log(300000)))), 64 * rng.randint(1, 72), 64 * rng.randint(1, 72)
+        products.append((rng.choice(nt_host.OUTPUTS), M, N, K, rng.randint(1, 40)))
+    for (out, M, N, K, batch), (shape, tiles, us) in zip(products, nt_host.shapes(products)):
+        allowed = [i for i, s in enumerate(nt_host.SHAPES) if not (s == "128x256" and K < 256) and not (s == "256x256" and K < 1024)]
+        assert all(math.isfinite(v) and v > 0 for v in us)
+        assert nt_host.SHAPES.index(shape) == min(allowed, key=lambda i: us[i]), (out, M, N, K, batch)
+        bm, bn = map(int, shape.split()[0].split("x"))
+        assert tiles == -(-M // bm) * -(-N // bn) * batch
+
+
+def test_estimates_grow_with_the_work():
+    sizes = [("gelu", M, 768, K, 4) for K in (64, 256, 1024, 4096) for M in (64, 1000, 12608, 100000)]
+    rows = [us for _, _, us in nt_host.shapes(sizes)]
+    for i in range(len(sizes)):
+        for j in range(i):
+            if sizes[j][1] <= sizes[i][1] and sizes[j][3] <= sizes[i][3]:
+                assert all(a <= b * (1 + 1e-12) for a, b in zip(rows[j], rows[i])), (sizes[j], sizes[i])
+
+
+def test_shapes_of_the_encoder():
+    got = nt_host.shapes([p[1:] for p in nt_host.model_products(768, 3072, True, 12608, 8)])
+    assert [g[0] for g in got] == ["128x256", "128x256", "128x256", "256x256", "128x256", "128x256", "256x256", "128x256", "256x256"]
