@@ -56,7 +56,7 @@ struct ResWs {
     long long mdB, mdhB;               // elements of one blocked [M][d] / [M][dh] activation
     long long wB[2];                   // elements of one blocked [d][dh] / [dh][d] weight
     bf16_t *WTt;                       // [d][d], shared: teacher map transposed
-    float *PART;   long long sPART;    // [2][wave_rows][d] partial dgamma, dbeta
+    float *PART;   long long sPART;    // [2][rows of partial sums][d] partial dgamma, dbeta
     float *LPART;  long long sLPART;   // loss partials
     bf16_t *ZERO;                      // 256 bytes of zeros (stand-in rows of ragged GEMM slabs)
     float *SPLITK; long long split_floats;   // partial weight gradients of a launch, [K][ranges][its part of a worker's gradient]
@@ -108,8 +108,8 @@ static ResWs carve(const ModelDims &dm, void *ws, size_t *total)
     w.W1b = (bf16_t *)take(w.sW, 2, K);  w.W1Tb = (bf16_t *)take(w.sW, 2, K);
     w.W2b = (bf16_t *)take(w.sW, 2, K);  w.W2Tb = (bf16_t *)take(w.sW, 2, K);
     w.WTt = (bf16_t *)take(blk_elems(d, d), 2, 1);
-    const long long wave_rows = ln_bwd_plan(K, M, d).waves;
-    w.sPART = padded((w.defer ? sub : 1) * 2 * wave_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
+    const long long part_rows = ln_bwd_plan(K, M, d).waves;
+    w.sPART = padded((w.defer ? sub : 1) * 2 * part_rows * d, 4); w.PART = (float *)take(w.sPART, 4, K);
     w.sLPART = padded(4 * ((M + 63) / 64) * (d / 64) + 8, 4);   // a wavefront of a tile each: most for 64 x 64
      w.LPART = (float *)take(w.sLPART, 4, K);
     w.ZERO = (bf16_t *)take(128, 2, 1);
@@ -314,11 +314,13 @@ __global__ __launch_bounds__(256) void sample_ln_kernel(float *__restrict__ X, l
 //   dn = du*gamma; dx_out = dx_in + rstd*(dn - mean(dn) - xhat*mean(dn*xhat))
 // dx_out may be dx_in (each element is read and then written by the same lane): the launcher does
 // that, so the update of dx is one stream of addresses instead of two.
-// and per-wavefront partial sums of dgamma = sum_m du*xhat, dbeta = sum_m du (reduced by
-// colsum_final_kernel).  TODX: the first sub-block's input is data, whose gradient nobody reads: only the sums then.
+// and partial sums of dgamma = sum_m du*xhat, dbeta = sum_m du (reduced by
+// colsum_final_kernel) of each workgroup's W wavefronts together.  TODX: the first sub-block's input is data, whose gradient nobody
+// reads: only the sums then.
 // NT: all but the bf16 gradient, which the next products read, with streaming accesses (ln_stream).
-template <int VPL, int LPR, int R, bool NT, typename TDU, bool TODX>
-__global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU, long long sDU,
+// W = 1: a wavefront's sums are a partial row by themselves, four wavefronts a workgroup.
+template <int VPL, int LPR, int R, bool NT, typename TDU, bool TODX, int W>
+__global__ __launch_bounds__(W == 1 ? 256 : 64 * W) void ln_bwd_kernel(const TDU *__restrict__ DU, long long sDU,
                                                      const float *__restrict__ X, long long sX,
                                                      const float *__restrict__ MU,
                                                      const float *__restrict__ RSTD, long long sStat,
@@ -327,12 +329,13 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU,
                                                      float *DXout, long long sDX,
                                                      bf16_t *__restrict__ DXb, long long sDXb,
                                                      float *__restrict__ PART, long long sPART,
-                                                     int wave_rows, int M, int d)
+                                                     int part_rows, int M, int d)
 {
     constexpr int G = 64 / LPR;                          // rows side by side
-    const int z = blockIdx.y;
-    const int wr = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & (LPR - 1), grp = (threadIdx.x & 63) / LPR;
-    if (wr >= wave_rows) return;
+    __shared__ float sums[W == 1 ? 1 : W][W == 1 ? 1 : 2][W == 1 ? 1 : 4 * VPL * LPR];
+    const int z = blockIdx.y, wave = threadIdx.x >> 6, wave_rows = part_rows * W;
+    const int wr = blockIdx.x * (W == 1 ? 4 : W) + wave, lane = threadIdx.x & (LPR - 1), grp = (threadIdx.x & 63) / LPR;
+    if (W == 1 && wr >= wave_rows) return;
     const float *gam = theta + (long long)z * sTh + off_gamma;
     const TDU *du_z = DU + (long long)z * sDU;
     const float *x_z = X + (long long)z * sX, *di_z = DXin + (long long)z * sDX;
@@ -423,10 +426,29 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TDU *__restrict__ DU,
             for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int o = LPR; o < 64; o <<= 1) { dg[c][e] += __shfl_xor(dg[c][e], o, 64); db[c][e] += __shfl_xor(db[c][e], o, 64); }
-        if (grp > 0) return;
+        if (W == 1 && grp > 0) return;
+    }
+    if constexpr (W > 1) {                               // the wavefronts' sums, in order
+        if (grp == 0) {
+#pragma unroll
+            for (int c = 0; c < VPL; ++c) {
+                const int j = (lane + c * LPR) * 4;
+                *(float4 *)&sums[wave][0][j] = make_float4(dg[c][0], dg[c][1], dg[c][2], dg[c][3]);
+                *(float4 *)&sums[wave][1][j] = make_float4(db[c][0], db[c][1], db[c][2], db[c][3]);
+            }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < 2 * d; i += 64 * W) {
+            const int beta = i >= d, j = i - beta * d;
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < W; ++w) s += sums[w][beta][j];
+            PART[(long long)z * sPART + ((long long)beta * part_rows + blockIdx.x) * d + j] = s;
+        }
+        return;
     }
     float *pg = PART + (long long)z * sPART + (long long)wr * d;
-    float *pb = PART + (long long)z * sPART + ((long long)wave_rows + wr) * d;
+    float *pb = PART + (long long)z * sPART + ((long long)part_rows + wr) * d;
 #pragma unroll
     for (int c = 0; c < VPL; ++c) {
         const int j = (lane + c * LPR) * 4;
@@ -808,7 +830,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     const long long Md = (long long)M * d;            // a row-major [M][d] array (fp32 state and its relatives)
     const long long MdB = w.mdB, MdhB = w.mdhB;       // a blocked [M][d] / [M][dh] bf16 array
     const LnBwdPlan ln_plan = ln_bwd_plan(K, M, d);
-    const int wave_rows = (int)ln_plan.waves;
+    const int part_rows = (int)ln_plan.waves;
 
     AttnArgs att{};
     if (heads > 0) {
@@ -844,18 +866,19 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
     // (d loss / d state sub, also in bf16), and the LayerNorm parameter gradients
     int loss_parts = 0;
     auto ln_bwd = [&](int sub, long long off_gamma) -> hipError_t {
-        dim3 grid((unsigned)((wave_rows + 3) / 4), (unsigned)K);
+        dim3 grid((unsigned)(ln_plan.few ? part_rows : (part_rows + 3) / 4), (unsigned)K);
         bf16_t *const dxb_to = w.DXb + (long long)(w.defer && sub > 0 ? sub - 1 : 0) * Md;   // of the sub-block before, if there is one
 #define LN_BWD_ARGS w.X + (long long)sub * Md, w.sX, w.MU + (long long)sub * M, w.RSTD + (long long)sub * M, w.sStat, theta, P, off_gamma, \
-                    w.DX, w.DX, w.sDX, dxb_to, w.sDXb, w.PART + (w.defer ? 2LL * sub * wave_rows * d : 0), w.sPART, wave_rows, M, d
-#define LN_BWD_R(VPL, LPR, R, NT) do { \
-            if (du16 && sub > 0) ln_bwd_kernel<VPL, LPR, R, NT, bf16_t, true><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
-            else if (du16) ln_bwd_kernel<VPL, LPR, R, NT, bf16_t, false><<<grid, 256, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
-            else if (sub > 0) ln_bwd_kernel<VPL, LPR, R, NT, float, true><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); \
-            else ln_bwd_kernel<VPL, LPR, R, NT, float, false><<<grid, 256, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); } while (0)
-#define LN_BWD(VPL, LPR) do { if (ln_plan.few) LN_BWD_R(VPL, LPR, ln_bwd_rows(VPL, true), false); \
-                              else if (!stream) LN_BWD_R(VPL, LPR, ln_bwd_rows(VPL, false), false); \
-                              else LN_BWD_R(VPL, LPR, ln_bwd_rows(VPL, false), true); } while (0)
+                    w.DX, w.DX, w.sDX, dxb_to, w.sDXb, w.PART + (w.defer ? 2LL * sub * part_rows * d : 0), w.sPART, part_rows, M, d
+#define LN_BWD_R(VPL, LPR, R, NT, W) do { \
+            const unsigned threads = W == 1 ? 256 : 64 * W; \
+            if (du16 && sub > 0) ln_bwd_kernel<VPL, LPR, R, NT, bf16_t, true, W><<<grid, threads, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
+            else if (du16) ln_bwd_kernel<VPL, LPR, R, NT, bf16_t, false, W><<<grid, threads, 0, s>>>(DU16, sDU16, LN_BWD_ARGS); \
+            else if (sub > 0) ln_bwd_kernel<VPL, LPR, R, NT, float, true, W><<<grid, threads, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); \
+            else ln_bwd_kernel<VPL, LPR, R, NT, float, false, W><<<grid, threads, 0, s>>>(w.DU, w.sDU, LN_BWD_ARGS); } while (0)
+#define LN_BWD(VPL, LPR) do { if (ln_plan.few) LN_BWD_R(VPL, LPR, 1, false, LN_FEW_WAVES); \
+                              else if (!stream) LN_BWD_R(VPL, LPR, ln_bwd_rows(VPL), false, 1); \
+                              else LN_BWD_R(VPL, LPR, ln_bwd_rows(VPL), true, 1); } while (0)
         LN_BY_WIDTH(d, LN_BWD);
 #undef LN_BWD
 #undef LN_BWD_R
@@ -863,7 +886,7 @@ hipError_t launch_resmlp_grad(const ModelDims &dm, const float *theta, float *g,
         TRY(hipGetLastError());
         // the sums over wavefronts: after each pass, or after the last one for all where the partial rows are kept
         if (w.defer && sub > 0) return hipSuccess;
-        ColsumArgs q{w.PART, w.sPART, wave_rows, d, g, P, {0, per_attn}, per_block, nsub, w.defer ? 2 * nsub * L : 2,
+        ColsumArgs q{w.PART, w.sPART, part_rows, d, g, P, {0, per_attn}, per_block, nsub, w.defer ? 2 * nsub * L : 2,
                      w.LPART, w.sLPART, loss_parts, 0.5f / ((float)M * (float)d), loss};
         if (!w.defer || nsub == 1) { q.off[0] = off_gamma; q.nsub = 1; }
         colsum_final_kernel<<<dim3((unsigned)((d + 63) / 64), (unsigned)K, (unsigned)(q.sums + (sub == 0 ? 1 : 0))), 64 * COLSUM_WAVES, 0, s>>>(q);
