@@ -12,7 +12,8 @@
 // of its columns, which it holds for all workers, and in a recorded iteration the averaging and
 // the scheduler's step.  Iterations enqueued together (qsr_run) of a worker that fits one workgroup need no launch between
 // them at all: linreg_run_kernel.  256 iterations of 4 x 1024 features x 32 samples: 2879 us with four
-// kernels per iteration (residuals, gradient, update, averaging), 1900 with two, 646 together.
+// kernels per iteration (residuals, gradient, update, averaging), 1900 with two, 502 together
+// (644 where each of the 28 rounds ended a launch).
 #include "opt_elem.h"
 #include "philox.h"
 #include "qsr_internal.h"
@@ -60,8 +61,13 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Iterations together: X and the observation noise of RUN_SLOTS iterations at a time, drawn ahead
 constexpr int RUN_SLOTS = LINREG_RUN_AHEAD;
 static inline long long slot_worker_floats(const ModelDims &d) { return d.B * run_shape(d).d4 + (d.B + 3) / 4 * 4; }
-// ... and two copies of the parameters
-static inline long long run_floats(const ModelDims &d) { return RUN_SLOTS * d.K * slot_worker_floats(d) + 2LL * d.K * run_shape(d).d4; }
+// ... and what the workers exchange where a round ends, two rounds of it: a word for each parameter, [worker][wavefront of the row][of a
+// lane's four][lane]
+static inline long long run_words(const ModelDims &d) { return 2LL * d.K * run_shape(d).row * 256; }
+static inline long long run_floats(const ModelDims &d)
+{
+    return (RUN_SLOTS * d.K * slot_worker_floats(d) + 1) / 2 * 2 + 2 * run_words(d);
+}
 
 // exchanges inside a wavefront: lane l gets the value of lane l ^ 8, l ^ 7, l ^ 2, l ^ 1
 template <int CTRL>
@@ -273,14 +279,12 @@ __global__ __launch_bounds__(320) void linreg_residual_kernel(
 }
 
 // Step 3 with the OPT update, one workgroup per 64 columns of KW workers.  The samples of a worker are cut into `runs` runs of
-// `per`, whose sums are added in order; each of its S wavefronts (threadIdx.y) takes `each` consecutive ones, eight samples'
-// loads in flight, and leaves their sums in LDS, and the first one adds them up and updates the columns.  All K workers
-// (KW = K, S = 16 / K): the launch can average as well (average, if the device's scheduler says that a round ends),
-// with the averaging kernel's arithmetic.  KW = 1, a wavefront per run: iterations one by one of workers that
-// linreg_run_kernel takes too, in its runs either way.  st_next as in the update kernels.  Bound by latency, of the
-// instructions too (each launch fetches them anew: 16 samples unrolled, or the next eight requested ahead in code of their
-// own, 0.5 to 1 us slower), so that wavefronts of one run (SEVERAL false) have no ends of runs to look for: 16 x 1100 x 32 11.2 us an
-// iteration, 12.3 with them.  4 x 1024 x 32, KW = 1: 3.4 us (4.2 with KW = K).
+// `per`, whose sums are added in order; each of its wavefronts (threadIdx.y) takes one, eight samples' loads in
+// flight, and leaves their sum in LDS, and the first one adds them up and updates the columns.  KW = 1: workers that
+// linreg_run_kernel takes too, in its runs.  Else all K, 16 / K wavefronts each: the launch can average as well (average, if the
+// device's scheduler says that a round ends), with the averaging kernel's arithmetic.  st_next as in the update kernels.  Bound by
+// latency, of the instructions too (each launch fetches them anew: 16 samples unrolled, or the next eight requested ahead
+// in code of their own, 0.5 to 1 us slower).  4 x 1024 x 32, KW = 1: 3.4 us (4.2 with KW = K).
 struct LinregStep {
     float *theta, *g, *s0, *s1;          // s1: AdamW
     const StepScalars *sc;
@@ -290,18 +294,18 @@ struct LinregGradStep {
     const float *X, *r;
     LinregStep p;
     float *loss;
-    int K, runs, each, per, B, average, apart;   // apart: the scheduler's step has a workgroup of its own
+    int K, runs, per, B, average, apart;   // apart: the scheduler's step has a workgroup of its own
     long long d, ldx;
     const DevState *st;
     DevState *st_next;
     SchedParams sp;
 };
-template <bool ADAMW, bool SEVERAL>
+template <bool ADAMW>
 __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(LinregGradStep a)
 {
     const LinregStep &p = a.p;
     const DevState *const st = a.st;
-    const int runs = a.runs, each = a.each, per = a.per, B = a.B;
+    const int runs = a.runs, per = a.per, B = a.B;
     const long long d = a.d, ldx = a.ldx;
     extern __shared__ float step_part[];                 // [KW][runs][64]
     float (*part)[64] = (float (*)[64])step_part;
@@ -325,14 +329,11 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(LinregGradStep
         th = p.theta[o]; m = p.s0[o];
         if (ADAMW) v = p.s1[o];
     }
-    const int run0 = min(runs, s * each), run1 = min(runs, run0 + each);
-    const int i0 = min(B, run0 * per), i1 = min(B, run1 * per);
+    const int i0 = min(B, s * per), i1 = min(B, i0 + per);
     const float *rk = a.r + (long long)k * B;
     const float rv = i0 + lane < i1 ? rk[i0 + lane] : 0.f;      // the wavefront's residuals, one a lane
     const float *row = a.X + ((long long)k * B + i0) * ldx;
     const unsigned col = (unsigned)min(j, d - 1);
-    float (*to)[64] = part + kw * runs + run0;           // of the run at hand, which ends behind sample `end`
-    int end = i0 + per;
     float acc = 0.f;
     for (int i = i0; i < i1; i += 8) {                   // a short last group is filled up with weight 0
         float xv[8];
@@ -342,12 +343,9 @@ __global__ __launch_bounds__(1024) void linreg_grad_update_kernel(LinregGradStep
             row += i + u + 1 < i1 ? ldx : 0;
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            acc = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(rv), i - i0 + u)), xv[u], acc);
-            if (SEVERAL && i + u + 1 == end && end < i1) { (*to++)[lane] = acc; acc = 0.f; end += per; }
-        }
+        for (int u = 0; u < 8; ++u) acc = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(rv), i - i0 + u)), xv[u], acc);
     }
-    if (i0 < i1) (*to)[lane] = acc;
+    if (i0 < i1) part[kw * runs + s][lane] = acc;
     if (blockIdx.x == 0 && s == 0) {
         float l = 0.f;
         for (int i = lane; i < B; i += 64) l = fmaf(rk[i], rk[i], l);
@@ -477,31 +475,16 @@ bool linreg_can_fuse(const ModelDims &d)
 }
 
 // How linreg_grad_update_kernel shares the samples out
-struct StepShape { int KW, S, runs, each, per; };
-static StepShape step_shape(const ModelDims &d, bool average)
+struct StepShape { int KW, S, runs, per; };
+static StepShape step_shape(const ModelDims &d)
 {
-    const bool run = linreg_can_run(d), alone = run && !average;
+    const bool run = linreg_can_run(d);
     StepShape q;
-    q.KW = alone ? 1 : d.K;
-    q.S = alone ? run_shape(d).groups : 16 / d.K;
+    q.KW = run ? 1 : d.K;
+    q.S = run ? run_shape(d).groups : 16 / d.K;
     q.per = run ? run_shape(d).per : (int)((d.B + q.S - 1) / q.S);
-    q.runs = (int)((d.B + q.per - 1) / q.per);           // none of them empty
-    q.each = (q.runs + q.S - 1) / q.S;
+    q.runs = (int)((d.B + q.per - 1) / q.per);           // at most S, none of them empty
     return q;
-}
-
-// A round of one iteration in two kernels takes longer with the samples of a wavefront, as linreg_run_kernel with the samples
-// and columns of a workgroup.  us a round, two kernels / linreg_run_kernel (two replayed kernels with samples cut into 16 / K runs):
-//   1 x 117 x 38 6.5 / 7.2 (7.6)    4 x 1024 x 32 7.1 / 9.7 (7.6)   16 x 1024 x 8 8.1 / 9.1 (7.9)    3 x 512 x 64 8.0 / 9.5 (8.2)
-//   8 x 256 x 128 16.1 / 10.2 (14.5)   7 x 64 x 128 15.3 / 8.5 (13.5)   16 x 1024 x 32 12.3 / 11.1 (11.7)   6 x 668 x 28 9.0 / 9.3 (8.1)
-// Over 245 random sizes the choice is within 0.6 % of the better one on average (12.5 % at most), and 9 % faster than the
-// replayed kernels; slower than those where five runs go to four to six workers' wavefronts unevenly: 4 x 668 x 25 8.5 (7.6).
-bool linreg_single_rounds(const ModelDims &d)
-{
-    if (!linreg_can_run(d)) return false;
-    const StepShape q = step_shape(d, true);
-    const int samples = q.each * q.per;
-    return samples <= 8 || (samples <= 16 && (q.per > 4 || d.d_in > 768)) || (samples <= 24 && q.per > 4 && d.d_in > 768);
 }
 
 hipError_t launch_linreg_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
@@ -516,17 +499,17 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
                                      hipStream_t s)
 {
     if (!linreg_can_fuse(d)) return hipErrorInvalidValue;
-    const StepShape q = step_shape(d, average);
-    if (q.each * q.per > 64) return hipErrorInvalidValue;        // a wavefront's residuals lie one a lane
+    const StepShape q = step_shape(d);
+    // a wavefront's residuals lie one a lane; the average needs all workers in a workgroup
+    if (q.per > 64 || (average && q.KW < d.K)) return hipErrorInvalidValue;
     // The scheduler's step in a workgroup of its own: off the critical path, a workgroup more to start.  us an iteration at rounds
     // of one, apart / in the last wavefront: 1 x 4096 x 128 8.7 / 9.1, 12 x 2048 x 10 8.0 / 8.3, 5 x 1027 x 100 12.7 / 12.6, 3 x 1003 x 17
     // (single iterations) 7.2 / 6.9
     const bool apart = st_next != nullptr && d.d_in > 1536;
-    const LinregGradStep a{(const float *)ws, linreg_r(d, ws), LinregStep{theta, g, s0, s1, sc, c1, c2, eps}, loss, d.K, q.runs, q.each,
+    const LinregGradStep a{(const float *)ws, linreg_r(d, ws), LinregStep{theta, g, s0, s1, sc, c1, c2, eps}, loss, d.K, q.runs,
                            q.per, (int)d.B, average ? 1 : 0, apart ? 1 : 0, d.d_in, row_stride(d), st, st_next, sp};
     const dim3 grid((unsigned)((d.d_in + 63) / 64 + (apart ? 1 : 0)), (unsigned)(d.K / q.KW)), block(64, (unsigned)q.S, (unsigned)q.KW);
-    auto kern = q.each > 1 ? (s1 ? linreg_grad_update_kernel<true, true> : linreg_grad_update_kernel<false, true>)
-                           : (s1 ? linreg_grad_update_kernel<true, false> : linreg_grad_update_kernel<false, false>);
+    auto kern = s1 ? linreg_grad_update_kernel<true> : linreg_grad_update_kernel<false>;
     kern<<<grid, block, (size_t)q.KW * q.runs * 64 * sizeof(float), s>>>(a);
     return hipGetLastError();
 }
@@ -534,29 +517,40 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // ---------------------------------------------------------------------------------------------
 // iterations together
 // ---------------------------------------------------------------------------------------------
-// Consecutive iterations of one round in one launch, a workgroup of 16 wavefronts per worker: its parameters and momentum stay
+// Consecutive iterations in one launch, a workgroup of 16 wavefronts per worker: its parameters and momentum stay
 // in registers, an iteration's inputs too, from the residuals to the gradient, and what has to be summed across wavefronts
 // goes through LDS with two barriers per iteration.  The inputs depend on nothing that the iterations compute: the
 // launch's other workgroups draw those of later iterations into the workspace (slot = iteration mod RUN_SLOTS), so that a worker
 // only reads its own, one iteration ahead, into a second set of registers; these reads (128 KiB an iteration at 32 x 1024, 2000
 // cycles of a compute unit's first-level cache) are spread over the iteration, where a burst of them holds up
 // the arithmetic behind it (2.1 us an iteration, spread 1.5, without them 1.1).
-// Between launches of a call the parameters stay in the workspace, two copies that launches read and write in turn, so that a
-// round's averaging is the next launch's: every worker reads all rows, where the device's scheduler says that the round ended
-// (a launch of its own: 4 us a round).  An iteration at rounds of 8 (us; two kernels an iteration): 4 x 1024 x 32 2.5 (7.3), 16 x
-// 1024 x 32 3.2 (11.3), 8 x 256 x 128 2.8 (14), 1 x 64 x 128 2.3 (7.1), 1 x 1024 x 8 1.6 (6.6).
+//
+// Where a round ends, which every workgroup takes from its own reading of the schedule, the workers hand each other their parameters
+// through the workspace: one 64-bit word for each, the value beside the iteration it is from, written and read past the
+// caches that XCDs do not share.  A reader that finds the iteration has the value, and no flag, fence or launch is needed.  Rounds of a
+// launch take two sets of words in turn: whoever writes a set again has read, in the other one, what all workers wrote behind
+// their reading of this one.  The launch that draws a call's first inputs fills the words with an iteration that ends no round of the call.
+// The wait is for workgroups that run or will: the K <= 16 workers are their launch's first workgroups, and the host
+// keeps to devices and streams with compute units for 16 such launches at once.  Should a launch all the same have waited RUN_POLLS times
+// (minutes), it waits no more and leaves NaN.
+// Bound by the round trips to memory, 1.5 us for one and the words' way there.  us an iteration at rounds of 1 / 2 / 8, against launches that
+// end with the round (those of one iteration: two kernels, the second averages):
+//   4 x 1024 features x 32 samples 4.0 / 2.8 / 2.0, 7.2 / 5.5 / 2.5;  16 x 1024 x 32 7.9 / 4.9 / 2.7, 11.0 / 6.6 / 2.8;
+//   16 x 257 x 8 5.7 / 3.5 / 1.7, 8.6 / 4.6 / 1.9;  1 x 256 x 64 2.4 / 1.9 / 1.6, 7.1 / 4.6 / 2.1
+// A lane's words next to each other instead of 64 apart take 0.7 us more a round, two workers a group of wavefronts at a time
+// 0.5 more up to four workers and 0.2 less at sixteen.
+constexpr int RUN_POLLS = 1 << 27;
 struct LinregRun {
-    LinregStep p;                        // p.theta: where the parameters go
-    const float *theta_in;               // where they come from: rows of ld_in (ld_out: p.theta's)
-    long long ld_in, ld_out;
-    const DevState *st_mean;             // != nullptr: averaged on the way in, if this state was the last of its round
+    LinregStep p;
     const float *wstar;
     float *slots, *loss;
+    unsigned long long *words;           // exchanged parameters: [2][K][row][4][64]
     int K, B, d, d4, per, n_it, n_draw, draw_off;   // n_draw iterations from the current one plus draw_off on
+    unsigned ends;                       // iterations that end a round, as the host's mirror expects
     float sigma;
     uint64_t seed;
     const DevState *st;
-    DevState *st_next, *st_last;         // after the launch's iterations, and before the last of them
+    DevState *st_next;                   // after the launch's iterations
     SchedParams sp;
 };
 
@@ -595,6 +589,9 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
     const long long k_floats = (long long)a.B * a.d4 + (a.B + 3) / 4 * 4;
     const int workers = a.n_it > 0 ? a.K + 1 : 0;
     if ((int)blockIdx.x >= workers) {
+        if (workers == 0)
+            for (int i = blockIdx.x * 1024 + threadIdx.x; i < 2 * a.K * ROW * 256; i += gridDim.x * 1024)
+                __hip_atomic_store(a.words + i, (unsigned long long)a.st->t << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         run_draw(a, blockIdx.x - workers, ((a.B * a.d + 3) / 4 + (a.B + 3) / 4 + 1023) / 1024, k_floats);
         return;
     }
@@ -602,16 +599,17 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
         if (threadIdx.x > 0) return;
         DevState nx = *a.st;
         SchedParams sp = a.sp;
-        sp.expect_sync = 0;                              // only the last iteration may end a round
-        for (int i = 0; i + 1 < a.n_it; ++i) sched_advance(&nx, sp);
-        *a.st_last = nx;
-        sched_advance(&nx, a.sp);
+        for (int i = 0; i < a.n_it; ++i) {
+            sp.expect_sync = (int)(a.ends >> i & 1);
+            sched_advance(&nx, sp);
+        }
         *a.st_next = nx;
         return;
     }
     __shared__ __attribute__((aligned(16))) float red[16 * PER][4];     // inner products: [sample][wavefront of its row]
     __shared__ float4 part[16][64];                                     // gradient: [wavefront][lane], four columns
     __shared__ float res[16 * PER];                                     // residuals of the last iteration
+    __shared__ float4 other[16][64];                                    // the averaging's, besides part
     const int k = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s = wave / ROW, cw = wave - s * ROW;
     const bool busy = s < GROUPS;                        // three wavefronts a row: one of the sixteen is left over
@@ -622,28 +620,12 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
 
     float th[4] = {0.f, 0.f, 0.f, 0.f}, m[4] = {0.f, 0.f, 0.f, 0.f}, v[4] = {0.f, 0.f, 0.f, 0.f}, ws[4] = {0.f, 0.f, 0.f, 0.f};
     float g[4] = {0.f, 0.f, 0.f, 0.f};
-    const bool mean = a.st_mean != nullptr && a.st_mean->h + 1 == a.st_mean->H;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         if (in && c + e < a.d) {
-            m[e] = a.p.s0[o + e]; ws[e] = a.wstar[c + e];
+            m[e] = a.p.s0[o + e]; ws[e] = a.wstar[c + e]; th[e] = a.p.theta[o + e];
             if (ADAMW) v[e] = a.p.s1[o + e];
-            if (!mean) th[e] = a.theta_in[k * a.ld_in + c + e];
         }
-    if (mean && in) {                                    // rows of the workspace: whole groups of four
-        float4 row[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) row[q] = *(const float4 *)(a.theta_in + min(q, a.K - 1) * a.ld_in + c);
-        float sum[4] = {0.f, 0.f, 0.f, 0.f}, err[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int q = 0; q < 16; ++q)
-            if (q < a.K) {
-                add_comp(sum[0], err[0], row[q].x); add_comp(sum[1], err[1], row[q].y);
-                add_comp(sum[2], err[2], row[q].z); add_comp(sum[3], err[3], row[q].w);
-            }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) th[e] = c + e < a.d ? (sum[e] + err[e]) / (float)a.K : 0.f;
-    }
     if (tid < 16 * PER) {                                // rows of fewer than four wavefronts
 #pragma unroll
         for (int e = 0; e < 4; ++e) red[tid][e] = 0.f;
@@ -660,8 +642,51 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    // the launch's per-iteration scalars, one iteration a lane
+    // the launch's per-iteration scalars, one iteration a lane, and the period of a round that starts behind it
     const StepScalars mine = a.p.sc[t0 + min(lane, a.n_it - 1)];
+    const int period = (int)min(get_H(a.sp, t0 + 1 + min(lane, a.n_it - 1)), 1ll << 20);
+    int to_go = (int)min(a.st->H - a.st->h, 1ll << 20);  // iterations to the end of the round
+    int set = 0, polls = 0;
+    // This worker's parameters to the others and everybody's mean, over the workers in order, each addition error-free: a worker a
+    // group of wavefronts, GROUPS at a time through LDS, two places in turn
+    auto average = [&](int it) {
+        const unsigned t = (unsigned)t0 + it + 1;
+        unsigned long long *const words = a.words + (set * a.K * ROW + cw) * 256 + lane;
+        set ^= 1;
+        if (s == 0 && in) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                __hip_atomic_store(words + k * ROW * 256 + e * 64, (unsigned long long)t << 32 | (unsigned)__float_as_int(th[e]),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        float sum[4] = {0.f, 0.f, 0.f, 0.f}, err[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < a.K; k0 += GROUPS) {
+            float4 (*const rows)[64] = k0 / GROUPS % 2 ? part : other;   // part: nobody reads it behind the first barrier here
+            if (in && k0 + s < a.K) {
+                unsigned long long w[4];
+                bool there;
+                do {
+                    there = true;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        w[e] = __hip_atomic_load(words + (k0 + s) * ROW * 256 + e * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) there &= (unsigned)(w[e] >> 32) == t;
+                } while (!there && ++polls < RUN_POLLS);
+                auto value = [&](int e) { return there ? __int_as_float((int)(unsigned)w[e]) : NAN; };
+                rows[wave][lane] = make_float4(value(0), value(1), value(2), value(3));
+            }
+            barrier();
+            if (in)
+                for (int q = 0; q < min(GROUPS, a.K - k0); ++q) {
+                    const float4 r = rows[cw + q * ROW][lane];
+                    add_comp(sum[0], err[0], r.x); add_comp(sum[1], err[1], r.y);
+                    add_comp(sum[2], err[2], r.z); add_comp(sum[3], err[3], r.w);
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) th[e] = in && c + e < a.d ? (sum[e] + err[e]) / (float)a.K : 0.f;
+    };
     auto scalar = [&](float x, int it) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), it)); };
     barrier();
     auto iterate = [&](int it, In &q, In &ahead) {
@@ -716,6 +741,10 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
             if (ADAMW) adamw_elem(th[e], g[e], m[e], v[e], sc.x, sc.y, sc.z, a.p.c1, a.p.c2, a.p.eps);
             else sgdm_elem(th[e], g[e], m[e], sc.x, a.p.c1, a.p.c2);
         }
+        if (--to_go == 0) {
+            to_go = __builtin_amdgcn_readlane(period, it);
+            average(it);
+        }
     };
     In q0, q1;
     load_noise(slot(0), q0);
@@ -729,7 +758,7 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (in && c + e < a.d) {
-                a.p.theta[k * a.ld_out + c + e] = th[e]; a.p.s0[o + e] = m[e]; a.p.g[o + e] = g[e];
+                a.p.theta[o + e] = th[e]; a.p.s0[o + e] = m[e]; a.p.g[o + e] = g[e];
                 if (ADAMW) a.p.s1[o + e] = v[e];
             }
     }
@@ -746,21 +775,18 @@ hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *
                              float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
                              const SchedParams &sp, hipStream_t s)
 {
-    if (!linreg_can_run(d) || span.n_it < 0 || span.n_draw < 0 || span.n_it > RUN_SLOTS || span.draw_off + span.n_draw > RUN_SLOTS)
+    if (!linreg_can_run(d) || span.n_it < 0 || span.n_draw < 0 || span.n_it > LINREG_RUN_MAX || span.draw_off + span.n_draw > RUN_SLOTS)
         return hipErrorInvalidValue;
     const RunShape q = run_shape(d);
     LinregRun a{};
     a.slots = linreg_slots(d, ws);
-    float *const kept = a.slots + RUN_SLOTS * d.K * slot_worker_floats(d);
-    auto copy = [&](int i) { return i < 0 ? theta : kept + (long long)i * d.K * q.d4; };
-    a.p = LinregStep{copy(span.out), g, s0, s1, sc, c1, c2, eps};
-    a.theta_in = copy(span.in);
-    a.ld_in = span.in < 0 ? d.d_in : q.d4; a.ld_out = span.out < 0 ? d.d_in : q.d4;
-    a.st_mean = span.in < 0 ? nullptr : span.st_mean;
+    a.words = (unsigned long long *)(a.slots + (RUN_SLOTS * d.K * slot_worker_floats(d) + 1) / 2 * 2);
+    a.p = LinregStep{theta, g, s0, s1, sc, c1, c2, eps};
+    a.ends = span.ends;
     a.wstar = wstar; a.loss = loss;
     a.K = d.K; a.B = (int)d.B; a.d = (int)d.d_in; a.d4 = q.d4; a.per = q.per;
     a.n_it = span.n_it; a.n_draw = span.n_draw; a.draw_off = span.draw_off;
-    a.sigma = d.data_sigma; a.seed = d.seed; a.st = span.st; a.st_next = span.st_next; a.st_last = span.st_last; a.sp = sp;
+    a.sigma = d.data_sigma; a.seed = d.seed; a.st = span.st; a.st_next = span.st_next; a.sp = sp;
     const int blocks = (int)((d.B * d.d_in + 3) / 4 + (d.B + 3) / 4 + 1023) / 1024;
     const unsigned grid = (unsigned)((a.n_it > 0 ? d.K + 1 : 0) + a.n_draw * d.K * blocks);
     if (grid == 0) return hipSuccess;

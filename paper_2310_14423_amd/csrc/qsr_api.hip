@@ -33,13 +33,13 @@ struct TimedPair {
 struct qsr_ctx {
     qsr_config cfg;
     hipStream_t stream;
-    int device;
+    int device, compute_units;
     float *params, *grads, *state0, *state1;
     const float *model_const;
     void *workspace;
     size_t workspace_bytes;
     // library-owned device memory
-    DevState *d_state;       // two copies; `cur` is the one the next kernels read (see ticked); two more for qsr_run's averaging
+    DevState *d_state;       // two copies; `cur` is the one the next kernels read (see ticked)
     int cur;
     bool ticked;             // the update kernel has advanced the scheduler (into the copy that is current now) for
                              // the local step whose qsr_maybe_sync is pending
@@ -373,13 +373,14 @@ static int init_impl(qsr_ctx *c, const float *theta0)
     HIP_TRY(hipGetDevice(&c->device));
     hipDeviceProp_t prop;
     HIP_TRY(hipGetDeviceProperties(&prop, c->device));
+    c->compute_units = prop.multiProcessorCount;
     if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0) return QSR_ENOGPU;
     {   // set-up of the entry point that must not allocate later: find its array on this device now
         int rc = clip_static_setup(nullptr);
         if (rc != QSR_OK) return rc;
     }
 
-    HIP_TRY(hipMalloc((void **)&c->d_state, 4 * sizeof(DevState)));
+    HIP_TRY(hipMalloc((void **)&c->d_state, 2 * sizeof(DevState)));
     HIP_TRY(hipMalloc((void **)&c->d_eta, T * sizeof(double)));
     HIP_TRY(hipMalloc((void **)&c->d_scal, T * sizeof(StepScalars)));
     HIP_TRY(hipMalloc((void **)&c->d_log_t, T * sizeof(long long)));
@@ -669,69 +670,51 @@ static int run_one_by_one(qsr_ctx *c, long long n)
     return QSR_OK;
 }
 
-// Least squares on workers that fit one workgroup: launches that end where a round does, each drawing inputs ahead for the
-// launches behind it, but none beyond this call.  Rounds of one iteration take two kernels instead, the second of which
-// averages, where that is faster (linreg_single_rounds); from launches behind one another they do so from SINGLE_ROUNDS
-// such rounds in a row on, since the parameters then go through the caller's array and a launch of the averaging.
-constexpr int SINGLE_ROUNDS = 4;
+// Least squares on workers that fit one workgroup: launches of up to LINREG_RUN_MAX iterations, rounds ending inside them, each
+// drawing inputs ahead for the launches behind it, but none beyond this call.  The first takes few, so that not many
+// inputs have to be drawn ahead of everything.
+constexpr long long LINREG_RUN_FIRST = 8;
 static int run_linreg(qsr_ctx *c, long long n)
 {
     const qsr_config &cfg = c->cfg;
     const bool sgd = cfg.opt == QSR_OPT_SGDM;
     const float c1 = (float)(sgd ? cfg.momentum : 1.0 - cfg.beta1), c2 = (float)(sgd ? cfg.weight_decay : 1.0 - cfg.beta2);
-    float *const state1 = sgd ? nullptr : c->state1;
     long long drawn = 0;                                 // iterations from the current one on
-    int from = -1, last = 0;                             // where the parameters are; the st_last of the next launch
-    auto launch = [&](const LinregSpan &span, const SchedParams &sp) {
-        return launch_linreg_run(c->dims, c->params, c->grads, c->state0, state1, c->model_const, c->workspace, c->d_loss,
-                                 c->d_scal, c1, c2, (float)cfg.eps, span, sp, c->stream);
-    };
-    // whether the rounds from iteration t on, the first of H iterations, are `rounds` of one iteration each
-    auto singles = [&](long long t, long long H, int rounds) {
-        if (!linreg_single_rounds(c->dims)) return false;
-        for (; rounds > 0 && H == 1; --rounds, ++t) H = host_get_H(c->sp, c->eta.data(), t + 1);
-        return rounds == 0;
+    auto launch = [&](const LinregSpan &span) {
+        return launch_linreg_run(c->dims, c->params, c->grads, c->state0, sgd ? nullptr : c->state1, c->model_const, c->workspace,
+                                 c->d_loss, c->d_scal, c1, c2, (float)cfg.eps, span, c->sp, c->stream);
     };
     while (n > 0) {
-        const long long left = c->m_H - c->m_h;
-        SchedParams sp = c->sp;
-        if (from < 0 && c->m_h == 0 && singles(c->m_t, c->m_H, 1)) {
-            sp.expect_sync = 1;
-            HIP_TRY(launch_linreg_residual(c->dims, c->params, c->model_const, c->workspace, st_cur(c), c->stream));
-            HIP_TRY(launch_linreg_grad_update(c->dims, c->params, c->grads, c->state0, state1, c->workspace, c->d_loss, c->d_scal,
-                                              c1, c2, (float)cfg.eps, st_cur(c), c->d_state + (c->cur ^ 1), true, sp, c->stream));
-            c->cur ^= 1;
-            mirror_advance(c);
-            c->t_host += 1;
-            n -= 1;
-            drawn = 0;
-            continue;
-        }
-        long long seg = n < left ? n : left;
-        if (seg > LINREG_RUN_MAX) seg = LINREG_RUN_MAX;
+        long long seg = n < LINREG_RUN_MAX ? n : LINREG_RUN_MAX;
         if (drawn == 0) {                                // the first launch's inputs
-            HIP_TRY(launch({0, 0, (int)seg, -1, -1, st_cur(c), nullptr, nullptr, nullptr}, sp));
+            if (seg > LINREG_RUN_FIRST) seg = LINREG_RUN_FIRST;
+            HIP_TRY(launch({0, 0, (int)seg, 0, st_cur(c), nullptr}));
             drawn = seg;
         }
         if (seg > drawn) seg = drawn;
-        const bool sync = seg == left;
-        sp.expect_sync = sync ? 1 : 0;
         const long long draws = (n < LINREG_RUN_AHEAD ? n : LINREG_RUN_AHEAD) - drawn;
-        const bool leave = seg == n || (sync && n - seg >= SINGLE_ROUNDS &&
-                                        singles(c->m_t + seg, host_get_H(c->sp, c->eta.data(), c->m_t + seg), SINGLE_ROUNDS));
-        const int to = leave ? -1 : from == 0 ? 1 : 0;
-        DevState *const st_last = c->d_state + 2 + last;
-        HIP_TRY(launch({(int)seg, (int)drawn, (int)draws, from, to, st_cur(c), c->d_state + (c->cur ^ 1), st_last,
-                        c->d_state + 2 + (last ^ 1)}, sp));
+        unsigned ends = 0;
+        for (long long i = 0, left = c->m_H - c->m_h; i < seg; ++i)
+            if (--left == 0) { ends |= 1u << i; left = host_get_H(c->sp, c->eta.data(), c->m_t + i + 1); }
+        HIP_TRY(launch({(int)seg, (int)drawn, (int)draws, ends, st_cur(c), c->d_state + (c->cur ^ 1)}));
+        for (long long i = 0; i < seg; ++i) mirror_advance(c);
         drawn += draws - seg;
         c->cur ^= 1;
-        for (long long i = 0; i < seg; ++i) mirror_advance(c);
         c->t_host += seg;
         n -= seg;
-        from = to; last ^= 1;
-        if (leave && sync) HIP_TRY(launch_average_rows(c->params, cfg.K, cfg.P, st_last, c->stream));
     }
     return QSR_OK;
+}
+
+// The K workers of such a launch wait for each other, so all have to be resident, a compute unit each, whatever else is: streams
+// that may use fewer than 16 K compute units take their iterations one by one (16 launches at once are four processes' hardware queues).
+static bool workers_fit(const qsr_ctx *c)
+{
+    uint32_t mask[32] = {0};
+    if (hipExtStreamGetCUMask(c->stream, 32, mask) != hipSuccess) { (void)hipGetLastError(); return false; }
+    int units = 0;
+    for (uint32_t m : mask) units += __builtin_popcount(m);
+    return units >= 16 * c->cfg.K && c->compute_units >= 16 * c->cfg.K;
 }
 
 // Every kernel of an iteration takes t, h, H and the averaging decision from device memory, and
@@ -741,7 +724,7 @@ extern "C" int qsr_run(qsr_ctx *c, int64_t n)
 {
     if (!c || n < 0) return QSR_EINVAL;
     if (c->need_sync_call || n > c->cfg.T - c->t_host) return QSR_ESTATE;
-    if (c->run_linreg && n >= 2 && !c->timing && !caller_records(c->stream)) return run_linreg(c, n);
+    if (c->run_linreg && n >= 2 && !c->timing && !caller_records(c->stream) && workers_fit(c)) return run_linreg(c, n);
     const long long per = c->run_linreg ? 0 : c->graph_iters;
     // the null stream cannot be captured; with timing on every launch gets its own event bracket
     if (c->timing || c->stream == nullptr || per < 1 || n < 1 + 2 * per) return run_one_by_one(c, n);

@@ -174,7 +174,7 @@ hipError_t launch_linreg_grad(const ModelDims &d, const float *theta, float *g, 
 
 // The same gradient in two launches of which the second also takes the OPT update (s1 != nullptr: AdamW with
 // c1 = 1 - beta1, c2 = 1 - beta2; else SGD with c1 = mu, c2 = lambda), the scheduler's step (st_next as above)
-// and, with average, the round's averaging where the device's scheduler says so.
+// and, with average, the round's averaging where the device's scheduler says so (not for workers that linreg_can_run).
 bool linreg_can_fuse(const ModelDims &d);
 hipError_t launch_linreg_residual(const ModelDims &d, const float *theta, const float *wstar, void *ws,
                                   const DevState *st, hipStream_t s);
@@ -183,19 +183,17 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
                                      const DevState *st, DevState *st_next, bool average, const SchedParams &sp,
                                      hipStream_t s);
 
-// Iterations together: n_it of them, of one round, for workers that fit one workgroup each (least squares), and the draws of
-// n_draw iterations from the current one plus draw_off on, which a later call's iterations read.  The same bits as one by one.
-constexpr int LINREG_RUN_AHEAD = 32, LINREG_RUN_MAX = 16;      // draws held, iterations of a launch
+// Iterations together: n_it of them with the averaging of the rounds that they end, for workers that fit one workgroup each (least
+// squares), and the draws of n_draw iterations from the current one plus draw_off on, which a later launch's iterations read.  The
+// same bits as one by one.  A launch of draws alone (n_it = 0) has to come first in a call, and the launches of a call one behind the other.
+constexpr int LINREG_RUN_AHEAD = 64, LINREG_RUN_MAX = 32;      // draws held, iterations of a launch
 struct LinregSpan {
     int n_it, draw_off, n_draw;
-    int in, out;                     // parameters read and written: -1 the caller's, 0 and 1 copies in the workspace
+    unsigned ends;                   // bit i: iteration i ends a round, as the host's mirror expects
     const DevState *st;
-    DevState *st_next, *st_last;     // the state after the iterations, and before the last of them
-    const DevState *st_mean;         // a copy read is averaged first, if this st_last was the end of a round
+    DevState *st_next;               // the state after the iterations
 };
 bool linreg_can_run(const ModelDims &d);
-// whether rounds of one iteration are faster in two kernels that average than as such a launch each
-bool linreg_single_rounds(const ModelDims &d);
 hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws,
                              float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
                              const SchedParams &sp, hipStream_t s);

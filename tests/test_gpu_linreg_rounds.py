@@ -1,0 +1,70 @@
+"""GPU: least-squares rounds that end inside a launch of several iterations (csrc/grad_linreg.hip: the workers exchange their
+parameters there, as many at a time as a workgroup has groups of wavefronts) give, bit for bit, what the same iterations give one by
+one: worker counts around those groups for one to four wavefronts a row, rounds that end on a launch's first and last
+iteration, several calls, a call that repeats iterations that the exchange still holds words of, and contexts on streams side by side."""
+import numpy as np
+import pytest
+
+import workloads
+from util import assert_mirror_matches_device, gpu_ctx
+
+pytestmark = pytest.mark.gpu
+
+
+def same(a, b):
+    import torch
+    assert a.get_state() == b.get_state()
+    for x, y in zip((a.params, a.grads, a.state0, a.state1), (b.params, b.grads, b.state0, b.state1)):
+        assert x is y is None or torch.equal(x, y)
+    assert np.array_equal(a.read_loss(), b.read_loss())
+
+
+@pytest.mark.parametrize("K,d,B,opt", [
+    (1, 1024, 32, "sgdm"), (4, 1021, 32, "sgdm"), (5, 1024, 9, "adamw"), (8, 1000, 20, "sgdm"), (9, 770, 5, "sgdm"),
+    (5, 700, 25, "sgdm"), (6, 768, 25, "adamw"), (11, 513, 10, "sgdm"), (8, 512, 30, "sgdm"), (9, 260, 30, "adamw"),
+    (16, 256, 32, "sgdm"), (16, 7, 3, "adamw")])
+@pytest.mark.parametrize("H", [1, 3, 8])
+def test_rounds_inside_launches(K, d, B, opt, H):
+    kw = dict(mu=0.9, lam=1e-4) if opt == "sgdm" else dict(beta1=0.9, beta2=0.99, eps=1e-3, lam=0.01)
+    w = workloads.get("lsq", K=K, d_in=d, B_loc=B, T=200, opt=opt, eta_max=0.1 / (1 + d / B), H_base=H, alpha=0.0, power=0, **kw)
+    ref, ctx = gpu_ctx(w), gpu_ctx(w)
+    for n in (3, 150, 47):
+        ref.step(n)
+        ctx.run(n)
+        same(ref, ctx)
+    assert_mirror_matches_device(ctx)
+    assert list(ctx.read_sync_log()[1]) == list(ref.read_sync_log()[1])
+    ctx.close(); ref.close()
+
+
+def test_iterations_repeated():
+    """The schedule set back between calls: the words of a call before are of iterations that end rounds again."""
+    w = workloads.get("lsq", K=7, d_in=300, B_loc=20, T=90, H_base=2, alpha=0.0, power=0)
+    ref, ctx = gpu_ctx(w), gpu_ctx(w)
+    for c, go in ((ref, ref.step), (ctx, ctx.run)):
+        go(70)
+        c.set_state((10, 5, 0, 2))
+        go(70)
+    same(ref, ctx)
+    ctx.close(); ref.close()
+
+
+def test_side_by_side():
+    """Contexts of sixteen workers on streams of their own, enqueued in turn: each one's launches wait only for their own workers."""
+    import torch
+    w = workloads.get("lsq", K=16, d_in=500, B_loc=24, T=240, H_base=1, alpha=0.0, power=0)
+    ref = gpu_ctx(w)
+    ref.step(240)
+    ctxs = []
+    for _ in range(4):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            ctxs.append(gpu_ctx(w))
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for c in ctxs:
+            c.run(60)
+    torch.cuda.synchronize()
+    for c in ctxs:
+        same(ref, c)
+        c.close()
+    ref.close()
