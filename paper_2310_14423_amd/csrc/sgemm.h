@@ -356,7 +356,8 @@ __global__ __launch_bounds__(64 * WT) void dgemm_nn_kernel(GemmArgs a)
 // The fp64 matrix instruction issues at 75-78 TFLOP/s from one wavefront per SIMD on (70-72 with the conversions);
 // 8 x 128 x 784 x 1024: 46.3 us with guarded loads straight to registers, 35.9 us this way (four groups, two stages);
 // 5 x 50 x 333 x 500 and 5 x 50 x 500 x 100, few tiles: 28-32 us with 64x64 tiles and two groups from registers, 13.7 us with
-// 32x32 tiles and sixteen.
+// 32x32 tiles and sixteen whose sums went through LDS in four steps to the first, which wrote the tile alone (in an iteration: 11.8), 8.4 and 9.0 us with one step
+// and a share of the tile for each (8 x 128 x 784 x 1024 in an iteration: 37.2 -> 35.4).
 template <int EPI, int KSPLIT, int WT, int NS, bool BX4>
 __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_lds_kernel(GemmArgs a)
 {
@@ -485,39 +486,38 @@ __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_lds_kernel(GemmArgs
         }
     }
     float *C = a.C + bz * a.sC;
-    if constexpr (KSPLIT > 1) {       // the groups' partial sums, added pairwise in a fixed order
-        __syncthreads();              // the rings are done with
-        double *dpart = (double *)dg_ring;
+    // The groups' partial sums, each wavefront's in the ring it is done with; each adds up, pairwise in a fixed order, and
+    // writes its share of the tile
+    double *const dpart = (double *)dg_ring;
+    constexpr int RING = NS * STAGE / 2, EACH = 16 / KSPLIT; // doubles of a ring, accumulator elements of a wavefront
+    static_assert(RING >= 16 * 64 && 16 % KSPLIT == 0, "a wavefront's accumulators in its ring");
+    if constexpr (KSPLIT > 1) {
 #pragma unroll
-        for (int stride = KSPLIT / 2; stride >= 1; stride >>= 1) {
-            if (grp >= stride && grp < 2 * stride) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) dpart[(((grp - stride) * WT + w4) * 16 + i) * 64 + lane] = dacc[i >> 3][(i >> 2) & 1][i & 3];
-            }
-            __syncthreads();
-            if (grp < stride) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) dacc[i >> 3][(i >> 2) & 1][i & 3] += dpart[((grp * WT + w4) * 16 + i) * 64 + lane];
-            }
-            __syncthreads();
-        }
-        if (grp > 0) return;
+        for (int i = 0; i < 16; ++i) dpart[wv * RING + i * 64 + lane] = dacc[i >> 3][(i >> 2) & 1][i & 3];
+        __syncthreads();
     }
-    // accumulator element e of lane l is C[4*e + l/16][l%16] of its 16x16 block
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int u = 0; u < EACH; ++u) {
+        const int i = grp * EACH + u;
+        // accumulator element e of lane l is C[4*e + l/16][l%16] of its 16x16 block
+        const int gm = m0 + (i >> 3) * 16 + 4 * (i & 3) + q;
+        const int gn = n0 + ((i >> 2) & 1) * 16 + r;
+        double v;
+        if constexpr (KSPLIT > 1) {
+            double part[KSPLIT];
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
+            for (int g = 0; g < KSPLIT; ++g) part[g] = dpart[(g * WT + w4) * RING + i * 64 + lane];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int gm = m0 + bi * 16 + 4 * e + q;
-                const int gn = n0 + bj * 16 + r;
-                if (gm >= a.M || gn >= a.N) continue;
-                double v = dacc[bi][bj][e];
-                if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS) v += (double)a.bias[bz * a.sBias + gn];
-                if (EPI == EPI_BIAS_RELU) v = v > 0.0 ? v : 0.0;
-                C[(long long)gm * a.ldc + gn] = (float)v;
-            }
+            for (int stride = KSPLIT / 2; stride >= 1; stride >>= 1)
+#pragma unroll
+                for (int g = 0; g < stride; ++g) part[g] += part[g + stride];
+            v = part[0];
+        } else v = dacc[u >> 3][(u >> 2) & 1][u & 3];
+        if (gm >= a.M || gn >= a.N) continue;
+        if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS) v += (double)a.bias[bz * a.sBias + gn];
+        if (EPI == EPI_BIAS_RELU) v = v > 0.0 ? v : 0.0;
+        C[(long long)gm * a.ldc + gn] = (float)v;
+    }
 #undef DG_WAIT_VM
 #undef DG_WAIT_LDS
 }
@@ -526,8 +526,7 @@ template <int EPI, int KSPLIT, int WT, int NS>
 inline hipError_t launch_dgemm_lds(const GemmArgs &a, int batch, bool bx4, hipStream_t s)
 {
     constexpr int TILE = WT == 4 ? 64 : 32;
-    constexpr size_t ring = (size_t)WT * KSPLIT * NS * 4096, parts = (size_t)(KSPLIT / 2) * WT * 16 * 64 * 8;
-    constexpr size_t smem = ring > parts ? ring : parts;
+    constexpr size_t smem = (size_t)WT * KSPLIT * NS * 4096;
     static_assert(smem <= 160 * 1024, "rings");
     static bool raised = false;               // per instantiation; contexts are not thread-safe
     if (smem > 64 * 1024 && !raised) {
