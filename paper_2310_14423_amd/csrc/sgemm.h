@@ -48,8 +48,9 @@ typedef double f64x4_t __attribute__((ext_vector_type(4)));
 // compute unit (with a static array for the sums in each kind of tile it was 56, and two did).
 struct SgemmSlabs { float A[16][96], B[16][96]; };
 template <int KSPLIT> union SgemmLds {
+    static_assert(KSPLIT == 2, "one group or two");
     SgemmSlabs slab[KSPLIT];
-    float part[KSPLIT - 1][4][16][64];
+    float part[KSPLIT][4][8][64];
 };
 template <> union SgemmLds<1> { SgemmSlabs slab[1]; };
 static_assert(sizeof(SgemmLds<2>) == 24 * 1024, "partial sums inside the slabs");
@@ -170,31 +171,40 @@ __device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, in
         }
     }
     float *C = a.C + bz * a.sC;
-    if constexpr (KSPLIT > 1) {       // the other groups' partial sums, added in group order
-        if (TA && !TB && col_wg) __syncthreads();     // the column sums are read
-        if (grp > 0) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) lds.part[grp - 1][tid >> 6][i][lane] = acc[i];
-        }
-        __syncthreads();
-        if (grp > 0) return;
-#pragma unroll
-        for (int g = 0; g < KSPLIT - 1; ++g)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] += lds.part[g][tid >> 6][i][lane];
-    }
-
-    // accumulator element i of lane l is C[(i/4)*8 + (l/32)*4 + i%4][l%32] of the wavefront's block
+    // Accumulator element i of lane l is C[(i/4)*8 + (l/32)*4 + i%4][l%32] of the wavefront's block.  Two groups add up and write
+    // half of the tile each (in group order); what the epilogue reads comes before, clamped into the matrix: behind a
+    // test and a wait of its own, each of the sixteen loads took its latency (5 x 50 x 500 x 100, both products in a launch: 12.9 ->
+    // 10.2 us).
+    constexpr int EACH = 16 / KSPLIT;
     const int gn = n0 + wn * 32 + (lane & 31);
+    auto row = [&](int u) { const int i = grp * EACH + u; return m0 + wm * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3); };
+    float aux[EACH];
+    if (EPI == EPI_MASK_POS) {
+        const float *x = a.aux + bz * a.sC + min(gn, a.N - 1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int gm = m0 + wm * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-        if (gm >= a.M || gn >= a.N) continue;
-        float v = acc[i];
-        if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS) v += a.bias[bz * a.sBias + gn];
-        if (EPI == EPI_BIAS_RELU) v = v > 0.f ? v : 0.f;
-        if (EPI == EPI_MASK_POS) v = a.aux[bz * a.sC + (long long)gm * a.ldc + gn] > 0.f ? v : 0.f;
-        C[(long long)gm * a.ldc + gn] = v;
+        for (int u = 0; u < EACH; ++u) aux[u] = x[(long long)min(row(u), a.M - 1) * a.ldc];
+    }
+    float out[EACH];
+    if constexpr (KSPLIT == 2) {
+        if (TA && !TB && col_wg) __syncthreads();     // the column sums are read
+#pragma unroll
+        for (int u = 0; u < EACH; ++u) lds.part[grp][tid >> 6][u][lane] = grp == 0 ? acc[EACH + u] : acc[u];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < EACH; ++u) {
+            const float other = lds.part[grp ^ 1][tid >> 6][u][lane];
+            out[u] = (grp == 0 ? acc[u] : acc[EACH + u]) + other;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < EACH; ++u) out[u] = acc[u];
+    }
+#pragma unroll
+    for (int u = 0; u < EACH; ++u) {
+        if (row(u) >= a.M || gn >= a.N) continue;
+        float v = out[u];
+        if (EPI == EPI_MASK_POS) v = aux[u] > 0.f ? v : 0.f;
+        C[(long long)row(u) * a.ldc + gn] = v;
     }
 }
 
@@ -356,8 +366,9 @@ __global__ __launch_bounds__(64 * WT) void dgemm_nn_kernel(GemmArgs a)
 // The fp64 matrix instruction issues at 75-78 TFLOP/s from one wavefront per SIMD on (70-72 with the conversions);
 // 8 x 128 x 784 x 1024: 46.3 us with guarded loads straight to registers, 35.9 us this way (four groups, two stages);
 // 5 x 50 x 333 x 500 and 5 x 50 x 500 x 100, few tiles: 28-32 us with 64x64 tiles and two groups from registers, 13.7 us with
-// 32x32 tiles and sixteen whose sums went through LDS in four steps to the first, which wrote the tile alone (in an iteration: 11.8), 8.4 and 9.0 us with one step
-// and a share of the tile for each (8 x 128 x 784 x 1024 in an iteration: 37.2 -> 35.4).
+// 32x32 tiles and sixteen.  In an iteration these took 11.8 us where the groups' sums went through LDS in four steps to the
+// first, which wrote the tile alone, and take 8.4 and 9.0 with one step and a share of the tile for each group (8 x 128 x 784 x
+// 1024: 37.2 -> 35.4).
 template <int EPI, int KSPLIT, int WT, int NS, bool BX4>
 __global__ __launch_bounds__(64 * WT * KSPLIT) void dgemm_nn_lds_kernel(GemmArgs a)
 {
