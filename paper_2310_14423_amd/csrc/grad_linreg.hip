@@ -12,7 +12,7 @@
 // of its columns, which it holds for all workers, and in a recorded iteration the averaging and
 // the scheduler's step.  Iterations enqueued together (qsr_run) of a worker that fits one workgroup need no launch between
 // them at all: linreg_run_kernel.  256 iterations of 4 x 1024 features x 32 samples: 2879 us with four
-// kernels per iteration (residuals, gradient, update, averaging), 1900 with two, 502 together
+// kernels per iteration (residuals, gradient, update, averaging), 1900 with two, 563 together
 // (644 where each of the 28 rounds ended a launch).
 #include "opt_elem.h"
 #include "philox.h"
@@ -61,13 +61,10 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Iterations together: X and the observation noise of RUN_SLOTS iterations at a time, drawn ahead
 constexpr int RUN_SLOTS = LINREG_RUN_AHEAD;
 static inline long long slot_worker_floats(const ModelDims &d) { return d.B * run_shape(d).d4 + (d.B + 3) / 4 * 4; }
-// ... and what the workers exchange where a round ends, two rounds of it: a word for each parameter, [worker][wavefront of the row][of a
-// lane's four][lane]
-static inline long long run_words(const ModelDims &d) { return 2LL * d.K * run_shape(d).row * 256; }
-static inline long long run_floats(const ModelDims &d)
-{
-    return (RUN_SLOTS * d.K * slot_worker_floats(d) + 1) / 2 * 2 + 2 * run_words(d);
-}
+static inline long long run_floats(const ModelDims &d) { return RUN_SLOTS * d.K * slot_worker_floats(d); }
+// What the workers exchange where a round ends, two rounds of it: a word for each parameter, [worker][wavefront of the row][of a lane's
+// four][lane]
+size_t linreg_run_words_bytes(const ModelDims &d) { return 2 * (size_t)d.K * run_shape(d).row * 256 * sizeof(unsigned long long); }
 
 // exchanges inside a wavefront: lane l gets the value of lane l ^ 8, l ^ 7, l ^ 2, l ^ 1
 template <int CTRL>
@@ -526,7 +523,7 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // the arithmetic behind it (2.1 us an iteration, spread 1.5, without them 1.1).
 //
 // Where a round ends, which every workgroup takes from its own reading of the schedule, the workers hand each other their parameters
-// through the workspace: one 64-bit word for each, the value beside the iteration it is from, written and read past the
+// through memory: one 64-bit word for each, the value beside the iteration it is from, written and read past the
 // caches that XCDs do not share.  A reader that finds the iteration has the value, and no flag, fence or launch is needed.  Rounds of a
 // launch take two sets of words in turn: whoever writes a set again has read, in the other one, what all workers wrote behind
 // their reading of this one.  The launch that draws a call's first inputs fills the words with an iteration that ends no round of the call.
@@ -535,8 +532,10 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // (minutes), it waits no more and leaves NaN.
 // Bound by the round trips to memory, 1.5 us for one and the words' way there.  us an iteration at rounds of 1 / 2 / 8, against launches that
 // end with the round (those of one iteration: two kernels, the second averages):
-//   4 x 1024 features x 32 samples 4.0 / 2.8 / 2.0, 7.2 / 5.5 / 2.5;  16 x 1024 x 32 7.9 / 4.9 / 2.7, 11.0 / 6.6 / 2.8;
-//   16 x 257 x 8 5.7 / 3.5 / 1.7, 8.6 / 4.6 / 1.9;  1 x 256 x 64 2.4 / 1.9 / 1.6, 7.1 / 4.6 / 2.1
+//   4 x 1024 features x 32 samples 4.1 / 3.0 / 2.2, 7.2 / 5.5 / 2.5;  16 x 1024 x 32 8.0 / 5.0 / 2.75, 11.0 / 6.6 / 2.77;
+//   16 x 257 x 8 5.8 / 3.6 / 1.86, 8.6 / 4.6 / 1.88;  1 x 256 x 64 2.6 / 2.1 / 1.7, 7.1 / 4.6 / 2.1
+// (launches of 32 iterations, from 64 held ahead, would take another 0.2 off).  Draws that bypass the caches slow the workers' reads:
+// 0.8 us an iteration.
 // A lane's words next to each other instead of 64 apart take 0.7 us more a round, two workers a group of wavefronts at a time
 // 0.5 more up to four workers and 0.2 less at sixteen.
 constexpr int RUN_POLLS = 1 << 27;
@@ -771,7 +770,7 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
     }
 }
 
-hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws,
+hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws, void *words,
                              float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
                              const SchedParams &sp, hipStream_t s)
 {
@@ -780,7 +779,7 @@ hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *
     const RunShape q = run_shape(d);
     LinregRun a{};
     a.slots = linreg_slots(d, ws);
-    a.words = (unsigned long long *)(a.slots + (RUN_SLOTS * d.K * slot_worker_floats(d) + 1) / 2 * 2);
+    a.words = (unsigned long long *)words;
     a.p = LinregStep{theta, g, s0, s1, sc, c1, c2, eps};
     a.ends = span.ends;
     a.wstar = wstar; a.loss = loss;

@@ -45,6 +45,7 @@ struct qsr_ctx {
                              // the local step whose qsr_maybe_sync is pending
     bool fuse_linreg;        // least squares: the gradient kernel takes the update of its columns too
     bool run_linreg;         //   and iterations enqueued together need no launch of their own
+    void *d_words;           //   but words for what the workers exchange where a round ends
     double *d_eta;
     StepScalars *d_scal;
     long long *d_log_t, *d_log_H;
@@ -354,6 +355,7 @@ static void free_ctx(qsr_ctx *c)
     for (auto &p : c->pairs) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
     for (auto e : c->free_events) (void)hipEventDestroy(e);
     if (c->d_state) (void)hipFree(c->d_state);
+    if (c->d_words) (void)hipFree(c->d_words);
     if (c->d_eta) (void)hipFree(c->d_eta);
     if (c->d_scal) (void)hipFree(c->d_scal);
     if (c->d_log_t) (void)hipFree(c->d_log_t);
@@ -381,6 +383,7 @@ static int init_impl(qsr_ctx *c, const float *theta0)
     }
 
     HIP_TRY(hipMalloc((void **)&c->d_state, 2 * sizeof(DevState)));
+    if (c->run_linreg) HIP_TRY(hipMalloc(&c->d_words, linreg_run_words_bytes(c->dims)));
     HIP_TRY(hipMalloc((void **)&c->d_eta, T * sizeof(double)));
     HIP_TRY(hipMalloc((void **)&c->d_scal, T * sizeof(StepScalars)));
     HIP_TRY(hipMalloc((void **)&c->d_log_t, T * sizeof(long long)));
@@ -444,7 +447,7 @@ extern "C" int qsr_init(const qsr_config *cfg, float *params, float *grads, floa
     c->params = params; c->grads = grads; c->state0 = state0;
     c->state1 = cfg->opt == QSR_OPT_ADAMW ? state1 : nullptr;
     c->model_const = model_const; c->workspace = workspace; c->workspace_bytes = workspace_bytes;
-    c->d_state = nullptr; c->d_eta = nullptr; c->d_scal = nullptr; c->d_log_t = nullptr;
+    c->d_state = nullptr; c->d_words = nullptr; c->d_eta = nullptr; c->d_scal = nullptr; c->d_log_t = nullptr;
     c->d_log_H = nullptr; c->d_loss = nullptr; c->h_state = nullptr;
     c->d_clip_part = nullptr; c->d_clip_coef = nullptr;
     c->t_host = 0; c->need_sync_call = false; c->timing = false; c->capturing = false;
@@ -682,7 +685,7 @@ static int run_linreg(qsr_ctx *c, long long n)
     long long drawn = 0;                                 // iterations from the current one on
     auto launch = [&](const LinregSpan &span) {
         return launch_linreg_run(c->dims, c->params, c->grads, c->state0, sgd ? nullptr : c->state1, c->model_const, c->workspace,
-                                 c->d_loss, c->d_scal, c1, c2, (float)cfg.eps, span, c->sp, c->stream);
+                                 c->d_words, c->d_loss, c->d_scal, c1, c2, (float)cfg.eps, span, c->sp, c->stream);
     };
     while (n > 0) {
         long long seg = n < LINREG_RUN_MAX ? n : LINREG_RUN_MAX;

@@ -186,7 +186,7 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // Iterations together: n_it of them with the averaging of the rounds that they end, for workers that fit one workgroup each (least
 // squares), and the draws of n_draw iterations from the current one plus draw_off on, which a later launch's iterations read.  The
 // same bits as one by one.  A launch of draws alone (n_it = 0) has to come first in a call, and the launches of a call one behind the other.
-constexpr int LINREG_RUN_AHEAD = 64, LINREG_RUN_MAX = 32;      // draws held, iterations of a launch
+constexpr int LINREG_RUN_AHEAD = 32, LINREG_RUN_MAX = 16;      // draws held, iterations of a launch
 struct LinregSpan {
     int n_it, draw_off, n_draw;
     unsigned ends;                   // bit i: iteration i ends a round, as the host's mirror expects
@@ -194,7 +194,9 @@ struct LinregSpan {
     DevState *st_next;               // the state after the iterations
 };
 bool linreg_can_run(const ModelDims &d);
-hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws,
+// what the workers exchange where a round ends (device memory, 8-byte aligned, contents irrelevant before a call)
+size_t linreg_run_words_bytes(const ModelDims &d);
+hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws, void *words,
                              float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
                              const SchedParams &sp, hipStream_t s);
 
