@@ -181,8 +181,9 @@ int qsr_maybe_sync(qsr_ctx *ctx);
 /* n global iterations of Alg. 2, each a qsr_local_step followed by its qsr_maybe_sync, with the
  * same results bit for bit.  Every kernel reads t, h, H and the averaging decision from device
  * memory, so the launches of an iteration do not depend on t.
- *  - LINREG whose workers fit a workgroup each (see qsr_workspace_bytes): they go in
- *    launches of up to 16 each, whatever rounds end inside, on any stream that may use 16 compute units a worker.
+ *  - LINREG whose workers fit a workgroup each (see qsr_workspace_bytes): the iterations go in launches
+ *    of up to 16 each, whatever rounds end inside them.  The workers of a launch wait for each other where a
+ *    round ends, so a stream that may use fewer than 16 compute units a worker takes its iterations one by one.
  *  - Other small models: on a stream other than the null stream, with n large enough to pay for it,
  *    the launches of several iterations are recorded once into a HIP graph (kernel nodes only) that is
  *    replayed, which removes most of the launch cost of short iterations.
