@@ -45,7 +45,9 @@ enum {
     QSR_ENOGPU = -5,   /* no usable gfx950 device                                       */
     QSR_EMIRROR = -6,  /* the host's mirror of the schedule and the device scheduler took
                           different decisions (a defect: results after it are not Alg. 2's) */
-    QSR_ELIMIT = -7    /* size beyond the fixed capacity of an entry point that allocates nothing */
+    QSR_ELIMIT = -7,   /* size beyond the fixed capacity of an entry point that allocates nothing */
+    QSR_EWAIT = -8     /* workers of a qsr_run launch waited for each other in vain (see there): the
+                          parameters hold NaN                                             */
 };
 
 enum { QSR_OPT_SGDM = 0, QSR_OPT_ADAMW = 1 };
@@ -184,6 +186,10 @@ int qsr_maybe_sync(qsr_ctx *ctx);
  *  - LINREG whose workers fit a workgroup each (see qsr_workspace_bytes): the iterations go in launches
  *    of up to 16 each, whatever rounds end inside them.  The workers of a launch wait for each other where a
  *    round ends, so a stream that may use fewer than 16 compute units a worker takes its iterations one by one.
+ *    Up to 16 such launches may be under way on a device at once (other contexts, streams and processes counted),
+ *    with room left for them by whatever else runs: a worker that waits for minutes gives up,
+ *    the parameters become NaN, and every call that reads the state returns QSR_EWAIT until
+ *    qsr_set_state or qsr_restart.
  *  - Other small models: on a stream other than the null stream, with n large enough to pay for it,
  *    the launches of several iterations are recorded once into a HIP graph (kernel nodes only) that is
  *    replayed, which removes most of the launch cost of short iterations.

@@ -64,7 +64,10 @@ static inline long long slot_worker_floats(const ModelDims &d) { return d.B * ru
 static inline long long run_floats(const ModelDims &d) { return RUN_SLOTS * d.K * slot_worker_floats(d); }
 // What the workers exchange where a round ends, two rounds of it: a word for each parameter, [worker][wavefront of the row][of a lane's
 // four][lane]
-size_t linreg_run_words_bytes(const ModelDims &d) { return 2 * (size_t)d.K * run_shape(d).row * 256 * sizeof(unsigned long long); }
+static inline size_t exchange_bytes(const ModelDims &d) { return 2 * (size_t)d.K * run_shape(d).row * 256 * sizeof(unsigned long long); }
+// ... and behind them the flag of a wait given up
+size_t linreg_run_words_bytes(const ModelDims &d) { return exchange_bytes(d) + sizeof(int); }
+int *linreg_gave_up(const ModelDims &d, void *words) { return (int *)((char *)words + exchange_bytes(d)); }
 
 // exchanges inside a wavefront: lane l gets the value of lane l ^ 8, l ^ 7, l ^ 2, l ^ 1
 template <int CTRL>
@@ -528,8 +531,8 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // launch take two sets of words in turn: whoever writes a set again has read, in the other one, what all workers wrote behind
 // their reading of this one.  The launch that draws a call's first inputs fills the words with an iteration that ends no round of the call.
 // The wait is for workgroups that run or will: the K <= 16 workers are their launch's first workgroups, and the host
-// keeps to devices and streams with compute units for 16 such launches at once.  Should a launch all the same have waited RUN_POLLS times
-// (minutes), it waits no more and leaves NaN.
+// keeps to devices and streams with compute units for 16 such launches at once.  Should a lane all the same have looked a.polls times
+// (minutes), it waits no more, leaves NaN and sets a flag that every later reading of the state reports.
 // Bound by the round trips to memory, 1.5 us for one and the words' way there.  us an iteration at rounds of 1 / 2 / 8, against launches that
 // end with the round (those of one iteration: two kernels, the second averages):
 //   4 x 1024 features x 32 samples 4.1 / 3.0 / 2.2, 7.2 / 5.5 / 2.5;  16 x 1024 x 32 8.0 / 5.0 / 2.75, 11.0 / 6.6 / 2.77;
@@ -538,12 +541,12 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // 0.8 us an iteration.
 // A lane's words next to each other instead of 64 apart take 0.7 us more a round, two workers a group of wavefronts at a time
 // 0.5 more up to four workers and 0.2 less at sixteen.
-constexpr int RUN_POLLS = 1 << 27;
 struct LinregRun {
     LinregStep p;
     const float *wstar;
     float *slots, *loss;
     unsigned long long *words;           // exchanged parameters: [2][K][row][4][64]
+    int polls;                           // looks before a wait is given up (none, and no word counts, below 0)
     int K, B, d, d4, per, n_it, n_draw, draw_off;   // n_draw iterations from the current one plus draw_off on
     unsigned ends;                       // iterations that end a round, as the host's mirror expects
     float sigma;
@@ -645,7 +648,7 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
     const StepScalars mine = a.p.sc[t0 + min(lane, a.n_it - 1)];
     const int period = (int)min(get_H(a.sp, t0 + 1 + min(lane, a.n_it - 1)), 1ll << 20);
     int to_go = (int)min(a.st->H - a.st->h, 1ll << 20);  // iterations to the end of the round
-    int set = 0, polls = 0;
+    int set = 0, polls = a.polls;
     // This worker's parameters to the others and everybody's mean, over the workers in order, each addition error-free: a worker a
     // group of wavefronts, GROUPS at a time through LDS, two places in turn
     auto average = [&](int it) {
@@ -671,7 +674,9 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
                         w[e] = __hip_atomic_load(words + (k0 + s) * ROW * 256 + e * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) there &= (unsigned)(w[e] >> 32) == t;
-                } while (!there && ++polls < RUN_POLLS);
+                } while (!there && --polls > 0);
+                there &= polls >= 0;
+                if (!there) *(int *)(a.words + 2 * a.K * ROW * 256) = 1;
                 auto value = [&](int e) { return there ? __int_as_float((int)(unsigned)w[e]) : NAN; };
                 rows[wave][lane] = make_float4(value(0), value(1), value(2), value(3));
             }
@@ -780,6 +785,7 @@ hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *
     LinregRun a{};
     a.slots = linreg_slots(d, ws);
     a.words = (unsigned long long *)words;
+    a.polls = span.polls - 1;
     a.p = LinregStep{theta, g, s0, s1, sc, c1, c2, eps};
     a.ends = span.ends;
     a.wstar = wstar; a.loss = loss;

@@ -45,7 +45,8 @@ struct qsr_ctx {
                              // the local step whose qsr_maybe_sync is pending
     bool fuse_linreg;        // least squares: the gradient kernel takes the update of its columns too
     bool run_linreg;         //   and iterations enqueued together need no launch of their own
-    void *d_words;           //   but words for what the workers exchange where a round ends
+    void *d_words;           //   but words for what the workers exchange where a round ends, and a flag if that failed
+    int run_polls;           //   looks for another worker's words before it has
     double *d_eta;
     StepScalars *d_scal;
     long long *d_log_t, *d_log_H;
@@ -54,7 +55,7 @@ struct qsr_ctx {
     float *d_clip_coef;      // [K] factors, then [K] gradient norms
     // host mirrors
     std::vector<double> eta;
-    DevState *h_state;       // pinned
+    DevState *h_state;       // pinned, and behind it the flag in d_words
     long long t_host;        // local steps enqueued
     bool need_sync_call;     // a local step was enqueued and its maybe_sync not yet
     // Mirror of the device scheduler's integers (t, s, h, H), advanced on the host with the same
@@ -368,6 +369,8 @@ static void free_ctx(qsr_ctx *c)
     delete c;
 }
 
+static int *dev_gave_up(qsr_ctx *c) { return c->run_linreg ? linreg_gave_up(c->dims, c->d_words) : nullptr; }
+
 static int init_impl(qsr_ctx *c, const float *theta0)
 {
     const qsr_config &cfg = c->cfg;
@@ -393,7 +396,7 @@ static int init_impl(qsr_ctx *c, const float *theta0)
         HIP_TRY(hipMalloc((void **)&c->d_clip_part, (size_t)cfg.K * clip_blocks_per_row(cfg.P) * sizeof(double)));
         HIP_TRY(hipMalloc((void **)&c->d_clip_coef, 2 * (size_t)cfg.K * sizeof(float)));
     }
-    HIP_TRY(hipHostMalloc((void **)&c->h_state, sizeof(DevState), hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc((void **)&c->h_state, sizeof(DevState) + sizeof(int), hipHostMallocDefault));
 
     std::vector<StepScalars> sc;
     build_eta(&cfg, c->eta);
@@ -413,7 +416,7 @@ static int init_impl(qsr_ctx *c, const float *theta0)
     HIP_TRY(launch_fill_zero(c->d_loss, cfg.K, c->stream));
     // everything the context's kernels read is written on c->stream: a stream that does not wait for the null stream would
     // overtake work put there
-    HIP_TRY(launch_sched_init(c->d_state, c->sp, c->stream));
+    HIP_TRY(launch_sched_init(c->d_state, c->sp, dev_gave_up(c), c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     mirror_reset(c, 0, 0, 0, host_get_H(c->sp, c->eta.data(), 0));
     return QSR_OK;
@@ -465,6 +468,7 @@ extern "C" int qsr_init(const qsr_config *cfg, float *params, float *grads, floa
     c->dims = make_dims(cfg);
     c->fuse_linreg = fuses_linreg(cfg, c->dims);
     c->run_linreg = runs_linreg(cfg, c->dims);
+    c->run_polls = LINREG_RUN_POLLS;
     rc = init_impl(c, theta0);
     c->cfg.milestones = nullptr;
     c->cfg.eta_table = nullptr;
@@ -691,7 +695,7 @@ static int run_linreg(qsr_ctx *c, long long n)
         long long seg = n < LINREG_RUN_MAX ? n : LINREG_RUN_MAX;
         if (drawn == 0) {                                // the first launch's inputs
             if (seg > LINREG_RUN_FIRST) seg = LINREG_RUN_FIRST;
-            HIP_TRY(launch({0, 0, (int)seg, 0, st_cur(c), nullptr}));
+            HIP_TRY(launch({0, 0, (int)seg, 0, 0, st_cur(c), nullptr}));
             drawn = seg;
         }
         if (seg > drawn) seg = drawn;
@@ -699,7 +703,7 @@ static int run_linreg(qsr_ctx *c, long long n)
         unsigned ends = 0;
         for (long long i = 0, left = c->m_H - c->m_h; i < seg; ++i)
             if (--left == 0) { ends |= 1u << i; left = host_get_H(c->sp, c->eta.data(), c->m_t + i + 1); }
-        HIP_TRY(launch({(int)seg, (int)drawn, (int)draws, ends, st_cur(c), c->d_state + (c->cur ^ 1)}));
+        HIP_TRY(launch({(int)seg, (int)drawn, (int)draws, ends, c->run_polls, st_cur(c), c->d_state + (c->cur ^ 1)}));
         for (long long i = 0; i < seg; ++i) mirror_advance(c);
         drawn += draws - seg;
         c->cur ^= 1;
@@ -718,6 +722,14 @@ static bool workers_fit(const qsr_ctx *c)
     int units = 0;
     for (uint32_t m : mask) units += __builtin_popcount(m);
     return units >= 16 * c->cfg.K && c->compute_units >= 16 * c->cfg.K;
+}
+
+// For tests, and not in qsr.h: how many looks a worker takes before it gives up
+extern "C" int qsr_debug_wait_limit(qsr_ctx *c, int polls)
+{
+    if (!c || polls < 0) return QSR_EINVAL;
+    c->run_polls = polls;
+    return QSR_OK;
 }
 
 // Every kernel of an iteration takes t, h, H and the averaging decision from device memory, and
@@ -781,9 +793,13 @@ extern "C" int qsr_run(qsr_ctx *c, int64_t n)
 static int fetch_state(qsr_ctx *c)
 {
     const DevState *st = c->d_state + (c->ticked ? c->cur ^ 1 : c->cur);
+    int *const gave_up = (int *)(c->h_state + 1);
+    *gave_up = 0;
     HIP_TRY(hipMemcpyAsync(c->h_state, st, sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
+    if (c->run_linreg) HIP_TRY(hipMemcpyAsync(gave_up, dev_gave_up(c), sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     const DevState &d = *c->h_state;
+    if (*gave_up) return QSR_EWAIT;
     if (d.mismatch) return QSR_EMIRROR;
     if (c->replayed && (d.t != c->m_t || d.s != c->m_s || d.h != c->m_h || d.H != c->m_H)) return QSR_EMIRROR;
     if (c->need_sync_call) { c->h_state->t += 1; c->h_state->h += 1; }
@@ -858,7 +874,7 @@ extern "C" int qsr_set_state(qsr_ctx *c, const int64_t state[4])
     if (t < 0 || t > T || s < 0 || s > t || h < 0 || h > t) return QSR_EINVAL;
     if (t == T ? (H != 0 || h != 0) : (H < 1 || h >= H || H - h > T - t)) return QSR_EINVAL;
     if (c->need_sync_call) return QSR_ESTATE;
-    HIP_TRY(launch_sched_set(st_cur(c), c->sp, t, s, h, H, c->stream));
+    HIP_TRY(launch_sched_set(st_cur(c), c->sp, t, s, h, H, dev_gave_up(c), c->stream));
     c->t_host = t;
     mirror_reset(c, t, s, h, H);
     return QSR_OK;
@@ -867,7 +883,7 @@ extern "C" int qsr_set_state(qsr_ctx *c, const int64_t state[4])
 extern "C" int qsr_restart(qsr_ctx *c)
 {
     if (!c) return QSR_EINVAL;
-    HIP_TRY(launch_sched_init(c->d_state, c->sp, c->stream));
+    HIP_TRY(launch_sched_init(c->d_state, c->sp, dev_gave_up(c), c->stream));
     c->t_host = 0;
     c->need_sync_call = false;
     c->ticked = false;
@@ -946,6 +962,7 @@ extern "C" const char *qsr_strerror(int code)
     case QSR_ENOMEM: return "workspace too small or allocation failed";
     case QSR_ENOGPU: return "no gfx950 device";
     case QSR_EMIRROR: return "host schedule mirror and device scheduler disagree";
+    case QSR_EWAIT: return "workers of a launch waited for each other in vain: the parameters are NaN";
     case QSR_ELIMIT: return "beyond the fixed capacity of an entry point that allocates nothing";
     default: return "unknown error";
     }

@@ -92,10 +92,10 @@ enum : uint32_t { STREAM_GRAD = 0, STREAM_X = 1, STREAM_NOISE = 2, STREAM_LABEL 
 void set_last_hip_error(int code);
 
 // ---- launchers (each returns the hipError_t of its launch) --------------------------------
-// st[0] and st[1] <- the state at t = 0 (both copies)
-hipError_t launch_sched_init(DevState *st, SchedParams sp, hipStream_t s);
+// st[0] and st[1] <- the state at t = 0 (both copies); both clear *gave_up (linreg_gave_up) unless it is NULL
+hipError_t launch_sched_init(DevState *st, SchedParams sp, int *gave_up, hipStream_t s);
 hipError_t launch_sched_set(DevState *st, SchedParams sp, long long t, long long s_, long long h, long long H,
-                            hipStream_t s);
+                            int *gave_up, hipStream_t s);
 // *dst <- *src (the two copies of the scheduler state)
 hipError_t launch_sched_copy(DevState *dst, const DevState *src, hipStream_t s);
 // end of an iteration (where no update kernel has taken the step): t += 1, h += 1 and, if that was the round's
@@ -187,15 +187,19 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // squares), and the draws of n_draw iterations from the current one plus draw_off on, which a later launch's iterations read.  The
 // same bits as one by one.  A launch of draws alone (n_it = 0) has to come first in a call, and the launches of a call one behind the other.
 constexpr int LINREG_RUN_AHEAD = 32, LINREG_RUN_MAX = 16;      // draws held, iterations of a launch
+constexpr int LINREG_RUN_POLLS = 1 << 27;                      // looks, of about a microsecond, before a wait is given up
 struct LinregSpan {
     int n_it, draw_off, n_draw;
     unsigned ends;                   // bit i: iteration i ends a round, as the host's mirror expects
+    int polls;                       // looks before a wait is given up
     const DevState *st;
     DevState *st_next;               // the state after the iterations
 };
 bool linreg_can_run(const ModelDims &d);
-// what the workers exchange where a round ends (device memory, 8-byte aligned, contents irrelevant before a call)
+// what the workers exchange where a round ends (device memory, 8-byte aligned, contents irrelevant before a call), and a flag that a
+// launch sets where a wait is given up (launch_sched_init and launch_sched_set clear it)
 size_t linreg_run_words_bytes(const ModelDims &d);
+int *linreg_gave_up(const ModelDims &d, void *words);
 hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws, void *words,
                              float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
                              const SchedParams &sp, hipStream_t s);

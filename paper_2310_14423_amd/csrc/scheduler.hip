@@ -7,23 +7,25 @@
 
 namespace qsr {
 
-// st: both copies of the state, which start equal
-__global__ void sched_init_kernel(DevState *st, SchedParams sp)
+// st: both copies of the state, which start equal; gave_up: a context's flag of waits given up (grad_linreg.hip), if it has one
+__global__ void sched_init_kernel(DevState *st, SchedParams sp, int *gave_up)
 {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     const DevState first{0, 0, 0, get_H(sp, 0), 0};
     st[0] = first;
     st[1] = first;
+    if (gave_up) *gave_up = 0;
 }
 
 // resume: install a saved (t, s, h, H); log entries of earlier rounds are cleared
 __global__ void sched_set_kernel(DevState *st, SchedParams sp, long long t, long long s, long long h,
-                                 long long H)
+                                 long long H, int *gave_up)
 {
     for (long long i = threadIdx.x; i < s; i += blockDim.x) { sp.log_t[i] = 0; sp.log_H[i] = 0; }
     if (threadIdx.x != 0) return;
     st->t = t; st->s = s; st->h = h; st->H = H;
     st->mismatch = 0;
+    if (gave_up) *gave_up = 0;
 }
 
 // the last launch of an iteration when no other kernel closes it
@@ -43,15 +45,15 @@ hipError_t launch_sched_copy(DevState *dst, const DevState *src, hipStream_t s)
     sched_copy_kernel<<<1, 64, 0, s>>>(dst, src);
     return hipGetLastError();
 }
-hipError_t launch_sched_init(DevState *st, SchedParams sp, hipStream_t s)
+hipError_t launch_sched_init(DevState *st, SchedParams sp, int *gave_up, hipStream_t s)
 {
-    sched_init_kernel<<<1, 64, 0, s>>>(st, sp);
+    sched_init_kernel<<<1, 64, 0, s>>>(st, sp, gave_up);
     return hipGetLastError();
 }
 hipError_t launch_sched_set(DevState *st, SchedParams sp, long long t, long long s_, long long h, long long H,
-                            hipStream_t s)
+                            int *gave_up, hipStream_t s)
 {
-    sched_set_kernel<<<1, 256, 0, s>>>(st, sp, t, s_, h, H);
+    sched_set_kernel<<<1, 256, 0, s>>>(st, sp, t, s_, h, H, gave_up);
     return hipGetLastError();
 }
 hipError_t launch_sched_advance(DevState *st, SchedParams sp, hipStream_t s)

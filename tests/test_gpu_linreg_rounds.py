@@ -1,10 +1,11 @@
 """GPU: least-squares rounds that end inside a launch of several iterations (csrc/grad_linreg.hip: the workers exchange their
 parameters there, as many at a time as a workgroup has groups of wavefronts) give, bit for bit, what the same iterations give one by
 one: worker counts around those groups for one to four wavefronts a row, rounds that end on a launch's first and last
-iteration, several calls, a call that repeats iterations that the exchange still holds words of, and contexts on streams side by side."""
+iteration, several calls, a call that repeats iterations that the exchange still holds words of, a wait that is given up, and contexts on streams side by side."""
 import numpy as np
 import pytest
 
+import paper_2310_14423_amd as qsr
 import workloads
 from util import assert_mirror_matches_device, gpu_ctx
 
@@ -45,6 +46,32 @@ def test_iterations_repeated():
         go(70)
         c.set_state((10, 5, 0, 2))
         go(70)
+    same(ref, ctx)
+    ctx.close(); ref.close()
+
+
+def test_wait_given_up():
+    """A worker that finds no word in the looks it may take (here none) leaves NaN, and every reading of the state says so until a state is
+    installed, by either call; then the results are the right ones again."""
+    w = workloads.get("lsq", K=5, d_in=700, B_loc=25, T=60, H_base=3, alpha=0.0, power=0)
+    ref, ctx = gpu_ctx(w), gpu_ctx(w)
+    th0 = ctx.params.clone()
+    limit = qsr.lib().qsr_debug_wait_limit
+    for install in (ctx.restart, lambda: ctx.set_state((0, 0, 0, 3))):
+        assert limit(ctx._ctx, 0) == 0
+        ctx.run(20)
+        ctx.run(10)                         # and another call behind it
+        for read in (ctx.get_state, ctx.get_H, ctx.read_sync_log, ctx.read_timing):
+            with pytest.raises(qsr.QSRError) as e:
+                read()
+            assert e.value.code == -8
+        assert ctx.params.isnan().all()
+        assert limit(ctx._ctx, 1 << 27) == 0
+        ctx.params.copy_(th0); ctx.state0.zero_()
+        install()
+        assert ctx.get_state() == (0, 0, 0, 3)
+    ref.step(30)
+    ctx.run(30)
     same(ref, ctx)
     ctx.close(); ref.close()
 
