@@ -184,8 +184,8 @@ int qsr_maybe_sync(qsr_ctx *ctx);
  * same results bit for bit.  Every kernel reads t, h, H and the averaging decision from device
  * memory, so the launches of an iteration do not depend on t.
  *  - LINREG whose workers fit a workgroup each (see qsr_workspace_bytes): the iterations go in launches
- *    of up to 16 each, whatever rounds end inside them.  The workers of a launch wait for each other where a
- *    round ends, so a stream that may use fewer than 16 compute units a worker takes its iterations one by one.
+ *    of up to 16 each, on any stream, also where rounds end inside them.  There the workers of a launch wait for each
+ *    other, so on a stream that may use fewer than 16 compute units a worker launches end with the round.
  *    Up to 16 such launches may be under way on a device at once (other contexts, streams and processes counted),
  *    with room left for them by whatever else runs: a worker that waits for minutes gives up,
  *    the parameters become NaN, and every call that reads the state returns QSR_EWAIT until

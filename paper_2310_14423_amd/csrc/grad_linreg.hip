@@ -62,12 +62,12 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr int RUN_SLOTS = LINREG_RUN_AHEAD;
 static inline long long slot_worker_floats(const ModelDims &d) { return d.B * run_shape(d).d4 + (d.B + 3) / 4 * 4; }
 static inline long long run_floats(const ModelDims &d) { return RUN_SLOTS * d.K * slot_worker_floats(d); }
-// What the workers exchange where a round ends, two rounds of it: a word for each parameter, [worker][wavefront of the row][of a lane's
-// four][lane]
+// Library memory of a context: what the workers exchange where a round ends inside a launch, two rounds of it, a word for each
+// parameter, [worker][wavefront of the row][of a lane's four][lane]; the flag of a wait given up; two copies of the parameters
 static inline size_t exchange_bytes(const ModelDims &d) { return 2 * (size_t)d.K * run_shape(d).row * 256 * sizeof(unsigned long long); }
-// ... and behind them the flag of a wait given up
-size_t linreg_run_words_bytes(const ModelDims &d) { return exchange_bytes(d) + sizeof(int); }
-int *linreg_gave_up(const ModelDims &d, void *words) { return (int *)((char *)words + exchange_bytes(d)); }
+static inline float *copies(const ModelDims &d, void *shared) { return (float *)((char *)shared + exchange_bytes(d) + 256); }
+size_t linreg_run_shared_bytes(const ModelDims &d) { return exchange_bytes(d) + 256 + 2 * (size_t)d.K * run_shape(d).d4 * sizeof(float); }
+int *linreg_gave_up(const ModelDims &d, void *shared) { return (int *)((char *)shared + exchange_bytes(d)); }
 
 // exchanges inside a wavefront: lane l gets the value of lane l ^ 8, l ^ 7, l ^ 2, l ^ 1
 template <int CTRL>
@@ -524,11 +524,14 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // only reads its own, one iteration ahead, into a second set of registers; these reads (128 KiB an iteration at 32 x 1024, 2000
 // cycles of a compute unit's first-level cache) are spread over the iteration, where a burst of them holds up
 // the arithmetic behind it (2.1 us an iteration, spread 1.5, without them 1.1).
+// Between launches of a call the parameters stay in library memory, two copies that launches read and write in turn, so that the
+// averaging of a round that ended with a launch is the next one's: every worker reads all rows, where the device's scheduler
+// has just begun a round (a launch of its own: 4 us).  With WAIT a launch averages at its own end, and has no registers for more.
 //
-// Where a round ends, which every workgroup takes from its own reading of the schedule, the workers hand each other their parameters
-// through memory: one 64-bit word for each, the value beside the iteration it is from, written and read past the
-// caches that XCDs do not share.  A reader that finds the iteration has the value, and no flag, fence or launch is needed.  Rounds of a
-// launch take two sets of words in turn: whoever writes a set again has read, in the other one, what all workers wrote behind
+// WAIT: rounds end inside the launch too.  There, as every workgroup takes from its own reading of the schedule, the workers hand
+// each other their parameters through memory: one 64-bit word for each, the value beside the iteration it is from, written and read past
+// the caches that XCDs do not share.  A reader that finds the iteration has the value, and no flag, fence or launch is needed.  Rounds
+// of a launch take two sets of words in turn: whoever writes a set again has read, in the other one, what all workers wrote behind
 // their reading of this one.  The launch that draws a call's first inputs fills the words with an iteration that ends no round of the call.
 // The wait is for workgroups that run or will: the K <= 16 workers are their launch's first workgroups, and the host
 // keeps to devices and streams with compute units for 16 such launches at once.  Should a lane all the same have looked a.polls times
@@ -541,18 +544,23 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
 // 0.8 us an iteration.
 // A lane's words next to each other instead of 64 apart take 0.7 us more a round, two workers a group of wavefronts at a time
 // 0.5 more up to four workers and 0.2 less at sixteen.
+// Without a round's end inside, launches without that code: it takes 6 to 18 registers more and a microsecond a launch (16 x 1000 x 20,
+// rounds of 16, 128 iterations 276 us and 314 with it in all launches; 2 x 256 x 32, one long round, 185 and 199).
 struct LinregRun {
-    LinregStep p;
+    LinregStep p;                        // p.theta: where the parameters go
+    const float *theta_in;               // where they come from: rows of ld_in (ld_out: p.theta's)
+    long long ld_in, ld_out;
     const float *wstar;
     float *slots, *loss;
     unsigned long long *words;           // exchanged parameters: [2][K][row][4][64]
     int polls;                           // looks before a wait is given up (none, and no word counts, below 0)
     int K, B, d, d4, per, n_it, n_draw, draw_off;   // n_draw iterations from the current one plus draw_off on
     unsigned ends;                       // iterations that end a round, as the host's mirror expects
+    int carried;                         // theta_in is averaged on the way in, if its round ended (not with WAIT)
     float sigma;
     uint64_t seed;
     const DevState *st;
-    DevState *st_next;                   // after the launch's iterations
+    DevState *st_next, *st_last;         // after the launch's iterations, and before the last of them
     SchedParams sp;
 };
 
@@ -584,7 +592,7 @@ __device__ __forceinline__ void run_draw(const LinregRun &a, int block, int bloc
     }
 }
 
-template <int ROW, int PER, bool ADAMW>
+template <int ROW, int PER, bool ADAMW, bool WAIT>
 __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
 {
     constexpr int GROUPS = 16 / ROW;
@@ -603,6 +611,7 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
         SchedParams sp = a.sp;
         for (int i = 0; i < a.n_it; ++i) {
             sp.expect_sync = (int)(a.ends >> i & 1);
+            if (i + 1 == a.n_it) *a.st_last = nx;
             sched_advance(&nx, sp);
         }
         *a.st_next = nx;
@@ -611,7 +620,7 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
     __shared__ __attribute__((aligned(16))) float red[16 * PER][4];     // inner products: [sample][wavefront of its row]
     __shared__ float4 part[16][64];                                     // gradient: [wavefront][lane], four columns
     __shared__ float res[16 * PER];                                     // residuals of the last iteration
-    __shared__ float4 other[16][64];                                    // the averaging's, besides part
+    __shared__ float4 other[WAIT ? 16 : 1][64];                         // the averaging's, besides part
     const int k = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s = wave / ROW, cw = wave - s * ROW;
     const bool busy = s < GROUPS;                        // three wavefronts a row: one of the sixteen is left over
@@ -622,12 +631,28 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
 
     float th[4] = {0.f, 0.f, 0.f, 0.f}, m[4] = {0.f, 0.f, 0.f, 0.f}, v[4] = {0.f, 0.f, 0.f, 0.f}, ws[4] = {0.f, 0.f, 0.f, 0.f};
     float g[4] = {0.f, 0.f, 0.f, 0.f};
+    const bool mean = !WAIT && a.carried && a.st->h == 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         if (in && c + e < a.d) {
-            m[e] = a.p.s0[o + e]; ws[e] = a.wstar[c + e]; th[e] = a.p.theta[o + e];
+            m[e] = a.p.s0[o + e]; ws[e] = a.wstar[c + e];
             if (ADAMW) v[e] = a.p.s1[o + e];
+            if (!mean) th[e] = a.theta_in[k * a.ld_in + c + e];
         }
+    if (mean && in) {                                    // rows of a copy: whole groups of four
+        float4 row[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) row[q] = *(const float4 *)(a.theta_in + min(q, a.K - 1) * a.ld_in + c);
+        float sum[4] = {0.f, 0.f, 0.f, 0.f}, err[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            if (q < a.K) {
+                add_comp(sum[0], err[0], row[q].x); add_comp(sum[1], err[1], row[q].y);
+                add_comp(sum[2], err[2], row[q].z); add_comp(sum[3], err[3], row[q].w);
+            }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) th[e] = c + e < a.d ? (sum[e] + err[e]) / (float)a.K : 0.f;
+    }
     if (tid < 16 * PER) {                                // rows of fewer than four wavefronts
 #pragma unroll
         for (int e = 0; e < 4; ++e) red[tid][e] = 0.f;
@@ -646,8 +671,11 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
     };
     // the launch's per-iteration scalars, one iteration a lane, and the period of a round that starts behind it
     const StepScalars mine = a.p.sc[t0 + min(lane, a.n_it - 1)];
-    const int period = (int)min(get_H(a.sp, t0 + 1 + min(lane, a.n_it - 1)), 1ll << 20);
-    int to_go = (int)min(a.st->H - a.st->h, 1ll << 20);  // iterations to the end of the round
+    int period = 0, to_go = 0;                           // to_go: iterations to the end of the round
+    if constexpr (WAIT) {
+        period = (int)min(get_H(a.sp, t0 + 1 + min(lane, a.n_it - 1)), 1ll << 20);
+        to_go = (int)min(a.st->H - a.st->h, 1ll << 20);
+    }
     int set = 0, polls = a.polls;
     // This worker's parameters to the others and everybody's mean, over the workers in order, each addition error-free: a worker a
     // group of wavefronts, GROUPS at a time through LDS, two places in turn
@@ -745,9 +773,11 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
             if (ADAMW) adamw_elem(th[e], g[e], m[e], v[e], sc.x, sc.y, sc.z, a.p.c1, a.p.c2, a.p.eps);
             else sgdm_elem(th[e], g[e], m[e], sc.x, a.p.c1, a.p.c2);
         }
-        if (--to_go == 0) {
-            to_go = __builtin_amdgcn_readlane(period, it);
-            average(it);
+        if constexpr (WAIT) {
+            if (--to_go == 0) {
+                to_go = __builtin_amdgcn_readlane(period, it);
+                average(it);
+            }
         }
     };
     In q0, q1;
@@ -762,7 +792,7 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (in && c + e < a.d) {
-                a.p.theta[o + e] = th[e]; a.p.s0[o + e] = m[e]; a.p.g[o + e] = g[e];
+                a.p.theta[k * a.ld_out + c + e] = th[e]; a.p.s0[o + e] = m[e]; a.p.g[o + e] = g[e];
                 if (ADAMW) a.p.s1[o + e] = v[e];
             }
     }
@@ -775,30 +805,53 @@ __global__ __launch_bounds__(1024) void linreg_run_kernel(LinregRun a)
     }
 }
 
-hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws, void *words,
+hipError_t launch_linreg_average_copy(const ModelDims &d, void *shared, int copy, const DevState *st, hipStream_t s)
+{
+    const long long d4 = run_shape(d).d4;
+    return launch_average_rows(copies(d, shared) + copy * d.K * d4, d.K, d4, st, s);
+}
+
+// us that an exchange takes: 1.7 (2 workers x 256 features), 2.2 (4 x 1024), 2.6 (8 x 256), 4.0 (16 x 257), 6.0 (16 x 1000)
+double linreg_exchange_us(const ModelDims &d)
+{
+    const int groups = run_shape(d).groups;
+    return 1.0 + 0.8 * ((d.K + groups - 1) / groups) + 0.1 * d.K;
+}
+
+hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws, void *shared,
                              float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
                              const SchedParams &sp, hipStream_t s)
 {
     if (!linreg_can_run(d) || span.n_it < 0 || span.n_draw < 0 || span.n_it > LINREG_RUN_MAX || span.draw_off + span.n_draw > RUN_SLOTS)
         return hipErrorInvalidValue;
+    // a round that ends before the last iteration needs workers that wait
+    if (!span.wait && span.n_it > 0 && (span.ends & ((1u << (span.n_it - 1)) - 1)) != 0) return hipErrorInvalidValue;
+    if (span.wait && span.mean) return hipErrorInvalidValue;
     const RunShape q = run_shape(d);
     LinregRun a{};
     a.slots = linreg_slots(d, ws);
-    a.words = (unsigned long long *)words;
+    a.words = (unsigned long long *)shared;
     a.polls = span.polls - 1;
-    a.p = LinregStep{theta, g, s0, s1, sc, c1, c2, eps};
+    auto copy = [&](int i) { return i < 0 ? theta : copies(d, shared) + (long long)i * d.K * q.d4; };
+    a.p = LinregStep{copy(span.out), g, s0, s1, sc, c1, c2, eps};
+    a.theta_in = copy(span.in);
+    a.ld_in = span.in < 0 ? d.d_in : q.d4; a.ld_out = span.out < 0 ? d.d_in : q.d4;
+    a.carried = span.mean;
     a.ends = span.ends;
     a.wstar = wstar; a.loss = loss;
     a.K = d.K; a.B = (int)d.B; a.d = (int)d.d_in; a.d4 = q.d4; a.per = q.per;
     a.n_it = span.n_it; a.n_draw = span.n_draw; a.draw_off = span.draw_off;
-    a.sigma = d.data_sigma; a.seed = d.seed; a.st = span.st; a.st_next = span.st_next; a.sp = sp;
+    a.sigma = d.data_sigma; a.seed = d.seed; a.st = span.st; a.st_next = span.st_next; a.st_last = span.st_last; a.sp = sp;
     const int blocks = (int)((d.B * d.d_in + 3) / 4 + (d.B + 3) / 4 + 1023) / 1024;
     const unsigned grid = (unsigned)((a.n_it > 0 ? d.K + 1 : 0) + a.n_draw * d.K * blocks);
     if (grid == 0) return hipSuccess;
-#define RUN(ROW, PER) do { if (s1) linreg_run_kernel<ROW, PER, true><<<grid, 1024, 0, s>>>(a); else linreg_run_kernel<ROW, PER, false><<<grid, 1024, 0, s>>>(a); } while (0)
-#define RUN_ROW(ROW) do { if (q.per <= 2) RUN(ROW, 2); else if (q.per <= 4) RUN(ROW, 4); else RUN(ROW, 8); } while (0)
+#define RUN(ROW, PER, ADAMW) do { if (span.wait) linreg_run_kernel<ROW, PER, ADAMW, true><<<grid, 1024, 0, s>>>(a); \
+                                  else linreg_run_kernel<ROW, PER, ADAMW, false><<<grid, 1024, 0, s>>>(a); } while (0)
+#define RUN_OPT(ROW, PER) do { if (s1) RUN(ROW, PER, true); else RUN(ROW, PER, false); } while (0)
+#define RUN_ROW(ROW) do { if (q.per <= 2) RUN_OPT(ROW, 2); else if (q.per <= 4) RUN_OPT(ROW, 4); else RUN_OPT(ROW, 8); } while (0)
     if (q.row == 1) RUN_ROW(1); else if (q.row == 2) RUN_ROW(2); else if (q.row == 3) RUN_ROW(3); else RUN_ROW(4);
 #undef RUN_ROW
+#undef RUN_OPT
 #undef RUN
     return hipGetLastError();
 }

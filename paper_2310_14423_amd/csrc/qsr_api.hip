@@ -39,13 +39,13 @@ struct qsr_ctx {
     void *workspace;
     size_t workspace_bytes;
     // library-owned device memory
-    DevState *d_state;       // two copies; `cur` is the one the next kernels read (see ticked)
+    DevState *d_state;       // two copies; `cur` is the one the next kernels read (see ticked); a third for qsr_run's averaging
     int cur;
     bool ticked;             // the update kernel has advanced the scheduler (into the copy that is current now) for
                              // the local step whose qsr_maybe_sync is pending
     bool fuse_linreg;        // least squares: the gradient kernel takes the update of its columns too
     bool run_linreg;         //   and iterations enqueued together need no launch of their own
-    void *d_words;           //   but words for what the workers exchange where a round ends, and a flag if that failed
+    void *d_shared;          //   but memory for what the workers exchange where a round ends, and a flag if that failed
     int run_polls;           //   looks for another worker's words before it has
     double *d_eta;
     StepScalars *d_scal;
@@ -55,7 +55,7 @@ struct qsr_ctx {
     float *d_clip_coef;      // [K] factors, then [K] gradient norms
     // host mirrors
     std::vector<double> eta;
-    DevState *h_state;       // pinned, and behind it the flag in d_words
+    DevState *h_state;       // pinned, and behind it the flag in d_shared
     long long t_host;        // local steps enqueued
     bool need_sync_call;     // a local step was enqueued and its maybe_sync not yet
     // Mirror of the device scheduler's integers (t, s, h, H), advanced on the host with the same
@@ -356,7 +356,7 @@ static void free_ctx(qsr_ctx *c)
     for (auto &p : c->pairs) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
     for (auto e : c->free_events) (void)hipEventDestroy(e);
     if (c->d_state) (void)hipFree(c->d_state);
-    if (c->d_words) (void)hipFree(c->d_words);
+    if (c->d_shared) (void)hipFree(c->d_shared);
     if (c->d_eta) (void)hipFree(c->d_eta);
     if (c->d_scal) (void)hipFree(c->d_scal);
     if (c->d_log_t) (void)hipFree(c->d_log_t);
@@ -369,7 +369,7 @@ static void free_ctx(qsr_ctx *c)
     delete c;
 }
 
-static int *dev_gave_up(qsr_ctx *c) { return c->run_linreg ? linreg_gave_up(c->dims, c->d_words) : nullptr; }
+static int *dev_gave_up(qsr_ctx *c) { return c->run_linreg ? linreg_gave_up(c->dims, c->d_shared) : nullptr; }
 
 static int init_impl(qsr_ctx *c, const float *theta0)
 {
@@ -385,8 +385,8 @@ static int init_impl(qsr_ctx *c, const float *theta0)
         if (rc != QSR_OK) return rc;
     }
 
-    HIP_TRY(hipMalloc((void **)&c->d_state, 2 * sizeof(DevState)));
-    if (c->run_linreg) HIP_TRY(hipMalloc(&c->d_words, linreg_run_words_bytes(c->dims)));
+    HIP_TRY(hipMalloc((void **)&c->d_state, 3 * sizeof(DevState)));
+    if (c->run_linreg) HIP_TRY(hipMalloc(&c->d_shared, linreg_run_shared_bytes(c->dims)));
     HIP_TRY(hipMalloc((void **)&c->d_eta, T * sizeof(double)));
     HIP_TRY(hipMalloc((void **)&c->d_scal, T * sizeof(StepScalars)));
     HIP_TRY(hipMalloc((void **)&c->d_log_t, T * sizeof(long long)));
@@ -450,7 +450,7 @@ extern "C" int qsr_init(const qsr_config *cfg, float *params, float *grads, floa
     c->params = params; c->grads = grads; c->state0 = state0;
     c->state1 = cfg->opt == QSR_OPT_ADAMW ? state1 : nullptr;
     c->model_const = model_const; c->workspace = workspace; c->workspace_bytes = workspace_bytes;
-    c->d_state = nullptr; c->d_words = nullptr; c->d_eta = nullptr; c->d_scal = nullptr; c->d_log_t = nullptr;
+    c->d_state = nullptr; c->d_shared = nullptr; c->d_eta = nullptr; c->d_scal = nullptr; c->d_log_t = nullptr;
     c->d_log_H = nullptr; c->d_loss = nullptr; c->h_state = nullptr;
     c->d_clip_part = nullptr; c->d_clip_coef = nullptr;
     c->t_host = 0; c->need_sync_call = false; c->timing = false; c->capturing = false;
@@ -677,44 +677,74 @@ static int run_one_by_one(qsr_ctx *c, long long n)
     return QSR_OK;
 }
 
-// Least squares on workers that fit one workgroup: launches of up to LINREG_RUN_MAX iterations, rounds ending inside them, each
-// drawing inputs ahead for the launches behind it, but none beyond this call.  The first takes few, so that not many
-// inputs have to be drawn ahead of everything.
+// Least squares on workers that fit one workgroup: launches of up to LINREG_RUN_MAX iterations, each drawing inputs ahead for the
+// launches behind it, but none beyond this call.  `wait`: rounds may end inside them.
 constexpr long long LINREG_RUN_FIRST = 8;
-static int run_linreg(qsr_ctx *c, long long n)
+constexpr double LINREG_LAUNCH_US = 6.5;                 // from a launch to the next
+static int run_linreg(qsr_ctx *c, long long n, bool wait)
 {
     const qsr_config &cfg = c->cfg;
     const bool sgd = cfg.opt == QSR_OPT_SGDM;
     const float c1 = (float)(sgd ? cfg.momentum : 1.0 - cfg.beta1), c2 = (float)(sgd ? cfg.weight_decay : 1.0 - cfg.beta2);
+    const double exchange = linreg_exchange_us(c->dims);
     long long drawn = 0;                                 // iterations from the current one on
+    int from = -1;                                       // where the parameters are
+    bool due = false;                                    // and whether they are to be averaged
+    DevState *const st_last = c->d_state + 2;
+    auto average = [&](int copy) {
+        return copy < 0 ? launch_average_rows(c->params, cfg.K, cfg.P, st_last, c->stream)
+                        : launch_linreg_average_copy(c->dims, c->d_shared, copy, st_last, c->stream);
+    };
     auto launch = [&](const LinregSpan &span) {
         return launch_linreg_run(c->dims, c->params, c->grads, c->state0, sgd ? nullptr : c->state1, c->model_const, c->workspace,
-                                 c->d_words, c->d_loss, c->d_scal, c1, c2, (float)cfg.eps, span, c->sp, c->stream);
+                                 c->d_shared, c->d_loss, c->d_scal, c1, c2, (float)cfg.eps, span, c->sp, c->stream);
     };
     while (n > 0) {
+        const long long left = c->m_H - c->m_h;
         long long seg = n < LINREG_RUN_MAX ? n : LINREG_RUN_MAX;
-        if (drawn == 0) {                                // the first launch's inputs
-            if (seg > LINREG_RUN_FIRST) seg = LINREG_RUN_FIRST;
-            HIP_TRY(launch({0, 0, (int)seg, 0, 0, st_cur(c), nullptr}));
+        if (!wait && left < seg) seg = left;
+        if (drawn == 0) {                                // the first launch's inputs, ahead of everything: few, but no launch more for that
+            const long long rest = left <= seg ? left : (n - 1) % LINREG_RUN_MAX + 1, first = rest > LINREG_RUN_FIRST ? rest : LINREG_RUN_FIRST;
+            if (seg > first) seg = first;
+            HIP_TRY(launch({0, 0, (int)seg, -1, -1, false, false, 0, 0, st_cur(c), nullptr, nullptr}));
             drawn = seg;
         }
         if (seg > drawn) seg = drawn;
-        const long long draws = (n < LINREG_RUN_AHEAD ? n : LINREG_RUN_AHEAD) - drawn;
+        // The rounds that end in the launch.  Where the last of them ends before it, the launch ends with that one if that is cheaper
+        // for each of its iterations than another exchange (rounds of 12 with 16 workers 0.54 and 0.8 us), by a fifth if others
+        // stay inside: launches short of one or two iterations add up to one more.
         unsigned ends = 0;
-        for (long long i = 0, left = c->m_H - c->m_h; i < seg; ++i)
-            if (--left == 0) { ends |= 1u << i; left = host_get_H(c->sp, c->eta.data(), c->m_t + i + 1); }
-        HIP_TRY(launch({(int)seg, (int)drawn, (int)draws, ends, c->run_polls, st_cur(c), c->d_state + (c->cur ^ 1)}));
+        long long end = 0;
+        int rounds = 0;
+        for (long long i = 0, to_go = left; i < seg; ++i)
+            if (--to_go == 0) {
+                ends |= 1u << i; end = i + 1; ++rounds;
+                to_go = host_get_H(c->sp, c->eta.data(), c->m_t + i + 1);
+            }
+        const double with = (LINREG_LAUNCH_US + rounds * exchange) / (double)seg;
+        if (end > 0 && end < seg && seg < n &&
+            (LINREG_LAUNCH_US + (rounds - 1) * exchange) / (double)end < (rounds > 1 ? with / 1.2 : with))
+            seg = end;
+        const bool done = seg == n, sync = end == seg, inside = rounds > (sync ? 1 : 0);
+        if (inside && due) { HIP_TRY(average(from)); due = false; }
+        const long long draws = (n < LINREG_RUN_AHEAD ? n : LINREG_RUN_AHEAD) - drawn;
+        const int to = done ? -1 : from == 0 ? 1 : 0;
+        HIP_TRY(launch({(int)seg, (int)drawn, (int)draws, from, to, inside, due, ends, c->run_polls, st_cur(c),
+                        c->d_state + (c->cur ^ 1), st_last}));
         for (long long i = 0; i < seg; ++i) mirror_advance(c);
         drawn += draws - seg;
         c->cur ^= 1;
         c->t_host += seg;
         n -= seg;
+        from = to;
+        due = sync && !inside;
     }
+    if (due) HIP_TRY(average(-1));
     return QSR_OK;
 }
 
-// The K workers of such a launch wait for each other, so all have to be resident, a compute unit each, whatever else is: streams
-// that may use fewer than 16 K compute units take their iterations one by one (16 launches at once are four processes' hardware queues).
+// Workers that wait for each other all have to be resident, a compute unit each, whatever else is: on streams that may use fewer than
+// 16 K compute units launches end with the round (16 launches at once are four processes' hardware queues).
 static bool workers_fit(const qsr_ctx *c)
 {
     uint32_t mask[32] = {0};
@@ -739,7 +769,7 @@ extern "C" int qsr_run(qsr_ctx *c, int64_t n)
 {
     if (!c || n < 0) return QSR_EINVAL;
     if (c->need_sync_call || n > c->cfg.T - c->t_host) return QSR_ESTATE;
-    if (c->run_linreg && n >= 2 && !c->timing && !caller_records(c->stream) && workers_fit(c)) return run_linreg(c, n);
+    if (c->run_linreg && n >= 2 && !c->timing && !caller_records(c->stream)) return run_linreg(c, n, workers_fit(c));
     const long long per = c->run_linreg ? 0 : c->graph_iters;
     // the null stream cannot be captured; with timing on every launch gets its own event bracket
     if (c->timing || c->stream == nullptr || per < 1 || n < 1 + 2 * per) return run_one_by_one(c, n);

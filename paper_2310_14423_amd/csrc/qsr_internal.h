@@ -183,24 +183,31 @@ hipError_t launch_linreg_grad_update(const ModelDims &d, float *theta, float *g,
                                      const DevState *st, DevState *st_next, bool average, const SchedParams &sp,
                                      hipStream_t s);
 
-// Iterations together: n_it of them with the averaging of the rounds that they end, for workers that fit one workgroup each (least
+// Iterations together: n_it of them, for workers that fit one workgroup each (least
 // squares), and the draws of n_draw iterations from the current one plus draw_off on, which a later launch's iterations read.  The
 // same bits as one by one.  A launch of draws alone (n_it = 0) has to come first in a call, and the launches of a call one behind the other.
 constexpr int LINREG_RUN_AHEAD = 32, LINREG_RUN_MAX = 16;      // draws held, iterations of a launch
 constexpr int LINREG_RUN_POLLS = 1 << 27;                      // looks, of about a microsecond, before a wait is given up
 struct LinregSpan {
     int n_it, draw_off, n_draw;
+    int in, out;                     // parameters read and written: -1 the caller's, 0 and 1 copies in `shared`
+    bool wait;                       // rounds end inside the launch, where the workers wait for each other; otherwise one may end with it,
+                                     // whose averaging is left to the next launch or to launch_average_rows
+    bool mean;                       // if a round has just ended, the parameters read are averaged first (not with wait)
     unsigned ends;                   // bit i: iteration i ends a round, as the host's mirror expects
     int polls;                       // looks before a wait is given up
     const DevState *st;
-    DevState *st_next;               // the state after the iterations
+    DevState *st_next, *st_last;     // the state after the iterations, and before the last of them
 };
 bool linreg_can_run(const ModelDims &d);
-// what the workers exchange where a round ends (device memory, 8-byte aligned, contents irrelevant before a call), and a flag that a
-// launch sets where a wait is given up (launch_sched_init and launch_sched_set clear it)
-size_t linreg_run_words_bytes(const ModelDims &d);
-int *linreg_gave_up(const ModelDims &d, void *words);
-hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws, void *words,
+// `shared`, device memory (256-byte aligned, contents irrelevant before a call): what the workers exchange where a round ends, copies of the
+// parameters, and a flag that a launch sets where a wait is given up (launch_sched_init and launch_sched_set clear it)
+size_t linreg_run_shared_bytes(const ModelDims &d);
+int *linreg_gave_up(const ModelDims &d, void *shared);
+double linreg_exchange_us(const ModelDims &d);
+// the averaging of a copy, if *st says that the round ends
+hipError_t launch_linreg_average_copy(const ModelDims &d, void *shared, int copy, const DevState *st, hipStream_t s);
+hipError_t launch_linreg_run(const ModelDims &d, float *theta, float *g, float *s0, float *s1, const float *wstar, void *ws, void *shared,
                              float *loss, const StepScalars *sc, float c1, float c2, float eps, const LinregSpan &span,
                              const SchedParams &sp, hipStream_t s);
 
