@@ -262,15 +262,17 @@ __global__ __launch_bounds__(64 * LOGIT_WAVES) void mlp2_logits_ce_kernel(const 
     if (lane == 0) pt[16] = ls;
 }
 
-// Output layer backward for at most 16 classes, one workgroup per 32 hidden units of a worker:
+// Output layer backward for at most 16 classes, one workgroup per UNITS hidden units of a worker:
 // gW2[j][c] = sum_i hid[i][j] dlogit[i][c], dhid[i][j] = [hid[i][j] > 0] sum_c dlogit[i][c] W2[j][c],
-// gb1[j] = sum_i dhid[i][j]; a thread owns a hidden unit and every sixteenth sample (its loads of hid go
-// out eight at a time before the first is used), the sixteen partial sums are added pairwise
+// gb1[j] = sum_i dhid[i][j]; a thread owns a hidden unit and every SHARES-th sample (its loads of hid go
+// out eight at a time before the first is used), the SHARES partial sums are added pairwise
 // through LDS.  The first workgroup of a worker also adds up the tiles of
 // mlp2_logits_ce_kernel: gb2 and the mean cross-entropy.  (These were three launches of the tiled
-// GEMM and a column-sum kernel, 5 to 9 us each whatever they did.)  32 units, so that 8 workers with 1024 fill the chip:
-// 8.2 us with 128 samples of 10 classes, with 64 units and eight shares of the samples 10.0.
-constexpr int OUT_UNITS = 32, OUT_SHARES = 512 / OUT_UNITS;
+// GEMM and a column-sum kernel, 5 to 9 us each whatever they did.)  32 units while each workgroup has a compute unit to itself, 64
+// beyond: every workgroup stages all of dlogit, and two on a compute unit do so one behind the other (us, 32 / 64, 10 classes):
+//   8 x 1024 units, 128 samples (256 workgroups of 32) 8.2 / 9.4;  8 x 1056 (264) 12.0 / 10.4;  16 x 1024 (512) 15.4 / 10.8;
+//   4 x 2048, 512 samples 22.5 / 29.2;  16 x 4096, 512 samples 120 / 101;  16 classes, 16 x 1024, 32 samples 15.4 / 10.0
+template <int UNITS>
 __global__ __launch_bounds__(512) void mlp2_out_bwd_kernel(const float *__restrict__ hid,
                                                            const float *__restrict__ dlogit,
                                                            const float *__restrict__ theta,
@@ -280,9 +282,10 @@ __global__ __launch_bounds__(512) void mlp2_out_bwd_kernel(const float *__restri
                                                            float *__restrict__ loss, int B, int dh, int ldh, int C)
 {
     __shared__ __attribute__((aligned(16))) float dl_s[128][16];
-    __shared__ float red[OUT_SHARES][OUT_UNITS][17];
-    const int tid = threadIdx.x, tj = tid % OUT_UNITS, ti = tid / OUT_UNITS;
-    const int k = blockIdx.y, j0 = blockIdx.x * OUT_UNITS, j = j0 + tj;
+    constexpr int SHARES = 512 / UNITS;
+    __shared__ float red[SHARES][UNITS][17];
+    const int tid = threadIdx.x, tj = tid % UNITS, ti = tid / UNITS;
+    const int k = blockIdx.y, j0 = blockIdx.x * UNITS, j = j0 + tj;
     const bool jin = j < dh;
     float w2[16], gw[16], cs = 0.f;
 #pragma unroll
@@ -300,16 +303,16 @@ __global__ __launch_bounds__(512) void mlp2_out_bwd_kernel(const float *__restri
         }
         __syncthreads();
 #pragma unroll 1
-        for (int part8 = 0; part8 < 128 / OUT_SHARES; part8 += 8) {
+        for (int part8 = 0; part8 < 128 / SHARES; part8 += 8) {
             float hv[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int i = i0 + ti + OUT_SHARES * (part8 + u);
+                const int i = i0 + ti + SHARES * (part8 + u);
                 hv[u] = (jin && i < B) ? hk[(long long)i * ldh + j] : 0.f;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int rr = ti + OUT_SHARES * (part8 + u), i = i0 + rr;
+                const int rr = ti + SHARES * (part8 + u), i = i0 + rr;
                 const float4 *dl4 = (const float4 *)dl_s[rr];
                 const float4 x0 = dl4[0], x1 = dl4[1], x2 = dl4[2], x3 = dl4[3];
                 const float dl[16] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w,
@@ -330,13 +333,13 @@ __global__ __launch_bounds__(512) void mlp2_out_bwd_kernel(const float *__restri
     red[ti][tj][16] = cs;
     __syncthreads();
     float *gk = g + (long long)k * P;
-    for (int idx = tid; idx < OUT_UNITS * 17; idx += 512) {
+    for (int idx = tid; idx < UNITS * 17; idx += 512) {
         const int jj = idx / 17, c = idx - jj * 17;
-        float v[OUT_SHARES];
+        float v[SHARES];
 #pragma unroll
-        for (int t = 0; t < OUT_SHARES; ++t) v[t] = red[t][jj][c];
+        for (int t = 0; t < SHARES; ++t) v[t] = red[t][jj][c];
 #pragma unroll
-        for (int n = OUT_SHARES / 2; n >= 1; n >>= 1)
+        for (int n = SHARES / 2; n >= 1; n >>= 1)
 #pragma unroll
             for (int t = 0; t < n; ++t) v[t] += v[t + n];
         if (j0 + jj < dh) {
@@ -384,7 +387,9 @@ hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, co
         mlp2_logits_ce_kernel<<<dim3((unsigned)tiles, (unsigned)K), 64 * LOGIT_WAVES, 0, s>>>(
             w.hid, theta, P, oW2, ob2, w.label, w.logit, w.part, (int)B, (int)dh, (int)w.ldh, (int)dz);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        mlp2_out_bwd_kernel<<<dim3((unsigned)((dh + OUT_UNITS - 1) / OUT_UNITS), (unsigned)K), 512, 0, s>>>(
+        const bool small = (dh + 31) / 32 * K <= 256;
+        auto back = small ? mlp2_out_bwd_kernel<32> : mlp2_out_bwd_kernel<64>;
+        back<<<dim3((unsigned)(small ? (dh + 31) / 32 : (dh + 63) / 64), (unsigned)K), 512, 0, s>>>(
             w.hid, w.logit, theta, w.dhid, g, P, oW2, ob1, ob2, w.part, tiles, loss, (int)B, (int)dh, (int)w.ldh, (int)dz);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {

@@ -1,6 +1,6 @@
 """GPU: the perceptron's output layer for at most 16 classes at the edges of what a workgroup takes: samples in sixteens (logits) and
 hundreds and twenty-eights (backward), hidden units in sixteens, sixteen wavefronts' shares of them, some without any, and, backward, in
-thirty-twos; one, two and sixteen classes."""
+thirty-twos up to 256 workgroups and in sixty-fours beyond; one, two and sixteen classes."""
 import pytest
 
 from test_gpu_parity import test_mlp2_gradient_single_step as gradient_case
@@ -16,6 +16,9 @@ pytestmark = pytest.mark.gpu
     dict(d_in=70, d_hidden=257, d_out=10, B_loc=16, K=2),
     dict(d_in=70, d_hidden=65, d_out=7, B_loc=129, K=2),
     dict(d_in=70, d_hidden=40, d_out=2, B_loc=260, K=1),
+    dict(d_in=10, d_hidden=1024, d_out=10, B_loc=20, K=8),      # 256 workgroups of 32 units
+    dict(d_in=10, d_hidden=1025, d_out=10, B_loc=129, K=8),     # 136 of 64, the last with one unit
+    dict(d_in=10, d_hidden=1983, d_out=16, B_loc=33, K=5),      # 155 of 64, the last one unit short
 ])
 def test_output_layer(dims):
     gradient_case(dims)
