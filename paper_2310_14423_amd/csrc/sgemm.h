@@ -50,7 +50,7 @@ struct SgemmSlabs { float A[16][96], B[16][96]; };
 template <int KSPLIT> union SgemmLds {
     static_assert(KSPLIT == 2, "one group or two");
     SgemmSlabs slab[KSPLIT];
-    float part[KSPLIT][4][8][64];
+    float part[4][16][64];                               // the second group's sums
 };
 template <> union SgemmLds<1> { SgemmSlabs slab[1]; };
 static_assert(sizeof(SgemmLds<2>) == 24 * 1024, "partial sums inside the slabs");
@@ -171,40 +171,38 @@ __device__ __forceinline__ void sgemm_tile(const GemmArgs &a, int bx, int by, in
         }
     }
     float *C = a.C + bz * a.sC;
-    // Accumulator element i of lane l is C[(i/4)*8 + (l/32)*4 + i%4][l%32] of the wavefront's block.  Two groups add up and write
-    // half of the tile each (in group order); what the epilogue reads comes before, clamped into the matrix: behind a
-    // test and a wait of its own, each of the sixteen loads took its latency (5 x 50 x 500 x 100, both products in a launch: 12.9 ->
-    // 10.2 us).
-    constexpr int EACH = 16 / KSPLIT;
+    // The second group's sums go to the first, which writes the tile alone: the second's wavefronts make room for the next
+    // workgroup's.  (Half of the tile written by each: 8 x 400 x 784 x 1024 74.7 against 66.9 us, 1 x 70 x 300 x 500 7.0 against 5.6.)
+    if constexpr (KSPLIT == 2) {
+        if (TA && !TB && col_wg) __syncthreads();     // the column sums are read
+        if (grp > 0) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) lds.part[tid >> 6][i][lane] = acc[i];
+        }
+        __syncthreads();
+        if (grp > 0) return;
+    }
+    // Accumulator element i of lane l is C[(i/4)*8 + (l/32)*4 + i%4][l%32] of the wavefront's block.  What the epilogue reads comes before
+    // the first use, clamped into the matrix: behind a test and a wait of its own, each of the sixteen loads took its latency
+    // (4 x 70 x 500 x 100, both products in a launch: 12.3 -> 9.6 us).
     const int gn = n0 + wn * 32 + (lane & 31);
-    auto row = [&](int u) { const int i = grp * EACH + u; return m0 + wm * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3); };
-    float aux[EACH];
+    auto row = [&](int i) { return m0 + wm * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3); };
+    float aux[16];
     if (EPI == EPI_MASK_POS) {
         const float *x = a.aux + bz * a.sC + min(gn, a.N - 1);
 #pragma unroll
-        for (int u = 0; u < EACH; ++u) aux[u] = x[(long long)min(row(u), a.M - 1) * a.ldc];
+        for (int i = 0; i < 16; ++i) aux[i] = x[(long long)min(row(i), a.M - 1) * a.ldc];
     }
-    float out[EACH];
     if constexpr (KSPLIT == 2) {
-        if (TA && !TB && col_wg) __syncthreads();     // the column sums are read
 #pragma unroll
-        for (int u = 0; u < EACH; ++u) lds.part[grp][tid >> 6][u][lane] = grp == 0 ? acc[EACH + u] : acc[u];
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            const float other = lds.part[grp ^ 1][tid >> 6][u][lane];
-            out[u] = (grp == 0 ? acc[u] : acc[EACH + u]) + other;
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) out[u] = acc[u];
+        for (int i = 0; i < 16; ++i) acc[i] += lds.part[tid >> 6][i][lane];
     }
 #pragma unroll
-    for (int u = 0; u < EACH; ++u) {
-        if (row(u) >= a.M || gn >= a.N) continue;
-        float v = out[u];
-        if (EPI == EPI_MASK_POS) v = aux[u] > 0.f ? v : 0.f;
-        C[(long long)row(u) * a.ldc + gn] = v;
+    for (int i = 0; i < 16; ++i) {
+        if (row(i) >= a.M || gn >= a.N) continue;
+        float v = acc[i];
+        if (EPI == EPI_MASK_POS) v = aux[i] > 0.f ? v : 0.f;
+        C[(long long)row(i) * a.ldc + gn] = v;
     }
 }
 
