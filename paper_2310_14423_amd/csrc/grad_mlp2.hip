@@ -134,18 +134,6 @@ __global__ __launch_bounds__(256) void mlp2_softmax_ce_kernel(float *__restrict_
     if (lane == 0) sample_loss[(long long)k * B + i] = logf(se) - zy;
 }
 
-// Output layer forward and loss for at most 16 classes, one workgroup per 16 samples of a worker:
-// logits = hid W2 + b2 with products and sums in double precision on the fp64 matrix cores (one
-// 16x16x4 instruction covers 16 samples x 16 classes x 4 hidden units; the sixteen wavefronts take a
-// sixteenth of the hidden units each, and the first four add up the partial results, in order, of four samples each), then
-// the softmax of each row across the 16 lanes that hold it: the maximum is subtracted in double
-// before anything is rounded to fp32.  At the workload's step size the logits grow into the hundreds
-// within a few iterations, where one fp32 ulp of a logit (6e-5 at 600) would be the relative error
-// of the probability computed from it; the difference to the largest logit is small and rounds
-// harmlessly.  Written: dlogit = (softmax - onehot)/B, and per tile the column sums of dlogit and
-// the summed cross-entropy (mlp2_out_bwd_kernel adds the tiles up).
-// Bound by latency, 64 workgroups at 8 x 128 samples: 8.2 us with 1024 hidden units, 10 classes (10.8 with eight wavefronts, the
-// softmax of all sixteen samples in the first one and exchanges through LDS).
 // Exchanges inside a row of 16 lanes: with lane ^ 1, ^ 2, ^ 7, ^ 8 (in a sum or a maximum ^ 7 stands for ^ 4: the four
 // lanes of a group already hold the same)
 template <int CTRL> __device__ __forceinline__ float row_get(float v)
@@ -171,8 +159,23 @@ __device__ __forceinline__ double row_max(double v)
     return t > v ? t : v;
 }
 
-constexpr int LOGIT_WAVES = 16;
-__global__ __launch_bounds__(64 * LOGIT_WAVES) void mlp2_logits_ce_kernel(const float *__restrict__ hid,
+// Output layer forward and loss for at most 16 classes, one workgroup per 16 samples of a worker:
+// logits = hid W2 + b2 with products and sums in double precision on the fp64 matrix cores (one
+// 16x16x4 instruction covers 16 samples x 16 classes x 4 hidden units; each of the WAVES wavefronts takes its
+// share of the hidden units, and the first four add up the partial results, in order, of four samples each), then
+// the softmax of each row across the 16 lanes that hold it: the maximum is subtracted in double
+// before anything is rounded to fp32.  At the workload's step size the logits grow into the hundreds
+// within a few iterations, where one fp32 ulp of a logit (6e-5 at 600) would be the relative error
+// of the probability computed from it; the difference to the largest logit is small and rounds
+// harmlessly.  Written: dlogit = (softmax - onehot)/B, and per tile the column sums of dlogit and
+// the summed cross-entropy (mlp2_out_bwd_kernel adds the tiles up).
+// Bound by latency, 64 workgroups at 8 x 128 samples: 8.2 us with 1024 hidden units, 10 classes (10.8 with eight wavefronts, the
+// softmax of all sixteen samples in the first one and exchanges through LDS).  Sixteen wavefronts while each workgroup has a
+// compute unit to itself, eight beyond (us, 16 / 8, at 64, 1024 and 3000 units):
+//   128 workgroups 4.0 / 3.8, 8.5 / 9.4, 18.0 / 20.4;  256 4.0 / 3.9, 9.4 / 9.8, 19.6 / 21.6;  264 5.7 / 4.2, 15.5 / 14.1, 33.6 / 30.7;
+//   512 6.0 / 4.4, 16.7 / 15.1, 36.9 / 33.0;  2048 17.8 / 9.3, 58 / 44, 171 / 147
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void mlp2_logits_ce_kernel(const float *__restrict__ hid,
                                                              const float *__restrict__ theta, long long P,
                                                              long long oW2, long long ob2,
                                                              const int *__restrict__ label,
@@ -180,14 +183,14 @@ __global__ __launch_bounds__(64 * LOGIT_WAVES) void mlp2_logits_ce_kernel(const 
                                                              float *__restrict__ part,
                                                              int B, int dh, int ldh, int C)
 {
-    __shared__ double dpart[LOGIT_WAVES][4][64];
+    __shared__ double dpart[WAVES][4][64];
     __shared__ float2 row_out[4][64];                    // a lane's dlogit and its row's loss
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int r = lane & 15, q = lane >> 4;
     const int k = blockIdx.y, row0 = blockIdx.x * 16;
     const float *A = hid + (long long)k * B * ldh;
     const float *W = theta + (long long)k * P + oW2;
-    const int ng = (dh + 15) / 16, ngw = (ng + LOGIT_WAVES - 1) / LOGIT_WAVES;
+    const int ng = (dh + 15) / 16, ngw = (ng + WAVES - 1) / WAVES;
     const int g0 = w * ngw, g1 = min(ng, g0 + ngw);
     const int arow = row0 + r;
 
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(64 * LOGIT_WAVES) void mlp2_logits_ce_kernel(const 
     if (w < 4) {
         double z = dpart[0][w][lane];
 #pragma unroll
-        for (int g = 1; g < LOGIT_WAVES; ++g) z += dpart[g][w][lane];
+        for (int g = 1; g < WAVES; ++g) z += dpart[g][w][lane];
         const bool cin = r < C;
         const int row = row0 + 4 * w + q;
         const bool rin = row < B;
@@ -384,7 +387,9 @@ hipError_t launch_mlp2_grad(const ModelDims &d, const float *theta, float *g, co
         // logits, softmax and loss in one launch; gW2, dhid, gb1 (and the sums that finish gb2 and
         // the loss) in a second
         const int tiles = (int)((B + 15) / 16);
-        mlp2_logits_ce_kernel<<<dim3((unsigned)tiles, (unsigned)K), 64 * LOGIT_WAVES, 0, s>>>(
+        const bool many = (long long)tiles * K > 256;
+        auto logits = many ? mlp2_logits_ce_kernel<8> : mlp2_logits_ce_kernel<16>;
+        logits<<<dim3((unsigned)tiles, (unsigned)K), many ? 512 : 1024, 0, s>>>(
             w.hid, theta, P, oW2, ob2, w.label, w.logit, w.part, (int)B, (int)dh, (int)w.ldh, (int)dz);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const bool small = (dh + 31) / 32 * K <= 256;
