@@ -219,6 +219,19 @@ __device__ __forceinline__ int quotient(int n, int d, float inv)
     return q;
 }
 
+// A kernel's arguments, BYTES of them beginning with these two, requested at once.  Left to the compiler, each load goes out shortly before
+// its use, and a wavefront that has nothing else to do waits for one line of the arguments after the other: the launches of 2310 products
+// of 142 random blocks take 0.972 of that, those below 6 us 0.962.
+template <size_t BYTES>
+__device__ __forceinline__ void request_arguments(const GemmNT &p, const NtGrid &g)
+{
+    const auto *args = (__attribute__((address_space(4))) const int *)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int LAST = (int)(BYTES / 4) - 1, THIRD = LAST > 32 ? 32 : LAST;      // lines of 16 words
+    static_assert(sizeof(GemmNT) + sizeof(NtGrid) > 64 && LAST < 48, "the first two lines by the values, a third by its first word");
+    asm volatile("" :: "s"(p.A), "s"(p.B), "s"(p.lda), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.sA), "s"(p.sB), "s"(g.nx), "s"(g.ny), "s"(g.per_z),
+                 "s"(g.tiles), "s"(g.share), "s"(g.inv_per_z), "s"(g.inv_panel), "s"(args[THIRD]));
+}
+
 // f(n - 1), ..., f(0), the numbers as types
 template <int N, class F>
 __device__ __forceinline__ void unrolled(F f)
@@ -233,8 +246,9 @@ __device__ __forceinline__ void unrolled(F f)
 // A, then [BN rows][32 k] of B, rows of 64 B, slot s of row r holding piece s ^ ((r >> 3) & 1) * 2.
 // WPS: wavefronts per SIMD the registers are budgeted for.
 template <int BM, int BN, int WM, int WN, int WPS, int NS, bool BLKA, class Epi>
-__global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT p, Epi epi, NtGrid g)
+__global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT p, NtGrid g, Epi epi)
 {
+    request_arguments<sizeof(GemmNT) + sizeof(NtGrid) + sizeof(Epi)>(p, g);
     constexpr int BK = 32, NW = WM * WN;
     constexpr int TM = BM / WM / 16, TN = BN / WN / 16, MM = TM * TN;
     constexpr int CA = BM / 16, CB = BN / 16;           // 1 KiB chunks (16 rows x 64 B) per stage
@@ -254,7 +268,7 @@ __global__ __launch_bounds__(WM * WN * 64, WPS) void gemm_nt_bf16_kernel(GemmNT 
     // (Panels of 2, 3, 6 or 12 tiles: the same to 3 %, the narrow ones slower at N = 768.)
     int tile = (blockIdx.x % 8) * g.share + blockIdx.x / 8;
     if (tile >= g.tiles) return;
-    // all of a wavefront's requests depend on these: the arguments in one load, quotients by multiplication
+    // all of a wavefront's requests depend on these: quotients by multiplication
     const int z = quotient(tile, g.per_z, g.inv_per_z);
     tile -= z * g.per_z;
     constexpr int PANEL = 4;
@@ -487,7 +501,7 @@ inline hipError_t launch_gemm_nt(const GemmNT &p, const Epi &epi, int batch, hip
     NtGrid g;
     g.nx = (p.N + BN - 1) / BN; g.ny = (p.M + BM - 1) / BM; g.per_z = g.nx * g.ny; g.tiles = (int)tiles; g.share = (int)(grid.x / 8);
     g.inv_per_z = 1.0f / (float)g.per_z; g.inv_panel = 1.0f / (float)(4 * g.ny);
-    kern<<<grid, WM * WN * 64, smem, s>>>(p, epi, g);
+    kern<<<grid, WM * WN * 64, smem, s>>>(p, g, epi);
     return hipGetLastError();
 }
 
