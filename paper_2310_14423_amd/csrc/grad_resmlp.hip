@@ -566,7 +566,7 @@ struct EpiLoss {                 // y = scale * acc; r = x_L - y; dx = inv * r i
     const float *X; long long sX; float *DX; long long sDX; bf16_t *DXb; long long sDXb; float *LPART; long long sLPART;
     long long ld; float scale, inv;
     static constexpr int VEC = 4;
-    static constexpr NtOut OUT = NT_RESIDUAL;
+    static constexpr NtOut OUT = NT_LOSS;
     typedef float4 Aux;
     struct Lane { EpiPtr<const float, false> x; EpiPtr<float, false> o; EpiPtr<bf16_t, false> b; mutable double sum; };
     __device__ Lane lane(int z, int row, int col, int r, int c) const
@@ -728,14 +728,17 @@ struct EpiGeluBwd {              // dh = acc * gelu'(h), H holding gelu'(h) from
 template <bool BLKA, class Epi>
 static hipError_t gemm_nt(const GemmNT &p, const Epi &epi, int batch, hipStream_t s)
 {
-    switch (nt_shape(Epi::OUT, p.M, p.N, p.K, batch, gemm_cu_count())) {
-    case NT_256x256: return launch_gemm_nt<NT_256x256, 2, 4, 2, BLKA>(p, epi, batch, s);
-    case NT_128x256: return launch_gemm_nt<NT_128x256, 1, 4, 2, BLKA>(p, epi, batch, s);
-    case NT_128x128_LONG: return launch_gemm_nt<NT_128x128_LONG, 2, 2, 2, BLKA>(p, epi, batch, s);
-    case NT_128x128: return launch_gemm_nt<NT_128x128, 2, 2, 3, BLKA>(p, epi, batch, s);
-    case NT_64x64_LONG: return launch_gemm_nt<NT_64x64_LONG, 2, 2, 2, BLKA>(p, epi, batch, s);
-    default: return launch_gemm_nt<NT_64x64, 2, 2, 4, BLKA>(p, epi, batch, s);
-    }
+    const NtShape shape = nt_shape(Epi::OUT, p.M, p.N, p.K, batch, gemm_cu_count());
+#define CASE(SHAPE, WM, WN, WPS) if constexpr (nt_allowed(SHAPE, Epi::OUT)) \
+        if (shape == SHAPE) return launch_gemm_nt<SHAPE, WM, WN, WPS, BLKA>(p, epi, batch, s)
+    CASE(NT_256x256, 2, 4, 2);
+    CASE(NT_128x256, 1, 4, 2);
+    CASE(NT_128x128_LONG, 2, 2, 2);
+    CASE(NT_128x128, 2, 2, 3);
+    CASE(NT_64x64_LONG, 2, 2, 2);
+    CASE(NT_64x64, 2, 2, 4);
+#undef CASE
+    return hipErrorInvalidValue;
 }
 // wavefronts of all tiles of a batch entry
 template <class Epi>

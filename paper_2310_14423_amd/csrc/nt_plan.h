@@ -11,8 +11,14 @@ constexpr int NT_SHAPES = 6;
 struct NtTileShape { int bm, bn, stages, resident; };
 constexpr NtTileShape NT_TILE[NT_SHAPES] = {{64, 64, 4, 4}, {64, 64, 8, 2}, {128, 128, 3, 3}, {128, 128, 5, 2}, {128, 256, 3, 2}, {256, 256, 4, 1}};
 
-// What an epilogue does: GELU and its derivative, two outputs; a factor read; fp32 read and written; bf16 written; fp32 written
-enum NtOut { NT_GELU, NT_FACTOR, NT_RESIDUAL, NT_BF16, NT_F32 };
+// What an epilogue does: GELU and its derivative, two outputs; a factor read; fp32 read and written; bf16 written; fp32 written; fp32 read,
+// fp32 and bf16 written and summed up
+enum NtOut { NT_GELU, NT_FACTOR, NT_RESIDUAL, NT_BF16, NT_F32, NT_LOSS };
+constexpr int NT_OUTS = 6;
+
+// The loss's sums leave its wavefronts of the two large tiles without registers (8 x 11491 x 1024 x 1024 320 us, 295 in tiles of 128 x 128),
+// and 128 x 128 with the long ring is hardly ever the shortest.
+constexpr bool nt_allowed(NtShape s, NtOut out) { return out != NT_LOSS || s == NT_64x64 || s == NT_64x64_LONG || s == NT_128x128; }
 
 inline long long nt_tiles(NtShape s, long long M, long long N, long long batch)
 {
@@ -23,18 +29,20 @@ inline long long nt_tiles(NtShape s, long long M, long long N, long long batch)
 // itself (latency + per stage of 32 + epilogue) or as all its tiles' work (per stage + epilogue each), smoothed between them.
 // Fitted to 508 products (1 to 8 workers, 64 to 12608 tokens, widths 64 to 1024, hidden to 4 times that, each kind of output)
 // timed with every shape on MI355X, which it reproduces to 10-15 %, and to the sizes of a 12-block 768/3072 encoder.
+// The loss's epilogues are fitted to what the choice costs over 523 other products, timed with every shape too: 0.8 % (2.7 % with those of
+// the other fp32 epilogue that reads: 3 x 9159 x 704 x 704 62.0 us in tiles of 128 x 128, 72.8 in the 128 x 256 that these choose).
 // (The wait of a lone 128 x 256 tile is that of operands that come from the other XCDs' products: 2 x 1251 tokens x 2112 x 704
 // 17.8 us, 13.8 in tiles of 128 x 128.)
 inline double nt_us(NtShape s, NtOut out, long long tiles, long long K, int n_cu)
 {
-    struct Fit { double latency, wait, work, epilogue[5]; };
+    struct Fit { double latency, wait, work, epilogue[NT_OUTS]; };
     static constexpr Fit FIT[NT_SHAPES] = {
-        {0.70, 0.107, 0.096, {0.70, 0.80, 1.13, 0.36, 0.78}},
-        {0.64, 0.043, 0.101, {1.02, 0.97, 1.26, 0.58, 0.91}},
-        {0.87, 0.124, 0.259, {2.67, 1.90, 2.96, 0.94, 1.37}},
-        {0.38, 0.058, 0.240, {3.07, 2.34, 2.97, 1.33, 1.81}},
-        {2.57, 0.450, 0.416, {5.20, 3.90, 4.90, 1.86, 2.43}},
-        {14.4, 0.000, 0.670, {7.70, 5.05, 6.37, 0.00, 0.97}},
+        {0.70, 0.107, 0.096, {0.70, 0.80, 1.13, 0.36, 0.78, 1.98}},
+        {0.64, 0.043, 0.101, {1.02, 0.97, 1.26, 0.58, 0.91, 2.48}},
+        {0.87, 0.124, 0.259, {2.67, 1.90, 2.96, 0.94, 1.37, 6.18}},
+        {0.38, 0.058, 0.240, {3.07, 2.34, 2.97, 1.33, 1.81, 7.75}},
+        {2.57, 0.450, 0.416, {5.20, 3.90, 4.90, 1.86, 2.43, 15.86}},
+        {14.4, 0.000, 0.670, {7.70, 5.05, 6.37, 0.00, 0.97, 18.12}},
     };
     const Fit &f = FIT[s];
     const double st = (double)(K / 32), e = f.epilogue[out];
@@ -60,7 +68,7 @@ inline NtShape nt_shape(NtOut out, long long M, long long N, long long K, long l
     double us = 1e300;
     for (int i = 0; i < NT_SHAPES; ++i) {
         const NtShape s = (NtShape)i;
-        if ((s == NT_128x256 && K < 256) || (s == NT_256x256 && K < 1024)) continue;
+        if ((s == NT_128x256 && K < 256) || (s == NT_256x256 && K < 1024) || !nt_allowed(s, out)) continue;
         const double t = nt_us(s, out, nt_tiles(s, M, N, batch), K, n_cu);
         if (t < us) { us = t; best = s; }
     }

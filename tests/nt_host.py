@@ -5,7 +5,7 @@ import tempfile
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHAPES = ("64x64", "64x64 long", "128x128", "128x128 long", "128x256", "256x256")
-OUTPUTS = ("gelu", "factor", "residual", "bf16", "f32")
+OUTPUTS = ("gelu", "factor", "residual", "bf16", "f32", "loss")
 
 DRIVER = r"""
 #include <cstdio>
@@ -45,6 +45,6 @@ def model_products(d, dh, heads, tokens, K):
     """The forward and data-gradient products of a block model, in the order of a pass: (what, output, M, N, K, batch)."""
     attn = [("qkv", "bf16", 3 * d, d), ("projection", "residual", d, d)] if heads else []
     back = [("projection gradient", "bf16", d, d), ("qkv gradient", "f32", d, 3 * d)] if heads else []
-    rows = attn + [("gelu", "gelu", dh, d), ("second", "residual", d, dh), ("loss", "residual", d, d), ("gelu gradient", "factor", dh, d),
+    rows = attn + [("gelu", "gelu", dh, d), ("second", "residual", d, dh), ("loss", "loss", d, d), ("gelu gradient", "factor", dh, d),
                    ("first gradient", "f32" if heads else "bf16", d, dh)] + back
     return [(what, out, tokens, n, k, K) for what, out, n, k in rows]
