@@ -1,5 +1,5 @@
-"""GPU: the block models' gradients at the sizes where the GEMMs change their tile shape or split, against the
-oracle with the bf16 tolerances of test_gpu_parity.py (which also says where they come from)."""
+"""GPU: the block models' gradients at narrow widths, many and few tokens, and at the sizes where the weight gradients change their tile shape
+or split (the other products' shapes: test_gpu_nt_shapes.py), against the oracle with the bf16 tolerances of test_gpu_parity.py (which also says where they come from)."""
 import numpy as np
 import pytest
 
@@ -12,11 +12,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dims", [
-    # NT GEMMs with N = d_hidden on 128 x 128 tiles (192 of them, ragged rows, two stages), N = d_in on 64 x 64 with two groups
+    # contractions of two stages, into outputs 16 times as wide and ragged rows; of 32 stages into one tile's width
     dict(d_in=64, d_hidden=1024, n_blocks=1, B_loc=700, K=4),
-    # on 128 x 256 tiles (1024 of them: the first number that takes them), the last row tile ragged
+    # a hidden layer 64 times as wide as the model
     dict(d_in=64, d_hidden=4096, n_blocks=1, B_loc=1021, K=8),
-    # N = 192, on 64 x 64 tiles, and one and a half 128 x 128 tiles wide (768 of them: the first number that takes them)
+    # 192 columns: three tiles of 64, one and a half of 128; many tokens
     dict(d_in=192, d_hidden=64, n_blocks=1, B_loc=4000, K=8),
     dict(d_in=192, d_hidden=64, n_blocks=1, B_loc=6100, K=8),
     # weight gradients on 128 x 128 tiles with two groups (128 of them), a short token count for both groups

@@ -40,14 +40,18 @@ def test_rounds_inside_launches(K, d, B, opt, H):
     ctx.close(); ref.close()
 
 
-def test_iterations_repeated():
-    """The schedule set back between calls: the words of a call before are of iterations that end rounds again."""
+@pytest.mark.parametrize("back", [2, 4, 6])
+def test_iterations_repeated(back):
+    """The schedule set back between calls, to where the next rounds end with iterations that the exchange still holds words of: the last
+    launch of the first call leaves those of iterations 70 and 68, one in each set of words.  The second call's first round reads the first set
+    and waits for iteration 70, 68 or 66, its second round the other one and waits for 72, 70 or 68: whichever set holds which, a word taken for
+    new meets its reader in two of the three, with parameters that have moved since."""
     w = workloads.get("lsq", K=7, d_in=300, B_loc=20, T=90, H_base=2, alpha=0.0, power=0)
     ref, ctx = gpu_ctx(w), gpu_ctx(w)
     for c, go in ((ref, ref.step), (ctx, ctx.run)):
         go(70)
-        c.set_state((10, 5, 0, 2))
-        go(70)
+        c.set_state((70 - back, 35 - back // 2, 0, 2))
+        go(20)
     same(ref, ctx)
     ctx.close(); ref.close()
 

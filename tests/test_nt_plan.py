@@ -53,3 +53,11 @@ def test_shapes_of_plain_outputs():
     sizes = [(7, 10296, 896, 896), (8, 1576, 768, 768), (3, 1672, 2304, 768), (6, 4235, 320, 960)]
     assert [g[0] for g in nt_host.shapes([(out, M, N, K, Z) for Z, M, N, K in sizes for out in ("bf16", "f32")])] == ["256x256"] * 8
     assert "256x256" not in [g[0] for g in nt_host.shapes([(out, M, N, K, Z) for Z, M, N, K in sizes for out in ("gelu", "factor", "residual")])]
+
+
+def test_gpu_cases_take_every_shape():
+    """The cases of test_gpu_nt_shapes.py run each kind of output in each shape that it may take."""
+    from test_gpu_nt_shapes import CASES
+    products = [p[1:] for c in CASES for p in nt_host.model_products(c["d_in"], c["d_hidden"], "n_heads" in c, c["B_loc"], c["K"])]
+    taken = {(p[0], g[0]) for p, g in zip(products, nt_host.shapes(products))}
+    assert taken == {(out, s) for out in nt_host.OUTPUTS for s in nt_host.SHAPES if out != "loss" or s in ("64x64", "64x64 long", "128x128")}
