@@ -57,14 +57,11 @@ inline double nt_us(NtShape s, NtOut out, long long tiles, long long K, int n_cu
     return (double)full * round(NT_TILE[s].resident) + (rest > 0 ? round(rest) : 0.0);
 }
 
-// The contraction from which on 256 x 256 is allowed.  Its row is a fit of whole rounds on the bounds of its parameters, not of a tile's time, and
-// below that it promises too much: where it would be taken at 768 to 1023 the launch is 6 % longer with GELU (31 products) and a residual (27),
-// 4 % with a factor (39), and 1.7 % shorter with a plain output (66: 7 x 10296 x 896 x 896 144 -> 125 us, 8 x 1576 x 768 x 768 29.2 -> 24.3);
-// at 512 to 767 it is longer with all of them.
-constexpr int nt_long(NtOut out) { return out == NT_BF16 || out == NT_F32 ? 768 : 1024; }
-
-// The shape with the least estimate, of those that the estimate is right for: the two large ones not for short contractions, where
-// their epilogues are most of a tile's time.
+// The shape with the least estimate, of those that the estimate is right for.  128 x 256 from a contraction of 256 on.  256 x 256 from 1024 on:
+// its row is a fit of whole rounds on the bounds of its parameters, not of a tile's time, and promises too much below.  Where it would be
+// taken at 768 to 1023 the launch is 6 % longer with GELU (31 products) and a residual (27) and 4 % with a factor (39).  With a plain output it is 1.7 %
+// shorter by itself (66 products), but whole models of such products run no faster for it (12 of 3 to 6 blocks at 0.987 to 1.012 of the time,
+// 0.999 on average): the chip runs them at its power limit.
 // Over the products above its choices take 1.3 % longer than the best; the rule by tile counts that it replaces, with shapes for a
 // full chip and two groups of wavefronts on a long contraction, 5.1 %.  E.g. (us; before) 2 x 1040 x 192 x 768 5.5 (6.1), 5 x 2945 x
 // 256 x 1024 12.1 (15.8), 2 x 9381 x 448 x 1344 32.1 (39.9).
@@ -74,7 +71,7 @@ inline NtShape nt_shape(NtOut out, long long M, long long N, long long K, long l
     double us = 1e300;
     for (int i = 0; i < NT_SHAPES; ++i) {
         const NtShape s = (NtShape)i;
-        if ((s == NT_128x256 && K < 256) || (s == NT_256x256 && K < nt_long(out)) || !nt_allowed(s, out)) continue;
+        if ((s == NT_128x256 && K < 256) || (s == NT_256x256 && K < 1024) || !nt_allowed(s, out)) continue;
         const double t = nt_us(s, out, nt_tiles(s, M, N, batch), K, n_cu);
         if (t < us) { us = t; best = s; }
     }

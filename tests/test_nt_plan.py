@@ -18,8 +18,7 @@ def test_shapes_of_random_products():
         M, N, K = int(math.exp(rng.uniform(0, math.log(300000)))), 64 * rng.randint(1, 72), 64 * rng.randint(1, 72)
         products.append((rng.choice(nt_host.OUTPUTS), M, N, K, rng.randint(1, 40)))
     for (out, M, N, K, batch), (shape, tiles, us) in zip(products, nt_host.shapes(products)):
-        long = 768 if out in ("bf16", "f32") else 1024
-        allowed = [i for i, s in enumerate(nt_host.SHAPES) if not (s == "128x256" and K < 256) and not (s == "256x256" and K < long)
+        allowed = [i for i, s in enumerate(nt_host.SHAPES) if not (s == "128x256" and K < 256) and not (s == "256x256" and K < 1024)
                    and not (out == "loss" and s not in ("64x64", "64x64 long", "128x128"))]
         assert all(math.isfinite(v) and v > 0 for v in us)
         assert nt_host.SHAPES.index(shape) == min(allowed, key=lambda i: us[i]), (out, M, N, K, batch)
@@ -38,21 +37,14 @@ def test_estimates_grow_with_the_work():
 
 def test_shapes_of_the_encoder():
     got = nt_host.shapes([p[1:] for p in nt_host.model_products(768, 3072, True, 12608, 8)])
-    assert [g[0] for g in got] == ["256x256", "128x256", "128x256", "256x256", "128x128", "128x256", "256x256", "256x256", "256x256"]
+    assert [g[0] for g in got] == ["128x256", "128x256", "128x256", "256x256", "128x128", "128x256", "256x256", "128x256", "256x256"]
 
 
 def test_shapes_of_the_loss():
-    """Where the tiles of another epilogue's estimate took 12 to 20 % longer than these (the shortest of all by timing, or within 2 % of it)."""
+    """Where the tiles of another epilogue's estimate took 12 to 20 % longer than these (the shortest of all by timing, or within 3 % of it)."""
     sizes = [(3, 9159, 704, "128x128"), (5, 5242, 512, "128x128"), (6, 3930, 896, "128x128"), (8, 11491, 1024, "128x128"), (5, 860, 512, "64x64"),
              (5, 1278, 384, "64x64"), (2, 11304, 192, "64x64"), (4, 5553, 192, "64x64")]
     assert [g[0] for g in nt_host.shapes([("loss", M, d, d, K) for K, M, d, _ in sizes])] == [s[3] for s in sizes]
-
-
-def test_shapes_of_plain_outputs():
-    """From a contraction of 768 on in the large tile, which is 2 to 20 % shorter here, other kinds of output not."""
-    sizes = [(7, 10296, 896, 896), (8, 1576, 768, 768), (3, 1672, 2304, 768), (6, 4235, 320, 960)]
-    assert [g[0] for g in nt_host.shapes([(out, M, N, K, Z) for Z, M, N, K in sizes for out in ("bf16", "f32")])] == ["256x256"] * 8
-    assert "256x256" not in [g[0] for g in nt_host.shapes([(out, M, N, K, Z) for Z, M, N, K in sizes for out in ("gelu", "factor", "residual")])]
 
 
 def test_gpu_cases_take_every_shape():
