@@ -11,7 +11,7 @@ LIB = os.path.join(PKG, "libqsr.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 instructions
          # a kernel's first arguments in its registers when a wavefront starts, without a load: 1 to 1.5 % of the chains of short
-         # launches (two encoder blocks of 1040 tokens 184.8 -> 181.7 us)
+         # launches (two encoder blocks of 1040 tokens 184.8 -> 181.7 us); single iterations of least squares take the same time
          "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wall", "-Wno-unused-function"]
 

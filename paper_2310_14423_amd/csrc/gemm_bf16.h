@@ -150,7 +150,7 @@ __device__ __forceinline__ void epilogue_via_lds(f32x4 (&acc)[TM][TN], float *st
     constexpr int RPI = 64 / LPR;                      // rows per read instruction
     constexpr int ITERS = (32 + RPI - 1) / RPI;
     static_assert(32 % RPI == 0, "rows per instruction must divide the block");
-    const bool active = 64 % LPR == 0 || lane < RPI * LPR;   // TN = 3: some of the last lanes are idle
+    const bool active = 64 % LPR == 0 || lane < RPI * LPR;   // W = 96: some of the last lanes are idle
     const int r0 = active ? lane / LPR : 0, c = (lane % LPR) * VEC;
     const auto lp = epi.lane(z, row0, col0, r0, c);
     typename Epi::Aux aux[2][ITERS];

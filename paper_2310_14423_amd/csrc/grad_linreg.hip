@@ -12,7 +12,7 @@
 // of its columns, which it holds for all workers, and in a recorded iteration the averaging and
 // the scheduler's step.  Iterations enqueued together (qsr_run) of a worker that fits one workgroup need no launch between
 // them at all: linreg_run_kernel.  256 iterations of 4 x 1024 features x 32 samples: 2879 us with four
-// kernels per iteration (residuals, gradient, update, averaging), 1900 with two, 563 together
+// kernels per iteration (residuals, gradient, update, averaging), 1900 with two, 560 together
 // (644 where each of the 28 rounds ended a launch).
 #include "opt_elem.h"
 #include "philox.h"

@@ -10,18 +10,19 @@ namespace qsr {
 
 // Rows of a lane group in flight at once
 constexpr int ln_bwd_rows(int vpl) { return vpl == 1 ? 2 : 1; }
-// Few rows: a step of one row a lane group for each wavefront, and the sums of a workgroup's wavefronts added up in LDS.
+// Few rows: the wavefronts of a workgroup, whose sums are added up in LDS
 constexpr int LN_FEW_WAVES = 8;
 
 // The wavefronts of a worker take steps of `step` rows (64 / LPR side by side, ln_bwd_rows of each in flight) in turn.
-// Few enough of them that all wavefronts of the launch are resident at once (a launch of 1.5 times the chip's wavefront slots
-// runs as one full wave of workgroups and a half-empty one: 283 against 234 us at 8 x 12608 rows of 768), resident wavefronts
-// per compute unit following from the kernel's registers; not fewer than four rows each, since each leaves a row of partial
-// sums for the parameter gradients (two each: 7 x 852 tokens of 704, three blocks with attention, 1374 against 1357 us an
-// iteration; at least 16, few tokens left most of the chip idle: 27 us a pass at 2 x 1040 rows of 192).
-// Where a launch has few rows, its time is a wavefront's instructions one after the other, so a wavefront takes one step of one
-// row a lane group: 2 x 1040 rows of 192 4.3 us, 5.7 with four rows in flight and four times the code; 3 x 247 of 128 6.6 and 4.7
-// with two of them.  The workgroup's sums are added up in LDS, so that the sums behind read fewer rows (4.0 -> 3.6 us).
+// Many rows (more than four for each wavefront that the chip holds): as many wavefronts as are resident at once, which follows from the kernel's
+// registers (a launch of 1.5 times the chip's wavefront slots runs as one full wave of workgroups and a half-empty one: 283 against
+// 234 us at 8 x 12608 rows of 768).  Each leaves a row of partial sums for the parameter gradients.
+// Few rows: one step of one row a lane group for each wavefront, up to four times as many wavefronts as the chip holds, eight of them to a row of
+// partial sums.  A launch's time is then a wavefront's instructions one after the other: 2 x 1040 rows of 192 4.3 us, 5.7 with four rows in
+// flight in four times the code; and the sums behind read fewer rows (4.0 -> 3.6 us).  Up to four rows a slot the two launches together are
+// faster for it at all widths, against resident wavefronts of four rows or more each with a row of partial sums (us, this pass twice with one launch of sums):
+//   2 x 10240 rows of 128 24.7 (25.8), of 192 32.1 (37.5), of 512 55.8 (69.5), 2 x 8192 of 768 71.0 (84.3), 2 x 6144 of 1024 76.5 (85.2);
+//   at one row a slot, 2 x 2560 of 192 14.8 (18.4), of 512 23.1 (26.5), 2 x 2048 of 768 23.3 (31.9), 2 x 1536 of 1024 26.2 (35.5).
 // `waves`: what leaves a row of partial sums, of a worker: wavefronts or, with few rows, the workgroups that add theirs up.
 struct LnBwdPlan { bool few; int step; long long waves; };
 inline LnBwdPlan ln_bwd_plan(long long K, long long M, long long d)
